@@ -122,7 +122,8 @@ def _decode_caches(sh, w, c, nb, gen, layer):
     kc = torch.empty(bt, nb, hk, 128, d, dtype=sh.torch_dtype, device=DEV).normal_(generator=gen)
     vc = torch.empty(bt, nb, hk, d, 128, dtype=sh.torch_dtype, device=DEV).normal_(generator=gen)
     u = synth.direction(w, 0, 0, DEV)
-    planted = torch.tensor(synth.planted_blocks(w, layer, 0), device=DEV)
+    # (sequences of a ragged batch may all be shorter than the context the blocks are drawn for)
+    planted = torch.tensor([b for b in synth.planted_blocks(w, layer, 0) if b < nb], dtype=torch.int64, device=DEV)
     kc[:, planted] += (w.shift * u)[None, None, :, None, :].to(kc.dtype)
     return kc, vc, synth.pick_rep_keys_blocked(kc, sh.n_rep)
 
