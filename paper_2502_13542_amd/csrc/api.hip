@@ -131,6 +131,7 @@ PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int
   return r;
 }
 bool decode_mfma_supported(const actqkv_shape& sh, int m);
+bool decode_fused_supported(const actqkv_shape& sh);
 size_t decode_mfma_scratch_floats(const actqkv_shape& sh, int batch, int k_cap);
 int launch_attention_decode_mfma(const actqkv_shape& sh, int batch, const void* q, const void* k_cache,
                                  const void* v_cache, int64_t seq_stride, int nb_capacity,
@@ -414,7 +415,7 @@ int actqkv_decode_select_attention(const actqkv_shape* shape, int batch, const v
                                    float* lse, void* workspace, size_t ws_bytes, void* stream) {
   ACTQKV_TRY(check_shape(shape));
   ACTQKV_TRY(check_batch(batch));
-  if (!decode_mfma_supported(*shape, 1))
+  if (!decode_fused_supported(*shape))
     return set_error(ACTQKV_ESHAPE, "decode_select_attention: bf16, head_dim 128 and at most 8 query heads per KV head");
   if (flags & ~ACTQKV_SELECT_ENTROPY_TOPK)
     return set_error(ACTQKV_EINVAL, "decode_select_attention: unknown flag bits: %d", flags);
@@ -473,7 +474,7 @@ int actqkv_decode_layer(const actqkv_shape* shape, int batch, const void* q, con
                         void* workspace, size_t ws_bytes, void* stream) {
   ACTQKV_TRY(check_shape(shape));
   ACTQKV_TRY(check_batch(batch));
-  if (!decode_mfma_supported(*shape, 1))
+  if (!decode_fused_supported(*shape))
     return set_error(ACTQKV_ESHAPE, "decode_layer: bf16, head_dim 128 and at most 8 query heads per KV head");
   if (flags & ~(ACTQKV_SELECT_ENTROPY_TOPK | ACTQKV_DECODE_NO_WAIT))
     return set_error(ACTQKV_EINVAL, "decode_layer: unknown flag bits: %d", flags);

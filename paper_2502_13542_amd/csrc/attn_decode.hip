@@ -1,21 +1,24 @@
 // Retrieval attention of a decode step (Sec. 3.1, Eq. (3): one query token per sequence
-// over [k^t, K*]; bf16 storage, fp32 accumulation).  HBM-bound: every selected key and
+// over [k^t, K*]; bf16 or fp32 storage, fp32 accumulation).  HBM-bound: every selected key and
 // value byte is read exactly once, by exactly one wavefront.
 //
-// A wavefront owns work items of 64 keys (half a block) of one (sequence, KV head): initial
+// A wavefront owns work items of up to 64 keys (half a block) of one (sequence, KV head): initial
 // tokens, the blocks chosen by the selection step or the local span up to the new token; the
-// keys and the values of an item are requested together, before anything is computed.  The G query heads of the KV head ride along as columns of a 16-wide matrix-core
-// tile, so a key or value byte is loaded once for all of them, straight from global memory
-// into MFMA operands (no LDS staging: nothing is shared between wavefronts):
-//   S^T[key][head] = K[key][:] Q^T        v_mfma_f32_16x16x32_bf16, A = 16 keys x 32 channels
+// keys and the values of an item are requested together, before anything is computed.  The G query
+// heads of the KV head ride along as columns of a 16-wide matrix-core tile, so a key or value
+// byte is loaded once for all of them, straight from global memory into MFMA operands (no LDS
+// staging: nothing is shared between wavefronts):
+//   S^T[key][head] = K[key][:] Q^T        bf16: v_mfma_f32_16x16x32_bf16, A = 16 keys x 32 channels
 //   O^T[d][head]  += V^T[d][keys] P^T     A = 16 channels x 32 keys of the transposed V block
-// A lane of an A operand reads 16 contiguous bytes and four lanes cover 64 contiguous
-// bytes of a row.  Keys enter S^T in a permuted row order such that each lane's accumulator
-// registers hold 8 consecutive keys of every 32-key step, which is exactly the B-operand
-// layout of the second product; no cross-lane traffic is needed apart from two shuffles
-// for the row maximum.  The 8 wavefronts of a workgroup merge their (max, sum, O) through
-// LDS.  If one workgroup covers a whole (sequence, KV head) it writes the output itself;
-// otherwise the workgroups store partials and the one that finishes last merges them.
+// (fp32: v_mfma_f32_16x16x4_f32, four per 16-byte load).  Every lane of an A operand reads 16
+// contiguous bytes and four lanes cover 64 contiguous bytes of a row.  The keys enter S^T in an
+// order that leaves the scores in exactly the B-operand layout of the second product; no
+// cross-lane traffic is needed apart from two shuffles for the row maximum.  The fp32 items are
+// 16 KB of keys and 16 KB of values like those of bf16 with 128 channels; at 8 query heads of 64
+// channels and 4 sequences a launch takes 13.6 us, against 942 us as one thread per query row.
+// The 8 wavefronts of a workgroup merge their (max, sum, O) through LDS.  If one workgroup covers
+// a whole (sequence, KV head) it writes the output itself; otherwise the workgroups store
+// partials and the one that finishes last merges them.
 #include <algorithm>
 #include <mutex>
 
@@ -27,23 +30,20 @@
 
 namespace actqkv {
 
-constexpr int kDcD = 128;
 constexpr int kDcMaxWaves = 8;   // 512 threads: the register budget stays at 256 per lane
 constexpr int kDcThreads = kDcMaxWaves * 64;
-constexpr int kDcItemKeys = 64;  // keys per work item (half a block)
-constexpr int kDcSteps = kDcItemKeys / 32, kDcPerTile = kBlock / kDcItemKeys;
 
 struct DcParams {
-  const uint16_t* q;
-  const uint16_t* k_cache;
-  const uint16_t* v_cache;
+  const void* q;            // storage type T of the kernel, as all tensors
+  const void* k_cache;
+  const void* v_cache;
   int64_t seq_stride;
   int nb_capacity;
   const int32_t* n_ctx;
   const int32_t* idx;
   const int32_t* n_sel;
   int k_cap;
-  uint16_t* out;
+  void* out;
   float* lse;
   uint32_t* part;           // [batch][Hk][n_wg][G][D + 2] fp32 bits
   unsigned int* counters;   // one ticket counter per (sequence, KV head), zero between launches
@@ -65,72 +65,146 @@ struct DcSelectParams {
 
 __device__ __forceinline__ bf16x8 dc_as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-// Keys and values of one work item (kDcItemKeys keys of a tile of one KV head) on their way into
-// MFMA operands, and the key positions [lo, hi) of the item that the query may see.
+// The two matrix-core forms of an item.  kSubs accumulators of 16 keys x 16 heads hold the scores;
+// key_of says which key of the item register i of accumulator j is in lane quarter kq.  kK and kV
+// count the 16-byte loads of a lane for the item's keys and values, kQ those of its query.
+template <typename T, int D> struct DcShape;
+// bf16, v_mfma_f32_16x16x32_bf16.  MFMA row r of sub-tile h of 32-key step st is key
+// 32*st + 8*(r/4) + 4*h + r%4, so that lane quarter kq ends up with keys 32*st + 8*kq + 4*h + i in
+// register i: 8 consecutive keys per 32-key step, which is the B operand of the second product.
+template <int D>
+struct DcShape<uint16_t, D> {
+  static constexpr int kKeys = 64;                 // keys per work item (half a block)
+  static constexpr int kSubs = kKeys / 16, kSteps = kKeys / 32;
+  static constexpr int kQ = D / 32, kK = kSubs * kQ, kV = (D / 16) * kSteps;
+  __device__ static __forceinline__ int key_of(int j, int i, int kq) { return 32 * (j >> 1) + 8 * kq + 4 * (j & 1) + i; }
+  // element offsets of a lane's operands from the item's first key (K rows) / first key column (V^T rows)
+  __device__ static __forceinline__ int k_lane(int n, int kq) { return (8 * (n >> 2) + (n & 3)) * D + 8 * kq; }
+  __device__ static __forceinline__ int k_off(int l) { return (32 * (l / (2 * kQ)) + 4 * ((l / kQ) & 1)) * D + (l % kQ) * 32; }
+  __device__ static __forceinline__ int v_lane(int n, int kq) { return n * kBlock + 8 * kq; }
+  __device__ static __forceinline__ int v_off(int l) { return 16 * (l / kSteps) * kBlock + 32 * (l % kSteps); }
+  __device__ static __forceinline__ int q_lane(int kq) { return 8 * kq; }
+  static constexpr int kQStep = 32;
+  __device__ static __forceinline__ void scores(const u32x4 (&ka)[kK], const u32x4 (&qb)[kQ], f32x4 (&sc)[kSubs]) {
+#pragma unroll
+    for (int ks = 0; ks < kQ; ++ks)      // the sub-tiles take turns: no MFMA waits for the one before it
+#pragma unroll
+      for (int j = 0; j < kSubs; ++j)
+        sc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dc_as_bf16x8(ka[j * kQ + ks]), dc_as_bf16x8(qb[ks]), sc[j], 0, 0, 0);
+  }
+  __device__ static __forceinline__ void values(const u32x4 (&va)[kV], const f32x4 (&sc)[kSubs], f32x4 (&acc)[D / 16]) {
+    typedef __attribute__((ext_vector_type(8))) float f32x8;
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+      f32x8 pf = {sc[2 * st][0], sc[2 * st][1], sc[2 * st][2], sc[2 * st][3],
+                  sc[2 * st + 1][0], sc[2 * st + 1][1], sc[2 * st + 1][2], sc[2 * st + 1][3]};
+      const bf16x8 pb = __builtin_convertvector(pf, bf16x8);
+#pragma unroll
+      for (int dg = 0; dg < D / 16; ++dg)
+        acc[dg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dc_as_bf16x8(va[dg * kSteps + st]), pb, acc[dg], 0, 0, 0);
+    }
+  }
+};
+// fp32, v_mfma_f32_16x16x4_f32 (fp32 products and sums throughout): the 16 channels of a step are
+// dealt to the lane quarters four at a time, so that a lane's operand is a 16-byte load; register i
+// of accumulator j is key 16*j + 4*kq + i, and the four MFMAs of the second product take the keys
+// 4*kq + i, i = 0 .. 3, of every quarter: the scores are its B operand as they are.
+template <int D>
+struct DcShape<float, D> {
+  static constexpr int kKeys = 4096 / D;           // 16 KB of keys and 16 KB of values, as for bf16 with D = 128
+  static constexpr int kSubs = kKeys / 16;
+  static constexpr int kQ = D / 16, kK = kSubs * kQ, kV = (D / 16) * kSubs;
+  __device__ static __forceinline__ int key_of(int j, int i, int kq) { return 16 * j + 4 * kq + i; }
+  __device__ static __forceinline__ int k_lane(int n, int kq) { return n * D + 4 * kq; }
+  __device__ static __forceinline__ int k_off(int l) { return 16 * (l / kQ) * D + (l % kQ) * 16; }
+  __device__ static __forceinline__ int v_lane(int n, int kq) { return n * kBlock + 4 * kq; }
+  __device__ static __forceinline__ int v_off(int l) { return 16 * (l / kSubs) * kBlock + 16 * (l % kSubs); }
+  __device__ static __forceinline__ int q_lane(int kq) { return 4 * kq; }
+  static constexpr int kQStep = 16;
+  __device__ static __forceinline__ void scores(const u32x4 (&ka)[kK], const u32x4 (&qb)[kQ], f32x4 (&sc)[kSubs]) {
+#pragma unroll
+    for (int ks = 0; ks < kQ; ++ks)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < kSubs; ++j)
+          sc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(ka[j * kQ + ks][i]), __uint_as_float(qb[ks][i]), sc[j], 0, 0, 0);
+  }
+  __device__ static __forceinline__ void values(const u32x4 (&va)[kV], const f32x4 (&sc)[kSubs], f32x4 (&acc)[D / 16]) {
+#pragma unroll
+    for (int j = 0; j < kSubs; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int dg = 0; dg < D / 16; ++dg)
+          acc[dg] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(va[dg * kSubs + j][i]), sc[j][i], acc[dg], 0, 0, 0);
+  }
+};
+
+// Keys and values of one work item (kKeys keys of a tile of one KV head) on their way into MFMA
+// operands, and the key positions [lo, hi) of the item that the query may see.
+template <typename T, int D>
 struct DcItem {
-  u32x4 ka[8 * kDcSteps];
-  u32x4 va[8 * kDcSteps];
+  u32x4 ka[DcShape<T, D>::kK];
+  u32x4 va[DcShape<T, D>::kV];
   int kpos0, lo, hi;
 };
 // Running softmax state of a wavefront: lane (n, kq) holds channels 16*dg + 4*kq + i of head n.
+template <int D>
 struct DcAcc {
   float m_run, l_run;
-  f32x4 acc_o[8];
+  f32x4 acc_o[D / 16];
+  __device__ __forceinline__ void clear() {
+    m_run = -INFINITY;
+    l_run = 0.f;
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) acc_o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 };
 
 // Item `it` of a tile list -> its block and visible span; false if the query sees none of it.
-__device__ __forceinline__ bool dc_item_span(const TileList& tl, int it, int& block, int& part, DcItem& r) {
+template <typename T, int D>
+__device__ __forceinline__ bool dc_item_span(const TileList& tl, int it, int& block, int& part, DcItem<T, D>& r) {
+  constexpr int kKeys = DcShape<T, D>::kKeys, kPerTile = kBlock / kKeys;
   int lo, hi;
-  tl.get(it / kDcPerTile, block, lo, hi);
-  part = it % kDcPerTile;
-  r.kpos0 = block * kBlock + part * kDcItemKeys;
+  tl.get(it / kPerTile, block, lo, hi);
+  part = it % kPerTile;
+  r.kpos0 = block * kBlock + part * kKeys;
   r.lo = max(lo, r.kpos0);
-  r.hi = min(hi, r.kpos0 + kDcItemKeys);
+  r.hi = min(hi, r.kpos0 + kKeys);
   return r.hi > r.lo;
 }
 
 // Requests the item's keys AND values (nothing is computed before both are on their way).
-// A operands of S^T: MFMA row r of sub-tile h of 32-key step st is key 32*st + 8*(r/4) + 4*h + r%4,
-// so that lane quarter kq ends up with keys 32*st + 8*kq + 4*h + i in register i.
-// V^T A operands: lane (row = channel within a group of 16, kq) reads keys 32*st + 8*kq .. +7.
-__device__ __forceinline__ void dc_issue(DcItem& r, const uint16_t* kc, const uint16_t* vc, int block, int part,
+template <typename T, int D>
+__device__ __forceinline__ void dc_issue(DcItem<T, D>& r, const T* kc, const T* vc, int block, int part,
                                          int hk, int n_kv_heads, int n, int kq) {
-  const size_t tile = (size_t(block) * n_kv_heads + hk) * size_t(kBlock) * kDcD;
-  const uint16_t* kbase = kc + tile + size_t(part) * kDcItemKeys * kDcD + size_t(8 * (n >> 2) + (n & 3)) * kDcD + 8 * kq;
-  const uint16_t* vbase = vc + tile + part * kDcItemKeys + size_t(n) * kBlock + 8 * kq;
+  typedef DcShape<T, D> S;
+  const size_t tile = (size_t(block) * n_kv_heads + hk) * size_t(kBlock) * D;
+  const T* kbase = kc + tile + size_t(part) * S::kKeys * D + S::k_lane(n, kq);
+  const T* vbase = vc + tile + part * S::kKeys + S::v_lane(n, kq);
 #pragma unroll
-  for (int st = 0; st < kDcSteps; ++st)
+  for (int l = 0; l < S::kK; ++l) r.ka[l] = *reinterpret_cast<const u32x4*>(kbase + S::k_off(l));
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        r.ka[(st * 2 + h) * 4 + ks] =
-            *reinterpret_cast<const u32x4*>(kbase + size_t(32 * st + 4 * h) * kDcD + ks * 32);
-#pragma unroll
-  for (int dg = 0; dg < 8; ++dg)
-#pragma unroll
-    for (int st = 0; st < kDcSteps; ++st)
-      r.va[dg * kDcSteps + st] = *reinterpret_cast<const u32x4*>(vbase + size_t(16 * dg) * kBlock + 32 * st);
+  for (int l = 0; l < S::kV; ++l) r.va[l] = *reinterpret_cast<const u32x4*>(vbase + S::v_off(l));
 }
 
 // Scores, mask, online softmax and O^T += V^T P^T for one item.
-__device__ __forceinline__ void dc_consume(const DcItem& r, const bf16x8 (&qb)[4], DcAcc& a, float scale_log2e,
-                                           int kq) {
-  f32x4 sc[2 * kDcSteps];
+template <typename T, int D>
+__device__ __forceinline__ void dc_consume(const DcItem<T, D>& r, const u32x4 (&qb)[DcShape<T, D>::kQ], DcAcc<D>& a,
+                                           float scale_log2e, int kq) {
+  typedef DcShape<T, D> S;
+  f32x4 sc[S::kSubs];
 #pragma unroll
-  for (int j = 0; j < 2 * kDcSteps; ++j) sc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks)       // the sub-tiles take turns: no MFMA waits for the one before it
-#pragma unroll
-    for (int j = 0; j < 2 * kDcSteps; ++j)
-      sc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dc_as_bf16x8(r.ka[j * 4 + ks]), qb[ks], sc[j], 0, 0, 0);
-  // mask and online softmax: sc[2*st + h][i] is key kpos0 + 32*st + 8*kq + 4*h + i
+  for (int j = 0; j < S::kSubs; ++j) sc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  S::scores(r.ka, qb, sc);
+  // mask and online softmax
   float mx = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < 2 * kDcSteps; ++j)
+  for (int j = 0; j < S::kSubs; ++j)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int kp = r.kpos0 + 32 * (j >> 1) + 8 * kq + 4 * (j & 1) + i;
+      const int kp = r.kpos0 + S::key_of(j, i, kq);
       const float v = (kp >= r.lo && kp < r.hi) ? sc[j][i] : -INFINITY;
       sc[j][i] = v;
       mx = fmaxf(mx, v);
@@ -142,7 +216,7 @@ __device__ __forceinline__ void dc_consume(const DcItem& r, const bf16x8 (&qb)[4
   a.m_run = m_new;
   float psum = 0.f;
 #pragma unroll
-  for (int j = 0; j < 2 * kDcSteps; ++j)
+  for (int j = 0; j < S::kSubs; ++j)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float pv = __builtin_amdgcn_exp2f(sc[j][i] * scale_log2e - m_new);
@@ -153,53 +227,47 @@ __device__ __forceinline__ void dc_consume(const DcItem& r, const bf16x8 (&qb)[4
   psum += __shfl_xor(psum, 32, 64);
   a.l_run = a.l_run * alpha + psum;
 #pragma unroll
-  for (int dg = 0; dg < 8; ++dg) a.acc_o[dg] *= alpha;
-  typedef __attribute__((ext_vector_type(8))) float f32x8;
-#pragma unroll
-  for (int st = 0; st < kDcSteps; ++st) {
-    f32x8 pf = {sc[2 * st][0], sc[2 * st][1], sc[2 * st][2], sc[2 * st][3],
-                sc[2 * st + 1][0], sc[2 * st + 1][1], sc[2 * st + 1][2], sc[2 * st + 1][3]};
-    const bf16x8 pb = __builtin_convertvector(pf, bf16x8);
-#pragma unroll
-    for (int dg = 0; dg < 8; ++dg)
-      a.acc_o[dg] =
-          __builtin_amdgcn_mfma_f32_16x16x32_bf16(dc_as_bf16x8(r.va[dg * kDcSteps + st]), pb, a.acc_o[dg], 0, 0, 0);
-  }
+  for (int dg = 0; dg < D / 16; ++dg) a.acc_o[dg] *= alpha;
+  S::values(r.va, sc, a.acc_o);
 }
 
-// Q^T as B operand: lane (n, kq) holds channels ks*32 + 8*kq .. +7 of head n (zero for n >= G)
+// Q^T as B operand: lane (n, kq) holds its quarter's channels of head n (zero for n >= G)
+template <typename T, int D>
 __device__ __forceinline__ void dc_load_q(const DcParams& p, int s, int hk, int group, int n, int kq,
-                                          bf16x8 (&qb)[4]) {
-  const uint16_t* qp = p.q + (size_t(s) * p.n_q_heads + hk * group + min(n, group - 1)) * kDcD + 8 * kq;
+                                          u32x4 (&qb)[DcShape<T, D>::kQ]) {
+  typedef DcShape<T, D> S;
+  const T* qp = static_cast<const T*>(p.q) + (size_t(s) * p.n_q_heads + hk * group + min(n, group - 1)) * D + S::q_lane(kq);
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    u32x4 v = *reinterpret_cast<const u32x4*>(qp + ks * 32);
+  for (int ks = 0; ks < S::kQ; ++ks) {
+    u32x4 v = *reinterpret_cast<const u32x4*>(qp + ks * S::kQStep);
     if (n >= group) v = u32x4{0u, 0u, 0u, 0u};
-    qb[ks] = dc_as_bf16x8(v);
+    qb[ks] = v;
   }
 }
 
 // The wavefronts of a workgroup merge their (max, sum, O) through LDS.  If one workgroup covers
 // the whole (sequence, KV head) it writes the output itself; otherwise the workgroups store
 // partials and the one that finishes last merges them.  dc_lds: n_waves * G * (D + 2) floats.
-__device__ __forceinline__ void dc_finish(const DcParams& p, const DcAcc& a, float* dc_lds, int s, int hk, int wg,
+template <typename T, int D>
+__device__ __forceinline__ void dc_finish(const DcParams& p, const DcAcc<D>& a, float* dc_lds, int s, int hk, int wg,
                                           int group, int n, int kq, int wave, int n_waves) {
   float* red_ml = dc_lds;                        // [n_waves][group][2]
   float* red_o = dc_lds + n_waves * group * 2;   // [n_waves][group][D]
+  T* out = static_cast<T*>(p.out);
   if (n < group) {
     if (kq == 0) {
       red_ml[(wave * group + n) * 2 + 0] = a.m_run;
       red_ml[(wave * group + n) * 2 + 1] = a.l_run;
     }
 #pragma unroll
-    for (int dg = 0; dg < 8; ++dg)
-      *reinterpret_cast<f32x4*>(&red_o[(wave * group + n) * kDcD + 16 * dg + 4 * kq]) = a.acc_o[dg];
+    for (int dg = 0; dg < D / 16; ++dg)
+      *reinterpret_cast<f32x4*>(&red_o[(wave * group + n) * D + 16 * dg + 4 * kq]) = a.acc_o[dg];
   }
   __syncthreads();
-  uint32_t* pair_part = p.part + (size_t(s) * p.n_kv_heads + hk) * p.n_wg * group * (kDcD + 2);
-  uint32_t* part = pair_part + size_t(wg) * group * (kDcD + 2);
-  for (int e = threadIdx.x; e < group * kDcD; e += blockDim.x) {
-    const int h = e / kDcD, d = e - h * kDcD;
+  uint32_t* pair_part = p.part + (size_t(s) * p.n_kv_heads + hk) * p.n_wg * group * (D + 2);
+  uint32_t* part = pair_part + size_t(wg) * group * (D + 2);
+  for (int e = threadIdx.x; e < group * D; e += blockDim.x) {
+    const int h = e / D, d = e - h * D;
     float mm = -INFINITY;
     for (int w = 0; w < n_waves; ++w) mm = fmaxf(mm, red_ml[(w * group + h) * 2]);
     const float m_safe = mm == -INFINITY ? 0.f : mm;
@@ -207,18 +275,18 @@ __device__ __forceinline__ void dc_finish(const DcParams& p, const DcAcc& a, flo
     for (int w = 0; w < n_waves; ++w) {
       const float sc_w = __builtin_amdgcn_exp2f(red_ml[(w * group + h) * 2] - m_safe);
       l += sc_w * red_ml[(w * group + h) * 2 + 1];
-      o += sc_w * red_o[(w * group + h) * kDcD + d];
+      o += sc_w * red_o[(w * group + h) * D + d];
     }
     if (p.n_wg == 1) {
       const int head = hk * group + h;
-      p.out[(size_t(s) * p.n_q_heads + head) * kDcD + d] = uint16_t(f32_to_bf16_bits(l > 0.f ? o / l : 0.f));
+      store_elem(out + (size_t(s) * p.n_q_heads + head) * D + d, l > 0.f ? o / l : 0.f);
       if (p.lse != nullptr && d == 0)
         p.lse[size_t(s) * p.n_q_heads + head] = (mm + log2f(l)) * 0.6931471805599453f;
     } else {
-      st_agent(part + size_t(h) * (kDcD + 2) + d, __float_as_uint(o));
+      st_agent(part + size_t(h) * (D + 2) + d, __float_as_uint(o));
       if (d == 0) {
-        st_agent(part + size_t(h) * (kDcD + 2) + kDcD, __float_as_uint(mm));
-        st_agent(part + size_t(h) * (kDcD + 2) + kDcD + 1, __float_as_uint(l));
+        st_agent(part + size_t(h) * (D + 2) + D, __float_as_uint(mm));
+        st_agent(part + size_t(h) * (D + 2) + D + 1, __float_as_uint(l));
       }
     }
   }
@@ -228,19 +296,19 @@ __device__ __forceinline__ void dc_finish(const DcParams& p, const DcAcc& a, flo
 
   // ---- the workgroup that finished last merges the partials, in workgroup order:
   //   out[head][:] = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w
-  const size_t stride = size_t(group) * (kDcD + 2);
+  const size_t stride = size_t(group) * (D + 2);
   constexpr int kB = 8;
-  for (int e = threadIdx.x; e < group * kDcD; e += blockDim.x) {
-    const int h = e / kDcD, d = e - h * kDcD;
-    const uint32_t* src = pair_part + size_t(h) * (kDcD + 2);
+  for (int e = threadIdx.x; e < group * D; e += blockDim.x) {
+    const int h = e / D, d = e - h * D;
+    const uint32_t* src = pair_part + size_t(h) * (D + 2);
     float mm = -INFINITY, l = 0.f, o = 0.f;
     for (int w0 = 0; w0 < p.n_wg; w0 += kB) {
       uint32_t pm[kB], pl[kB], po[kB];
 #pragma unroll
       for (int i = 0; i < kB; ++i) {               // all loads first: they overlap
         const int w = w0 + i < p.n_wg ? w0 + i : w0;
-        pm[i] = ld_agent(src + w * stride + kDcD);
-        pl[i] = ld_agent(src + w * stride + kDcD + 1);
+        pm[i] = ld_agent(src + w * stride + D);
+        pl[i] = ld_agent(src + w * stride + D + 1);
         po[i] = ld_agent(src + w * stride + d);
       }
 #pragma unroll
@@ -258,7 +326,7 @@ __device__ __forceinline__ void dc_finish(const DcParams& p, const DcAcc& a, flo
     }
     const float inv = l > 0.f ? 1.f / l : 0.f;
     const int head = hk * group + h;
-    p.out[(size_t(s) * p.n_q_heads + head) * kDcD + d] = uint16_t(f32_to_bf16_bits(o * inv));
+    store_elem(out + (size_t(s) * p.n_q_heads + head) * D + d, o * inv);
     if (p.lse != nullptr && d == 0)
       p.lse[size_t(s) * p.n_q_heads + head] = (mm + log2f(l)) * 0.6931471805599453f;
   }
@@ -266,6 +334,7 @@ __device__ __forceinline__ void dc_finish(const DcParams& p, const DcAcc& a, flo
 
 // grid (n_wg, Hk, batch); blockDim = 64 * (wavefronts per workgroup).  Item i of the tile list
 // of a (sequence, KV head) goes to wavefront i mod (all wavefronts of the pair).
+template <typename T, int D>
 __global__ __launch_bounds__(kDcThreads) void attn_decode_kernel(DcParams p) {
   extern __shared__ __attribute__((aligned(16))) float dc_lds[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
@@ -278,27 +347,26 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_kernel(DcParams p) {
   const size_t sel_row = p.sel_per_head ? size_t(s) * p.n_kv_heads + hk : size_t(s);
   const TileList tl = make_tile_list(g, n_ctx - 1, p.idx + sel_row * p.k_cap, p.n_sel[sel_row], p.k_cap,
                                      p.nb_capacity);
-  const int n_items = tl.count() * kDcPerTile;
-  bf16x8 qb[4];
-  dc_load_q(p, s, hk, group, n, kq, qb);
-  DcAcc a;
-  a.m_run = -INFINITY;
-  a.l_run = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) a.acc_o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const uint16_t* kc = p.k_cache + size_t(s) * p.seq_stride;
-  const uint16_t* vc = p.v_cache + size_t(s) * p.seq_stride;
+  const int n_items = tl.count() * (kBlock / DcShape<T, D>::kKeys);
+  u32x4 qb[DcShape<T, D>::kQ];
+  dc_load_q<T, D>(p, s, hk, group, n, kq, qb);
+  DcAcc<D> a;
+  a.clear();
+  const T* kc = static_cast<const T*>(p.k_cache) + size_t(s) * p.seq_stride;
+  const T* vc = static_cast<const T*>(p.v_cache) + size_t(s) * p.seq_stride;
 
   for (int it = wg * n_waves + wave; it < n_items; it += p.n_wg * n_waves) {
-    DcItem r;
+    DcItem<T, D> r;
     int block, part;
     if (!dc_item_span(tl, it, block, part, r)) continue;   // wave-uniform
     dc_issue(r, kc, vc, block, part, hk, p.n_kv_heads, n, kq);
     __builtin_amdgcn_sched_barrier(0);   // all key and value loads are in flight before the first MFMA
     dc_consume(r, qb, a, p.scale_log2e, kq);
   }
-  dc_finish(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
+  dc_finish<T, D>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 }
+
+constexpr int kDcD = 128;        // the kernels below: bf16, 128 channels per head
 
 // The same attention with the selection step (Sec. 4.2, Eq. (11), Eq. (12); Alg. 1) inside it:
 // the step needs a launch of its own only because of its latency (two memory round trips and a
@@ -345,20 +413,17 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
   const WindowGeom g = window_geom(n_ctx, 1, p.n_init, p.n_local);
   // the list without the selection: initial tokens, then the local span
   const TileList fixed = make_tile_list(g, n_ctx - 1, nullptr, 0, p.k_cap, p.nb_capacity);
-  const int n_fixed = fixed.count() * kDcPerTile;
-  bf16x8 qb[4];
-  dc_load_q(p, s, hk, group, n, kq, qb);
-  DcAcc a;
-  a.m_run = -INFINITY;
-  a.l_run = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) a.acc_o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const uint16_t* kc = p.k_cache + size_t(s) * p.seq_stride;
-  const uint16_t* vc = p.v_cache + size_t(s) * p.seq_stride;
+  const int n_fixed = fixed.count() * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
+  u32x4 qb[DcShape<uint16_t, kDcD>::kQ];
+  dc_load_q<uint16_t, kDcD>(p, s, hk, group, n, kq, qb);
+  DcAcc<kDcD> a;
+  a.clear();
+  const uint16_t* kc = static_cast<const uint16_t*>(p.k_cache) + size_t(s) * p.seq_stride;
+  const uint16_t* vc = static_cast<const uint16_t*>(p.v_cache) + size_t(s) * p.seq_stride;
 
   // this wavefront's first item, if it is one that does not depend on the selection
   const int it0 = wg * n_waves + wave, stride = p.n_wg * n_waves;
-  DcItem r0;
+  DcItem<uint16_t, kDcD> r0;
   int block0, part0;
   const bool have0 = it0 < n_fixed && dc_item_span(fixed, it0, block0, part0, r0);
   if (have0) dc_issue(r0, kc, vc, block0, part0, hk, p.n_kv_heads, n, kq);
@@ -379,9 +444,9 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
   chosen.n_tail_tiles = 0;
   chosen.n_sel = min(max(sel_lds.count, 0), p.k_cap);
   chosen.idx = sel_lds.sel;
-  const int n_items = n_fixed + chosen.n_sel * kDcPerTile;
+  const int n_items = n_fixed + chosen.n_sel * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
   for (int it = it0 < n_fixed ? it0 + stride : it0; it < n_items; it += stride) {
-    DcItem r;
+    DcItem<uint16_t, kDcD> r;
     int block, part;
     const bool ok = it < n_fixed ? dc_item_span(fixed, it, block, part, r)
                                  : dc_item_span(chosen, it - n_fixed, block, part, r);
@@ -390,7 +455,7 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
     __builtin_amdgcn_sched_barrier(0);
     dc_consume(r, qb, a, p.scale_log2e, kq);
   }
-  dc_finish(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
+  dc_finish<uint16_t, kDcD>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 }
 
 // ---- a whole decode layer in ONE launch ---------------------------------------------------
@@ -448,11 +513,11 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   const int n_ctx = min(max(p.n_ctx[s], 1), p.nb_capacity * kBlock);
   const WindowGeom g = window_geom(n_ctx, 1, p.n_init, p.n_local);
   const TileList fixed = make_tile_list(g, n_ctx - 1, nullptr, 0, p.k_cap, p.nb_capacity);
-  const int n_fixed = fixed.count() * kDcPerTile;
+  const int n_fixed = fixed.count() * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
 
   // ---- the probe: the query summed over the G heads of every KV head, and its norm.  The
   // query loads go out before the key loads (outstanding loads are counted in order).
-  const uint16_t* __restrict__ qrow = p.q + size_t(s) * p.n_q_heads * kDcD;
+  const uint16_t* __restrict__ qrow = static_cast<const uint16_t*>(p.q) + size_t(s) * p.n_q_heads * kDcD;
   const int n_chunks = key_len / V;
   auto load_q = [&](int c, int g0, float (&x)[4][V]) {
     const int h = (c * V) / kDcD, dd = c * V - h * kDcD;
@@ -473,8 +538,8 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   };
   float x0[4][V];
   load_q(min(tid, n_chunks - 1), 0, x0);
-  bf16x8 qb[4];
-  dc_load_q(p, s, hk, group, n, kq, qb);              // Q^T operand of the attention, from the same 8 KB
+  u32x4 qb[DcShape<uint16_t, kDcD>::kQ];
+  dc_load_q<uint16_t, kDcD>(p, s, hk, group, n, kq, qb);              // Q^T operand of the attention, from the same 8 KB
   __builtin_amdgcn_sched_barrier(0);
   if (tid < n_chunks) {
     float acc[V];
@@ -552,18 +617,15 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   // ---- The wavefront that owns the item holding the step's own token writes that token into the
   // cache (its KV head's key row and value column) and waits for the stores, so that its loads
   // of the item see it; nobody else reads those cache lines in this launch.
-  DcAcc a;
-  a.m_run = -INFINITY;
-  a.l_run = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) a.acc_o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const uint16_t* kc = p.k_cache + size_t(s) * p.seq_stride;
-  const uint16_t* vc = p.v_cache + size_t(s) * p.seq_stride;
+  DcAcc<kDcD> a;
+  a.clear();
+  const uint16_t* kc = static_cast<const uint16_t*>(p.k_cache) + size_t(s) * p.seq_stride;
+  const uint16_t* vc = static_cast<const uint16_t*>(p.v_cache) + size_t(s) * p.seq_stride;
   // item i of the list goes to wavefront i mod (all wavefronts of the pair), wavefront-major across
   // the pair's workgroups, so that every workgroup gets its share of short lists
   const int it0 = wave * p.n_wg + wg, stride = p.n_wg * n_waves;
   // item of the fixed list that holds position pos_new: the last tile of the list, by construction
-  const int it_new = (fixed.count() - 1) * kDcPerTile + (pos_new % kBlock) / kDcItemKeys;
+  const int it_new = (fixed.count() - 1) * (kBlock / DcShape<uint16_t, kDcD>::kKeys) + (pos_new % kBlock) / DcShape<uint16_t, kDcD>::kKeys;
   if (lp.k_new != nullptr && it0 == it_new % stride) {
     const int block = pos_new / kBlock, j0 = pos_new - block * kBlock;
     const size_t tile = size_t(s) * p.seq_stride + (size_t(block) * p.n_kv_heads + hk) * size_t(kBlock) * kDcD;
@@ -585,7 +647,7 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   // wavefront set aside for those reads still shares the compute unit's load queue with the
   // other seven: both orders were slower than this one.)
   for (int it = it0; it < n_fixed; it += stride) {
-    DcItem r;
+    DcItem<uint16_t, kDcD> r;
     int block, part;
     if (!dc_item_span(fixed, it, block, part, r)) continue;   // wave-uniform
     dc_issue(r, kc, vc, block, part, hk, p.n_kv_heads, n, kq);
@@ -629,18 +691,18 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   chosen.n_tail_tiles = 0;
   chosen.n_sel = min(max(sel_lds.count, 0), p.k_cap);
   chosen.idx = sel_lds.sel;
-  const int n_items = n_fixed + chosen.n_sel * kDcPerTile;
+  const int n_items = n_fixed + chosen.n_sel * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
   int it = it0;
   while (it < n_fixed) it += stride;
   for (; it < n_items; it += stride) {
-    DcItem r;
+    DcItem<uint16_t, kDcD> r;
     int block, part;
     if (!dc_item_span(chosen, it - n_fixed, block, part, r)) continue;   // wave-uniform
     dc_issue(r, kc, vc, block, part, hk, p.n_kv_heads, n, kq);
     __builtin_amdgcn_sched_barrier(0);
     dc_consume(r, qb, a, p.scale_log2e, kq);
   }
-  dc_finish(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
+  dc_finish<uint16_t, kDcD>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 
   // ---- the last workgroup of the sequence to get here (nobody polls any more) resets the counters
   if (tid == 0) {
@@ -652,27 +714,32 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   }
 }
 
-bool decode_mfma_supported(const actqkv_shape& sh, int m) {
-  const int g = sh.n_q_heads / sh.n_kv_heads;
-  return sh.dtype == ACTQKV_BF16 && sh.head_dim == kDcD && m == 1 && g <= 8;
+// One query token per sequence, any storage type and head size the library takes.
+bool decode_mfma_supported(const actqkv_shape& sh, int m) { return m == 1 && sh.n_q_heads / sh.n_kv_heads <= 8; }
+// The kernels that do more than the attention exist for the serving shape only.
+bool decode_fused_supported(const actqkv_shape& sh) {
+  return decode_mfma_supported(sh, 1) && sh.dtype == ACTQKV_BF16 && sh.head_dim == kDcD;
 }
 
 // Launch shape: workgroups of 8 wavefronts; about 2048 wavefronts in total (two per SIMD,
-// each with a whole tile's loads in flight) unless the tile list is shorter than that.
+// each with a whole item's loads in flight) unless the item list is shorter than that.
 // One workgroup per (sequence, KV head) writes the output itself; with more, the one that
 // finishes last merges the partials.
-static int decode_tiles_max(const actqkv_shape& sh, int k_cap) {
-  return (sh.n_init + kBlock - 1) / kBlock + k_cap + sh.n_local / kBlock + 2;
+static int decode_items_max(const actqkv_shape& sh, int k_cap) {
+  const int tiles = (sh.n_init + kBlock - 1) / kBlock + k_cap + sh.n_local / kBlock + 2;
+  const int keys = sh.dtype == ACTQKV_F32 ? (sh.head_dim == 64 ? DcShape<float, 64>::kKeys : DcShape<float, 128>::kKeys)
+                                          : DcShape<uint16_t, 128>::kKeys;
+  return tiles * (kBlock / keys);
 }
 int decode_mfma_workgroups(const actqkv_shape& sh, int batch, int k_cap) {
   const int pairs = batch * sh.n_kv_heads;
   const int want = (2048 + pairs * kDcMaxWaves - 1) / (pairs * kDcMaxWaves);
-  const int most = (decode_tiles_max(sh, k_cap) * kDcPerTile + kDcMaxWaves - 1) / kDcMaxWaves;
+  const int most = (decode_items_max(sh, k_cap) + kDcMaxWaves - 1) / kDcMaxWaves;
   return want < 1 ? 1 : (want > most ? most : want);
 }
 
 size_t decode_mfma_scratch_floats(const actqkv_shape& sh, int batch, int k_cap) {
-  return size_t(batch) * sh.n_q_heads * decode_mfma_workgroups(sh, batch, k_cap) * (kDcD + 2);
+  return size_t(batch) * sh.n_q_heads * decode_mfma_workgroups(sh, batch, k_cap) * (sh.head_dim + 2);
 }
 
 static DcParams decode_params(const actqkv_shape& sh, int batch, const void* q, const void* k_cache,
@@ -680,9 +747,9 @@ static DcParams decode_params(const actqkv_shape& sh, int batch, const void* q, 
                               const int32_t* idx, const int32_t* n_sel, int k_cap, void* out, float* lse,
                               float* scratch, unsigned int* counters, float scale, int sel_per_head) {
   DcParams p;
-  p.q = static_cast<const uint16_t*>(q);
-  p.k_cache = static_cast<const uint16_t*>(k_cache);
-  p.v_cache = static_cast<const uint16_t*>(v_cache);
+  p.q = q;
+  p.k_cache = k_cache;
+  p.v_cache = v_cache;
   p.seq_stride = seq_stride;
   p.nb_capacity = nb_capacity;
   p.n_ctx = n_ctx;
@@ -690,7 +757,7 @@ static DcParams decode_params(const actqkv_shape& sh, int batch, const void* q, 
   p.n_sel = n_sel;
   p.sel_per_head = sel_per_head;
   p.k_cap = k_cap;
-  p.out = static_cast<uint16_t*>(out);
+  p.out = out;
   p.lse = lse;
   p.part = reinterpret_cast<uint32_t*>(scratch);
   p.counters = counters;
@@ -711,10 +778,20 @@ int launch_attention_decode_mfma(const actqkv_shape& sh, int batch, const void* 
   const DcParams p = decode_params(sh, batch, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx, idx, n_sel,
                                    k_cap, out, lse, scratch, counters, scale, sel_per_head);
   const int group = sh.n_q_heads / sh.n_kv_heads;
-  const size_t lds = size_t(kDcMaxWaves) * group * (kDcD + 2) * sizeof(float);
+  const size_t lds = size_t(kDcMaxWaves) * group * (sh.head_dim + 2) * sizeof(float);
   if (p.n_wg > 1 && size_t(batch) * sh.n_kv_heads > kTicketCounters)
     return set_error(ACTQKV_EINVAL, "decode attention: more split (sequence, KV head) pairs than ticket counters");
-  hipLaunchKernelGGL(attn_decode_kernel, dim3(p.n_wg, sh.n_kv_heads, batch), dim3(kDcThreads), lds, stream, p);
+  const dim3 grid(p.n_wg, sh.n_kv_heads, batch), block(kDcThreads);
+  if (sh.dtype == ACTQKV_F32) {
+    if (sh.head_dim == 64)
+      hipLaunchKernelGGL((attn_decode_kernel<float, 64>), grid, block, lds, stream, p);
+    else
+      hipLaunchKernelGGL((attn_decode_kernel<float, 128>), grid, block, lds, stream, p);
+  } else if (sh.head_dim == 64) {
+    hipLaunchKernelGGL((attn_decode_kernel<uint16_t, 64>), grid, block, lds, stream, p);
+  } else {
+    hipLaunchKernelGGL((attn_decode_kernel<uint16_t, 128>), grid, block, lds, stream, p);
+  }
   return hip_status("attention (decode)");
 }
 

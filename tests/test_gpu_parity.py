@@ -1106,6 +1106,44 @@ def test_decode_attention_that_selects_for_itself(n, k_cap, mode):
         assert int(b[1][s_]) == count and b[0][s_].tolist()[:count] == want
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("fp32", 64), ("fp32", 128), ("bf16", 128)])
+@pytest.mark.parametrize("group,copies", [(4, 1), (7, 12)])
+def test_decode_attention_at_the_edges_of_its_items(dtype, d, group, copies):
+    """One query token per sequence at context lengths around the sizes a wavefront's work item (32 or
+    64 keys), a matrix-core tile (16) and a block have, shorter and longer than the initial tokens,
+    with and without retrieved blocks; as few sequences as are spread over several workgroups each,
+    and as many as have a workgroup to themselves."""
+    sh = LayerShape(2 * group, 2, d, 128, 4, 128, 256, dtype)
+    cs = B.c_shape(sh)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    n_ctx = [1, 2, 15, 16, 17, 31, 32, 33, 63, 65, 127, 128, 129, 160, 384, 385, 417, 1151, 1152] * copies
+    bt, nb, k_cap = len(n_ctx), 9, 5
+    g = torch.Generator().manual_seed(d + group)
+    ks = [torch.randn(nb * 128, 2, d, generator=g).to(td) for _ in range(19)]
+    vs = [torch.randn(nb * 128, 2, d, generator=g).to(td) for _ in range(19)]
+    kc = torch.stack([H.blocked_k(ks[s % 19].to(DEV), sh, nb) for s in range(bt)])
+    vc = torch.stack([H.blocked_vt(vs[s % 19].to(DEV), sh, nb) for s in range(bt)])
+    q = torch.randn(bt, 1, 2 * group, d, generator=g).to(td)
+    idx, n_sel, chosen = torch.full((bt, k_cap), -1, dtype=torch.int32), torch.zeros(bt, dtype=torch.int32), []
+    for s in range(bt):
+        b, e = H.eligible_range(sh, n_ctx[s] - 1)
+        pick = (torch.randperm(max(e - b, 0), generator=g)[: k_cap] + b).tolist()
+        idx[s, : len(pick)] = torch.tensor(pick, dtype=torch.int32)
+        n_sel[s] = len(pick)
+        chosen.append(pick)
+    out = torch.zeros(bt, 1, 2 * group, d, dtype=td, device=DEV)
+    ws = torch.zeros(B.workspace_bytes(cs, bt, 1, nb, k_cap), dtype=torch.uint8, device=DEV)
+    for _ in range(2):                                   # the second call finds the counters as the first left them
+        B.retrieval_attention(cs, bt, 1, q.to(DEV), kc, vc, kc.stride(0), nb,
+                              torch.tensor(n_ctx, dtype=torch.int32, device=DEV), idx.to(DEV), n_sel.to(DEV), k_cap,
+                              out, None, ws)
+    torch.cuda.synchronize()
+    for s in list(range(19)) + [bt - 1]:
+        pos = orc.key_positions(n_ctx[s] - 1, n_ctx[s] - 1, chosen[s], sh.n_init, sh.n_local, 128)
+        ref = orc.attention_rows(f64(q[s]), f64(ks[s % 19]), f64(vs[s % 19]), pos, group)
+        assert out_error(out[s], ref) < TOL_OUT[dtype], (s, n_ctx[s])
+
+
 def test_largest_batch_of_a_decode_step():
     """1024 sequences (the largest batch the library takes) through the decode step in two
     launches: short ragged contexts, selections against the oracle's rule on the GPU's scores,
