@@ -12,9 +12,9 @@
 // KV head sit on one XCD (blockIdx % Hk picks the head), so that head's gathered
 // tiles stay in that XCD's L2.
 //
-// Data flow per tile.  K [128 keys][D] and V^T [D][128 keys] go from HBM straight into
-// LDS (global_load_lds_dwordx4, double buffered, 16-byte chunks XOR-swizzled with the row
-// index so that operand reads of 16 consecutive rows hit all 64 banks).  A 16x16x32 tiling
+// Data flow per tile.  K [128 keys][D] and V^T [D][128 keys] (D = 64 or 128 channels) go from HBM
+// straight into LDS (buffer_load_dwordx4 ... lds, double buffered, 16-byte chunks XOR-swizzled with
+// the row index so that operand reads of 16 consecutive rows hit all 64 banks).  A 16x16x32 tiling
 // with one wavefront per SIMD and no key splits was measured and rejected: one wavefront
 // can only issue a 1 KB LDS operand read every ~35 cycles, which caps a 16-cycle MFMA per
 // read at ~40 % and left that variant at 0.4 PFLOP/s.  Each wavefront computes S^T = K Q^T with
@@ -36,12 +36,8 @@ namespace actqkv {
 
 constexpr int kPfThreads = 512;
 constexpr int kPfWaves = 8;
-constexpr int kPfD = 128;
-constexpr int kRowPad = 128;                         // bf16 elements per LDS row (16 chunks of 16 bytes)
-constexpr int kTileElems = kBlock * kRowPad;         // one K or V^T tile in LDS
-constexpr int kPfMaxTiles = 96;                      // initial + selected (<= 64) + local + window
-constexpr int kPfLdsBytes = 2 * 2 * kTileElems * 2 + kPfMaxTiles * 12;  // 2 stages x (K, V^T) + tile table
-constexpr int kPfPartWords = 17;                     // 64-bit words per lane: 16 x 4 bf16 + (max, sum)
+template <int D> constexpr int kPfTileBytes = kBlock * D * 2;           // one K or V^T tile of a (block, KV head)
+template <int D> constexpr int kPfLdsBytes = 2 * 2 * kPfTileBytes<D>;   // 2 stages x (K, V^T)
 constexpr int kMaxPfSplits = 8;
 constexpr float kLazyMaxLog2 = 8.f;                  // how far a tile's maximum may exceed the reference one
 constexpr int kPfOrderMax = 64;                      // batch entries the queue hands out longest first
@@ -110,13 +106,14 @@ struct PfParams {
 
 // Final normalisation and store of one lane's share of a query row:
 // acc_o[db][4j + r] is channel d = db*32 + 8j + 4*half + r.
-__device__ __forceinline__ void store_rows(const PfParams& p, const f32x16 (&acc_o)[4], float m_run,
+template <int D>
+__device__ __forceinline__ void store_rows(const PfParams& p, const f32x16 (&acc_o)[D / 32], float m_run,
                                            float l_tot, int s, int my_row, int head, int half) {
   const size_t grow = (size_t(s) * p.m + my_row) * p.n_q_heads + head;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  uint16_t* op = p.out + grow * kPfD;
+  uint16_t* op = p.out + grow * D;
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+  for (int db = 0; db < D / 32; ++db)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       u32x2 v;
@@ -129,8 +126,9 @@ __device__ __forceinline__ void store_rows(const PfParams& p, const f32x16 (&acc
 }
 
 // One work item: piece `slot` of the query tiles of (sequence s, KV head hk).
-template <bool kInLoop>
+template <int D, bool kInLoop>
 __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* lds, int hk, int slot, int s) {
+  constexpr int kDb = D / 32, kKs = D / 16;      // 32-channel groups of the output, 16-channel steps of a score
   // (inside an item loop the thread index is made opaque, so that nothing derived from it is
   // hoisted out of the loop and kept in registers across the whole item)
   int tid = threadIdx.x;
@@ -187,18 +185,18 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
   // accumulators at minus the reference maximum would spare the multiply-add per score, but the
   // second rounding of the queries moves large logits by 2^-9 of their size: 2 % output error on
   // heavy-tailed inputs.)
-  bf16x8 qreg[kPfD / 16];
+  bf16x8 qreg[kKs];
   {
     const int r = min(my_row, p.m - 1);
-    const uint16_t* qp = p.q + ((size_t(s) * p.m + r) * p.n_q_heads + head) * kPfD + 8 * half;
+    const uint16_t* qp = p.q + ((size_t(s) * p.m + r) * p.n_q_heads + head) * D + 8 * half;
 #pragma unroll
-    for (int ks = 0; ks < kPfD / 16; ++ks)
+    for (int ks = 0; ks < kKs; ++ks)
       qreg[ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(qp + ks * 16));
   }
 
-  f32x16 acc_o[4];
+  f32x16 acc_o[kDb];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < kDb; ++i)
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc_o[i][j] = 0.f;
   float m_run = -INFINITY;                // running max (log2 units)
@@ -206,81 +204,85 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
 
   const char* kc = reinterpret_cast<const char*>(p.k_cache + size_t(s) * p.seq_stride);
   const char* vc = reinterpret_cast<const char*>(p.v_cache + size_t(s) * p.seq_stride);
-  constexpr uint32_t kTileBytes = kBlock * kPfD * 2;     // one (block, KV head) tile in HBM
-  constexpr uint32_t kSlotBytes = kTileElems * 2;        // one tile in LDS
+  constexpr uint32_t kTileBytes = kPfTileBytes<D>;
+  // LDS: stage s holds K at 2s * kTileBytes and V^T at (2s + 1) * kTileBytes
   char* lds_b = reinterpret_cast<char*>(lds);
-  // LDS: stage s holds K at (2s) * kSlotBytes and V^T at (2s + 1) * kSlotBytes; behind the
-  // stages sits the table {block, lo, hi} of this workgroup's tiles (the selected indices
-  // are read from global memory once, not once per use).
-  int* tile_tab = reinterpret_cast<int*>(lds_b + 4 * kSlotBytes);
-  for (int i = tid; i < t_end - t_begin; i += kPfThreads) {
-    int block, lo, hi;
-    tl.get(t_begin + i, block, lo, hi);
-    tile_tab[3 * i + 0] = block;
-    tile_tab[3 * i + 1] = lo;
-    tile_tab[3 * i + 2] = hi;
-  }
-  __syncthreads();
 
-  // Tiles go from HBM straight into LDS (global_load_lds_dwordx4: lane i of a wavefront
-  // fills the i-th 16-byte chunk of a contiguous 1 KB piece of LDS, i.e. 4 rows; no staging
-  // registers, no ds_write).  Wavefront w fills rows 16*w .. 16*w + 15 of a K and of a V^T
-  // tile with 4 such loads each.  The 16 chunks of an LDS row are XOR-swizzled with
-  // (row % 16), so that the 16 rows an MFMA operand load touches hit all 64 banks; the
-  // swizzle is applied on the global side: the lane that fills chunk c' of row r fetches
-  // chunk c' ^ (r % 16) of that row.
-  const int lq = lane >> 4, c16 = lane & 15;
-  const uint32_t g_row = uint32_t(16 * wave + lq) * (kPfD * 2);          // + 4*i rows per load
-  const uint32_t g_chunk = uint32_t(c16 ^ lq) << 4;                      // ^ (i << 6)
+  // Tiles go from HBM straight into LDS (buffer_load_dwordx4 ... lds: lane i of a wavefront
+  // fills the i-th 16-byte chunk of a contiguous 1 KB piece of LDS; no staging registers, no
+  // ds_write).  Each wavefront fills an eighth of a K and of a V^T tile.  The 16-byte chunks of
+  // an LDS row are XOR-swizzled with a key made of the row, so that the 16 rows an MFMA operand
+  // load touches hit all 64 banks: rows of 256 bytes (V^T, and K with 128 channels) take
+  // row % 16, rows of 128 bytes (K with 64 channels: two of them span the banks) take
+  // (row / 2) % 8.  The swizzle is applied on the global side: the lane that fills chunk c' of
+  // row r fetches chunk c' ^ key(r) of that row.
+  constexpr int kLoads = D / 32;                       // 1 KB pieces of a tile per wavefront
+  constexpr uint32_t kKRow = D * 2;                    // bytes of a K row
+  constexpr int kKPerPiece = 1024 / kKRow;             // K rows of a piece
   // per-lane byte offsets inside a tile, one per load; the tile's base and the LDS
   // destination are the same for all lanes and stay in scalar registers
-  uint32_t go[4];
+  uint32_t gk[kLoads], gv[kLoads];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) go[i] = g_row + i * 4 * (kPfD * 2) + (g_chunk ^ (uint32_t(i) << 6));
+  for (int i = 0; i < kLoads; ++i) {
+    const int kr = (kLoads * wave + i) * kKPerPiece + lane / (64 / kKPerPiece);
+    const int kc16 = lane % (64 / kKPerPiece);
+    gk[i] = uint32_t(kr) * kKRow + (uint32_t(kc16 ^ (D == 128 ? kr & 15 : (kr >> 1) & 7)) << 4);
+    const int vr = (kLoads * wave + i) * 4 + (lane >> 4);
+    gv[i] = uint32_t(vr) * 256 + (uint32_t((lane & 15) ^ (vr & 15)) << 4);
+  }
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  auto fetch_tile = [&](int u, int stage) {
-    const int block = __builtin_amdgcn_readfirstlane(tile_tab[3 * u]);
+  // tile t of the list -> its block and visible span, in scalar registers
+  auto tile_at = [&](int t, int& block, int& lo, int& hi) {
+    tl.get(t, block, lo, hi);
+    block = __builtin_amdgcn_readfirstlane(block);
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    hi = __builtin_amdgcn_readfirstlane(hi);
+  };
+  auto fetch_tile = [&](int block, int stage) {
     const size_t off = (size_t(block) * p.n_kv_heads + hk) * kTileBytes;
     const char* kt = uniform_ptr(kc + off);
     const char* vt = uniform_ptr(vc + off);
-    char* dst = lds_b + stage * 2 * kSlotBytes + wave_s * (16 * kRowPad * 2);
+    char* dst = lds_b + stage * 2 * kTileBytes + wave_s * (kTileBytes / 8);
     const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kt), 0, kTileBytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vt), 0, kTileBytes, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (__attribute__((address_space(3))) void*)(dst + i * 4 * (kRowPad * 2)), 16, go[i], 0, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (__attribute__((address_space(3))) void*)(dst + kSlotBytes + i * 4 * (kRowPad * 2)), 16, go[i], 0, 0, 0);
+    for (int i = 0; i < kLoads; ++i) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (__attribute__((address_space(3))) void*)(dst + i * 1024), 16, gk[i], 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (__attribute__((address_space(3))) void*)(dst + kTileBytes + i * 1024), 16, gv[i], 0, 0, 0);
     }
   };
 
-  if (t_begin < t_end) fetch_tile(0, 0);
+  int block = 0, lo = 0, hi = 0;
+  if (t_begin < t_end) {
+    tile_at(t_begin, block, lo, hi);
+    fetch_tile(block, 0);
+  }
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
   const int a_row = perm_row(n);
-  // Byte offsets of this lane's MFMA A operands inside a K / V^T slot.  K: row perm(n), chunk
-  // 2*ks + half, swizzle key perm(n) % 16; V^T: row n, chunk c = 4*kb + 2*s2 + half, swizzle
-  // key n % 16.  A row is 256 bytes, so the offset of chunk pair c is that of pair 0 with
-  // c << 5 XOR-ed in: one register per operand kind and one XOR per read, instead of eight
-  // registers each.  The 32-row blocks (kb, db) add a compile-time constant.
-  uint32_t a_off0 = uint32_t(a_row) * (kRowPad * 2) + (uint32_t(half ^ (a_row & 15)) << 4);
-  uint32_t v_off0 = uint32_t(n) * (kRowPad * 2) + (uint32_t(half ^ (n & 15)) << 4);
+  // Byte offsets of this lane's MFMA A operands inside a K / V^T tile.  K: row perm(n), chunk
+  // 2*ks + half; V^T: row n, chunk c = 4*kb + 2*s2 + half; both XOR-ed with the row's swizzle
+  // key.  The offset of chunk pair c is that of pair 0 with c << 5 XOR-ed in: one register per
+  // operand kind and one XOR per read, instead of eight registers each.  The 32-row blocks
+  // (kb, db) add a compile-time constant.
+  uint32_t a_off0 = uint32_t(a_row) * kKRow + (uint32_t(half ^ (D == 128 ? a_row & 15 : (a_row >> 1) & 7)) << 4);
+  uint32_t v_off0 = uint32_t(n) * 256 + (uint32_t(half ^ (n & 15)) << 4);
   float l_run = 0.f;                           // this lane's share of the running sum of its query row
   for (int t = t_begin; t < t_end; ++t) {
-    const int u = t - t_begin, stage = u & 1;
+    const int stage = (t - t_begin) & 1;
     // (opaque per iteration: the XOR-ed offsets are recomputed, not kept across the loop)
     asm volatile("" : "+v"(a_off0), "+v"(v_off0));
 
-    const int block = __builtin_amdgcn_readfirstlane(tile_tab[3 * u]);
-    const int lo = __builtin_amdgcn_readfirstlane(tile_tab[3 * u + 1]);
-    const int hi = __builtin_amdgcn_readfirstlane(tile_tab[3 * u + 2]);
+    int block_next = 0, lo_next = 0, hi_next = 0;
+    if (t + 1 < t_end) tile_at(t + 1, block_next, lo_next, hi_next);
     const int kpos0 = block * kBlock;
     // the wavefront skips tiles none of its rows can see; it masks tiles that are
     // clipped or that reach past its first row's position
     const bool visible = head_ok && hi > lo && lo <= g.w0 + min(wrow0 + 31, p.m - 1);
     const bool masked = lo > kpos0 || hi < kpos0 + kBlock || hi - 1 > g.w0 + wrow0;
-    const char* ks_ = lds_b + stage * 2 * kSlotBytes;
-    const char* vs_ = ks_ + kSlotBytes;
+    const char* ks_ = lds_b + stage * 2 * kTileBytes;
+    const char* vs_ = ks_ + kTileBytes;
     f32x16 acc_s[4];
     if (visible) {
       // ---- S^T = K Q^T : 4 groups of 32 keys
@@ -290,22 +292,23 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
       // independent one after 32)
       // (written in the order it should issue: a ring of 8 operands, each read 8 MFMAs ahead)
       auto k_read = [&](int i) {
-        return *reinterpret_cast<const u32x4*>(ks_ + (a_off0 ^ (uint32_t(i >> 2) << 5)) + (i & 3) * 32 * (kRowPad * 2));
+        return *reinterpret_cast<const u32x4*>(ks_ + (a_off0 ^ (uint32_t(i >> 2) << 5)) + (i & 3) * 32 * kKRow);
       };
+      constexpr int kScore = 4 * kKs;                  // MFMAs of the scores
       u32x4 ring[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) ring[i] = k_read(i);
 #pragma unroll
-      for (int i = 0; i < 32; ++i) {
+      for (int i = 0; i < kScore; ++i) {
         const int ks = i >> 2, kb = i & 3;
         acc_s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ring[i & 7]), qreg[ks], ks == 0 ? zero16 : acc_s[kb], 0, 0, 0);
-        if (i + 8 < 32) ring[i & 7] = k_read(i + 8);
+        if (i + 8 < kScore) ring[i & 7] = k_read(i + 8);
       }
       // issue order: 8 operand reads ahead of the first MFMA, then one read per MFMA, so that an
       // operand is requested about 8 MFMAs before it is needed (0x100 = LDS read, 0x008 = MFMA)
       __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
 #pragma unroll
-      for (int i = 0; i < 24; ++i) {
+      for (int i = 0; i < kScore - 8; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
@@ -317,7 +320,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     // compiler must treat LDS operations as completing out of order and waits for ALL
     // outstanding operand reads before each use, which stalled the score phase every 8 MFMAs.
     // It still has the softmax and the value phase of this tile to land.
-    if (t + 1 < t_end) fetch_tile(u + 1, stage ^ 1);
+    if (t + 1 < t_end) fetch_tile(block_next, stage ^ 1);
     if (visible) {
       // register i of group kb holds key kpos0 + kb*32 + 16*(i/8) + 8*half + (i%8)
       if (masked) {
@@ -332,9 +335,9 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
       }
       // ---- online softmax, one query per lane (two lanes share a query: n and n+32)
       // the first V^T operands are requested now and land during the max reduction;
-      // operand j = 4 * (2*kb + s2) + db belongs to keys kb*32 + s2*16 .. +15, rows db*32 .. +31
+      // operand j = kDb * (2*kb + s2) + db belongs to keys kb*32 + s2*16 .. +15, rows db*32 .. +31
       auto v_read = [&](int j) {
-        return *reinterpret_cast<const u32x4*>(vs_ + (v_off0 ^ (uint32_t(j >> 2) << 5)) + (j & 3) * 32 * (kRowPad * 2));
+        return *reinterpret_cast<const u32x4*>(vs_ + (v_off0 ^ (uint32_t(j / kDb) << 5)) + (j % kDb) * 32 * 256);
       };
       u32x4 vring[8];
 #pragma unroll
@@ -355,7 +358,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
       m_run = m_new;
       if (!__all(alpha == 1.f)) {
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < kDb; ++db)
 #pragma unroll
           for (int i = 0; i < 16; ++i) acc_o[db][i] *= alpha;
         l_run *= alpha;
@@ -376,19 +379,23 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
         add_bf16x8(l_run, pb, bf16_ones);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int db = 0; db < 4; ++db) {
+        for (int db = 0; db < kDb; ++db) {
           if (kb < 3) {
+            constexpr int kExp = 8 / kDb;
 #pragma unroll
-            for (int i = 8 * s2 + 2 * db; i < 8 * s2 + 2 * db + 2; ++i)
+            for (int i = 8 * s2 + kExp * db; i < 8 * s2 + kExp * (db + 1); ++i)
               acc_s[kb + 1][i] = __builtin_amdgcn_exp2f(acc_s[kb + 1][i] * p.scale_log2e - m_safe);
           }
           __builtin_amdgcn_sched_barrier(0);
-          const int j = 4 * g8 + db;
+          const int j = kDb * g8 + db;
           acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vring[j & 7]), pb, acc_o[db], 0, 0, 0);
-          if (j + 8 < 32) vring[j & 7] = v_read(j + 8);
+          if (j + 8 < 8 * kDb) vring[j & 7] = v_read(j + 8);
         }
       }
     }
+    block = block_next;
+    lo = lo_next;
+    hi = hi_next;
     __builtin_amdgcn_s_waitcnt(0);   // this wavefront's pieces of the next tile have landed in LDS
     __syncthreads();
   }
@@ -396,46 +403,47 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
   // ---- epilogue
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   if (splits == 1) {
-    if (row_ok) store_rows(p, acc_o, m_run, l_tot, s, my_row, head, half);
+    if (row_ok) store_rows<D>(p, acc_o, m_run, l_tot, s, my_row, head, half);
     return;
   }
   // The split stores its normalised output as bf16 in the order the registers hold it
   // (register-major, lane-minor: every store instruction writes one contiguous 512-byte
   // row), plus its running max and sum.
+  constexpr int kWords = 4 * kDb + 1;              // 64-bit words per lane: groups of four bf16, then (max, sum)
   __shared__ int last_flag;
   const size_t group_id = (size_t(s) * p.n_qtiles + qtile) * p.n_kv_heads + hk;
   uint64_t* group_part = p.part + ((size_t(s) * p.n_kv_heads + hk) * p.slots + (slot - split)) *
-                                      (kPfWaves * (kPfPartWords * 64));
+                                      (kPfWaves * (kWords * 64));
   {
-    uint64_t* mine = group_part + (size_t(split) * kPfWaves + wave) * (kPfPartWords * 64);
+    uint64_t* mine = group_part + (size_t(split) * kPfWaves + wave) * (kWords * 64);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < kDb; ++db)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const uint32_t lo = pack_bf16x2(acc_o[db][4 * i] * inv, acc_o[db][4 * i + 1] * inv);
         const uint32_t hi = pack_bf16x2(acc_o[db][4 * i + 2] * inv, acc_o[db][4 * i + 3] * inv);
         st_agent(mine + (db * 4 + i) * 64 + lane, uint64_t(lo) | (uint64_t(hi) << 32));
       }
-    st_agent(mine + 16 * 64 + lane, uint64_t(__float_as_uint(m_run)) | (uint64_t(__float_as_uint(l_tot)) << 32));
+    st_agent(mine + 4 * kDb * 64 + lane, uint64_t(__float_as_uint(m_run)) | (uint64_t(__float_as_uint(l_tot)) << 32));
   }
   if (!last_of_group(p.counters + group_id, unsigned(splits), &last_flag)) return;
 
   // ---- the last split of the query tile merges all of them, in split order:
   //   out = sum_s w_s o_s / sum_s w_s with w_s = l_s 2^(m_s - M), M = max_s m_s
   // (its own piece is read back like the others, so the result does not depend on who is last)
-  const uint64_t* piece0 = group_part + size_t(wave) * (kPfPartWords * 64) + lane;
-  const size_t piece_stride = size_t(kPfWaves) * (kPfPartWords * 64);
+  const uint64_t* piece0 = group_part + size_t(wave) * (kWords * 64) + lane;
+  const size_t piece_stride = size_t(kPfWaves) * (kWords * 64);
   // the loads of the first pieces go out together with the (max, sum) words of all pieces
   constexpr int kMergeBatch = 3;
-  uint64_t ml[kMaxPfSplits], raw[kMergeBatch][16];
+  uint64_t ml[kMaxPfSplits], raw[kMergeBatch][4 * kDb];
 #pragma unroll
   for (int s2 = 0; s2 < kMaxPfSplits; ++s2)
-    ml[s2] = s2 < splits ? ld_agent(piece0 + s2 * piece_stride + 16 * 64) : 0;
+    ml[s2] = s2 < splits ? ld_agent(piece0 + s2 * piece_stride + 4 * kDb * 64) : 0;
 #pragma unroll
   for (int j = 0; j < kMergeBatch; ++j)
 #pragma unroll
-    for (int k = 0; k < 16; ++k) raw[j][k] = j < splits ? ld_agent(piece0 + j * piece_stride + k * 64) : 0;
+    for (int k = 0; k < 4 * kDb; ++k) raw[j][k] = j < splits ? ld_agent(piece0 + j * piece_stride + k * 64) : 0;
   __builtin_amdgcn_sched_barrier(0);
   float w_s[kMaxPfSplits + kMergeBatch];
   float m_all = -INFINITY;
@@ -450,7 +458,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
                             : 0.f;
   float l_all = 0.f;
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+  for (int db = 0; db < kDb; ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc_o[db][i] = 0.f;
 #pragma unroll
@@ -460,7 +468,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
 #pragma unroll
         for (int j = 0; j < kMergeBatch; ++j)
 #pragma unroll
-          for (int k = 0; k < 16; ++k)
+          for (int k = 0; k < 4 * kDb; ++k)
             raw[j][k] = b0 + j < splits ? ld_agent(piece0 + (b0 + j) * piece_stride + k * 64) : 0;
       }
 #pragma unroll
@@ -468,7 +476,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
         const float w = w_s[b0 + j];
         l_all += w;
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < kDb; ++db)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const uint32_t lo = uint32_t(raw[j][db * 4 + i]), hi = uint32_t(raw[j][db * 4 + i] >> 32);
@@ -480,7 +488,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
       }
     }
   }
-  if (row_ok) store_rows(p, acc_o, m_all, l_all, s, my_row, head, half);
+  if (row_ok) store_rows<D>(p, acc_o, m_all, l_all, s, my_row, head, half);
 }
 
 // blockIdx.x = w * Hk + hk: consecutive ids differ in hk, and ids are dealt round-robin to the
@@ -491,12 +499,14 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
 // how many blocks they retrieve, and a fixed assignment would wait for the unluckiest
 // workgroup.  Nobody waits for anybody: a workgroup leaves when the counter runs out, and the
 // last one to leave puts the counters back to zero for the next launch.
+template <int D>
 __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_kernel(PfParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   const int item = blockIdx.x / p.n_kv_heads, s = item / p.slots;
-  attn_prefill_item<false>(p, lds, blockIdx.x % p.n_kv_heads, item - s * p.slots, s);
+  attn_prefill_item<D, false>(p, lds, blockIdx.x % p.n_kv_heads, item - s * p.slots, s);
 }
 
+template <int D>
 __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_queued_kernel(PfParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   __shared__ int next_item;
@@ -538,7 +548,7 @@ __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_queued_kernel(Pf
       s = order[s];
       slot = p.slots - 1 - slot;
     }
-    attn_prefill_item<true>(p, lds, hk, slot, s);
+    attn_prefill_item<D, true>(p, lds, hk, __builtin_amdgcn_readfirstlane(slot), __builtin_amdgcn_readfirstlane(s));
     __syncthreads();                         // everybody is done with the LDS tiles of this item
     item = draw();
   }
@@ -554,10 +564,7 @@ __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_queued_kernel(Pf
 }
 
 bool prefill_mfma_supported(const actqkv_shape& sh, int m) {
-  const int g = sh.n_q_heads / sh.n_kv_heads;
-  // longest possible tile list: initial + selected + local + window (+ 2 partial blocks)
-  const int tiles = sh.n_init / kBlock + 64 + sh.n_local / kBlock + (m + kBlock - 1) / kBlock + 2;
-  return sh.dtype == ACTQKV_BF16 && sh.head_dim == kPfD && m > 1 && g <= 8 && tiles <= kPfMaxTiles;
+  return sh.dtype == ACTQKV_BF16 && m > 1 && sh.n_q_heads / sh.n_kv_heads <= 8;
 }
 
 int prefill_mfma_qtiles(const actqkv_shape& sh, int m) {
@@ -571,19 +578,40 @@ int prefill_mfma_workgroups(const actqkv_shape& sh, int m) {
   return prefill_mfma_qtiles(sh, m) * sh.n_kv_heads;
 }
 
-// hipFuncSetAttribute once per process, from whichever thread comes first
+// hipFuncSetAttribute once per process and head size, from whichever thread comes first
+template <int D>
 static int prefill_lds_attribute() {
   static std::mutex mu;
   static bool attr_set = false;
   std::lock_guard<std::mutex> lock(mu);
   if (attr_set) return ACTQKV_OK;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kPfLdsBytes);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_kernel<D>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kPfLdsBytes<D>);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_queued_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kPfLdsBytes);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_queued_kernel<D>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kPfLdsBytes<D>);
   if (e != hipSuccess) return set_error(ACTQKV_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
   attr_set = true;
+  return ACTQKV_OK;
+}
+
+template <int D>
+static int launch_pf(PfParams p, int late_per_head, hipStream_t stream, hipStream_t stream_late) {
+  if (int rc = prefill_lds_attribute<D>()) return rc;
+  dim3 grid(p.wgs_per_head * p.n_kv_heads);
+  if (p.items_per_head > p.wgs_per_head)
+    hipLaunchKernelGGL(attn_prefill_mfma_queued_kernel<D>, grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
+  else
+    hipLaunchKernelGGL(attn_prefill_mfma_kernel<D>, grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
+  if (int rc = hip_status("attention (prefill, matrix cores)")) return rc;
+  if (late_per_head > 0) {
+    p.late = 1;
+    hipLaunchKernelGGL(attn_prefill_mfma_queued_kernel<D>, dim3(late_per_head * p.n_kv_heads), dim3(kPfThreads),
+                       kPfLdsBytes<D>, stream_late, p);
+    // (if this launch fails after the first one went out, the first team still does all the work, but
+    // the queue is not put back to zero: the workspace must be zero-filled again before its next use)
+    if (int rc = hip_status("attention (prefill, matrix cores, second team)")) return rc;
+  }
   return ACTQKV_OK;
 }
 
@@ -597,7 +625,6 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
                                   const PfSplits& splits, float* scratch, unsigned int* counters,
                                   float scale, int sel_per_head, int first_cus, int late_cus,
                                   hipStream_t stream, hipStream_t stream_late) {
-  if (int rc = prefill_lds_attribute()) return rc;
   PfParams p;
   p.q = static_cast<const uint16_t*>(q);
   p.k_cache = static_cast<const uint16_t*>(k_cache);
@@ -636,21 +663,8 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
   if (p.items_per_head <= p.wgs_per_head) late_per_head = 0;   // a workgroup per item: no queue, no second team
   p.team_total = (p.wgs_per_head + late_per_head) * sh.n_kv_heads;
   p.late = 0;
-  dim3 grid(p.wgs_per_head * sh.n_kv_heads);
-  if (p.items_per_head > p.wgs_per_head)
-    hipLaunchKernelGGL(attn_prefill_mfma_queued_kernel, grid, dim3(kPfThreads), kPfLdsBytes, stream, p);
-  else
-    hipLaunchKernelGGL(attn_prefill_mfma_kernel, grid, dim3(kPfThreads), kPfLdsBytes, stream, p);
-  if (int rc = hip_status("attention (prefill, matrix cores)")) return rc;
-  if (late_per_head > 0) {
-    p.late = 1;
-    hipLaunchKernelGGL(attn_prefill_mfma_queued_kernel, dim3(late_per_head * sh.n_kv_heads), dim3(kPfThreads),
-                       kPfLdsBytes, stream_late, p);
-    // (if this launch fails after the first one went out, the first team still does all the work, but
-    // the queue is not put back to zero: the workspace must be zero-filled again before its next use)
-    if (int rc = hip_status("attention (prefill, matrix cores, second team)")) return rc;
-  }
-  return ACTQKV_OK;
+  return sh.head_dim == 64 ? launch_pf<64>(p, late_per_head, stream, stream_late)
+                           : launch_pf<128>(p, late_per_head, stream, stream_late);
 }
 
 }  // namespace actqkv

@@ -347,6 +347,43 @@ def test_attention_over_the_largest_selection(dtype, d):
         assert err < TOL_OUT[dtype], f"window {i}: {err}"
 
 
+@pytest.mark.parametrize("dtype,d,group,m,nw", [("bf16", 64, 4, 65, 1), ("bf16", 64, 1, 33, 3), ("bf16", 64, 7, 257, 1),
+                                                ("bf16", 64, 8, 31, 160), ("bf16", 64, 2, 129, 40),
+                                                ("bf16", 128, 2, 4225, 1)])
+def test_prefill_attention_at_the_edges_of_its_tiles(dtype, d, group, m, nw):
+    """Windows of one sequence that end next to the 32 positions of a wavefront, the positions of a
+    workgroup and the 128 keys of a tile; key tiles cut into pieces, whole query tiles, and more work
+    items than compute units; a window of more than 4096 tokens."""
+    sh = LayerShape(2 * group, 2, d, 128, 4, 128, 256, dtype)
+    cs = B.c_shape(sh)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    k_cap, base = 4, 9 * 128 + 37
+    n_tok = base + nw * m
+    nb = (n_tok + 127) // 128
+    g = torch.Generator().manual_seed(d + group + m)
+    q = torch.randn(nw * m, 2 * group, d, generator=g).to(td)
+    k = torch.randn(nb * 128, 2, d, generator=g).to(td)
+    v = torch.randn(nb * 128, 2, d, generator=g).to(td)
+    w0 = [base + i * m for i in range(nw)]
+    idx, n_sel = torch.full((nw, k_cap), -1, dtype=torch.int32), torch.zeros(nw, dtype=torch.int32)
+    for i in range(nw):
+        b, e = H.eligible_range(sh, w0[i])
+        n_sel[i] = i % (k_cap + 1)
+        idx[i, : int(n_sel[i])] = (torch.randperm(e - b, generator=g)[: int(n_sel[i])] + b).int()
+    out = torch.zeros(nw * m, 2 * group, d, dtype=td, device=DEV)
+    ws = torch.zeros(B.workspace_bytes(cs, nw, m, nb, k_cap), dtype=torch.uint8, device=DEV)
+    for _ in range(2):                                   # the second call finds the counters as the first left them
+        B.retrieval_attention(cs, nw, m, q.to(DEV), H.blocked_k(k.to(DEV), sh, nb), H.blocked_vt(v.to(DEV), sh, nb), 0,
+                              nb, torch.tensor([w + m for w in w0], dtype=torch.int32, device=DEV), idx.to(DEV),
+                              n_sel.to(DEV), k_cap, out, None, ws)
+    torch.cuda.synchronize()
+    for i in sorted({0, nw // 2, nw - 1}):
+        for r in sorted({0, min(31, m - 1), min(32, m - 1), m // 2, m - 1}):
+            pos = orc.key_positions(w0[i], w0[i] + r, idx[i, : int(n_sel[i])].tolist(), sh.n_init, sh.n_local, 128)
+            ref = orc.attention_rows(f64(q[i * m + r])[None], f64(k), f64(v), pos, group)[0]
+            assert out_error(out[i * m + r], ref) < TOL_OUT[dtype], (i, r)
+
+
 @pytest.mark.parametrize("dtype,d,m,n_ctx", [("bf16", 128, 2, 700), ("bf16", 128, 33, 1500), ("fp32", 64, 3, 500)])
 def test_tiny_windows(dtype, d, m, n_ctx):
     """Windows of 2, 3 and 33 tokens (most rows of a query tile idle, a ragged last window)."""
