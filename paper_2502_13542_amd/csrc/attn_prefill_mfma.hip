@@ -2,8 +2,9 @@
 // (Sec. 3.1, Eq. (2): O^t = Attention(Q^t, [K^t, K*], [V^t, V*]); bf16 storage, fp32 accumulation).
 //
 // Work split.  A workgroup of 8 wavefronts owns 256 query rows that share one KV
-// head: all G query heads of the group times 256/G consecutive window positions;
-// each wavefront owns 32 rows (one head, 32 positions).  The key tiles of the
+// head, each wavefront 32 of them.  The rows are numbered position by position with the G
+// heads of the KV head side by side, so every group size fills the wavefronts (with a
+// wavefront per head, seven heads left one of eight idle: 1.92 instead of 1.87 ms for a pass over 50001 tokens).  The key tiles of the
 // window - initial tokens, the blocks chosen by actqkv_select (read from device
 // memory), the local span and the causal part of the window - form one list of
 // 128-key blocks; it is cut into `splits` contiguous pieces, one workgroup each,
@@ -36,6 +37,7 @@ namespace actqkv {
 
 constexpr int kPfThreads = 512;
 constexpr int kPfWaves = 8;
+constexpr int kPfRows = 32 * kPfWaves;               // query rows of a workgroup
 template <int D> constexpr int kPfTileBytes = kBlock * D * 2;           // one K or V^T tile of a (block, KV head)
 template <int D> constexpr int kPfLdsBytes = 2 * 2 * kPfTileBytes<D>;   // 2 stages x (K, V^T)
 constexpr int kMaxPfSplits = 8;
@@ -72,8 +74,6 @@ __device__ __forceinline__ const char* uniform_ptr(const char* ptr) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane(uint32_t(v >> 32));
   return reinterpret_cast<const char*>((uint64_t(hi) << 32) | lo);
 }
-
-__host__ __device__ __forceinline__ int padded_group(int g) { return g <= 1 ? 1 : (g <= 2 ? 2 : (g <= 4 ? 4 : 8)); }
 
 // MFMA row -> key row inside a 32-key group: swap bits 2 and 3.
 __device__ __forceinline__ int perm_row(int i) {
@@ -133,13 +133,9 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
   // hoisted out of the loop and kept in registers across the whole item)
   int tid = threadIdx.x;
   if (kInLoop) asm volatile("" : "+v"(tid));
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, half = lane >> 5;
   const int group = p.n_q_heads / p.n_kv_heads;
-  // a group size that does not divide 8 (7 heads per KV head, say) is rounded up to the next
-  // power of two: the surplus wavefronts help to fetch tiles and otherwise idle
-  const int waves_per_head = kPfWaves / padded_group(group);
-  const int pos_per_wg = 32 * waves_per_head;
 
   // The slots of a (sequence, KV head) are the pieces of its query tiles, in order.
   const int n_lo = p.n_qtiles - p.rem;
@@ -165,19 +161,23 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
   __syncthreads();
   const int n_ctx = min(max(n_ctx_raw, p.m), p.nb_capacity * kBlock);
   const WindowGeom g = window_geom(n_ctx, p.m, p.n_init, p.n_local);
-  const int row0 = qtile * pos_per_wg;                       // first window row of the workgroup
-  const int row_hi = min(row0 + pos_per_wg, p.m) - 1;
+  // The query rows of a (sequence, KV head) are numbered position by position, the G heads of a
+  // position next to each other; a workgroup takes kPfRows consecutive ones, a wavefront 32.
+  const int row_end = p.m * group;
+  const int row_hi = (min((qtile + 1) * kPfRows, row_end) - 1) / group;
   const TileList tl = make_tile_list(g, g.w0 + row_hi, idx_lds, n_sel_raw, p.k_cap, p.nb_capacity);
   const int n_tiles = tl.count();
   const int per = (n_tiles + splits - 1) / splits;
   const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
 
-  const int head_in_group = wave / waves_per_head;
-  const bool head_ok = head_in_group < group;
-  const int head = hk * group + min(head_in_group, group - 1);
-  const int wrow0 = row0 + (wave % waves_per_head) * 32;     // first window row of this wavefront
-  const int my_row = wrow0 + n;
-  const bool row_ok = my_row < p.m && head_ok;
+  const int frow0 = qtile * kPfRows + wave * 32;             // first query row of this wavefront
+  const bool wave_ok = frow0 < row_end;
+  const int wpos_lo = g.w0 + min(frow0, row_end - 1) / group;         // positions of its first and last row
+  const int wpos_hi = g.w0 + min(frow0 + 31, row_end - 1) / group;
+  const bool row_ok = frow0 + n < row_end;
+  const int frow = min(frow0 + n, row_end - 1);
+  const int my_row = frow / group;                           // window row (position) and head of this lane
+  const int head = hk * group + (frow - my_row * group);
   const int my_pos = g.w0 + my_row;                          // this lane's query position
 
   // Q^T as B operand: lane (n, half) holds d = ks*16 + 8*half .. +7 of query row n.  (Folding
@@ -187,8 +187,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
   // heavy-tailed inputs.)
   bf16x8 qreg[kKs];
   {
-    const int r = min(my_row, p.m - 1);
-    const uint16_t* qp = p.q + ((size_t(s) * p.m + r) * p.n_q_heads + head) * D + 8 * half;
+    const uint16_t* qp = p.q + ((size_t(s) * p.m + my_row) * p.n_q_heads + head) * D + 8 * half;
 #pragma unroll
     for (int ks = 0; ks < kKs; ++ks)
       qreg[ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(qp + ks * 16));
@@ -230,7 +229,6 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     const int vr = (kLoads * wave + i) * 4 + (lane >> 4);
     gv[i] = uint32_t(vr) * 256 + (uint32_t((lane & 15) ^ (vr & 15)) << 4);
   }
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   // tile t of the list -> its block and visible span, in scalar registers
   auto tile_at = [&](int t, int& block, int& lo, int& hi) {
     tl.get(t, block, lo, hi);
@@ -242,7 +240,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     const size_t off = (size_t(block) * p.n_kv_heads + hk) * kTileBytes;
     const char* kt = uniform_ptr(kc + off);
     const char* vt = uniform_ptr(vc + off);
-    char* dst = lds_b + stage * 2 * kTileBytes + wave_s * (kTileBytes / 8);
+    char* dst = lds_b + stage * 2 * kTileBytes + wave * (kTileBytes / 8);
     const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kt), 0, kTileBytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vt), 0, kTileBytes, 0x00020000);
 #pragma unroll
@@ -279,8 +277,8 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     const int kpos0 = block * kBlock;
     // the wavefront skips tiles none of its rows can see; it masks tiles that are
     // clipped or that reach past its first row's position
-    const bool visible = head_ok && hi > lo && lo <= g.w0 + min(wrow0 + 31, p.m - 1);
-    const bool masked = lo > kpos0 || hi < kpos0 + kBlock || hi - 1 > g.w0 + wrow0;
+    const bool visible = wave_ok && hi > lo && lo <= wpos_hi;
+    const bool masked = lo > kpos0 || hi < kpos0 + kBlock || hi - 1 > wpos_lo;
     const char* ks_ = lds_b + stage * 2 * kTileBytes;
     const char* vs_ = ks_ + kTileBytes;
     f32x16 acc_s[4];
@@ -568,9 +566,7 @@ bool prefill_mfma_supported(const actqkv_shape& sh, int m) {
 }
 
 int prefill_mfma_qtiles(const actqkv_shape& sh, int m) {
-  const int g = sh.n_q_heads / sh.n_kv_heads;
-  const int pos_per_wg = 32 * (kPfWaves / padded_group(g));
-  return (m + pos_per_wg - 1) / pos_per_wg;
+  return (m * (sh.n_q_heads / sh.n_kv_heads) + kPfRows - 1) / kPfRows;
 }
 
 // workgroups per (sequence, split): query tiles x KV heads
