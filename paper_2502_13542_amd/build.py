@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libactqkv.so")
 NATIVE = os.path.join(HERE, "_native.so")
 
-SOURCES = ["api.hip", "probe.hip", "score.hip", "select.hip", "attn_rows.hip",
+SOURCES = ["api.hip", "probe.hip", "score.hip", "select.hip", "attn_prefill_f32.hip",
            "attn_prefill_mfma.hip", "attn_decode.hip", "append.hip", "cutoff.hip", "gather.hip",
            "decode_retrieve.hip", "attn_static.hip"]
 

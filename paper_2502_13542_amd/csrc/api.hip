@@ -130,6 +130,14 @@ PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int
   r.slots = r.s_lo * n_qtiles + r.rem;
   return r;
 }
+bool prefill_f32_supported(const actqkv_shape& sh, int m);
+size_t prefill_f32_scratch_bytes(const actqkv_shape& sh, int batch, int m);
+size_t prefill_f32_scratch_most(const actqkv_shape& sh, int batch, int m);
+int launch_attention_prefill_f32(const actqkv_shape& sh, int batch, int m, const void* q, const void* k_cache,
+                                 const void* v_cache, int64_t seq_stride, int nb_capacity, const int32_t* n_ctx,
+                                 const int32_t* idx, const int32_t* n_sel, int k_cap, void* out, float* lse,
+                                 float* scratch, unsigned int* counters, float scale, int sel_per_head,
+                                 hipStream_t stream);
 bool decode_mfma_supported(const actqkv_shape& sh, int m);
 bool decode_fused_supported(const actqkv_shape& sh);
 size_t decode_mfma_scratch_floats(const actqkv_shape& sh, int batch, int k_cap);
@@ -157,6 +165,7 @@ size_t attention_scratch_bytes(const actqkv_shape& sh, int batch, int m, int k_c
     if (splits.slots > prefill_mfma_qtiles(sh, m))
       attn = size_t(batch) * sh.n_kv_heads * splits.slots * kPfPartialFloats * sizeof(float);
   }
+  if (prefill_f32_supported(sh, m)) attn = prefill_f32_scratch_bytes(sh, batch, m);
   return kCounterBytes + align_up(attn, 256);
 }
 
@@ -170,11 +179,11 @@ size_t workspace_bytes(const actqkv_shape& sh, int batch, int m, int nb_capacity
 
 // What a caller should allocate: enough for every call with 1 .. batch entries and windows of
 // 1 .. m tokens.  The need is not monotone: few short windows are cut into many pieces with
-// partial results, many long ones into none, and a window too long for the matrix-core kernel
-// needs no scratch at all; so a workspace sized for a layer's nominal window must also serve
+// partial results, many long ones into none; so a workspace sized for a layer's nominal window must also serve
 // its ragged last window and a decode step.
 static size_t workspace_bytes_upto(const actqkv_shape& sh, int batch, int m, int nb_capacity, int k_cap) {
   size_t need = 0;
+  if (prefill_f32_supported(sh, m)) need = kCounterBytes + align_up(prefill_f32_scratch_most(sh, batch, m), 256);
   for (int b = 1; b <= batch; ++b) {
     need = std::max(need, workspace_bytes(sh, b, 1, nb_capacity, k_cap));
     for (int mm = 32; mm < m + 32; mm += 32)       // query tiles are multiples of 32 positions
@@ -182,11 +191,6 @@ static size_t workspace_bytes_upto(const actqkv_shape& sh, int batch, int m, int
   }
   return need;
 }
-
-int launch_attention_rows(const actqkv_shape& sh, int batch, int m, const void* q, const void* k_cache,
-                          const void* v_cache, int64_t seq_stride, int nb_capacity,
-                          const int32_t* n_ctx, const int32_t* idx, const int32_t* n_sel, int k_cap,
-                          void* out, float* lse, float scale, int sel_per_head, hipStream_t stream);
 
 int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, const void* k_cache,
                      const void* v_cache, int64_t seq_stride, int nb_capacity, const int32_t* n_ctx,
@@ -204,8 +208,8 @@ int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, co
                                          prefill_splits(sh, batch, m, k_cap, first_cus), ws.scratch_f32(),
                                          ws.counters(), scale, sel_per_head, first_cus, late_cus, stream,
                                          stream_late);
-  return launch_attention_rows(sh, batch, m, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx, idx,
-                               n_sel, k_cap, out, lse, scale, sel_per_head, stream);
+  return launch_attention_prefill_f32(sh, batch, m, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx, idx, n_sel,
+                                      k_cap, out, lse, ws.scratch_f32(), ws.counters(), scale, sel_per_head, stream);
 }
 
 // Host-side checks of an attention call; `need` receives the scratch bytes the call uses.

@@ -349,7 +349,10 @@ def test_attention_over_the_largest_selection(dtype, d):
 
 @pytest.mark.parametrize("dtype,d,group,m,nw", [("bf16", 64, 4, 65, 1), ("bf16", 64, 1, 33, 3), ("bf16", 64, 7, 257, 1),
                                                 ("bf16", 64, 8, 31, 160), ("bf16", 64, 2, 129, 40),
-                                                ("bf16", 128, 2, 4225, 1)])
+                                                ("bf16", 128, 2, 4225, 1),
+                                                ("fp32", 64, 4, 65, 1), ("fp32", 128, 4, 33, 3), ("fp32", 64, 1, 257, 1),
+                                                ("fp32", 128, 8, 17, 40), ("fp32", 64, 7, 37, 90),
+                                                ("fp32", 128, 2, 4225, 1)])
 def test_prefill_attention_at_the_edges_of_its_tiles(dtype, d, group, m, nw):
     """Windows of one sequence that end next to the 32 positions of a wavefront, the positions of a
     workgroup and the 128 keys of a tile; key tiles cut into pieces, whole query tiles, and more work
