@@ -337,6 +337,18 @@ int actqkv_retrieval_attention_teams(const actqkv_shape* shape, int batch, int m
                                      void* workspace, size_t ws_bytes, int first_cus, int late_cus,
                                      void* stream, void* stream_late);
 
+/*
+ * n_windows windows of ONE sequence (one cache, m tokens each, q and out [n_windows][m][Hq][D]) in one
+ * launch on `cus` compute units (1 .. 256), with results bit for bit those of a call of
+ * actqkv_retrieval_attention per window: every window's keys are cut into the pieces they are cut
+ * into when it is alone.  bf16, m >= 2.  ws_bytes: n_windows times what one window needs is enough.
+ */
+int actqkv_retrieval_attention_windows(const actqkv_shape* shape, int n_windows, int m, const void* q,
+                                       const void* k_cache, const void* v_cache, int nb_capacity,
+                                       const int32_t* n_ctx, const int32_t* idx, const int32_t* n_sel, int k_cap,
+                                       void* out, float* lse, void* workspace, size_t ws_bytes, int cus,
+                                       void* stream);
+
 /* The first launch of a decode step: actqkv_append_kv with m = 1 and the probe of the step's
  * one-token window (actqkv_build_probe with m = 1 and no statistics: probe = the query,
  * Sec. 4.2) in ONE launch; the two are independent, and each is a few microseconds of work
@@ -460,6 +472,26 @@ int actqkv_gather_blocks(const actqkv_shape* shape, int batch, const void* k_sto
                          const int32_t* idx, const int32_t* n_sel, int k_cap, void* k_cache,
                          void* v_cache, int64_t cache_seq_stride, int nb_capacity, int slot0,
                          int32_t* idx_slots, void* stream);
+
+/*
+ * The same for a pass of many windows of one sequence whose slots outlive a window: the n_slots
+ * slots from slot0 on are a cache of the store, least recently used block first out.  A call
+ * serves a group of n_windows windows together (n_windows * k_cap <= 256).
+ *   idx, n_sel  [n_windows][k_cap], [n_windows], as written by actqkv_select (device memory)
+ *   n_slots     2 n_windows k_cap .. 512.  Slots that this group or the one before it uses are never
+ *               overwritten by the call, so the attention of the group before may still be running.
+ *   hereN_lo, hereN_hi, hereN_at  blocks [lo, hi) of the sequence lie in the working cache itself from block
+ *               `at` on, outside the slots, and are copied from there (hi <= lo: none do)
+ *   group       number of the call in the pass: 0, 1, 2, ...
+ *   state       device int32 [nb_store + 2 n_slots + 513]: every entry -2 before group 0, then left alone
+ *   idx_slots   out, [n_windows][k_cap]: the blocks' places in the working cache (-1: none), the selection
+ *               to hand to the attention
+ */
+int actqkv_gather_blocks_cached(const actqkv_shape* shape, int n_windows, const void* k_store, const void* v_store,
+                                int nb_store, const int32_t* idx, const int32_t* n_sel, int k_cap, void* k_cache,
+                                void* v_cache, int nb_capacity, int slot0, int n_slots, int here0_lo, int here0_hi,
+                                int here0_at, int here1_lo, int here1_hi, int here1_at, int group, int32_t* state,
+                                int32_t* idx_slots, void* stream);
 
 /* A plain copy of `bytes` bytes (a multiple of 16; both pointers memory the device can access -
  * device memory or pinned host memory -, 16-byte aligned, not overlapping) done by one kernel

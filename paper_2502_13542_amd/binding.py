@@ -81,6 +81,10 @@ SIGNATURES = {
                                               _vp, _vp, _vp, _sz, _i, _i, _vp, _vp]),
     "actqkv_copy_bytes": (_i, [_vp, _vp, _sz, _vp]),
     "actqkv_gather_blocks": (_i, [_shp, _i, _vp, _vp, _i64, _i, _vp, _vp, _i, _vp, _vp, _i64, _i, _i, _vp, _vp]),
+    "actqkv_gather_blocks_cached": (_i, [_shp, _i, _vp, _vp, _i, _vp, _vp, _i, _vp, _vp, _i, _i, _i, _i, _i, _i, _i,
+                                         _i, _i, _i, _vp, _vp, _vp]),
+    "actqkv_retrieval_attention_windows": (_i, [_shp, _i, _i, _vp, _vp, _vp, _i, _vp, _vp, _vp, _i, _vp, _vp, _vp, _sz,
+                                                _i, _vp]),
     "actqkv_last_error": (ctypes.c_char_p, []),
     "actqkv_version": (_i, []),
 }
@@ -225,6 +229,13 @@ def retrieval_attention_teams(shape: CShape, batch: int, m: int, q, k_cache, v_c
                                        n_sel, k_cap, out, lse, workspace, first_cus, late_cus, stream, stream_late)
 
 
+def retrieval_attention_windows(shape: CShape, n_windows: int, m: int, q, k_cache, v_cache, nb_capacity: int, n_ctx,
+                                idx, n_sel, k_cap: int, out, lse, workspace, cus: int = 256, stream=None) -> None:
+    """The attention of several windows of one sequence in one launch, each as if alone; see the header."""
+    _calls().retrieval_attention_windows(shape, n_windows, m, q, k_cache, v_cache, nb_capacity, n_ctx, idx, n_sel, k_cap,
+                                         out, lse, workspace, cus, stream)
+
+
 def cutoff_budgets(batch: int, n_layers: int, k_mean: float, k_cap: int, theta, budget, count, budget_left=None,
                    stream=None) -> None:
     _calls().cutoff_budgets(batch, n_layers, k_mean, k_cap, theta, budget, count, budget_left, stream)
@@ -264,6 +275,15 @@ def gather_blocks(shape: CShape, batch: int, k_store, v_store, store_seq_stride:
                   slot0: int, idx_slots, stream=None) -> None:
     _calls().gather_blocks(shape, batch, k_store, v_store, store_seq_stride, nb_store, idx, n_sel, k_cap, k_cache,
                            v_cache, cache_seq_stride, nb_capacity, slot0, idx_slots, stream)
+
+
+def gather_blocks_cached(shape: CShape, n_windows: int, k_store, v_store, nb_store: int, idx, n_sel, k_cap: int,
+                         k_cache, v_cache, nb_capacity: int, slot0: int, n_slots: int, here0, here1, group: int, state,
+                         idx_slots, stream=None) -> None:
+    """The blocks a group of windows selects into slots that keep their blocks; here0, here1: (lo, hi, at)
+    of blocks that lie in the cache itself.  See the header."""
+    _calls().gather_blocks_cached(shape, n_windows, k_store, v_store, nb_store, idx, n_sel, k_cap, k_cache, v_cache,
+                                  nb_capacity, slot0, n_slots, *here0, *here1, group, state, idx_slots, stream)
 
 
 def score_blocks(shape: CShape, batch: int, probe_kv, probe_norm, rep_keys, seq_stride: int,

@@ -196,7 +196,7 @@ int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, co
                      const void* v_cache, int64_t seq_stride, int nb_capacity, const int32_t* n_ctx,
                      const int32_t* idx, const int32_t* n_sel, int k_cap, void* out, float* lse,
                      const Workspace& ws, int sel_per_head, hipStream_t stream, int first_cus, int late_cus,
-                     hipStream_t stream_late) {
+                     hipStream_t stream_late, bool pieces_of_one) {
   const float scale = sh.softmax_scale > 0.f ? sh.softmax_scale : 1.f / std::sqrt(float(sh.head_dim));
   if (decode_mfma_supported(sh, m))   // (no queue: one launch does all the work)
     return launch_attention_decode_mfma(sh, batch, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx,
@@ -205,7 +205,8 @@ int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, co
   if (prefill_mfma_supported(sh, m))
     return launch_attention_prefill_mfma(sh, batch, m, q, k_cache, v_cache, seq_stride, nb_capacity,
                                          n_ctx, idx, n_sel, k_cap, out, lse,
-                                         prefill_splits(sh, batch, m, k_cap, first_cus), ws.scratch_f32(),
+                                         pieces_of_one ? prefill_splits(sh, 1, m, k_cap, kChipCus)
+                                                       : prefill_splits(sh, batch, m, k_cap, first_cus), ws.scratch_f32(),
                                          ws.counters(), scale, sel_per_head, first_cus, late_cus, stream,
                                          stream_late);
   return launch_attention_prefill_f32(sh, batch, m, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx, idx, n_sel,
@@ -256,6 +257,35 @@ __global__ __launch_bounds__(256) void copy_bytes_kernel(u32x4* __restrict__ dst
                                                          const u32x4* __restrict__ src, size_t n) {
   for (size_t i = size_t(blockIdx.x) * 256 + threadIdx.x; i < n; i += size_t(gridDim.x) * 256)
     dst[i] = src[i];
+}
+
+// The same over the host link: few workgroups with many words in flight each.  The link takes about
+// 57 GB/s whatever asks; a workgroup per 4 KB filled the memory system's queues with host accesses,
+// and a 2 us kernel beside an 8 MB copy took 87 us.
+constexpr int kLinkWgs = 8, kLinkBatch = 8;
+__global__ __launch_bounds__(256) void copy_bytes_link_kernel(u32x4* __restrict__ dst, const u32x4* __restrict__ src,
+                                                              size_t n) {
+  for (size_t i0 = size_t(blockIdx.x) * 256 * kLinkBatch; i0 < n; i0 += size_t(gridDim.x) * 256 * kLinkBatch) {
+    u32x4 x[kLinkBatch];
+#pragma unroll
+    for (int b = 0; b < kLinkBatch; ++b) {
+      const size_t i = i0 + b * 256 + threadIdx.x;
+      x[b] = src[i < n ? i : n - 1];
+    }
+#pragma unroll
+    for (int b = 0; b < kLinkBatch; ++b) {
+      const size_t i = i0 + b * 256 + threadIdx.x;
+      if (i < n) dst[i] = x[b];
+    }
+  }
+}
+static bool in_host_memory(const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeHost;
 }
 }  // namespace actqkv
 
@@ -398,6 +428,28 @@ int actqkv_retrieval_attention_teams(const actqkv_shape* shape, int batch, int m
     return set_error(ACTQKV_EINVAL, "late_cus %d neither 0 nor in n_kv_heads..%d", late_cus, kChipCus);
   return attention_checked(shape, batch, m, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx, idx, n_sel,
                            k_cap, out, lse, workspace, ws_bytes, 0, stream, first_cus, late_cus, stream_late);
+}
+
+int actqkv_retrieval_attention_windows(const actqkv_shape* shape, int n_windows, int m, const void* q,
+                                       const void* k_cache, const void* v_cache, int nb_capacity,
+                                       const int32_t* n_ctx, const int32_t* idx, const int32_t* n_sel, int k_cap,
+                                       void* out, float* lse, void* workspace, size_t ws_bytes, int cus,
+                                       void* stream) {
+  if (cus < 1 || cus > kChipCus) return set_error(ACTQKV_EINVAL, "cus %d outside 1..%d", cus, kChipCus);
+  size_t need = 0;
+  ACTQKV_TRY(check_batch(n_windows));
+  ACTQKV_TRY(attention_validate(shape, 1, m, q, k_cache, v_cache, 0, nb_capacity, n_ctx, idx, n_sel, k_cap, out, lse,
+                                kChipCus, &need));
+  if (!prefill_mfma_supported(*shape, m))
+    return set_error(ACTQKV_ESHAPE, "retrieval_attention_windows: bf16 and windows of at least 2 tokens");
+  need = kCounterBytes + (need - kCounterBytes) * n_windows;
+  if (workspace == nullptr || !aligned16(workspace))
+    return set_error(ACTQKV_EWORKSPACE, "workspace is NULL or not 16-byte aligned");
+  if (ws_bytes < need)
+    return set_error(ACTQKV_EWORKSPACE, "workspace has %zu bytes, retrieval_attention_windows needs %zu", ws_bytes, need);
+  Workspace ws{workspace, ws_bytes};
+  return launch_attention(*shape, n_windows, m, q, k_cache, v_cache, 0, nb_capacity, n_ctx, idx, n_sel, k_cap, out, lse,
+                          ws, 0, static_cast<hipStream_t>(stream), cus, 0, nullptr, true);
 }
 
 int actqkv_retrieval_attention_per_head(const actqkv_shape* shape, int batch, int m, const void* q,
@@ -570,6 +622,11 @@ int actqkv_copy_bytes(void* dst, const void* src, size_t bytes, void* stream) {
     return set_error(ACTQKV_EALIGN, "copy_bytes: pointers must be 16-byte aligned");
   if (bytes == 0) return ACTQKV_OK;
   const size_t n = bytes / 16;
+  if (in_host_memory(dst) || in_host_memory(src)) {
+    hipLaunchKernelGGL(copy_bytes_link_kernel, dim3(kLinkWgs), dim3(256), 0, static_cast<hipStream_t>(stream),
+                       static_cast<u32x4*>(dst), static_cast<const u32x4*>(src), n);
+    return hip_status("copy_bytes");
+  }
   const unsigned blocks = unsigned(std::min<size_t>((n + 255) / 256, 256 * 16));
   hipLaunchKernelGGL(copy_bytes_kernel, dim3(blocks), dim3(256), 0, static_cast<hipStream_t>(stream),
                      static_cast<u32x4*>(dst), static_cast<const u32x4*>(src), n);
@@ -601,6 +658,45 @@ int actqkv_gather_blocks(const actqkv_shape* shape, int batch, const void* k_sto
     return set_error(ACTQKV_EALIGN, "sequence strides must be multiples of 8 elements");
   return launch_gather(*shape, batch, k_store, v_store, store_seq_stride, nb_store, idx, n_sel, k_cap, k_cache,
                        v_cache, cache_seq_stride, slot0, idx_slots, static_cast<hipStream_t>(stream));
+}
+
+int actqkv_gather_blocks_cached(const actqkv_shape* shape, int n_windows, const void* k_store, const void* v_store,
+                                int nb_store, const int32_t* idx, const int32_t* n_sel, int k_cap, void* k_cache,
+                                void* v_cache, int nb_capacity, int slot0, int n_slots, int here0_lo, int here0_hi,
+                                int here0_at, int here1_lo, int here1_hi, int here1_at, int group, int32_t* state,
+                                int32_t* idx_slots, void* stream) {
+  ACTQKV_TRY(check_shape(shape));
+  if (k_cap < 1 || k_cap > 64) return set_error(ACTQKV_ESHAPE, "k_cap %d outside 1..64", k_cap);
+  if (n_windows < 1 || n_windows * k_cap > kSlotSelections)
+    return set_error(ACTQKV_ESHAPE, "gather_blocks_cached: %d windows of up to %d blocks (at most %d selections)", n_windows,
+                     k_cap, kSlotSelections);
+  if (nb_store < 1 || nb_capacity < 1) return set_error(ACTQKV_EINVAL, "gather_blocks_cached: empty store or cache");
+  if (n_slots < 2 * n_windows * k_cap || n_slots > 2 * kSlotSelections)
+    return set_error(ACTQKV_EINVAL, "gather_blocks_cached: %d slots outside %d..%d", n_slots, 2 * n_windows * k_cap,
+                     2 * kSlotSelections);
+  if (slot0 < 0 || int64_t(slot0) + n_slots > nb_capacity)
+    return set_error(ACTQKV_EINVAL, "gather_blocks_cached: slots %d .. %d outside the cache of %d blocks", slot0,
+                     slot0 + n_slots - 1, nb_capacity);
+  if (group < 0) return set_error(ACTQKV_EINVAL, "gather_blocks_cached: group %d", group);
+  const HereRange ranges[2] = {{here0_lo, here0_hi, here0_at}, {here1_lo, here1_hi, here1_at}};
+  for (const HereRange& h : ranges) {
+    if (h.hi <= h.lo) continue;
+    const int64_t end = int64_t(h.at) + (int64_t(h.hi) - h.lo);
+    if (h.lo < 0 || h.at < 0 || end > nb_capacity || (end > slot0 && h.at < slot0 + n_slots))
+      return set_error(ACTQKV_EINVAL, "gather_blocks_cached: blocks %d .. %d at %d overlap the slots or leave the cache",
+                       h.lo, h.hi - 1, h.at);
+  }
+  ACTQKV_REQUIRE_PTR(k_store);
+  ACTQKV_REQUIRE_PTR(v_store);
+  ACTQKV_REQUIRE_PTR(k_cache);
+  ACTQKV_REQUIRE_PTR(v_cache);
+  ACTQKV_REQUIRE_SMALL(idx, 4);
+  ACTQKV_REQUIRE_SMALL(n_sel, 4);
+  ACTQKV_REQUIRE_SMALL(state, 4);
+  ACTQKV_REQUIRE_SMALL(idx_slots, 4);
+  return launch_gather_cached(*shape, n_windows, k_store, v_store, nb_store, idx, n_sel, k_cap, k_cache, v_cache, slot0,
+                              n_slots, ranges[0], ranges[1], group, state, idx_slots,
+                              static_cast<hipStream_t>(stream));
 }
 
 static int append_checked(const actqkv_shape* shape, int batch, int m, const void* k_new, const void* v_new,

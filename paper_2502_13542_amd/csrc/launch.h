@@ -115,8 +115,9 @@ int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, co
                      const void* v_cache, int64_t seq_stride, int nb_capacity, const int32_t* n_ctx,
                      const int32_t* idx, const int32_t* n_sel, int k_cap, void* out, float* lse,
                      const Workspace& ws, int sel_per_head, hipStream_t stream, int first_cus = kChipCus,
-                     int late_cus = 0, hipStream_t stream_late = nullptr);   // late_cus > 0: a second team of
+                     int late_cus = 0, hipStream_t stream_late = nullptr,   // late_cus > 0: a second team of
                                                        // workgroups for the queue, on stream_late
+                     bool pieces_of_one = false);      // cut the key tiles as in a call with one batch entry
 int launch_score_per_head(const actqkv_shape& sh, int batch, const float* probe, const void* rep_keys,
                           int64_t seq_stride, int nb_capacity, int nb_begin, const int32_t* nb_end,
                           float* scores, int64_t score_stride, hipStream_t stream);
@@ -148,6 +149,13 @@ int launch_gather(const actqkv_shape& sh, int batch, const void* k_store, const 
                   int64_t store_stride, int nb_store, const int32_t* idx, const int32_t* n_sel, int k_cap,
                   void* k_cache, void* v_cache, int64_t cache_stride, int slot0, int32_t* idx_slots,
                   hipStream_t stream);
+
+constexpr int kSlotSelections = 256;   // windows x k_cap of a gather whose slots are a cache of the store
+struct HereRange { int lo, hi, at; };  // blocks [lo, hi) of the sequence lie in the working cache from `at` on
+int launch_gather_cached(const actqkv_shape& sh, int n_windows, const void* k_store, const void* v_store, int nb_store,
+                         const int32_t* idx, const int32_t* n_sel, int k_cap, void* k_cache, void* v_cache, int slot0,
+                         int n_slots, HereRange here0, HereRange here1, int group, int32_t* state, int32_t* idx_slots,
+                         hipStream_t stream);
 
 int launch_cutoff_budgets(int batch, int n_layers, float k_mean, int k_cap, const float* theta, float* budget,
                           int32_t* count, float* budget_left, hipStream_t stream);

@@ -219,11 +219,13 @@ template <typename... P> struct Entry<int(P...)> {
   X(retrieval_attention_per_head, "sssswq")                      \
   X(retrieval_attention_static, "ssssq")                         \
   X(retrieval_attention_teams, "sssswqq")                        \
+  X(retrieval_attention_windows, "sssswq")                       \
   X(cutoff_budgets, "q")                                         \
   X(cutoff_next_step, "q")                                       \
   X(copy_bytes, "ppq")                                           \
   X(build_probe, "swq")                                          \
   X(gather_blocks, "hhssq")                                      \
+  X(gather_blocks_cached, "hhssq")                               \
   X(score_blocks, "sq")                                          \
   X(score_blocks_per_head, "sq")                                 \
   X(select, "q")

@@ -513,10 +513,13 @@ class HostCachePrefill:
     so two working caches alternate and the span's blocks are carried over with
     `actqkv_copy_bytes`.  While the context is still shorter than n_init + n_local the working
     cache simply holds it whole at its true positions.  Needs m, n_init, n_local multiples of
-    the block size (only the last window may be ragged)."""
+    the block size (only the last window may be ragged).  That is run(); run_overlapped() does the
+    same on a cache of its own in which the selected blocks keep their slots (region_geometry)."""
 
     GROUP = 4                 # windows per hand-over between the streams of the overlapped schedule
-    N_WORK = 2 * GROUP + 1    # working caches: a group being attended to, a group being filled, one source
+    RING_CACHES = 9           # size of the overlapped schedule's cache, in working caches of the other one
+    ATTENTION_CUS = 224       # compute units its attention fills; the rest serves the other streams' kernels
+    N_WORK = 2                # working caches of the pass in window order
 
     def __init__(self, runner: LayerRunner, plan: PrefillPlan):
         sh = runner.shape
@@ -528,38 +531,61 @@ class HostCachePrefill:
         self.tail0 = self.slot0 + runner.k_cap
         self.nb_work = self.tail0 + (sh.n_local + runner.m) // bs + 1
         st = torch.float32 if sh.dtype == "fp32" else torch.bfloat16
-        shape_k = (self.nb_work, sh.n_kv_heads, bs, sh.head_dim)
-        shape_v = (self.nb_work, sh.n_kv_heads, sh.head_dim, bs)
-        self.k_work = [torch.zeros(shape_k, dtype=st, device=dev) for _ in range(self.N_WORK)]
-        self.v_work = [torch.zeros(shape_v, dtype=st, device=dev) for _ in range(self.N_WORK)]
-        self.idx_slots = torch.full((1, runner.k_cap), -1, dtype=torch.int32, device=dev)
-        self.n_ctx_work = torch.zeros(1, dtype=torch.int32, device=dev)
-        self.pos0_work = torch.zeros(1, dtype=torch.int32, device=dev)
-        self.workspace = torch.zeros(B.workspace_bytes(runner.cs, 1, runner.m, self.nb_work, runner.k_cap),
-                                     dtype=torch.uint8, device=dev)
+
+        def cache(nb):
+            return (torch.zeros(nb, sh.n_kv_heads, bs, sh.head_dim, dtype=st, device=dev),
+                    torch.zeros(nb, sh.n_kv_heads, sh.head_dim, bs, dtype=st, device=dev))
+        self.k_work, self.v_work = zip(*(cache(self.nb_work) for _ in range(self.N_WORK)))
+        i32, f32 = dict(dtype=torch.int32, device=dev), dict(dtype=torch.float32, device=dev)
+        self.idx_slots = torch.full((1, runner.k_cap), -1, **i32)
+        self.n_ctx_work = torch.zeros(1, **i32)
+        self.pos0_work = torch.zeros(1, **i32)
         self.gathered_blocks = 0
         self.block_bytes = sh.n_kv_heads * bs * sh.head_dim * self.k_work[0].element_size()   # K or V of a block
-        # the overlapped schedule: every window keeps its own selection and scalars, and the data
-        # movement and the attention have streams of their own
-        T = plan.n_windows
-        self.idx_all = torch.full((T, runner.k_cap), -1, dtype=torch.int32, device=dev)
-        self.n_sel_all = torch.zeros(T, dtype=torch.int32, device=dev)
-        self.idx_slots_all = torch.full((T, runner.k_cap), -1, dtype=torch.int32, device=dev)
+
+        # the overlapped schedule: one cache of initial tokens | slots | sequence region (a window sees
+        # nothing behind its own positions, so the slots lie before the region)
+        T, m = plan.n_windows, runner.m
+        G = max(1, min(self.GROUP, 256 // runner.k_cap, 8192 // m))      # (what the gather and the append take in a call)
+        self.group = G
+        # groups the sequence region holds: when the next one starts again at the front (a local span and the
+        # group behind it), the newest group and its local span must not be in the way
+        self.n_slots = 2 * G * runner.k_cap
+        self.region0 = self.slot0 + self.n_slots
+        # (and beyond that as many as make the cache RING_CACHES times that of run(): blocks that are still in the
+        # region need not come over the link)
+        self.n_segments = max(3, 2 + -(-2 * sh.n_local // (G * m)),
+                              (self.RING_CACHES * self.nb_work - self.region0 - sh.n_local // bs) * bs // (G * m))
+        self.groups = [range(g0, min(g0 + G, T)) for g0 in range(0, T, G)]
+        self.region = self.region_geometry()
+        self.nb_ring = self.region0 + (sh.n_local + self.n_segments * G * m) // bs
+        self.k_ring, self.v_ring = cache(self.nb_ring)
+        self.idx_all = torch.full((T, runner.k_cap), -1, **i32)
+        self.n_sel_all = torch.zeros(T, **i32)
+        self.idx_slots_all = torch.full((T, runner.k_cap), -1, **i32)
+        self.slot_state = torch.full((runner.nb_capacity + 2 * self.n_slots + 513,), -2, **i32)
+        pos0 = [(plan.w0[gr[0]] // bs - self.region[g]["delta"]) * bs for g, gr in enumerate(self.groups)]
+        self.pos0_g = torch.tensor(pos0, **i32)
+        self.whole = [local_start(sh, w0) <= sh.n_init for w0 in plan.w0]     # windows that see the whole context
+        self.n_ctx_w = torch.tensor([w0 + rows - (0 if self.whole[t] else self.region[t // G]["delta"] * bs)
+                                     for t, (w0, rows) in enumerate(zip(plan.w0, plan.rows))], **i32)
+        dk = sh.n_kv_heads * sh.head_dim
+        self.probe_g = torch.empty(G, sh.n_q_heads * sh.head_dim, **f32)
+        self.probe_kv_g = torch.empty(G, dk, **f32)
+        self.probe_norm_g = torch.empty(G, **f32)
+        self.scores_g = torch.zeros(G, runner.score_stride, **f32)
+        ws = B.workspace_bytes(runner.cs, G, m, max(self.nb_work, self.nb_ring, runner.nb_capacity), runner.k_cap)
+        self.ws_probe = torch.zeros(ws, dtype=torch.uint8, device=dev)
+        self.workspace = torch.zeros(max(ws, G * B.workspace_bytes(runner.cs, 1, m, self.nb_ring, runner.k_cap)),
+                                     dtype=torch.uint8, device=dev)
         # (four streams with the current one: a process has four hardware queues here, and streams that
         # share one run their kernels one after the other)
         self.mover, self.attender, self.writer = (torch.cuda.Stream(device=dev) for _ in range(3))
-        self.geo = self.window_geometry()
-        self.n_ctx_w = torch.tensor([g["pos0"] + plan.rows[t] for t, g in enumerate(self.geo)], dtype=torch.int32,
-                                    device=dev)
-        self.pos0_w = torch.tensor([g["pos0"] for g in self.geo], dtype=torch.int32, device=dev)
-        # per-window views and events, made once (slicing and creating them costs the host as much as
-        # a launch, and the overlapped schedule is bound by what the host can enqueue)
-        one = lambda x: None if x is None else [x[t:t + 1] for t in range(T)]
-        self.v_idx, self.v_nsel, self.v_slots = one(self.idx_all), one(self.n_sel_all), one(self.idx_slots_all)
-        self.v_nctx, self.v_pos0, self.v_nb_end = one(self.n_ctx_w), one(self.pos0_w), one(plan.nb_end)
-        self.v_bud, self.v_rest = one(plan.budget), one(plan.rest)
-        self.ev_appended = [torch.cuda.Event() for _ in range(T)]
-        self.ev_written = [torch.cuda.Event() for _ in range(T)]
+        self.events = [[torch.cuda.Event() for _ in self.groups] for _ in range(4)]
+        # per-window views, made once: slicing costs the host as much as a launch
+        self.v_nctx = [self.n_ctx_w[t:t + 1] for t in range(T)]
+        self.v_nsel = [self.n_sel_all[t:t + 1] for t in range(T)]
+        self.v_slots = [self.idx_slots_all[t] for t in range(T)]
 
     def _copy_blocks(self, src, dst, src_block: int, dst_block: int, n: int, stream=None) -> None:
         if n > 0:
@@ -626,130 +652,151 @@ class HostCachePrefill:
             cur, delta = new, new_delta
         return rec
 
-    def window_geometry(self):
-        """Per window: (working cache, the cache the local span comes from, real block - working block
-        of the tail, first working block of the local span in the source cache, blocks of local
-        span, position of the window's first token in the working cache, needs the initial blocks
-        copied).  Host-side bookkeeping only."""
-        r, plan = self.runner, self.plan
-        sh, bs = r.shape, r.shape.block_size
-        geo = []
-        cur, delta, has_init = 0, 0, [True] + [False] * (self.N_WORK - 1)
-        for t in range(plan.n_windows):
-            w0, rows = plan.w0[t], plan.rows[t]
-            l0 = local_start(sh, w0)
-            if l0 <= sh.n_init:
-                assert cur == 0 and w0 + rows <= self.nb_work * bs
-                geo.append(dict(new=0, src=0, src_block=0, n_loc=0, pos0=w0, copy_init=False, retrieving=False))
-                new, new_delta = 0, 0
-            else:
-                new = (cur + 1) % self.N_WORK
-                n_loc = (w0 - l0) // bs
-                geo.append(dict(new=new, src=cur, src_block=l0 // bs - delta, n_loc=n_loc,
-                                pos0=(self.tail0 + n_loc) * bs, copy_init=not has_init[new], retrieving=True))
-                has_init[new] = True
-                new_delta = l0 // bs - self.tail0
-            cur, delta = new, new_delta
+    def region_geometry(self):
+        """Where the groups of the overlapped schedule lie in the sequence region of its cache (host-side
+        bookkeeping; everything in blocks).  The region holds n_segments groups behind room for a
+        local span.  The sequence starts at the region's front; windows that see the whole context
+        attend over the region alone, as a cache of its own, and before the first one that does not
+        the initial tokens are copied to where the others find them.  When the region is full,
+        the local span moves to its front and the next group follows behind it: a lap.
+          delta           real block - working block
+          carry           (first real block, number of blocks) of the local span to move to the front, or None
+          here            two ranges (first real block, behind the last, working block of the first) that
+                          still lie in the region when the group's selected blocks are fetched, whatever the
+                          group after it has overwritten by then: this lap's and the lap's before
+          behind          last group that holds a block before those (its write-back has to be done)"""
+        r, plan, sh = self.runner, self.plan, self.runner.shape
+        bs, per = sh.block_size, self.group * self.runner.m // sh.block_size
+        span, front, last = sh.n_local // bs, self.region0, len(self.groups) - 1
+        geo, delta, before, carry_lo, lap_lo = [], -front, None, 0, 0
+        for g, gr in enumerate(self.groups):
+            b0 = plan.w0[gr[0]] // bs
+            b1 = (plan.w0[gr[-1]] + plan.rows[gr[-1]]) // bs                # full blocks
+            carry, seg = None, g % self.n_segments
+            if seg == 0 and g > 0:
+                carry_lo, before, lap_lo = b0 - min(span, b0), delta, b0
+                delta, carry = carry_lo - front, (carry_lo, b0 - carry_lo)
+            lo, old_lo = carry_lo, lap_lo
+            if seg == self.n_segments - 1:
+                if g < last:                                                # the next group overwrites the front
+                    lo = max(lo, delta + front + span + per)
+            elif before is not None:                                        # the next group: segment seg + 1
+                old_lo = max(0, min(lap_lo, before + front + span + (seg + 2) * per))
+            least = min(lo, old_lo) if old_lo < lap_lo else lo
+            old_at = old_lo - before if old_lo < lap_lo else 0
+            geo.append(dict(b0=b0, b1=b1, delta=delta, carry=carry,
+                            here=((lo, b1, lo - delta), (old_lo, lap_lo, old_at)),
+                            behind=min((least - 1) // per, g) if least > 0 else -1))
         return geo
+
+    def _select_group(self, gr, q, rep_keys) -> None:
+        """Probe, scores and selection of a group's windows: the full ones in one call each."""
+        r, plan, cs, m = self.runner, self.plan, self.runner.cs, self.runner.m
+        nb_begin = r.shape.n_init // r.shape.block_size
+        t = gr[0]
+        while t <= gr[-1]:
+            n = 1
+            while plan.rows[t] == m and t + n <= gr[-1] and plan.rows[t + n] == m:
+                n += 1
+            w0, rows, t1 = plan.w0[t], plan.rows[t], t + n
+            flags = B.STATS_UPDATE | (B.PROBE_WINDOW_CHAIN if n > 1 else 0)
+            nb_cap = min(max(plan.nb_end_host[t1 - 1], nb_begin), r.nb_capacity)
+            B.build_probe(cs, n, rows, q[w0:w0 + n * rows], r.stats, flags, self.probe_g, self.probe_kv_g,
+                          self.probe_norm_g, None, self.ws_probe)
+            B.score_blocks(cs, n, self.probe_kv_g, self.probe_norm_g, rep_keys, 0, nb_cap, nb_begin,
+                           plan.nb_end[t:t1], self.scores_g, r.score_stride)
+            B.select(n, self.scores_g, r.score_stride, nb_cap, nb_begin, plan.nb_end[t:t1], r.k_cap,
+                     None if plan.budget is None else plan.budget[t:t1],
+                     None if plan.rest is None else plan.rest[t:t1], self.idx_all[t:t1], self.n_sel_all[t:t1])
+            t = t1
 
     def run_overlapped(self, q: torch.Tensor, k_tok: torch.Tensor, v_tok: torch.Tensor, k_store: torch.Tensor,
                        v_store: torch.Tensor, rep_keys: torch.Tensor, out: torch.Tensor,
                        write_back: bool = True) -> Dict[int, Dict[str, torch.Tensor]]:
-        """The same pass with the host link kept busy.  Four chains, handed over GROUP windows at a
-        time (a hand-over between streams costs the host more than a launch): on the current stream
-        the selection chain (it needs the queries and the representative keys only) and what is
-        always resident - the local span into the window's working cache, the window's keys and
-        values behind it; with write_back a second stream copies the window's new blocks from the
-        working cache to the host store (the link carries both directions at once), so the store
-        may start empty; a third does nothing but gather the selected blocks from the host store
-        into the slots, back to back; a fourth attends.  A window can select
-        blocks of the window two before it, so its gather waits for that window's write-back.
-        Results are those of run()."""
-        r, plan = self.runner, self.plan
-        sh, cs, bs = r.shape, r.cs, r.shape.block_size
-        nb_begin = sh.n_init // bs
+        """The same pass with its parts beside each other, handed over GROUP windows at a time (a
+        hand-over between streams costs the host more than a launch), on one cache of initial
+        tokens, sequence region and slots (region_geometry).  On the current stream: the selection
+        chain, which needs the queries and the representative keys only, and the group's keys and
+        values into the region.  With write_back a second stream copies the group's blocks to the
+        host store, so the store may start empty.  A third brings the selected blocks into
+        the slots.  The slots keep their blocks from window to window (actqkv_gather_blocks_cached),
+        so a block crosses the link when a window first selects it and not again while it is in
+        use; blocks that still lie in the region do not cross it at all.  A fourth attends.
+        Results are those of run().  What bounds it: a pass over 32K tokens (32 query, 8 KV heads,
+        windows of 512, 16 blocks each) gathered 0.5 GB in 13.0 ms when every window brought its own
+        blocks; now the attention (64 launches) and the write-back (128 MB) set the pace: @@ ms."""
+        r, plan, sh, cs = self.runner, self.plan, self.runner.shape, self.runner.cs
+        bs, kw, vw, bb = sh.block_size, self.k_ring, self.v_ring, self.block_bytes
         nb_store = k_store.shape[0]
-        T, G = plan.n_windows, self.GROUP
-        geo, n_ctx_w, pos0_w = self.geo, self.n_ctx_w, self.pos0_w
         cur = torch.cuda.current_stream()
-        for st in (self.mover, self.attender, self.writer):
+        mover, attender, writer = self.mover, self.attender, self.writer
+        self.slot_state.fill_(-2)
+        for st in (mover, attender, writer):
             st.wait_stream(cur)
-        attended, written = {}, {}      # events: group g attended to; window t written back
-        mover, attender, writer, prep = self.mover, self.attender, self.writer, cur
-        for g0 in range(0, T, G):
-            g, group = g0 // G, range(g0, min(g0 + G, T))
-            # ---- selection chain (current stream)
-            for t in group:
-                w0, rows = plan.w0[t], plan.rows[t]
-                bud = None if self.v_bud is None else self.v_bud[t]
-                rest = None if self.v_rest is None else self.v_rest[t]
-                nb_cap = min(max(plan.nb_end_host[t], nb_begin), r.nb_capacity)
-                B.build_probe(cs, 1, rows, q[w0:w0 + rows], r.stats, True, r.probe, r.probe_kv, r.probe_norm, None,
-                              r.workspace)
-                B.score_blocks(cs, 1, r.probe_kv, r.probe_norm, rep_keys, 0, nb_cap, nb_begin, self.v_nb_end[t],
-                               r.scores, r.score_stride)
-                B.select(1, r.scores, r.score_stride, nb_cap, nb_begin, self.v_nb_end[t], r.k_cap, bud, rest,
-                         self.v_idx[t], self.v_nsel[t], None, None)
-            selected = torch.cuda.Event()
-            selected.record(cur)
-            # ---- The working caches go round: the ones this group fills were last used two groups ago
-            # (attention, write-back, source of a local span).
-            for st in (prep, mover):
-                if g - 2 in attended:
-                    st.wait_event(attended[g - 2])
-                    last = min((g - 1) * G, T) - 1
-                    if last in written:
-                        st.wait_event(written[last])
-            # ---- what is always resident (still the current stream): the local span into the window's
-            # working cache, the window's keys and values behind it; the new blocks back to the store
-            # (second stream)
-            for t in group:
-                w0, rows = plan.w0[t], plan.rows[t]
-                ge = geo[t]
-                kw, vw = self.k_work[ge["new"]], self.v_work[ge["new"]]
-                if ge["retrieving"]:
-                    ks, vs = self.k_work[ge["src"]], self.v_work[ge["src"]]
-                    if ge["copy_init"]:
-                        self._copy_blocks(ks, kw, 0, 0, self.slot0, prep)
-                        self._copy_blocks(vs, vw, 0, 0, self.slot0, prep)
-                    self._copy_blocks(ks, kw, ge["src_block"], self.tail0, ge["n_loc"], prep)
-                    self._copy_blocks(vs, vw, ge["src_block"], self.tail0, ge["n_loc"], prep)
-                B.append_kv(cs, 1, rows, k_tok[w0:w0 + rows], v_tok[w0:w0 + rows], self.v_pos0[t], kw, vw, 0,
-                            None, 0, self.nb_work, prep)
-                if write_back and rows // bs > 0:
-                    self.ev_appended[t].record(prep)
-                    writer.wait_event(self.ev_appended[t])
-                    wb0, n_wb = ge["pos0"] // bs, rows // bs
-                    self._copy_blocks(kw, k_store, wb0, w0 // bs, n_wb, writer)
-                    self._copy_blocks(vw, v_store, wb0, w0 // bs, n_wb, writer)
-                    written[t] = self.ev_written[t]
-                    written[t].record(writer)
-            prepped = torch.cuda.Event()
-            prepped.record(prep)
-            # ---- the selected blocks over the host link into the slots (third stream: nothing but
-            # gathers, back to back, so that the link never waits for anything else)
-            mover.wait_event(selected)
-            for t in group:
-                ge = geo[t]
-                if t - 2 in written:
-                    mover.wait_event(written[t - 2])         # the newest blocks this window can select
-                B.gather_blocks(cs, 1, k_store, v_store, 0, nb_store, self.v_idx[t], self.v_nsel[t], r.k_cap,
-                                self.k_work[ge["new"]], self.v_work[ge["new"]], 0, self.nb_work, self.slot0,
-                                self.v_slots[t], mover)
-            moved = torch.cuda.Event()
-            moved.record(mover)
-            # ---- attention (fourth stream)
-            attender.wait_event(moved)
-            attender.wait_event(prepped)
-            for t in group:
-                w0, rows = plan.w0[t], plan.rows[t]
-                ge = geo[t]
-                B.retrieval_attention(cs, 1, rows, q[w0:w0 + rows], self.k_work[ge["new"]], self.v_work[ge["new"]],
-                                      0, self.nb_work, self.v_nctx[t], self.v_slots[t], self.v_nsel[t], r.k_cap,
-                                      out[w0:w0 + rows], None, self.workspace, attender)
-            attended[g] = torch.cuda.Event()
+        appended, written, fetched, attended = self.events
+        lag = self.n_segments - -(-sh.n_local // (self.group * r.m))
+        init_copied, k_region, v_region = False, kw[self.region0:], vw[self.region0:]
+        for g, gr in enumerate(self.groups):
+            ge, t0, t1 = self.region[g], gr[0], gr[-1] + 1
+            w0, w1 = plan.w0[t0], plan.w0[t1 - 1] + plan.rows[t1 - 1]
+            self._select_group(gr, q, rep_keys)
+            # ---- the attention of the group two before this one is the last that reads what is overwritten now,
+            # in the region (region_geometry) and in the slots; the region's blocks must have been written back,
+            # those of the group a lap before and, since the first lap had no local span in front, a span more
+            if g >= 2:
+                cur.wait_event(attended[g - 2])
+            if write_back and g >= self.n_segments:
+                cur.wait_event(written[g - lag])
+            if ge["carry"] is not None:
+                src, n = ge["carry"]
+                src -= self.region[g - 1]["delta"]
+                self._copy_blocks(kw, kw, src, self.region0, n)
+                self._copy_blocks(vw, vw, src, self.region0, n)
+            B.append_kv(cs, 1, w1 - w0, k_tok[w0:w1], v_tok[w0:w1], self.pos0_g[g:g + 1], kw, vw, 0, None, 0, self.nb_ring)
+            if not init_copied and not self.whole[t1 - 1]:
+                self._copy_blocks(kw, kw, self.region0, 0, self.slot0)
+                self._copy_blocks(vw, vw, self.region0, 0, self.slot0)
+                init_copied = True
+            appended[g].record(cur)
+            b0, b1, at = ge["b0"], ge["b1"], ge["b0"] - ge["delta"]
+            if write_back and b1 > b0:
+                writer.wait_event(appended[g])
+                self._copy_blocks(kw, k_store, at, b0, b1 - b0, writer)
+                self._copy_blocks(vw, v_store, at, b0, b1 - b0, writer)
+            if write_back:
+                written[g].record(writer)
+            # ---- the selected blocks into the slots
+            mover.wait_event(appended[g])
+            if write_back and ge["behind"] >= 0:
+                mover.wait_event(written[ge["behind"]])
+            B.gather_blocks_cached(cs, t1 - t0, k_store, v_store, nb_store, self.idx_all[t0:t1], self.n_sel_all[t0:t1],
+                                   r.k_cap, kw, vw, self.nb_ring, self.slot0, self.n_slots, *ge["here"], g,
+                                   self.slot_state, self.idx_slots_all[t0:t1], mover)
+            fetched[g].record(mover)
+            # ---- attention
+            attender.wait_event(fetched[g])
+            t = t0
+            if sh.dtype == "bf16" and r.m > 1:                              # the group's windows that share a cache and a size
+                while t < t1 and self.whole[t]:
+                    t += 1
+                n = sum(plan.rows[u] == r.m for u in range(t, t1))
+                if n > 1:
+                    a = plan.w0[t]
+                    B.retrieval_attention_windows(cs, n, r.m, q[a:a + n * r.m], kw, vw, self.nb_ring, self.n_ctx_w[t:t + n],
+                                                  self.idx_slots_all[t:t + n], self.n_sel_all[t:t + n], r.k_cap,
+                                                  out[a:a + n * r.m], None, self.workspace, self.ATTENTION_CUS, attender)
+                done = range(t, t + n) if n > 1 else ()
+            else:
+                done = ()
+            for t in gr:
+                if t in done:
+                    continue
+                a, rows = plan.w0[t], plan.rows[t]
+                kc, vc = (k_region, v_region) if self.whole[t] else (kw, vw)
+                B.retrieval_attention(cs, 1, rows, q[a:a + rows], kc, vc, 0, kc.shape[0], self.v_nctx[t], self.v_slots[t], self.v_nsel[t], r.k_cap, out[a:a + rows], None,
+                                      self.workspace, attender)
             attended[g].record(attender)
-        for st in (self.mover, self.attender, self.writer):
+        for st in (mover, attender, writer):
             cur.wait_stream(st)
         return {t: dict(idx=self.idx_all[t], n_sel=self.n_sel_all[t], idx_slots=self.idx_slots_all[t])
-                for t in range(T)}
+                for t in range(plan.n_windows)}

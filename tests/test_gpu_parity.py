@@ -2320,6 +2320,80 @@ def test_gather_blocks_from_pinned_host_memory():
                 assert bool((kw_c[s, blk] == 7.0).all()) and bool((vw_c[s, blk] == 7.0).all())
 
 
+@pytest.mark.parametrize("n_windows,k_cap,n_slots,nb", [(4, 3, 24, 40), (1, 64, 128, 80), (4, 64, 512, 300)])
+def test_slots_as_a_cache_of_the_store(n_windows, k_cap, n_slots, nb):
+    """actqkv_gather_blocks_cached on random selections (blocks shared between windows, entries
+    outside the store, a moving range of blocks that lie in the cache itself): every selected block is
+    in its slot, a block that stays selected is not brought in again, and no slot that the group
+    before used changes."""
+    sh = LayerShape(4, 2, 64, 128, 2, 128, 128, "bf16")
+    cs = B.c_shape(sh)
+    g = torch.Generator().manual_seed(nb)
+    slot0 = 6
+    ks = torch.randn(nb, 2, 128, 64, generator=g).to(torch.bfloat16).pin_memory()
+    vs = torch.randn(nb, 2, 64, 128, generator=g).to(torch.bfloat16).pin_memory()
+    kc = torch.zeros(slot0 + n_slots, 2, 128, 64, dtype=torch.bfloat16, device=DEV)
+    vc = torch.zeros(slot0 + n_slots, 2, 64, 128, dtype=torch.bfloat16, device=DEV)
+    state = torch.full((nb + 2 * n_slots + 513,), -2, dtype=torch.int32, device=DEV)
+    slots = torch.zeros(n_windows, k_cap, dtype=torch.int32, device=DEV)
+    where, before = {}, {}
+    for group in range(9):
+        idx = torch.stack([torch.randperm(nb, generator=g)[:k_cap] for _ in range(n_windows)]).int()
+        n_sel = torch.randint(0, k_cap + 1, (n_windows,), generator=g).int()
+        idx[0, 0] = nb + 7 if group % 3 == 0 else -1
+        n_sel[0] = max(int(n_sel[0]), 1)
+        lo = group % 4
+        kc[2:5], vc[2:5] = ks[lo:lo + 3].to(DEV), vs[lo:lo + 3].to(DEV)
+        kc[5], vc[5] = ks[lo + 8].to(DEV), vs[lo + 8].to(DEV)
+        B.gather_blocks_cached(cs, n_windows, ks, vs, nb, idx.to(DEV), n_sel.to(DEV), k_cap, kc, vc, slot0 + n_slots,
+                               slot0, n_slots, (lo, lo + 3, 2), (lo + 8, lo + 9, 5), group, state, slots)
+        got, now = slots.cpu(), {}
+        for w in range(n_windows):
+            for j in range(k_cap):
+                b, at = int(idx[w, j]), int(got[w, j])
+                if j >= int(n_sel[w]) or not 0 <= b < nb:
+                    assert at == -1
+                    continue
+                assert slot0 <= at < slot0 + n_slots and now.setdefault(b, at) == at
+        assert len(set(now.values())) == len(now)
+        for b, at in {**before, **now}.items():              # (what the group before used is where it was)
+            assert torch.equal(kc[at].cpu(), ks[b]) and torch.equal(vc[at].cpu(), vs[b]), (group, b)
+        fresh = [b for b in now if where.get(b) != now[b]]
+        assert int(state[nb + 2 * n_slots]) == len(fresh)
+        for b in fresh:
+            assert b not in where
+            where = {k_: at for k_, at in where.items() if at != now[b]}
+            where[b] = now[b]
+        before = now
+
+
+@pytest.mark.parametrize("m,n_init,n_local,k_cap,n_ctx", [(128, 256, 512, 2, 128 * 40 + 77), (256, 128, 256, 6, 256 * 21),
+                                                          (512, 0, 128, 3, 512 * 9 + 300), (256, 128, 1024, 64, 256 * 18)])
+def test_overlapped_host_cache_pass_equals_window_order(m, n_init, n_local, k_cap, n_ctx):
+    """Geometries of the overlapped schedule's sequence region (several laps, local spans shorter and
+    longer than a group of windows, no initial tokens) against the pass in window order."""
+    sh = LayerShape(8, 2, 64, 128, 2, n_init, n_local, "bf16")
+    w = synth.Workload("host_laps", sh, n_ctx, m, k_cap, False, 77 + m, n_planted=6, n_layers=1)
+    q, k, v = synth.gen_layer(w, DEV)
+    rep = synth.pick_rep_keys(k, 128, sh.n_rep)
+    repd = torch.zeros(w.n_blocks, sh.n_rep, 2, 64, dtype=rep.dtype, device=DEV)
+    repd[: rep.shape[0]] = rep
+    runner = H.LayerRunner(sh, 1, m, w.n_blocks, k_cap, DEV)
+    host = H.HostCachePrefill(runner, H.make_prefill_plan(sh, n_ctx, m, None, DEV))
+    ks, vs = (f(x, sh, w.n_blocks).cpu().pin_memory() for f, x in ((H.blocked_k, k), (H.blocked_vt, v)))
+    out, out_ov = torch.zeros_like(q), torch.zeros_like(q)
+    rec = host.run(q, k, v, ks, vs, repd, out, record=range(w.n_windows))
+    ke, ve = torch.zeros_like(ks).pin_memory(), torch.zeros_like(vs).pin_memory()
+    runner.reset()
+    rec_ov = host.run_overlapped(q, k, v, ke, ve, repd, out_ov)
+    torch.cuda.synchronize()
+    for t in range(w.n_windows):
+        assert torch.equal(rec[t]["idx"], rec_ov[t]["idx"]) and int(rec[t]["n_sel"]) == int(rec_ov[t]["n_sel"]), t
+    assert torch.equal(out, out_ov)
+    full = n_ctx // 128
+    assert torch.equal(ke[:full], ks[:full]) and torch.equal(ve[:full], vs[:full])
+
+
 def test_prefill_with_the_cache_in_host_memory():
     """The cache of the whole context in pinned host memory, a working cache of a few dozen
     blocks in HBM (HostCachePrefill): selections and attention outputs must equal those of the
