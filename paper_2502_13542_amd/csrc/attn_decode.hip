@@ -403,9 +403,12 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
   SelectIo io = sp.io;
   io.write = wg == 0 && hk == 0;
   if (selector) {
-    select_wave(sc_mem, s, n_elig, sp.nb_begin, p.k_cap, sp.entropy_topk, io, sel_lds.sel, &sel_lds.count);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    if (lane == 0) __hip_atomic_store(&sel_ready, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_s_setprio(3);       // the others only issue loads meanwhile, and wait for this
+    select_wave(sc_mem, s, n_elig, sp.nb_begin, p.k_cap, sp.entropy_topk, io, sel_lds.sel, &sel_lds.count, [&] {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      if (lane == 0) __hip_atomic_store(&sel_ready, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    });
+    __builtin_amdgcn_s_setprio(0);
   }
   // the scores of the sequence for the workgroup-wide selection: the load of the first 512 does not wait for anything
   const ScoreRow<kDcThreads> sc{sc_mem, (!by_wave && int(threadIdx.x) < p.nb_capacity - sp.nb_begin) ? sc_mem[threadIdx.x] : 0.f};
@@ -721,8 +724,11 @@ bool decode_fused_supported(const actqkv_shape& sh) {
   return decode_mfma_supported(sh, 1) && sh.dtype == ACTQKV_BF16 && sh.head_dim == kDcD;
 }
 
-// Launch shape: workgroups of 8 wavefronts; about 2048 wavefronts in total (two per SIMD,
-// each with a whole item's loads in flight) unless the item list is shorter than that.
+// Launch shape: workgroups of 8 wavefronts, one per compute unit (two wavefronts per SIMD, each with
+// a whole item's loads in flight, 256 KB per compute unit, several times what the memory's latency
+// asks for), and never more workgroups than compute units while a pair has one: 192 pairs (16
+// blocks each) take 62 us on 192 compute units and 80 us as 384 workgroups, whose second round
+// leaves half the chip idle; 96 pairs (10 blocks) 29 us as 192, 40 us as 288.  A workgroup per 8 items at most.
 // One workgroup per (sequence, KV head) writes the output itself; with more, the one that
 // finishes last merges the partials.
 static int decode_items_max(const actqkv_shape& sh, int k_cap) {
@@ -733,7 +739,7 @@ static int decode_items_max(const actqkv_shape& sh, int k_cap) {
 }
 int decode_mfma_workgroups(const actqkv_shape& sh, int batch, int k_cap) {
   const int pairs = batch * sh.n_kv_heads;
-  const int want = (2048 + pairs * kDcMaxWaves - 1) / (pairs * kDcMaxWaves);
+  const int want = kChipCus / pairs;
   const int most = (decode_items_max(sh, k_cap) + kDcMaxWaves - 1) / kDcMaxWaves;
   return want < 1 ? 1 : (want > most ? most : want);
 }

@@ -68,9 +68,9 @@ __device__ __forceinline__ void store_elem(float* p, float v) { *p = v; }
 __device__ __forceinline__ void store_elem(uint16_t* p, float v) { *p = uint16_t(f32_to_bf16_bits(v)); }
 
 // ---- wave / workgroup reductions ------------------------------------------
-// The value of lane (lane ^ J), J a power of two, without the LDS crossbar where the data-parallel
-// primitives reach: quad permutes for 1 and 2, two masked row shifts for 4 and 8 (banks of four
-// lanes take the value from J lanes above or below), a swizzle for 16; only 32 is a general shuffle.
+// The value of lane (lane ^ J), J a power of two, by the data-parallel primitives, without the LDS
+// crossbar: quad permutes for 1 and 2, two masked row shifts for 4 and 8 (banks of four lanes take
+// the value from J lanes above or below), for 16 and 32 an exchange of half the rows of two copies.
 template <int J>
 __device__ __forceinline__ uint32_t lane_xor32(uint32_t v) {
   if constexpr (J == 1) {
@@ -83,34 +83,45 @@ __device__ __forceinline__ uint32_t lane_xor32(uint32_t v) {
   } else if constexpr (J == 8) {
     const uint32_t t = __builtin_amdgcn_update_dpp(v, v, 0x108, 0xF, 0x3, false);   // row_shl:8 into banks 0, 1
     return __builtin_amdgcn_update_dpp(t, v, 0x118, 0xF, 0xC, false);               // row_shr:8 into banks 2, 3
-  } else if constexpr (J == 16) {
-    return uint32_t(__builtin_amdgcn_ds_swizzle(int(v), (16 << 10) | 0x1F));  // bit mode: xor 16 inside 32 lanes
   } else {
-    static_assert(J == 32, "lane distance");
-    return uint32_t(__shfl_xor(int(v), 32, 64));
+    static_assert(J == 16 || J == 32, "lane distance");
+    // element 0: the lower rows of both copies (rows 0, 2 for 16), element 1: the upper ones
+    const auto r = J == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false)
+                           : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (threadIdx.x & J) ? r[0] : r[1];
+  }
+}
+// v combined with the value of lane (lane ^ J) by a commutative operation: for 16 and 32 the two
+// copies after the exchange are the two operands, whichever lane asks.
+template <int J, typename Op>
+__device__ __forceinline__ float lane_pair(float v, Op op) {
+  if constexpr (J == 16 || J == 32) {
+    const uint32_t u = __float_as_uint(v);
+    const auto r = J == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
+                           : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  } else {
+    return op(v, __uint_as_float(lane_xor32<J>(__float_as_uint(v))));
   }
 }
 template <int J>
 __device__ __forceinline__ float lane_xor_f32(float v) {
   return __uint_as_float(lane_xor32<J>(__float_as_uint(v)));
 }
+template <typename Op>
+__device__ __forceinline__ float wave_all(float v, Op op) {
+  v = lane_pair<32>(v, op);
+  v = lane_pair<16>(v, op);
+  v = lane_pair<8>(v, op);
+  v = lane_pair<4>(v, op);
+  v = lane_pair<2>(v, op);
+  return lane_pair<1>(v, op);
+}
 __device__ __forceinline__ float wave_sum(float v) {
-  v += lane_xor_f32<32>(v);
-  v += lane_xor_f32<16>(v);
-  v += lane_xor_f32<8>(v);
-  v += lane_xor_f32<4>(v);
-  v += lane_xor_f32<2>(v);
-  v += lane_xor_f32<1>(v);
-  return v;
+  return wave_all(v, [](float a, float b) { return a + b; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-  v = fmaxf(v, lane_xor_f32<32>(v));
-  v = fmaxf(v, lane_xor_f32<16>(v));
-  v = fmaxf(v, lane_xor_f32<8>(v));
-  v = fmaxf(v, lane_xor_f32<4>(v));
-  v = fmaxf(v, lane_xor_f32<2>(v));
-  v = fmaxf(v, lane_xor_f32<1>(v));
-  return v;
+  return wave_all(v, [](float a, float b) { return fmaxf(a, b); });
 }
 // Sum over the workgroup; every thread gets the result.  `red` holds >= 32 floats of LDS.
 __device__ __forceinline__ float block_sum(float v, float* red) {

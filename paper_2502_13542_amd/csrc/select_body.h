@@ -95,34 +95,47 @@ struct SelectIo {
   const int32_t* count_in = nullptr;
 };
 
-// Eq. (12), the budget update that follows it, and E^l (Alg. 1); called by one thread.
-__device__ __forceinline__ int cutoff_count(float theta, int s, int n, int k_cap, const SelectIo& io) {
-  float b_l;
+// What Eq. (12) needs of the cut-off state, requested before anything else.
+struct CutoffIn {
+  float b_kv, rest;
+  int count;
+  __device__ __forceinline__ CutoffIn(int s, const SelectIo& io)
+      : b_kv(io.budget_in != nullptr ? io.budget_in[s] : 0.f), rest(io.budget_in != nullptr ? io.theta_rest_sum[s] : 0.f),
+        count(io.count_in != nullptr ? io.count_in[s] : 0) {}
+};
+// Eq. (12), the budget update that follows it, and E^l (Alg. 1).
+struct Cutoff {
+  float theta, b_l, after;
   int e;
-  if (io.density_only) {
-    if (io.write && io.theta) io.theta[s] = theta;
-    return 0;
+  __device__ __forceinline__ Cutoff(float theta_, int n, int k_cap, const CutoffIn& in, const SelectIo& io)
+      : theta(theta_), b_l(0.f), after(0.f), e(0) {
+    if (io.density_only) return;
+    if (io.count_in != nullptr) {
+      e = min(max(in.count, 0), min(k_cap, n));
+      b_l = float(e);
+    } else if (io.budget_in != nullptr) {
+      const float den = theta + in.rest;
+      b_l = den > 0.f ? theta / den * in.b_kv : in.b_kv;
+      e = min(int(fminf(fmaxf(floorf(b_l + 0.5f), 1.f), float(k_cap))), n);
+      after = in.b_kv - b_l;
+    } else {
+      e = min(k_cap, n);
+      b_l = float(e);
+    }
   }
-  if (io.count_in != nullptr) {
-    e = min(max(io.count_in[s], 0), min(k_cap, n));
-    b_l = float(e);
-  } else if (io.budget_in != nullptr) {
-    float b_kv = io.budget_in[s], rest = io.theta_rest_sum[s];
-    float den = theta + rest;
-    b_l = den > 0.f ? theta / den * b_kv : b_kv;
-    float r = fminf(fmaxf(floorf(b_l + 0.5f), 1.f), float(k_cap));
-    e = min(int(r), n);
-    if (io.write && io.budget_after != nullptr) io.budget_after[s] = b_kv - b_l;
-  } else {
-    e = min(k_cap, n);
-    b_l = float(e);
-  }
-  if (io.write) {
-    io.n_sel[s] = e;
+  // called by one thread
+  __device__ __forceinline__ void store(int s, const SelectIo& io) const {
     if (io.theta) io.theta[s] = theta;
+    if (io.density_only) return;
+    io.n_sel[s] = e;
     if (io.budget) io.budget[s] = b_l;
+    if (io.count_in == nullptr && io.budget_in != nullptr && io.budget_after != nullptr) io.budget_after[s] = after;
   }
-  return e;
+};
+__device__ __forceinline__ int cutoff_count(float theta, int s, int n, int k_cap, const CutoffIn& in, const SelectIo& io) {
+  const Cutoff c(theta, n, k_cap, in, io);
+  if (io.write) c.store(s, io);
+  return c.e;
 }
 
 // LDS of one selecting workgroup; after select_body, count and sel[0 .. k_cap) hold the result.
@@ -143,6 +156,7 @@ __device__ __forceinline__ void select_body(const Scores& sc, int s, int n, int 
   constexpr int kWaves = kThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int32_t* my_idx = io.idx + size_t(s) * k_cap;
+  const CutoffIn state(s, io);
   if (n == 0) {
     if (io.density_only) {
       if (tid == 0 && io.write && io.theta) io.theta[s] = 0.f;
@@ -178,7 +192,7 @@ __device__ __forceinline__ void select_body(const Scores& sc, int s, int n, int 
     }
     z = block_sum(z, lds.red);
     t = block_sum(t, lds.red);
-    if (tid == 0) lds.count = cutoff_count(fmaxf(logf(z) + mx - t / z, 0.f), s, n, k_cap, io);
+    if (tid == 0) lds.count = cutoff_count(fmaxf(logf(z) + mx - t / z, 0.f), s, n, k_cap, state, io);
     if (io.density_only) {
       __syncthreads();
       return;
@@ -219,7 +233,7 @@ __device__ __forceinline__ void select_body(const Scores& sc, int s, int n, int 
       z += __shfl_xor(z, o, 64);
       t += __shfl_xor(t, o, 64);
     }
-    if (lane == 0) lds.count = cutoff_count(fmaxf(logf(z) + mx - t / z, 0.f), s, n, k_cap, io);
+    if (lane == 0) lds.count = cutoff_count(fmaxf(logf(z) + mx - t / z, 0.f), s, n, k_cap, state, io);
   }
   __syncthreads();
   if (io.density_only) return;        // (density over the best blocks: the tournament had to run first)
@@ -232,114 +246,134 @@ __device__ __forceinline__ void select_body(const Scores& sc, int s, int n, int 
 }
 
 // ---- the same step by ONE wavefront, for rows of at most 64 * kSelWavePerLane scores ----------
-// For the decode attention that selects for itself: a selection spread over a workgroup couples
-// every wavefront to the slowest one at each of its barriers, and there the slowest one is stuck
-// handing 32 KB of load requests to a memory pipeline that is full.  One wavefront that has issued
-// nothing else needs no barrier at all: its lanes keep the scores in registers (lane l: blocks l,
-// l + 64, ...), the density is two passes over them with lane exchanges, and the E best blocks come
-// out one per round (the largest key of all lanes, which is unique, is taken and struck out).
-// Same keys, same ties, same Eq. (11), Eq. (12) as select_body; the sums run in another order.
+// A selection spread over a workgroup couples its wavefronts at a dozen barriers; one wavefront needs
+// none.  In the decode attention that selects for itself the others are stuck handing 32 KB of
+// load requests each to a full memory pipeline meanwhile; as a launch of its own the step is nothing
+// but latency.  Lane l keeps the scores of blocks l, l + 64, ... in registers.  The density is two
+// passes over them.  The E best blocks come out one per round: every lane knows its best score and
+// where it is, the best of all lanes is a 32-bit maximum over the lanes (exchanges without LDS), a
+// ballot names its lane (several lanes with equal scores: the lowest block of them, the rare
+// path), and only that lane looks for its next best.  About 250 cycles a round at 1024 scores, 120
+// at 64; with 64-bit keys and a search through all registers in every lane it was 1000.
+// Same ties, same Eq. (11), Eq. (12) as select_body; the sums run in another order.
 constexpr int kSelWavePerLane = 16;
 
-__device__ __forceinline__ unsigned long long wave_max64(unsigned long long v) {
-  v = umax64(v, lane_xor64<32>(v));
-  v = umax64(v, lane_xor64<16>(v));
-  v = umax64(v, lane_xor64<8>(v));
-  v = umax64(v, lane_xor64<4>(v));
-  v = umax64(v, lane_xor64<2>(v));
-  v = umax64(v, lane_xor64<1>(v));
-  return v;
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  v = max(uint32_t(r[0]), uint32_t(r[1]));
+  r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = max(uint32_t(r[0]), uint32_t(r[1]));
+  v = max(v, lane_xor32<8>(v));
+  v = max(v, lane_xor32<4>(v));
+  v = max(v, lane_xor32<2>(v));
+  v = max(v, lane_xor32<1>(v));
+  return __builtin_amdgcn_readfirstlane(v);
 }
 
 // Called by all 64 lanes of one wavefront; sel[0 .. k_cap) and *count (LDS or any memory the
-// wavefront may write) receive the result, and the global outputs are written if io.write.
-// kPerLane: scores a lane holds (n <= 64 * kPerLane).
-template <int kPerLane>
-__device__ __forceinline__ void select_wave_n(const float* __restrict__ sc_mem, int s, int n, int nb_begin, int k_cap,
-                                              int entropy_topk, const SelectIo& io, int* sel, int* count) {
-  constexpr int kSelWavePerLane = kPerLane;
+// wavefront may write) receive the result, then publish() is called, then the global outputs are
+// written if io.write.
+template <typename Publish>
+__device__ __forceinline__ void select_wave(const float* __restrict__ sc_mem, int s, int n, int nb_begin, int k_cap,
+                                            int entropy_topk, const SelectIo& io, int* sel, int* count,
+                                            Publish&& publish) {
+  constexpr int kPer = kSelWavePerLane, kPart = 4;               // registers are walked a part at a time, as far as n goes
   const int lane = threadIdx.x & 63;
-  int32_t* my_idx = io.idx + size_t(s) * k_cap;
-  float v[kSelWavePerLane];
+  const int per = __builtin_amdgcn_readfirstlane((n + 63) >> 6);
+  float v[kPer];
 #pragma unroll
-  for (int i = 0; i < kSelWavePerLane; ++i) {                    // every load before the first use
+  for (int i = 0; i < kPer; ++i) {                               // every load before the first use
     const int b = lane + 64 * i;
     v[i] = b < n ? sc_mem[b] : -INFINITY;
   }
-  if (n == 0) {
-    if (lane < k_cap) {
-      sel[lane] = -1;
-      if (io.write) my_idx[lane] = -1;
-    }
-    if (lane == 0) {
-      *count = 0;
-      if (io.write) {
-        io.n_sel[s] = 0;
-        if (io.theta) io.theta[s] = 0.f;
-        if (io.budget) io.budget[s] = 0.f;
-        if (io.budget_in != nullptr && io.budget_after != nullptr) io.budget_after[s] = io.budget_in[s];
-      }
-    }
-    return;
-  }
-  int e_count = 0;
-  if (!entropy_topk) {
+  const CutoffIn in(s, io);
+  float theta = 0.f;
+  if (!entropy_topk && n > 0) {
     float mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < kSelWavePerLane; ++i) mx = fmaxf(mx, v[i]);
+    for (int i = 0; i < kPer; ++i) mx = fmaxf(mx, v[i]);
     mx = wave_max(mx);
     float z = 0.f, t = 0.f;
 #pragma unroll
-    for (int i = 0; i < kSelWavePerLane; ++i) {
-      if (lane + 64 * i < n) {
-        const float e = __expf(v[i] - mx);
-        z += e;
-        t += e * v[i];
+    for (int c = 0; c < kPer; c += kPart)
+      if (c < per) {
+#pragma unroll
+        for (int i = c; i < c + kPart; ++i)
+          if (lane + 64 * i < n) {
+            const float e = __expf(v[i] - mx);
+            z += e;
+            t += e * v[i];
+          }
       }
-    }
     z = wave_sum(z);
     t = wave_sum(t);
-    if (lane == 0) e_count = cutoff_count(fmaxf(logf(z) + mx - t / z, 0.f), s, n, k_cap, io);
-    e_count = __shfl(e_count, 0, 64);
+    theta = fmaxf(logf(z) + mx - t / z, 0.f);
   }
-  unsigned long long key[kSelWavePerLane];
+  Cutoff cut(theta, n, k_cap, in, io);
+  if (n == 0) cut.b_l = 0.f, cut.after = in.b_kv;                // nothing to select, nothing spent
+  int mine = -1;                                                 // lane r: the r-th best block
+  uint32_t mine_key = 0u;
+  const int rounds = __builtin_amdgcn_readfirstlane(io.density_only && !entropy_topk ? 0 : entropy_topk ? min(k_cap, n) : cut.e);
+  if (rounds > 0) {
+    uint32_t key[kPer], best = 0u;                               // 0: no block (any more); best: the lane's largest,
+    int at = 0;                                                  // in register `at`
 #pragma unroll
-  for (int i = 0; i < kSelWavePerLane; ++i) {
-    const int b = lane + 64 * i;
-    key[i] = b < n ? select_key(v[i], nb_begin + b) : 0ull;
+    for (int i = 0; i < kPer; ++i)
+      key[i] = lane + 64 * i < n ? max(uint32_t(select_key(v[i], 0) >> 32), 1u) : 0u;
+    auto find_best = [&] {
+      best = 0u;
+      at = 0;
+#pragma unroll
+      for (int c = 0; c < kPer; c += kPart)
+        if (c < per) {
+#pragma unroll
+          for (int i = c; i < c + kPart; ++i) {
+            at = key[i] > best ? i : at;
+            best = max(best, key[i]);
+          }
+        }
+    };
+    find_best();
+    for (int r = 0; r < rounds; ++r) {
+      const uint32_t top = wave_max_u32(best);
+      const unsigned long long who = __ballot(best == top);
+      int w = __builtin_ctzll(who);
+      if ((who & (who - 1ull)) != 0ull) {
+        const uint32_t low = wave_max_u32(best == top ? ~uint32_t(lane + 64 * at) : 0u);
+        w = int(~low) & 63;
+      }
+      const int b = w + 64 * __builtin_amdgcn_readlane(at, w);
+      if (lane == r) {
+        mine = nb_begin + b;
+        mine_key = top;
+      }
+      if (lane == w) {
+#pragma unroll
+        for (int c = 0; c < kPer; c += kPart)
+          if (c < per) {
+#pragma unroll
+            for (int i = c; i < c + kPart; ++i) key[i] = i == at ? 0u : key[i];
+          }
+        find_best();
+      }
+    }
   }
-  const int rounds = entropy_topk ? min(k_cap, n) : e_count;
-  unsigned long long mine = 0ull;                                // lane r: the r-th best key
-  for (int r = 0; r < rounds; ++r) {
-    unsigned long long best = 0ull;
-#pragma unroll
-    for (int i = 0; i < kSelWavePerLane; ++i) best = umax64(best, key[i]);
-    best = wave_max64(best);
-    if (lane == r) mine = best;
-#pragma unroll
-    for (int i = 0; i < kSelWavePerLane; ++i) key[i] = key[i] == best ? 0ull : key[i];
-  }
-  if (entropy_topk) {
-    const bool in = lane < rounds;
-    const float sv = in ? key_score(mine) : 0.f;
-    const float mx = __shfl(sv, 0, 64);
-    const float e = in ? __expf(sv - mx) : 0.f;
+  if (entropy_topk && n > 0) {
+    const bool have = lane < rounds;
+    const float sv = have ? key_score(static_cast<unsigned long long>(mine_key) << 32) : 0.f;
+    const float mx = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(sv)));
+    const float e = have ? __expf(sv - mx) : 0.f;
     const float z = wave_sum(e), t = wave_sum(e * sv);
-    if (lane == 0) e_count = cutoff_count(fmaxf(logf(z) + mx - t / z, 0.f), s, n, k_cap, io);
-    e_count = __shfl(e_count, 0, 64);
+    cut = Cutoff(fmaxf(logf(z) + mx - t / z, 0.f), n, k_cap, in, io);
   }
-  if (lane < k_cap) {
-    const int b = lane < e_count ? int(0xffffffffu - uint32_t(mine)) : -1;
-    sel[lane] = b;
-    if (io.write) my_idx[lane] = b;
+  if (lane >= cut.e) mine = -1;
+  if (lane < k_cap) sel[lane] = mine;
+  if (lane == 0) *count = cut.e;
+  publish();
+  if (io.write) {
+    if (lane < k_cap && !io.density_only) io.idx[size_t(s) * k_cap + lane] = mine;
+    if (lane == 0) cut.store(s, io);
   }
-  if (lane == 0) *count = e_count;
-}
-__device__ __forceinline__ void select_wave(const float* __restrict__ sc_mem, int s, int n, int nb_begin, int k_cap,
-                                            int entropy_topk, const SelectIo& io, int* sel, int* count) {
-  // (one instantiation: with a second one for rows of at most 512 scores, which halves the work of
-  // a round, the decode step was 2 % slower - measured three times in alternation on one box)
-  select_wave_n<kSelWavePerLane>(sc_mem, s, n, nb_begin, k_cap, entropy_topk, io, sel, count);
 }
 
 // The scores of one sequence as select_body reads them: the first kThreads stay in a register
