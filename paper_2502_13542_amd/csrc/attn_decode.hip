@@ -32,6 +32,7 @@ namespace actqkv {
 
 constexpr int kDcMaxWaves = 8;   // 512 threads: the register budget stays at 256 per lane
 constexpr int kDcThreads = kDcMaxWaves * 64;
+constexpr int kDcMaxSpread = 16; // workgroups per (sequence, KV head)
 
 struct DcParams {
   const void* q;            // storage type T of the kernel, as all tensors
@@ -175,10 +176,10 @@ __device__ __forceinline__ bool dc_item_span(const TileList& tl, int it, int& bl
   return r.hi > r.lo;
 }
 
-// Requests the item's keys AND values (nothing is computed before both are on their way).
+// Requests the item's keys and values.
 template <typename T, int D>
-__device__ __forceinline__ void dc_issue(DcItem<T, D>& r, const T* kc, const T* vc, int block, int part,
-                                         int hk, int n_kv_heads, int n, int kq) {
+__device__ __forceinline__ void dc_issue(DcItem<T, D>& r, const T* kc, const T* vc, int block, int part, int hk,
+                                         int n_kv_heads, int n, int kq) {
   typedef DcShape<T, D> S;
   const size_t tile = (size_t(block) * n_kv_heads + hk) * size_t(kBlock) * D;
   const T* kbase = kc + tile + size_t(part) * S::kKeys * D + S::k_lane(n, kq);
@@ -189,28 +190,24 @@ __device__ __forceinline__ void dc_issue(DcItem<T, D>& r, const T* kc, const T* 
   for (int l = 0; l < S::kV; ++l) r.va[l] = *reinterpret_cast<const u32x4*>(vbase + S::v_off(l));
 }
 
-// Scores, mask, online softmax and O^T += V^T P^T for one item.
+// Mask and online softmax of an item's scores (keys kpos0 .., visible [lo, hi)): sc becomes the probabilities.
 template <typename T, int D>
-__device__ __forceinline__ void dc_consume(const DcItem<T, D>& r, const u32x4 (&qb)[DcShape<T, D>::kQ], DcAcc<D>& a,
+__device__ __forceinline__ void dc_softmax(DcAcc<D>& a, f32x4 (&sc)[DcShape<T, D>::kSubs], int kpos0, int lo, int hi,
                                            float scale_log2e, int kq) {
   typedef DcShape<T, D> S;
-  f32x4 sc[S::kSubs];
-#pragma unroll
-  for (int j = 0; j < S::kSubs; ++j) sc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  S::scores(r.ka, qb, sc);
-  // mask and online softmax
+  const auto larger = [](float x, float y) { return fmaxf(x, y); };
+  const auto sum = [](float x, float y) { return x + y; };
   float mx = -INFINITY;
 #pragma unroll
   for (int j = 0; j < S::kSubs; ++j)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int kp = r.kpos0 + S::key_of(j, i, kq);
-      const float v = (kp >= r.lo && kp < r.hi) ? sc[j][i] : -INFINITY;
+      const int kp = kpos0 + S::key_of(j, i, kq);
+      const float v = (kp >= lo && kp < hi) ? sc[j][i] : -INFINITY;
       sc[j][i] = v;
       mx = fmaxf(mx, v);
     }
-  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  mx = lane_pair<32>(lane_pair<16>(mx, larger), larger);
   const float m_new = fmaxf(a.m_run, mx * scale_log2e);   // finite: the item has a visible key
   const float alpha = __builtin_amdgcn_exp2f(a.m_run - m_new);
   a.m_run = m_new;
@@ -223,26 +220,57 @@ __device__ __forceinline__ void dc_consume(const DcItem<T, D>& r, const u32x4 (&
       sc[j][i] = pv;
       psum += pv;
     }
-  psum += __shfl_xor(psum, 16, 64);
-  psum += __shfl_xor(psum, 32, 64);
+  psum = lane_pair<32>(lane_pair<16>(psum, sum), sum);
   a.l_run = a.l_run * alpha + psum;
 #pragma unroll
   for (int dg = 0; dg < D / 16; ++dg) a.acc_o[dg] *= alpha;
-  S::values(r.va, sc, a.acc_o);
 }
 
-// Q^T as B operand: lane (n, kq) holds its quarter's channels of head n (zero for n >= G)
+// Walks the items it, it + stride, ... < n_items of a tile list: keys and values of an item are requested
+// together, before anything is computed.  (Refilling the key registers with the next item's as soon
+// as the scores have used them gains 1-2 % where a wavefront has six items and loses 4 % where it has one.)
+// before(): called once, behind the first item's requests.
+template <typename T, int D, typename Before>
+__device__ __forceinline__ void dc_walk(const TileList& tl, int it, int stride, int n_items, const T* kc, const T* vc,
+                                        const u32x4 (&qb)[DcShape<T, D>::kQ], DcAcc<D>& a, float scale_log2e, int hk,
+                                        int n_kv_heads, int n, int kq, Before&& before) {
+  typedef DcShape<T, D> S;
+  DcItem<T, D> r;
+  auto request_next = [&] {                                  // (wave-uniform) the next item the query sees something of
+    int block, part;
+    for (; it < n_items; it += stride)
+      if (dc_item_span<T, D>(tl, it, block, part, r)) {
+        it += stride;
+        dc_issue(r, kc, vc, block, part, hk, n_kv_heads, n, kq);
+        return true;
+      }
+    return false;
+  };
+  bool more = request_next();
+  __builtin_amdgcn_sched_barrier(0);
+  before();
+  __builtin_amdgcn_sched_barrier(0);
+  while (more) {
+    f32x4 sc[S::kSubs];
+#pragma unroll
+    for (int j = 0; j < S::kSubs; ++j) sc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    S::scores(r.ka, qb, sc);
+    dc_softmax<T, D>(a, sc, r.kpos0, r.lo, r.hi, scale_log2e, kq);
+    S::values(r.va, sc, a.acc_o);
+    more = request_next();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Q^T as B operand: lane (n, kq) holds its quarter's channels of head n.  Columns n >= G repeat the last
+// head; nobody reads what they give.  (Zeros there would make the first key loads wait for the query.)
 template <typename T, int D>
 __device__ __forceinline__ void dc_load_q(const DcParams& p, int s, int hk, int group, int n, int kq,
                                           u32x4 (&qb)[DcShape<T, D>::kQ]) {
   typedef DcShape<T, D> S;
   const T* qp = static_cast<const T*>(p.q) + (size_t(s) * p.n_q_heads + hk * group + min(n, group - 1)) * D + S::q_lane(kq);
 #pragma unroll
-  for (int ks = 0; ks < S::kQ; ++ks) {
-    u32x4 v = *reinterpret_cast<const u32x4*>(qp + ks * S::kQStep);
-    if (n >= group) v = u32x4{0u, 0u, 0u, 0u};
-    qb[ks] = v;
-  }
+  for (int ks = 0; ks < S::kQ; ++ks) qb[ks] = *reinterpret_cast<const u32x4*>(qp + ks * S::kQStep);
 }
 
 // The wavefronts of a workgroup merge their (max, sum, O) through LDS.  If one workgroup covers
@@ -297,7 +325,7 @@ __device__ __forceinline__ void dc_finish(const DcParams& p, const DcAcc<D>& a, 
   // ---- the workgroup that finished last merges the partials, in workgroup order:
   //   out[head][:] = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w
   const size_t stride = size_t(group) * (D + 2);
-  constexpr int kB = 8;
+  constexpr int kB = kDcMaxSpread;
   for (int e = threadIdx.x; e < group * D; e += blockDim.x) {
     const int h = e / D, d = e - h * D;
     const uint32_t* src = pair_part + size_t(h) * (D + 2);
@@ -342,27 +370,24 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_kernel(DcParams p) {
   const int wg = blockIdx.x, hk = blockIdx.y, s = blockIdx.z;
   const int group = p.n_q_heads / p.n_kv_heads;
 
-  const int n_ctx = min(max(p.n_ctx[s], 1), p.nb_capacity * kBlock);
-  const WindowGeom g = window_geom(n_ctx, 1, p.n_init, p.n_local);
+  // (the block numbers are requested together with the scalars they are used with)
+  __shared__ int32_t sel[64];
   const size_t sel_row = p.sel_per_head ? size_t(s) * p.n_kv_heads + hk : size_t(s);
-  const TileList tl = make_tile_list(g, n_ctx - 1, p.idx + sel_row * p.k_cap, p.n_sel[sel_row], p.k_cap,
-                                     p.nb_capacity);
-  const int n_items = tl.count() * (kBlock / DcShape<T, D>::kKeys);
+  const int n_ctx_raw = p.n_ctx[s], n_sel_raw = p.n_sel[sel_row];
+  if (int(threadIdx.x) < p.k_cap) sel[threadIdx.x] = p.idx[sel_row * p.k_cap + threadIdx.x];
   u32x4 qb[DcShape<T, D>::kQ];
   dc_load_q<T, D>(p, s, hk, group, n, kq, qb);
+  __syncthreads();
+  const int n_ctx = min(max(n_ctx_raw, 1), p.nb_capacity * kBlock);
+  const WindowGeom g = window_geom(n_ctx, 1, p.n_init, p.n_local);
+  const TileList tl = make_tile_list(g, n_ctx - 1, sel, n_sel_raw, p.k_cap, p.nb_capacity);
+  const int n_items = tl.count() * (kBlock / DcShape<T, D>::kKeys);
   DcAcc<D> a;
   a.clear();
   const T* kc = static_cast<const T*>(p.k_cache) + size_t(s) * p.seq_stride;
   const T* vc = static_cast<const T*>(p.v_cache) + size_t(s) * p.seq_stride;
 
-  for (int it = wg * n_waves + wave; it < n_items; it += p.n_wg * n_waves) {
-    DcItem<T, D> r;
-    int block, part;
-    if (!dc_item_span(tl, it, block, part, r)) continue;   // wave-uniform
-    dc_issue(r, kc, vc, block, part, hk, p.n_kv_heads, n, kq);
-    __builtin_amdgcn_sched_barrier(0);   // all key and value loads are in flight before the first MFMA
-    dc_consume(r, qb, a, p.scale_log2e, kq);
-  }
+  dc_walk<T, D>(tl, wave * p.n_wg + wg, p.n_wg * n_waves, n_items, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq, [] {});
   dc_finish<T, D>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 }
 
@@ -424,40 +449,29 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
   const uint16_t* kc = static_cast<const uint16_t*>(p.k_cache) + size_t(s) * p.seq_stride;
   const uint16_t* vc = static_cast<const uint16_t*>(p.v_cache) + size_t(s) * p.seq_stride;
 
-  // this wavefront's first item, if it is one that does not depend on the selection
-  const int it0 = wg * n_waves + wave, stride = p.n_wg * n_waves;
-  DcItem<uint16_t, kDcD> r0;
-  int block0, part0;
-  const bool have0 = it0 < n_fixed && dc_item_span(fixed, it0, block0, part0, r0);
-  if (have0) dc_issue(r0, kc, vc, block0, part0, hk, p.n_kv_heads, n, kq);
-  __builtin_amdgcn_sched_barrier(0);
-
-  if (!by_wave) select_body<kDcThreads>(sc, s, n_elig, sp.nb_begin, p.k_cap, sp.entropy_topk, io, sel_lds);
-  __builtin_amdgcn_sched_barrier(0);
-  if (have0) dc_consume(r0, qb, a, p.scale_log2e, kq);
+  // The items that do not depend on the selection come first in the list.  Neighbouring items go to
+  // different workgroups; the wavefronts that select come last, short lists do not reach them.
+  const int it0 = wave * p.n_wg + wg;
+  const int stride = p.n_wg * n_waves;
+  dc_walk<uint16_t, kDcD>(fixed, it0, stride, n_fixed, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq, [&] {
+    if (!by_wave) select_body<kDcThreads>(sc, s, n_elig, sp.nb_begin, p.k_cap, sp.entropy_topk, io, sel_lds);
+  });
   if (by_wave) {
     // the selector has long finished as a rule; it always does, whatever the others do
     while (__hip_atomic_load(&sel_ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0) __builtin_amdgcn_s_sleep(1);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   }
 
-  // the rest of the list: what is left of the fixed items, then the selected blocks
+  // the selected blocks
   TileList chosen = fixed;
   chosen.n_init_tiles = 0;
   chosen.n_tail_tiles = 0;
   chosen.n_sel = min(max(sel_lds.count, 0), p.k_cap);
   chosen.idx = sel_lds.sel;
-  const int n_items = n_fixed + chosen.n_sel * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
-  for (int it = it0 < n_fixed ? it0 + stride : it0; it < n_items; it += stride) {
-    DcItem<uint16_t, kDcD> r;
-    int block, part;
-    const bool ok = it < n_fixed ? dc_item_span(fixed, it, block, part, r)
-                                 : dc_item_span(chosen, it - n_fixed, block, part, r);
-    if (!ok) continue;                   // wave-uniform
-    dc_issue(r, kc, vc, block, part, hk, p.n_kv_heads, n, kq);
-    __builtin_amdgcn_sched_barrier(0);
-    dc_consume(r, qb, a, p.scale_log2e, kq);
-  }
+  const int n_chosen = chosen.n_sel * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
+  const int done = it0 < n_fixed ? (n_fixed - it0 + stride - 1) / stride : 0;      // of this wavefront's turns
+  dc_walk<uint16_t, kDcD>(chosen, it0 + done * stride - n_fixed, stride, n_chosen, kc, vc, qb, a, p.scale_log2e, hk,
+                          p.n_kv_heads, n, kq, [] {});
   dc_finish<uint16_t, kDcD>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 }
 
@@ -649,14 +663,7 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   // the reads of the scores wait behind the items' 32 KB - loads return in order - and a
   // wavefront set aside for those reads still shares the compute unit's load queue with the
   // other seven: both orders were slower than this one.)
-  for (int it = it0; it < n_fixed; it += stride) {
-    DcItem<uint16_t, kDcD> r;
-    int block, part;
-    if (!dc_item_span(fixed, it, block, part, r)) continue;   // wave-uniform
-    dc_issue(r, kc, vc, block, part, hk, p.n_kv_heads, n, kq);
-    __builtin_amdgcn_sched_barrier(0);
-    dc_consume(r, qb, a, p.scale_log2e, kq);
-  }
+  dc_walk<uint16_t, kDcD>(fixed, it0, stride, n_fixed, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq, [] {});
 
   // ---- the sequence's scores: wait (bounded) until every workgroup has published its share
   if (tid == 0) {
@@ -694,17 +701,10 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   chosen.n_tail_tiles = 0;
   chosen.n_sel = min(max(sel_lds.count, 0), p.k_cap);
   chosen.idx = sel_lds.sel;
-  const int n_items = n_fixed + chosen.n_sel * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
-  int it = it0;
-  while (it < n_fixed) it += stride;
-  for (; it < n_items; it += stride) {
-    DcItem<uint16_t, kDcD> r;
-    int block, part;
-    if (!dc_item_span(chosen, it - n_fixed, block, part, r)) continue;   // wave-uniform
-    dc_issue(r, kc, vc, block, part, hk, p.n_kv_heads, n, kq);
-    __builtin_amdgcn_sched_barrier(0);
-    dc_consume(r, qb, a, p.scale_log2e, kq);
-  }
+  const int n_chosen = chosen.n_sel * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
+  const int done = it0 < n_fixed ? (n_fixed - it0 + stride - 1) / stride : 0;      // of this wavefront's turns
+  dc_walk<uint16_t, kDcD>(chosen, it0 + done * stride - n_fixed, stride, n_chosen, kc, vc, qb, a, p.scale_log2e, hk,
+                          p.n_kv_heads, n, kq, [] {});
   dc_finish<uint16_t, kDcD>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 
   // ---- the last workgroup of the sequence to get here (nobody polls any more) resets the counters
@@ -725,10 +725,12 @@ bool decode_fused_supported(const actqkv_shape& sh) {
 }
 
 // Launch shape: workgroups of 8 wavefronts, one per compute unit (two wavefronts per SIMD, each with
-// a whole item's loads in flight, 256 KB per compute unit, several times what the memory's latency
-// asks for), and never more workgroups than compute units while a pair has one: 192 pairs (16
-// blocks each) take 62 us on 192 compute units and 80 us as 384 workgroups, whose second round
-// leaves half the chip idle; 96 pairs (10 blocks) 29 us as 192, 40 us as 288.  A workgroup per 8 items at most.
+// a whole item's loads in flight), and never more workgroups than compute units while a pair has
+// one: 192 pairs (16 blocks each) take 62 us on 192 compute units and 80 us as 384 workgroups, whose
+// second round leaves half the chip idle.  Few pairs are spread as thin as that allows, a wavefront
+// or two of work per compute unit: one compute unit does not get more than 35-50 GB/s of scattered
+// 16 KB tiles, so 8 pairs with 10 blocks each take 20.1 us as 4 workgroups per pair, 12.4 us as 16, and
+// 14.8 us as 32 (the merge grows with their number).
 // One workgroup per (sequence, KV head) writes the output itself; with more, the one that
 // finishes last merges the partials.
 static int decode_items_max(const actqkv_shape& sh, int k_cap) {
@@ -739,9 +741,7 @@ static int decode_items_max(const actqkv_shape& sh, int k_cap) {
 }
 int decode_mfma_workgroups(const actqkv_shape& sh, int batch, int k_cap) {
   const int pairs = batch * sh.n_kv_heads;
-  const int want = kChipCus / pairs;
-  const int most = (decode_items_max(sh, k_cap) + kDcMaxWaves - 1) / kDcMaxWaves;
-  return want < 1 ? 1 : (want > most ? most : want);
+  return std::max(1, std::min({kChipCus / pairs, kDcMaxSpread, decode_items_max(sh, k_cap)}));
 }
 
 size_t decode_mfma_scratch_floats(const actqkv_shape& sh, int batch, int k_cap) {
