@@ -100,8 +100,6 @@ static int check_blocks(int nb_capacity, int nb_begin, int k_cap, bool use_k) {
   } while (0)
 
 bool prefill_mfma_supported(const actqkv_shape& sh, int m);
-int prefill_mfma_workgroups(const actqkv_shape& sh, int m);
-int prefill_mfma_qtiles(const actqkv_shape& sh, int m);
 int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, const void* q,
                                   const void* k_cache, const void* v_cache, int64_t seq_stride,
                                   int nb_capacity, const int32_t* n_ctx, const int32_t* idx,
@@ -110,26 +108,6 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
                                   float scale, int sel_per_head, int first_cus, int late_cus,
                                   hipStream_t stream, hipStream_t stream_late);
 
-// Enough key splits to give every compute unit it may fill a workgroup, never more than 8
-// per query tile; what does not divide evenly goes to the last query tiles of the window.
-PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
-  (void)k_cap;
-  PfSplits r{1, 0, 1};
-  if (!prefill_mfma_supported(sh, m)) return r;
-  const int n_qtiles = prefill_mfma_qtiles(sh, m);
-  const int pairs = batch * sh.n_kv_heads;                   // each has n_qtiles query tiles
-  int per_pair = cus / (pairs > 0 ? pairs : 1);              // workgroups one pair may have
-  if (per_pair < n_qtiles) per_pair = n_qtiles;
-  r.s_lo = per_pair / n_qtiles;
-  if (r.s_lo >= 8) {
-    r.s_lo = 8;
-    r.rem = 0;
-  } else {
-    r.rem = per_pair - r.s_lo * n_qtiles;
-  }
-  r.slots = r.s_lo * n_qtiles + r.rem;
-  return r;
-}
 bool prefill_f32_supported(const actqkv_shape& sh, int m);
 size_t prefill_f32_scratch_bytes(const actqkv_shape& sh, int batch, int m);
 size_t prefill_f32_scratch_most(const actqkv_shape& sh, int batch, int m);
@@ -162,7 +140,7 @@ size_t attention_scratch_bytes(const actqkv_shape& sh, int batch, int m, int k_c
   if (prefill_mfma_supported(sh, m)) {
     // partial results exist only where a query tile's key tiles are cut into pieces
     const PfSplits splits = prefill_splits(sh, batch, m, k_cap, cus);
-    if (splits.slots > prefill_mfma_qtiles(sh, m))
+    if (splits.slots > splits.n_qtiles)
       attn = size_t(batch) * sh.n_kv_heads * splits.slots * kPfPartialFloats * sizeof(float);
   }
   if (prefill_f32_supported(sh, m)) attn = prefill_f32_scratch_bytes(sh, batch, m);
@@ -184,11 +162,9 @@ size_t workspace_bytes(const actqkv_shape& sh, int batch, int m, int nb_capacity
 static size_t workspace_bytes_upto(const actqkv_shape& sh, int batch, int m, int nb_capacity, int k_cap) {
   size_t need = 0;
   if (prefill_f32_supported(sh, m)) need = kCounterBytes + align_up(prefill_f32_scratch_most(sh, batch, m), 256);
-  for (int b = 1; b <= batch; ++b) {
-    need = std::max(need, workspace_bytes(sh, b, 1, nb_capacity, k_cap));
-    for (int mm = 32; mm < m + 32; mm += 32)       // query tiles are multiples of 32 positions
-      need = std::max(need, workspace_bytes(sh, b, std::min(mm, m), nb_capacity, k_cap));
-  }
+  if (prefill_mfma_supported(sh, m)) need = kCounterBytes + prefill_partials_most(sh, batch, m);
+  for (int b = 1; b <= batch; ++b) need = std::max(need, workspace_bytes(sh, b, 1, nb_capacity, k_cap));
+  need = std::max(need, kCounterBytes + align_up(probe_call_floats(sh, batch, m) * sizeof(float), 256));
   return need;
 }
 

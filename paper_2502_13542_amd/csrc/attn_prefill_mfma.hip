@@ -28,6 +28,7 @@
 // undone for free because a lane's 8 consecutive accumulator registers then hold
 // 8 consecutive keys.
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "common.h"
@@ -37,7 +38,7 @@ namespace actqkv {
 
 constexpr int kPfThreads = 512;
 constexpr int kPfWaves = 8;
-constexpr int kPfRows = 32 * kPfWaves;               // query rows of a workgroup
+template <int KS> constexpr int kPfRows = 32 * kPfWaves / KS;   // query rows of a workgroup
 template <int D> constexpr int kPfTileBytes = kBlock * D * 2;           // one K or V^T tile of a (block, KV head)
 template <int D> constexpr int kPfLdsBytes = 2 * 2 * kPfTileBytes<D>;   // 2 stages x (K, V^T)
 constexpr int kMaxPfSplits = 8;
@@ -92,7 +93,7 @@ struct PfParams {
   int k_cap;
   uint16_t* out;
   float* lse;
-  uint64_t* part;          // [workgroup][split][wave][16 x 4 bf16 + (max, sum)][64 lanes]
+  uint64_t* part;          // [workgroup][split][wave][its 32-channel groups x 4 x 4 bf16 | (max, sum)][64 lanes]
   unsigned int* counters;  // one ticket counter per (sequence, query tile, KV head), zero between launches
   int m, n_q_heads, n_kv_heads, n_init, n_local;
   int s_lo, rem, slots, n_qtiles;   // pieces per query tile (PfSplits)
@@ -105,15 +106,15 @@ struct PfParams {
 };
 
 // Final normalisation and store of one lane's share of a query row:
-// acc_o[db][4j + r] is channel d = db*32 + 8j + 4*half + r.
-template <int D>
-__device__ __forceinline__ void store_rows(const PfParams& p, const f32x16 (&acc_o)[D / 32], float m_run,
+// acc_o[j][4i + r] is channel (db0 + j)*32 + 8i + 4*half + r.
+template <int D, int N>
+__device__ __forceinline__ void store_rows(const PfParams& p, const f32x16 (&acc_o)[N], int db0, float m_run,
                                            float l_tot, int s, int my_row, int head, int half) {
   const size_t grow = (size_t(s) * p.m + my_row) * p.n_q_heads + head;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  uint16_t* op = p.out + grow * D;
+  uint16_t* op = p.out + grow * D + db0 * 32;
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
+  for (int db = 0; db < N; ++db)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       u32x2 v;
@@ -121,20 +122,24 @@ __device__ __forceinline__ void store_rows(const PfParams& p, const f32x16 (&acc
       v.y = pack_bf16x2(acc_o[db][4 * j + 2] * inv, acc_o[db][4 * j + 3] * inv);
       *reinterpret_cast<u32x2*>(op + db * 32 + 8 * j + 4 * half) = v;
     }
-  if (p.lse != nullptr && half == 0)
+  if (p.lse != nullptr && half == 0 && db0 == 0)
     p.lse[(size_t(s) * p.n_q_heads + head) * p.m + my_row] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
 }
 
 // One work item: piece `slot` of the query tiles of (sequence s, KV head hk).
-template <int D, bool kInLoop>
+template <int D, int KS, bool kInLoop>
 __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* lds, int hk, int slot, int s) {
   constexpr int kDb = D / 32, kKs = D / 16;      // 32-channel groups of the output, 16-channel steps of a score
+  constexpr int kRows = kPfRows<KS>, kRowGroups = kPfWaves / KS;   // query rows, groups of 32 of them
+  constexpr int kNg = 4 / KS;                    // 32-key groups of a tile that are this wavefront's
   // (inside an item loop the thread index is made opaque, so that nothing derived from it is
   // hoisted out of the loop and kept in registers across the whole item)
   int tid = threadIdx.x;
   if (kInLoop) asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, half = lane >> 5;
+  const int rg = wave % kRowGroups, quarter = wave / kRowGroups;   // its rows, its share of the keys of every tile
+  const int kb0 = quarter * kNg;
   const int group = p.n_q_heads / p.n_kv_heads;
 
   // The slots of a (sequence, KV head) are the pieces of its query tiles, in order.
@@ -162,15 +167,15 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
   const int n_ctx = min(max(n_ctx_raw, p.m), p.nb_capacity * kBlock);
   const WindowGeom g = window_geom(n_ctx, p.m, p.n_init, p.n_local);
   // The query rows of a (sequence, KV head) are numbered position by position, the G heads of a
-  // position next to each other; a workgroup takes kPfRows consecutive ones, a wavefront 32.
+  // position next to each other; a workgroup takes kRows consecutive ones, a wavefront 32.
   const int row_end = p.m * group;
-  const int row_hi = (min((qtile + 1) * kPfRows, row_end) - 1) / group;
+  const int row_hi = (min((qtile + 1) * kRows, row_end) - 1) / group;
   const TileList tl = make_tile_list(g, g.w0 + row_hi, idx_lds, n_sel_raw, p.k_cap, p.nb_capacity);
   const int n_tiles = tl.count();
   const int per = (n_tiles + splits - 1) / splits;
   const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
 
-  const int frow0 = qtile * kPfRows + wave * 32;             // first query row of this wavefront
+  const int frow0 = qtile * kRows + rg * 32;                 // first query row of this wavefront
   const bool wave_ok = frow0 < row_end;
   const int wpos_lo = g.w0 + min(frow0, row_end - 1) / group;         // positions of its first and last row
   const int wpos_hi = g.w0 + min(frow0 + 31, row_end - 1) / group;
@@ -277,41 +282,50 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     const int kpos0 = block * kBlock;
     // the wavefront skips tiles none of its rows can see; it masks tiles that are
     // clipped or that reach past its first row's position
-    const bool visible = wave_ok && hi > lo && lo <= wpos_hi;
+    const int sub0 = kpos0 + kb0 * 32;             // first key of this wavefront's share
+    const bool visible = wave_ok && hi > max(lo, sub0) && max(lo, sub0) <= wpos_hi;
     const bool masked = lo > kpos0 || hi < kpos0 + kBlock || hi - 1 > wpos_lo;
     const char* ks_ = lds_b + stage * 2 * kTileBytes;
     const char* vs_ = ks_ + kTileBytes;
-    f32x16 acc_s[4];
+    f32x16 acc_s[kNg];
     if (visible) {
-      // ---- S^T = K Q^T : 4 groups of 32 keys
+      // ---- S^T = K Q^T : kNg groups of 32 keys
       const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      // the four key groups take turns, so that an MFMA never waits for the one just before it
-      // (a dependent 32x32x16 MFMA issues only about 90 cycles after its producer, an
-      // independent one after 32)
+      // the key groups take turns (a single one is summed in two halves), so that an MFMA does not
+      // wait for the one just before it (a dependent 32x32x16 MFMA issues only about 90 cycles
+      // after its producer, an independent one after 32)
       // (written in the order it should issue: a ring of 8 operands, each read 8 MFMAs ahead)
+      constexpr int kChains = kNg == 1 ? 2 : kNg;
       auto k_read = [&](int i) {
-        return *reinterpret_cast<const u32x4*>(ks_ + (a_off0 ^ (uint32_t(i >> 2) << 5)) + (i & 3) * 32 * kKRow);
+        return *reinterpret_cast<const u32x4*>(ks_ + (a_off0 ^ (uint32_t(i / kNg) << 5)) + (kb0 + i % kNg) * 32 * kKRow);
       };
-      constexpr int kScore = 4 * kKs;                  // MFMAs of the scores
-      u32x4 ring[8];
+      constexpr int kScore = kNg * kKs, kRing = kScore < 8 ? kScore : 8;      // MFMAs of the scores
+      u32x4 ring[kRing];
+      f32x16 acc[kChains];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) ring[i] = k_read(i);
+      for (int i = 0; i < kRing; ++i) ring[i] = k_read(i);
 #pragma unroll
       for (int i = 0; i < kScore; ++i) {
-        const int ks = i >> 2, kb = i & 3;
-        acc_s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ring[i & 7]), qreg[ks], ks == 0 ? zero16 : acc_s[kb], 0, 0, 0);
-        if (i + 8 < kScore) ring[i & 7] = k_read(i + 8);
+        const int c = i % kChains;
+        acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ring[i % kRing]), qreg[i / kNg], i < kChains ? zero16 : acc[c], 0, 0, 0);
+        if (i + kRing < kScore) ring[i % kRing] = k_read(i + kRing);
       }
       // issue order: 8 operand reads ahead of the first MFMA, then one read per MFMA, so that an
       // operand is requested about 8 MFMAs before it is needed (0x100 = LDS read, 0x008 = MFMA)
-      __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, kRing, 0);
 #pragma unroll
-      for (int i = 0; i < kScore - 8; ++i) {
+      for (int i = 0; i < kScore - kRing; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
-      __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, kRing, 0);
       __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kb = 0; kb < kNg; ++kb) acc_s[kb] = acc[kb];
+      if constexpr (kNg == 1) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc_s[0][i] += acc[1][i];
+      }
     }
     // The next tile is requested here, after the score MFMAs and not at the top of the
     // iteration: while an LDS-direct load (a FLAT-encoded instruction) is in flight the
@@ -320,32 +334,33 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     // It still has the softmax and the value phase of this tile to land.
     if (t + 1 < t_end) fetch_tile(block_next, stage ^ 1);
     if (visible) {
-      // register i of group kb holds key kpos0 + kb*32 + 16*(i/8) + 8*half + (i%8)
+      // register i of group kb holds key kpos0 + (kb0 + kb)*32 + 16*(i/8) + 8*half + (i%8)
       if (masked) {
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
+        for (int kb = 0; kb < kNg; ++kb)
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
-            const int kp = kpos0 + kb * 32 + 16 * (i >> 3) + 8 * half + (i & 7);
+            const int kp = kpos0 + (kb0 + kb) * 32 + 16 * (i >> 3) + 8 * half + (i & 7);
             const bool ok = kp >= lo && kp < hi && kp <= my_pos;
             acc_s[kb][i] = ok ? acc_s[kb][i] : -INFINITY;
           }
       }
       // ---- online softmax, one query per lane (two lanes share a query: n and n+32)
       // the first V^T operands are requested now and land during the max reduction;
-      // operand j = kDb * (2*kb + s2) + db belongs to keys kb*32 + s2*16 .. +15, rows db*32 .. +31
+      // operand j = kDb * (2*kb + s2) + db belongs to keys (kb0 + kb)*32 + s2*16 .. +15, rows db*32 .. +31
       auto v_read = [&](int j) {
-        return *reinterpret_cast<const u32x4*>(vs_ + (v_off0 ^ (uint32_t(j / kDb) << 5)) + (j % kDb) * 32 * 256);
+        return *reinterpret_cast<const u32x4*>(vs_ + (v_off0 ^ (uint32_t(2 * kb0 + j / kDb) << 5)) + (j % kDb) * 32 * 256);
       };
-      u32x4 vring[8];
+      constexpr int kValue = 2 * kNg * kDb, kVRing = kValue < 8 ? kValue : 8;
+      u32x4 vring[kVRing];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) vring[i] = v_read(i);
+      for (int i = 0; i < kVRing; ++i) vring[i] = v_read(i);
       float mx = acc_s[0][0];
 #pragma unroll
-      for (int kb = 0; kb < 4; ++kb)
+      for (int kb = 0; kb < kNg; ++kb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc_s[kb][i]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      mx = lane_pair<32>(mx, [](float x, float y) { return fmaxf(x, y); });
       // the reference maximum follows the true one lazily: it moves only when a tile exceeds
       // it by more than 2^8, so the rescaling of the accumulators below is rare after the first
       // tiles; probabilities up to 2^8 are as exact in bf16 and fp32 as those up to 1
@@ -369,7 +384,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
       // V^T operand is read 8 MFMAs ahead.  The row sums add the bf16 probabilities the product
       // itself uses, a pair per instruction, each lane summing its own 64 keys of the tile.
 #pragma unroll
-      for (int g8 = 0; g8 < 8; ++g8) {
+      for (int g8 = 0; g8 < 2 * kNg; ++g8) {
         const int kb = g8 >> 1, s2 = g8 & 1;
         const bf16x8 pb = pack8(acc_s[kb][8 * s2 + 0], acc_s[kb][8 * s2 + 1], acc_s[kb][8 * s2 + 2],
                                 acc_s[kb][8 * s2 + 3], acc_s[kb][8 * s2 + 4], acc_s[kb][8 * s2 + 5],
@@ -378,7 +393,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int db = 0; db < kDb; ++db) {
-          if (kb < 3) {
+          if (kb < kNg - 1) {
             constexpr int kExp = 8 / kDb;
 #pragma unroll
             for (int i = 8 * s2 + kExp * db; i < 8 * s2 + kExp * (db + 1); ++i)
@@ -386,8 +401,8 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
           }
           __builtin_amdgcn_sched_barrier(0);
           const int j = kDb * g8 + db;
-          acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vring[j & 7]), pb, acc_o[db], 0, 0, 0);
-          if (j + 8 < 8 * kDb) vring[j & 7] = v_read(j + 8);
+          acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vring[j % kVRing]), pb, acc_o[db], 0, 0, 0);
+          if (j + kVRing < kValue) vring[j % kVRing] = v_read(j + kVRing);
         }
       }
     }
@@ -399,66 +414,131 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
   }
 
   // ---- epilogue
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  float l_tot = lane_pair<32>(l_run, [](float x, float y) { return x + y; });
+  // The wavefronts that share query rows merge in LDS (the tiles are no longer needed): each puts down
+  // its output, its maximum and its sum and takes over kMine of the 32-channel groups:
+  //   out = sum_w 2^(m_w - M) o_w / sum_w 2^(m_w - M) l_w
+  constexpr int kMine = kDb > KS ? kDb / KS : 1;     // channel groups of a wavefront from here on
+  f32x16 acc_f[kMine];
+  const int db0 = quarter * kMine;
+  const bool has_mine = db0 < kDb;
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int db = 0; db < kDb; ++db) acc_f[db] = acc_o[db];
+  } else {
+    __shared__ float ml_lds[kPfWaves][2][32];
+    f32x4* o_lds = reinterpret_cast<f32x4*>(lds);    // [wavefront][channel group][register / 4][lane]
+#pragma unroll
+    for (int db = 0; db < kDb; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        o_lds[((wave * kDb + db) * 4 + i) * 64 + lane] =
+            f32x4{acc_o[db][4 * i], acc_o[db][4 * i + 1], acc_o[db][4 * i + 2], acc_o[db][4 * i + 3]};
+    if (half == 0) {
+      ml_lds[wave][0][n] = m_run;
+      ml_lds[wave][1][n] = l_tot;
+    }
+    __syncthreads();
+    float m_of[KS], l_of[KS], m_all = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < KS; ++w) {
+      m_of[w] = ml_lds[w * kRowGroups + rg][0][n];
+      l_of[w] = ml_lds[w * kRowGroups + rg][1][n];
+      m_all = fmaxf(m_all, m_of[w]);
+    }
+    const float m_ref = m_all == -INFINITY ? 0.f : m_all;
+    l_tot = 0.f;
+#pragma unroll
+    for (int db = 0; db < kMine; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc_f[db][i] = 0.f;
+#pragma unroll
+    for (int w = 0; w < KS; ++w) {
+      const float weight = __builtin_amdgcn_exp2f(m_of[w] - m_ref);
+      l_tot += weight * l_of[w];
+      if (has_mine) {
+#pragma unroll
+        for (int db = 0; db < kMine; ++db)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const f32x4 o = o_lds[(((w * kRowGroups + rg) * kDb + db0 + db) * 4 + i) * 64 + lane];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc_f[db][4 * i + r] += weight * o[r];
+          }
+      }
+    }
+    m_run = m_all;
+  }
   if (splits == 1) {
-    if (row_ok) store_rows<D>(p, acc_o, m_run, l_tot, s, my_row, head, half);
+    if (row_ok && has_mine) store_rows<D, kMine>(p, acc_f, db0, m_run, l_tot, s, my_row, head, half);
     return;
   }
-  // The split stores its normalised output as bf16 in the order the registers hold it
-  // (register-major, lane-minor: every store instruction writes one contiguous 512-byte
-  // row), plus its running max and sum.
-  constexpr int kWords = 4 * kDb + 1;              // 64-bit words per lane: groups of four bf16, then (max, sum)
+  // The piece stores its output in the order the registers hold it (register-major, lane-minor: every
+  // store instruction writes one contiguous 512-byte row), plus its running max and sum: of a whole
+  // query tile normalised and as bf16 (64 KB), of fewer rows as it is.
+  constexpr bool kHalf = KS == 1;
+  constexpr int kPerGroup = kHalf ? 4 : 8;         // 64-bit words of a channel group
+  constexpr int kWords = kPerGroup * kMine + 1;    // 64-bit words per lane: the output, then (max, sum)
   __shared__ int last_flag;
   const size_t group_id = (size_t(s) * p.n_qtiles + qtile) * p.n_kv_heads + hk;
   uint64_t* group_part = p.part + ((size_t(s) * p.n_kv_heads + hk) * p.slots + (slot - split)) *
                                       (kPfWaves * (kWords * 64));
-  {
+  if (has_mine) {
     uint64_t* mine = group_part + (size_t(split) * kPfWaves + wave) * (kWords * 64);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
 #pragma unroll
-    for (int db = 0; db < kDb; ++db)
+    for (int db = 0; db < kMine; ++db)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t lo = pack_bf16x2(acc_o[db][4 * i] * inv, acc_o[db][4 * i + 1] * inv);
-        const uint32_t hi = pack_bf16x2(acc_o[db][4 * i + 2] * inv, acc_o[db][4 * i + 3] * inv);
-        st_agent(mine + (db * 4 + i) * 64 + lane, uint64_t(lo) | (uint64_t(hi) << 32));
+      for (int i = 0; i < kPerGroup; ++i) {
+        uint32_t lo, hi;
+        if constexpr (kHalf) {
+          lo = pack_bf16x2(acc_f[db][4 * i] * inv, acc_f[db][4 * i + 1] * inv);
+          hi = pack_bf16x2(acc_f[db][4 * i + 2] * inv, acc_f[db][4 * i + 3] * inv);
+        } else {
+          lo = __float_as_uint(acc_f[db][2 * i]);
+          hi = __float_as_uint(acc_f[db][2 * i + 1]);
+        }
+        st_agent(mine + (db * kPerGroup + i) * 64 + lane, uint64_t(lo) | (uint64_t(hi) << 32));
       }
-    st_agent(mine + 4 * kDb * 64 + lane, uint64_t(__float_as_uint(m_run)) | (uint64_t(__float_as_uint(l_tot)) << 32));
+    st_agent(mine + (kWords - 1) * 64 + lane, uint64_t(__float_as_uint(m_run)) | (uint64_t(__float_as_uint(l_tot)) << 32));
   }
-  if (!last_of_group(p.counters + group_id, unsigned(splits), &last_flag)) return;
+  if (!last_of_group(p.counters + group_id, unsigned(splits), &last_flag) || !has_mine) return;
 
-  // ---- the last split of the query tile merges all of them, in split order:
-  //   out = sum_s w_s o_s / sum_s w_s with w_s = l_s 2^(m_s - M), M = max_s m_s
+  // ---- the last piece of the query tile merges all of them, in order:
+  //   out = sum_s w_s o_s / sum_s w_s with w_s = l_s 2^(m_s - M), M = max_s m_s, o_s normalised
+  //   (not normalised: sum_s v_s O_s / sum_s v_s l_s with v_s = 2^(m_s - M))
   // (its own piece is read back like the others, so the result does not depend on who is last)
   const uint64_t* piece0 = group_part + size_t(wave) * (kWords * 64) + lane;
   const size_t piece_stride = size_t(kPfWaves) * (kWords * 64);
   // the loads of the first pieces go out together with the (max, sum) words of all pieces
-  constexpr int kMergeBatch = 3;
-  uint64_t ml[kMaxPfSplits], raw[kMergeBatch][4 * kDb];
+  constexpr int kMergeBatch = kWords <= 9 ? 4 : 3;
+  uint64_t ml[kMaxPfSplits], raw[kMergeBatch][kWords - 1];
 #pragma unroll
   for (int s2 = 0; s2 < kMaxPfSplits; ++s2)
-    ml[s2] = s2 < splits ? ld_agent(piece0 + s2 * piece_stride + 4 * kDb * 64) : 0;
+    ml[s2] = s2 < splits ? ld_agent(piece0 + s2 * piece_stride + (kWords - 1) * 64) : 0;
 #pragma unroll
   for (int j = 0; j < kMergeBatch; ++j)
 #pragma unroll
-    for (int k = 0; k < 4 * kDb; ++k) raw[j][k] = j < splits ? ld_agent(piece0 + j * piece_stride + k * 64) : 0;
+    for (int k = 0; k < kWords - 1; ++k) raw[j][k] = j < splits ? ld_agent(piece0 + j * piece_stride + k * 64) : 0;
   __builtin_amdgcn_sched_barrier(0);
   float w_s[kMaxPfSplits + kMergeBatch];
-  float m_all = -INFINITY;
+  float m_all = -INFINITY, l_all = 0.f;
 #pragma unroll
   for (int s2 = 0; s2 < kMaxPfSplits; ++s2)
     if (s2 < splits) m_all = fmaxf(m_all, __uint_as_float(uint32_t(ml[s2])));
   const float m_safe = m_all == -INFINITY ? 0.f : m_all;
 #pragma unroll
-  for (int s2 = 0; s2 < kMaxPfSplits + kMergeBatch; ++s2)
-    w_s[s2] = s2 < splits ? __uint_as_float(uint32_t(ml[s2 < kMaxPfSplits ? s2 : 0] >> 32)) *
-                                  __builtin_amdgcn_exp2f(__uint_as_float(uint32_t(ml[s2 < kMaxPfSplits ? s2 : 0])) - m_safe)
-                            : 0.f;
-  float l_all = 0.f;
+  for (int s2 = 0; s2 < kMaxPfSplits + kMergeBatch; ++s2) {
+    const uint64_t of = ml[s2 < kMaxPfSplits ? s2 : 0];
+    const float v = s2 < splits ? __builtin_amdgcn_exp2f(__uint_as_float(uint32_t(of)) - m_safe) : 0.f;
+    const float vl = s2 < splits ? v * __uint_as_float(uint32_t(of >> 32)) : 0.f;
+    l_all += vl;
+    w_s[s2] = kHalf ? vl : v;
+  }
 #pragma unroll
-  for (int db = 0; db < kDb; ++db)
+  for (int db = 0; db < kMine; ++db)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc_o[db][i] = 0.f;
+    for (int i = 0; i < 16; ++i) acc_f[db][i] = 0.f;
 #pragma unroll
   for (int b0 = 0; b0 < kMaxPfSplits; b0 += kMergeBatch) {
     if (b0 < splits) {
@@ -466,27 +546,31 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
 #pragma unroll
         for (int j = 0; j < kMergeBatch; ++j)
 #pragma unroll
-          for (int k = 0; k < 4 * kDb; ++k)
+          for (int k = 0; k < kWords - 1; ++k)
             raw[j][k] = b0 + j < splits ? ld_agent(piece0 + (b0 + j) * piece_stride + k * 64) : 0;
       }
 #pragma unroll
       for (int j = 0; j < kMergeBatch; ++j) {
         const float w = w_s[b0 + j];
-        l_all += w;
 #pragma unroll
-        for (int db = 0; db < kDb; ++db)
+        for (int db = 0; db < kMine; ++db)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const uint32_t lo = uint32_t(raw[j][db * 4 + i]), hi = uint32_t(raw[j][db * 4 + i] >> 32);
-            acc_o[db][4 * i + 0] += w * bf16_lo(lo);
-            acc_o[db][4 * i + 1] += w * bf16_hi(lo);
-            acc_o[db][4 * i + 2] += w * bf16_lo(hi);
-            acc_o[db][4 * i + 3] += w * bf16_hi(hi);
+          for (int i = 0; i < kPerGroup; ++i) {
+            const uint32_t lo = uint32_t(raw[j][db * kPerGroup + i]), hi = uint32_t(raw[j][db * kPerGroup + i] >> 32);
+            if constexpr (kHalf) {
+              acc_f[db][4 * i + 0] += w * bf16_lo(lo);
+              acc_f[db][4 * i + 1] += w * bf16_hi(lo);
+              acc_f[db][4 * i + 2] += w * bf16_lo(hi);
+              acc_f[db][4 * i + 3] += w * bf16_hi(hi);
+            } else {
+              acc_f[db][2 * i] += w * __uint_as_float(lo);
+              acc_f[db][2 * i + 1] += w * __uint_as_float(hi);
+            }
           }
       }
     }
   }
-  if (row_ok) store_rows<D>(p, acc_o, m_all, l_all, s, my_row, head, half);
+  if (row_ok) store_rows<D, kMine>(p, acc_f, db0, m_all, l_all, s, my_row, head, half);
 }
 
 // blockIdx.x = w * Hk + hk: consecutive ids differ in hk, and ids are dealt round-robin to the
@@ -497,14 +581,14 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
 // how many blocks they retrieve, and a fixed assignment would wait for the unluckiest
 // workgroup.  Nobody waits for anybody: a workgroup leaves when the counter runs out, and the
 // last one to leave puts the counters back to zero for the next launch.
-template <int D>
+template <int D, int KS>
 __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_kernel(PfParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   const int item = blockIdx.x / p.n_kv_heads, s = item / p.slots;
-  attn_prefill_item<D, false>(p, lds, blockIdx.x % p.n_kv_heads, item - s * p.slots, s);
+  attn_prefill_item<D, KS, false>(p, lds, blockIdx.x % p.n_kv_heads, item - s * p.slots, s);
 }
 
-template <int D>
+template <int D, int KS>
 __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_queued_kernel(PfParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   __shared__ int next_item;
@@ -546,7 +630,7 @@ __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_queued_kernel(Pf
       s = order[s];
       slot = p.slots - 1 - slot;
     }
-    attn_prefill_item<D, true>(p, lds, hk, __builtin_amdgcn_readfirstlane(slot), __builtin_amdgcn_readfirstlane(s));
+    attn_prefill_item<D, KS, true>(p, lds, hk, __builtin_amdgcn_readfirstlane(slot), __builtin_amdgcn_readfirstlane(s));
     __syncthreads();                         // everybody is done with the LDS tiles of this item
     item = draw();
   }
@@ -565,50 +649,100 @@ bool prefill_mfma_supported(const actqkv_shape& sh, int m) {
   return sh.dtype == ACTQKV_BF16 && m > 1 && sh.n_q_heads / sh.n_kv_heads <= 8;
 }
 
-int prefill_mfma_qtiles(const actqkv_shape& sh, int m) {
-  return (m * (sh.n_q_heads / sh.n_kv_heads) + kPfRows - 1) / kPfRows;
+static int prefill_mfma_qtiles(const actqkv_shape& sh, int m, int ks) {
+  const int rows = kPfRows<1> / ks;
+  return (m * (sh.n_q_heads / sh.n_kv_heads) + rows - 1) / rows;
 }
 
-// workgroups per (sequence, split): query tiles x KV heads
-int prefill_mfma_workgroups(const actqkv_shape& sh, int m) {
-  return prefill_mfma_qtiles(sh, m) * sh.n_kv_heads;
+// How a call is cut up: the query rows of a workgroup (kPfRows of ks), the pieces of the key tiles.
+//
+// Whole query tiles of 256 rows use the matrix cores and the L2 best, but a single window has few
+// of them, and cutting its key tiles into pieces for other workgroups costs 10 to 15 us: partial
+// results out, a ticket, and one compute unit reading all of them back.  With fewer rows per
+// workgroup (its wavefronts share the keys of a tile and merge in LDS) there are fewer pieces and
+// less to merge, but a tile costs 16 % (2 sharing) or 69 % (4) more per row.  The choice is the least of
+// what the busiest compute unit needs by these measured figures, in us; windows of 512 tokens, 32
+// query and 8 KV heads, 10 blocks: 35.8 as 256 rows in 4 pieces, 32.3 as 128 rows in 2, 34.8 as 64 rows
+// in one; 128 tokens: 28.7, 20.4, 17.1; 32 windows of 512 in a call: 597, 692, 1009.
+PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
+  PfSplits r{1, 0, 1, 1, 1};
+  if (!prefill_mfma_supported(sh, m)) return r;
+  constexpr double kTileUs[] = {3.7, 2.1, 1.5}, kMergeUs[] = {6., 3.5, 2.}, kMergePieceUs[] = {1.1, 0.7, 0.5};
+  constexpr double kItemUs = 8.;
+  const int pairs = batch * sh.n_kv_heads;
+  // key tiles of the last query tile and of an average one; half of k_cap retrieved
+  const double longest = (sh.n_init + sh.n_local + m) / double(kBlock) + k_cap / 2.0;
+  const double average = longest - m / double(2 * kBlock);
+  double best = 0.;
+  for (int i = 0; i < 3; ++i) {
+    PfSplits c;
+    c.ks = 1 << i;
+    c.n_qtiles = prefill_mfma_qtiles(sh, m, c.ks);
+    // pieces where the query tiles leave compute units idle, never more than 8 per query tile; of whole
+    // query tiles, what does not divide evenly goes to the last ones of the window
+    const int per_pair = std::max(cus / pairs, c.n_qtiles);    // workgroups one pair may have
+    c.s_lo = std::min(per_pair / c.n_qtiles, kMaxPfSplits);
+    c.rem = c.s_lo == kMaxPfSplits || c.ks > 1 ? 0 : per_pair - c.s_lo * c.n_qtiles;
+    c.slots = c.s_lo * c.n_qtiles + c.rem;
+    const double rounds = double(pairs) * c.slots / cus;
+    double us = std::max(std::ceil(longest / c.s_lo), rounds * average / c.s_lo) * kTileUs[i] + kItemUs * std::max(rounds, 1.);
+    if (c.slots > c.n_qtiles) us += kMergeUs[i] + kMergePieceUs[i] * c.s_lo;
+    if (i == 0 || us < best) {
+      best = us;
+      r = c;
+    }
+  }
+  return r;
 }
 
-// hipFuncSetAttribute once per process and head size, from whichever thread comes first
-template <int D>
+// Partial results of any call of up to `batch` windows of up to m tokens: pieces exist only while they
+// and the query tiles fit the compute units.
+size_t prefill_partials_most(const actqkv_shape& sh, int batch, int m) {
+  const size_t most = size_t(batch) * sh.n_kv_heads * prefill_mfma_qtiles(sh, m, 4) * kMaxPfSplits;
+  return std::min(size_t(kChipCus), most) * kPfPartialFloats * sizeof(float);
+}
+
+// hipFuncSetAttribute once per process and variant, from whichever thread comes first
+template <int D, int KS>
 static int prefill_lds_attribute() {
   static std::mutex mu;
   static bool attr_set = false;
   std::lock_guard<std::mutex> lock(mu);
   if (attr_set) return ACTQKV_OK;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_kernel<D>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_kernel<D, KS>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kPfLdsBytes<D>);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_queued_kernel<D>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_queued_kernel<D, KS>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kPfLdsBytes<D>);
   if (e != hipSuccess) return set_error(ACTQKV_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
   attr_set = true;
   return ACTQKV_OK;
 }
 
-template <int D>
+template <int D, int KS>
 static int launch_pf(PfParams p, int late_per_head, hipStream_t stream, hipStream_t stream_late) {
-  if (int rc = prefill_lds_attribute<D>()) return rc;
+  if (int rc = prefill_lds_attribute<D, KS>()) return rc;
   dim3 grid(p.wgs_per_head * p.n_kv_heads);
   if (p.items_per_head > p.wgs_per_head)
-    hipLaunchKernelGGL(attn_prefill_mfma_queued_kernel<D>, grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
+    hipLaunchKernelGGL((attn_prefill_mfma_queued_kernel<D, KS>), grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
   else
-    hipLaunchKernelGGL(attn_prefill_mfma_kernel<D>, grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
+    hipLaunchKernelGGL((attn_prefill_mfma_kernel<D, KS>), grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
   if (int rc = hip_status("attention (prefill, matrix cores)")) return rc;
   if (late_per_head > 0) {
     p.late = 1;
-    hipLaunchKernelGGL(attn_prefill_mfma_queued_kernel<D>, dim3(late_per_head * p.n_kv_heads), dim3(kPfThreads),
+    hipLaunchKernelGGL((attn_prefill_mfma_queued_kernel<D, KS>), dim3(late_per_head * p.n_kv_heads), dim3(kPfThreads),
                        kPfLdsBytes<D>, stream_late, p);
     // (if this launch fails after the first one went out, the first team still does all the work, but
     // the queue is not put back to zero: the workspace must be zero-filled again before its next use)
     if (int rc = hip_status("attention (prefill, matrix cores, second team)")) return rc;
   }
   return ACTQKV_OK;
+}
+template <int D>
+static int launch_pf_ks(int ks, const PfParams& p, int late_per_head, hipStream_t stream, hipStream_t stream_late) {
+  return ks == 1   ? launch_pf<D, 1>(p, late_per_head, stream, stream_late)
+         : ks == 2 ? launch_pf<D, 2>(p, late_per_head, stream, stream_late)
+                   : launch_pf<D, 4>(p, late_per_head, stream, stream_late);
 }
 
 // first_cus: compute units the first team may fill (the pieces in `splits` were chosen for it);
@@ -644,7 +778,7 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
   p.s_lo = splits.s_lo;
   p.rem = splits.rem;
   p.slots = splits.slots;
-  p.n_qtiles = prefill_mfma_qtiles(sh, m);
+  p.n_qtiles = splits.n_qtiles;
   p.scale_log2e = scale * 1.4426950408889634f;
   if (splits.slots < p.n_qtiles || splits.slots != splits.s_lo * p.n_qtiles + splits.rem)
     return set_error(ACTQKV_EINVAL, "prefill attention: inconsistent split of the key tiles");
@@ -659,8 +793,8 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
   if (p.items_per_head <= p.wgs_per_head) late_per_head = 0;   // a workgroup per item: no queue, no second team
   p.team_total = (p.wgs_per_head + late_per_head) * sh.n_kv_heads;
   p.late = 0;
-  return sh.head_dim == 64 ? launch_pf<64>(p, late_per_head, stream, stream_late)
-                           : launch_pf<128>(p, late_per_head, stream, stream_late);
+  return sh.head_dim == 64 ? launch_pf_ks<64>(splits.ks, p, late_per_head, stream, stream_late)
+                           : launch_pf_ks<128>(splits.ks, p, late_per_head, stream, stream_late);
 }
 
 }  // namespace actqkv

@@ -60,13 +60,15 @@ inline size_t probe_call_floats(const actqkv_shape& sh, int batch, int m) {
   return (slabs > rows ? slabs : rows) + 4;
 }
 
-// Key-tile splits of the prefill attention.
+// How a prefill attention call is cut up.  ks: wavefronts of a workgroup that share query rows (1, 2, 4),
+// n_qtiles: query tiles of 256 / ks rows per (sequence, KV head).
 // The first n_qtiles - rem query tiles of a sequence are cut into s_lo pieces, the last rem
 // (which see more of the causal window) into s_lo + 1; slots = pieces per (sequence, KV head).
 struct PfSplits {
-  int s_lo, rem, slots;
+  int s_lo, rem, slots, ks, n_qtiles;
 };
 PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int cus);   // cus: compute units to fill
+size_t prefill_partials_most(const actqkv_shape& sh, int batch, int m);
 // prefill on the matrix cores: per workgroup and piece, 8 wavefronts x (16 eight-byte words of
 // four bf16 of normalised output + one word (max, sum)) x 64 lanes, counted in floats
 constexpr size_t kPfPartialFloats = 8 * (32 + 2) * 64;
