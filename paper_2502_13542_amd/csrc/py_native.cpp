@@ -13,6 +13,7 @@
 //   h  like s, but pinned host memory will do    w  workspace (a size_t parameter follows: its bytes)
 //   p  address (an integer)                      q  stream, None for the current one
 // A tensor parameter accepts None (the library decides whether it may be NULL).
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <c10/hip/HIPStream.h>
@@ -190,6 +191,9 @@ template <typename... P> struct Entry<int(P...)> {
       PyErr_SetString(PyExc_RuntimeError, "the loaded library does not have this entry point");
       return nullptr;
     }
+    // (a tensor without memory, of a fake or a sparse kind for instance, throws when it is asked for an
+    // address; C++ exceptions end here, as Python ones)
+    HANDLE_TH_ERRORS
     Args a;
     a.at = args;
     a.end = args + n;
@@ -200,12 +204,16 @@ template <typename... P> struct Entry<int(P...)> {
       a.ok = false;
     }
     if (!a.ok) return nullptr;
-    const int rc = std::apply(fn, values);
+    int rc;
+    Py_BEGIN_ALLOW_THREADS                                 // (a launch waits while its queue is full)
+    rc = std::apply(fn, values);
+    Py_END_ALLOW_THREADS
     if (rc != ACTQKV_OK) {
       raise(rc, g_last_error != nullptr ? g_last_error() : "");
       return nullptr;
     }
     Py_RETURN_NONE;
+    END_HANDLE_TH_ERRORS
   }
 };
 

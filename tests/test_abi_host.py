@@ -306,3 +306,27 @@ def test_cutoff_next_step_rejects(lib):
     assert call(batch=0) == -1 and call(k=0.0) == -1 and call(prior=-1.0) == -1
     assert call(L=0) == -2 and call(L=2000) == -2
     assert call(ts=None) == -1 and call(b=None) == -1 and call(r=A16 + 2) == -3
+
+
+def test_cpp_exceptions_reach_python():
+    """What torch throws while a call's arguments are taken (no GPU for the current stream, a tensor
+    without memory) is a Python exception, not the end of the process."""
+    import subprocess
+    import sys
+    code = """
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+from paper_2502_13542_amd import binding as B
+def call(t):
+    try:
+        B.cutoff_next_step(1, 1, 1., 1., t, t, t, t, t)
+    except RuntimeError:
+        print("raised")
+    return t
+call(None)
+with FakeTensorMode():
+    torch.func.vmap(call)(torch.empty(4, 64, device="cuda"))
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-1000:]
+    assert r.stdout.split() == ["raised", "raised"]
