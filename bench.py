@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 matrix-core peak
 PEAK_HBM_GBS = 8000.0
-PEAK_FP32_TFLOPS = 157.3    # fp32 vector arithmetic (the fp32 workload's attention runs in row kernels)
+PEAK_FP32_TFLOPS = 157.3    # fp32 on the matrix cores (and, the same figure, on the vector units)
 
 
 def log(msg: str) -> None:

@@ -189,8 +189,8 @@ def decode_retrieve(shape: CShape, batch: int, q_tok, k_new, v_new, pos0, k_cach
     """Cache update, probe, scores and selection of a decode step in one call; see the header."""
     _calls().decode_retrieve(shape, batch, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride, rep_keys,
                              rep_seq_stride, nb_capacity, nb_begin, nb_end, probe, probe_kv, probe_norm, scores,
-                             score_stride, k_cap, flags, budget_remaining, theta_rest_sum, idx, n_sel, theta, budget,
-                             stream)
+                             score_stride, k_cap, int(flags), budget_remaining, theta_rest_sum, idx, n_sel, theta,
+                             budget, stream)
 
 
 def decode_select_attention(shape: CShape, batch: int, q, k_cache, v_cache, seq_stride: int, nb_capacity: int,
@@ -199,7 +199,7 @@ def decode_select_attention(shape: CShape, batch: int, q, k_cache, v_cache, seq_
                             stream=None, flags: int = 0) -> None:
     """Selection and attention of a decode step in one launch; see the header."""
     _calls().decode_select_attention(shape, batch, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx, scores,
-                                     score_stride, nb_begin, nb_end, k_cap, flags, budget_in, theta_rest_sum,
+                                     score_stride, nb_begin, nb_end, k_cap, int(flags), budget_in, theta_rest_sum,
                                      budget_after, idx, n_sel, theta, budget, out, lse, workspace, stream)
 
 
@@ -209,7 +209,7 @@ def decode_layer(shape: CShape, batch: int, q, k_new, v_new, k_cache, v_cache, c
                  budget, out, lse, workspace, stream=None, flags: int = 0) -> None:
     """A whole layer of a decode step in one launch; see the header."""
     _calls().decode_layer(shape, batch, q, k_new, v_new, k_cache, v_cache, cache_seq_stride, rep_keys, rep_seq_stride,
-                          nb_capacity, n_ctx, nb_begin, nb_end, scores, score_stride, k_cap, flags, budget_in,
+                          nb_capacity, n_ctx, nb_begin, nb_end, scores, score_stride, k_cap, int(flags), budget_in,
                           theta_rest_sum, budget_after, idx, n_sel, theta, budget, out, lse, workspace, stream)
 
 
@@ -226,7 +226,8 @@ def retrieval_attention_teams(shape: CShape, batch: int, m: int, q, k_cache, v_c
     """The attention on first_cus compute units, with an optional second team of late_cus workgroups
     launched on stream_late; see the header."""
     _calls().retrieval_attention_teams(shape, batch, m, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx, idx,
-                                       n_sel, k_cap, out, lse, workspace, first_cus, late_cus, stream, stream_late)
+                                       n_sel, k_cap, out, lse, workspace, int(first_cus), int(late_cus), stream,
+                                       stream_late)
 
 
 def retrieval_attention_windows(shape: CShape, n_windows: int, m: int, q, k_cache, v_cache, nb_capacity: int, n_ctx,
@@ -266,8 +267,8 @@ def copy_bytes_at(dst, dst_byte: int, src, src_byte: int, n_bytes: int, stream=N
 
 def build_probe(shape: CShape, batch: int, m: int, q_win, stats, update_stats, probe, probe_kv,
                 probe_norm, weights, workspace, stream=None) -> None:
-    _calls().build_probe(shape, batch, m, q_win, stats, update_stats, probe, probe_kv, probe_norm, weights, workspace,
-                         stream)
+    _calls().build_probe(shape, batch, m, q_win, stats, int(update_stats), probe, probe_kv, probe_norm, weights,
+                         workspace, stream)
 
 
 def gather_blocks(shape: CShape, batch: int, k_store, v_store, store_seq_stride: int, nb_store: int,
@@ -302,7 +303,7 @@ def score_blocks_per_head(shape: CShape, batch: int, probe, rep_keys, seq_stride
 def select(batch: int, scores, score_stride: int, nb_capacity: int, nb_begin: int, nb_end,
            k_cap: int, budget_remaining, theta_rest_sum, idx, n_sel, theta=None, budget=None,
            stream=None, flags: int = 0) -> None:
-    _calls().select(batch, scores, score_stride, nb_capacity, nb_begin, nb_end, k_cap, flags, budget_remaining,
+    _calls().select(batch, scores, score_stride, nb_capacity, nb_begin, nb_end, k_cap, int(flags), budget_remaining,
                     theta_rest_sum, idx, n_sel, theta, budget, stream)
 
 

@@ -643,7 +643,7 @@ int actqkv_gather_blocks_cached(const actqkv_shape* shape, int n_windows, const 
                                 int32_t* idx_slots, void* stream) {
   ACTQKV_TRY(check_shape(shape));
   if (k_cap < 1 || k_cap > 64) return set_error(ACTQKV_ESHAPE, "k_cap %d outside 1..64", k_cap);
-  if (n_windows < 1 || n_windows * k_cap > kSlotSelections)
+  if (n_windows < 1 || n_windows > kSlotSelections / k_cap)
     return set_error(ACTQKV_ESHAPE, "gather_blocks_cached: %d windows of up to %d blocks (at most %d selections)", n_windows,
                      k_cap, kSlotSelections);
   if (nb_store < 1 || nb_capacity < 1) return set_error(ACTQKV_EINVAL, "gather_blocks_cached: empty store or cache");

@@ -724,10 +724,10 @@ class HostCachePrefill:
         use; blocks that still lie in the region do not cross it at all.  A fourth attends.
         Results are those of run().  What bounds it: a pass over 32K tokens (32 query, 8 KV heads,
         windows of 512, 16 blocks each) gathered 0.5 GB in 13.0 ms when every window brought its own
-        blocks; now the attention (64 launches) and the write-back (128 MB) set the pace: @@ ms."""
+        blocks; now the attention and the write-back (128 MB) set the pace: 5.0 ms."""
         r, plan, sh, cs = self.runner, self.plan, self.runner.shape, self.runner.cs
         bs, kw, vw, bb = sh.block_size, self.k_ring, self.v_ring, self.block_bytes
-        nb_store = k_store.shape[0]
+        nb_store = min(k_store.shape[0], r.nb_capacity)     # what slot_state has room for; no selection is past it
         cur = torch.cuda.current_stream()
         mover, attender, writer = self.mover, self.attender, self.writer
         self.slot_state.fill_(-2)
@@ -793,8 +793,8 @@ class HostCachePrefill:
                     continue
                 a, rows = plan.w0[t], plan.rows[t]
                 kc, vc = (k_region, v_region) if self.whole[t] else (kw, vw)
-                B.retrieval_attention(cs, 1, rows, q[a:a + rows], kc, vc, 0, kc.shape[0], self.v_nctx[t], self.v_slots[t], self.v_nsel[t], r.k_cap, out[a:a + rows], None,
-                                      self.workspace, attender)
+                B.retrieval_attention(cs, 1, rows, q[a:a + rows], kc, vc, 0, kc.shape[0], self.v_nctx[t], self.v_slots[t],
+                                      self.v_nsel[t], r.k_cap, out[a:a + rows], None, self.workspace, attender)
             attended[g].record(attender)
         for st in (mover, attender, writer):
             cur.wait_stream(st)

@@ -243,7 +243,7 @@ def test_geometry_variants(n_init, n_local):
 @pytest.mark.parametrize("m,n_ctx,attend", [(2048, 3 * 2048 + 300, [1, 3]), (4096, 2 * 4096 + 128, [1, 2])])
 def test_windows_larger_than_the_benchmarked_one(m, n_ctx, attend):
     """Windows of 2048 tokens (16 key tiles of the window itself: still the matrix-core kernel) and
-    of 4096 (more tiles than its tile table holds: the row kernel), bf16, ragged last window;
+    of 4096 (many tiles per window), bf16, ragged last window;
     probes, scores and selections of every window, attention of the windows in `attend`."""
     sh = LayerShape(8, 2, 128, 128, 4, 128, 256, "bf16")
     w = synth.Workload(f"window_{m}", sh, n_ctx, m, 6, True, 4242 + m, n_planted=4)
@@ -470,10 +470,10 @@ def _lse_reference(q_row, k, pos, group):
 
 @pytest.mark.parametrize("dtype,d,m,nw", [("bf16", 128, 512, 1),     # key tiles cut into pieces, merged
                                           ("bf16", 128, 512, 8),     # whole query tiles per workgroup
-                                          ("fp32", 64, 256, 2),      # row kernel
+                                          ("fp32", 64, 256, 2),      # fp32 prefill kernel
                                           ("bf16", 128, 1, 3),       # decode, several workgroups per pair
                                           ("bf16", 128, 1, 200),     # decode, one workgroup per pair
-                                          ("fp32", 64, 1, 3)])       # decode, row kernel
+                                          ("fp32", 64, 1, 3)])       # decode in fp32
 def test_log_sum_exp_output(dtype, d, m, nw):
     """The optional lse output [batch][H][m] of every attention kernel: the natural-log sum of the
     exponentials of the scaled logits over exactly the keys a row sees."""
@@ -2392,6 +2392,30 @@ def test_overlapped_host_cache_pass_equals_window_order(m, n_init, n_local, k_ca
     assert torch.equal(out, out_ov)
     full = n_ctx // 128
     assert torch.equal(ke[:full], ks[:full]) and torch.equal(ve[:full], vs[:full])
+
+
+def test_overlapped_host_cache_pass_takes_a_store_larger_than_the_context():
+    """The slots' state has an entry per block of the runner; a store for a longer context than the
+    plan's (and the runner's) changes nothing, and the store behind the context stays as it was."""
+    sh, m, k_cap, n_ctx = LayerShape(8, 2, 64, 128, 2, 128, 256, "bf16"), 256, 4, 256 * 12
+    w = synth.Workload("host_large_store", sh, n_ctx, m, k_cap, False, 91, n_planted=6, n_layers=1)
+    q, k, v = synth.gen_layer(w, DEV)
+    rep = synth.pick_rep_keys(k, 128, sh.n_rep)
+    repd = torch.zeros(w.n_blocks, sh.n_rep, 2, 64, dtype=rep.dtype, device=DEV)
+    repd[: rep.shape[0]] = rep
+    got = []
+    for extra in (0, 1000):
+        runner = H.LayerRunner(sh, 1, m, w.n_blocks, k_cap, DEV)
+        host = H.HostCachePrefill(runner, H.make_prefill_plan(sh, n_ctx, m, None, DEV))
+        nb = w.n_blocks + extra
+        ks, vs = (torch.full((nb, 2, *s), 7.0, dtype=torch.bfloat16).pin_memory() for s in ((128, 64), (64, 128)))
+        out = torch.zeros_like(q)
+        rec = host.run_overlapped(q, k, v, ks, vs, repd, out)
+        torch.cuda.synchronize()
+        assert bool((ks[w.n_blocks:] == 7.0).all()) and bool((vs[w.n_blocks:] == 7.0).all())
+        got.append((out, ks[: w.n_blocks].clone(), vs[: w.n_blocks].clone(), [x["idx"].clone() for x in rec.values()]))
+    a, b = got
+    assert all(torch.equal(x, y) for x, y in zip(a[:3], b[:3])) and all(torch.equal(x, y) for x, y in zip(a[3], b[3]))
 
 
 def test_prefill_with_the_cache_in_host_memory():
