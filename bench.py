@@ -630,9 +630,10 @@ def bench_prefill_host_cache(args, torch, B, H, synth):
     return {"metric": "prefill retrieval-attn tokens/s per layer, cache in pinned host memory",
             "value": w.n_ctx / dt, "unit": "tokens/s", "ms_per_step": dt * 1e3, "steps": steps,
             "config": {"workload": w.name, "working_cache_blocks": host.nb_work, "working_caches": host.N_WORK,
+                       "overlapped_cache_blocks": host.nb_ring,
                        "context_blocks": w.n_blocks,
                        "launch": ("hip graph replay" if graph is not None else "eager") +
-                                 ", four streams: selection chain, data movement (local span, append, gather), "
+                                 ", four streams: selection chain and append, selected blocks into their slots, "
                                  "write-back, attention",
                        "ms_per_step_window_order_one_stream": dt_order * 1e3,
                        "output_equals_window_order": same},
@@ -642,10 +643,11 @@ def bench_prefill_host_cache(args, torch, B, H, synth):
                        "launches_with_blocks": len(g_with), "avg_launch_us": g_us / max(len(g_with), 1),
                        "bytes_per_launch": blocks * block_bytes / max(len(g_with), 1),
                        "timing": "HIP events around every gather launch of one in-order pass"},
-            "host_link": {"blocks_gathered_per_pass": blocks, "gather_bytes_per_pass": blocks * block_bytes,
+            # (in the timed schedule a selected block crosses the link only when it is neither in a slot nor in the
+            # sequence region; how many do is known on the device only)
+            "host_link": {"blocks_selected_per_pass": blocks, "selected_bytes_per_pass": blocks * block_bytes,
                           "write_back_bytes_per_pass": wb_bytes,
-                          "gather_GBps_over_the_whole_pass": blocks * block_bytes / dt / 1e9,
-                          "both_directions_GBps_over_the_whole_pass": (blocks * block_bytes + wb_bytes) / dt / 1e9}}
+                          "write_back_GBps_over_the_whole_pass": wb_bytes / dt / 1e9}}
 
 
 def bench_decode(args, torch, B, H, synth):

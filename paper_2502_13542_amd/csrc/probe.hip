@@ -24,12 +24,10 @@ namespace actqkv {
 
 constexpr int kColLanes = 8;      // 16-byte column lanes of a slab
 constexpr int kRowsPerThread = 16;   // 16-byte loads a thread keeps in flight
-constexpr int kStatsRowLanes = 32;
-constexpr int kStatsRowsPerPass = kStatsRowLanes * kRowsPerThread;
 
 // apart[j] = sum over the slab's channels of (q_jc - mean_c)^2 / var_c for the rows of the
 // window (Eq. (7) summed over a slab); x holds pass 0 of the rows when there is one pass only.
-template <typename T, typename LoadPass>
+template <typename T, int RL, typename LoadPass>
 __device__ __forceinline__ void bias_partials(typename Vec<T>::raw (&x)[kRowsPerThread], LoadPass&& load_pass,
                                               const float* mu_lds, const float* iv_lds,
                                               float* __restrict__ apart, int m, int m_pad, int n_pass,
@@ -43,7 +41,7 @@ __device__ __forceinline__ void bias_partials(typename Vec<T>::raw (&x)[kRowsPer
   }
   for (int pass = 0; pass < n_pass; ++pass) {
     if (n_pass > 1) load_pass(pass);
-    const int r0 = pass * kStatsRowsPerPass + rl * kRowsPerThread;
+    const int r0 = (pass * RL + rl) * kRowsPerThread;
     float a[kRowsPerThread];
 #pragma unroll
     for (int i = 0; i < kRowsPerThread; ++i) {
@@ -71,16 +69,20 @@ __device__ __forceinline__ void bias_partials(typename Vec<T>::raw (&x)[kRowsPer
   }
 }
 
-// grid (column slabs of 8*V channels, batch); 256 threads = 8 column lanes x 32 row lanes;
-// row lane rl takes rows rl*16 .. rl*16+15 of every pass of 512 rows.
+// grid (column slabs of 8*V channels, batch); 8 column lanes x RL row lanes; row lane rl takes rows
+// rl*16 .. rl*16+15 of every pass of 16 RL rows.
 // Pass 1 (update != 0): sums of (q - shift), shift = the old mean (or the window's first
 // query when there is no history), which keeps the squares free of cancellation; pairwise
 // merge into the running mean and M2.  The count n is published by the next kernel of the
 // chain (every workgroup here reads the old one).
 // Pass 2 (m > 1): apart[slab][j] = sum over the slab's channels of (q_jc - mean_c)^2 / var_c.
-// A window of at most 512 rows stays in registers between the passes.
-template <typename T>
-__global__ __launch_bounds__(256) void probe_stats_bias_kernel(const T* __restrict__ q_win,
+// A window of at most 16 RL rows stays in registers between the passes.  RL follows the window's
+// length (launch_probe_t): there is one workgroup per slab however long the window is, and a pass
+// costs a memory round trip, so the more rows are requested at once the better.
+// Windows of 4096 and 2563 tokens, 8 heads of 128 channels (16 slabs): both windows' probe, score,
+// selection and attention 239 us with 32 row lanes here and 64 in weigh, 214 with 128 in both.
+template <typename T, int RL>
+__global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const T* __restrict__ q_win,
                                                                float* __restrict__ stats,
                                                                float* __restrict__ scratch, int update,
                                                                int m, int m_pad, int d, float eps,
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(256) void probe_stats_bias_kernel(const T* __restri
   constexpr int V = Vec<T>::N;
   constexpr int SLAB = kColLanes * V;
   typedef typename Vec<T>::raw raw_t;
-  __shared__ float red[2][kStatsRowLanes][SLAB];
+  __shared__ float red[2][RL][SLAB];
   __shared__ float mu_lds[SLAB], iv_lds[SLAB];
   const int s = blockIdx.y;
   const T* q = q_win + size_t(s) * m * d;
@@ -98,36 +100,48 @@ __global__ __launch_bounds__(256) void probe_stats_bias_kernel(const T* __restri
   const int cl = threadIdx.x % kColLanes, rl = threadIdx.x / kColLanes;
   const int ch0 = blockIdx.x * SLAB + cl * V;
   const bool col_ok = ch0 < d;
+  // the old statistics and the window's first query are requested before the queries: the counter of
+  // outstanding loads is in order, and asked for later they would be a round trip of their own
   const float n_old = st[0];
-  const int n_pass = (m + kStatsRowsPerPass - 1) / kStatsRowsPerPass;
+  const int col = threadIdx.x, ch = blockIdx.x * SLAB + col;      // the first threads: the channel they merge
+  float mean_a = 0.f, m2_a = 0.f, first = 0.f;
+  if (col < SLAB && ch < d) {
+    mean_a = st[4 + ch];
+    m2_a = st[4 + d + ch];
+    first = to_f32(q[ch]);
+  }
+  float c[V], c_first[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) c[v] = c_first[v] = 0.f;
+  if (update && col_ok) {
+#pragma unroll
+    for (int v = 0; v < V; ++v) c[v] = st[4 + ch0 + v];
+    Vec<T>::load(q + ch0, c_first);
+  }
+  const int n_pass = (m + RL * kRowsPerThread - 1) / (RL * kRowsPerThread);
 
   raw_t x[kRowsPerThread];
   auto load_pass = [&](int pass) {
 #pragma unroll
     for (int i = 0; i < kRowsPerThread; ++i) {   // all loads first: they overlap
-      const int r = pass * kStatsRowsPerPass + rl * kRowsPerThread + i;
+      const int r = (pass * RL + rl) * kRowsPerThread + i;
       x[i] = Vec<T>::load_raw(q + size_t(r < m ? r : 0) * d + (col_ok ? ch0 : 0));
     }
   };
   load_pass(0);
 
   if (update) {
-    float c[V], s1[V], s2[V];
+    float s1[V], s2[V];
 #pragma unroll
-    for (int v = 0; v < V; ++v) c[v] = s1[v] = s2[v] = 0.f;
-    if (col_ok) {
-      if (n_old > 0.f) {
-#pragma unroll
-        for (int v = 0; v < V; ++v) c[v] = st[4 + ch0 + v];
-      } else {
-        Vec<T>::load(q + ch0, c);
-      }
+    for (int v = 0; v < V; ++v) {
+      c[v] = n_old > 0.f ? c[v] : c_first[v];
+      s1[v] = s2[v] = 0.f;
     }
     for (int pass = 0; pass < n_pass; ++pass) {
       if (pass > 0) load_pass(pass);
 #pragma unroll
       for (int i = 0; i < kRowsPerThread; ++i) {
-        if (pass * kStatsRowsPerPass + rl * kRowsPerThread + i < m) {
+        if ((pass * RL + rl) * kRowsPerThread + i < m) {
           float f[V];
           Vec<T>::widen(x[i], f);
 #pragma unroll
@@ -147,32 +161,30 @@ __global__ __launch_bounds__(256) void probe_stats_bias_kernel(const T* __restri
     __syncthreads();
   }
   {
-    const int col = threadIdx.x, ch = blockIdx.x * SLAB + col;
     if (col < SLAB && ch >= d) mu_lds[col] = iv_lds[col] = 0.f;
     if (col < SLAB && ch < d) {
       float mean, m2, n_new;
       if (update) {
         float t1 = 0.f, t2 = 0.f;
-#pragma unroll
-        for (int k = 0; k < kStatsRowLanes; ++k) {
+#pragma unroll 16
+        for (int k = 0; k < RL; ++k) {
           t1 += red[0][k][col];
           t2 += red[1][k][col];
         }
         const float nb = float(m);
         n_new = n_old + nb;
-        const float mean_a = st[4 + ch];
-        const float shift = n_old > 0.f ? mean_a : to_f32(q[ch]);
+        const float shift = n_old > 0.f ? mean_a : first;
         const float mean_b = shift + t1 / nb;
         const float m2_b = fmaxf(t2 - t1 * t1 / nb, 0.f);
         const float delta = mean_b - mean_a;
         mean = n_old > 0.f ? mean_a + delta * (nb / n_new) : mean_b;
-        m2 = n_old > 0.f ? st[4 + d + ch] + m2_b + delta * delta * (n_old * nb / n_new) : m2_b;
+        m2 = n_old > 0.f ? m2_a + m2_b + delta * delta * (n_old * nb / n_new) : m2_b;
         st[4 + ch] = mean;
         st[4 + d + ch] = m2;
       } else {
         n_new = n_old;
-        mean = st[4 + ch];
-        m2 = st[4 + d + ch];
+        mean = mean_a;
+        m2 = m2_a;
       }
       const float var = n_new > 1.f ? m2 / (n_new - 1.f) : 0.f;
       mu_lds[col] = mean;
@@ -182,24 +194,7 @@ __global__ __launch_bounds__(256) void probe_stats_bias_kernel(const T* __restri
   if (m == 1) return;   // a single token is its own probe: no weights needed
   __syncthreads();
 
-  bias_partials<T>(x, load_pass, mu_lds, iv_lds, apart, m, m_pad, n_pass, cl, rl);
-}
-
-// probe_kv and the norm of the probe; run by one workgroup that sees the whole probe.
-__device__ __forceinline__ void probe_finish(const float* probe, float* probe_kv, float* probe_norm,
-                                             int n_q_heads, int n_kv_heads, int head_dim,
-                                             float* red) {
-  const int g = n_q_heads / n_kv_heads, d = n_q_heads * head_dim;
-  float ss = 0.f;
-  for (int ch = threadIdx.x; ch < d; ch += blockDim.x) ss += probe[ch] * probe[ch];
-  ss = block_sum(ss, red);
-  if (threadIdx.x == 0) *probe_norm = sqrtf(ss);
-  for (int e = threadIdx.x; e < n_kv_heads * head_dim; e += blockDim.x) {
-    int hk = e / head_dim, dd = e - hk * head_dim;
-    float t = 0.f;
-    for (int i = 0; i < g; ++i) t += probe[(hk * g + i) * head_dim + dd];
-    probe_kv[e] = t;
-  }
+  bias_partials<T, RL>(x, load_pass, mu_lds, iv_lds, apart, m, m_pad, n_pass, cl, rl);
 }
 
 // ---- consecutive windows of one sequence in one call
@@ -492,17 +487,15 @@ __global__ __launch_bounds__(1024) void probe_chain_finish_kernel(
   }
 }
 
-constexpr int kWeighRowLanes = 64;
 constexpr int kWeighRows = 8;    // rows a thread takes per pass
-constexpr int kWeighRowsPerPass = kWeighRowLanes * kWeighRows;
 constexpr int kWeighSlabBatch = 16;
 
-// grid (column slabs of 8*V channels, batch); 512 threads = 8 column lanes x 64 row lanes.
+// grid (column slabs of 8*V channels, batch); 8 column lanes x RL row lanes.
 // Every workgroup adds the slabs' partials up to a_j (slab order), turns them into the
 // weights of Eq. (9) and sums w_j q_j over all rows for its channels.  The queries of the
 // first pass are requested before the partials, so both are in flight together.
-template <typename T>
-__global__ __launch_bounds__(512) void probe_weigh_kernel(const T* __restrict__ q_win,
+template <typename T, int RL>
+__global__ __launch_bounds__(kColLanes * RL) void probe_weigh_kernel(const T* __restrict__ q_win,
                                                           const float* __restrict__ scratch,
                                                           float* __restrict__ stats, int add_count,
                                                           int mean_pooling,
@@ -512,10 +505,11 @@ __global__ __launch_bounds__(512) void probe_weigh_kernel(const T* __restrict__ 
                                                           size_t scratch_stride, size_t stats_stride) {
   constexpr int V = Vec<T>::N;
   constexpr int SLAB = kColLanes * V;
+  constexpr int kThreads = kColLanes * RL, kRows = RL * kWeighRows;      // threads, rows of a pass
   typedef typename Vec<T>::raw raw_t;
   __shared__ float red[32];
   __shared__ float w_lds[kMaxWindow];
-  __shared__ float buf[8][SLAB];
+  __shared__ float buf[kThreads / 64][SLAB];
   const int s = blockIdx.y;
   const T* q = q_win + size_t(s) * m * d;
   const float* apart = scratch + size_t(s) * scratch_stride;
@@ -528,14 +522,14 @@ __global__ __launch_bounds__(512) void probe_weigh_kernel(const T* __restrict__ 
   auto load_pass = [&](int pass) {
 #pragma unroll
     for (int i = 0; i < kWeighRows; ++i) {
-      const int r = pass * kWeighRowsPerPass + rl * kWeighRows + i;
+      const int r = pass * kRows + rl * kWeighRows + i;
       x[i] = Vec<T>::load_raw(q + size_t(r < m ? r : 0) * d + (col_ok ? ch0 : 0));
     }
   };
   load_pass(0);
 
   float tsum = 0.f;
-  for (int j = threadIdx.x; j < m && !mean_pooling; j += 512) {
+  for (int j = threadIdx.x; j < m && !mean_pooling; j += kThreads) {
     float t = 0.f;
     for (int s0 = 0; s0 < n_slabs; s0 += kWeighSlabBatch) {
       float p[kWeighSlabBatch];
@@ -555,12 +549,12 @@ __global__ __launch_bounds__(512) void probe_weigh_kernel(const T* __restrict__ 
   float acc[V];
 #pragma unroll
   for (int v = 0; v < V; ++v) acc[v] = 0.f;
-  const int n_pass = (m + kWeighRowsPerPass - 1) / kWeighRowsPerPass;
+  const int n_pass = (m + kRows - 1) / kRows;
   for (int pass = 0; pass < n_pass; ++pass) {
     if (pass > 0) load_pass(pass);
 #pragma unroll
     for (int i = 0; i < kWeighRows; ++i) {
-      const int r = pass * kWeighRowsPerPass + rl * kWeighRows + i;
+      const int r = pass * kRows + rl * kWeighRows + i;
       const float w = r < m ? (total > 0.f ? w_lds[r] * inv_total : uniform) : 0.f;
       float f[V];
       Vec<T>::widen(x[i], f);
@@ -568,7 +562,7 @@ __global__ __launch_bounds__(512) void probe_weigh_kernel(const T* __restrict__ 
       for (int v = 0; v < V; ++v) acc[v] += w * f[v];
     }
   }
-  // the 8 row lanes of a wave first, then the 8 waves through LDS
+  // the 8 row lanes of a wave first, then the waves through LDS
 #pragma unroll
   for (int v = 0; v < V; ++v) {
     acc[v] += __shfl_xor(acc[v], 8, 64);
@@ -586,27 +580,41 @@ __global__ __launch_bounds__(512) void probe_weigh_kernel(const T* __restrict__ 
     if (ch < d) {
       float t = 0.f;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) t += buf[i][threadIdx.x];
+      for (int i = 0; i < kThreads / 64; ++i) t += buf[i][threadIdx.x];
       probe_out[size_t(s) * d + ch] = t;
     }
   }
   if (blockIdx.x == 0 && weights_out != nullptr) {
-    for (int j = threadIdx.x; j < m; j += 512)
+    for (int j = threadIdx.x; j < m; j += kThreads)
       weights_out[size_t(s) * m + j] = total > 0.f ? w_lds[j] * inv_total : uniform;
   }
 }
 
-// One workgroup per sequence that sees the whole probe.
-__global__ __launch_bounds__(1024) void probe_finish_kernel(const float* __restrict__ probe,
-                                                            float* __restrict__ probe_kv_out,
-                                                            float* __restrict__ probe_norm_out,
-                                                            int n_q_heads, int n_kv_heads,
-                                                            int head_dim) {
+// One workgroup per sequence: the norm of the probe and its per-KV-head sum.  All latency (one
+// workgroup, 16 KB), so every element is read once, 16 bytes a lane, and serves both.
+constexpr int kFinishThreads = 512;
+__global__ __launch_bounds__(kFinishThreads) void probe_finish_kernel(const float* __restrict__ probe,
+                                                                      float* __restrict__ probe_kv_out,
+                                                                      float* __restrict__ probe_norm_out,
+                                                                      int n_q_heads, int n_kv_heads,
+                                                                      int head_dim) {
   __shared__ float red[32];
-  const int s = blockIdx.x;
-  probe_finish(probe + size_t(s) * n_q_heads * head_dim,
-               probe_kv_out + size_t(s) * n_kv_heads * head_dim, probe_norm_out + s, n_q_heads,
-               n_kv_heads, head_dim, red);
+  const int s = blockIdx.x, g = n_q_heads / n_kv_heads, dk = n_kv_heads * head_dim;
+  const float* p = probe + size_t(s) * n_q_heads * head_dim;
+  float ss = 0.f;
+  for (int e = threadIdx.x * 4; e < dk; e += kFinishThreads * 4) {     // (head_dim is a multiple of 4)
+    const int hk = e / head_dim, dd = e - hk * head_dim;
+    f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int i = 0; i < g; ++i) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(p + (hk * g + i) * head_dim + dd);
+      ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+      t += v;
+    }
+    *reinterpret_cast<f32x4*>(probe_kv_out + size_t(s) * dk + e) = t;
+  }
+  ss = block_sum(ss, red);
+  if (threadIdx.x == 0) probe_norm_out[s] = sqrtf(ss);
 }
 
 // A window of one token (decode): the probe is the query (probe_identity.h).
@@ -676,8 +684,14 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
   }
   update_stats &= ACTQKV_STATS_UPDATE;
   if (update_stats || (m > 1 && !mean_pooling)) {
-    hipLaunchKernelGGL(probe_stats_bias_kernel<T>, dim3(n_slabs, batch), dim3(256), 0, stream, q_win,
-                       stats, scratch, update_stats, m, m_pad, d, eps, stats_stride, scratch_stride);
+    // the fewest row lanes that hold the window in registers, 128 at most (a workgroup has 1024 threads)
+    auto launch = [&](auto kernel, int row_lanes) {
+      hipLaunchKernelGGL(kernel, dim3(n_slabs, batch), dim3(kColLanes * row_lanes), 0, stream, q_win, stats, scratch,
+                         update_stats, m, m_pad, d, eps, stats_stride, scratch_stride);
+    };
+    if (m <= 32 * kRowsPerThread) launch(probe_stats_bias_kernel<T, 32>, 32);
+    else if (m <= 64 * kRowsPerThread) launch(probe_stats_bias_kernel<T, 64>, 64);
+    else launch(probe_stats_bias_kernel<T, 128>, 128);
   }
   if (m == 1) {
     hipLaunchKernelGGL(probe_identity_kernel<T>, dim3(batch), dim3(1024), size_t(d) * sizeof(float),
@@ -686,10 +700,13 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
                        sh.n_kv_heads, sh.head_dim);
     return hip_status("probe");
   }
-  hipLaunchKernelGGL(probe_weigh_kernel<T>, dim3(n_slabs, batch), dim3(512), 0, stream, q_win, scratch,
-                     stats, update_stats, mean_pooling, probe, weights, m, m_pad, n_slabs, d, scratch_stride,
-                     stats_stride);
-  hipLaunchKernelGGL(probe_finish_kernel, dim3(batch), dim3(1024), 0, stream, probe, probe_kv,
+  auto weigh = [&](auto kernel, int row_lanes) {
+    hipLaunchKernelGGL(kernel, dim3(n_slabs, batch), dim3(kColLanes * row_lanes), 0, stream, q_win, scratch, stats,
+                       update_stats, mean_pooling, probe, weights, m, m_pad, n_slabs, d, scratch_stride, stats_stride);
+  };
+  if (m <= 64 * kWeighRows) weigh(probe_weigh_kernel<T, 64>, 64);
+  else weigh(probe_weigh_kernel<T, 128>, 128);
+  hipLaunchKernelGGL(probe_finish_kernel, dim3(batch), dim3(kFinishThreads), 0, stream, probe, probe_kv,
                      probe_norm, sh.n_q_heads, sh.n_kv_heads, sh.head_dim);
   (void)V;
   return hip_status("probe");

@@ -280,6 +280,33 @@ def test_probe_with_statistics_used_as_they_are(dtype):
     assert int(torch.argmax(wts[0])) == 7
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("m", [2, 511, 512, 513, 1024, 1025, 2048, 2049])
+def test_probe_at_the_edges_of_its_row_lanes(m, dtype):
+    """The lengths where build_probe takes more row lanes per workgroup or another pass over the
+    window, behind a window that leaves statistics, against the oracle."""
+    hq, hkv, d, m0 = 6, 2, 64, 300
+    sh = LayerShape(hq, hkv, d, 128, 4, 128, 256, dtype)
+    cs = B.c_shape(sh)
+    g = torch.Generator().manual_seed(m)
+    q = (torch.randn(m0 + m, hq, d, generator=g) * 1.3 + 0.2).to(sh.torch_dtype)
+    q[m0 + m // 2, :, 5] *= 9.0
+    qd = q.to(DEV)
+    runner = H.LayerRunner(sh, 1, max(m, m0), 8, 4, DEV)
+    wts = torch.zeros(1, m, device=DEV)
+    stats = orc.RunningStats(hq * d)
+    for lo, hi, w in ((0, m0, None), (m0, m0 + m, wts)):
+        B.build_probe(cs, 1, hi - lo, qd[lo:hi].contiguous(), runner.stats, True, runner.probe, runner.probe_kv,
+                      runner.probe_norm, w, runner.workspace)
+        torch.cuda.synchronize()
+        qw = f64(q[lo:hi]).reshape(hi - lo, -1)
+        probe, weights = orc.probe_query(qw, orc.activation_bias(qw, *stats.update(qw)))
+    assert rel_to_max(runner.probe[0], probe) < TOL_PROBE and rel_to_max(wts[0], weights) < TOL_WEIGHT
+    p = np.asarray(probe).reshape(hkv, hq // hkv, d)
+    assert rel_to_max(runner.probe_kv.reshape(-1), p.sum(1).reshape(-1)) < TOL_PROBE
+    assert abs(float(runner.probe_norm[0]) / float(np.linalg.norm(p)) - 1) < TOL_PROBE
+
+
 def test_probe_of_the_largest_window():
     """actqkv_build_probe with m = 8192, the largest window the library takes, against the oracle
     (statistics of two windows, bias, weights, probe)."""
