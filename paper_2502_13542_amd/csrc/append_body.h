@@ -39,24 +39,46 @@ __device__ __forceinline__ void append_body(int role, int seg, int s, const T* _
     const size_t tile = (size_t(block) * n_kv_heads + hk) * kBlock * head_dim;
     T* kd = k_cache + size_t(s) * cache_stride + tile + size_t(j0) * head_dim;
     T* vd = v_cache + size_t(s) * cache_stride + tile;
-    T* vt = reinterpret_cast<T*>(ap_lds);                           // [head_dim][kBlock + 2]
-    constexpr int kPad = kBlock + 2;
-    const int chunks = head_dim / V;
-    for (int i = threadIdx.x; i < n_tok * chunks; i += kThreads) {
-      const int tk = i / chunks, c = i - tk * chunks;
-      const size_t src = size_t(lo - pos0 + tk) * row_len + size_t(hk) * head_dim + c * V;
-      const typename Vec<T>::raw kraw = Vec<T>::load_raw(kn + src);
-      const typename Vec<T>::raw vraw = Vec<T>::load_raw(vn + src);
-      *reinterpret_cast<typename Vec<T>::raw*>(kd + size_t(tk) * head_dim + c * V) = kraw;
-      alignas(16) T ve[V];
-      *reinterpret_cast<typename Vec<T>::raw*>(ve) = vraw;
+    T* vt = reinterpret_cast<T*>(ap_lds);                           // [head_dim][kBlock + 2], by place in the block
+    constexpr int kPad = kBlock + 2, kBatch = 2;
+    typedef typename Vec<T>::raw raw_t;
+    const int chunks = head_dim / V, n = n_tok * chunks;
+    for (int i0 = threadIdx.x; i0 < n; i0 += kBatch * kThreads) {
+      raw_t kraw[kBatch], vraw[kBatch];
 #pragma unroll
-      for (int e = 0; e < V; ++e) vt[(c * V + e) * kPad + tk] = ve[e];
+      for (int b = 0; b < kBatch; ++b) {                             // all loads first: they overlap
+        const int i = i0 + b * kThreads < n ? i0 + b * kThreads : i0;
+        const int tk = i / chunks, c = i - tk * chunks;
+        const size_t src = size_t(lo - pos0 + tk) * row_len + size_t(hk) * head_dim + c * V;
+        kraw[b] = Vec<T>::load_raw(kn + src);
+        vraw[b] = Vec<T>::load_raw(vn + src);
+      }
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) {
+        const int i = i0 + b * kThreads;
+        if (i < n) {
+          const int tk = i / chunks, c = i - tk * chunks;
+          *reinterpret_cast<raw_t*>(kd + size_t(tk) * head_dim + c * V) = kraw[b];
+          alignas(16) T ve[V];
+          *reinterpret_cast<raw_t*>(ve) = vraw[b];
+#pragma unroll
+          for (int e = 0; e < V; ++e) vt[(c * V + e) * kPad + j0 + tk] = ve[e];
+        }
+      }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < head_dim * n_tok; i += kThreads) {
-      const int d = i / n_tok, tk = i - d * n_tok;
-      vd[size_t(d) * kBlock + j0 + tk] = vt[d * kPad + tk];
+    // V neighbouring places of a channel's row per lane: one 16-byte store where all of them are new
+    const int g0 = j0 / V, groups = (j0 + n_tok - 1) / V - g0 + 1;
+    for (int i = threadIdx.x; i < head_dim * groups; i += kThreads) {
+      const int d = i / groups, j = (g0 + i - d * groups) * V;
+      const T* from = vt + d * kPad + j;
+      T* to = vd + size_t(d) * kBlock + j;
+      if (j >= j0 && j + V <= j0 + n_tok) {
+        const uint32_t* w = reinterpret_cast<const uint32_t*>(from);           // (an even number of elements in)
+        *reinterpret_cast<u32x4*>(to) = u32x4{w[0], w[1], w[2], w[3]};
+      } else {
+        for (int t = max(j0 - j, 0); t < min(V, j0 + n_tok - j); ++t) to[t] = from[t];
+      }
     }
     return;
   }
@@ -64,7 +86,7 @@ __device__ __forceinline__ void append_body(int role, int seg, int s, const T* _
   // ---- representatives of the block, if these tokens complete it
   if (hi != block * kBlock + kBlock || rep_keys == nullptr) return;
   float* norm = reinterpret_cast<float*>(ap_lds);                  // [kBlock]
-  int* chosen = reinterpret_cast<int*>(ap_lds) + kBlock;           // [kBlock]: output slot or -1
+  int* chosen = reinterpret_cast<int*>(ap_lds) + kBlock;           // [kBlock]
   const T* kb = k_cache + size_t(s) * cache_stride + size_t(block) * n_kv_heads * kBlock * head_dim;
   auto token_chunk = [&](int tk, int c) -> const T* {   // chunk c (V elements) of the token's [Hk][D] keys
     const int pos = block * kBlock + tk;
@@ -99,34 +121,37 @@ __device__ __forceinline__ void append_body(int role, int seg, int s, const T* _
     }
   }
   __syncthreads();
-  if (threadIdx.x < kBlock) {
-    const int i = threadIdx.x;
-    const float mine = norm[i];
-    int rank = 0;
-    for (int j = 0; j < kBlock; ++j) {
-      const float o = norm[j];
-      rank += (o > mine) || (o == mine && j < i);
+  {
+    // the place of a token among all of them: 8 neighbouring lanes compare it with 16 tokens each
+    const int part = threadIdx.x & 7;
+    for (int tk = threadIdx.x >> 3; tk < kBlock; tk += kThreads >> 3) {
+      const float mine = norm[tk];
+      int rank = 0;
+#pragma unroll
+      for (int i = 0; i < kBlock / 8; ++i) {
+        const int j = part + 8 * i;
+        const float o = norm[j];
+        rank += (o > mine) || (o == mine && j < tk);
+      }
+      rank += __shfl_xor(rank, 1, 64);
+      rank += __shfl_xor(rank, 2, 64);
+      rank += __shfl_xor(rank, 4, 64);
+      if (part == 0) chosen[tk] = rank < n_rep ? 1 : 0;
     }
-    chosen[i] = rank < n_rep ? 1 : 0;
   }
   __syncthreads();
-  int slot_of_mine = -1;
-  if (threadIdx.x < kBlock) {
-    const int i = threadIdx.x;
-    int before = 0;
-    for (int j = 0; j < i; ++j) before += chosen[j];
-    slot_of_mine = chosen[i] ? before : -1;
-  }
-  __syncthreads();
-  if (threadIdx.x < kBlock) chosen[threadIdx.x] = slot_of_mine;
-  __syncthreads();
+  // every wavefront has the chosen tokens as two masks; slot r takes the r-th of them
+  static_assert(kBlock == 128, "two masks of 64 tokens");
+  const unsigned long long first = __ballot(chosen[threadIdx.x & 63]), second = __ballot(chosen[64 + (threadIdx.x & 63)]);
+  const int n_first = __popcll(first), n_chosen = min(n_first + __popcll(second), n_rep);
   T* rd = rep_keys + size_t(s) * rep_stride + size_t(block) * n_rep * row_len;
-  for (int i = threadIdx.x; i < kBlock * chunks; i += kThreads) {
-    const int tk = i / chunks, c = i - tk * chunks;
-    const int slot = chosen[tk];
-    if (slot >= 0)
-      *reinterpret_cast<typename Vec<T>::raw*>(rd + size_t(slot) * row_len + size_t(c) * V) =
-          Vec<T>::load_raw(token_chunk(tk, c));
+  for (int i = threadIdx.x; i < n_chosen * chunks; i += kThreads) {
+    const int slot = i / chunks, c = i - slot * chunks;
+    unsigned long long left = slot < n_first ? first : second;
+    for (int r = slot < n_first ? slot : slot - n_first; r > 0; --r) left &= left - 1;
+    const int tk = __ffsll(left) - 1 + (slot < n_first ? 0 : 64);
+    *reinterpret_cast<typename Vec<T>::raw*>(rd + size_t(slot) * row_len + size_t(c) * V) =
+        Vec<T>::load_raw(token_chunk(tk, c));
   }
 }
 

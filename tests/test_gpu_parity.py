@@ -1313,6 +1313,42 @@ def test_append_kv_builds_the_cache_and_the_representatives(dtype, hq, hkv, d, c
     assert not rep[n // 128:].any(), "representatives of an incomplete block were written"
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("fp32", 64), ("fp32", 128)])
+@pytest.mark.parametrize("pos0,m", [(0, 128), (0, 7), (1, 8), (7, 2), (8, 120), (3, 381), (127, 130)])
+def test_append_kv_at_the_edges_of_its_stores(dtype, d, pos0, m):
+    """Chunks that begin and end inside a group of values stored together: what is new lands, what lay
+    beside it stays.  Keys of equal norm: the representatives are the first of them."""
+    hk, nb, r = 2, 4, 4
+    sh = LayerShape(4, hk, d, 128, r, 128, 256, dtype)
+    g = torch.Generator().manual_seed(pos0 * 1000 + m + d)
+    k = torch.randn(nb * 128, hk, d, generator=g).sign().to(sh.torch_dtype)
+    v = torch.randn(nb * 128, hk, d, generator=g).to(sh.torch_dtype)
+    k[[5, 64, 200, 330]] *= 2
+    kd, vd = k.to(DEV), v.to(DEV)
+    want_k, want_v = H.blocked_k(kd, sh, nb), H.blocked_vt(vd, sh, nb)
+    kc, vc = torch.full_like(want_k, 9.0), torch.full_like(want_v, 9.0)
+    # the tokens before the chunk are in the cache already
+    old = torch.zeros(nb, 128, dtype=torch.bool, device=DEV)
+    new = old.clone()
+    old.view(-1)[:pos0] = True
+    new.view(-1)[pos0:pos0 + m] = True
+    at_k, at_v = (lambda x: x[:, None, :, None]), (lambda x: x[:, None, None, :])
+    kc, vc = torch.where(at_k(old), want_k, kc), torch.where(at_v(old), want_v, vc)
+    expect_k, expect_v = torch.where(at_k(new), want_k, kc), torch.where(at_v(new), want_v, vc)
+    rep = torch.full((nb, r, hk, d), 5.0, dtype=sh.torch_dtype, device=DEV)
+    B.append_kv(B.c_shape(sh), 1, m, kd[pos0:pos0 + m].contiguous(), vd[pos0:pos0 + m].contiguous(),
+                torch.tensor([pos0], dtype=torch.int32, device=DEV), kc, vc, 0, rep, 0, nb)
+    torch.cuda.synchronize()
+    assert torch.equal(kc, expect_k) and torch.equal(vc, expect_v)
+    done = range(pos0 // 128, (pos0 + m) // 128)
+    expect = torch.full_like(rep, 5.0).cpu()
+    for b in done:
+        norm = (k[b * 128:(b + 1) * 128].double() ** 2).sum((1, 2))
+        best = sorted(range(128), key=lambda i: (-float(norm[i]), i))[:r]
+        expect[b] = k[[b * 128 + i for i in sorted(best)]]
+    assert torch.equal(rep.cpu(), expect)
+
+
 def test_append_kv_on_random_chunk_sequences():
     """20 random shapes and sequences of chunk lengths (single tokens, pieces that end on, just
     before and just behind block boundaries, long windows); half of the single tokens go through
