@@ -38,7 +38,7 @@ def main() -> int:
     n = args.calls
     lines = [f"# {args.title}", ""]
     if args.command:
-        lines += ["Commands (from /tmp on the GPU box, TMPDIR=/tmp; one counter group per run):", "", "```",
+        lines += ["Commands (from /tmp, TMPDIR=/tmp; one counter group per run):", "", "```",
                   args.command, "```", ""]
     lines += [f"Sums over the dispatches of {args.kernel} in one pass, divided by the {n} calls of the pass "
               f"({len(next(iter(disp.values()), ()))} dispatches).", "",

@@ -54,7 +54,7 @@ def main() -> int:
             groups[(name, wg)].append(t1 - t0)
     lines = [f"# {args.title}", ""]
     if args.command:
-        lines += ["Command (from /tmp on the GPU box, TMPDIR=/tmp, repository at $GRAFT_REPO_ROOT):", "",
+        lines += ["Command (from /tmp, TMPDIR=/tmp, repository at $GRAFT_REPO_ROOT):", "",
                   "```", args.command, "```", ""]
     lines += ["Kernels of libactqkv.so from the kernel trace; durations in microseconds (start to end stamp of "
               "the dispatch); \"workgroups\" is given where launches of one kernel are listed per launch shape.", "",
