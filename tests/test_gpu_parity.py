@@ -414,6 +414,38 @@ def test_prefill_attention_at_the_edges_of_its_tiles(dtype, d, group, m, nw):
             assert out_error(out[i * m + r], ref) < TOL_OUT[dtype], (i, r)
 
 
+@pytest.mark.parametrize("d,group,m,nw", [(64, 4, 1, 6), (64, 8, 1, 300)])
+def test_probabilities_keep_more_than_bf16(d, group, m, nw):
+    """The calls whose probabilities are not rounded to bf16 before the product with the values: every element
+    is the exact result rounded to bf16 (2^-8) but for 2^-14 of sum_j p_j |v_j| (two bf16 terms leave 2^-16 of a
+    probability, the fp32 score of 64 to 128 products below 2^-16, its exponential and the fp32 sums below 2^-16
+    each).  The queries are long, so few keys carry a row and a rounding of a probability to bf16 shows."""
+    sh = LayerShape(2 * group, 2, d, 128, 4, 128, 256, "bf16")
+    cs = B.c_shape(sh)
+    k_cap, base = 4, 9 * 128 + 37
+    nb = (base + nw * m + 127) // 128
+    g = torch.Generator().manual_seed(d + group + m)
+    q = (4 * torch.randn(nw * m, 2 * group, d, generator=g)).to(torch.bfloat16)
+    k = torch.randn(nb * 128, 2, d, generator=g).to(torch.bfloat16)
+    v = torch.randn(nb * 128, 2, d, generator=g).to(torch.bfloat16)
+    w0 = [base + i * m for i in range(nw)]
+    idx = torch.stack([(torch.randperm(H.eligible_range(sh, w)[1] - 1, generator=g)[:k_cap] + 1).int() for w in w0])
+    out = torch.zeros(nw * m, 2 * group, d, dtype=torch.bfloat16, device=DEV)
+    ws = torch.zeros(B.workspace_bytes(cs, nw, m, nb, k_cap), dtype=torch.uint8, device=DEV)
+    B.retrieval_attention(cs, nw, m, q.to(DEV), H.blocked_k(k.to(DEV), sh, nb), H.blocked_vt(v.to(DEV), sh, nb), 0, nb,
+                          torch.tensor([w + m for w in w0], dtype=torch.int32, device=DEV), idx.to(DEV),
+                          torch.full((nw,), k_cap, dtype=torch.int32, device=DEV), k_cap, out, None, ws)
+    torch.cuda.synchronize()
+    worst = 0.
+    for i in sorted({0, nw // 2, nw - 1}):
+        for r in sorted({0, min(40, m - 1), m // 2, m - 1}):
+            pos = orc.key_positions(w0[i], w0[i] + r, idx[i].tolist(), sh.n_init, sh.n_local, 128)
+            ref = orc.attention_rows(f64(q[i * m + r])[None], f64(k), f64(v), pos, group)[0]
+            size = orc.attention_rows(f64(q[i * m + r])[None], f64(k), np.abs(f64(v)), pos, group)[0]
+            worst = max(worst, float((np.abs(f64(out[i * m + r]) - ref) / (2. ** -8 * np.abs(ref) + 2. ** -14 * size)).max()))
+    assert worst <= 1., worst
+
+
 @pytest.mark.parametrize("dtype,d,m,n_ctx", [("bf16", 128, 2, 700), ("bf16", 128, 33, 1500), ("fp32", 64, 3, 500)])
 def test_tiny_windows(dtype, d, m, n_ctx):
     """Windows of 2, 3 and 33 tokens (most rows of a query tile idle, a ragged last window)."""
