@@ -38,6 +38,9 @@ namespace actqkv {
 
 constexpr int kPfThreads = 512;
 constexpr int kPfWaves = 8;
+// Whether key tiles may be cut into pieces: fp32 partial results of a whole query tile with 128 channels would be
+// twice kPfPartialFloats (and 256 of them more than the library's own scratch array holds).
+template <int D, int KS, bool kTwoTermP> constexpr bool kPfPieces = D == 64 || KS > 1 || !kTwoTermP;
 template <int KS> constexpr int kPfRows = 32 * kPfWaves / KS;   // query rows of a workgroup
 template <int D> constexpr int kPfTileBytes = kBlock * D * 2;           // one K or V^T tile of a (block, KV head)
 template <int D> constexpr int kPfLdsBytes = 2 * 2 * kPfTileBytes<D>;   // 2 stages x (K, V^T)
@@ -126,8 +129,8 @@ __device__ __forceinline__ void store_rows(const PfParams& p, const f32x16 (&acc
     p.lse[(size_t(s) * p.n_q_heads + head) * p.m + my_row] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
 }
 
-// One work item: piece `slot` of the query tiles of (sequence s, KV head hk).
-template <int D, int KS, bool kInLoop>
+// One work item: piece `slot` of the query tiles of (sequence s, KV head hk).  kTwoTermP: see prefill_two_terms.
+template <int D, int KS, bool kTwoTermP, bool kInLoop>
 __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* lds, int hk, int slot, int s) {
   constexpr int kDb = D / 32, kKs = D / 16;      // 32-channel groups of the output, 16-channel steps of a score
   constexpr int kRows = kPfRows<KS>, kRowGroups = kPfWaves / KS;   // query rows, groups of 32 of them
@@ -382,14 +385,27 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
       // ---- O^T += V^T P^T.  Written in issue order: the exponentials of the next 32 keys sit
       // between the MFMAs of these 32 (the vector ALU works while the matrix pipe does), and every
       // V^T operand is read 8 MFMAs ahead.  The row sums add the bf16 probabilities the product
-      // itself uses, a pair per instruction, each lane summing its own 64 keys of the tile.
+      // itself uses, a pair per instruction, each lane summing its own 64 keys of the tile (with two
+      // terms the fp32 ones).
 #pragma unroll
       for (int g8 = 0; g8 < 2 * kNg; ++g8) {
         const int kb = g8 >> 1, s2 = g8 & 1;
         const bf16x8 pb = pack8(acc_s[kb][8 * s2 + 0], acc_s[kb][8 * s2 + 1], acc_s[kb][8 * s2 + 2],
                                 acc_s[kb][8 * s2 + 3], acc_s[kb][8 * s2 + 4], acc_s[kb][8 * s2 + 5],
                                 acc_s[kb][8 * s2 + 6], acc_s[kb][8 * s2 + 7]);
-        add_bf16x8(l_run, pb, bf16_ones);
+        bf16x8 pl;                         // with two terms: what the rounding to bf16 left of the probabilities
+        if constexpr (kTwoTermP) {
+          typedef __attribute__((ext_vector_type(8))) float f32x8;
+          const f32x8 wide = __builtin_convertvector(pb, f32x8);
+          float left[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) left[i] = acc_s[kb][8 * s2 + i] - wide[i];
+#pragma unroll
+          for (int i = 0; i < 8; i += 2) l_run += acc_s[kb][8 * s2 + i] + acc_s[kb][8 * s2 + i + 1];
+          pl = pack8(left[0], left[1], left[2], left[3], left[4], left[5], left[6], left[7]);
+        } else {
+          add_bf16x8(l_run, pb, bf16_ones);
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int db = 0; db < kDb; ++db) {
@@ -402,6 +418,8 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
           __builtin_amdgcn_sched_barrier(0);
           const int j = kDb * g8 + db;
           acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vring[j % kVRing]), pb, acc_o[db], 0, 0, 0);
+          if constexpr (kTwoTermP)
+            acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vring[j % kVRing]), pl, acc_o[db], 0, 0, 0);
           if (j + kVRing < kValue) vring[j % kVRing] = v_read(j + kVRing);
         }
       }
@@ -469,14 +487,14 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     }
     m_run = m_all;
   }
-  if (splits == 1) {
+  if (splits == 1 || !kPfPieces<D, KS, kTwoTermP>) {
     if (row_ok && has_mine) store_rows<D, kMine>(p, acc_f, db0, m_run, l_tot, s, my_row, head, half);
     return;
   }
   // The piece stores its output in the order the registers hold it (register-major, lane-minor: every
   // store instruction writes one contiguous 512-byte row), plus its running max and sum: of a whole
-  // query tile normalised and as bf16 (64 KB), of fewer rows as it is.
-  constexpr bool kHalf = KS == 1;
+  // query tile of one-term probabilities normalised and as bf16 (64 KB), otherwise as it is.
+  constexpr bool kHalf = KS == 1 && !kTwoTermP;
   constexpr int kPerGroup = kHalf ? 4 : 8;         // 64-bit words of a channel group
   constexpr int kWords = kPerGroup * kMine + 1;    // 64-bit words per lane: the output, then (max, sum)
   __shared__ int last_flag;
@@ -581,14 +599,14 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
 // how many blocks they retrieve, and a fixed assignment would wait for the unluckiest
 // workgroup.  Nobody waits for anybody: a workgroup leaves when the counter runs out, and the
 // last one to leave puts the counters back to zero for the next launch.
-template <int D, int KS>
+template <int D, int KS, bool kTwoTermP>
 __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_kernel(PfParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   const int item = blockIdx.x / p.n_kv_heads, s = item / p.slots;
-  attn_prefill_item<D, KS, false>(p, lds, blockIdx.x % p.n_kv_heads, item - s * p.slots, s);
+  attn_prefill_item<D, KS, kTwoTermP, false>(p, lds, blockIdx.x % p.n_kv_heads, item - s * p.slots, s);
 }
 
-template <int D, int KS>
+template <int D, int KS, bool kTwoTermP>
 __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_queued_kernel(PfParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   __shared__ int next_item;
@@ -630,7 +648,7 @@ __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_queued_kernel(Pf
       s = order[s];
       slot = p.slots - 1 - slot;
     }
-    attn_prefill_item<D, KS, true>(p, lds, hk, __builtin_amdgcn_readfirstlane(slot), __builtin_amdgcn_readfirstlane(s));
+    attn_prefill_item<D, KS, kTwoTermP, true>(p, lds, hk, __builtin_amdgcn_readfirstlane(slot), __builtin_amdgcn_readfirstlane(s));
     __syncthreads();                         // everybody is done with the LDS tiles of this item
     item = draw();
   }
@@ -649,6 +667,18 @@ bool prefill_mfma_supported(const actqkv_shape& sh, int m) {
   return sh.dtype == ACTQKV_BF16 && m > 1 && sh.n_q_heads / sh.n_kv_heads <= 8;
 }
 
+// Two-term probabilities: they enter the second product as the value rounded to bf16 plus what the rounding left,
+// again as bf16, which keeps 16 of their bits; their sums and the partial results are fp32.  Always with 64
+// channels, and with 128 where the longest possible tile list (64 selected blocks) passes 96 tiles: these calls
+// had fp32 probabilities before they came to the matrix cores, the others have always had bf16 ones.
+// Relative error against 64 bits, a window of 4096 tokens, 32 query and 8 KV heads of 64 channels: 2.2954e-3 with
+// one term, 1.6583e-3 with two and as fp32, which is what the rounding of the output alone gives; 128 channels:
+// 2.3107e-3, 1.6582e-3, 1.6582e-3.  It costs half as many MFMAs again: 158 -> 210 us, 235 -> 317 us; a window of 256 tokens of
+// 8 query and 2 KV heads of 64 channels 13.5 -> 14.0 us.  (As one thread per query row: 10.7 ms, 27.8 ms, 1.4 ms.)
+static bool prefill_two_terms(const actqkv_shape& sh, int m) {
+  return sh.head_dim == 64 || sh.n_init / kBlock + 64 + sh.n_local / kBlock + (m + kBlock - 1) / kBlock + 2 > 96;
+}
+
 static int prefill_mfma_qtiles(const actqkv_shape& sh, int m, int ks) {
   const int rows = kPfRows<1> / ks;
   return (m * (sh.n_q_heads / sh.n_kv_heads) + rows - 1) / rows;
@@ -662,8 +692,11 @@ static int prefill_mfma_qtiles(const actqkv_shape& sh, int m, int ks) {
 // workgroup (its wavefronts share the keys of a tile and merge in LDS) there are fewer pieces and
 // less to merge, but a tile costs 16 % (2 sharing) or 69 % (4) more per row.  The choice is the least of
 // what the busiest compute unit needs by these measured figures, in us; windows of 512 tokens, 32
-// query and 8 KV heads, 10 blocks: 35.8 as 256 rows in 4 pieces, 32.3 as 128 rows in 2, 34.8 as 64 rows
+// query and 8 KV heads of 128 channels, 10 blocks: 35.8 as 256 rows in 4 pieces, 32.3 as 128 rows in 2, 34.8 as 64 rows
 // in one; 128 tokens: 28.7, 20.4, 17.1; 32 windows of 512 in a call: 597, 692, 1009.
+// With 64 channels a tile is half the work and with two-term probabilities half as much again, in the same
+// proportions: over windows of 32 to 4096 tokens and groups of 1, 4 and 7 heads (3500 to 8192 tokens with 128 channels), alone and up
+// to 32 in a call, the choice took at most 8 % longer than the best of the three, as a rule 0 to 3 %.
 PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
   PfSplits r{1, 0, 1, 1, 1};
   if (!prefill_mfma_supported(sh, m)) return r;
@@ -681,8 +714,9 @@ PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int
     // pieces where the query tiles leave compute units idle, never more than 8 per query tile; of whole
     // query tiles, what does not divide evenly goes to the last ones of the window
     const int per_pair = std::max(cus / pairs, c.n_qtiles);    // workgroups one pair may have
-    c.s_lo = std::min(per_pair / c.n_qtiles, kMaxPfSplits);
-    c.rem = c.s_lo == kMaxPfSplits || c.ks > 1 ? 0 : per_pair - c.s_lo * c.n_qtiles;
+    const bool pieces = sh.head_dim == 64 || c.ks > 1 || !prefill_two_terms(sh, m);    // kPfPieces
+    c.s_lo = pieces ? std::min(per_pair / c.n_qtiles, kMaxPfSplits) : 1;
+    c.rem = c.s_lo == kMaxPfSplits || c.ks > 1 || !pieces ? 0 : per_pair - c.s_lo * c.n_qtiles;
     c.slots = c.s_lo * c.n_qtiles + c.rem;
     const double rounds = double(pairs) * c.slots / cus;
     double us = std::max(std::ceil(longest / c.s_lo), rounds * average / c.s_lo) * kTileUs[i] + kItemUs * std::max(rounds, 1.);
@@ -703,34 +737,34 @@ size_t prefill_partials_most(const actqkv_shape& sh, int batch, int m) {
 }
 
 // hipFuncSetAttribute once per process and variant, from whichever thread comes first
-template <int D, int KS>
+template <int D, int KS, bool kTwoTermP>
 static int prefill_lds_attribute() {
   static std::mutex mu;
   static bool attr_set = false;
   std::lock_guard<std::mutex> lock(mu);
   if (attr_set) return ACTQKV_OK;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_kernel<D, KS>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_kernel<D, KS, kTwoTermP>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kPfLdsBytes<D>);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_queued_kernel<D, KS>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_queued_kernel<D, KS, kTwoTermP>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kPfLdsBytes<D>);
   if (e != hipSuccess) return set_error(ACTQKV_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
   attr_set = true;
   return ACTQKV_OK;
 }
 
-template <int D, int KS>
+template <int D, int KS, bool kTwoTermP>
 static int launch_pf(PfParams p, int late_per_head, hipStream_t stream, hipStream_t stream_late) {
-  if (int rc = prefill_lds_attribute<D, KS>()) return rc;
+  if (int rc = prefill_lds_attribute<D, KS, kTwoTermP>()) return rc;
   dim3 grid(p.wgs_per_head * p.n_kv_heads);
   if (p.items_per_head > p.wgs_per_head)
-    hipLaunchKernelGGL((attn_prefill_mfma_queued_kernel<D, KS>), grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
+    hipLaunchKernelGGL((attn_prefill_mfma_queued_kernel<D, KS, kTwoTermP>), grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
   else
-    hipLaunchKernelGGL((attn_prefill_mfma_kernel<D, KS>), grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
+    hipLaunchKernelGGL((attn_prefill_mfma_kernel<D, KS, kTwoTermP>), grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
   if (int rc = hip_status("attention (prefill, matrix cores)")) return rc;
   if (late_per_head > 0) {
     p.late = 1;
-    hipLaunchKernelGGL((attn_prefill_mfma_queued_kernel<D, KS>), dim3(late_per_head * p.n_kv_heads), dim3(kPfThreads),
+    hipLaunchKernelGGL((attn_prefill_mfma_queued_kernel<D, KS, kTwoTermP>), dim3(late_per_head * p.n_kv_heads), dim3(kPfThreads),
                        kPfLdsBytes<D>, stream_late, p);
     // (if this launch fails after the first one went out, the first team still does all the work, but
     // the queue is not put back to zero: the workspace must be zero-filled again before its next use)
@@ -738,11 +772,11 @@ static int launch_pf(PfParams p, int late_per_head, hipStream_t stream, hipStrea
   }
   return ACTQKV_OK;
 }
-template <int D>
+template <int D, bool kTwoTermP>
 static int launch_pf_ks(int ks, const PfParams& p, int late_per_head, hipStream_t stream, hipStream_t stream_late) {
-  return ks == 1   ? launch_pf<D, 1>(p, late_per_head, stream, stream_late)
-         : ks == 2 ? launch_pf<D, 2>(p, late_per_head, stream, stream_late)
-                   : launch_pf<D, 4>(p, late_per_head, stream, stream_late);
+  return ks == 1   ? launch_pf<D, 1, kTwoTermP>(p, late_per_head, stream, stream_late)
+         : ks == 2 ? launch_pf<D, 2, kTwoTermP>(p, late_per_head, stream, stream_late)
+                   : launch_pf<D, 4, kTwoTermP>(p, late_per_head, stream, stream_late);
 }
 
 // first_cus: compute units the first team may fill (the pieces in `splits` were chosen for it);
@@ -793,8 +827,9 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
   if (p.items_per_head <= p.wgs_per_head) late_per_head = 0;   // a workgroup per item: no queue, no second team
   p.team_total = (p.wgs_per_head + late_per_head) * sh.n_kv_heads;
   p.late = 0;
-  return sh.head_dim == 64 ? launch_pf_ks<64>(splits.ks, p, late_per_head, stream, stream_late)
-                           : launch_pf_ks<128>(splits.ks, p, late_per_head, stream, stream_late);
+  if (sh.head_dim == 64) return launch_pf_ks<64, true>(splits.ks, p, late_per_head, stream, stream_late);
+  return prefill_two_terms(sh, m) ? launch_pf_ks<128, true>(splits.ks, p, late_per_head, stream, stream_late)
+                                  : launch_pf_ks<128, false>(splits.ks, p, late_per_head, stream, stream_late);
 }
 
 }  // namespace actqkv
