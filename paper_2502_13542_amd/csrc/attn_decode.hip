@@ -238,39 +238,35 @@ __device__ __forceinline__ void dc_softmax(DcAcc<D>& a, f32x4 (&sc)[DcShape<T, D
   for (int dg = 0; dg < D / 16; ++dg) a.acc_o[dg] *= alpha;
 }
 
+// Scores, mask, online softmax and O^T += V^T P^T for one item.
+template <typename T, int D>
+__device__ __forceinline__ void dc_consume(const DcItem<T, D>& r, const u32x4 (&qb)[DcShape<T, D>::kQ], DcAcc<D>& a,
+                                           float scale_log2e, int kq) {
+  typedef DcShape<T, D> S;
+  f32x4 sc[S::kSubs];
+#pragma unroll
+  for (int j = 0; j < S::kSubs; ++j) sc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  S::scores(r.ka, qb, sc);
+  dc_softmax<T, D>(a, sc, r.kpos0, r.lo, r.hi, scale_log2e, kq);
+  S::values(r.va, sc, a.acc_o);
+}
+
 // Walks the items it, it + stride, ... < n_items of a tile list: keys and values of an item are requested
 // together, before anything is computed.  (Refilling the key registers with the next item's as soon
-// as the scores have used them gains 1-2 % where a wavefront has six items and loses 4 % where it has one.)
-// before(): called once, behind the first item's requests.
-template <typename T, int D, typename Before>
+// as the scores have used them gains 1-2 % where a wavefront has six items and loses 4 % where it has one.
+// Requesting the next item at the end of the loop's body instead of at its head costs 3 to 5 %: 64 pairs with 10
+// blocks each take 15.5 us instead of 14.9, 128 pairs 24.0 instead of 23.6.)
+template <typename T, int D>
 __device__ __forceinline__ void dc_walk(const TileList& tl, int it, int stride, int n_items, const T* kc, const T* vc,
                                         const u32x4 (&qb)[DcShape<T, D>::kQ], DcAcc<D>& a, float scale_log2e, int hk,
-                                        int n_kv_heads, int n, int kq, Before&& before) {
-  typedef DcShape<T, D> S;
-  DcItem<T, D> r;
-  auto request_next = [&] {                                  // (wave-uniform) the next item the query sees something of
+                                        int n_kv_heads, int n, int kq) {
+  for (; it < n_items; it += stride) {
+    DcItem<T, D> r;
     int block, part;
-    for (; it < n_items; it += stride)
-      if (dc_item_span<T, D>(tl, it, block, part, r)) {
-        it += stride;
-        dc_issue(r, kc, vc, block, part, hk, n_kv_heads, n, kq);
-        return true;
-      }
-    return false;
-  };
-  bool more = request_next();
-  __builtin_amdgcn_sched_barrier(0);
-  before();
-  __builtin_amdgcn_sched_barrier(0);
-  while (more) {
-    f32x4 sc[S::kSubs];
-#pragma unroll
-    for (int j = 0; j < S::kSubs; ++j) sc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    S::scores(r.ka, qb, sc);
-    dc_softmax<T, D>(a, sc, r.kpos0, r.lo, r.hi, scale_log2e, kq);
-    S::values(r.va, sc, a.acc_o);
-    more = request_next();
-    __builtin_amdgcn_sched_barrier(0);
+    if (!dc_item_span<T, D>(tl, it, block, part, r)) continue;   // wave-uniform
+    dc_issue(r, kc, vc, block, part, hk, n_kv_heads, n, kq);
+    __builtin_amdgcn_sched_barrier(0);   // all key and value loads are in flight before the first MFMA
+    dc_consume<T, D>(r, qb, a, scale_log2e, kq);
   }
 }
 
@@ -283,6 +279,46 @@ __device__ __forceinline__ void dc_load_q(const DcParams& p, int s, int hk, int 
   const T* qp = static_cast<const T*>(p.q) + (size_t(s) * p.n_q_heads + hk * group + min(n, group - 1)) * D + S::q_lane(kq);
 #pragma unroll
   for (int ks = 0; ks < S::kQ; ++ks) qb[ks] = *reinterpret_cast<const u32x4*>(qp + ks * S::kQStep);
+}
+
+// The workgroup that finished last merges the partials of its pair's n_wg <= kB workgroups, in their order:
+//   out[head][:] = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w
+// All loads go out first, so that they overlap, and every one of them goes past the L2: with room for 16 partials
+// where there are two, 128 pairs with 10 blocks each take 25.8 us instead of 25.1.
+template <typename T, int D, int kB>
+__device__ __forceinline__ void dc_merge(const DcParams& p, const uint32_t* pair_part, int s, int hk, int group) {
+  T* out = static_cast<T*>(p.out);
+  const size_t stride = size_t(group) * (D + 2);
+  for (int e = threadIdx.x; e < group * D; e += blockDim.x) {
+    const int h = e / D, d = e - h * D;
+    const uint32_t* src = pair_part + size_t(h) * (D + 2);
+    uint32_t pm[kB], pl[kB], po[kB];
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+      const int w = i < p.n_wg ? i : 0;
+      pm[i] = ld_agent(src + w * stride + D);
+      pl[i] = ld_agent(src + w * stride + D + 1);
+      po[i] = ld_agent(src + w * stride + d);
+    }
+    float mm = -INFINITY, l = 0.f, o = 0.f;
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+      if (i < p.n_wg) {
+        const float pmf = __uint_as_float(pm[i]);
+        const float m_new = fmaxf(mm, pmf);
+        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+        const float wa = __builtin_amdgcn_exp2f(mm - m_safe), wb = __builtin_amdgcn_exp2f(pmf - m_safe);
+        l = l * wa + __uint_as_float(pl[i]) * wb;
+        o = o * wa + __uint_as_float(po[i]) * wb;
+        mm = m_new;
+      }
+    }
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    const int head = hk * group + h;
+    store_elem(out + (size_t(s) * p.n_q_heads + head) * D + d, o * inv);
+    if (p.lse != nullptr && d == 0)
+      p.lse[size_t(s) * p.n_q_heads + head] = (mm + log2f(l)) * 0.6931471805599453f;
+  }
 }
 
 // The wavefronts of a workgroup merge their (max, sum, O) through LDS.  If one workgroup covers
@@ -334,42 +370,10 @@ __device__ __forceinline__ void dc_finish(const DcParams& p, const DcAcc<D>& a, 
   __shared__ int last_flag;
   if (!last_of_group(p.counters + size_t(s) * p.n_kv_heads + hk, unsigned(p.n_wg), &last_flag)) return;
 
-  // ---- the workgroup that finished last merges the partials, in workgroup order:
-  //   out[head][:] = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w
-  const size_t stride = size_t(group) * (D + 2);
-  constexpr int kB = kDcMaxSpread;
-  for (int e = threadIdx.x; e < group * D; e += blockDim.x) {
-    const int h = e / D, d = e - h * D;
-    const uint32_t* src = pair_part + size_t(h) * (D + 2);
-    float mm = -INFINITY, l = 0.f, o = 0.f;
-    for (int w0 = 0; w0 < p.n_wg; w0 += kB) {
-      uint32_t pm[kB], pl[kB], po[kB];
-#pragma unroll
-      for (int i = 0; i < kB; ++i) {               // all loads first: they overlap
-        const int w = w0 + i < p.n_wg ? w0 + i : w0;
-        pm[i] = ld_agent(src + w * stride + D);
-        pl[i] = ld_agent(src + w * stride + D + 1);
-        po[i] = ld_agent(src + w * stride + d);
-      }
-#pragma unroll
-      for (int i = 0; i < kB; ++i) {
-        if (w0 + i < p.n_wg) {
-          const float pmf = __uint_as_float(pm[i]);
-          const float m_new = fmaxf(mm, pmf);
-          const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-          const float wa = __builtin_amdgcn_exp2f(mm - m_safe), wb = __builtin_amdgcn_exp2f(pmf - m_safe);
-          l = l * wa + __uint_as_float(pl[i]) * wb;
-          o = o * wa + __uint_as_float(po[i]) * wb;
-          mm = m_new;
-        }
-      }
-    }
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-    const int head = hk * group + h;
-    store_elem(out + (size_t(s) * p.n_q_heads + head) * D + d, o * inv);
-    if (p.lse != nullptr && d == 0)
-      p.lse[size_t(s) * p.n_q_heads + head] = (mm + log2f(l)) * 0.6931471805599453f;
-  }
+  if (p.n_wg <= 4)
+    dc_merge<T, D, 4>(p, pair_part, s, hk, group);
+  else
+    dc_merge<T, D, kDcMaxSpread>(p, pair_part, s, hk, group);
 }
 
 // grid (n_wg, Hk, batch); blockDim = 64 * (wavefronts per workgroup).  Item i of the tile list
@@ -382,24 +386,22 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_kernel(DcParams p) {
   const int wg = blockIdx.x, hk = blockIdx.y, s = blockIdx.z;
   const int group = p.n_q_heads / p.n_kv_heads;
 
-  // (the block numbers are requested together with the scalars they are used with)
-  __shared__ int32_t sel[64];
+  // (a wavefront reads the few block numbers it needs itself: bringing the list into LDS for all of them, behind
+  // a barrier, costs 0.2 to 1.1 us of 9 to 36)
   const size_t sel_row = p.sel_per_head ? size_t(s) * p.n_kv_heads + hk : size_t(s);
   const int n_ctx_raw = p.n_ctx[s], n_sel_raw = p.n_sel[sel_row];
-  if (int(threadIdx.x) < p.k_cap) sel[threadIdx.x] = p.idx[sel_row * p.k_cap + threadIdx.x];
   u32x4 qb[DcShape<T, D>::kQ];
   dc_load_q<T, D>(p, s, hk, group, n, kq, qb);
-  __syncthreads();
   const int n_ctx = min(max(n_ctx_raw, 1), p.nb_capacity * kBlock);
   const WindowGeom g = window_geom(n_ctx, 1, p.n_init, p.n_local);
-  const TileList tl = make_tile_list(g, n_ctx - 1, sel, n_sel_raw, p.k_cap, p.nb_capacity);
+  const TileList tl = make_tile_list(g, n_ctx - 1, p.idx + sel_row * p.k_cap, n_sel_raw, p.k_cap, p.nb_capacity);
   const int n_items = tl.count() * (kBlock / DcShape<T, D>::kKeys);
   DcAcc<D> a;
   a.clear();
   const T* kc = static_cast<const T*>(p.k_cache) + size_t(s) * p.seq_stride;
   const T* vc = static_cast<const T*>(p.v_cache) + size_t(s) * p.seq_stride;
 
-  dc_walk<T, D>(tl, wave * p.n_wg + wg, p.n_wg * n_waves, n_items, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq, [] {});
+  dc_walk<T, D>(tl, wave * p.n_wg + wg, p.n_wg * n_waves, n_items, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
   dc_finish<T, D>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 }
 
@@ -461,13 +463,20 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
   const uint16_t* kc = static_cast<const uint16_t*>(p.k_cache) + size_t(s) * p.seq_stride;
   const uint16_t* vc = static_cast<const uint16_t*>(p.v_cache) + size_t(s) * p.seq_stride;
 
-  // The items that do not depend on the selection come first in the list.  Neighbouring items go to
-  // different workgroups; the wavefronts that select come last, short lists do not reach them.
+  // The items that do not depend on the selection come first in the list, and this wavefront's first one is
+  // requested before the selection.  Neighbouring items go to different workgroups; the wavefronts that
+  // select come last, short lists do not reach them.
   const int it0 = wave * p.n_wg + wg;
   const int stride = p.n_wg * n_waves;
-  dc_walk<uint16_t, kDcD>(fixed, it0, stride, n_fixed, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq, [&] {
-    if (!by_wave) select_body<kDcThreads>(sc, s, n_elig, sp.nb_begin, p.k_cap, sp.entropy_topk, io, sel_lds);
-  });
+  DcItem<uint16_t, kDcD> r0;
+  int block0, part0;
+  const bool have0 = it0 < n_fixed && dc_item_span<uint16_t, kDcD>(fixed, it0, block0, part0, r0);
+  if (have0) dc_issue(r0, kc, vc, block0, part0, hk, p.n_kv_heads, n, kq);
+  __builtin_amdgcn_sched_barrier(0);
+  if (!by_wave) select_body<kDcThreads>(sc, s, n_elig, sp.nb_begin, p.k_cap, sp.entropy_topk, io, sel_lds);
+  __builtin_amdgcn_sched_barrier(0);
+  if (have0) dc_consume<uint16_t, kDcD>(r0, qb, a, p.scale_log2e, kq);
+  dc_walk<uint16_t, kDcD>(fixed, it0 + stride, stride, n_fixed, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
   if (by_wave) {
     // the selector has long finished as a rule; it always does, whatever the others do
     while (__hip_atomic_load(&sel_ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0) __builtin_amdgcn_s_sleep(1);
@@ -483,7 +492,7 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
   const int n_chosen = chosen.n_sel * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
   const int done = it0 < n_fixed ? (n_fixed - it0 + stride - 1) / stride : 0;      // of this wavefront's turns
   dc_walk<uint16_t, kDcD>(chosen, it0 + done * stride - n_fixed, stride, n_chosen, kc, vc, qb, a, p.scale_log2e, hk,
-                          p.n_kv_heads, n, kq, [] {});
+                          p.n_kv_heads, n, kq);
   dc_finish<uint16_t, kDcD>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 }
 
@@ -675,7 +684,7 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   // the reads of the scores wait behind the items' 32 KB - loads return in order - and a
   // wavefront set aside for those reads still shares the compute unit's load queue with the
   // other seven: both orders were slower than this one.)
-  dc_walk<uint16_t, kDcD>(fixed, it0, stride, n_fixed, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq, [] {});
+  dc_walk<uint16_t, kDcD>(fixed, it0, stride, n_fixed, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
 
   // ---- the sequence's scores: wait (bounded) until every workgroup has published its share
   if (tid == 0) {
@@ -716,7 +725,7 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   const int n_chosen = chosen.n_sel * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
   const int done = it0 < n_fixed ? (n_fixed - it0 + stride - 1) / stride : 0;      // of this wavefront's turns
   dc_walk<uint16_t, kDcD>(chosen, it0 + done * stride - n_fixed, stride, n_chosen, kc, vc, qb, a, p.scale_log2e, hk,
-                          p.n_kv_heads, n, kq, [] {});
+                          p.n_kv_heads, n, kq);
   dc_finish<uint16_t, kDcD>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 
   // ---- the last workgroup of the sequence to get here (nobody polls any more) resets the counters
@@ -738,8 +747,8 @@ bool decode_fused_supported(const actqkv_shape& sh) {
 
 // Launch shape: workgroups of 8 wavefronts, one per compute unit (two wavefronts per SIMD, each with
 // a whole item's loads in flight), and never more workgroups than compute units while a pair has
-// one: 192 pairs (16 blocks each) take 62 us on 192 compute units and 80 us as 384 workgroups, whose
-// second round leaves half the chip idle.  Few pairs are spread as thin as that allows, a wavefront
+// one: with 16 blocks each, 132 to 192 pairs take 45 to 50 us one workgroup each and 58 to 60 us as two, whose
+// second round leaves half the chip idle; 136 to 240 pairs with 10 blocks 34 to 40 us against 41 to 44.  Few pairs are spread as thin as that allows, a wavefront
 // or two of work per compute unit: one compute unit does not get more than 35-50 GB/s of scattered
 // 16 KB tiles, so 8 pairs with 10 blocks each take 20.1 us as 4 workgroups per pair, 12.4 us as 16, and
 // 14.8 us as 32 (the merge grows with their number).
