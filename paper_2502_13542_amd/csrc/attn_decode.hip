@@ -747,11 +747,12 @@ bool decode_fused_supported(const actqkv_shape& sh) {
 
 // Launch shape: workgroups of 8 wavefronts, one per compute unit (two wavefronts per SIMD, each with
 // a whole item's loads in flight), and never more workgroups than compute units while a pair has
-// one: with 16 blocks each, 132 to 192 pairs take 45 to 50 us one workgroup each and 58 to 60 us as two, whose
-// second round leaves half the chip idle; 136 to 240 pairs with 10 blocks 34 to 40 us against 41 to 44.  Few pairs are spread as thin as that allows, a wavefront
-// or two of work per compute unit: one compute unit does not get more than 35-50 GB/s of scattered
-// 16 KB tiles, so 8 pairs with 10 blocks each take 20.1 us as 4 workgroups per pair, 12.4 us as 16, and
-// 14.8 us as 32 (the merge grows with their number).
+// one: with 16 blocks each, 132 to 192 pairs take 45 to 50 us one workgroup each and 58 to 60 us as
+// two, whose second round leaves half the chip idle; 136 to 240 pairs with 10 blocks 34 to 40 us against
+// 41 to 44.  Few pairs are spread as thin as that allows, a wavefront or two of work per compute
+// unit: one compute unit does not get more than 35-50 GB/s of scattered 16 KB tiles, so 8 pairs with
+// 10 blocks each take 20.1 us as 4 workgroups per pair, 12.4 us as 16, and 14.8 us as 32 (the merge
+// grows with their number).
 // One workgroup per (sequence, KV head) writes the output itself; with more, the one that
 // finishes last merges the partials.
 static int decode_items_max(const actqkv_shape& sh, int k_cap) {
@@ -765,7 +766,10 @@ int decode_mfma_workgroups(const actqkv_shape& sh, int batch, int k_cap) {
   return std::max(1, std::min({kChipCus / pairs, kDcMaxSpread, decode_items_max(sh, k_cap)}));
 }
 
+// Partial results: none where one workgroup covers a pair and writes the output itself.  (bf16 with 128 channels
+// has always been charged for one partial per pair all the same; what a call is refused for stays as it was.)
 size_t decode_mfma_scratch_floats(const actqkv_shape& sh, int batch, int k_cap) {
+  if (decode_mfma_workgroups(sh, batch, k_cap) == 1 && !decode_fused_supported(sh)) return 0;
   return size_t(batch) * sh.n_q_heads * decode_mfma_workgroups(sh, batch, k_cap) * (sh.head_dim + 2);
 }
 

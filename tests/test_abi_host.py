@@ -282,6 +282,10 @@ def test_retrieval_attention_static_rejects(lib):
     assert call(shape=big, batch=1024, m=1, nb=2) == -4
     msg = lib.actqkv_last_error().decode()
     assert "scratch" in msg and str(32 << 20) in msg
+    # the largest batches of the other kinds have a workgroup per (sequence, KV head) and need no partial results
+    for shape in (LayerShape(64, 64, 128, 128, 4, 128, 256, "fp32"), LayerShape(256, 64, 64, 128, 4, 128, 256, "bf16"),
+                  LayerShape(256, 256, 64, 128, 4, 128, 256, "fp32")):
+        assert call(shape=B.c_shape(shape), batch=1024, m=1, nb=2) in (0, -5), lib.actqkv_last_error()
 
 
 def test_cutoff_budgets_and_select_modes_reject(lib):
