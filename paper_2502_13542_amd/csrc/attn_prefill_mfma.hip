@@ -47,7 +47,11 @@ template <int D> constexpr int kPfLdsBytes = 2 * 2 * kPfTileBytes<D>;   // 2 sta
 constexpr int kMaxPfSplits = 8;
 constexpr float kLazyMaxLog2 = 8.f;                  // how far a tile's maximum may exceed the reference one
 constexpr int kPfOrderMax = 64;                      // batch entries the queue hands out longest first
-constexpr int kPfQueueDone = 128;                    // index of the "left" counter behind the per-head queue counters
+// Index of the "left" counter behind the per-head queue counters: 16384 channels in heads of 64 are 256 KV heads.
+// It is the first of the decode layer's counters; every launch leaves both at zero, and calls that share a workspace
+// are ordered.
+constexpr int kPfQueueDone = 256;
+static_assert(kPfQueueDone + 1 <= kSeqCounterOffset - kTicketCounters + kSeqCounters, "queue counters");
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -818,8 +822,6 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
     return set_error(ACTQKV_EINVAL, "prefill attention: inconsistent split of the key tiles");
   if (splits.slots > p.n_qtiles && size_t(batch) * p.n_qtiles * sh.n_kv_heads > kTicketCounters)
     return set_error(ACTQKV_EINVAL, "prefill attention: more split query tiles than ticket counters");
-  if (sh.n_kv_heads > kPfQueueDone)
-    return set_error(ACTQKV_ESHAPE, "prefill attention: more than %d KV heads", kPfQueueDone);
   p.items_per_head = splits.slots * batch;
   p.wgs_per_head = std::min(p.items_per_head, std::max(1, first_cus / sh.n_kv_heads));
   p.queue = counters + kTicketCounters;

@@ -77,7 +77,8 @@ constexpr int kMaxWindow = 8192;
 // head of the workspace: 1024 uint32 tickets, then the work queue counters of the prefill attention
 constexpr size_t kTicketCounters = 1024;
 constexpr size_t kCounterBytes = 8192;
-// behind the queue counters: two counters per sequence for the decode layer in one launch
+// behind the 256 heads' queue counters: two counters per sequence for the decode layer in one launch (the first
+// is also the prefill queue's last, see kPfQueueDone)
 constexpr size_t kSeqCounterOffset = kTicketCounters + 256, kSeqCounters = 768;
 constexpr int kChipCus = 256;   // compute units of the chip
 constexpr int kMaxBatch = 1024;

@@ -447,6 +447,35 @@ def test_probabilities_keep_more_than_bf16(d, group, m, nw):
     assert worst <= 1., worst
 
 
+@pytest.mark.parametrize("hk,nw", [(129, 1), (256, 1), (256, 3)])
+def test_prefill_attention_of_many_kv_heads(hk, nw):
+    """More KV heads than 128, which only fit with 64 channels each: a workgroup per work item, and (3 windows) more
+    work items than workgroups, drawn from a counter per head; twice, so that the counters are as they were."""
+    sh = LayerShape(hk, hk, 64, 128, 4, 128, 128, "bf16")
+    cs = B.c_shape(sh)
+    m, k_cap, base = 40, 2, 5 * 128 + 9
+    n_tok = base + nw * m
+    nb = (n_tok + 127) // 128
+    g = torch.Generator().manual_seed(hk + nw)
+    q, k, v = (torch.randn(n, hk, 64, generator=g).to(torch.bfloat16) for n in (nw * m, nb * 128, nb * 128))
+    w0 = [base + i * m for i in range(nw)]
+    idx = torch.tensor([[1, 3], [2, 3], [3, 1]][:nw], dtype=torch.int32)
+    n_sel = torch.tensor([2 - i % 2 for i in range(nw)], dtype=torch.int32)
+    ws = torch.zeros(B.workspace_bytes(cs, nw, m, nb, k_cap), dtype=torch.uint8, device=DEV)
+    for _ in range(2):
+        out = torch.zeros(nw * m, hk, 64, dtype=torch.bfloat16, device=DEV)
+        B.retrieval_attention(cs, nw, m, q.to(DEV), H.blocked_k(k.to(DEV), sh, nb), H.blocked_vt(v.to(DEV), sh, nb), 0,
+                              nb, torch.tensor([w + m for w in w0], dtype=torch.int32, device=DEV), idx.to(DEV),
+                              n_sel.to(DEV), k_cap, out, None, ws)
+        torch.cuda.synchronize()
+        for i in range(nw):
+            for r in (0, m - 1):
+                pos = orc.key_positions(w0[i], w0[i] + r, idx[i, : int(n_sel[i])].tolist(), sh.n_init, sh.n_local, 128)
+                ref = orc.attention_rows(f64(q[i * m + r])[None], f64(k), f64(v), pos, 1)[0]
+                assert out_error(out[i * m + r], ref) < TOL_OUT["bf16"], (i, r)
+    assert int(ws[:8192].view(torch.int32).abs().sum()) == 0          # the counters are as they were
+
+
 @pytest.mark.parametrize("dtype,d,m,n_ctx", [("bf16", 128, 2, 700), ("bf16", 128, 33, 1500), ("fp32", 64, 3, 500)])
 def test_tiny_windows(dtype, d, m, n_ctx):
     """Windows of 2, 3 and 33 tokens (most rows of a query tile idle, a ragged last window)."""
