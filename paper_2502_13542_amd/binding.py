@@ -108,7 +108,7 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
         fn = getattr(lib, name)
         fn.restype, fn.argtypes = res, args
     native = importlib.import_module("._native", __package__)
-    native.load(path, ActQKVError, _is_pinned)
+    native.load(path, ActQKVError)
     _lib, _native = lib, native
     return lib
 
@@ -125,22 +125,10 @@ def _check(rc: int) -> None:
         raise ActQKVError(rc, load_library().actqkv_last_error().decode())
 
 
-_PINNED_STORAGES = {}     # storage address -> is it pinned (asking the runtime costs more than a launch)
-
-
-def _is_pinned(t: torch.Tensor) -> bool:
-    key = t.untyped_storage().data_ptr()
-    hit = _PINNED_STORAGES.get(key)
-    if hit is None:
-        if len(_PINNED_STORAGES) > 4096:
-            _PINNED_STORAGES.clear()
-        hit = _PINNED_STORAGES[key] = bool(t.is_pinned())
-    return hit
-
-
 def _ptr_readable(t: torch.Tensor, dtype=None) -> int:
-    """A tensor a kernel may read in place: device memory or pinned host memory."""
-    if not (t.is_cuda or _is_pinned(t)):
+    """A tensor a kernel may read in place: device memory or pinned host memory.  (The runtime is asked each
+    time: an address that was pinned once may belong to pageable memory by now.)"""
+    if not (t.is_cuda or t.is_pinned()):
         raise ActQKVError(-1, "tensor is neither on the GPU nor in pinned host memory")
     if not t.is_contiguous():
         raise ActQKVError(-1, "tensor is not contiguous")

@@ -28,7 +28,6 @@
 namespace {
 
 PyObject* g_error = nullptr;         // ActQKVError(code, message)
-PyObject* g_is_pinned = nullptr;     // tensor -> bool
 
 bool raise(int code, const char* message) {
   PyObject* e = PyObject_CallFunction(g_error, "is", code, message);
@@ -67,10 +66,9 @@ struct Args {
       return nullptr;
     }
     const at::Tensor& t = THPVariable_Unpack(o);
-    if (!t.is_cuda() && !(host_too && pinned(o))) {
-      if (!PyErr_Occurred())
-        raise(ACTQKV_EINVAL, host_too ? "tensor is neither on the GPU nor in pinned host memory" : "tensor is not on the GPU");
-      ok = false;
+    // (the runtime is asked about every host tensor: an answer kept by address would outlive the tensor)
+    if (!t.is_cuda() && !(host_too && t.is_pinned())) {
+      ok = raise(ACTQKV_EINVAL, host_too ? "tensor is neither on the GPU nor in pinned host memory" : "tensor is not on the GPU");
     } else if (!t.is_contiguous()) {
       ok = raise(ACTQKV_EINVAL, "tensor is not contiguous");
     } else if (!any_type && t.scalar_type() != want) {
@@ -80,13 +78,6 @@ struct Args {
     if (!ok) return nullptr;
     ws_bytes = t.nbytes();
     return t.data_ptr();
-  }
-
-  bool pinned(PyObject* o) {
-    PyObject* r = PyObject_CallFunctionObjArgs(g_is_pinned, o, nullptr);
-    const bool yes = r != nullptr && PyObject_IsTrue(r) == 1;
-    Py_XDECREF(r);
-    return yes;
   }
 
   c10::ScalarType storage() const { return shape.dtype == ACTQKV_F32 ? c10::kFloat : c10::kBFloat16; }
@@ -245,11 +236,11 @@ template <typename... P> struct Entry<int(P...)> {
   }
 ACTQKV_ENTRIES(ACTQKV_DEFINE)
 
-// load(path, error class, is_pinned): finds the entry points in the library at `path`
+// load(path, error class): finds the entry points in the library at `path`
 PyObject* py_load(PyObject*, PyObject* args) {
   const char* path;
-  PyObject *error, *is_pinned;
-  if (!PyArg_ParseTuple(args, "sOO", &path, &error, &is_pinned)) return nullptr;
+  PyObject* error;
+  if (!PyArg_ParseTuple(args, "sO", &path, &error)) return nullptr;
   void* lib = dlopen(path, RTLD_NOW | RTLD_LOCAL);
   if (lib == nullptr) {
     PyErr_SetString(PyExc_OSError, dlerror());
@@ -260,9 +251,7 @@ PyObject* py_load(PyObject*, PyObject* args) {
   ACTQKV_ENTRIES(ACTQKV_FIND)
   g_last_error = reinterpret_cast<const char* (*)()>(dlsym(lib, "actqkv_last_error"));
   Py_INCREF(error);
-  Py_INCREF(is_pinned);
   Py_XSETREF(g_error, error);
-  Py_XSETREF(g_is_pinned, is_pinned);
   Py_RETURN_NONE;
 }
 

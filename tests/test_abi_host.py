@@ -312,6 +312,21 @@ def test_cutoff_next_step_rejects(lib):
     assert call(ts=None) == -1 and call(b=None) == -1 and call(r=A16 + 2) == -3
 
 
+def test_pinned_verdict_does_not_outlive_its_tensor(monkeypatch):
+    """A host tensor at an address where a pinned one was before is asked about anew (and the other way round): a
+    kernel that reads pageable memory in place faults."""
+    import torch
+    memory, verdict = bytearray(64), [True]
+    monkeypatch.setattr(torch.Tensor, "is_pinned", lambda self, *a: verdict[0])
+    at = lambda: torch.frombuffer(memory, dtype=torch.uint8)
+    assert B._ptr_readable(at()) == at().data_ptr()
+    verdict[0] = False
+    with pytest.raises(B.ActQKVError, match="pinned"):
+        B._ptr_readable(at())
+    verdict[0] = True
+    assert B._ptr_readable(at()) == at().data_ptr()
+
+
 def test_cpp_exceptions_reach_python():
     """What torch throws while a call's arguments are taken (no GPU for the current stream, a tensor
     without memory) is a Python exception, not the end of the process."""
