@@ -78,12 +78,6 @@ struct DcShape<uint16_t, D> {
   static constexpr int kKeys = 64;                 // keys per work item (half a block)
   static constexpr int kSubs = kKeys / 16, kSteps = kKeys / 32;
   static constexpr int kQ = D / 32, kK = kSubs * kQ, kV = (D / 16) * kSteps;
-  // With 64 channels the probabilities enter the second product as two bf16 terms, the rounded value and what the
-  // rounding left, which keeps 16 of their bits: such calls had fp32 probabilities before they came to the
-  // matrix cores.  Against 64 bits (8 query, 2 KV heads, 16K tokens, 8 blocks) the relative error is 1.7269e-3, what
-  // the rounding of the output alone gives, and 1.8350e-3 with one term; the launch is bound by its
-  // bytes: 6.9 us, 6.6 to 7.2 with one term.  (With 128 channels it has always been one term.)
-  static constexpr bool kTwoTermP = D == 64;
   __device__ static __forceinline__ int key_of(int j, int i, int kq) { return 32 * (j >> 1) + 8 * kq + 4 * (j & 1) + i; }
   // element offsets of a lane's operands from the item's first key (K rows) / first key column (V^T rows)
   __device__ static __forceinline__ int k_lane(int n, int kq) { return (8 * (n >> 2) + (n & 3)) * D + 8 * kq; }
@@ -100,6 +94,13 @@ struct DcShape<uint16_t, D> {
         sc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dc_as_bf16x8(ka[j * kQ + ks]), dc_as_bf16x8(qb[ks]), sc[j], 0, 0, 0);
   }
   __device__ static __forceinline__ void values(const u32x4 (&va)[kV], const f32x4 (&sc)[kSubs], f32x4 (&acc)[D / 16]) {
+    // The probabilities enter as two bf16 terms, the rounded value and what the rounding left, which keeps 16 of
+    // their bits.  With one term the error grows with the keys a wavefront walks (a row's largest probability so far
+    // is exactly 1, and fewer wavefronts have fewer of them).  Relative error against 64 bits, mean of 8 inputs, 48
+    // sequences with 28 query and 4 KV heads of 128 channels: one term 1.768e-3 in two workgroups per pair, 1.791e-3
+    // in one, two terms 1.676e-3; with 64 channels (8 query, 2 KV heads) one term 1.835e-3, two 1.727e-3, as
+    // with fp32 probabilities.  A launch is bound by its bytes: a step of 16 sequences takes 186 us with two terms
+    // and 188 with one, of 48 sequences 138 with both.
     typedef __attribute__((ext_vector_type(8))) float f32x8;
 #pragma unroll
     for (int st = 0; st < kSteps; ++st) {
@@ -109,12 +110,10 @@ struct DcShape<uint16_t, D> {
 #pragma unroll
       for (int dg = 0; dg < D / 16; ++dg)
         acc[dg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dc_as_bf16x8(va[dg * kSteps + st]), pb, acc[dg], 0, 0, 0);
-      if constexpr (kTwoTermP) {
-        const bf16x8 pl = __builtin_convertvector(pf - __builtin_convertvector(pb, f32x8), bf16x8);
+      const bf16x8 pl = __builtin_convertvector(pf - __builtin_convertvector(pb, f32x8), bf16x8);
 #pragma unroll
-        for (int dg = 0; dg < D / 16; ++dg)
-          acc[dg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dc_as_bf16x8(va[dg * kSteps + st]), pl, acc[dg], 0, 0, 0);
-      }
+      for (int dg = 0; dg < D / 16; ++dg)
+        acc[dg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dc_as_bf16x8(va[dg * kSteps + st]), pl, acc[dg], 0, 0, 0);
     }
   }
 };

@@ -414,7 +414,7 @@ def test_prefill_attention_at_the_edges_of_its_tiles(dtype, d, group, m, nw):
             assert out_error(out[i * m + r], ref) < TOL_OUT[dtype], (i, r)
 
 
-@pytest.mark.parametrize("d,group,m,nw", [(64, 4, 1, 6), (64, 8, 1, 300), (64, 4, 65, 1), (64, 1, 300, 1), (64, 2, 1024, 1),
+@pytest.mark.parametrize("d,group,m,nw", [(64, 4, 1, 6), (64, 8, 1, 300), (128, 1, 1, 6), (128, 8, 1, 300), (64, 4, 65, 1), (64, 1, 300, 1), (64, 2, 1024, 1),
                                           (64, 8, 129, 40), (128, 1, 3457, 1), (128, 4, 3457, 1), (128, 8, 3457, 5)])
 def test_probabilities_keep_more_than_bf16(d, group, m, nw):
     """The calls whose probabilities are not rounded to bf16 before the product with the values: every element
