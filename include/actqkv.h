@@ -339,7 +339,8 @@ int actqkv_retrieval_attention_teams(const actqkv_shape* shape, int batch, int m
 
 /*
  * n_windows windows of ONE sequence (one cache, m tokens each, q and out [n_windows][m][Hq][D]) in one
- * launch on `cus` compute units (1 .. 256), with results bit for bit those of a call of
+ * launch on `cus` compute units (1 .. 256; several launches for more windows than the workspace has
+ * counters for, at least 8 of them in each), with results bit for bit those of a call of
  * actqkv_retrieval_attention per window: every window's keys are cut into the pieces they are cut
  * into when it is alone.  bf16, m >= 2.  ws_bytes: n_windows times what one window needs is enough.
  */

@@ -424,8 +424,17 @@ int actqkv_retrieval_attention_windows(const actqkv_shape* shape, int n_windows,
   if (ws_bytes < need)
     return set_error(ACTQKV_EWORKSPACE, "workspace has %zu bytes, retrieval_attention_windows needs %zu", ws_bytes, need);
   Workspace ws{workspace, ws_bytes};
-  return launch_attention(*shape, n_windows, m, q, k_cache, v_cache, 0, nb_capacity, n_ctx, idx, n_sel, k_cap, out, lse,
-                          ws, 0, static_cast<hipStream_t>(stream), cus, 0, nullptr, true);
+  // a query tile in pieces has a ticket counter: as many windows in a launch as there are counters for (the pieces
+  // of a window alone fill the chip, so more in a launch would gain nothing)
+  const PfSplits splits = prefill_splits(*shape, 1, m, k_cap, kChipCus);
+  const int per = splits.slots > splits.n_qtiles ? int(kTicketCounters) / (splits.n_qtiles * shape->n_kv_heads) : n_windows;
+  const size_t row = size_t(m) * shape->n_q_heads, elem = shape->head_dim * sizeof(uint16_t);
+  for (int w = 0; w < n_windows; w += per)
+    ACTQKV_TRY(launch_attention(*shape, std::min(per, n_windows - w), m, static_cast<const char*>(q) + w * row * elem,
+                                k_cache, v_cache, 0, nb_capacity, n_ctx + w, idx + size_t(w) * k_cap, n_sel + w, k_cap,
+                                static_cast<char*>(out) + w * row * elem, lse == nullptr ? nullptr : lse + w * row, ws, 0,
+                                static_cast<hipStream_t>(stream), cus, 0, nullptr, true));
+  return ACTQKV_OK;
 }
 
 int actqkv_retrieval_attention_per_head(const actqkv_shape* shape, int batch, int m, const void* q,

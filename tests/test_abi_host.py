@@ -270,6 +270,20 @@ def test_retrieval_attention_teams_rejects(lib):
     assert call(q=None) == -1 and call(out=A16 + 2) == -3 and call(ws=None) == -4 and call(wsb=8) == -4
 
 
+def test_retrieval_attention_windows_rejects(lib):
+    cs, fp32 = B.c_shape(LLAMA), B.c_shape(LayerShape(32, 8, 128, 128, 4, 128, 512, "fp32"))
+    call = lambda shape=cs, nw=4, m=512, **k: lib.actqkv_retrieval_attention_windows(
+        ctypes.byref(shape), nw, m, k.get("q", A16), A16, A16, k.get("nb", 64), A16, A16, A16, k.get("k_cap", 16),
+        k.get("out", A16), k.get("lse"), k.get("ws", A16), k.get("wsb", 1 << 30), k.get("cus", 224), None)
+    assert call(cus=0) == -1 and call(cus=257) == -1 and b"cus" in lib.actqkv_last_error()
+    assert call(nw=0) == -1 and call(nw=1025) == -2 and call(m=0) == -1 and call(m=8193) == -2
+    assert call(shape=fp32) == -2 and call(m=1) == -2 and b"bf16" in lib.actqkv_last_error()
+    assert call(nb=3) == -1 and call(k_cap=65) == -2
+    assert call(q=None) == -1 and call(out=A16 + 2) == -3 and call(lse=A16 + 2) == -3
+    one = lib.actqkv_workspace_bytes(ctypes.byref(cs), 1, 512, 64, 16)
+    assert call(ws=None) == -4 and call(nw=200, wsb=one) == -4 and b"needs" in lib.actqkv_last_error()
+
+
 def test_retrieval_attention_static_rejects(lib):
     """The entry point that allocates nothing: argument errors as in actqkv_retrieval_attention, and
     a call whose scratch need exceeds the library's own array is refused before anything runs."""

@@ -447,6 +447,38 @@ def test_probabilities_keep_more_than_bf16(d, group, m, nw):
     assert worst <= 1., worst
 
 
+@pytest.mark.parametrize("hq,hk,d,m,nw,cus", [(32, 8, 128, 128, 17, 256), (32, 8, 128, 512, 3, 224), (28, 4, 128, 77, 33, 7),
+                                              (8, 2, 64, 129, 5, 256), (2, 2, 64, 2, 300, 31)])
+def test_windows_of_one_sequence_in_one_call(hq, hk, d, m, nw, cus):
+    """actqkv_retrieval_attention_windows gives, bit for bit, what a call per window gives, also with more
+    windows than a launch has ticket counters for."""
+    sh = LayerShape(hq, hk, d, 128, 4, 128, 256, "bf16")
+    cs = B.c_shape(sh)
+    k_cap, base = 6, 12 * 128 + 5
+    nb = (base + nw * m + 127) // 128
+    g = torch.Generator().manual_seed(nw + m)
+    q, k, v = (torch.randn(n, h, d, generator=g).to(torch.bfloat16).to(DEV)
+               for n, h in ((nw * m, hq), (nb * 128, hk), (nb * 128, hk)))
+    kc, vc = H.blocked_k(k, sh, nb), H.blocked_vt(v, sh, nb)
+    w0 = [base + i * m for i in range(nw)]
+    idx = torch.stack([torch.randperm(H.eligible_range(sh, w)[1] - 1, generator=g)[:k_cap] + 1 for w in w0]).int().to(DEV)
+    n_sel = torch.randint(0, k_cap + 1, (nw,), generator=g).int().to(DEV)
+    n_ctx = torch.tensor([w + m for w in w0], dtype=torch.int32, device=DEV)
+    one = B.workspace_bytes(cs, 1, m, nb, k_cap)
+    ws, ws_all = (torch.zeros(n, dtype=torch.uint8, device=DEV) for n in (one, nw * one))
+    out, out_all = torch.zeros_like(q), torch.zeros_like(q)
+    lse, lse_all = (torch.zeros(nw, hq, m, device=DEV) for _ in range(2))
+    for i in range(nw):
+        B.retrieval_attention(cs, 1, m, q[i * m:(i + 1) * m], kc, vc, 0, nb, n_ctx[i:i + 1], idx[i], n_sel[i:i + 1], k_cap,
+                              out[i * m:(i + 1) * m], lse[i], ws)
+    for _ in range(2):                                   # (twice: the counters are as they were)
+        out_all.zero_()
+        lse_all.zero_()
+        B.retrieval_attention_windows(cs, nw, m, q, kc, vc, nb, n_ctx, idx, n_sel, k_cap, out_all, lse_all, ws_all, cus)
+        torch.cuda.synchronize()
+        assert torch.equal(out, out_all) and torch.equal(lse, lse_all)
+
+
 @pytest.mark.parametrize("hk,nw", [(129, 1), (256, 1), (256, 3)])
 def test_prefill_attention_of_many_kv_heads(hk, nw):
     """More KV heads than 128, which only fit with 64 channels each: a workgroup per work item, and (3 windows) more
