@@ -284,6 +284,24 @@ def test_retrieval_attention_windows_rejects(lib):
     assert call(ws=None) == -4 and call(nw=200, wsb=one) == -4 and b"needs" in lib.actqkv_last_error()
 
 
+def test_gather_blocks_cached_rejects(lib):
+    cs = B.c_shape(LLAMA)
+    call = lambda nw=4, k_cap=16, **k: lib.actqkv_gather_blocks_cached(
+        ctypes.byref(cs), nw, k.get("store", A16), A16, k.get("nb_store", 256), k.get("idx", A16), A16, k_cap,
+        k.get("cache", A16), A16, k.get("nb", 300), k.get("slot0", 1), k.get("n_slots", 128), *k.get("here0", (0, 0, 0)),
+        *k.get("here1", (0, 0, 0)), k.get("group", 0), k.get("state", A16), A16, None)
+    assert call(k_cap=0) == -2 and call(k_cap=65) == -2 and call(nw=0) == -2 and call(nw=17) == -2
+    assert b"selections" in lib.actqkv_last_error()
+    assert call(nb_store=0) == -1 and call(n_slots=127) == -1 and call(n_slots=513) == -1
+    assert call(slot0=-1) == -1 and call(slot0=173) == -1 and b"outside the cache" in lib.actqkv_last_error()
+    assert call(group=-1) == -1
+    # a range that lies in the cache may not touch the slots (1 .. 128) nor leave the cache
+    for here in ((0, 2, 0), (5, 7, 128), (0, 8, 293), (-1, 3, 200), (0, 3, -1)):
+        assert call(here0=here) == -1 and call(here1=here) == -1, here
+        assert b"overlap the slots" in lib.actqkv_last_error()
+    assert call(store=None) == -1 and call(cache=A16 + 2) == -3 and call(idx=A16 + 2) == -3 and call(state=None) == -1
+
+
 def test_retrieval_attention_static_rejects(lib):
     """The entry point that allocates nothing: argument errors as in actqkv_retrieval_attention, and
     a call whose scratch need exceeds the library's own array is refused before anything runs."""
