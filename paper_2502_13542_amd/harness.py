@@ -501,23 +501,27 @@ class PrefillPipeline:
 class HostCachePrefill:
     """Single-sequence prefill of one layer with the key-value cache in pinned host memory
     (Sec. 3.1: the cache may be kept in CPU memory).  HBM holds the representative keys of all
-    blocks (scoring never touches the cache) and a working cache of n_init/Bs + k_cap +
-    (n_local + m)/Bs + 1 blocks: the initial tokens, k_cap slots that `actqkv_gather_blocks`
-    fills from the host store with the blocks a window selects, then the local span and the
-    window itself.  The attention runs on the working cache as on any cache: the local span and
-    the window sit at positions shifted by a multiple of the block size (only the order of the
-    positions matters to the kernel), the selection it is given are the slot numbers.
+    blocks (scoring never touches the cache) and a number of blocks that does not depend on the
+    context's length: RING_CACHES working caches of nb_work = n_init/Bs + k_cap + (n_local + m)/Bs + 1
+    blocks, or what the overlapped schedule needs at least where that is more (nb_ring).  With windows
+    of 512 tokens, a local span of 512 and 16 blocks selected nb_work is 26 and nb_ring 229, so the host
+    store saves memory where the context is longer than that, 29K tokens.
 
-    Per window: the window's keys and values (token-major, as a model hands them over) are
-    appended behind the local span (`actqkv_append_kv`); the local span moves with the window,
-    so two working caches alternate and the span's blocks are carried over with
-    `actqkv_copy_bytes`.  While the context is still shorter than n_init + n_local the working
-    cache simply holds it whole at its true positions.  Needs m, n_init, n_local multiples of
-    the block size (only the last window may be ragged).  That is run(); run_overlapped() does the
-    same on a cache of its own in which the selected blocks keep their slots (region_geometry)."""
+    run(), window by window, uses two working caches: the initial tokens, k_cap slots that
+    `actqkv_gather_blocks` fills from the host store with the blocks a window selects, then the
+    local span and the window itself.  The attention runs on the working cache as on any cache: the
+    local span and the window sit at positions shifted by a multiple of the block size (only the
+    order of the positions matters to the kernel), the selection it is given are the slot numbers.
+    The window's keys and values (token-major, as a model hands them over) are appended behind the
+    local span (`actqkv_append_kv`); the local span moves with the window, so the two working caches
+    alternate and the span's blocks are carried over with `actqkv_copy_bytes`.  While the context
+    is still shorter than n_init + n_local the working cache simply holds it whole at its true
+    positions.  Needs m, n_init, n_local multiples of the block size (only the last window may be
+    ragged).  run_overlapped() does the same on all of the memory as one cache, in which the selected
+    blocks keep their slots (region_geometry)."""
 
     GROUP = 4                 # windows per hand-over between the streams of the overlapped schedule
-    RING_CACHES = 9           # size of the overlapped schedule's cache, in working caches of the other one
+    RING_CACHES = 9           # blocks kept in HBM, in working caches of the pass in window order
     ATTENTION_CUS = 224       # compute units its attention fills; the rest serves the other streams' kernels
     N_WORK = 2                # working caches of the pass in window order
 
@@ -535,13 +539,12 @@ class HostCachePrefill:
         def cache(nb):
             return (torch.zeros(nb, sh.n_kv_heads, bs, sh.head_dim, dtype=st, device=dev),
                     torch.zeros(nb, sh.n_kv_heads, sh.head_dim, bs, dtype=st, device=dev))
-        self.k_work, self.v_work = zip(*(cache(self.nb_work) for _ in range(self.N_WORK)))
         i32, f32 = dict(dtype=torch.int32, device=dev), dict(dtype=torch.float32, device=dev)
         self.idx_slots = torch.full((1, runner.k_cap), -1, **i32)
         self.n_ctx_work = torch.zeros(1, **i32)
         self.pos0_work = torch.zeros(1, **i32)
         self.gathered_blocks = 0
-        self.block_bytes = sh.n_kv_heads * bs * sh.head_dim * self.k_work[0].element_size()   # K or V of a block
+        self.block_bytes = sh.n_kv_heads * bs * sh.head_dim * st.itemsize   # K or V of a block
 
         # the overlapped schedule: one cache of initial tokens | slots | sequence region (a window sees
         # nothing behind its own positions, so the slots lie before the region)
@@ -560,6 +563,10 @@ class HostCachePrefill:
         self.region = self.region_geometry()
         self.nb_ring = self.region0 + (sh.n_local + self.n_segments * G * m) // bs
         self.k_ring, self.v_ring = cache(self.nb_ring)
+        # the working caches of run() lie in the same memory: a pass is one or the other
+        assert self.N_WORK * self.nb_work <= self.nb_ring
+        self.k_work, self.v_work = ([x[i * self.nb_work:(i + 1) * self.nb_work] for i in range(self.N_WORK)]
+                                    for x in (self.k_ring, self.v_ring))
         self.idx_all = torch.full((T, runner.k_cap), -1, **i32)
         self.n_sel_all = torch.zeros(T, **i32)
         self.idx_slots_all = torch.full((T, runner.k_cap), -1, **i32)
@@ -726,7 +733,7 @@ class HostCachePrefill:
         windows of 512, 16 blocks each) gathered 0.5 GB in 13.0 ms when every window brought its own
         blocks; now the attention and the write-back (128 MB) set the pace: 5.0 ms."""
         r, plan, sh, cs = self.runner, self.plan, self.runner.shape, self.runner.cs
-        bs, kw, vw, bb = sh.block_size, self.k_ring, self.v_ring, self.block_bytes
+        bs, kw, vw = sh.block_size, self.k_ring, self.v_ring
         nb_store = min(k_store.shape[0], r.nb_capacity)     # what slot_state has room for; no selection is past it
         cur = torch.cuda.current_stream()
         mover, attender, writer = self.mover, self.attender, self.writer

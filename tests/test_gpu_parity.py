@@ -2551,6 +2551,32 @@ def test_overlapped_host_cache_pass_equals_window_order(m, n_init, n_local, k_ca
     assert torch.equal(ke[:full], ks[:full]) and torch.equal(ve[:full], vs[:full])
 
 
+@pytest.mark.parametrize("m,k_cap,n_ctx", [(512, 16, 512 * 9), (256, 4, 256 * 40 + 77)])
+def test_host_cache_passes_share_their_blocks(m, k_cap, n_ctx):
+    """What the two passes keep in HBM is one memory of at most nine working caches however long the context is,
+    and neither pass depends on what the other left there."""
+    sh = LayerShape(8, 2, 64, 128, 2, 128, 512, "bf16")
+    w = synth.Workload("host_share", sh, n_ctx, m, k_cap, False, 5 + m, n_planted=6, n_layers=1)
+    q, k, v = synth.gen_layer(w, DEV)
+    rep = synth.pick_rep_keys(k, 128, sh.n_rep)
+    repd = torch.zeros(w.n_blocks, sh.n_rep, 2, 64, dtype=rep.dtype, device=DEV)
+    repd[: rep.shape[0]] = rep
+    runner = H.LayerRunner(sh, 1, m, w.n_blocks, k_cap, DEV)
+    host = H.HostCachePrefill(runner, H.make_prefill_plan(sh, n_ctx, m, None, DEV))
+    kept = {x.untyped_storage().data_ptr(): x.untyped_storage().nbytes()
+            for x in (*host.k_work, *host.v_work, host.k_ring, host.v_ring)}
+    assert sum(kept.values()) <= 9 * host.nb_work * 2 * host.block_bytes
+    ks, vs = (f(x, sh, w.n_blocks).cpu().pin_memory() for f, x in ((H.blocked_k, k), (H.blocked_vt, v)))
+    outs = []
+    for one in (host.run, host.run_overlapped, host.run, host.run_overlapped):
+        runner.reset()
+        out = torch.zeros_like(q)
+        one(q, k, v, ks, vs, repd, out)
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert all(torch.equal(outs[0], o) for o in outs[1:])
+
+
 def test_overlapped_host_cache_pass_takes_a_store_larger_than_the_context():
     """The slots' state has an entry per block of the runner; a store for a longer context than the
     plan's (and the runner's) changes nothing, and the store behind the context stays as it was."""
