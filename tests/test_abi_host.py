@@ -344,6 +344,27 @@ def test_cutoff_next_step_rejects(lib):
     assert call(ts=None) == -1 and call(b=None) == -1 and call(r=A16 + 2) == -3
 
 
+def test_another_build_may_lack_entry_points(tmp_path):
+    """ACTQKV_LIB names another build for comparisons, an older one too: what it lacks raises when it is called."""
+    import subprocess
+    import sys
+    (tmp_path / "old.c").write_text("int actqkv_version(void) { return 1; }\n"
+                                    "const char* actqkv_last_error(void) { return \"\"; }\n")
+    old = str(tmp_path / "old.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", str(tmp_path / "old.c"), "-o", old], check=True)
+    code = """
+from paper_2502_13542_amd import binding as B
+print(B.version())
+try:
+    B.select(1, None, 1, 1, 0, None, 1, None, None, None, None)
+except RuntimeError as e:
+    print("lacks" if "does not have this entry point" in str(e) else e)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120,
+                       env={**os.environ, "ACTQKV_LIB": old})
+    assert r.returncode == 0 and r.stdout.split() == ["1", "lacks"], r.stdout + r.stderr[-1000:]
+
+
 def test_pinned_verdict_does_not_outlive_its_tensor(monkeypatch):
     """A host tensor at an address where a pinned one was before is asked about anew (and the other way round): a
     kernel that reads pageable memory in place faults."""
