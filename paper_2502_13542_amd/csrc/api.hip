@@ -116,7 +116,6 @@ int launch_attention_prefill_f32(const actqkv_shape& sh, int batch, int m, const
                                  const int32_t* idx, const int32_t* n_sel, int k_cap, void* out, float* lse,
                                  float* scratch, unsigned int* counters, float scale, int sel_per_head,
                                  hipStream_t stream);
-bool decode_mfma_supported(const actqkv_shape& sh, int m);
 bool decode_fused_supported(const actqkv_shape& sh);
 size_t decode_mfma_scratch_floats(const actqkv_shape& sh, int batch, int k_cap);
 int launch_attention_decode_mfma(const actqkv_shape& sh, int batch, const void* q, const void* k_cache,
@@ -136,7 +135,7 @@ int launch_attention_decode_select(const actqkv_shape& sh, int batch, const void
 // scratch of the attention alone: the ticket and queue counters, then the partial results
 size_t attention_scratch_bytes(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
   size_t attn = 0;
-  if (decode_mfma_supported(sh, m)) attn = decode_mfma_scratch_floats(sh, batch, k_cap) * sizeof(float);
+  if (m == 1) attn = decode_mfma_scratch_floats(sh, batch, k_cap) * sizeof(float);
   if (prefill_mfma_supported(sh, m)) {
     // partial results exist only where a query tile's key tiles are cut into pieces
     const PfSplits splits = prefill_splits(sh, batch, m, k_cap, cus);
@@ -174,7 +173,7 @@ int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, co
                      const Workspace& ws, int sel_per_head, hipStream_t stream, int first_cus, int late_cus,
                      hipStream_t stream_late, bool pieces_of_one) {
   const float scale = sh.softmax_scale > 0.f ? sh.softmax_scale : 1.f / std::sqrt(float(sh.head_dim));
-  if (decode_mfma_supported(sh, m))   // (no queue: one launch does all the work)
+  if (m == 1)   // (no queue: one launch does all the work)
     return launch_attention_decode_mfma(sh, batch, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx,
                                         idx, n_sel, k_cap, out, lse, ws.scratch_f32(), ws.counters(), scale,
                                         sel_per_head, stream);

@@ -737,11 +737,9 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   }
 }
 
-// One query token per sequence, any storage type and head size the library takes.
-bool decode_mfma_supported(const actqkv_shape& sh, int m) { return m == 1 && sh.n_q_heads / sh.n_kv_heads <= 8; }
-// The kernels that do more than the attention exist for the serving shape only.
+// The attention of one query token per sequence takes every storage type and head size the library does.  The kernels that do more than the attention exist for the serving shape only.
 bool decode_fused_supported(const actqkv_shape& sh) {
-  return decode_mfma_supported(sh, 1) && sh.dtype == ACTQKV_BF16 && sh.head_dim == kDcD;
+  return sh.dtype == ACTQKV_BF16 && sh.head_dim == kDcD;
 }
 
 // Launch shape: workgroups of 8 wavefronts, one per compute unit (two wavefronts per SIMD, each with

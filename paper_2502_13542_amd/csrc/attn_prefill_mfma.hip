@@ -668,7 +668,7 @@ __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_queued_kernel(Pf
 }
 
 bool prefill_mfma_supported(const actqkv_shape& sh, int m) {
-  return sh.dtype == ACTQKV_BF16 && m > 1 && sh.n_q_heads / sh.n_kv_heads <= 8;
+  return sh.dtype == ACTQKV_BF16 && m > 1;
 }
 
 // Two-term probabilities: they enter the second product as the value rounded to bf16 plus what the rounding left,
