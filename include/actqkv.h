@@ -316,7 +316,7 @@ int actqkv_retrieval_attention_per_head(const actqkv_shape* shape, int batch, in
  * depend on earlier selections but on no attention): the launch shape is an argument of the call.
  *   first_cus  1..256: the attention fills only that many of the chip's 256 compute units and
  *            leaves the rest to the concurrent work (a single window is cut into fewer pieces;
- *            a batch of windows (m > 1, bf16, head_dim 128), whose (query tile, KV head) items go
+ *            a batch of windows (m > 1, bf16), whose (query tile, KV head) items go
  *            through a queue, gets that many persistent workgroups).
  *   late_cus   0, or n_kv_heads..256: a second team of that many workgroups for the same queue,
  *            launched by this call on `stream_late`, typically the stream that carries the other
@@ -408,7 +408,7 @@ int actqkv_decode_retrieve(const actqkv_shape* shape, int batch, const void* q_t
  *            them writes budget_after (NULL: not written).
  *   idx, n_sel (required), theta, budget (optional)  outputs as of actqkv_select.
  * Results: the selection is that of actqkv_select (the density up to the order of an fp32
- * sum, since 512 instead of 1024 threads add it up); the output is that of
+ * sum); the output is that of
  * actqkv_retrieval_attention up to fp32 summation order (the key spans are merged in another
  * order). */
 int actqkv_decode_select_attention(const actqkv_shape* shape, int batch, const void* q,

@@ -737,7 +737,8 @@ __global__ __launch_bounds__(kDcThreads) void decode_layer_kernel(DcParams p, Dc
   }
 }
 
-// The attention of one query token per sequence takes every storage type and head size the library does.  The kernels that do more than the attention exist for the serving shape only.
+// The attention of one query token per sequence takes every storage type and head size the library
+// does.  The kernels that do more than the attention exist for the serving shape only.
 bool decode_fused_supported(const actqkv_shape& sh) {
   return sh.dtype == ACTQKV_BF16 && sh.head_dim == kDcD;
 }

@@ -1,14 +1,15 @@
 // Retrieval attention of a prefill window on the matrix cores
 // (Sec. 3.1, Eq. (2): O^t = Attention(Q^t, [K^t, K*], [V^t, V*]); bf16 storage, fp32 accumulation).
 //
-// Work split.  A workgroup of 8 wavefronts owns 256 query rows that share one KV
-// head, each wavefront 32 of them.  The rows are numbered position by position with the G
-// heads of the KV head side by side, so every group size fills the wavefronts (with a
-// wavefront per head, seven heads left one of eight idle: 1.92 instead of 1.87 ms for a pass over 50001 tokens).  The key tiles of the
-// window - initial tokens, the blocks chosen by actqkv_select (read from device
-// memory), the local span and the causal part of the window - form one list of
-// 128-key blocks; it is cut into `splits` contiguous pieces, one workgroup each,
-// so that a 512-token window still fills all 256 compute units; the workgroup that
+// Work split.  A workgroup of 8 wavefronts owns 256 / KS query rows that share one KV
+// head, 32 of them for KS wavefronts (KS = 1, 2 or 4), which share the keys of every tile and merge
+// in LDS at the end; prefill_splits says when.  The rows are numbered position by position with
+// the G heads of the KV head side by side, so every group size fills the wavefronts (with a
+// wavefront per head, seven heads left one of eight idle: 1.92 instead of 1.87 ms for a pass over
+// 50001 tokens).  The key tiles of the window - initial tokens, the blocks chosen by
+// actqkv_select (read from device memory), the local span and the causal part of the window -
+// form one list of 128-key blocks; it is cut into `splits` contiguous pieces, one workgroup
+// each, so that a 512-token window still fills all 256 compute units; the workgroup that
 // finishes last among the pieces of a query tile merges them.  Workgroups of one
 // KV head sit on one XCD (blockIdx % Hk picks the head), so that head's gathered
 // tiles stay in that XCD's L2.

@@ -69,8 +69,10 @@ struct PfSplits {
 };
 PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int cus);   // cus: compute units to fill
 size_t prefill_partials_most(const actqkv_shape& sh, int batch, int m);
-// prefill on the matrix cores: per workgroup and piece, 8 wavefronts x (16 eight-byte words of
-// four bf16 of normalised output + one word (max, sum)) x 64 lanes, counted in floats
+// prefill on the matrix cores: per workgroup and piece, 8 wavefronts x (at most 16 eight-byte words of
+// output + one word (max, sum)) x 64 lanes, counted in floats.  A word of output is four normalised bf16 for whole
+// query tiles with one-term probabilities, otherwise two fp32: 16 words either way, and 8 for 64 query
+// rows (128 with 64 channels per head)
 constexpr size_t kPfPartialFloats = 8 * (32 + 2) * 64;
 constexpr int kMaxWindow = 8192;
 

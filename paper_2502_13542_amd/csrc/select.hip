@@ -1,6 +1,6 @@
 // Information density, per-layer budget and block selection
-// (Sec. 4.2, Eq. (11), Eq. (12); Alg. 1, second and third loop): one workgroup of 16
-// wavefronts per sequence runs the selection step.
+// (Sec. 4.2, Eq. (11), Eq. (12); Alg. 1, second and third loop): one wavefront per sequence runs
+// the selection step, for long rows or many blocks one workgroup of 16 wavefronts (launch_select).
 #include "common.h"
 #include "launch.h"
 #include "select_body.h"

@@ -1,8 +1,8 @@
 // The selection step as a device function: information density, per-layer budget and the
 // tournament for the best blocks (Sec. 4.2, Eq. (11), Eq. (12); Alg. 1, second and third loop).
-// Shared by the selection kernel (one workgroup of 1024 threads per sequence) and by the decode
-// attention that selects for itself (every workgroup of 512 threads repeats its sequence's
-// selection while its first keys and values are on their way).
+// Shared by the selection kernels (one workgroup of 1024 threads per sequence, or one wavefront:
+// select_wave) and by the decode attention that selects for itself (every workgroup of 512 threads, or
+// a wavefront of it, repeats its sequence's selection while the first keys and values are on their way).
 //
 // The density is a two-pass softmax entropy over the eligible scores (or, as a variant, over the
 // scores of the k_cap best blocks once the tournament has found them).  The E best blocks come

@@ -1,5 +1,5 @@
 """GPU parity: every entry point of libactqkv.so against the CPU oracle, element by
-element, on the same seeded inputs.  All calls go through the C ABI (ctypes binding)."""
+element, on the same seeded inputs.  All calls go through the C ABI (binding.py)."""
 import ctypes
 import math
 
@@ -2682,8 +2682,8 @@ def test_prefill_with_the_cache_in_host_memory():
 def test_retrieval_per_kv_head(dtype, hq, hkv, d, m, n_ctx):
     """The per-KV-head variant: actqkv_score_blocks_per_head, actqkv_select on batch * Hk rows
     (with a cut-off state per row) and actqkv_retrieval_attention_per_head against the oracle's
-    retrieve_per_head / retrieval_attention_per_head, for a prefill window (matrix-core and
-    row kernels) and a decode step."""
+    retrieve_per_head / retrieval_attention_per_head, for a prefill window (bf16 and
+    fp32 kernels) and a decode step."""
     sh = LayerShape(hq, hkv, d, 128, 4, 128, 256, dtype)
     cs = B.c_shape(sh)
     td = torch.bfloat16 if dtype == "bf16" else torch.float32
