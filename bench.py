@@ -4,14 +4,14 @@
 Prefill (the headline).  A step is one whole single-layer windowed prefill of the
 workload's context: for every window, actqkv_build_probe -> actqkv_score_blocks ->
 actqkv_select -> actqkv_retrieval_attention, in order, on one stream, with all inputs
-resident in HBM.  The default workload is the benchmark's configs[2] (LLaMA3-8B layer,
-128K tokens, window 512, top-k 32 with the dynamic cut-off): the one its metric
-"tokens/s per layer @128K" is quoted on.  The step's launches are captured once in a HIP
+resident in HBM.  The default workload is c3_128k (LLaMA3-8B layer, 128K tokens,
+window 512, top-k 32 with the dynamic cut-off): the one the metric "tokens/s per layer
+@128K" is quoted on.  The step's launches are captured once in a HIP
 graph (checked against the eager result on several replays) and the timed region replays
 it; then one eager pass of the same step brackets every attention launch with HIP events
 on its stream for the roofline figure (a graph cannot hold timing events).
 
-Decode (second part of the metric).  configs[3]: 16 sequences x 32 layers x 64K cached
+Decode (second part of the metric).  c4_decode: 16 sequences x 32 layers x 64K cached
 tokens, one new token per sequence per step, per-layer dynamic cut-off; a step is all 32
 layers; reported as us/step with the HBM roofline of the decode attention kernel.
 
@@ -477,7 +477,7 @@ def _recall_of(w, torch, B, H, synth, selections=None):
 
 
 def bench_prefill_layers(args, torch, B, H, synth):
-    """configs[4]-style run: all `--layers` layers of one sequence, every layer with its own
+    """c5_200k-style run: all `--layers` layers of one sequence, every layer with its own
     seeded inputs, outlier rate, statistics and cut-off profile, in the benchmarked schedule
     (one call per step and chunk of windows, attention on a second stream), layer after layer
     in one HIP graph.  Reported in token-layers per second, i.e. the per-layer rate."""
@@ -651,7 +651,7 @@ def bench_prefill_host_cache(args, torch, B, H, synth):
 
 
 def bench_decode(args, torch, B, H, synth):
-    """configs[3]: batch 16 x 32 layers x 64K cached tokens, `decode_steps` steps."""
+    """c4_decode: batch 16 x 32 layers x 64K cached tokens, `decode_steps` steps."""
     dev = "cuda:0"
     w = synth.WORKLOADS["c4_decode"]
     if args.decode_layers:
@@ -926,7 +926,7 @@ def main() -> int:
     ap.add_argument("--attention-cus", type=int, default=224,
                     help="prefill, two streams: compute units the attention may fill")
     ap.add_argument("--layers", type=int, default=1,
-                    help="prefill: > 1 runs that many layers of the workload (configs[4]: --workload c5_200k "
+                    help="prefill: > 1 runs that many layers of the workload (as in --workload c5_200k "
                          "--layers 32), each with its own inputs, and reports only that run")
     ap.add_argument("--host-cache", action="store_true",
                     help="also time the prefill pass with the cache in pinned host memory (reported as "

@@ -92,19 +92,19 @@ class Workload:
 _LLAMA = LayerShape(32, 8, 128, 128, 4, 128, 512, "bf16")
 
 WORKLOADS: Dict[str, Workload] = {
-    # configs[0]: small fp32 case, full parity on every window.
+    # small fp32 case, full parity on every window.
     "c1_8k_fp32": Workload("c1_8k_fp32", LayerShape(8, 2, 64, 128, 4, 128, 256, "fp32"),
                            8192, 256, 8, False, MASTER_SEED + 0, outlier_rate=0.02,
                            outlier_kind="boost", n_planted=8),
-    # configs[1]: LLaMA3-8B layer, 32K prefill.
+    # LLaMA3-8B layer, 32K prefill.
     "c2_32k": Workload("c2_32k", _LLAMA, 32768, 512, 16, False, MASTER_SEED + 1),
-    # configs[2]: 128K prefill with the dynamic cut-off (the headline metric).
+    # 128K prefill with the dynamic cut-off (the headline metric).
     "c3_128k": Workload("c3_128k", _LLAMA, 131072, 512, 32, True, MASTER_SEED + 2,
                         n_planted=32),
-    # configs[3]: decode, 16 sequences x 32 layers x 64K cached tokens.
+    # decode, 16 sequences x 32 layers x 64K cached tokens.
     "c4_decode": Workload("c4_decode", _LLAMA, 65536, 1, 32, True, MASTER_SEED + 3,
                           n_planted=32, n_layers=32, batch=16, decode_steps=256),
-    # configs[4]: 200K-token stream, 32 layers.
+    # 200K-token stream, 32 layers.
     "c5_200k": Workload("c5_200k", _LLAMA, 204800, 512, 32, True, MASTER_SEED + 4,
                         n_planted=32, n_layers=32, outlier_rate=0.0175),
 }

@@ -87,7 +87,7 @@ def run_prefill_case(w: synth.Workload, attend=None, use_cutoff=None, layer=0):
 
 
 def test_c1_fp32_full_parity():
-    # configs[0] as it is: every window, every row
+    # c1_8k_fp32 as it is: every window, every row
     n_exact, n_win = run_prefill_case(synth.WORKLOADS["c1_8k_fp32"])
     assert n_exact >= n_win - 2
 
@@ -108,25 +108,25 @@ def test_llama_shape_bf16_cutoff_ragged():
 
 
 def test_c2_32k_full_size_sampled_windows():
-    # configs[1] at full size, in the launch configuration bench.py uses; the oracle checks the
+    # c2_32k at full size, in the launch configuration bench.py uses; the oracle checks the
     # probe and the selection of every window and the attention of a spread of windows
     run_prefill_case(synth.WORKLOADS["c2_32k"], attend=[0, 1, 7, 31, 63])
 
 
 def test_c3_128k_full_size_sampled_windows():
-    # configs[2] (the benchmarked workload) at full size with the dynamic cut-off
+    # c3_128k (the benchmarked workload) at full size with the dynamic cut-off
     run_prefill_case(synth.WORKLOADS["c3_128k"], attend=[2, 64, 255])
 
 
 def test_c5_200k_full_size_sampled_windows():
-    # configs[4] at full size in its ragged form (200,000 tokens: the last window has 320 rows),
+    # c5_200k at full size in its ragged form (200,000 tokens: the last window has 320 rows),
     # its last layer (3 % outlier tokens): every window's probe, scores, density, budget and
     # selection, and the attention of a spread of windows
     run_prefill_case(synth.scaled(synth.WORKLOADS["c5_200k"], n_ctx=200000), attend=[5, 211, 390], layer=31)
 
 
 def test_c3_128k_two_stream_pipeline_as_benchmarked():
-    """configs[2] at full size in the schedules of PrefillPipeline, the last one being the one
+    """c3_128k at full size in the schedules of PrefillPipeline, the last one being the one
     bench.py times: (1) three streams, calls of one window each: probes, then scoring and
     selection 16 windows behind them, then the attention of up to 32 windows per launch with 224
     of the 256 compute units; (2) the same with scoring and selection on the probes' stream;
@@ -1118,7 +1118,7 @@ def test_decode_step_batch(dtype, hq, hkv, n_ctxs, launches):
 
 
 def test_decode_full_size_layer_as_benchmarked():
-    """One layer of configs[3] at full size in the launch configuration bench.py times: 16
+    """One layer of c4_decode at full size in the launch configuration bench.py times: 16
     sequences with 65536 cached tokens each (4.3 GB of keys and values), a new token appended,
     k_cap 32 with the cut-off; the selection and the output of sampled sequences against the
     oracle, the whole batch for finiteness and for equality between two runs."""
