@@ -237,20 +237,36 @@ __global__ __launch_bounds__(256) void copy_bytes_kernel(u32x4* __restrict__ dst
 // The same over the host link: few workgroups with many words in flight each.  The link takes about
 // 57 GB/s whatever asks; a workgroup per 4 KB filled the memory system's queues with host accesses,
 // and a 2 us kernel beside an 8 MB copy took 87 us.
+// Stores into host memory go past the L2 (system scope: sc0 and sc1).  Ordinary ones stay there as dirty lines of
+// memory behind the link, and every kernel on the chip waits for their evictions: the attention of four windows takes
+// 171 us, 457 beside such a copy and 175 beside this one, which is also the faster copy (55 GB/s instead of 48).
+// With fewer workgroups and ordinary stores it is one or the other: 2 of them 187 us and 45 GB/s, 4 281 us.
 constexpr int kLinkWgs = 8, kLinkBatch = 8;
+template <bool kToHost>
 __global__ __launch_bounds__(256) void copy_bytes_link_kernel(u32x4* __restrict__ dst, const u32x4* __restrict__ src,
                                                               size_t n) {
-  for (size_t i0 = size_t(blockIdx.x) * 256 * kLinkBatch; i0 < n; i0 += size_t(gridDim.x) * 256 * kLinkBatch) {
+  constexpr int kPiece = 256 * kLinkBatch;
+  for (size_t i0 = size_t(blockIdx.x) * kPiece; i0 < n; i0 += size_t(gridDim.x) * kPiece) {
     u32x4 x[kLinkBatch];
 #pragma unroll
     for (int b = 0; b < kLinkBatch; ++b) {
       const size_t i = i0 + b * 256 + threadIdx.x;
       x[b] = src[i < n ? i : n - 1];
     }
+    if constexpr (kToHost) {
+      constexpr int kSystemScope = 1 | 16;             // sc0, sc1
+      const size_t left = n - i0;                      // (what lies behind the piece or the copy is not written)
+      const __amdgpu_buffer_rsrc_t to =
+          __builtin_amdgcn_make_buffer_rsrc(dst + i0, 0, int(left < kPiece ? left : kPiece) * 16, 0x00020000);
 #pragma unroll
-    for (int b = 0; b < kLinkBatch; ++b) {
-      const size_t i = i0 + b * 256 + threadIdx.x;
-      if (i < n) dst[i] = x[b];
+      for (int b = 0; b < kLinkBatch; ++b)
+        __builtin_amdgcn_raw_buffer_store_b128(x[b], to, (b * 256 + int(threadIdx.x)) * 16, 0, kSystemScope);
+    } else {
+#pragma unroll
+      for (int b = 0; b < kLinkBatch; ++b) {
+        const size_t i = i0 + b * 256 + threadIdx.x;
+        if (i < n) dst[i] = x[b];
+      }
     }
   }
 }
@@ -606,9 +622,10 @@ int actqkv_copy_bytes(void* dst, const void* src, size_t bytes, void* stream) {
     return set_error(ACTQKV_EALIGN, "copy_bytes: pointers must be 16-byte aligned");
   if (bytes == 0) return ACTQKV_OK;
   const size_t n = bytes / 16;
-  if (in_host_memory(dst) || in_host_memory(src)) {
-    hipLaunchKernelGGL(copy_bytes_link_kernel, dim3(kLinkWgs), dim3(256), 0, static_cast<hipStream_t>(stream),
-                       static_cast<u32x4*>(dst), static_cast<const u32x4*>(src), n);
+  const bool to_host = in_host_memory(dst);
+  if (to_host || in_host_memory(src)) {
+    hipLaunchKernelGGL(to_host ? copy_bytes_link_kernel<true> : copy_bytes_link_kernel<false>, dim3(kLinkWgs), dim3(256), 0,
+                       static_cast<hipStream_t>(stream), static_cast<u32x4*>(dst), static_cast<const u32x4*>(src), n);
     return hip_status("copy_bytes");
   }
   const unsigned blocks = unsigned(std::min<size_t>((n + 255) / 256, 256 * 16));
