@@ -16,6 +16,8 @@
 // into the running statistics one after the other, but a merge is a function of each window's
 // own (mean, M2) only, so everything else is done for all windows at once (kernels further
 // down).  Four launches for n windows instead of 3 n.
+#include <algorithm>
+
 #include "common.h"
 #include "launch.h"
 #include "probe_identity.h"
@@ -54,9 +56,9 @@ __device__ __forceinline__ void bias_partials(typename Vec<T>::raw (&x)[kRowsPer
         t += e * e * iv[v];
       }
       // the 8 column lanes of a row are neighbouring lanes of one wave
-      t += __shfl_xor(t, 1, 64);
-      t += __shfl_xor(t, 2, 64);
-      t += __shfl_xor(t, 4, 64);
+      t += lane_xor_f32<1>(t);
+      t += lane_xor_f32<2>(t);
+      t += lane_xor_f32<4>(t);
       a[i] = r0 + i < m ? t : 0.f;
     }
     if (cl == 0 && r0 < m_pad) {
@@ -218,70 +220,78 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const 
 // own mean), pprobe [n][chunks][d], asum [n][chunks rounded up to 16], a [n][m rounded up to 16].
 constexpr int kRmThreads = 256;
 
+// grid (chunks, windows, ceil(d / V / cols)): a workgroup takes `cols` 16-byte channel groups (64 .. 256) of the chunk's
+// rows, row lane rl of 256 / cols the rows rl, rl + lanes, ..., and the lanes' sums are added in their order.  A compute
+// unit does not get more than 35-50 GB/s, so the channels are cut finer where there are few chunks; 16 rows are
+// requested together.
 template <typename T>
 __global__ __launch_bounds__(kRmThreads) void probe_rows_moments_kernel(const T* __restrict__ q_win,
                                                                         float* __restrict__ part, int m, int d,
-                                                                        int n_chunks) {
+                                                                        int n_chunks, int cols) {
   constexpr int V = Vec<T>::N;
-  constexpr int G = 2;                               // 16-byte channel groups per thread
-  constexpr int R = 8;                               // rows requested together
+  constexpr int R = 16;                              // rows requested together
   typedef typename Vec<T>::raw raw_t;
+  __shared__ f32x4 sums[kRmThreads * 2 * V / 4];
   const int rc = blockIdx.x, w = blockIdx.y;
   const T* q = q_win + size_t(w) * m * d;
-  int ch[G];
-  bool ok[G];
-  float c[G][V], s1[G][V], s2[G][V];
+  const int rls = kRmThreads / cols, rl = int(threadIdx.x) / cols, col = int(threadIdx.x) - rl * cols;
+  const int ch = (int(blockIdx.z) * cols + col) * V;
+  const bool ok = ch < d && rl < rls;
+  float c[V], s1[V], s2[V];
+  Vec<T>::load(q + (ok ? ch : 0), c);
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    ch[g] = ((blockIdx.z * G + g) * kRmThreads + threadIdx.x) * V;
-    ok[g] = ch[g] < d;
-    Vec<T>::load(q + (ok[g] ? ch[g] : 0), c[g]);
-#pragma unroll
-    for (int v = 0; v < V; ++v) s1[g][v] = s2[g][v] = 0.f;
-  }
+  for (int v = 0; v < V; ++v) s1[v] = s2[v] = 0.f;
   const int r0 = rc * kRowChunk, r1 = min(r0 + kRowChunk, m);
-  for (int r = r0; r < r1; r += R) {
-    raw_t x[R][G];
+  for (int r = r0 + rl; r < r1; r += R * rls) {
+    raw_t x[R];
 #pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-        x[i][g] = Vec<T>::load_raw(q + size_t(min(r + i, r1 - 1)) * d + (ok[g] ? ch[g] : 0));
+    for (int i = 0; i < R; ++i) x[i] = Vec<T>::load_raw(q + size_t(min(r + i * rls, r1 - 1)) * d + (ok ? ch : 0));
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      if (r + i < r1) {
+      if (r + i * rls < r1) {
+        float f[V];
+        Vec<T>::widen(x[i], f);
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          float f[V];
-          Vec<T>::widen(x[i][g], f);
-#pragma unroll
-          for (int v = 0; v < V; ++v) {
-            const float t = f[v] - c[g][v];
-            s1[g][v] += t;
-            s2[g][v] += t * t;
-          }
+        for (int v = 0; v < V; ++v) {
+          const float t = f[v] - c[v];
+          s1[v] += t;
+          s2[v] += t * t;
         }
       }
     }
   }
-  float* p1 = part + (size_t(w) * n_chunks + rc) * 2 * d;
+  if (rls > 1) {
+    f32x4* mine = sums + threadIdx.x * (2 * V / 4);
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    if (ok[g]) {
+    for (int v = 0; v < V; v += 4) {
+      mine[v / 4] = f32x4{s1[v], s1[v + 1], s1[v + 2], s1[v + 3]};
+      mine[(V + v) / 4] = f32x4{s2[v], s2[v + 1], s2[v + 2], s2[v + 3]};
+    }
+    __syncthreads();
+    if (rl > 0) return;
+    for (int o = 1; o < rls; ++o) {
+      const f32x4* from = sums + (o * cols + col) * (2 * V / 4);
 #pragma unroll
-      for (int v = 0; v < V; v += 4) {
-        *reinterpret_cast<f32x4*>(p1 + ch[g] + v) = f32x4{s1[g][v], s1[g][v + 1], s1[g][v + 2], s1[g][v + 3]};
-        *reinterpret_cast<f32x4*>(p1 + d + ch[g] + v) = f32x4{s2[g][v], s2[g][v + 1], s2[g][v + 2], s2[g][v + 3]};
+      for (int v = 0; v < V; ++v) {
+        s1[v] += from[v / 4][v % 4];
+        s2[v] += from[(V + v) / 4][v % 4];
       }
     }
   }
+  if (!ok) return;
+  float* p1 = part + (size_t(w) * n_chunks + rc) * 2 * d;
+#pragma unroll
+  for (int v = 0; v < V; v += 4) {
+    *reinterpret_cast<f32x4*>(p1 + ch + v) = f32x4{s1[v], s1[v + 1], s1[v + 2], s1[v + 3]};
+    *reinterpret_cast<f32x4*>(p1 + d + ch + v) = f32x4{s2[v], s2[v + 1], s2[v + 2], s2[v + 3]};
+  }
 }
 
-// grid (d / 32), 1024 threads = 32 channels x 32 window lanes.  Window lane wl first turns the
-// chunk sums of windows wl, wl + 32, ... into the window's own (mean, M2) in LDS; then window
-// lane 0 merges them into the running statistics in window order (the merge of Eq. (8), as in
-// probe_stats_bias_kernel).  The count is published by the next kernel (every thread here
-// reads the old one).
+// grid (d / 32), 1024 threads = 32 channels x 32 lanes.  The chunk sums of every window become the window's own
+// (mean, M2) in LDS: with fewer than 32 windows several lanes share one (32 / n, rounded down to a power of two), lane
+// u of them the chunks u, u + share, ..., whose sums are added in lane order.  Then lane 0 merges the windows into the
+// running statistics in window order (the merge of Eq. (8), as in probe_stats_bias_kernel).  The count is published by
+// the next kernel (every thread here reads the old one).
 template <typename T>
 __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __restrict__ q_win,
                                                                  const float* __restrict__ part,
@@ -289,24 +299,55 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
                                                                  float* __restrict__ stat_out, int n, int m,
                                                                  int d, int n_chunks, float eps) {
   extern __shared__ float wm[];                      // [n][2][32]: the windows' own mean and M2
+  __shared__ float lane_sum[2][32][32];
+  constexpr int kBatch = 8;                          // chunks requested together
   const int cl = threadIdx.x & 31, wl = threadIdx.x >> 5;
   const int ch = blockIdx.x * 32 + cl;
   const float nb = float(m);
-  if (ch < d) {
-    for (int w = wl; w < n; w += 32) {
+  int share = 1;
+  while (share * 2 * n <= 32) share *= 2;
+  const int u = wl % share;
+  float n_run = 0.f, mean = 0.f, m2 = 0.f;
+  if (wl == 0 && ch < d) n_run = stats[0], mean = stats[4 + ch], m2 = stats[4 + d + ch];   // (in flight meanwhile)
+  for (int w0 = 0; w0 < n; w0 += 32 / share) {
+    const int w = w0 + wl / share;
+    const bool live = w < n && ch < d;
+    float t1 = 0.f, t2 = 0.f;
+    const float first = live ? to_f32(q_win[size_t(w) * m * d + ch]) : 0.f;
+    if (live) {
       const float* p1 = part + size_t(w) * n_chunks * 2 * d + ch;
-      float t1 = 0.f, t2 = 0.f;
-      for (int rc = 0; rc < n_chunks; ++rc) {
-        t1 += p1[size_t(rc) * 2 * d];
-        t2 += p1[size_t(rc) * 2 * d + d];
+      for (int rc = u; rc < n_chunks; rc += kBatch * share) {
+        float a[kBatch], b[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {           // all loads first: they overlap
+          const int c = rc + i * share < n_chunks ? rc + i * share : rc;
+          a[i] = p1[size_t(c) * 2 * d];
+          b[i] = p1[size_t(c) * 2 * d + d];
+        }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+          t1 += rc + i * share < n_chunks ? a[i] : 0.f;
+          t2 += rc + i * share < n_chunks ? b[i] : 0.f;
+        }
       }
-      wm[(w * 2 + 0) * 32 + cl] = to_f32(q_win[size_t(w) * m * d + ch]) + t1 / nb;
+    }
+    if (share > 1) {                                 // (one round: all windows have their lanes)
+      lane_sum[0][wl][cl] = t1;
+      lane_sum[1][wl][cl] = t2;
+      __syncthreads();
+      if (u == 0)
+        for (int o = 1; o < share; ++o) {
+          t1 += lane_sum[0][wl + o][cl];
+          t2 += lane_sum[1][wl + o][cl];
+        }
+    }
+    if (live && u == 0) {
+      wm[(w * 2 + 0) * 32 + cl] = first + t1 / nb;
       wm[(w * 2 + 1) * 32 + cl] = fmaxf(t2 - t1 * t1 / nb, 0.f);
     }
   }
   __syncthreads();
   if (wl != 0 || ch >= d) return;
-  float n_run = stats[0], mean = stats[4 + ch], m2 = stats[4 + d + ch];
   for (int w = 0; w < n; ++w) {
     const float mean_b = wm[(w * 2 + 0) * 32 + cl], m2_b = wm[(w * 2 + 1) * 32 + cl];
     const float n_new = n_run + nb;
@@ -329,27 +370,42 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
   stats[4 + d + ch] = m2;
 }
 
-// grid (chunks, windows), 4 wavefronts; wavefront v takes rows v, v + 4, ... of the chunk, a lane
-// the 16-byte groups lane, lane + 64, ... of a row (NI of them: d <= 64 * NI * V channels).
-// LDS: mean and 1/var of the window (2 d floats), reused for the sum over the 4 wavefronts.
-template <typename T>
-__global__ __launch_bounds__(kRmThreads) void probe_rows_bias_weigh_kernel(
+// grid (chunks, windows), NW wavefronts; wavefront v takes rows v, v + NW, ... of the chunk, a lane
+// the 16-byte groups lane, lane + 64, ... of a row (NI of them: d <= 64 * NI * V channels), R rows at a time and the
+// next R in flight meanwhile (8 groups of each).  NI is the least that holds a row: with room for 4096 channels whatever
+// the row (and half of the lanes of rows_moments idle, 8 rows at once), the four launches of 32 windows of 256 tokens with
+// 512 channels took 49 us, 26 so; of 4 windows of 512 tokens with 4096 channels 50, 36 (chunks of 32 rows).
+// LDS: mean and 1/var of the window (2 kRowLen floats), reused for the sum over the wavefronts.
+template <typename T, int NI, int NW>
+__global__ __launch_bounds__(64 * NW) void probe_rows_bias_weigh_kernel(
     const T* __restrict__ q_win, const float* __restrict__ stat_in, float* __restrict__ stats, float add_count,
     int mean_pooling, float* __restrict__ pprobe, float* __restrict__ asum, float* __restrict__ a_rows, int m,
-    int m_pad, int d, int n_chunks, int asum_stride) {
+    int m_pad, int d, int rows, int n_chunks, int asum_stride) {
   constexpr int V = Vec<T>::N;
-  constexpr int NI = 64 / V;
+  constexpr int R = NI < 8 ? 8 / NI : 1;
   typedef typename Vec<T>::raw raw_t;
   constexpr int kRowLen = 64 * NI * V;                             // channels a wavefront covers
-  extern __shared__ __attribute__((aligned(16))) float rw_lds[];   // [2][kRowLen]
-  __shared__ float red[4];
+  extern __shared__ __attribute__((aligned(16))) float rw_lds[];   // [max(2 kRowLen, NW / 2 d)]
+  __shared__ float red[NW];
   const int rc = blockIdx.x, w = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const T* q = q_win + size_t(w) * m * d;
   float* mu = rw_lds;
   float* iv = rw_lds + kRowLen;
+  const int r0 = rc * rows, r1 = min(r0 + rows, m);
+  auto load_rows = [&](int r, raw_t (&x)[R][NI]) {
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int c = (lane + 64 * i) * V;
+        x[j][i] = Vec<T>::load_raw(q + size_t(min(r + j * NW, r1 - 1)) * d + (c < d ? c : 0));
+      }
+  };
+  raw_t x[R][NI];
+  load_rows(r0 + wave, x);
   // channels past d (rows shorter than a wavefront's 64 * NI * V) get mean 0 and weight 0
-  for (int i = threadIdx.x * 4; i < kRowLen; i += kRmThreads * 4) {
+  for (int i = threadIdx.x * 4; i < kRowLen; i += 64 * NW * 4) {
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     *reinterpret_cast<f32x4*>(mu + i) = i < d ? *reinterpret_cast<const f32x4*>(stat_in + size_t(w) * 3 * d + i) : zero;
     *reinterpret_cast<f32x4*>(iv + i) = i < d ? *reinterpret_cast<const f32x4*>(stat_in + size_t(w) * 3 * d + d + i) : zero;
@@ -362,27 +418,17 @@ __global__ __launch_bounds__(kRmThreads) void probe_rows_bias_weigh_kernel(
 #pragma unroll
     for (int v = 0; v < V; ++v) acc[i][v] = 0.f;
   float a_sum = 0.f;
-  const int r0 = rc * kRowChunk, r1 = min(r0 + kRowChunk, m);
-  auto load_row = [&](int r, raw_t (&x)[NI]) {
+  for (int r = r0 + wave; r < r1; r += R * NW) {
+    // the wavefront's next rows are requested before these are used (the last ones ask for the chunk's last row once
+    // more, which costs nothing that matters)
+    raw_t xn[R][NI];
+    load_rows(r + R * NW, xn);
+    float t[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) t[j] = 0.f;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int c = (lane + 64 * i) * V;
-      x[i] = Vec<T>::load_raw(q + size_t(r) * d + (c < d ? c : 0));
-    }
-  };
-  raw_t x[NI];
-  if (r0 + wave < r1) load_row(r0 + wave, x);
-  for (int r = r0 + wave; r < r1; r += 4) {
-    // the wavefront's next row is requested before this one is used: a row's worth of loads is in
-    // flight the whole time (the last row asks for itself once more, which costs nothing that matters)
-    raw_t xn[NI];
-    load_row(r + 4 < r1 ? r + 4 : r, xn);
-    float t = 0.f;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int c = (lane + 64 * i) * V;
-      float f[V];
-      Vec<T>::widen(x[i], f);
       f32x4 mu4[V / 4], iv4[V / 4];
 #pragma unroll
       for (int u = 0; u < V / 4; ++u) {
@@ -390,26 +436,41 @@ __global__ __launch_bounds__(kRmThreads) void probe_rows_bias_weigh_kernel(
         iv4[u] = *reinterpret_cast<const f32x4*>(iv + c + 4 * u);
       }
 #pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const float e = f[v] - mu4[v >> 2][v & 3];
-        t += e * e * iv4[v >> 2][v & 3];
+      for (int j = 0; j < R; ++j) {
+        float f[V];
+        Vec<T>::widen(x[j][i], f);
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const float e = f[v] - mu4[v >> 2][v & 3];
+          t[j] += e * e * iv4[v >> 2][v & 3];
+        }
       }
     }
-    float a = wave_sum(t);                           // |phi_j|_1 of Eq. (7), the row's weight before normalisation
-    if (mean_pooling) a = 1.f;
-    if (lane == 0) a_rows[size_t(w) * m_pad + r] = a;
-    a_sum += a;
+    float a[R];                                      // |phi_j|_1 of Eq. (7), the row's weight before normalisation
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      float f[V];
-      Vec<T>::widen(x[i], f);
-#pragma unroll
-      for (int v = 0; v < V; ++v) acc[i][v] += a * f[v];
+    for (int j = 0; j < R; ++j) {
+      const int row = r + j * NW;
+      a[j] = wave_sum(t[j]);
+      if (mean_pooling) a[j] = 1.f;
+      if (row >= r1) a[j] = 0.f;
+      if (lane == 0 && row < r1) a_rows[size_t(w) * m_pad + row] = a[j];
+      a_sum += a[j];
     }
 #pragma unroll
-    for (int i = 0; i < NI; ++i) x[i] = xn[i];
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        float f[V];
+        Vec<T>::widen(x[j][i], f);
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[i][v] += a[j] * f[v];
+      }
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+#pragma unroll
+      for (int i = 0; i < NI; ++i) x[j][i] = xn[j][i];
   }
-  // sum over the 4 wavefronts, in a fixed order: (0 + 2) + (1 + 3)
+  // sum over the wavefronts, in a fixed order: halves onto halves
   __syncthreads();                                   // mean and 1/var are no longer needed
   if (lane == 0) red[wave] = a_sum;
   auto put = [&](float* dst) {
@@ -433,16 +494,22 @@ __global__ __launch_bounds__(kRmThreads) void probe_rows_bias_weigh_kernel(
       }
     }
   };
-  if (wave >= 2) put(rw_lds + (wave - 2) * d);
-  __syncthreads();
-  if (wave < 2) add(rw_lds + wave * d);
-  __syncthreads();
-  if (wave == 1) put(rw_lds);
-  __syncthreads();
+#pragma unroll
+  for (int h = NW / 2; h > 0; h /= 2) {
+    if (wave >= h && wave < 2 * h) put(rw_lds + (wave - h) * d);
+    __syncthreads();
+    if (wave < h) add(rw_lds + wave * d);
+    if (h > 1) __syncthreads();
+  }
   if (wave == 0) {
-    add(rw_lds);
     put(pprobe + (size_t(w) * n_chunks + rc) * d);
-    if (lane == 0) asum[size_t(w) * asum_stride + rc] = (red[0] + red[2]) + (red[1] + red[3]);
+    if (lane == 0) {
+#pragma unroll
+      for (int h = NW / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int v = 0; v < h; ++v) red[v] += red[v + h];
+      asum[size_t(w) * asum_stride + rc] = red[0];
+    }
   }
 }
 
@@ -465,7 +532,15 @@ __global__ __launch_bounds__(1024) void probe_chain_finish_kernel(
   float ss = 0.f;
   for (int ch = threadIdx.x; ch < d; ch += 1024) {
     float t = 0.f;
-    for (int rc = 0; rc < n_chunks; ++rc) t += pprobe[(size_t(w) * n_chunks + rc) * d + ch];
+    constexpr int kBatch = 8;
+    for (int rc = 0; rc < n_chunks; rc += kBatch) {
+      float x[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i)               // all loads first: they overlap
+        x[i] = pprobe[(size_t(w) * n_chunks + (rc + i < n_chunks ? rc + i : rc)) * d + ch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) t += rc + i < n_chunks ? x[i] : 0.f;
+    }
     t = uniform ? stat_in[size_t(w) * 3 * d + 2 * d + ch] : t * inv;
     probe[ch] = t;
     probe_lds[ch] = t;
@@ -488,7 +563,20 @@ __global__ __launch_bounds__(1024) void probe_chain_finish_kernel(
 }
 
 constexpr int kWeighRows = 8;    // rows a thread takes per pass
-constexpr int kWeighSlabBatch = 16;
+// The slabs' partials of one row, kBatch of them requested together: one round trip for 16 slabs, two for 64 (four as
+// 16 at a time: the probe of 256 tokens with 4096 channels 14.8 us, 13.5 so).
+template <int kBatch>
+__device__ __forceinline__ float slab_sum(const float* __restrict__ apart, int n_slabs, int m_pad) {
+  float t = 0.f;
+  for (int s0 = 0; s0 < n_slabs; s0 += kBatch) {
+    float p[kBatch];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) p[i] = apart[size_t(s0 + i < n_slabs ? s0 + i : s0) * m_pad];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) t += s0 + i < n_slabs ? p[i] : 0.f;
+  }
+  return t;
+}
 
 // grid (column slabs of 8*V channels, batch); 8 column lanes x RL row lanes.
 // Every workgroup adds the slabs' partials up to a_j (slab order), turns them into the
@@ -530,15 +618,8 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_weigh_kernel(const T* __
 
   float tsum = 0.f;
   for (int j = threadIdx.x; j < m && !mean_pooling; j += kThreads) {
-    float t = 0.f;
-    for (int s0 = 0; s0 < n_slabs; s0 += kWeighSlabBatch) {
-      float p[kWeighSlabBatch];
-#pragma unroll
-      for (int i = 0; i < kWeighSlabBatch; ++i)   // all loads first: they overlap
-        p[i] = apart[size_t(s0 + i < n_slabs ? s0 + i : s0) * m_pad + j];
-#pragma unroll
-      for (int i = 0; i < kWeighSlabBatch; ++i) t += s0 + i < n_slabs ? p[i] : 0.f;
-    }
+    const float t = n_slabs <= 8 ? slab_sum<8>(apart + j, n_slabs, m_pad) : n_slabs <= 16 ? slab_sum<16>(apart + j, n_slabs, m_pad)
+                                                                              : slab_sum<32>(apart + j, n_slabs, m_pad);
     w_lds[j] = t;
     tsum += t;
   }
@@ -565,9 +646,9 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_weigh_kernel(const T* __
   // the 8 row lanes of a wave first, then the waves through LDS
 #pragma unroll
   for (int v = 0; v < V; ++v) {
-    acc[v] += __shfl_xor(acc[v], 8, 64);
-    acc[v] += __shfl_xor(acc[v], 16, 64);
-    acc[v] += __shfl_xor(acc[v], 32, 64);
+    acc[v] += lane_xor_f32<8>(acc[v]);
+    acc[v] += lane_xor_f32<16>(acc[v]);
+    acc[v] += lane_xor_f32<32>(acc[v]);
   }
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (lane < kColLanes) {
@@ -648,9 +729,13 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
   static_assert(kColLanes * 8 == kProbeSlabBytes / 2 && kColLanes * 4 == kProbeSlabBytes / 4, "slab width");
   float* scratch = ws.scratch_f32();
   const int mean_pooling = (update_stats & ACTQKV_PROBE_MEAN_POOLING) != 0;
-  if (update_stats & ACTQKV_PROBE_WINDOW_CHAIN) {
+  // A long window of few channels is a chain of one: a slab has one workgroup however long the window is (4096 tokens:
+  // 512 channels 32.6 us in slabs, 22.6 row by row; 1024 channels 33.0, 28.9; but 2048 tokens of 1024 channels 20.8, 23.5,
+  // and 4096 channels never).
+  const bool long_window = batch == 1 && (update_stats & ACTQKV_STATS_UPDATE) && m >= 2048 && m >= 4 * d;
+  if ((update_stats & ACTQKV_PROBE_WINDOW_CHAIN) || long_window) {
     // the batch entries are consecutive windows of one sequence with one set of statistics
-    if (d > 64 * 64) {
+    if (d > 64 * 64) {          // (not a long window: 4 d is more than the longest)
       // rows wider than a wavefront of the row-major kernels holds: window after window
       const int dk = sh.n_kv_heads * sh.head_dim;
       for (int w = 0; w < batch; ++w) {
@@ -668,18 +753,36 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
     float* pprobe = stat + cl.stat;
     float* asum = pprobe + cl.pprobe;
     float* a_rows = asum + cl.asum;
-    const int n_chunks = cl.n_chunks;
-    hipLaunchKernelGGL(probe_rows_moments_kernel<T>, dim3(n_chunks, batch, (d + 2 * kRmThreads * V - 1) / (2 * kRmThreads * V)),
-                       dim3(kRmThreads), 0, stream, q_win, part, m, d, n_chunks);
+    const int n_chunks = cl.n_chunks, groups = d / V;
+    // channels of a workgroup: fewer where the chunks alone would leave compute units idle
+    int cols = std::min(groups, kRmThreads);
+    while (cols > 64 && batch * n_chunks * ((groups + cols - 1) / cols) < kChipCus) cols = std::max(cols / 2, 64);
+    hipLaunchKernelGGL(probe_rows_moments_kernel<T>, dim3(n_chunks, batch, (groups + cols - 1) / cols), dim3(kRmThreads), 0,
+                       stream, q_win, part, m, d, n_chunks, cols);
     hipLaunchKernelGGL(probe_chain_stats_kernel<T>, dim3((d + 31) / 32), dim3(1024), size_t(batch) * 64 * sizeof(float),
                        stream, q_win, part, stats, stat, batch, m, d, n_chunks, eps);
-    hipLaunchKernelGGL(probe_rows_bias_weigh_kernel<T>, dim3(n_chunks, batch), dim3(kRmThreads),
-                       size_t(2) * 4096 * sizeof(float), stream, q_win, stat, stats, float(batch) * float(m), mean_pooling,
-                       pprobe, asum, a_rows, m, m_pad, d, n_chunks, cl.asum_stride);
+    // Few chunks: half as long in the second pass.  Twice as many partial probes take the place of the moments, which
+    // chain_stats has used up, and their sums that of the partial probes.
+    const bool halves = batch * n_chunks <= kChipCus / 2 && n_chunks <= 16;
+    const int rows = halves ? kRowChunk / 2 : kRowChunk, n_parts = (m + rows - 1) / rows;
+    const int asum_stride = halves ? (n_parts + 15) / 16 * 16 : cl.asum_stride;
+    if (halves) {
+      asum = pprobe;                                  // (2 chunks floats and less than 16 more of chunks * d)
+      pprobe = part;
+    }
+    auto bias_weigh = [&](auto kernel, int ni, int waves) {
+      const size_t lds = std::max(size_t(2) * 64 * ni * V, size_t(waves / 2) * d) * sizeof(float);
+      hipLaunchKernelGGL(kernel, dim3(n_parts, batch), dim3(64 * waves), lds, stream, q_win, stat, stats,
+                         float(batch) * float(m), mean_pooling, pprobe, asum, a_rows, m, m_pad, d, rows, n_parts, asum_stride);
+    };
+    if (groups <= 64) bias_weigh(probe_rows_bias_weigh_kernel<T, 1, 8>, 1, 8);
+    else if (groups <= 128) bias_weigh(probe_rows_bias_weigh_kernel<T, 2, 8>, 2, 8);
+    else if (groups <= 256) bias_weigh(probe_rows_bias_weigh_kernel<T, 4, 8>, 4, 8);
+    else if (groups <= 512) bias_weigh(probe_rows_bias_weigh_kernel<T, 8, 4>, 8, 4);
+    else bias_weigh(probe_rows_bias_weigh_kernel<T, 16, 4>, 16, 4);
     hipLaunchKernelGGL(probe_chain_finish_kernel, dim3(batch), dim3(1024), size_t(d) * sizeof(float), stream, pprobe,
-                       asum, a_rows, stat,
-                       probe, probe_kv, probe_norm, weights, m, m_pad, d, n_chunks, cl.asum_stride, sh.n_q_heads,
-                       sh.n_kv_heads, sh.head_dim);
+                       asum, a_rows, stat, probe, probe_kv, probe_norm, weights, m, m_pad, d, n_parts, asum_stride,
+                       sh.n_q_heads, sh.n_kv_heads, sh.head_dim);
     return hip_status("probe");
   }
   update_stats &= ACTQKV_STATS_UPDATE;

@@ -926,6 +926,17 @@ def test_copy_bytes():
     assert torch.equal(dst, src)
 
 
+@pytest.mark.parametrize("n", [16, 32768 - 16, 32768, 32768 + 16, 8 * 32768 + 48, (1 << 20) + 16])
+def test_copy_into_host_memory(n):
+    """The stores of a copy into pinned memory are bounded by the piece and by the copy's end."""
+    src = torch.randint(0, 256, (n,), dtype=torch.uint8, generator=torch.Generator().manual_seed(n)).to(DEV)
+    dst = torch.full((n + 8192,), 7, dtype=torch.uint8, pin_memory=True)
+    B.copy_bytes_at(dst, 4096, src, 0, n)
+    torch.cuda.synchronize()
+    assert torch.equal(dst[4096:4096 + n], src.cpu())
+    assert (dst[:4096] == 7).all() and (dst[4096 + n:] == 7).all()
+
+
 # ---------------------------------------------------------------- select alone: ties, cut-off, sizes
 def _select_case(scores: np.ndarray, nb_begin: int, k_cap: int, cutoff, topk: bool = False):
     n = len(scores)
@@ -2395,6 +2406,13 @@ def test_mean_pooling_probe_variant():
     ("bf16", 32, 8, 128, 512, (3, 5)),      # the benchmarked shape; a second call continues the first
     ("fp32", 6, 2, 64, 96, (1, 4)),         # fp32 storage, group size 3; a call of one window
     ("bf16", 8, 8, 128, 1100, (19,)),       # more than one pass of rows, more windows than a merge batch
+    ("bf16", 8, 2, 64, 130, (1, 2)),        # rows of 64 groups of 16 bytes, chunks of 32 rows with a remainder
+    ("bf16", 7, 7, 64, 70, (33,)),          # rows that leave lanes idle, more windows than merge lanes
+    ("bf16", 16, 2, 128, 200, (2,)),        # 256 groups
+    ("bf16", 28, 4, 128, 1100, (1,)),       # 448 groups, 18 chunks
+    ("fp32", 32, 8, 128, 65, (2, 3)),       # 1024 groups
+    ("bf16", 8, 2, 64, 2049, (-2,)),        # long windows of few channels, a call each without the flag
+    ("fp32", 8, 2, 64, 2048, (-1,)),
 ])
 def test_probe_of_consecutive_windows_in_one_call(dtype, hq, hkv, d, m, calls):
     """ACTQKV_PROBE_WINDOW_CHAIN: n consecutive windows of one sequence in one build_probe call
@@ -2403,6 +2421,8 @@ def test_probe_of_consecutive_windows_in_one_call(dtype, hq, hkv, d, m, calls):
     sh = LayerShape(hq, hkv, d, 128, 4, 128, 512, dtype)
     cs = B.c_shape(sh)
     dd = hq * d
+    flags = B.STATS_UPDATE | (B.PROBE_WINDOW_CHAIN if calls[0] > 0 else 0)
+    calls = calls if calls[0] > 0 else (1,) * -calls[0]
     n_total = sum(calls)
     _say(f"[case] probe chain {dtype} H{hq}/Hk{hkv}/D{d} m={m} calls={calls}")
     g = torch.Generator().manual_seed(99 + m)
@@ -2421,7 +2441,7 @@ def test_probe_of_consecutive_windows_in_one_call(dtype, hq, hkv, d, m, calls):
     wts = torch.zeros(n_total, m, device=DEV)
     t0 = 0
     for n in calls:
-        B.build_probe(cs, n, m, qd[t0:t0 + n], stats, B.STATS_UPDATE | B.PROBE_WINDOW_CHAIN, probe[t0:t0 + n],
+        B.build_probe(cs, n, m, qd[t0:t0 + n], stats, flags, probe[t0:t0 + n],
                       probe_kv[t0:t0 + n], norm[t0:t0 + n], wts[t0:t0 + n], ws)
         t0 += n
     torch.cuda.synchronize()
