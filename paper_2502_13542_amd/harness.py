@@ -5,6 +5,7 @@ arithmetic step of the path runs inside libactqkv.so.
 """
 from __future__ import annotations
 
+import contextlib
 from dataclasses import dataclass
 from typing import Dict, List, Optional, Sequence, Tuple
 
@@ -27,6 +28,31 @@ def eligible_range(shape: LayerShape, w0: int) -> Tuple[int, int]:
     """[nb_begin, nb_end): blocks wholly between the initial tokens and the local span."""
     nb_begin = shape.n_init // shape.block_size
     return nb_begin, max(nb_begin, local_start(shape, w0) // shape.block_size)
+
+
+# ---------------------------------------------------------------- streams
+def side_streams(n: int, device) -> List[torch.cuda.Stream]:
+    """n <= 4 streams for work that is to run at the same time.  A process has four hardware queues here, and streams
+    that share one run their kernels one after the other.  Streams made one after the other are dealt to the queues in
+    turn, so these have a queue each; but one of them may have the queue of the caller's current stream, which
+    therefore only waits (on_streams).  With the selection chain on the current stream and three more, a host-cache
+    pass over 32K tokens took 3.4, 4.0, 4.5 or 5.6 ms by the streams its object had got; 3.4 to 3.5 so."""
+    return [torch.cuda.Stream(device=device) for _ in range(n)]
+
+
+@contextlib.contextmanager
+def on_streams(lead: torch.cuda.Stream):
+    """The body's calls on `lead`, behind what the current stream holds; the current stream goes on behind `lead`.  Under
+    capture they stay on the current stream: a graph's branches have no stream of their own, and the runtime's
+    end-of-capture call crashes on streams that were forked from a forked stream."""
+    outer = torch.cuda.current_stream()
+    if outer == lead or torch.cuda.is_current_stream_capturing():
+        yield
+        return
+    lead.wait_stream(outer)
+    with torch.cuda.stream(lead):
+        yield
+    outer.wait_stream(lead)
 
 
 # ---------------------------------------------------------------- layouts
@@ -585,9 +611,7 @@ class HostCachePrefill:
         self.ws_probe = torch.zeros(ws, dtype=torch.uint8, device=dev)
         self.workspace = torch.zeros(max(ws, G * B.workspace_bytes(runner.cs, 1, m, self.nb_ring, runner.k_cap)),
                                      dtype=torch.uint8, device=dev)
-        # (four streams with the current one: a process has four hardware queues here, and streams that
-        # share one run their kernels one after the other)
-        self.mover, self.attender, self.writer = (torch.cuda.Stream(device=dev) for _ in range(3))
+        self.lead, self.mover, self.attender, self.writer = side_streams(4, dev)
         self.events = [[torch.cuda.Event() for _ in self.groups] for _ in range(4)]
         # per-window views, made once: slicing costs the host as much as a launch
         self.v_nctx = [self.n_ctx_w[t:t + 1] for t in range(T)]
@@ -722,7 +746,7 @@ class HostCachePrefill:
                        write_back: bool = True) -> Dict[int, Dict[str, torch.Tensor]]:
         """The same pass with its parts beside each other, handed over GROUP windows at a time (a
         hand-over between streams costs the host more than a launch), on one cache of initial
-        tokens, sequence region and slots (region_geometry).  On the current stream: the selection
+        tokens, sequence region and slots (region_geometry).  On a stream of its own: the selection
         chain, which needs the queries and the representative keys only, and the group's keys and
         values into the region.  With write_back a second stream copies the group's blocks to the
         host store, so the store may start empty.  A third brings the selected blocks into
@@ -731,7 +755,11 @@ class HostCachePrefill:
         use; blocks that still lie in the region do not cross it at all.  A fourth attends.
         Results are those of run().  What bounds it: a pass over 32K tokens (32 query, 8 KV heads,
         windows of 512, 16 blocks each) gathered 0.5 GB in 12.9 ms when every window brought its own
-        blocks; now the attention sets the pace, 84 % of 5.0 to 5.2 ms beside 128 MB of write-back."""
+        blocks; now the attention (16 launches of 151 us) and 128 MB of write-back (2.4 ms) go side by side: 3.4 ms."""
+        with on_streams(self.lead):
+            return self._run_overlapped(q, k_tok, v_tok, k_store, v_store, rep_keys, out, write_back)
+
+    def _run_overlapped(self, q, k_tok, v_tok, k_store, v_store, rep_keys, out, write_back):
         r, plan, sh, cs = self.runner, self.plan, self.runner.shape, self.runner.cs
         bs, kw, vw = sh.block_size, self.k_ring, self.v_ring
         nb_store = min(k_store.shape[0], r.nb_capacity)     # what slot_state has room for; no selection is past it
