@@ -250,24 +250,27 @@ __device__ __forceinline__ void select_body(const Scores& sc, int s, int n, int 
 // none.  In the decode attention that selects for itself the others are stuck handing 32 KB of
 // load requests each to a full memory pipeline meanwhile; as a launch of its own the step is nothing
 // but latency.  Lane l keeps the scores of blocks l, l + 64, ... in registers.  The density is two
-// passes over them.  The E best blocks come out one per round: every lane knows its best score and
-// where it is, the best of all lanes is a 32-bit maximum over the lanes (exchanges without LDS), a
-// ballot names its lane (several lanes with equal scores: the lowest block of them, the rare
-// path), and only that lane looks for its next best.  About 250 cycles a round at 1024 scores, 120
-// at 64; with 64-bit keys and a search through all registers in every lane it was 1000.
+// passes over them.  The E best blocks come out one per round: every lane knows its three best scores and
+// where they are, the best of all lanes is a 32-bit maximum by row shifts and broadcasts (an instruction per
+// step), a ballot names its lane (several lanes with equal scores: the lowest block of them, the rare
+// path), and that lane goes on with its next; only a lane that has given all three looks through its registers again,
+// for what comes behind them.  A launch over 500 blocks, 10 and 32 of them chosen: 7.7 and 14.7 us with one best per lane
+// and a search after every round, 6.3 and 10.2 so; a decode step of one sequence with 8K tokens 21.1 and 19.7.
 // Same ties, same Eq. (11), Eq. (12) as select_body; the sums run in another order.
 constexpr int kSelWavePerLane = 16;
 
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_max_u32(uint32_t v) {      // lanes without a source: v
+  return max(v, uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kCtrl, kRows, 0xF, false)));
+}
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-  auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  v = max(uint32_t(r[0]), uint32_t(r[1]));
-  r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  v = max(uint32_t(r[0]), uint32_t(r[1]));
-  v = max(v, lane_xor32<8>(v));
-  v = max(v, lane_xor32<4>(v));
-  v = max(v, lane_xor32<2>(v));
-  v = max(v, lane_xor32<1>(v));
-  return __builtin_amdgcn_readfirstlane(v);
+  v = dpp_max_u32<0x111, 0xF>(v);                                  // row_shr 1, 2, 4, 8: lane 15 of a row has its maximum
+  v = dpp_max_u32<0x112, 0xF>(v);
+  v = dpp_max_u32<0x114, 0xF>(v);
+  v = dpp_max_u32<0x118, 0xF>(v);
+  v = dpp_max_u32<0x142, 0xA>(v);                                  // row_bcast 15 into rows 1, 3, then 31 into rows 2, 3
+  v = dpp_max_u32<0x143, 0xC>(v);
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
 // Called by all 64 lanes of one wavefront; sel[0 .. k_cap) and *count (LDS or any memory the
@@ -315,25 +318,35 @@ __device__ __forceinline__ void select_wave(const float* __restrict__ sc_mem, in
   uint32_t mine_key = 0u;
   const int rounds = __builtin_amdgcn_readfirstlane(io.density_only && !entropy_topk ? 0 : entropy_topk ? min(k_cap, n) : cut.e);
   if (rounds > 0) {
-    uint32_t key[kPer], best = 0u;                               // 0: no block (any more); best: the lane's largest,
-    int at = 0;                                                  // in register `at`
+    uint32_t key[kPer];                                          // 0: no block
 #pragma unroll
     for (int i = 0; i < kPer; ++i)
       key[i] = lane + 64 * i < n ? max(uint32_t(select_key(v[i], 0) >> 32), 1u) : 0u;
-    auto find_best = [&] {
-      best = 0u;
-      at = 0;
+    // the lane's three best behind (than, at_than) in the order of descending keys and ascending registers, and the
+    // registers they are in
+    uint32_t best, next, third;
+    int at, at2, at3;
+    auto find_three = [&](uint32_t than, int at_than) {
+      best = next = third = 0u;
+      at = at2 = at3 = 0;
 #pragma unroll
       for (int c = 0; c < kPer; c += kPart)
         if (c < per) {
 #pragma unroll
           for (int i = c; i < c + kPart; ++i) {
-            at = key[i] > best ? i : at;
-            best = max(best, key[i]);
+            const uint32_t k = key[i] < than || (key[i] == than && i > at_than) ? key[i] : 0u;
+            const bool c1 = k > best, c2 = k > next, c3 = k > third;
+            at3 = c2 ? at2 : c3 ? i : at3;
+            at2 = c1 ? at : c2 ? i : at2;
+            at = c1 ? i : at;
+            third = max(third, min(next, k));
+            next = max(next, min(best, k));
+            best = max(best, k);
           }
         }
     };
-    find_best();
+    find_three(0xffffffffu, -1);
+    int left = n > lane ? (n - lane + 63) >> 6 : 0;              // the lane's blocks that have not come out
     for (int r = 0; r < rounds; ++r) {
       const uint32_t top = wave_max_u32(best);
       const unsigned long long who = __ballot(best == top);
@@ -342,19 +355,18 @@ __device__ __forceinline__ void select_wave(const float* __restrict__ sc_mem, in
         const uint32_t low = wave_max_u32(best == top ? ~uint32_t(lane + 64 * at) : 0u);
         w = int(~low) & 63;
       }
-      const int b = w + 64 * __builtin_amdgcn_readlane(at, w);
-      if (lane == r) {
-        mine = nb_begin + b;
-        mine_key = top;
-      }
-      if (lane == w) {
-#pragma unroll
-        for (int c = 0; c < kPer; c += kPart)
-          if (c < per) {
-#pragma unroll
-            for (int i = c; i < c + kPart; ++i) key[i] = i == at ? 0u : key[i];
-          }
-        find_best();
+      const int i_top = __builtin_amdgcn_readlane(at, w), b = w + 64 * i_top;
+      mine = lane == r ? nb_begin + b : mine;
+      mine_key = lane == r ? top : mine_key;
+      const bool won = lane == w;
+      best = won ? next : best;
+      at = won ? at2 : at;
+      next = won ? third : next;
+      at2 = won ? at3 : at2;
+      third = won ? 0u : third;
+      left -= won;
+      if (per > 3 && __ballot(won && best == 0u && left > 0) != 0ull) {
+        if (won) find_three(top, i_top);
       }
     }
   }

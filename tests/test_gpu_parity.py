@@ -926,6 +926,34 @@ def test_copy_bytes():
     assert torch.equal(dst, src)
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 129, 257, 1000, 1024])
+def test_selection_by_one_wavefront_where_few_lanes_hold_the_best(n):
+    """The wavefront keeps three candidates per lane (block i is lane i % 64's): the best blocks all in one lane, in two,
+    all scores equal, the lowest scores there are, and ties between lanes and inside one, against a stable sort."""
+    k = 32
+    g = torch.Generator().manual_seed(n)
+    rows = torch.randn(6, 1024, generator=g)
+    rows[0, ::64] += 10                                          # one lane's
+    rows[1, 5::64] = 9.0                                         # one lane's, all equal
+    rows[1, 6::64] += 8
+    rows[2] = 0.25
+    rows[3] = float("-inf")
+    rows[4] = (rows[4] * 2).round() / 2                          # many ties
+    rows[5, ::2] = -0.0                                          # the two zeros tie
+    rows[5, 1::2] = 0.0
+    sc = rows.to(DEV)
+    idx = torch.full((6, k), -2, dtype=torch.int32, device=DEV)
+    n_sel = torch.zeros(6, dtype=torch.int32, device=DEV)
+    nb_end = torch.full((6,), n, dtype=torch.int32, device=DEV)
+    B.select(6, sc, 1024, 1024, 0, nb_end, k, None, None, idx, n_sel, None, None)
+    torch.cuda.synchronize()
+    e = min(k, n)
+    assert n_sel.tolist() == [e] * 6
+    for s in range(6):
+        want = sorted(range(n), key=lambda b: (-float(rows[s, b]), b))[:e]
+        assert idx[s].tolist() == want + [-1] * (k - e), f"row {s}"
+
+
 @pytest.mark.parametrize("n", [16, 32768 - 16, 32768, 32768 + 16, 8 * 32768 + 48, (1 << 20) + 16])
 def test_copy_into_host_memory(n):
     """The stores of a copy into pinned memory are bounded by the piece and by the copy's end."""
