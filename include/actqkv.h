@@ -362,6 +362,23 @@ int actqkv_append_kv_probe(const actqkv_shape* shape, int batch, const void* q_t
                            int nb_capacity, float* probe, float* probe_kv, float* probe_norm,
                            void* stream);
 
+/* A window from its queries to its output in ONE call: actqkv_build_probe, actqkv_score_blocks, actqkv_select and
+ * actqkv_retrieval_attention with the arguments of the four calls, on one workspace (it must satisfy the largest of
+ * them).  Same results (for one window of one sequence the probe's norm, and with it the scores, up to the order of an
+ * fp32 sum: it is then taken in the scoring launch, a launch less).
+ *   nb_scored    nb_capacity of the scoring and the selection (an upper bound of nb_end); nb_capacity is that of the
+ *                caches.
+ *   The other arguments as in the four calls; rep_seq_stride and cache_seq_stride are their seq_stride.
+ * Errors: as in the four calls; nothing is launched if one of them would be refused. */
+int actqkv_window_step(const actqkv_shape* shape, int batch, int m, const void* q_win, float* stats,
+                       int update_stats, float* probe, float* probe_kv, float* probe_norm, float* weights,
+                       const void* rep_keys, int64_t rep_seq_stride, int nb_scored, int nb_begin,
+                       const int32_t* nb_end, float* scores, int64_t score_stride, int k_cap, int flags,
+                       float* budget_remaining, const float* theta_rest_sum, int32_t* idx, int32_t* n_sel,
+                       float* theta, float* budget, const void* k_cache, const void* v_cache,
+                       int64_t cache_seq_stride, int nb_capacity, const int32_t* n_ctx, void* out, float* lse,
+                       void* workspace, size_t ws_bytes, void* stream);
+
 /* Everything of a decode step that comes before the attention, in ONE call of two launches
  * instead of four: the cache update (Sec. 3.1, Eq. (4); actqkv_append_kv with m = 1), the probe
  * of the one-token window (the query itself, Sec. 4.2; actqkv_build_probe with m = 1 and no

@@ -79,6 +79,8 @@ SIGNATURES = {
                                  _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
     "actqkv_retrieval_attention_teams": (_i, [_shp, _i, _i, _vp, _vp, _vp, _i64, _i, _vp, _vp, _vp, _i,
                                               _vp, _vp, _vp, _sz, _i, _i, _vp, _vp]),
+    "actqkv_window_step": (_i, [_shp, _i, _i, _vp, _vp, _i, _vp, _vp, _vp, _vp, _vp, _i64, _i, _i, _vp, _vp, _i64, _i, _i, _vp,
+                                _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i64, _i, _vp, _vp, _vp, _vp, _sz, _vp]),
     "actqkv_copy_bytes": (_i, [_vp, _vp, _sz, _vp]),
     "actqkv_gather_blocks": (_i, [_shp, _i, _vp, _vp, _i64, _i, _vp, _vp, _i, _vp, _vp, _i64, _i, _i, _vp, _vp]),
     "actqkv_gather_blocks_cached": (_i, [_shp, _i, _vp, _vp, _i, _vp, _vp, _i, _vp, _vp, _i, _i, _i, _i, _i, _i, _i,
@@ -169,6 +171,17 @@ def append_kv_probe(shape: CShape, batch: int, q_tok, k_new, v_new, pos0, k_cach
                     probe_norm, stream=None) -> None:
     _calls().append_kv_probe(shape, batch, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride, rep_keys,
                              rep_seq_stride, nb_capacity, probe, probe_kv, probe_norm, stream)
+
+
+def window_step(shape: CShape, batch: int, m: int, q_win, stats, update_stats: int, probe, probe_kv, probe_norm, weights,
+                rep_keys, rep_seq_stride: int, nb_scored: int, nb_begin: int, nb_end, scores, score_stride: int, k_cap: int,
+                budget_remaining, theta_rest_sum, idx, n_sel, theta, budget, k_cache, v_cache, cache_seq_stride: int,
+                nb_capacity: int, n_ctx, out, lse, workspace, stream=None, flags: int = 0) -> None:
+    """Probe, scores, selection and attention of a window in one call; see the header."""
+    _calls().window_step(shape, batch, m, q_win, stats, int(update_stats), probe, probe_kv, probe_norm, weights, rep_keys,
+                         rep_seq_stride, nb_scored, nb_begin, nb_end, scores, score_stride, k_cap, int(flags),
+                         budget_remaining, theta_rest_sum, idx, n_sel, theta, budget, k_cache, v_cache, cache_seq_stride,
+                         nb_capacity, n_ctx, out, lse, workspace, stream)
 
 
 def decode_retrieve(shape: CShape, batch: int, q_tok, k_new, v_new, pos0, k_cache, v_cache,

@@ -296,9 +296,9 @@ size_t actqkv_workspace_bytes(const actqkv_shape* shape, int batch, int m, int n
   return workspace_bytes_upto(*shape, batch, m, nb_capacity, k_cap);
 }
 
-int actqkv_build_probe(const actqkv_shape* shape, int batch, int m, const void* q_win, float* stats,
-                       int update_stats, float* probe, float* probe_kv, float* probe_norm,
-                       float* weights, void* workspace, size_t ws_bytes, void* stream) {
+static int build_probe_check(const actqkv_shape* shape, int batch, int m, const void* q_win, const float* stats,
+                             int update_stats, const float* probe, const float* probe_kv, const float* probe_norm,
+                             const float* weights, const void* workspace, size_t ws_bytes) {
   ACTQKV_TRY(check_shape(shape));
   ACTQKV_TRY(check_batch(batch));
   if (m < 1) return set_error(ACTQKV_EINVAL, "m %d < 1", m);
@@ -318,15 +318,12 @@ int actqkv_build_probe(const actqkv_shape* shape, int batch, int m, const void* 
   size_t need = kCounterBytes + probe_call_floats(*shape, batch, m) * sizeof(float);
   if (ws_bytes < need)
     return set_error(ACTQKV_EWORKSPACE, "workspace has %zu bytes, build_probe needs %zu", ws_bytes, need);
-  Workspace ws{workspace, ws_bytes};
-  return launch_probe(*shape, batch, m, q_win, stats, update_stats, probe, probe_kv, probe_norm,
-                      weights, ws, static_cast<hipStream_t>(stream));
+  return ACTQKV_OK;
 }
 
-int actqkv_score_blocks(const actqkv_shape* shape, int batch, const float* probe_kv,
-                        const float* probe_norm, const void* rep_keys, int64_t seq_stride,
-                        int nb_capacity, int nb_begin, const int32_t* nb_end, float* scores,
-                        int64_t score_stride, void* stream) {
+static int score_blocks_check(const actqkv_shape* shape, int batch, const float* probe_kv, const float* probe_norm,
+                              const void* rep_keys, int64_t seq_stride, int nb_capacity, int nb_begin, const int32_t* nb_end,
+                              const float* scores, int64_t score_stride) {
   ACTQKV_TRY(check_shape(shape));
   ACTQKV_TRY(check_batch(batch));
   ACTQKV_TRY(check_blocks(nb_capacity, nb_begin, 1, false));
@@ -343,14 +340,13 @@ int actqkv_score_blocks(const actqkv_shape* shape, int batch, const float* probe
     return set_error(ACTQKV_EINVAL, "seq_stride %lld < one sequence's representative keys %lld",
                      (long long)seq_stride, (long long)per_seq);
   if (seq_stride % 8 != 0) return set_error(ACTQKV_EALIGN, "seq_stride must be a multiple of 8 elements");
-  return launch_score(*shape, batch, probe_kv, probe_norm, rep_keys, seq_stride, nb_capacity, nb_begin,
-                      nb_end, scores, score_stride, static_cast<hipStream_t>(stream));
+  return ACTQKV_OK;
 }
 
-int actqkv_select(int batch, const float* scores, int64_t score_stride, int nb_capacity, int nb_begin,
-                  const int32_t* nb_end, int k_cap, int flags, float* budget_remaining,
-                  const float* theta_rest_sum, int32_t* idx, int32_t* n_sel, float* theta,
-                  float* budget, void* stream) {
+static int select_check(int batch, const float* scores, int64_t score_stride, int nb_capacity, int nb_begin,
+                        const int32_t* nb_end, int k_cap, int flags, const float* budget_remaining,
+                        const float* theta_rest_sum, const int32_t* idx, const int32_t* n_sel, const float* theta,
+                        const float* budget) {
   if (flags & ~(ACTQKV_SELECT_ENTROPY_TOPK | ACTQKV_SELECT_DENSITY_ONLY | ACTQKV_SELECT_GIVEN_COUNT))
     return set_error(ACTQKV_EINVAL, "select: unknown flag bits: %d", flags);
   if ((flags & ACTQKV_SELECT_DENSITY_ONLY) && (flags & ACTQKV_SELECT_GIVEN_COUNT))
@@ -374,6 +370,35 @@ int actqkv_select(int batch, const float* scores, int64_t score_stride, int nb_c
   if (score_stride < nb_capacity)
     return set_error(ACTQKV_EINVAL, "score_stride %lld < nb_capacity %d", (long long)score_stride,
                      nb_capacity);
+  return ACTQKV_OK;
+}
+
+int actqkv_build_probe(const actqkv_shape* shape, int batch, int m, const void* q_win, float* stats,
+                       int update_stats, float* probe, float* probe_kv, float* probe_norm,
+                       float* weights, void* workspace, size_t ws_bytes, void* stream) {
+  ACTQKV_TRY(build_probe_check(shape, batch, m, q_win, stats, update_stats, probe, probe_kv, probe_norm, weights, workspace,
+                               ws_bytes));
+  Workspace ws{workspace, ws_bytes};
+  return launch_probe(*shape, batch, m, q_win, stats, update_stats, probe, probe_kv, probe_norm,
+                      weights, ws, static_cast<hipStream_t>(stream));
+}
+
+int actqkv_score_blocks(const actqkv_shape* shape, int batch, const float* probe_kv,
+                        const float* probe_norm, const void* rep_keys, int64_t seq_stride,
+                        int nb_capacity, int nb_begin, const int32_t* nb_end, float* scores,
+                        int64_t score_stride, void* stream) {
+  ACTQKV_TRY(score_blocks_check(shape, batch, probe_kv, probe_norm, rep_keys, seq_stride, nb_capacity, nb_begin, nb_end, scores,
+                                score_stride));
+  return launch_score(*shape, batch, probe_kv, probe_norm, rep_keys, seq_stride, nb_capacity, nb_begin,
+                      nb_end, scores, score_stride, static_cast<hipStream_t>(stream));
+}
+
+int actqkv_select(int batch, const float* scores, int64_t score_stride, int nb_capacity, int nb_begin,
+                  const int32_t* nb_end, int k_cap, int flags, float* budget_remaining,
+                  const float* theta_rest_sum, int32_t* idx, int32_t* n_sel, float* theta,
+                  float* budget, void* stream) {
+  ACTQKV_TRY(select_check(batch, scores, score_stride, nb_capacity, nb_begin, nb_end, k_cap, flags, budget_remaining,
+                          theta_rest_sum, idx, n_sel, theta, budget));
   return launch_select(batch, scores, score_stride, nb_capacity, nb_begin, nb_end, k_cap, flags,
                        budget_remaining, theta_rest_sum, idx, n_sel, theta, budget,
                        static_cast<hipStream_t>(stream));
@@ -396,6 +421,38 @@ static int attention_checked(const actqkv_shape* shape, int batch, int m, const 
   return launch_attention(*shape, batch, m, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx, idx,
                           n_sel, k_cap, out, lse, ws, sel_per_head, static_cast<hipStream_t>(stream), first_cus,
                           late_cus, static_cast<hipStream_t>(stream_late));
+}
+
+int actqkv_window_step(const actqkv_shape* shape, int batch, int m, const void* q_win, float* stats, int update_stats,
+                       float* probe, float* probe_kv, float* probe_norm, float* weights, const void* rep_keys,
+                       int64_t rep_seq_stride, int nb_scored, int nb_begin, const int32_t* nb_end, float* scores,
+                       int64_t score_stride, int k_cap, int flags, float* budget_remaining, const float* theta_rest_sum,
+                       int32_t* idx, int32_t* n_sel, float* theta, float* budget, const void* k_cache, const void* v_cache,
+                       int64_t cache_seq_stride, int nb_capacity, const int32_t* n_ctx, void* out, float* lse,
+                       void* workspace, size_t ws_bytes, void* stream) {
+  // everything is checked before anything is launched
+  ACTQKV_TRY(build_probe_check(shape, batch, m, q_win, stats, update_stats, probe, probe_kv, probe_norm, weights, workspace,
+                               ws_bytes));
+  ACTQKV_TRY(score_blocks_check(shape, batch, probe_kv, probe_norm, rep_keys, rep_seq_stride, nb_scored, nb_begin, nb_end,
+                                scores, score_stride));
+  ACTQKV_TRY(select_check(batch, scores, score_stride, nb_scored, nb_begin, nb_end, k_cap, flags, budget_remaining,
+                          theta_rest_sum, idx, n_sel, theta, budget));
+  size_t need = 0;
+  ACTQKV_TRY(attention_validate(shape, batch, m, q_win, k_cache, v_cache, cache_seq_stride, nb_capacity, n_ctx, idx, n_sel,
+                                k_cap, out, lse, kChipCus, &need));
+  if (ws_bytes < need)
+    return set_error(ACTQKV_EWORKSPACE, "workspace has %zu bytes, window_step needs %zu", ws_bytes, need);
+  Workspace ws{workspace, ws_bytes};
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const bool apart = nb_scored > nb_begin && probe_finish_apart(*shape, batch, m, update_stats);
+  ACTQKV_TRY(launch_probe(*shape, batch, m, q_win, stats, update_stats, probe, probe_kv, probe_norm, weights, ws, st, !apart));
+  ACTQKV_TRY(apart ? launch_score_probe(*shape, probe, probe_kv, probe_norm, rep_keys, nb_scored, nb_begin, nb_end, scores, st)
+                   : launch_score(*shape, batch, probe_kv, probe_norm, rep_keys, rep_seq_stride, nb_scored, nb_begin, nb_end,
+                                  scores, score_stride, st));
+  ACTQKV_TRY(launch_select(batch, scores, score_stride, nb_scored, nb_begin, nb_end, k_cap, flags, budget_remaining,
+                           theta_rest_sum, idx, n_sel, theta, budget, st));
+  return launch_attention(*shape, batch, m, q_win, k_cache, v_cache, cache_seq_stride, nb_capacity, n_ctx, idx, n_sel, k_cap,
+                          out, lse, ws, 0, st);
 }
 
 int actqkv_retrieval_attention(const actqkv_shape* shape, int batch, int m, const void* q,

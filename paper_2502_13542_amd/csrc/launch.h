@@ -108,10 +108,16 @@ struct Workspace {
 // ---- launchers (one per entry point; arguments already validated) ----------
 int launch_probe(const actqkv_shape& sh, int batch, int m, const void* q_win, float* stats,
                  int update_stats, float* probe, float* probe_kv, float* probe_norm, float* weights,
-                 const Workspace& ws, hipStream_t stream);
+                 const Workspace& ws, hipStream_t stream, bool finish = true);   // finish: norm and per-KV-head sum
+// whether launch_probe can leave the norm and the per-KV-head sum to launch_score_probe
+bool probe_finish_apart(const actqkv_shape& sh, int batch, int m, int update_stats);
 int launch_score(const actqkv_shape& sh, int batch, const float* probe_kv, const float* probe_norm,
                  const void* rep_keys, int64_t seq_stride, int nb_capacity, int nb_begin,
                  const int32_t* nb_end, float* scores, int64_t score_stride, hipStream_t stream);
+// one sequence: norm and per-KV-head sum of the probe, and the scores, in one launch (at least one block)
+int launch_score_probe(const actqkv_shape& sh, const float* probe, float* probe_kv, float* probe_norm,
+                       const void* rep_keys, int nb_capacity, int nb_begin, const int32_t* nb_end, float* scores,
+                       hipStream_t stream);
 int launch_select(int batch, const float* scores, int64_t score_stride, int nb_capacity, int nb_begin,
                   const int32_t* nb_end, int k_cap, int flags, float* budget_remaining,
                   const float* theta_rest_sum, int32_t* idx, int32_t* n_sel, float* theta,

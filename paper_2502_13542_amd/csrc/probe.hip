@@ -715,10 +715,17 @@ __global__ __launch_bounds__(1024) void probe_identity_kernel(
                          probe_lds, red);
 }
 
+// A long window of few channels is a chain of one: a slab has one workgroup however long the window is (4096 tokens:
+// 512 channels 32.6 us in slabs, 22.6 row by row; 1024 channels 33.0, 28.9; but 2048 tokens of 1024 channels 20.8, 23.5,
+// and 4096 channels never).
+static bool long_window(const actqkv_shape& sh, int batch, int m, int update_stats) {
+  return batch == 1 && (update_stats & ACTQKV_STATS_UPDATE) && m >= 2048 && m >= 4 * sh.n_q_heads * sh.head_dim;
+}
+
 template <typename T>
 static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_win, float* stats,
                           int update_stats, float* probe, float* probe_kv, float* probe_norm,
-                          float* weights, const Workspace& ws, hipStream_t stream) {
+                          float* weights, const Workspace& ws, hipStream_t stream, bool finish) {
   constexpr int V = Vec<T>::N;
   const int d = sh.n_q_heads * sh.head_dim;
   const float eps = sh.var_eps > 0.f ? sh.var_eps : 1e-12f;
@@ -729,11 +736,7 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
   static_assert(kColLanes * 8 == kProbeSlabBytes / 2 && kColLanes * 4 == kProbeSlabBytes / 4, "slab width");
   float* scratch = ws.scratch_f32();
   const int mean_pooling = (update_stats & ACTQKV_PROBE_MEAN_POOLING) != 0;
-  // A long window of few channels is a chain of one: a slab has one workgroup however long the window is (4096 tokens:
-  // 512 channels 32.6 us in slabs, 22.6 row by row; 1024 channels 33.0, 28.9; but 2048 tokens of 1024 channels 20.8, 23.5,
-  // and 4096 channels never).
-  const bool long_window = batch == 1 && (update_stats & ACTQKV_STATS_UPDATE) && m >= 2048 && m >= 4 * d;
-  if ((update_stats & ACTQKV_PROBE_WINDOW_CHAIN) || long_window) {
+  if ((update_stats & ACTQKV_PROBE_WINDOW_CHAIN) || long_window(sh, batch, m, update_stats)) {
     // the batch entries are consecutive windows of one sequence with one set of statistics
     if (d > 64 * 64) {          // (not a long window: 4 d is more than the longest)
       // rows wider than a wavefront of the row-major kernels holds: window after window
@@ -742,7 +745,7 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
         const int rc = launch_probe_t<T>(sh, 1, m, q_win + size_t(w) * m * d, stats,
                                          update_stats & ~ACTQKV_PROBE_WINDOW_CHAIN, probe + size_t(w) * d,
                                          probe_kv + size_t(w) * dk, probe_norm + w,
-                                         weights != nullptr ? weights + size_t(w) * m : nullptr, ws, stream);
+                                         weights != nullptr ? weights + size_t(w) * m : nullptr, ws, stream, true);
         if (rc != ACTQKV_OK) return rc;
       }
       return ACTQKV_OK;
@@ -809,20 +812,25 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
   };
   if (m <= 64 * kWeighRows) weigh(probe_weigh_kernel<T, 64>, 64);
   else weigh(probe_weigh_kernel<T, 128>, 128);
-  hipLaunchKernelGGL(probe_finish_kernel, dim3(batch), dim3(kFinishThreads), 0, stream, probe, probe_kv,
-                     probe_norm, sh.n_q_heads, sh.n_kv_heads, sh.head_dim);
+  if (finish)
+    hipLaunchKernelGGL(probe_finish_kernel, dim3(batch), dim3(kFinishThreads), 0, stream, probe, probe_kv,
+                       probe_norm, sh.n_q_heads, sh.n_kv_heads, sh.head_dim);
   (void)V;
   return hip_status("probe");
 }
 
+bool probe_finish_apart(const actqkv_shape& sh, int batch, int m, int update_stats) {
+  return batch == 1 && m > 1 && !(update_stats & ACTQKV_PROBE_WINDOW_CHAIN) && !long_window(sh, batch, m, update_stats);
+}
+
 int launch_probe(const actqkv_shape& sh, int batch, int m, const void* q_win, float* stats,
                  int update_stats, float* probe, float* probe_kv, float* probe_norm, float* weights,
-                 const Workspace& ws, hipStream_t stream) {
+                 const Workspace& ws, hipStream_t stream, bool finish) {
   if (sh.dtype == ACTQKV_F32)
     return launch_probe_t<float>(sh, batch, m, static_cast<const float*>(q_win), stats, update_stats,
-                                 probe, probe_kv, probe_norm, weights, ws, stream);
+                                 probe, probe_kv, probe_norm, weights, ws, stream, finish);
   return launch_probe_t<uint16_t>(sh, batch, m, static_cast<const uint16_t*>(q_win), stats,
-                                  update_stats, probe, probe_kv, probe_norm, weights, ws, stream);
+                                  update_stats, probe, probe_kv, probe_norm, weights, ws, stream, finish);
 }
 
 }  // namespace actqkv

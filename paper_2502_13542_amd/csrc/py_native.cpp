@@ -227,7 +227,8 @@ template <typename... P> struct Entry<int(P...)> {
   X(gather_blocks_cached, "hhssq")                               \
   X(score_blocks, "sq")                                          \
   X(score_blocks_per_head, "sq")                                 \
-  X(select, "q")
+  X(select, "q")                                                 \
+  X(window_step, "ssssswq")
 
 #define ACTQKV_DEFINE(name, kinds)                                                          \
   Entry<decltype(actqkv_##name)> entry_##name;                                              \

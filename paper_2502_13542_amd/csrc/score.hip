@@ -41,6 +41,61 @@ __global__ __launch_bounds__(1024) void score_blocks_kernel(
   if (lane == 0) scores[size_t(s) * score_stride + b] = total;
 }
 
+// The same for one sequence whose probe is there, but not yet its norm and its sum over the G heads of a KV head: every
+// workgroup forms them for itself, while its first keys are on their way (the probe's loads go out first: outstanding
+// loads are counted in order), and the first one stores them.  The launch of one workgroup that did this took 1.9 us of
+// a window's chain with 512 channels and 4.0 with 4096; here it is 4 to 16 KB more per workgroup from the L2.
+template <typename T>
+__global__ __launch_bounds__(1024) void score_probe_kernel(const float* __restrict__ probe, float* __restrict__ probe_kv,
+                                                           float* __restrict__ probe_norm, const T* __restrict__ rep_keys,
+                                                           int nb_capacity, int nb_begin, const int32_t* __restrict__ nb_end,
+                                                           float* __restrict__ scores, int n_rep, int key_len, int group,
+                                                           int head_dim, float inv_sqrt_g) {
+  extern __shared__ __attribute__((aligned(16))) float probe_lds[];  // [key_len]
+  __shared__ float red[32];
+  constexpr int kHeads = 8;                                          // the largest group
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, step = int(blockDim.x) * 4;
+  auto load = [&](int e, f32x4 (&x)[kHeads]) {                       // channels e .. e + 3 of every head of their KV head
+    const int hk = e / head_dim, dd = e - hk * head_dim;
+#pragma unroll
+    for (int g = 0; g < kHeads; ++g) x[g] = *reinterpret_cast<const f32x4*>(probe + (hk * group + min(g, group - 1)) * head_dim + dd);
+  };
+  float ss = 0.f;
+  auto add = [&](int e, const f32x4 (&x)[kHeads]) {
+    f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < kHeads; ++g)
+      if (g < group) {
+        t += x[g];
+        ss += (x[g].x * x[g].x + x[g].y * x[g].y) + (x[g].z * x[g].z + x[g].w * x[g].w);
+      }
+    *reinterpret_cast<f32x4*>(probe_lds + e) = t;
+  };
+  const int e0 = int(threadIdx.x) * 4;
+  f32x4 x[kHeads];
+  load(min(e0, key_len - 4), x);
+  const int end = min(nb_end[0], nb_capacity);
+  __builtin_amdgcn_sched_barrier(0);
+  const int b = nb_begin + blockIdx.x * int(blockDim.x >> 6) + wave;
+  BlockScorer<T> scorer;
+  scorer.start(rep_keys + size_t(min(b, nb_capacity - 1)) * n_rep * key_len, n_rep, key_len, lane);
+  __builtin_amdgcn_sched_barrier(0);
+  if (e0 < key_len) add(e0, x);
+  for (int e = e0 + step; e < key_len; e += step) {
+    load(e, x);
+    add(e, x);
+  }
+  const float pn = sqrtf(block_sum(ss, red));                        // (its barriers also publish probe_lds)
+  if (blockIdx.x == 0) {
+    for (int e = e0; e < key_len; e += step)
+      *reinterpret_cast<f32x4*>(probe_kv + e) = *reinterpret_cast<const f32x4*>(probe_lds + e);
+    if (threadIdx.x == 0) *probe_norm = pn;
+  }
+  if (b >= end) return;
+  const float total = scorer.finish(probe_lds, pn, inv_sqrt_g);
+  if (lane == 0) scores[b] = total;
+}
+
 // The same score for every KV head on its own (the alternative to the head-merged reading):
 // scores[s][hk][b] = mean over the r keys of cos(probe of the G query heads of group hk, key of
 // head hk repeated to those heads) = mean_j <probe_kv[hk], k_j[hk]> / (|probe_hk| sqrt(G) |k_j[hk]|).
@@ -278,6 +333,33 @@ int launch_score_per_head(const actqkv_shape& sh, int batch, const float* probe,
   return hip_status("score_blocks_per_head");
 }
 
+// One wavefront per block.  A single long sequence (prefill) gets at most 64 workgroups,
+// so that the kernel fits beside a prefill attention that leaves 64 compute units free.
+static int score_waves(int batch, int n) {
+  int waves = 4;
+  if (batch == 1) {
+    while (waves < 16 && (n + waves - 1) / waves > 64) waves *= 2;
+  }
+  return waves;
+}
+
+int launch_score_probe(const actqkv_shape& sh, const float* probe, float* probe_kv, float* probe_norm,
+                       const void* rep_keys, int nb_capacity, int nb_begin, const int32_t* nb_end, float* scores,
+                       hipStream_t stream) {
+  const int n = nb_capacity - nb_begin, key_len = sh.n_kv_heads * sh.head_dim, group = sh.n_q_heads / sh.n_kv_heads;
+  const int waves = score_waves(1, n);
+  auto launch = [&](auto kernel, auto* keys) {
+    hipLaunchKernelGGL(kernel, dim3((n + waves - 1) / waves), dim3(64 * waves), size_t(key_len) * sizeof(float), stream, probe,
+                       probe_kv, probe_norm, keys, nb_capacity, nb_begin, nb_end, scores, sh.n_rep, key_len, group, sh.head_dim,
+                       1.f / sqrtf(float(group)));
+  };
+  if (sh.dtype == ACTQKV_F32)
+    launch(score_probe_kernel<float>, static_cast<const float*>(rep_keys));
+  else
+    launch(score_probe_kernel<uint16_t>, static_cast<const uint16_t*>(rep_keys));
+  return hip_status("score_blocks");
+}
+
 int launch_score(const actqkv_shape& sh, int batch, const float* probe_kv, const float* probe_norm,
                  const void* rep_keys, int64_t seq_stride, int nb_capacity, int nb_begin,
                  const int32_t* nb_end, float* scores, int64_t score_stride, hipStream_t stream) {
@@ -297,12 +379,7 @@ int launch_score(const actqkv_shape& sh, int batch, const float* probe_kv, const
                        batch, sh.n_rep, key_len, inv_sqrt_g);
     return hip_status("score_blocks");
   }
-  // One wavefront per block.  A single long sequence (prefill) gets at most 64 workgroups,
-  // so that the kernel fits beside a prefill attention that leaves 64 compute units free.
-  int waves = 4;
-  if (batch == 1) {
-    while (waves < 16 && (n + waves - 1) / waves > 64) waves *= 2;
-  }
+  const int waves = score_waves(batch, n);
   dim3 grid((n + waves - 1) / waves, batch), block(64 * waves);
   const size_t lds = size_t(key_len) * sizeof(float);
   if (sh.dtype == ACTQKV_F32)

@@ -116,7 +116,7 @@ class LayerRunner:
              budget_remaining: Optional[torch.Tensor] = None,
              theta_rest_sum: Optional[torch.Tensor] = None, update_stats: bool = True,
              m: Optional[int] = None, lse=None, stream=None) -> None:
-        """probe -> scores -> selection -> attention for one window (or decode step).
+        """probe -> scores -> selection -> attention for one window (or decode step), in one call.
         nb_end_max: host-side upper bound of nb_end, sizes the scoring launch.
         budget_remaining / theta_rest_sum: [batch] fp32 cut-off state, or None."""
         sh, cs, bt = self.shape, self.cs, self.batch
@@ -124,15 +124,11 @@ class LayerRunner:
         nb_begin = sh.n_init // sh.block_size
         cache_stride = k_cache.stride(0) if k_cache.dim() == 5 else 0
         rep_stride = rep_keys.stride(0) if rep_keys.dim() == 5 else 0
-        B.build_probe(cs, bt, m, q_win, self.stats, update_stats, self.probe, self.probe_kv,
-                      self.probe_norm, self.weights, self.workspace, stream)
         nb_cap = min(max(nb_end_max, nb_begin), self.nb_capacity)
-        B.score_blocks(cs, bt, self.probe_kv, self.probe_norm, rep_keys, rep_stride, nb_cap, nb_begin,
-                       nb_end, self.scores, self.score_stride, stream)
-        B.select(bt, self.scores, self.score_stride, nb_cap, nb_begin, nb_end, self.k_cap, budget_remaining,
-                 theta_rest_sum, self.idx, self.n_sel, self.theta, self.budget, stream)
-        B.retrieval_attention(cs, bt, m, q_win, k_cache, v_cache, cache_stride, self.nb_capacity, n_ctx,
-                              self.idx, self.n_sel, self.k_cap, out, lse, self.workspace, stream)
+        B.window_step(cs, bt, m, q_win, self.stats, update_stats, self.probe, self.probe_kv, self.probe_norm, self.weights,
+                      rep_keys, rep_stride, nb_cap, nb_begin, nb_end, self.scores, self.score_stride, self.k_cap,
+                      budget_remaining, theta_rest_sum, self.idx, self.n_sel, self.theta, self.budget, k_cache, v_cache,
+                      cache_stride, self.nb_capacity, n_ctx, out, lse, self.workspace, stream)
 
     def decode_step(self, q_tok: torch.Tensor, k_cache, v_cache, rep_keys, n_ctx: torch.Tensor,
                     nb_end: torch.Tensor, nb_end_max: int, out: torch.Tensor,

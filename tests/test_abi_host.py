@@ -96,6 +96,24 @@ def test_build_probe_rejects(lib):
     assert _probe(lib, cs, upd=8) == -1 and b"unknown bits" in lib.actqkv_last_error()
 
 
+def test_window_step_rejects(lib):
+    """What one of the four calls refuses, before anything is launched."""
+    cs = B.c_shape(LLAMA)
+    base = dict(shape=ctypes.byref(cs), batch=1, m=512, q=A16, stats=A16, upd=1, probe=A16, pkv=A16, pn=A16, w=None, rep=A16,
+                rs=0, nbs=400, nbb=1, nbe=A16, sc=A16, ss=512, k=32, fl=0, bud=None, rest=None, idx=A16, ns=A16, th=None, b=None,
+                kc=A16, vc=A16, cst=0, nb=512, n_ctx=A16, out=A16, lse=None, ws=A16, wsb=1 << 30, stream=None)
+    call = lambda **kw: lib.actqkv_window_step(*{**base, **kw}.values())  # noqa: E731
+    assert call(shape=None) == -1
+    assert call(q=None) == -1 and b"q_win" in lib.actqkv_last_error()
+    assert call(rep=A16 + 4) == -3 and b"rep_keys" in lib.actqkv_last_error()
+    assert call(ss=100) == -1 and b"score_stride" in lib.actqkv_last_error()
+    assert call(k=65) == -2 and call(idx=None) == -1
+    assert call(bud=A16) == -1 and b"together" in lib.actqkv_last_error()
+    assert call(kc=None) == -1 and b"k_cache" in lib.actqkv_last_error()
+    assert call(nb=3) == -1 and b"cannot hold" in lib.actqkv_last_error()
+    assert call(wsb=100) == -4
+
+
 @pytest.mark.parametrize("field,value,code", [("head_dim", 96, -2), ("n_kv_heads", 5, -2),
                                               ("block_size", 64, -2), ("n_rep", 17, -2),
                                               ("n_init", 100, -2), ("dtype", 7, -1),

@@ -926,6 +926,58 @@ def test_copy_bytes():
     assert torch.equal(dst, src)
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,d,m,batch,n_elig", [
+    ("bf16", 32, 8, 128, 512, 1, 9),        # norm and per-KV-head sum in the scoring launch: 16-byte groups of 1024 channels
+    ("bf16", 28, 4, 128, 33, 1, 70),        # seven heads, more blocks than one workgroup scores
+    ("fp32", 8, 2, 64, 2, 1, 1),            # fewer channels than a workgroup's threads take
+    ("fp32", 32, 32, 128, 5, 1, 3),         # more than one round of channels, one head
+    ("bf16", 8, 2, 64, 2049, 1, 3),         # a window whose probe comes from the row-major kernels
+    ("bf16", 8, 2, 128, 64, 1, 0),          # no block to score
+    ("bf16", 8, 2, 128, 64, 3, 5),          # three sequences
+    ("bf16", 8, 2, 128, 1, 2, 5),           # a window of one token
+])
+def test_window_step_equals_the_four_calls(dtype, hq, hkv, d, m, batch, n_elig):
+    """The results of build_probe, score_blocks, select and retrieval_attention, bit for bit but for the norm and the scores:
+    an fp32 sum of at most 4096 squares and one of at most 4096 products in another order (relative 4096 * 2^-24 at most)."""
+    sh = LayerShape(hq, hkv, d, 128, 4, 128, 256, dtype)
+    cs, dd, k_cap = B.c_shape(sh), hq * d, 4
+    n0 = 128 + 128 * n_elig + 256
+    nb = (n0 + m + 127) // 128
+    g = torch.Generator().manual_seed(m + hq)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rnd = lambda *x: torch.randn(*x, generator=g).to(td).to(DEV)  # noqa: E731
+    q, kc, vc, rep = rnd(batch, m, hq, d), rnd(batch, nb, hkv, 128, d), rnd(batch, nb, hkv, d, 128), rnd(batch, nb, 4, hkv, d)
+    i32, f32 = dict(dtype=torch.int32, device=DEV), dict(dtype=torch.float32, device=DEV)
+    n_ctx = torch.full((batch,), n0 + m, **i32)
+    nb_end = torch.full((batch,), 1 + n_elig, **i32)
+    got = []
+    for one_call in (False, True):
+        st = torch.zeros(batch, B.stats_floats(cs), **f32)
+        r = dict(stats=st, probe=torch.zeros(batch, dd, **f32), kv=torch.zeros(batch, hkv * d, **f32), w=torch.zeros(batch, m, **f32),
+                 norm=torch.zeros(batch, **f32), scores=torch.zeros(batch, nb, **f32), idx=torch.full((batch, k_cap), -2, **i32),
+                 n_sel=torch.zeros(batch, **i32), theta=torch.zeros(batch, **f32), bud=torch.zeros(batch, **f32),
+                 left=torch.full((batch,), 9.0, **f32), out=torch.zeros_like(q))
+        rest = torch.full((batch,), 1.5, **f32)
+        ws = torch.zeros(B.workspace_bytes(cs, batch, m, nb, k_cap), dtype=torch.uint8, device=DEV)
+        if one_call:
+            B.window_step(cs, batch, m, q, st, True, r["probe"], r["kv"], r["norm"], r["w"], rep, rep.stride(0), 1 + n_elig, 1, nb_end,
+                          r["scores"], nb, k_cap, r["left"], rest, r["idx"], r["n_sel"], r["theta"], r["bud"], kc, vc, kc.stride(0),
+                          nb, n_ctx, r["out"], None, ws)
+        else:
+            B.build_probe(cs, batch, m, q, st, True, r["probe"], r["kv"], r["norm"], r["w"], ws)
+            B.score_blocks(cs, batch, r["kv"], r["norm"], rep, rep.stride(0), 1 + n_elig, 1, nb_end, r["scores"], nb)
+            B.select(batch, r["scores"], nb, 1 + n_elig, 1, nb_end, k_cap, r["left"], rest, r["idx"], r["n_sel"], r["theta"], r["bud"])
+            B.retrieval_attention(cs, batch, m, q, kc, vc, kc.stride(0), nb, n_ctx, r["idx"], r["n_sel"], k_cap, r["out"], None, ws)
+        torch.cuda.synchronize()
+        got.append(r)
+    a, b = got
+    for name in ("stats", "probe", "w", "idx", "n_sel", "out"):
+        assert torch.equal(a[name], b[name]), name
+    bound = 4096 * 2.0 ** -24
+    for name in ("kv", "norm", "scores", "theta", "bud", "left"):
+        assert (a[name] - b[name]).abs().max() <= bound * a[name].abs().max(), name
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 129, 257, 1000, 1024])
 def test_selection_by_one_wavefront_where_few_lanes_hold_the_best(n):
     """The wavefront keeps three candidates per lane (block i is lane i % 64's): the best blocks all in one lane, in two,
