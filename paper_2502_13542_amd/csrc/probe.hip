@@ -208,7 +208,8 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const 
 // the bias weight a_j of a row is complete while the row is still in registers and Eq. (9)'s
 // weighted sum is taken in the same pass: the queries are read twice, not three times.
 //   rows_moments     (chunks x windows): sums of (q - c) and (q - c)^2 per channel over the
-//                    chunk's rows, c = the window's first query;
+//                    chunk's rows, c = the window's first query, for a single window the old mean
+//                    where there is one;
 //   chain_stats      per channel: every window's own (mean, M2) from its chunks, then the merges
 //                    of Eq. (8) window after window, which give the (mean, 1/var) each window
 //                    sees; stores the final statistics;
@@ -226,6 +227,7 @@ constexpr int kRmThreads = 256;
 // requested together.
 template <typename T>
 __global__ __launch_bounds__(kRmThreads) void probe_rows_moments_kernel(const T* __restrict__ q_win,
+                                                                        const float* __restrict__ stats,
                                                                         float* __restrict__ part, int m, int d,
                                                                         int n_chunks, int cols) {
   constexpr int V = Vec<T>::N;
@@ -239,6 +241,11 @@ __global__ __launch_bounds__(kRmThreads) void probe_rows_moments_kernel(const T*
   const bool ok = ch < d && rl < rls;
   float c[V], s1[V], s2[V];
   Vec<T>::load(q + (ok ? ch : 0), c);
+  if (gridDim.y == 1 && stats[0] > 0.f) {            // (n sums of squares about a point lose n * its distance^2)
+    const float* mean = stats + 4 + (ok ? ch : 0);
+#pragma unroll
+    for (int v = 0; v < V; ++v) c[v] = mean[v];
+  }
 #pragma unroll
   for (int v = 0; v < V; ++v) s1[v] = s2[v] = 0.f;
   const int r0 = rc * kRowChunk, r1 = min(r0 + kRowChunk, m);
@@ -342,7 +349,7 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
         }
     }
     if (live && u == 0) {
-      wm[(w * 2 + 0) * 32 + cl] = first + t1 / nb;
+      wm[(w * 2 + 0) * 32 + cl] = (n == 1 && n_run > 0.f ? mean : first) + t1 / nb;   // (n = 1: lane 0 alone comes here)
       wm[(w * 2 + 1) * 32 + cl] = fmaxf(t2 - t1 * t1 / nb, 0.f);
     }
   }
@@ -761,7 +768,7 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
     int cols = std::min(groups, kRmThreads);
     while (cols > 64 && batch * n_chunks * ((groups + cols - 1) / cols) < kChipCus) cols = std::max(cols / 2, 64);
     hipLaunchKernelGGL(probe_rows_moments_kernel<T>, dim3(n_chunks, batch, (groups + cols - 1) / cols), dim3(kRmThreads), 0,
-                       stream, q_win, part, m, d, n_chunks, cols);
+                       stream, q_win, stats, part, m, d, n_chunks, cols);
     hipLaunchKernelGGL(probe_chain_stats_kernel<T>, dim3((d + 31) / 32), dim3(1024), size_t(batch) * 64 * sizeof(float),
                        stream, q_win, part, stats, stat, batch, m, d, n_chunks, eps);
     // Few chunks: half as long in the second pass.  Twice as many partial probes take the place of the moments, which

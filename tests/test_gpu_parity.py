@@ -2544,6 +2544,30 @@ def test_probe_of_consecutive_windows_in_one_call(dtype, hq, hkv, d, m, calls):
         B.build_probe(cs, 2, m, qd[:2], stats, B.PROBE_WINDOW_CHAIN, probe[:2], probe_kv[:2], norm[:2], None, ws)
 
 
+@pytest.mark.parametrize("m", [4096, 2563, 512])
+def test_statistics_where_the_first_query_lies_far_from_the_others(m):
+    """A window whose first query is K away from the old mean, which the sums of the window are about: M2 grows by K^2,
+    and the at most 128 additions that see K^2 round by 2^-24 of it each (sums of 4096 queries about the first of them:
+    1e-3)."""
+    sh = LayerShape(8, 2, 64, 128, 4, 128, 512, "fp32")
+    cs = B.c_shape(sh)
+    _say(f"[case] far first query m={m}")
+    g = torch.Generator().manual_seed(5 + m)
+    q = torch.randn(2, m, 512, generator=g)
+    q[1, 0] += torch.linspace(30.0, 3000.0, 512)
+    qd = q.to(DEV)
+    stats = torch.zeros(B.stats_floats(cs), device=DEV)
+    ws = torch.zeros(B.workspace_bytes(cs, 1, m, 8, 4), dtype=torch.uint8, device=DEV)
+    probe, kv, norm = (torch.zeros(x, device=DEV) for x in (512, 128, 1))
+    rs = orc.RunningStats(512)
+    for t in range(2):
+        B.build_probe(cs, 1, m, qd[t], stats, B.STATS_UPDATE, probe, kv, norm, None, ws)
+        rs.update(f64(q[t]))
+    torch.cuda.synchronize()
+    err = np.abs(f64(stats)[4 + 512:4 + 1024] - rs.m2) / rs.m2
+    assert err.max() < 140 * 2.0 ** -24, err.max()
+
+
 def test_gather_blocks_from_pinned_host_memory():
     """actqkv_gather_blocks: the selected blocks of a store in pinned host memory land in the
     slots of the working cache, bit for bit; entries beyond n_sel and indices outside the store
