@@ -50,9 +50,11 @@ def on_streams(lead: torch.cuda.Stream):
         yield
         return
     lead.wait_stream(outer)
-    with torch.cuda.stream(lead):
-        yield
-    outer.wait_stream(lead)
+    try:
+        with torch.cuda.stream(lead):
+            yield
+    finally:                                                # (what is on `lead` uses the caller's tensors, also after an error)
+        outer.wait_stream(lead)
 
 
 # ---------------------------------------------------------------- layouts
