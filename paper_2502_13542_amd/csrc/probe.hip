@@ -221,6 +221,12 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const 
 // own mean), pprobe [n][chunks][d], asum [n][chunks rounded up to 16], a [n][m rounded up to 16].
 constexpr int kRmThreads = 256;
 
+// The point a channel's sums are about.  (An old mean that is infinite or NaN would make the window's own mean NaN too, and that
+// one is the probe where the bias weights are NaN.)
+__device__ __forceinline__ float moments_about(float first, float n_run, float old_mean) {
+  return n_run > 0.f && fabsf(old_mean) <= 3.4028235e38f ? old_mean : first;
+}
+
 // grid (chunks, windows, ceil(d / V / cols)): a workgroup takes `cols` 16-byte channel groups (64 .. 256) of the chunk's
 // rows, row lane rl of 256 / cols the rows rl, rl + lanes, ..., and the lanes' sums are added in their order.  A compute
 // unit does not get more than 35-50 GB/s, so the channels are cut finer where there are few chunks; 16 rows are
@@ -244,7 +250,7 @@ __global__ __launch_bounds__(kRmThreads) void probe_rows_moments_kernel(const T*
   if (gridDim.y == 1 && stats[0] > 0.f) {            // (n sums of squares about a point lose n * its distance^2)
     const float* mean = stats + 4 + (ok ? ch : 0);
 #pragma unroll
-    for (int v = 0; v < V; ++v) c[v] = mean[v];
+    for (int v = 0; v < V; ++v) c[v] = moments_about(c[v], 1.f, mean[v]);
   }
 #pragma unroll
   for (int v = 0; v < V; ++v) s1[v] = s2[v] = 0.f;
@@ -349,7 +355,7 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
         }
     }
     if (live && u == 0) {
-      wm[(w * 2 + 0) * 32 + cl] = (n == 1 && n_run > 0.f ? mean : first) + t1 / nb;   // (n = 1: lane 0 alone comes here)
+      wm[(w * 2 + 0) * 32 + cl] = (n == 1 ? moments_about(first, n_run, mean) : first) + t1 / nb;   // (n = 1: lane 0 alone comes here)
       wm[(w * 2 + 1) * 32 + cl] = fmaxf(t2 - t1 * t1 / nb, 0.f);
     }
   }

@@ -2570,6 +2570,28 @@ def test_statistics_where_the_first_query_lies_far_from_the_others(m):
     assert err.max() < 140 * 2.0 ** -24, err.max()
 
 
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("m,chain", [(4096, False), (700, False), (300, True)])
+def test_probe_where_a_running_mean_is_not_finite(m, chain, bad):
+    """Bias weights that are all NaN count as none: the probe is the window's mean, also in the channel whose running mean
+    is NaN or infinite.  A mean of m values as partial sums of at most 128 additions each way and about a point of at
+    most their own size: 260 * 2^-24 of the largest value."""
+    sh = LayerShape(8, 2, 64, 128, 4, 128, 512, "fp32")
+    cs = B.c_shape(sh)
+    q = torch.randn(1, m, 512, generator=torch.Generator().manual_seed(m))
+    stats = torch.zeros(B.stats_floats(cs))
+    stats[0] = 100.0
+    stats[4 + 512:4 + 1024] = 99.0
+    stats[4 + 7] = bad
+    ws = torch.zeros(B.workspace_bytes(cs, 1, m, 8, 4), dtype=torch.uint8, device=DEV)
+    probe, kv, norm, w = (torch.zeros(x, device=DEV) for x in (512, 128, 1, m))
+    B.build_probe(cs, 1, m, q.to(DEV), stats.to(DEV), B.STATS_UPDATE | (B.PROBE_WINDOW_CHAIN if chain else 0), probe, kv, norm, w, ws)
+    torch.cuda.synchronize()
+    assert (w - 1.0 / m).abs().max() <= 2.0 ** -23 / m
+    err = np.abs(f64(probe) - f64(q[0]).mean(axis=0))
+    assert err.max() < 260 * 2.0 ** -24 * float(q.abs().max()), err.max()
+
+
 def test_gather_blocks_from_pinned_host_memory():
     """actqkv_gather_blocks: the selected blocks of a store in pinned host memory land in the
     slots of the working cache, bit for bit; entries beyond n_sel and indices outside the store
