@@ -385,23 +385,24 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
 
 // grid (chunks, windows), NW wavefronts; wavefront v takes rows v, v + NW, ... of the chunk, a lane
 // the 16-byte groups lane, lane + 64, ... of a row (NI of them: d <= 64 * NI * V channels), R rows at a time and the
-// next R in flight meanwhile (8 groups of each).  NI is the least that holds a row: with room for 4096 channels whatever
+// next R in flight meanwhile (8 groups of each; with NI = 1 the chunk is R * NW rows and nothing follows).  For rows that are
+// not there the chunk's last one is requested once more (branches around the loads: 4 windows of 512 tokens with 4096 channels
+// 36.4 us instead of 35.3), and no weight is applied (0 times an infinite query is NaN).  NI is the least that holds a row: with room for 4096 channels whatever
 // the row (and half of the lanes of rows_moments idle, 8 rows at once), the four launches of 32 windows of 256 tokens with
 // 512 channels took 49 us, 26 so; of 4 windows of 512 tokens with 4096 channels 50, 36 (chunks of 32 rows).
 // LDS: mean and 1/var of the window (2 kRowLen floats), reused for the sum over the wavefronts.
-template <typename T, int NI, int NW>
+template <typename T, int NI, int NW, int R>
 __global__ __launch_bounds__(64 * NW) void probe_rows_bias_weigh_kernel(
     const T* __restrict__ q_win, const float* __restrict__ stat_in, float* __restrict__ stats, float add_count,
     int mean_pooling, float* __restrict__ pprobe, float* __restrict__ asum, float* __restrict__ a_rows, int m,
     int m_pad, int d, int rows, int n_chunks, int asum_stride) {
   constexpr int V = Vec<T>::N;
-  constexpr int R = NI < 8 ? 8 / NI : 1;
   typedef typename Vec<T>::raw raw_t;
   constexpr int kRowLen = 64 * NI * V;                             // channels a wavefront covers
   extern __shared__ __attribute__((aligned(16))) float rw_lds[];   // [max(2 kRowLen, NW / 2 d)]
   __shared__ float red[NW];
   const int rc = blockIdx.x, w = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const T* q = q_win + size_t(w) * m * d;
   float* mu = rw_lds;
   float* iv = rw_lds + kRowLen;
@@ -432,10 +433,9 @@ __global__ __launch_bounds__(64 * NW) void probe_rows_bias_weigh_kernel(
     for (int v = 0; v < V; ++v) acc[i][v] = 0.f;
   float a_sum = 0.f;
   for (int r = r0 + wave; r < r1; r += R * NW) {
-    // the wavefront's next rows are requested before these are used (the last ones ask for the chunk's last row once
-    // more, which costs nothing that matters)
+    // the wavefront's next rows are requested before these are used
     raw_t xn[R][NI];
-    load_rows(r + R * NW, xn);
+    if constexpr (NI > 1) load_rows(r + R * NW, xn);
     float t[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) t[j] = 0.f;
@@ -470,14 +470,17 @@ __global__ __launch_bounds__(64 * NW) void probe_rows_bias_weigh_kernel(
       a_sum += a[j];
     }
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+    for (int j = 0; j < R; ++j)
+      if (r + j * NW < r1) {
 #pragma unroll
-      for (int j = 0; j < R; ++j) {
-        float f[V];
-        Vec<T>::widen(x[j][i], f);
+        for (int i = 0; i < NI; ++i) {
+          float f[V];
+          Vec<T>::widen(x[j][i], f);
 #pragma unroll
-        for (int v = 0; v < V; ++v) acc[i][v] += a[j] * f[v];
+          for (int v = 0; v < V; ++v) acc[i][v] += a[j] * f[v];
+        }
       }
+    if constexpr (NI == 1) break;
 #pragma unroll
     for (int j = 0; j < R; ++j)
 #pragma unroll
@@ -791,11 +794,12 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
       hipLaunchKernelGGL(kernel, dim3(n_parts, batch), dim3(64 * waves), lds, stream, q_win, stat, stats,
                          float(batch) * float(m), mean_pooling, pprobe, asum, a_rows, m, m_pad, d, rows, n_parts, asum_stride);
     };
-    if (groups <= 64) bias_weigh(probe_rows_bias_weigh_kernel<T, 1, 8>, 1, 8);
-    else if (groups <= 128) bias_weigh(probe_rows_bias_weigh_kernel<T, 2, 8>, 2, 8);
-    else if (groups <= 256) bias_weigh(probe_rows_bias_weigh_kernel<T, 4, 8>, 4, 8);
-    else if (groups <= 512) bias_weigh(probe_rows_bias_weigh_kernel<T, 8, 4>, 8, 4);
-    else bias_weigh(probe_rows_bias_weigh_kernel<T, 16, 4>, 16, 4);
+    if (groups <= 64 && halves) bias_weigh(probe_rows_bias_weigh_kernel<T, 1, 8, 4>, 1, 8);
+    else if (groups <= 64) bias_weigh(probe_rows_bias_weigh_kernel<T, 1, 8, 8>, 1, 8);
+    else if (groups <= 128) bias_weigh(probe_rows_bias_weigh_kernel<T, 2, 8, 4>, 2, 8);
+    else if (groups <= 256) bias_weigh(probe_rows_bias_weigh_kernel<T, 4, 8, 2>, 4, 8);
+    else if (groups <= 512) bias_weigh(probe_rows_bias_weigh_kernel<T, 8, 4, 1>, 8, 4);
+    else if constexpr (V == 4) bias_weigh(probe_rows_bias_weigh_kernel<T, 16, 4, 1>, 16, 4);   // (4096 channels of 16 bits are 512)
     hipLaunchKernelGGL(probe_chain_finish_kernel, dim3(batch), dim3(1024), size_t(d) * sizeof(float), stream, pprobe,
                        asum, a_rows, stat, probe, probe_kv, probe_norm, weights, m, m_pad, d, n_parts, asum_stride,
                        sh.n_q_heads, sh.n_kv_heads, sh.head_dim);
@@ -828,7 +832,6 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
   if (finish)
     hipLaunchKernelGGL(probe_finish_kernel, dim3(batch), dim3(kFinishThreads), 0, stream, probe, probe_kv,
                        probe_norm, sh.n_q_heads, sh.n_kv_heads, sh.head_dim);
-  (void)V;
   return hip_status("probe");
 }
 

@@ -2592,6 +2592,35 @@ def test_probe_where_a_running_mean_is_not_finite(m, chain, bad):
     assert err.max() < 260 * 2.0 ** -24 * float(q.abs().max()), err.max()
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,d,m,n", [
+    ("bf16", 8, 2, 64, 70, 3),        # 64 groups of 16 bytes, chunks of 32 rows: 6 in the last, for 8 wavefronts of 4 rows
+    ("bf16", 8, 2, 64, 1100, 20),     # chunks of 64 rows: 12 in the last
+    ("fp32", 8, 2, 64, 37, 2),        # 128 groups, 5
+    ("bf16", 16, 2, 128, 1025, 12),   # 256 groups, 1
+    ("bf16", 28, 4, 128, 67, 2),      # 448 groups, 3, for 4 wavefronts
+    ("fp32", 32, 8, 128, 66, 2),      # 1024 groups, 2
+    ("bf16", 8, 2, 64, 2060, 1),      # a long window by itself
+])
+def test_mean_of_windows_with_an_infinite_query_in_the_last_row(dtype, hq, hkv, d, m, n):
+    """Mean pooling: a channel with one infinite query has an infinite mean (no weight is applied to rows that are not
+    there: 0 times infinity is NaN); the others have theirs, a sum of m values in any order, m * 2^-24 of the largest."""
+    sh = LayerShape(hq, hkv, d, 128, 4, 128, 512, dtype)
+    cs, dd = B.c_shape(sh), hq * d
+    q = torch.randn(n, m, dd, generator=torch.Generator().manual_seed(m)).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    q[:, -1, 5] = float("inf")
+    stats = torch.zeros(B.stats_floats(cs), device=DEV)
+    ws = torch.zeros(B.workspace_bytes(cs, n, m, 8, 4), dtype=torch.uint8, device=DEV)
+    probe, kv, norm, w = (torch.zeros(n, x, device=DEV) for x in (dd, hkv * d, 1, m))
+    flags = B.STATS_UPDATE | B.PROBE_MEAN_POOLING | (B.PROBE_WINDOW_CHAIN if n > 1 else 0)
+    B.build_probe(cs, n, m, q.to(DEV), stats, flags, probe, kv, norm, w, ws)
+    torch.cuda.synchronize()
+    got, want = f64(probe), f64(q).mean(axis=1)
+    assert (got[:, 5] == np.inf).all(), got[:, 5]
+    rest = np.arange(dd) != 5
+    largest = float(q[torch.isfinite(q)].abs().max())
+    assert np.abs(got[:, rest] - want[:, rest]).max() < m * 2.0 ** -24 * largest
+
+
 def test_gather_blocks_from_pinned_host_memory():
     """actqkv_gather_blocks: the selected blocks of a store in pinned host memory land in the
     slots of the working cache, bit for bit; entries beyond n_sel and indices outside the store
