@@ -304,13 +304,16 @@ __global__ __launch_bounds__(kRmThreads) void probe_rows_moments_kernel(const T*
 // (mean, M2) in LDS: with fewer than 32 windows several lanes share one (32 / n, rounded down to a power of two), lane
 // u of them the chunks u, u + share, ..., whose sums are added in lane order.  Then lane 0 merges the windows into the
 // running statistics in window order (the merge of Eq. (8), as in probe_stats_bias_kernel).  The count is published by
-// the next kernel (every thread here reads the old one).
+// the next kernel (every thread here reads the old one; `before` is what launches of this call have added to it).  At most
+// kChainTile windows a launch: 128 KB of LDS, and 8 KB for the lanes' sums.  (The tiles in one launch, as a loop: a window
+// of 4096 tokens with 512 channels 24.3 us instead of 23.7.)
+constexpr int kChainTile = 512;
 template <typename T>
 __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __restrict__ q_win,
                                                                  const float* __restrict__ part,
                                                                  float* __restrict__ stats,
                                                                  float* __restrict__ stat_out, int n, int m,
-                                                                 int d, int n_chunks, float eps) {
+                                                                 int d, int n_chunks, float eps, float before, int single) {
   extern __shared__ float wm[];                      // [n][2][32]: the windows' own mean and M2
   __shared__ float lane_sum[2][32][32];
   constexpr int kBatch = 8;                          // chunks requested together
@@ -321,7 +324,7 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
   while (share * 2 * n <= 32) share *= 2;
   const int u = wl % share;
   float n_run = 0.f, mean = 0.f, m2 = 0.f;
-  if (wl == 0 && ch < d) n_run = stats[0], mean = stats[4 + ch], m2 = stats[4 + d + ch];   // (in flight meanwhile)
+  if (wl == 0 && ch < d) n_run = stats[0] + before, mean = stats[4 + ch], m2 = stats[4 + d + ch];   // (in flight meanwhile)
   for (int w0 = 0; w0 < n; w0 += 32 / share) {
     const int w = w0 + wl / share;
     const bool live = w < n && ch < d;
@@ -355,7 +358,7 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
         }
     }
     if (live && u == 0) {
-      wm[(w * 2 + 0) * 32 + cl] = (n == 1 ? moments_about(first, n_run, mean) : first) + t1 / nb;   // (n = 1: lane 0 alone comes here)
+      wm[(w * 2 + 0) * 32 + cl] = (single ? moments_about(first, n_run, mean) : first) + t1 / nb;   // (a single window: lane 0 alone comes here)
       wm[(w * 2 + 1) * 32 + cl] = fmaxf(t2 - t1 * t1 / nb, 0.f);
     }
   }
@@ -778,8 +781,12 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
     while (cols > 64 && batch * n_chunks * ((groups + cols - 1) / cols) < kChipCus) cols = std::max(cols / 2, 64);
     hipLaunchKernelGGL(probe_rows_moments_kernel<T>, dim3(n_chunks, batch, (groups + cols - 1) / cols), dim3(kRmThreads), 0,
                        stream, q_win, stats, part, m, d, n_chunks, cols);
-    hipLaunchKernelGGL(probe_chain_stats_kernel<T>, dim3((d + 31) / 32), dim3(1024), size_t(batch) * 64 * sizeof(float),
-                       stream, q_win, part, stats, stat, batch, m, d, n_chunks, eps);
+    for (int w = 0; w < batch; w += kChainTile) {
+      const int n = std::min(batch - w, kChainTile);
+      hipLaunchKernelGGL(probe_chain_stats_kernel<T>, dim3((d + 31) / 32), dim3(1024), size_t(n) * 64 * sizeof(float), stream,
+                         q_win + size_t(w) * m * d, part + size_t(w) * n_chunks * 2 * d, stats, stat + size_t(w) * 3 * d, n, m, d,
+                         n_chunks, eps, float(w) * float(m), int(batch == 1));
+    }
     // Few chunks: half as long in the second pass.  Twice as many partial probes take the place of the moments, which
     // chain_stats has used up, and their sums that of the partial probes.
     const bool halves = batch * n_chunks <= kChipCus / 2 && n_chunks <= 16;

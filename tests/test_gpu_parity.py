@@ -2493,6 +2493,7 @@ def test_mean_pooling_probe_variant():
     ("bf16", 16, 2, 128, 200, (2,)),        # 256 groups
     ("bf16", 28, 4, 128, 1100, (1,)),       # 448 groups, 18 chunks
     ("fp32", 32, 8, 128, 65, (2, 3)),       # 1024 groups
+    ("bf16", 8, 2, 64, 3, (513, 1024)),     # a window more than are merged at a time; as many as a call takes
     ("bf16", 8, 2, 64, 2049, (-2,)),        # long windows of few channels, a call each without the flag
     ("fp32", 8, 2, 64, 2048, (-1,)),
 ])
