@@ -42,13 +42,8 @@ def side_streams(n: int, device) -> List[torch.cuda.Stream]:
 
 @contextlib.contextmanager
 def on_streams(lead: torch.cuda.Stream):
-    """The body's calls on `lead`, behind what the current stream holds; the current stream goes on behind `lead`.  Under
-    capture they stay on the current stream: a graph's branches have no stream of their own, and the runtime's
-    end-of-capture call crashes on streams that were forked from a forked stream."""
+    """The body's calls on `lead`, behind what the current stream holds; the current stream goes on behind `lead`."""
     outer = torch.cuda.current_stream()
-    if outer == lead or torch.cuda.is_current_stream_capturing():
-        yield
-        return
     lead.wait_stream(outer)
     try:
         with torch.cuda.stream(lead):
@@ -753,7 +748,11 @@ class HostCachePrefill:
         use; blocks that still lie in the region do not cross it at all.  A fourth attends.
         Results are those of run().  What bounds it: a pass over 32K tokens (32 query, 8 KV heads,
         windows of 512, 16 blocks each) gathered 0.5 GB in 12.9 ms when every window brought its own
-        blocks; now the attention (16 launches of 151 us) and 128 MB of write-back (2.4 ms) go side by side: 3.4 ms."""
+        blocks; now the attention (16 launches of 151 us) and 128 MB of write-back (2.4 ms) go side by side: 3.4 ms.
+
+        Not to be captured in a HIP graph (the runtime's end-of-capture call crashes on this schedule's streams)."""
+        if torch.cuda.is_current_stream_capturing():
+            raise RuntimeError("HostCachePrefill.run_overlapped cannot be captured in a HIP graph")
         with on_streams(self.lead):
             return self._run_overlapped(q, k_tok, v_tok, k_store, v_store, rep_keys, out, write_back)
 

@@ -420,3 +420,13 @@ with FakeTensorMode():
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr[-1000:]
     assert r.stdout.split() == ["raised", "raised"]
+
+
+def test_overlapped_host_cache_pass_refuses_capture(monkeypatch):
+    """Under capture nothing is enqueued: the end of a capture of its streams crashes the process."""
+    import torch
+    from paper_2502_13542_amd import harness as H
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: pytest.fail("a stream was used"))
+    with pytest.raises(RuntimeError, match="cannot be captured"):
+        object.__new__(H.HostCachePrefill).run_overlapped(*[None] * 7)

@@ -2821,7 +2821,7 @@ def test_prefill_with_the_cache_in_host_memory():
     # their own), with the host store EMPTY at the start: every block a window selects has been
     # written back from a working cache by then.  Twice in a row, eagerly (capturing this
     # four-stream schedule in a HIP graph ended in a host-side crash inside the runtime's
-    # end-of-capture call; the schedule is not captured anywhere).
+    # end-of-capture call; it refuses that).
     k_zero, v_zero = torch.zeros_like(k_store).pin_memory(), torch.zeros_like(v_store).pin_memory()
     out_ov = torch.zeros_like(qd)
 
