@@ -41,14 +41,17 @@ def side_streams(n: int, device) -> List[torch.cuda.Stream]:
 
 
 @contextlib.contextmanager
-def on_streams(lead: torch.cuda.Stream):
-    """The body's calls on `lead`, behind what the current stream holds; the current stream goes on behind `lead`."""
+def on_streams(lead: torch.cuda.Stream, others: Sequence[torch.cuda.Stream]):
+    """The body's calls on `lead`, behind what the current stream holds, with `others` for it to fork to.  What comes next
+    on `lead` and on the current stream goes on behind all of them."""
     outer = torch.cuda.current_stream()
     lead.wait_stream(outer)
     try:
         with torch.cuda.stream(lead):
             yield
-    finally:                                                # (what is on `lead` uses the caller's tensors, also after an error)
+    finally:            # (also after an error: they use the caller's tensors, and the next body the memory of this one)
+        for st in others:
+            lead.wait_stream(st)
         outer.wait_stream(lead)
 
 
@@ -753,7 +756,7 @@ class HostCachePrefill:
         Not to be captured in a HIP graph (the runtime's end-of-capture call crashes on this schedule's streams)."""
         if torch.cuda.is_current_stream_capturing():
             raise RuntimeError("HostCachePrefill.run_overlapped cannot be captured in a HIP graph")
-        with on_streams(self.lead):
+        with on_streams(self.lead, (self.mover, self.attender, self.writer)):
             return self._run_overlapped(q, k_tok, v_tok, k_store, v_store, rep_keys, out, write_back)
 
     def _run_overlapped(self, q, k_tok, v_tok, k_store, v_store, rep_keys, out, write_back):
@@ -828,7 +831,5 @@ class HostCachePrefill:
                 B.retrieval_attention(cs, 1, rows, q[a:a + rows], kc, vc, 0, kc.shape[0], self.v_nctx[t], self.v_slots[t],
                                       self.v_nsel[t], r.k_cap, out[a:a + rows], None, self.workspace, attender)
             attended[g].record(attender)
-        for st in (mover, attender, writer):
-            cur.wait_stream(st)
         return {t: dict(idx=self.idx_all[t], n_sel=self.n_sel_all[t], idx_slots=self.idx_slots_all[t])
                 for t in range(plan.n_windows)}

@@ -430,3 +430,35 @@ def test_overlapped_host_cache_pass_refuses_capture(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: pytest.fail("a stream was used"))
     with pytest.raises(RuntimeError, match="cannot be captured"):
         object.__new__(H.HostCachePrefill).run_overlapped(*[None] * 7)
+
+
+@pytest.mark.parametrize("fails", [False, True])
+def test_streams_of_a_pass_are_joined_after_an_error_too(monkeypatch, fails):
+    """Whatever ends the body, the caller's stream and the pass's own wait for every stream that it has used."""
+    import contextlib
+    import torch
+    from paper_2502_13542_amd import harness as H
+    log = []
+
+    class Stream:
+        def __init__(self, name):
+            self.name = name
+
+        def wait_stream(self, other):
+            log.append(self.name + " waits for " + other.name)
+
+    def body(self, *args):
+        log.append("body")
+        if fails:
+            raise B.ActQKVError(-1, "refused in mid-pass")
+
+    h = object.__new__(H.HostCachePrefill)
+    outer, h.lead, h.mover, h.attender, h.writer = (Stream(x) for x in ("caller", "lead", "mover", "attender", "writer"))
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: outer)
+    monkeypatch.setattr(torch.cuda, "stream", lambda s: contextlib.nullcontext())
+    monkeypatch.setattr(H.HostCachePrefill, "_run_overlapped", body)
+    with pytest.raises(B.ActQKVError) if fails else contextlib.nullcontext():
+        h.run_overlapped(*[None] * 7)
+    assert log == ["lead waits for caller", "body", "lead waits for mover", "lead waits for attender", "lead waits for writer",
+                   "caller waits for lead"]
