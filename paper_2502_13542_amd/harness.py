@@ -31,13 +31,38 @@ def eligible_range(shape: LayerShape, w0: int) -> Tuple[int, int]:
 
 
 # ---------------------------------------------------------------- streams
+def runs_beside(st: torch.cuda.Stream, busy: torch.cuda.Stream, src: torch.Tensor, host: torch.Tensor) -> bool:
+    """Whether `st` has another hardware queue than `busy`: 16 bytes on the one end before a copy over the host link on the
+    other that was there first (4 MB: about 20 and 78 us, 85 and 78 on one queue).  Waits for both."""
+    ends = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    B.copy_bytes_at(host, 0, src, 0, host.numel(), busy)
+    ends[0].record(busy)
+    B.copy_bytes_at(src, host.numel() + 16, src, host.numel(), 16, st)
+    ends[1].record(st)
+    for e in ends:
+        e.synchronize()
+    return ends[1].elapsed_time(ends[0]) > 0
+
+
 def side_streams(n: int, device) -> List[torch.cuda.Stream]:
-    """n <= 4 streams for work that is to run at the same time.  A process has four hardware queues here, and streams
-    that share one run their kernels one after the other.  Streams made one after the other are dealt to the queues in
-    turn, so these have a queue each; but one of them may have the queue of the caller's current stream, which
-    therefore only waits (on_streams).  With the selection chain on the current stream and three more, a host-cache
-    pass over 32K tokens took 3.4, 4.0, 4.5 or 5.6 ms by the streams its object had got; 3.4 to 3.5 so."""
-    return [torch.cuda.Stream(device=device) for _ in range(n)]
+    """n streams whose kernels run at the same time.  A process has four hardware queues here, and streams that share one
+    run their kernels one after the other.  Which new stream gets which queue is the runtime's affair (of a process's first
+    four the third and the fourth share one), so streams are taken until n of them have been seen to run beside each other; if
+    4 n are not enough, as where there are fewer queues, the rest share.  One of four has the queue of the caller's
+    current stream, which therefore only waits (on_streams).  A host-cache pass over 32K tokens takes 5.5 ms where attention
+    and write-back share a queue and 3.5 where nothing does, one over 128K 23.4 and 15.4.  The trials take 0.6 ms (a verdict
+    is wrong where the host is held up between two launches, 2 in 1000, and then another stream is taken)."""
+    size = 4 << 20
+    src = torch.empty(size + 32, dtype=torch.uint8, device=device)
+    host = torch.empty(size, dtype=torch.uint8, pin_memory=True)
+    kept: List[torch.cuda.Stream] = []
+    others: List[torch.cuda.Stream] = []
+    while len(kept) < n and len(kept) + len(others) < 4 * n:
+        st = torch.cuda.Stream(device=device)
+        B.copy_bytes_at(src, size + 16, src, size, 16, st)      # (a stream's first launch takes 0.2 to 3 ms)
+        st.synchronize()
+        (kept if all(runs_beside(st, k, src, host) for k in kept) else others).append(st)
+    return (kept + others)[:n]
 
 
 @contextlib.contextmanager
@@ -751,7 +776,7 @@ class HostCachePrefill:
         use; blocks that still lie in the region do not cross it at all.  A fourth attends.
         Results are those of run().  What bounds it: a pass over 32K tokens (32 query, 8 KV heads,
         windows of 512, 16 blocks each) gathered 0.5 GB in 12.9 ms when every window brought its own
-        blocks; now the attention (16 launches of 151 us) and 128 MB of write-back (2.4 ms) go side by side: 3.4 ms.
+        blocks; now the attention (16 launches of 151 us) and 128 MB of write-back (2.4 ms) go side by side: 3.5 ms.
 
         Not to be captured in a HIP graph (the runtime's end-of-capture call crashes on this schedule's streams)."""
         if torch.cuda.is_current_stream_capturing():

@@ -462,3 +462,20 @@ def test_streams_of_a_pass_are_joined_after_an_error_too(monkeypatch, fails):
         h.run_overlapped(*[None] * 7)
     assert log == ["lead waits for caller", "body", "lead waits for mover", "lead waits for attender", "lead waits for writer",
                    "caller waits for lead"]
+
+
+@pytest.mark.parametrize("queues,want", [
+    ([2, 3, 4, 4, 3, 2, 1], [2, 3, 4, 1]),        # as a process's first streams are dealt
+    ([4, 3, 2, 1], [4, 3, 2, 1]),
+    ([1, 2] * 8, [1, 2, 1, 2]),                   # fewer queues than streams: the rest share
+])
+def test_side_streams_have_a_queue_each(monkeypatch, queues, want):
+    import torch
+    from types import SimpleNamespace
+    from paper_2502_13542_amd import harness as H
+    dealt = iter(queues)
+    monkeypatch.setattr(torch.cuda, "Stream", lambda device: SimpleNamespace(queue=next(dealt), synchronize=lambda: None))
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: None)
+    monkeypatch.setattr(H.B, "copy_bytes_at", lambda *a: None)
+    monkeypatch.setattr(H, "runs_beside", lambda st, busy, src, host: st.queue != busy.queue, raising=False)
+    assert [st.queue for st in H.side_streams(4, "cuda")] == want

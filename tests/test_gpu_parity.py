@@ -2622,6 +2622,23 @@ def test_mean_of_windows_with_an_infinite_query_in_the_last_row(dtype, hq, hkv, 
     assert np.abs(got[:, rest] - want[:, rest]).max() < m * 2.0 ** -24 * largest
 
 
+def test_side_streams_run_beside_each_other():
+    """Sets of streams taken one after the other, whatever streams the process has made before: in each, work on one ends
+    before a copy that was there first on another; a stream does not run beside itself."""
+    size = 4 << 20
+    src = torch.zeros(size + 32, dtype=torch.uint8, device=DEV)
+    host = torch.zeros(size, dtype=torch.uint8, pin_memory=True)
+    for _ in range(3):
+        torch.cuda.Stream(device=DEV)
+        streams = H.side_streams(4, DEV)
+        torch.cuda.synchronize()
+        assert not H.runs_beside(streams[0], streams[0], src, host)
+        for a in streams:
+            for b in streams:
+                # (a host that is held up for 70 us between the two launches sees them one after the other)
+                assert a is b or any(H.runs_beside(a, b, src, host) for _ in range(3))
+
+
 def test_gather_blocks_from_pinned_host_memory():
     """actqkv_gather_blocks: the selected blocks of a store in pinned host memory land in the
     slots of the working cache, bit for bit; entries beyond n_sel and indices outside the store
