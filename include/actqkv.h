@@ -366,8 +366,8 @@ int actqkv_append_kv_probe(const actqkv_shape* shape, int batch, const void* q_t
  * actqkv_retrieval_attention with the arguments of the four calls, on one workspace (it must satisfy the largest of
  * them).  Same results (for one window of one sequence the probe's norm, and with it the scores, up to the order of an
  * fp32 sum: it is then taken in the scoring launch, a launch less).
- *   nb_scored    nb_capacity of the scoring and the selection (an upper bound of nb_end); nb_capacity is that of the
- *                caches.
+ *   nb_scored    nb_capacity of the scoring and the selection (an upper bound of nb_end): rep_keys holds as many blocks
+ *                per sequence, and those behind nb_end may be read too; nb_capacity is that of the caches.
  *   The other arguments as in the four calls; rep_seq_stride and cache_seq_stride are their seq_stride.
  * Errors: as in the four calls; nothing is launched if one of them would be refused. */
 int actqkv_window_step(const actqkv_shape* shape, int batch, int m, const void* q_win, float* stats,

@@ -149,7 +149,9 @@ class LayerRunner:
         nb_begin = sh.n_init // sh.block_size
         cache_stride = k_cache.stride(0) if k_cache.dim() == 5 else 0
         rep_stride = rep_keys.stride(0) if rep_keys.dim() == 5 else 0
-        nb_cap = min(max(nb_end_max, nb_begin), self.nb_capacity)
+        # (the scoring may read every block that it is told of, also those behind nb_end: none that rep_keys does not hold)
+        rows = rep_keys.shape[1] if rep_keys.dim() == 5 else rep_keys.numel() // (sh.n_rep * sh.n_kv_heads * sh.head_dim)
+        nb_cap = min(max(min(nb_end_max, rows), nb_begin), self.nb_capacity)
         B.window_step(cs, bt, m, q_win, self.stats, update_stats, self.probe, self.probe_kv, self.probe_norm, self.weights,
                       rep_keys, rep_stride, nb_cap, nb_begin, nb_end, self.scores, self.score_stride, self.k_cap,
                       budget_remaining, theta_rest_sum, self.idx, self.n_sel, self.theta, self.budget, k_cache, v_cache,

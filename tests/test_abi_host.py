@@ -422,6 +422,22 @@ with FakeTensorMode():
     assert r.stdout.split() == ["raised", "raised"]
 
 
+@pytest.mark.parametrize("lead", [(), (2,)])
+def test_a_window_scores_no_blocks_that_its_keys_do_not_hold(monkeypatch, lead):
+    """The scoring of a window may read every block that it is told of: of a loose bound of the eligible ones, those
+    that rep_keys holds."""
+    import torch
+    from paper_2502_13542_amd import harness as H
+    sh = LayerShape(8, 2, 64, 128, 4, 128, 256, "fp32")
+    runner = H.LayerRunner(sh, 2 if lead else 1, 16, 40, 4, "cpu")
+    told = []
+    monkeypatch.setattr(H.B, "window_step", lambda *a, **k: told.append(a[12]))
+    cache = torch.zeros(*lead, 1)
+    for held, bound in ((9, 40), (9, 5), (40, 100), (0, 3)):
+        runner.step(cache, cache, cache, torch.zeros(*lead, held, 4, 2, 64), None, None, bound, None)
+    assert told == [9, 5, 40, 1]
+
+
 def test_overlapped_host_cache_pass_refuses_capture(monkeypatch):
     """Under capture nothing is enqueued: the end of a capture of its streams crashes the process."""
     import torch
