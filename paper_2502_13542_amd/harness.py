@@ -44,24 +44,27 @@ def runs_beside(st: torch.cuda.Stream, busy: torch.cuda.Stream, src: torch.Tenso
     return ends[1].elapsed_time(ends[0]) > 0
 
 
-def side_streams(n: int, device) -> List[torch.cuda.Stream]:
-    """n streams whose kernels run at the same time.  A process has four hardware queues here, and streams that share one
-    run their kernels one after the other.  Which new stream gets which queue is the runtime's affair (of a process's first
-    four the third and the fourth share one), so streams are taken until n of them have been seen to run beside each other; if
-    4 n are not enough, as where there are fewer queues, the rest share.  One of four has the queue of the caller's
-    current stream, which therefore only waits (on_streams).  A host-cache pass over 32K tokens takes 5.5 ms where attention
-    and write-back share a queue and 3.5 where nothing does, one over 128K 23.4 and 15.4.  The trials take 0.6 ms (a verdict
-    is wrong where the host is held up between two launches, 2 in 1000, and then another stream is taken)."""
+def side_streams(n: int, device, beside: Sequence[torch.cuda.Stream] = ()) -> List[torch.cuda.Stream]:
+    """n streams whose kernels run at the same time as each other's and as those of `beside`.  A process has four hardware
+    queues here, and streams that share one run their kernels one after the other.  Which new stream gets which queue is
+    the runtime's affair (of a process's first four the third and the fourth share one), so streams are taken until n of them
+    have been seen to run beside each other; if 16 are not enough, as where there are fewer queues, the rest share (and
+    under capture, where nothing can be tried, all may).  One of four has the queue of the caller's current stream, which
+    therefore only waits (on_streams).  A host-cache pass over 32K tokens takes 5.5 ms where attention and write-back share
+    a queue and 3.5 where nothing does, one over 128K 23.4 and 15.4.  The trials for four take 0.6 ms (a verdict is wrong where
+    the host is held up between two launches, 2 in 1000, and then another stream is taken)."""
+    if torch.cuda.is_current_stream_capturing():
+        return [torch.cuda.Stream(device=device) for _ in range(n)]
     size = 4 << 20
     src = torch.empty(size + 32, dtype=torch.uint8, device=device)
     host = torch.empty(size, dtype=torch.uint8, pin_memory=True)
     kept: List[torch.cuda.Stream] = []
     others: List[torch.cuda.Stream] = []
-    while len(kept) < n and len(kept) + len(others) < 4 * n:
+    while len(kept) < n and len(kept) + len(others) < 16:
         st = torch.cuda.Stream(device=device)
         B.copy_bytes_at(src, size + 16, src, size, 16, st)      # (a stream's first launch takes 0.2 to 3 ms)
         st.synchronize()
-        (kept if all(runs_beside(st, k, src, host) for k in kept) else others).append(st)
+        (kept if all(runs_beside(st, k, src, host) for k in (*beside, *kept)) else others).append(st)
     return (kept + others)[:n]
 
 
@@ -291,12 +294,12 @@ class PrefillPipeline:
                  for n in (1, 2, self.MAX_CHUNK))
         self.ws_attn = torch.zeros(ws, dtype=torch.uint8, device=dev)
         self.ws_attn_b = torch.zeros(ws, dtype=torch.uint8, device=dev)   # two teams: chunks alternate workspaces
-        self.side = torch.cuda.Stream(device=dev)
+        # (one object in eight had `side` on the current stream's queue: 3.09 ms instead of 2.73 over 64K tokens)
+        self.side, self.side_score = side_streams(2, dev, [torch.cuda.current_stream(dev)])
         # the probe of every window, for the schedule that scores behind the probe chain
         dk = runner.shape.n_kv_heads * runner.shape.head_dim
         self.probe_kv = torch.empty(plan.n_windows, dk, dtype=torch.float32, device=dev)
         self.probe_norm = torch.empty(plan.n_windows, dtype=torch.float32, device=dev)
-        self.side_score = torch.cuda.Stream(device=dev)
         # the chunk-at-a-time schedule: probes and scores of up to MAX_CHUNK windows per call
         self.probe_chunk = torch.empty(self.MAX_CHUNK, runner.shape.n_q_heads * runner.shape.head_dim,
                                        dtype=torch.float32, device=dev)

@@ -480,18 +480,21 @@ def test_streams_of_a_pass_are_joined_after_an_error_too(monkeypatch, fails):
                    "caller waits for lead"]
 
 
-@pytest.mark.parametrize("queues,want", [
-    ([2, 3, 4, 4, 3, 2, 1], [2, 3, 4, 1]),        # as a process's first streams are dealt
-    ([4, 3, 2, 1], [4, 3, 2, 1]),
-    ([1, 2] * 8, [1, 2, 1, 2]),                   # fewer queues than streams: the rest share
+@pytest.mark.parametrize("queues,beside,want", [
+    ([2, 3, 4, 4, 3, 2, 1], [], [2, 3, 4, 1]),        # as a process's first streams are dealt
+    ([4, 3, 2, 1], [], [4, 3, 2, 1]),
+    ([1, 2] * 8, [], [1, 2, 1, 2]),                   # fewer queues than streams: the rest share
+    ([1, 4, 4, 3], [1], [4, 3]),                      # another one than a stream's that is there
 ])
-def test_side_streams_have_a_queue_each(monkeypatch, queues, want):
+def test_side_streams_have_a_queue_each(monkeypatch, queues, beside, want):
     import torch
     from types import SimpleNamespace
     from paper_2502_13542_amd import harness as H
     dealt = iter(queues)
     monkeypatch.setattr(torch.cuda, "Stream", lambda device: SimpleNamespace(queue=next(dealt), synchronize=lambda: None))
     monkeypatch.setattr(torch, "empty", lambda *a, **k: None)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
     monkeypatch.setattr(H.B, "copy_bytes_at", lambda *a: None)
     monkeypatch.setattr(H, "runs_beside", lambda st, busy, src, host: st.queue != busy.queue, raising=False)
-    assert [st.queue for st in H.side_streams(4, "cuda")] == want
+    there = [SimpleNamespace(queue=x) for x in beside]
+    assert [st.queue for st in H.side_streams(len(want), "cuda", there)] == want
