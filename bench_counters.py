@@ -12,15 +12,13 @@ import argparse
 import csv
 from collections import defaultdict
 
-CUS, SIMDS, XCDS = 256, 1024, 8
-
 
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("csv", nargs="+")
     ap.add_argument("--kernel", required=True)
     ap.add_argument("--calls", type=int, required=True, help="calls of the entry point in the pass")
-    ap.add_argument("--cus", type=int, default=CUS, help="compute units the kernel's first launch fills")
+    ap.add_argument("--waves-per-simd", type=int, default=2, help="wavefronts of the kernel that a SIMD holds")
     ap.add_argument("--title", required=True)
     ap.add_argument("--command", default="")
     ap.add_argument("--note", default="")
@@ -50,16 +48,16 @@ def main() -> int:
         lines.append(f"* Matrix-core instructions per call: {g('SQ_INSTS_MFMA'):,.0f} (wavefront level; 32x32x16 bf16: "
                      f"{g('SQ_INSTS_MFMA') * 32 * 32 * 16 * 2 / 1e9:.1f} GFLOP issued); busy cycles per instruction "
                      f"{g('SQ_VALU_MFMA_BUSY_CYCLES') / g('SQ_INSTS_MFMA'):.1f}.")
-    if g("GRBM_GUI_ACTIVE") and g("SQ_VALU_MFMA_BUSY_CYCLES"):
-        act = g("GRBM_GUI_ACTIVE") / XCDS
-        util = g("SQ_VALU_MFMA_BUSY_CYCLES") / (SIMDS * act)
-        lines.append(f"* GRBM_GUI_ACTIVE is counted per XCD: {act:,.0f} active cycles per call on each of the {XCDS}.  "
-                     f"Matrix-core busy cycles / ({SIMDS} SIMDs x active cycles) = {100 * util:.1f} % of the chip"
-                     + (f", {100 * util * CUS / args.cus:.1f} % of the {args.cus} compute units of the first launch"
-                        if args.cus != CUS else "") + ".")
+    # Cycles are those in which the kernel's wavefronts are resident: SQ_WAVE_CYCLES counts them per wavefront in units of
+    # four.  (GRBM_GUI_ACTIVE and SQ_BUSY_CYCLES also count what goes on between a dispatch and the next: 11 to 18 and 43 to
+    # 68 million a call for the same kernel, 574 to 582 here.)
+    if g("SQ_WAVE_CYCLES") and g("SQ_VALU_MFMA_BUSY_CYCLES"):
+        simd_cycles = 4 * g("SQ_WAVE_CYCLES") / args.waves_per_simd
+        lines.append(f"* Matrix-core busy cycles / cycles of the SIMDs that hold its wavefronts ({args.waves_per_simd} each; 4 x "
+                     f"SQ_WAVE_CYCLES / {args.waves_per_simd}) = {100 * g('SQ_VALU_MFMA_BUSY_CYCLES') / simd_cycles:.1f} %.")
         if g("SQ_INSTS_LDS"):
             lines.append(f"* LDS instructions per call: {g('SQ_INSTS_LDS'):,.0f} (1 KB operand reads almost all of "
-                         f"them): {g('SQ_INSTS_LDS') * 1024 / (act * args.cus):.0f} bytes per active cycle and "
+                         f"them): {g('SQ_INSTS_LDS') * 1024 / (simd_cycles / 4):.0f} bytes per cycle and "
                          f"compute unit in use; bank conflict cycles {g('SQ_LDS_BANK_CONFLICT'):,.0f}.")
     if g("SQ_WAVE_CYCLES"):
         w = g("SQ_WAVE_CYCLES")

@@ -84,7 +84,7 @@ def main() -> int:
     fetch, write = per_kernel(args.fetch, "FETCH_SIZE"), per_kernel(args.write, "WRITE_SIZE")
     if "copy_bytes_kernel" not in fetch or "copy_bytes_kernel" not in write:
         raise SystemExit("no copy_bytes_kernel dispatch in the counter files")
-    f_copy, w_copy = fetch["copy_bytes_kernel"][0], write["copy_bytes_kernel"][0]
+    f_copy, w_copy = max(fetch["copy_bytes_kernel"]), max(write["copy_bytes_kernel"])   # (side_streams copies a few bytes)
     f_scale, w_scale = args.copy_bytes / f_copy, args.copy_bytes / w_copy   # bytes per counter unit
 
     lines = [f"# HBM traffic per dispatch, {args.workload} (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE)", ""]
