@@ -108,7 +108,7 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib = ctypes.CDLL(path)
     for name, (res, args) in SIGNATURES.items():
         if path != LIB_PATH and not hasattr(lib, name):
-            continue                                   # an older build: a call of what it lacks raises
+            continue               # an older build: a call of what it lacks raises (LayerRunner.step needs actqkv_window_step)
         fn = getattr(lib, name)
         fn.restype, fn.argtypes = res, args
     native = importlib.import_module("._native", __package__)
