@@ -114,7 +114,7 @@ size_t prefill_f32_scratch_most(const actqkv_shape& sh, int batch, int m);
 int launch_attention_prefill_f32(const actqkv_shape& sh, int batch, int m, const void* q, const void* k_cache,
                                  const void* v_cache, int64_t seq_stride, int nb_capacity, const int32_t* n_ctx,
                                  const int32_t* idx, const int32_t* n_sel, int k_cap, void* out, float* lse,
-                                 float* scratch, unsigned int* counters, float scale, int sel_per_head,
+                                 float* scratch, float scale, int sel_per_head,
                                  hipStream_t stream);
 bool decode_fused_supported(const actqkv_shape& sh);
 size_t decode_mfma_scratch_floats(const actqkv_shape& sh, int batch, int k_cap);
@@ -185,7 +185,7 @@ int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, co
                                          ws.counters(), scale, sel_per_head, first_cus, late_cus, stream,
                                          stream_late);
   return launch_attention_prefill_f32(sh, batch, m, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx, idx, n_sel,
-                                      k_cap, out, lse, ws.scratch_f32(), ws.counters(), scale, sel_per_head, stream);
+                                      k_cap, out, lse, ws.scratch_f32(), scale, sel_per_head, stream);
 }
 
 // Host-side checks of an attention call; `need` receives the scratch bytes the call uses.

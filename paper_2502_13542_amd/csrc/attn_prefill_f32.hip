@@ -1,26 +1,32 @@
-// Retrieval attention of a prefill window in fp32 (Sec. 3.1, Eq. (2)): fp32 storage, and fp32
-// products and sums throughout (v_mfma_f32_32x32x2_f32), so nothing is rounded below fp32.
+// Retrieval attention of a prefill window in fp32 (Sec. 3.1, Eq. (2)): fp32 storage, and results as close to the exact
+// ones as fp32 products and sums give them, or closer.
 //
-// What bounds it: the matrix pipe, 256 fp32 operations per clock and compute unit, a sixteenth of
-// its bf16 rate.  Everything else (LDS reads, softmax, loads) is small beside a 64-cycle MFMA, so
-// the kernel is the bf16 one with fewer precautions: a workgroup of 4 wavefronts owns 128 query
-// rows that share a KV head (numbered position by position, the G heads side by side), a
-// wavefront 32 of them; half a block of keys at a time (16 KB of keys, 16 KB of values) goes from
-// memory straight into LDS, double buffered; two workgroups share a compute unit, so each SIMD
-// has a second wavefront for the matrix pipe while the first one is in its softmax.
+// The fp32 matrix instruction does 256 operations per clock and compute unit, a sixteenth of the 16-bit one.  So a value
+// enters as two halves of 11 bits, hi = f16(x f) and lo = f16(x f - hi), f a power of two, and a product as three of the
+// four half products, lo hi + hi lo + hi hi, exact each, summed in fp32 (lo lo is below 2^-24 of the product).
+// f brings the largest magnitude to [2^14, 2^15): per 16 (64 channels) or 8 (128) keys, per query row, and per quarter of the
+// channels of V, so a value 2^15 times smaller than the largest beside it still has all of its 24 bits and a smaller
+// one loses no more than 2^-39 of that largest.  The factor of the keys goes out of the scores with the softmax scale, that
+// of V at the end (it changes only where the magnitudes change, and takes the sums so far along).  Infinite elements
+// cannot be cut in two: where a tile has one its scores are taken again, or its infinite values added, in fp32 products.
+// Relative error against 64 bits, normal inputs, 64 channels: 32 windows of 256 tokens 4.97e-7 (fp32 products 7.65e-7), one
+// such window 2.9e-7 (4.0e-7), one of 4096 tokens 4.95e-7 (7.6e-7); 128 channels, 32 windows 5.2e-7 (8.1e-7).
 //
-// S^T = K Q^T leaves a lane with scores of ONE query (column lane % 32), and register r of lane
-// half h holds key 8 (r / 4) + 4 h + r % 4 of a 32-key group.  An MFMA of O^T += V^T P^T takes one
-// key from either half, so register r of both halves IS its B operand, without a conversion or a
-// lane exchange; its A operand is the same key pair of the V^T row, four keys per 16-byte LDS read.
-// The channels of the first product are dealt to the halves four at a time for the same reason.
+// A workgroup of 4 wavefronts owns 128 query rows that share a KV head (numbered position by position, the G heads side
+// by side), a wavefront 32 of them.  A tile is 4096 / D keys, 16 KB of keys and 16 KB of values: every wavefront brings a
+// quarter of each into registers a tile ahead, and cuts it into halves in LDS (double buffered) once its own products with
+// the tile before are out.  Two workgroups share a compute unit, so a SIMD has a second wavefront while the first is in
+// its softmax.  What bounds it: vector instructions (about 440 for 48 matrix ones per tile and wavefront; 70 % of the cycles
+// issue one, the matrix pipe is busy 40 %).
 //
-// A single window has few query tiles; then the key tiles are cut into pieces, one workgroup
-// each, and the workgroup that finishes last among the pieces of a query tile merges them.
-// A pass over 8192 tokens, windows of 256, 8 query and 2 KV heads of 64 channels: the attention
-// takes 244 us (96 TFLOP/s of the 153 a large fp32 product reaches), against 1645 us as one thread
-// per query row; what is left of the gap is that all its workgroups are resident at once and the
-// first windows see fewer keys.
+// S^T = K Q^T leaves a lane with scores of ONE query (column lane % 32).  Bits 2 and 3 of a key's number within 16 change
+// places on the way into the first product, so that register i of lane half h holds key 16 (i / 8) + 8 h + i % 8 of a
+// 32-key group: 8 registers are the B operand of a 16-key step of O^T += V^T P^T, without a lane exchange.
+//
+// A single window has few query tiles; then the key tiles are cut into pieces, one workgroup each, which a second launch
+// merges.  64 channels, 8 query and 2 KV heads, 8 blocks retrieved, against fp32 products with the merge in the last
+// workgroup: 32 windows of 256 tokens 245 -> 118 us, one of them 57 -> 19.4, of 4096 tokens 313 -> 136; 128 channels, 32
+// windows 460 -> 215.
 #include <algorithm>
 #include <mutex>
 
@@ -32,12 +38,18 @@ namespace actqkv {
 constexpr int kFfThreads = 256;
 constexpr int kFfWaves = 4;
 constexpr int kFfRows = 32 * kFfWaves;            // query rows of a workgroup
-constexpr int kFfTileBytes = 16384;               // K or V^T of a tile
-constexpr int kFfLdsBytes = 2 * 2 * kFfTileBytes; // 2 stages x (K, V^T)
+constexpr int kFfHalf = 8192;                     // one half (hi or lo) of K or V^T of a tile
+constexpr int kFfStageBytes = 4 * kFfHalf;
+constexpr int kFfLdsBytes = 2 * kFfStageBytes;
+constexpr int kFfLazy = 8;                        // see the running maximum
+constexpr int kFfTop = 14;                        // factors bring magnitudes up to [2^14, 2^15)
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 // Workgroups of a full launch: two per compute unit; with 128 channels a little less, so that their
 // partial results fit the library's own scratch array.
 template <int D> constexpr int kFfSlots = D == 64 ? 512 : 480;
-template <int D> constexpr size_t kFfPieceBytes = size_t(kFfWaves) * (D / 4 + 1) * 64 * 8;
+template <int D> constexpr size_t kFfPieceBytes = size_t(kFfWaves) * (D / 2 + 2) * 64 * 4;
 static_assert(kFfSlots<128> * kFfPieceBytes<128> + kCounterBytes <= ACTQKV_STATIC_SCRATCH_BYTES, "partial results");
 constexpr int kFfMaxSplits = 8;
 
@@ -53,45 +65,83 @@ struct FfParams {
   int k_cap;
   float* out;
   float* lse;
-  uint64_t* part;          // [workgroup][wavefront][D / 4 pairs of O | (max, sum)][64 lanes]
-  unsigned int* counters;  // one ticket counter per (sequence, query tile, KV head), zero between launches
+  float* part;             // [query tile and KV head][piece][wavefront][D / 8 x 4 of O | (max, sum)][64 lanes]
   int m, n_q_heads, n_kv_heads, n_init, n_local, n_qtiles, splits;
+  int per_chip;            // query tiles whose workgroups make one for every compute unit
   int sel_per_head;
   float scale_log2e;
 };
 
-// Final normalisation and store of one lane's share of a query row.
+// Two fp32 values times a power of two -> the packed halves hi (rounded) and lo (what the rounding left, rounded).
+__device__ __forceinline__ void ff_split(float x0, float x1, float scale, uint32_t& hi, uint32_t& lo) {
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(x0), "v"(scale));
+  asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(x1), "v"(scale));
+  asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(x0), "v"(scale), "v"(hi));
+  asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(x1), "v"(scale), "v"(hi));
+}
+// The same without a factor (the first half of the work is one conversion for both).
+__device__ __forceinline__ void ff_split(float x0, float x1, uint32_t& hi, uint32_t& lo) {
+  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x0, x1}, f16x2));
+  asm("v_fma_mixlo_f16 %0, %1, 1.0, -%2 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(x0), "v"(hi));
+  asm("v_fma_mixhi_f16 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(x1), "v"(hi));
+}
+__device__ __forceinline__ f16x8 ff_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
+__device__ __forceinline__ float ff_pow2(int e) { return __uint_as_float(uint32_t(e + 127) << 23); }   // -126 <= e <= 127
+__device__ __forceinline__ int ff_exponent(float x) { return int(__float_as_uint(x) >> 23) - 127; }     // of x >= 0
+constexpr float kFfMax = 3.4028235e38f, kFfMin = 1.17549435e-38f;
+// The power of two that takes values of at most mx into [2^14, 2^15), 2^100 at most.
+__device__ __forceinline__ int ff_fit(float mx) { return min(kFfTop - ff_exponent(mx), 100); }
+
+// What wavefront `wave` of piece `split` of a (query tile, KV head) leaves: D / 2 floats of output per lane, then (max, sum).
 template <int D>
-__device__ __forceinline__ void ff_store_row(const FfParams& p, const f32x16 (&acc_o)[D / 32], float m_run, float l_tot,
-                                             int s, int row, int head, int half) {
+__device__ __forceinline__ float* ff_piece(const FfParams& p, int item, int split, int wave) {
+  return p.part + ((size_t(item) * p.splits + split) * kFfWaves + wave) * ((D / 2 + 2) * 64);
+}
+
+// Final normalisation and store of one lane's share of a query row.  unit[u]: what block u of the accumulators
+// (D / 4 channels) has to be multiplied by.
+template <int D>
+__device__ __forceinline__ void ff_store_row(const FfParams& p, const f32x16 (&acc_o)[D / 32], const float (&unit)[4],
+                                             float m_run, float l_tot, int s, int row, int head, int half) {
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   float* op = p.out + ((size_t(s) * p.m + row) * p.n_q_heads + head) * D + 4 * half;
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j) {
+      const float f = unit[(db * 32 + 8 * j) / (D / 4)] * inv;
       *reinterpret_cast<f32x4*>(op + db * 32 + 8 * j) =
-          f32x4{acc_o[db][4 * j] * inv, acc_o[db][4 * j + 1] * inv, acc_o[db][4 * j + 2] * inv, acc_o[db][4 * j + 3] * inv};
+          f32x4{acc_o[db][4 * j] * f, acc_o[db][4 * j + 1] * f, acc_o[db][4 * j + 2] * f, acc_o[db][4 * j + 3] * f};
+    }
   if (p.lse != nullptr && half == 0)
     p.lse[(size_t(s) * p.n_q_heads + head) * p.m + row] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
 }
 
 template <int D>
 __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParams p) {
-  constexpr int kKeys = kFfTileBytes / (4 * D);     // keys of a tile: 64 or 32
+  constexpr int kKeys = 4096 / D;                   // keys of a tile: 64 or 32
   constexpr int kPerBlock = kBlock / kKeys;
-  constexpr int kG = kKeys / 32, kDb = D / 32, kQ = D / 8;
-  constexpr uint32_t kKRow = D * 4, kVRow = kKeys * 4;   // bytes of a K / V^T row in LDS
-  extern __shared__ __attribute__((aligned(16))) char ff_lds[];
+  constexpr int kG = kKeys / 32, kDb = D / 32, kQ = D / 16;
+  constexpr uint32_t kKRow = D * 2, kVRow = kKeys * 2;   // bytes of a K / V^T row in one of its two halves in LDS
+  extern __shared__ __attribute__((aligned(16))) char ff_lds[];   // [stage][K hi, K lo, V^T hi, V^T lo]
+  __shared__ float factors[2][2][4];                // [stage][K: what scores are multiplied by, V: what values were][wavefront]
   __shared__ int32_t idx_lds[64];
-  __shared__ int last_flag;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, half = lane >> 5;
   const int group = p.n_q_heads / p.n_kv_heads;
   // consecutive workgroups differ in the KV head (they go round the XCDs: a head's tiles stay in few L2s)
   const int hk = blockIdx.x % p.n_kv_heads, rest = blockIdx.x / p.n_kv_heads;
   const int split = rest % p.splits, qt = rest / p.splits;
-  const int qtile = qt % p.n_qtiles, s = qt / p.n_qtiles;
+  const int s = qt / p.n_qtiles;
+  int qtile = qt % p.n_qtiles;
+  // The last rows of a window see up to a window more keys than the first: the two workgroups that share a compute unit
+  // (per_chip query tiles apart) take them in opposite orders.  32 windows of 256 tokens 123.5 -> 116.5 us.
+  if (p.per_chip >= p.n_qtiles) {
+    if ((s * p.n_qtiles / p.per_chip) & 1) qtile = p.n_qtiles - 1 - qtile;
+  } else {
+    const int turn = qtile / p.per_chip;
+    if ((turn & 1) && (turn + 1) * p.per_chip <= p.n_qtiles) qtile = (2 * turn + 1) * p.per_chip - 1 - qtile;
+  }
 
   const size_t sel_row = p.sel_per_head ? size_t(s) * p.n_kv_heads + hk : size_t(s);
   const int32_t my_idx = tid < p.k_cap ? p.idx[sel_row * p.k_cap + tid] : -1;
@@ -116,206 +166,402 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
   const int my_row = frow / group, head = hk * group + (frow - my_row * group);
   const int my_pos = g.w0 + my_row;
 
-  f32x4 qreg[kQ];                                            // channels 8 j + 4 half .. + 3 of this lane's query
-  {
-    const float* qp = p.q + ((size_t(s) * p.m + my_row) * p.n_q_heads + head) * D + 4 * half;
+  // ---- tiles: a wavefront brings a quarter of the rows of K and of V^T into registers, 4 x 1 KB each
+  constexpr int kKPer = 1024 / (4 * D), kVPer = 1024 / (4 * kKeys);   // rows of 1 KB in memory
+  const int kc = lane % (64 / kKPer), vc = lane % (64 / kVPer);       // 16-byte piece of a row
+  const int kr0 = wave * (kKeys / 4) + lane / (64 / kKPer), vr0 = wave * (D / 4) + lane / (64 / kVPer);
+  const uint32_t gk = uint32_t(kr0) * (4 * D) + kc * 16, gv = uint32_t(vr0) * (4 * kBlock) + vc * 16;
+  // LDS rows are split into 16-byte chunks, XOR-swizzled with a key made of the row so that 16 rows that
+  // are read together hit all banks.
+  auto k_key = [](int r) { return uint32_t(D == 64 ? (r >> 1) & 7 : r & 15); };
+  auto v_key = [](int r) { return uint32_t(D == 64 ? (r >> 1) & 7 : (r >> 2) & 3); };
+  uint32_t wk[4], wv[4];                                     // where this lane's pieces go in a half
 #pragma unroll
-    for (int j = 0; j < kQ; ++j) qreg[j] = *reinterpret_cast<const f32x4*>(qp + 8 * j);
+  for (int i = 0; i < 4; ++i) {
+    const int kr = kr0 + i * kKPer, vr = vr0 + i * kVPer;
+    wk[i] = uint32_t(kr) * kKRow + ((uint32_t(kc >> 1) ^ k_key(kr)) << 4) + 8 * (kc & 1);
+    wv[i] = uint32_t(vr) * kVRow + ((uint32_t(vc >> 1) ^ v_key(vr)) << 4) + 8 * (vc & 1);
+  }
+  const char* kbase = reinterpret_cast<const char*>(p.k_cache + size_t(s) * p.seq_stride);
+  const char* vbase = reinterpret_cast<const char*>(p.v_cache + size_t(s) * p.seq_stride);
+  constexpr uint32_t kBlockBytes = uint32_t(kBlock) * D * 4;
+  struct Tile { int key0, lo, hi; };                         // first key, and the visible span within the tile
+  auto tile_at = [&](int t) {
+    int block, lo, hi;
+    tl.get(t / kPerBlock, block, lo, hi);
+    const int key0 = block * kBlock + (t % kPerBlock) * kKeys;
+    return Tile{__builtin_amdgcn_readfirstlane(key0), __builtin_amdgcn_readfirstlane(max(lo, key0)),
+                __builtin_amdgcn_readfirstlane(min(hi, key0 + kKeys))};
+  };
+  auto block_offset = [&](int key0) { return (size_t(key0 / kBlock) * p.n_kv_heads + hk) * kBlockBytes; };
+  f32x4 xk[4], xv[4];                                        // a tile on its way
+  auto fetch_tile = [&](const Tile& t) {
+    const size_t off = block_offset(t.key0);
+    const int k0 = t.key0 % kBlock;
+    const char* kp = kbase + off + size_t(k0) * (4 * D) + gk;
+    const char* vp = vbase + off + size_t(k0) * 4 + gv;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      xk[i] = *reinterpret_cast<const f32x4*>(kp + i * 1024);
+      xv[i] = *reinterpret_cast<const f32x4*>(vp + i * kVPer * (4 * kBlock));
+    }
+  };
+  int v_exp = 100, v_low = 1000;                             // this wavefront's values go in times 2^v_exp; the least so far
+  auto largest = [](const f32x4 (&x)[4]) {                   // magnitude, over the wavefront (NaN is passed over)
+    float mx = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; j += 2) mx = fmaxf(fmaxf(fabsf(x[i][j]), fabsf(x[i][j + 1])), mx);
+    return __uint_as_float(wave_max_u32(__float_as_uint(mx)));
+  };
+  // the tile in registers -> LDS, as halves; keys that no row of the workgroup sees count as zeros
+  auto store_tile = [&](const Tile& t, int stage) {
+    if (t.lo > t.key0 || t.hi < t.key0 + kKeys) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int kp = t.key0 + kr0 + i * kKPer, vp = t.key0 + 4 * vc;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          xk[i][j] = kp >= t.lo && kp < t.hi ? xk[i][j] : 0.f;
+          xv[i][j] = vp + j >= t.lo && vp + j < t.hi ? xv[i][j] : 0.f;
+        }
+      }
+    }
+    char* dst = ff_lds + stage * kFfStageBytes;
+    const float k_mx = largest(xk);
+    float v_mx = largest(xv);
+    const bool k_inf = !(k_mx <= kFfMax), v_inf = !(v_mx <= kFfMax);
+    if (__builtin_expect(v_inf, 0)) {                        // the finite ones; the infinite ones are added by the reader
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) xv[i][j] = isinf(xv[i][j]) ? 0.f : xv[i][j];
+      v_mx = largest(xv);
+    }
+    const int k_exp = ff_fit(k_mx);
+    {
+      // the factor of the values stays as it is while the largest of them comes to lie in [2^4, 2^15); it is raised
+      // by no more than keeps the sums of before in range
+      const int at = ff_exponent(v_mx) + v_exp;
+      if (v_mx > 0.f && (at > kFfTop || at < 4)) {
+        v_exp = min(min(kFfTop - 2 - (at - v_exp), 100), v_low + 60);
+        v_low = min(v_low, v_exp);
+      }
+    }
+    const float kf = ff_pow2(k_inf ? 0 : k_exp), vf = ff_pow2(v_exp);
+    if (lane == 0) {
+      factors[stage][0][wave] = k_inf ? -1.f : ff_pow2(-k_exp);
+      factors[stage][1][wave] = v_inf ? -vf : vf;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t h0, h1, l0, l1;
+      ff_split(xk[i][0], xk[i][1], kf, h0, l0);
+      ff_split(xk[i][2], xk[i][3], kf, h1, l1);
+      *reinterpret_cast<u32x2*>(dst + wk[i]) = u32x2{h0, h1};
+      *reinterpret_cast<u32x2*>(dst + kFfHalf + wk[i]) = u32x2{l0, l1};
+      ff_split(xv[i][0], xv[i][1], vf, h0, l0);
+      ff_split(xv[i][2], xv[i][3], vf, h1, l1);
+      *reinterpret_cast<u32x2*>(dst + 2 * kFfHalf + wv[i]) = u32x2{h0, h1};
+      *reinterpret_cast<u32x2*>(dst + 3 * kFfHalf + wv[i]) = u32x2{l0, l1};
+    }
+  };
+
+  Tile now{0, 0, 0}, next{0, 0, 0};
+  if (t_begin < t_end) {
+    now = tile_at(t_begin);
+    fetch_tile(now);
+  }
+  // ---- the queries: channels 16 j + 8 half .. + 7 of this lane's row, as halves of their multiples by 2^q_exp
+  const float* qrow = p.q + ((size_t(s) * p.m + my_row) * p.n_q_heads + head) * D;
+  u32x4 qh[kQ], ql[kQ];
+  float q_unit;                                              // scores times this are in units of log2
+  bool q_inf;
+  {
+    f32x4 x[2 * kQ];
+    float mx = 0.f;
+#pragma unroll
+    for (int j = 0; j < kQ; ++j) {
+      x[2 * j] = *reinterpret_cast<const f32x4*>(qrow + 16 * j + 8 * half);
+      x[2 * j + 1] = *reinterpret_cast<const f32x4*>(qrow + 16 * j + 8 * half + 4);
+    }
+#pragma unroll
+    for (int j = 0; j < 2 * kQ; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) mx = fmaxf(fmaxf(fabsf(x[j][i]), fabsf(x[j][i + 1])), mx);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    q_inf = __any(!(mx <= kFfMax));
+    const int e = mx <= kFfMax ? ff_fit(mx) : 0;
+    const float f = ff_pow2(e);
+    q_unit = p.scale_log2e * ff_pow2(-e);
+#pragma unroll
+    for (int j = 0; j < kQ; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t h, l;
+        ff_split(x[2 * j + (i >> 1)][2 * (i & 1)], x[2 * j + (i >> 1)][2 * (i & 1) + 1], f, h, l);
+        qh[j][i] = h;
+        ql[j][i] = l;
+      }
   }
   f32x16 acc_o[kDb];
 #pragma unroll
   for (int i = 0; i < kDb; ++i)
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc_o[i][j] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;                      // running max (log2 units), this lane's share of the sum
+  float v_in[4] = {1.f, 1.f, 1.f, 1.f};                      // acc_o holds sums of values times this
+  float m_run = -INFINITY, l_run = 0.f;                      // reference of the exponents (log2 units, the rows' maximum or close below), this lane's share of the sum
 
-  // LDS rows are split into 16-byte chunks, XOR-swizzled with a key made of the row so that 16
-  // consecutive rows hit all banks: row % 16, or (row / 2) % 8 where two rows span the banks.
-  auto k_key = [](int r) { return uint32_t(r & 15); };
-  auto v_key = [](int r) { return uint32_t(kVRow == 256 ? r & 15 : (r >> 1) & 7); };
-  constexpr int kKPer = 1024 / kKRow, kVPer = 1024 / kVRow;  // rows of a 1 KB piece (a wavefront's load)
-  uint32_t gk[4], gv[4];                                     // byte offsets of this lane's loads inside a block's tile
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int kr = (4 * wave + i) * kKPer + lane / (64 / kKPer), kc = lane % (64 / kKPer);
-    gk[i] = uint32_t(kr) * kKRow + ((uint32_t(kc) ^ k_key(kr)) << 4);
-    const int vr = (4 * wave + i) * kVPer + lane / (64 / kVPer), vc = lane % (64 / kVPer);
-    gv[i] = uint32_t(vr) * (kBlock * 4) + ((uint32_t(vc) ^ v_key(vr)) << 4);
-  }
-  const char* kbase = reinterpret_cast<const char*>(p.k_cache + size_t(s) * p.seq_stride);
-  const char* vbase = reinterpret_cast<const char*>(p.v_cache + size_t(s) * p.seq_stride);
-  auto tile_at = [&](int t, int& key0, int& lo, int& hi) {   // first key, and the visible span within the tile
-    int block;
-    tl.get(t / kPerBlock, block, lo, hi);
-    key0 = block * kBlock + (t % kPerBlock) * kKeys;
-    lo = max(lo, key0);
-    hi = min(hi, key0 + kKeys);
-    key0 = __builtin_amdgcn_readfirstlane(key0);
-    lo = __builtin_amdgcn_readfirstlane(lo);
-    hi = __builtin_amdgcn_readfirstlane(hi);
-  };
-  auto fetch_tile = [&](int key0, int stage) {
-    constexpr uint32_t kBlockBytes = uint32_t(kBlock) * D * 4;
-    const int block = key0 / kBlock, k0 = key0 % kBlock;
-    const size_t off = (size_t(block) * p.n_kv_heads + hk) * kBlockBytes;
-    const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kbase + off), 0, kBlockBytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vbase + off), 0, kBlockBytes, 0x00020000);
-    char* dst = ff_lds + stage * 2 * kFfTileBytes + wave * 4096;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (__attribute__((address_space(3))) void*)(dst + i * 1024), 16, gk[i], k0 * kKRow, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (__attribute__((address_space(3))) void*)(dst + kFfTileBytes + i * 1024), 16, gv[i], k0 * 4, 0, 0);
-    }
-  };
-
-  int key0 = 0, lo = 0, hi = 0;
   if (t_begin < t_end) {
-    tile_at(t_begin, key0, lo, hi);
-    fetch_tile(key0, 0);
+    store_tile(now, 0);
+    if (t_begin + 1 < t_end) {
+      next = tile_at(t_begin + 1);
+      fetch_tile(next);
+    }
   }
-  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
+  const int kn = (n & 0x13) | ((n & 4) << 1) | ((n & 8) >> 1);   // the key of this lane's row in the first product
   for (int t = t_begin; t < t_end; ++t) {
     const int stage = (t - t_begin) & 1;
-    int key_next = 0, lo_next = 0, hi_next = 0;
-    if (t + 1 < t_end) tile_at(t + 1, key_next, lo_next, hi_next);
+    const int key0 = now.key0, lo = now.lo, hi = now.hi;
     // the wavefront skips tiles none of its rows can see; it masks tiles that are clipped or reach
     // past its first row's position
     const bool visible = wave_ok && hi > lo && lo <= wpos_hi;
     const bool masked = lo > key0 || hi < key0 + kKeys || hi - 1 > wpos_lo;
-    const char* ks_ = ff_lds + stage * 2 * kFfTileBytes;
-    const char* vs_ = ks_ + kFfTileBytes;
-    f32x16 acc_s[kG];
+    const char* ks_ = ff_lds + stage * kFfStageBytes;
+    const char* vs_ = ks_ + 2 * kFfHalf;
     if (visible) {
+      f32x16 acc_s[kG];
+      float unit[2 * kG];                                    // per 16 keys
+      bool k_inf = q_inf;
+#pragma unroll
+      for (int b = 0; b < 2 * kG; ++b) {
+        const float f = factors[stage][0][D == 64 ? b : 2 * b + half];
+        k_inf |= __any(f < 0.f);
+        unit[b] = __builtin_amdgcn_fmed3f(q_unit * f, kFfMin, kFfMax);
+      }
 #pragma unroll
       for (int gg = 0; gg < kG; ++gg)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc_s[gg][i] = 0.f;
+      f16x8 kh[2][kG], kl[2][kG];                            // a step's operands are requested a step ahead
+      auto read_k = [&](int j) {
+#pragma unroll
+        for (int gg = 0; gg < kG; ++gg) {
+          const char* at = ks_ + uint32_t(gg * 32 + kn) * kKRow + ((uint32_t(2 * j + half) ^ k_key(kn)) << 4);
+          kh[j & 1][gg] = ff_f16x8(*reinterpret_cast<const u32x4*>(at));
+          kl[j & 1][gg] = ff_f16x8(*reinterpret_cast<const u32x4*>(at + kFfHalf));
+        }
+      };
+      read_k(0);
 #pragma unroll
       for (int j = 0; j < kQ; ++j) {
-        f32x4 ka[kG];
+        if (j + 1 < kQ) read_k(j + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int gg = 0; gg < kG; ++gg) acc_s[gg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl[j & 1][gg], ff_f16x8(qh[j]), acc_s[gg], 0, 0, 0);
+#pragma unroll
+        for (int gg = 0; gg < kG; ++gg) acc_s[gg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[j & 1][gg], ff_f16x8(ql[j]), acc_s[gg], 0, 0, 0);
+#pragma unroll
+        for (int gg = 0; gg < kG; ++gg) acc_s[gg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[j & 1][gg], ff_f16x8(qh[j]), acc_s[gg], 0, 0, 0);
+      }
+      if (__builtin_expect(k_inf, 0)) {
+        // an infinite key or query: the scores anew in fp32 products, from memory
 #pragma unroll
         for (int gg = 0; gg < kG; ++gg)
-          ka[gg] = *reinterpret_cast<const f32x4*>(ks_ + uint32_t(gg * 32 + n) * kKRow + ((uint32_t(2 * j + half) ^ k_key(n)) << 4));
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+          for (int i = 0; i < 16; ++i) acc_s[gg][i] = 0.f;
+        const float* kt = reinterpret_cast<const float*>(kbase + block_offset(key0)) + size_t(key0 % kBlock + kn) * D + half;
+#pragma unroll 1
+        for (int c = 0; c < D; c += 2)
 #pragma unroll
           for (int gg = 0; gg < kG; ++gg)
-            acc_s[gg] = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[gg][i], qreg[j][i], acc_s[gg], 0, 0, 0);
+            acc_s[gg] = __builtin_amdgcn_mfma_f32_32x32x2f32(kt[gg * 32 * D + c], qrow[c + half], acc_s[gg], 0, 0, 0);
+#pragma unroll
+        for (int b = 0; b < 2 * kG; ++b) unit[b] = p.scale_log2e;
       }
-    }
-    // (the next tile is requested behind the score reads: see attn_prefill_mfma.hip)
-    if (t + 1 < t_end) fetch_tile(key_next, stage ^ 1);
-    if (visible) {
       if (masked) {
 #pragma unroll
         for (int gg = 0; gg < kG; ++gg)
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
-            const int kp = key0 + gg * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
+            const int kp = key0 + gg * 32 + 16 * (i >> 3) + 8 * half + (i & 7);
             const bool ok = kp >= lo && kp < hi && kp <= my_pos;
             acc_s[gg][i] = ok ? acc_s[gg][i] : -INFINITY;
           }
       }
-      float mx = acc_s[0][0];
+      float mx = -INFINITY;
 #pragma unroll
-      for (int gg = 0; gg < kG; ++gg)
+      for (int b = 0; b < 2 * kG; ++b) {
+        float bm = acc_s[b >> 1][8 * (b & 1)];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc_s[gg][i]);
+        for (int i = 1; i < 8; ++i) bm = fmaxf(bm, acc_s[b >> 1][8 * (b & 1) + i]);
+        mx = fmaxf(mx, bm * unit[b]);
+      }
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m_run, mx * p.scale_log2e);
-      const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
-      m_run = m_new;
-      if (!__all(alpha == 1.f)) {
+      // the reference follows the maximum only when that has grown by more than 2^kFfLazy, as a rule in the first tiles
+      // (every lane takes the same branch: 32 rows have a new maximum in nearly every tile)
+      if (!__all(mx <= m_run + kFfLazy)) {
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
+        m_run = m_new;
 #pragma unroll
         for (int db = 0; db < kDb; ++db)
 #pragma unroll
           for (int i = 0; i < 16; ++i) acc_o[db][i] *= alpha;
         l_run *= alpha;
       }
-      float psum = 0.f;
+      const float shift = kFfTop - kFfLazy - (m_run == -INFINITY ? 0.f : m_run);
+      float v_now[4];
+      bool v_inf = false, same = true;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float f = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(factors[stage][1][u])));
+        v_inf |= f < 0.f;
+        v_now[u] = fabsf(f);
+        same &= v_now[u] == v_in[u];
+      }
+      if (!same) {                                           // wave-uniform
+#pragma unroll
+        for (int db = 0; db < kDb; ++db)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int u = (db * 32 + 8 * j) / (D / 4);
+            const float grow = v_now[u] / v_in[u];
+#pragma unroll
+            for (int i = 4 * j; i < 4 * j + 4; ++i) acc_o[db][i] *= grow;
+          }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v_in[u] = v_now[u];
+      }
+      float psum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int gg = 0; gg < kG; ++gg)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          acc_s[gg][i] = __builtin_amdgcn_exp2f(fmaf(acc_s[gg][i], p.scale_log2e, -m_safe));
-          psum += acc_s[gg][i];
+          acc_s[gg][i] = __builtin_amdgcn_exp2f(fmaf(acc_s[gg][i], unit[2 * gg + (i >> 3)], shift));
+          psum[i & 3] += acc_s[gg][i];
         }
-      l_run += psum;
+      l_run += (psum[0] + psum[1]) + (psum[2] + psum[3]);
 #pragma unroll
-      for (int gg = 0; gg < kG; ++gg)
+      for (int st = 0; st < 2 * kG; ++st) {
+        f16x8 vh[kDb], vl[kDb];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          f32x4 va[kDb];
-#pragma unroll
-          for (int db = 0; db < kDb; ++db)
-            va[db] = *reinterpret_cast<const f32x4*>(vs_ + uint32_t(db * 32 + n) * kVRow + ((uint32_t(gg * 8 + 2 * j + half) ^ v_key(n)) << 4));
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int db = 0; db < kDb; ++db)
-              acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[db][i], acc_s[gg][4 * j + i], acc_o[db], 0, 0, 0);
+        for (int db = 0; db < kDb; ++db) {
+          const char* at = vs_ + uint32_t(db * 32 + n) * kVRow + ((uint32_t(2 * st + half) ^ v_key(n)) << 4);
+          vh[db] = ff_f16x8(*reinterpret_cast<const u32x4*>(at));
+          vl[db] = ff_f16x8(*reinterpret_cast<const u32x4*>(at + kFfHalf));
         }
+        u32x4 ph, pl;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint32_t h, l;
+          ff_split(acc_s[st >> 1][8 * (st & 1) + 2 * i], acc_s[st >> 1][8 * (st & 1) + 2 * i + 1], h, l);
+          ph[i] = h;
+          pl[i] = l;
+        }
+#pragma unroll
+        for (int db = 0; db < kDb; ++db) acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl[db], ff_f16x8(ph), acc_o[db], 0, 0, 0);
+#pragma unroll
+        for (int db = 0; db < kDb; ++db) acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh[db], ff_f16x8(pl), acc_o[db], 0, 0, 0);
+#pragma unroll
+        for (int db = 0; db < kDb; ++db) acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh[db], ff_f16x8(ph), acc_o[db], 0, 0, 0);
+      }
+      if (__builtin_expect(v_inf, 0)) {
+        // infinite values went in as zeros; their products in fp32, from memory
+        const float* vt = reinterpret_cast<const float*>(vbase + block_offset(key0)) + size_t(n) * kBlock + key0 % kBlock;
+#pragma unroll
+        for (int gg = 0; gg < kG; ++gg)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int k = gg * 32 + 16 * (i >> 3) + 8 * half + (i & 7);
+            const bool seen = key0 + k >= lo && key0 + k < hi;
+#pragma unroll
+            for (int db = 0; db < kDb; ++db) {
+              const float x = vt[db * 32 * kBlock + k];
+              acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(seen && isinf(x) ? x : 0.f, acc_s[gg][i], acc_o[db], 0, 0, 0);
+            }
+          }
+      }
     }
-    key0 = key_next;
-    lo = lo_next;
-    hi = hi_next;
-    __builtin_amdgcn_s_waitcnt(0);   // this wavefront's pieces of the next tile have landed in LDS
+    if (t + 1 < t_end) {
+      store_tile(next, stage ^ 1);
+      now = next;
+      if (t + 2 < t_end) {
+        next = tile_at(t + 2);
+        fetch_tile(next);
+      }
+    }
     __syncthreads();
   }
 
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  const float l_tot = (l_run + __shfl_xor(l_run, 32, 64)) * ff_pow2(kFfLazy - kFfTop);
+  float unit[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) unit[u] = ff_pow2(kFfLazy - kFfTop) / v_in[u];
   if (p.splits == 1) {
-    if (row_ok) ff_store_row<D>(p, acc_o, m_run, l_tot, s, my_row, head, half);
+    if (row_ok) ff_store_row<D>(p, acc_o, unit, m_run, l_tot, s, my_row, head, half);
     return;
   }
   // ---- a piece stores its unnormalised output in the order the registers hold it, plus its max and sum
-  constexpr int kWords = D / 4 + 1;                          // 64-bit words per lane
-  const size_t pieces0 = (size_t(qt) * p.n_kv_heads + hk) * p.splits;
-  uint64_t* mine = p.part + ((pieces0 + split) * kFfWaves + wave) * (kWords * 64) + lane;
-  auto pack = [](float a, float b) { return uint64_t(__float_as_uint(a)) | (uint64_t(__float_as_uint(b)) << 32); };
+  float* mine = ff_piece<D>(p, (s * p.n_qtiles + qtile) * p.n_kv_heads + hk, split, wave);
 #pragma unroll
   for (int db = 0; db < kDb; ++db)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) st_agent(mine + (db * 8 + i) * 64, pack(acc_o[db][2 * i], acc_o[db][2 * i + 1]));
-  st_agent(mine + (kWords - 1) * 64, pack(m_run, l_tot));
-  if (!last_of_group(p.counters + size_t(qt) * p.n_kv_heads + hk, unsigned(p.splits), &last_flag)) return;
-  // ---- the last piece to finish merges them, in piece order:
-  //   out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s
-  const uint64_t* piece0 = p.part + (pieces0 * kFfWaves + wave) * (kWords * 64) + lane;
-  constexpr size_t kPieceStride = size_t(kFfWaves) * kWords * 64;
-  uint64_t ml[kFfMaxSplits];
+    for (int j = 0; j < 4; ++j) {
+      const float f = unit[(db * 32 + 8 * j) / (D / 4)];
+      *reinterpret_cast<f32x4*>(mine + ((db * 4 + j) * 64 + lane) * 4) =
+          f32x4{acc_o[db][4 * j] * f, acc_o[db][4 * j + 1] * f, acc_o[db][4 * j + 2] * f, acc_o[db][4 * j + 3] * f};
+    }
+  *reinterpret_cast<f32x2*>(mine + (D / 2) * 64 + lane * 2) = f32x2{m_run, l_tot};
+}
+
+// The pieces of a query tile, in their order:  out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
+// grid (4 wavefronts' rows of every query tile and KV head); a wavefront here takes a quarter of the channels of the
+// 32 rows.  A launch of its own: the last of 8 pieces to finish needed 31 us to read the others' 256 KB back (one
+// compute unit gets 8 GB/s of coherent 8-byte loads), a window of 256 tokens 50 us, as two launches 19.4.
+template <int D>
+__global__ __launch_bounds__(256) void attn_prefill_f32_merge_kernel(FfParams p) {
+  constexpr int kSlots = D / 32;                             // 16-byte groups of a lane here
+  const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+  const int n = lane & 31, half = lane >> 5, group = p.n_q_heads / p.n_kv_heads;
+  const int wave = blockIdx.x % kFfWaves, item = blockIdx.x / kFfWaves;
+  const int hk = item % p.n_kv_heads, qt = item / p.n_kv_heads, qtile = qt % p.n_qtiles, s = qt / p.n_qtiles;
+  const int frow = qtile * kFfRows + wave * 32 + n;
+  f32x2 ml[kFfMaxSplits];
+  f32x4 o[kFfMaxSplits][kSlots];
 #pragma unroll
-  for (int i = 0; i < kFfMaxSplits; ++i)
-    ml[i] = i < p.splits ? ld_agent(piece0 + i * kPieceStride + (kWords - 1) * 64) : pack(-INFINITY, 0.f);
-  float m_all = -INFINITY;
+  for (int i = 0; i < kFfMaxSplits; ++i) {                   // all loads first: they overlap
+    const float* piece = ff_piece<D>(p, item, min(i, p.splits - 1), wave);
+    ml[i] = *reinterpret_cast<const f32x2*>(piece + (D / 2) * 64 + lane * 2);
 #pragma unroll
-  for (int i = 0; i < kFfMaxSplits; ++i) m_all = fmaxf(m_all, __uint_as_float(uint32_t(ml[i])));
+    for (int k = 0; k < kSlots; ++k) o[i][k] = *reinterpret_cast<const f32x4*>(piece + ((part * kSlots + k) * 64 + lane) * 4);
+  }
+  float m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+  for (int i = 0; i < kFfMaxSplits; ++i) m_all = fmaxf(m_all, i < p.splits ? ml[i].x : -INFINITY);
   const float m_safe = m_all == -INFINITY ? 0.f : m_all;
-  float l_all = 0.f;
+  f32x4 sum[kSlots];
 #pragma unroll
-  for (int db = 0; db < kDb; ++db)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc_o[db][i] = 0.f;
+  for (int k = 0; k < kSlots; ++k) sum[k] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int i = 0; i < kFfMaxSplits; ++i) {
     if (i < p.splits) {
-      uint64_t raw[kWords - 1];
+      const float w = __builtin_amdgcn_exp2f(ml[i].x - m_safe);
+      l_all += w * ml[i].y;
 #pragma unroll
-      for (int k = 0; k < kWords - 1; ++k) raw[k] = ld_agent(piece0 + i * kPieceStride + k * 64);
-      const float w = __builtin_amdgcn_exp2f(__uint_as_float(uint32_t(ml[i])) - m_safe);
-      l_all += w * __uint_as_float(uint32_t(ml[i] >> 32));
-#pragma unroll
-      for (int db = 0; db < kDb; ++db)
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          acc_o[db][2 * k] += w * __uint_as_float(uint32_t(raw[db * 8 + k]));
-          acc_o[db][2 * k + 1] += w * __uint_as_float(uint32_t(raw[db * 8 + k] >> 32));
-        }
+      for (int k = 0; k < kSlots; ++k) sum[k] += w * o[i][k];
     }
   }
-  if (row_ok) ff_store_row<D>(p, acc_o, m_all, l_all, s, my_row, head, half);
+  if (frow >= p.m * group) return;
+  const int row = frow / group, head = hk * group + (frow - row * group);
+  const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
+  float* op = p.out + ((size_t(s) * p.m + row) * p.n_q_heads + head) * D + 4 * half;
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) *reinterpret_cast<f32x4*>(op + 8 * (part * kSlots + k)) = sum[k] * inv;
+  if (p.lse != nullptr && half == 0 && part == 0)
+    p.lse[(size_t(s) * p.n_q_heads + head) * p.m + row] = (m_all + log2f(l_all)) * 0.6931471805599453f;
 }
 
 bool prefill_f32_supported(const actqkv_shape& sh, int m) { return sh.dtype == ACTQKV_F32 && m > 1; }
@@ -358,13 +604,15 @@ static int launch_ff(const FfParams& p, int grid, hipStream_t stream) {
     }
   }
   hipLaunchKernelGGL(attn_prefill_f32_kernel<D>, dim3(grid), dim3(kFfThreads), kFfLdsBytes, stream, p);
+  if (p.splits > 1)
+    hipLaunchKernelGGL(attn_prefill_f32_merge_kernel<D>, dim3(grid / p.splits * kFfWaves), dim3(256), 0, stream, p);
   return hip_status("attention (prefill, fp32)");
 }
 
 int launch_attention_prefill_f32(const actqkv_shape& sh, int batch, int m, const void* q, const void* k_cache,
                                  const void* v_cache, int64_t seq_stride, int nb_capacity, const int32_t* n_ctx,
                                  const int32_t* idx, const int32_t* n_sel, int k_cap, void* out, float* lse,
-                                 float* scratch, unsigned int* counters, float scale, int sel_per_head,
+                                 float* scratch, float scale, int sel_per_head,
                                  hipStream_t stream) {
   FfParams p;
   p.q = static_cast<const float*>(q);
@@ -378,8 +626,7 @@ int launch_attention_prefill_f32(const actqkv_shape& sh, int batch, int m, const
   p.k_cap = k_cap;
   p.out = static_cast<float*>(out);
   p.lse = lse;
-  p.part = reinterpret_cast<uint64_t*>(scratch);
-  p.counters = counters;
+  p.part = scratch;
   p.m = m;
   p.n_q_heads = sh.n_q_heads;
   p.n_kv_heads = sh.n_kv_heads;
@@ -387,11 +634,10 @@ int launch_attention_prefill_f32(const actqkv_shape& sh, int batch, int m, const
   p.n_local = sh.n_local;
   p.n_qtiles = prefill_f32_qtiles(sh, m);
   p.splits = prefill_f32_splits(sh, batch, m);
+  p.per_chip = std::max(kChipCus / (sh.n_kv_heads * p.splits), 1);
   p.sel_per_head = sel_per_head;
   p.scale_log2e = scale * 1.4426950408889634f;
   const int64_t items = int64_t(batch) * sh.n_kv_heads * p.n_qtiles;
-  if (p.splits > 1 && items > int64_t(kTicketCounters))
-    return set_error(ACTQKV_EINVAL, "prefill attention: more split query tiles than ticket counters");
   if (items * p.splits > int64_t(INT32_MAX))
     return set_error(ACTQKV_ESHAPE, "prefill attention: %lld query tiles in a call", (long long)items);
   const int grid = int(items * p.splits);

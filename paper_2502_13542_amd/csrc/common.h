@@ -121,6 +121,20 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ float wave_max(float v) {
   return wave_all(v, [](float a, float b) { return fmaxf(a, b); });
 }
+// The maximum over the lanes, the same (scalar) value in all of them.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_max_u32(uint32_t v) {      // lanes without a source: v
+  return max(v, uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kCtrl, kRows, 0xF, false)));
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  v = dpp_max_u32<0x111, 0xF>(v);                                  // row_shr 1, 2, 4, 8: lane 15 of a row has its maximum
+  v = dpp_max_u32<0x112, 0xF>(v);
+  v = dpp_max_u32<0x114, 0xF>(v);
+  v = dpp_max_u32<0x118, 0xF>(v);
+  v = dpp_max_u32<0x142, 0xA>(v);                                  // row_bcast 15 into rows 1, 3, then 31 into rows 2, 3
+  v = dpp_max_u32<0x143, 0xC>(v);
+  return __builtin_amdgcn_readlane(v, 63);
+}
 // Sum over the workgroup; every thread gets the result.  `red` holds >= 32 floats of LDS.
 __device__ __forceinline__ float block_sum(float v, float* red) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;

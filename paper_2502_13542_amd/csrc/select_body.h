@@ -259,20 +259,6 @@ __device__ __forceinline__ void select_body(const Scores& sc, int s, int n, int 
 // Same ties, same Eq. (11), Eq. (12) as select_body; the sums run in another order.
 constexpr int kSelWavePerLane = 16;
 
-template <int kCtrl, int kRows>
-__device__ __forceinline__ uint32_t dpp_max_u32(uint32_t v) {      // lanes without a source: v
-  return max(v, uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kCtrl, kRows, 0xF, false)));
-}
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-  v = dpp_max_u32<0x111, 0xF>(v);                                  // row_shr 1, 2, 4, 8: lane 15 of a row has its maximum
-  v = dpp_max_u32<0x112, 0xF>(v);
-  v = dpp_max_u32<0x114, 0xF>(v);
-  v = dpp_max_u32<0x118, 0xF>(v);
-  v = dpp_max_u32<0x142, 0xA>(v);                                  // row_bcast 15 into rows 1, 3, then 31 into rows 2, 3
-  v = dpp_max_u32<0x143, 0xC>(v);
-  return __builtin_amdgcn_readlane(v, 63);
-}
-
 // Called by all 64 lanes of one wavefront; sel[0 .. k_cap) and *count (LDS or any memory the
 // wavefront may write) receive the result, then publish() is called, then the global outputs are
 // written if io.write.

@@ -447,6 +447,58 @@ def test_probabilities_keep_more_than_bf16(d, group, m, nw):
     assert worst <= 1., worst
 
 
+@pytest.mark.parametrize("d,group,m,nw", [(64, 4, 65, 1), (64, 4, 256, 40), (64, 2, 2100, 1), (128, 4, 33, 3), (128, 1, 300, 30)])
+@pytest.mark.parametrize("what", ["small and large", "tokens of all sizes", "infinite"])
+def test_fp32_prefill_attention_over_the_range_of_floats(d, group, m, nw, what):
+    """The halves that the products are taken in are made of values times a power of two, per 16 or 8 keys, per channels of
+    V and per query row.  Queries of 1e-12 with keys of 1e12 and values of 1e-20; tokens whose keys and values differ by up
+    to 2^20; infinite and NaN elements, where the result is what fp32 products give.  Memory behind the last token holds 1e30.
+    Bound: a score's D products and sums in fp32, (D + 16) 2^-24 sum_c |q_c k_c|, twice (numerator and
+    denominator) on every term of sum_j p_j |v_j|, and 2^-18 of that for exponentials, sums over the keys and the merge."""
+    sh = LayerShape(2 * group, 2, d, 128, 4, 128, 256, "fp32")
+    cs = B.c_shape(sh)
+    k_cap, base = 4, 9 * 128 + 37
+    n = base + nw * m
+    nb = (n + 127) // 128
+    g = torch.Generator().manual_seed(d + group + m)
+    q, k, v = (torch.randn(a, h, d, generator=g) for a, h in ((nw * m, 2 * group), (nb * 128, 2), (nb * 128, 2)))
+    if what == "small and large":
+        q, k, v = 1e-12 * q, 1e12 * k, 1e-20 * v
+    elif what == "tokens of all sizes":
+        k *= 2. ** torch.randint(-20, 1, (nb * 128, 1, 1), generator=g)
+        v *= 2. ** torch.randint(-20, 1, (nb * 128, 1, 1), generator=g)
+        q *= 2. ** torch.randint(-20, 1, (nw * m, 1, 1), generator=g)
+    w0 = [base + i * m for i in range(nw)]
+    idx = torch.stack([(torch.randperm(H.eligible_range(sh, w)[1] - 1, generator=g)[:k_cap] + 1).int() for w in w0])
+    if what == "infinite":
+        q[0, 0, 3], q[1, 1, 5] = np.inf, np.nan                          # two rows of the first window
+        for i, key in ((0, 7), (nw // 2, 40), (nw - 1, 100)):             # in blocks that all rows of a window see
+            v[int(idx[i, 1]) * 128 + key, 0, 9] = -np.inf
+            v[int(idx[i, 2]) * 128 + key, 0, 11] = np.nan
+            k[int(idx[i, 3]) * 128 + key, 1, 13] = np.inf
+    k[n:], v[n:] = 1e30, -1e30
+    out = torch.zeros(nw * m, 2 * group, d, device=DEV)
+    ws = torch.zeros(B.workspace_bytes(cs, nw, m, nb, k_cap), dtype=torch.uint8, device=DEV)
+    B.retrieval_attention(cs, nw, m, q.to(DEV), H.blocked_k(k.to(DEV), sh, nb), H.blocked_vt(v.to(DEV), sh, nb), 0, nb,
+                          torch.tensor([w + m for w in w0], dtype=torch.int32, device=DEV), idx.to(DEV),
+                          torch.full((nw,), k_cap, dtype=torch.int32, device=DEV), k_cap, out, None, ws)
+    torch.cuda.synchronize()
+    got = out.cpu().double()
+    for i in sorted({0, nw // 2, nw - 1}):
+        for r in sorted({0, 1, min(31, m - 1), min(32, m - 1), m // 2, m - 1}):
+            pos = torch.tensor(orc.key_positions(w0[i], w0[i] + r, idx[i].tolist(), sh.n_init, sh.n_local, 128))
+            kk, vv = k[pos].double().repeat_interleave(group, 1), v[pos].double().repeat_interleave(group, 1)
+            x = q[i * m + r].double()
+            p = torch.softmax((kk * x).sum(-1) / d ** 0.5, 0)[..., None]
+            ref, size = (p * vv).sum(0), (p * vv.abs()).sum(0)
+            o, finite = got[i * m + r], torch.isfinite(ref)
+            assert torch.equal(torch.isnan(o), torch.isnan(ref)), (i, r)
+            assert torch.equal(o[torch.isinf(ref)], ref[torch.isinf(ref)]), (i, r)
+            score = (kk * x).abs().sum(-1).max(0).values[:, None] / d ** 0.5
+            bound = (2 * (d + 16) * 2. ** -24 * score + 2. ** -18) * size
+            assert bool(((o - ref).abs() <= bound)[finite].all()), (i, r, float(((o - ref).abs() / bound)[finite].max()))
+
+
 @pytest.mark.parametrize("hq,hk,d,m,nw,cus", [(32, 8, 128, 128, 17, 256), (32, 8, 128, 512, 3, 224), (28, 4, 128, 77, 33, 7),
                                               (8, 2, 64, 129, 5, 256), (2, 2, 64, 2, 300, 31)])
 def test_windows_of_one_sequence_in_one_call(hq, hk, d, m, nw, cus):
