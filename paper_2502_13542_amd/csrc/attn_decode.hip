@@ -418,6 +418,7 @@ constexpr int kDcD = 128;        // the kernels below: bf16, 128 channels per he
 __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams p, DcSelectParams sp) {
   extern __shared__ __attribute__((aligned(16))) float dc_lds[];
   __shared__ SelectLds<kDcThreads> sel_lds;
+  __shared__ SelectWaveLds sel_wave_lds;
   __shared__ int sel_ready;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   constexpr int n_waves = kDcMaxWaves;
@@ -442,7 +443,7 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
   io.write = wg == 0 && hk == 0;
   if (selector) {
     __builtin_amdgcn_s_setprio(3);       // the others only issue loads meanwhile, and wait for this
-    select_wave(sc_mem, s, n_elig, sp.nb_begin, p.k_cap, sp.entropy_topk, io, sel_lds.sel, &sel_lds.count, [&] {
+    select_wave(sc_mem, s, n_elig, sp.nb_begin, p.k_cap, sp.entropy_topk, io, sel_wave_lds, sel_lds.sel, &sel_lds.count, [&] {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       if (lane == 0) __hip_atomic_store(&sel_ready, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     });

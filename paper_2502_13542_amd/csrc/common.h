@@ -135,6 +135,21 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   v = dpp_max_u32<0x143, 0xC>(v);
   return __builtin_amdgcn_readlane(v, 63);
 }
+// The sum over the lanes, the same (scalar) value in all of them: six additions that read a neighbour's lane themselves, where
+// wave_sum takes three instructions a step.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ float dpp_add_f32(float v) {            // lanes without a source: v
+  return v + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), kCtrl, kRows, 0xF, false));
+}
+__device__ __forceinline__ float wave_sum_scalar(float v) {
+  v = dpp_add_f32<0x111, 0xF>(v);
+  v = dpp_add_f32<0x112, 0xF>(v);
+  v = dpp_add_f32<0x114, 0xF>(v);
+  v = dpp_add_f32<0x118, 0xF>(v);
+  v = dpp_add_f32<0x142, 0xA>(v);
+  v = dpp_add_f32<0x143, 0xC>(v);
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
+}
 // Sum over the workgroup; every thread gets the result.  `red` holds >= 32 floats of LDS.
 __device__ __forceinline__ float block_sum(float v, float* red) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;

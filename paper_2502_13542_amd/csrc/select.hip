@@ -38,6 +38,7 @@ __global__ __launch_bounds__(64) void select_wave_kernel(
     const int32_t* __restrict__ nb_end, int k_cap, int flags, float* __restrict__ budget_remaining,
     const float* __restrict__ theta_rest_sum, int32_t* __restrict__ idx, int32_t* __restrict__ n_sel,
     float* __restrict__ theta_out, float* __restrict__ budget_out) {
+  __shared__ SelectWaveLds lds;
   __shared__ int sel[64], count;
   const int s = blockIdx.x;
   const int end = min(max(nb_end[s], nb_begin), nb_capacity);
@@ -45,7 +46,7 @@ __global__ __launch_bounds__(64) void select_wave_kernel(
   io.density_only = (flags & ACTQKV_SELECT_DENSITY_ONLY) != 0;
   if (flags & ACTQKV_SELECT_GIVEN_COUNT) io.count_in = n_sel;
   select_wave(scores + size_t(s) * score_stride + nb_begin, s, max(end - nb_begin, 0), nb_begin, k_cap,
-              (flags & ACTQKV_SELECT_ENTROPY_TOPK) != 0, io, sel, &count, [] {});
+              (flags & ACTQKV_SELECT_ENTROPY_TOPK) != 0, io, lds, sel, &count, [] {});
 }
 
 int launch_select(int batch, const float* scores, int64_t score_stride, int nb_capacity, int nb_begin,

@@ -249,22 +249,48 @@ __device__ __forceinline__ void select_body(const Scores& sc, int s, int n, int 
 // A selection spread over a workgroup couples its wavefronts at a dozen barriers; one wavefront needs
 // none.  In the decode attention that selects for itself the others are stuck handing 32 KB of
 // load requests each to a full memory pipeline meanwhile; as a launch of its own the step is nothing
-// but latency.  Lane l keeps the scores of blocks l, l + 64, ... in registers.  The density is two
-// passes over them.  The E best blocks come out one per round: every lane knows its three best scores and
+// but latency: an instruction that waits for the one before it takes 8 cycles.  Lane l keeps the scores of blocks l, l + 64, ...
+// in registers.  The density is two passes over them.  Then the candidates: of a row of more than 64 blocks those that are
+// no smaller than the E-th largest of the lanes' maxima (E values at least are that large, so the E best are among them;
+// of random scores a few more than E), put one to a lane through LDS in the order of their blocks.  A candidate's place is the
+// number of larger ones, counted against every one of them: three instructions each and none that waits.  Up to 4 blocks
+// (3 of 62: 3.4 us round by round, 4.0 so), and more than 64 candidates (many equal scores, or E beyond 32), come out
+// round by round, 130 cycles each and more where lanes have to search again: every lane knows its three best scores and
 // where they are, the best of all lanes is a 32-bit maximum by row shifts and broadcasts (an instruction per
-// step), a ballot names its lane (several lanes with equal scores: the lowest block of them, the rare
-// path), and that lane goes on with its next; only a lane that has given all three looks through its registers again,
-// for what comes behind them.  A launch over 500 blocks, 10 and 32 of them chosen: 7.7 and 14.7 us with one best per lane
-// and a search after every round, 6.3 and 10.2 so; a decode step of one sequence with 8K tokens 21.1 and 19.7.
+// step), a ballot names its lane (several lanes with equal scores: the lowest block of them), and that lane goes on with
+// its next; only a lane that has given all three looks through its registers again, for what comes behind them.
+// As a launch of its own, round by round / by candidates: 10 of 60 blocks 3.9 / 3.4 us, 10 of 500 4.5 / 3.6, 32 of 500 8.5 / 4.2,
+// 32 of 1000 in 32 rows 12.0 / 5.3 (an empty launch behind another takes 1.7).
 // Same ties, same Eq. (11), Eq. (12) as select_body; the sums run in another order.
 constexpr int kSelWavePerLane = 16;
+constexpr int kSelFewRounds = 4;
 
-// Called by all 64 lanes of one wavefront; sel[0 .. k_cap) and *count (LDS or any memory the
-// wavefront may write) receive the result, then publish() is called, then the global outputs are
-// written if io.write.
+struct SelectWaveLds {
+  uint32_t key[64];
+  int block[64];
+};
+
+// How many of the keys of lanes 0 .. count - 1 come before this lane's: larger ones, and equal ones of lower lanes.
+// (count is wave-uniform; lanes from count on hold 0.)
+__device__ __forceinline__ int wave_place(uint32_t key, int count, int lane) {
+  int before = 0;
+  for (int j0 = 0; j0 < count; j0 += 16) {
+#pragma unroll
+    for (int j = j0; j < j0 + 16; ++j) before += uint32_t(__builtin_amdgcn_readlane(int(key), j)) > key;
+  }
+  // equal keys share a place: then the places do not add up
+  const float sum = wave_sum_scalar(lane < count ? float(before) : 0.f);     // (at most 2016: exact)
+  if (sum != float(count * (count - 1) / 2)) {
+    for (int j = 0; j < count; ++j) before += uint32_t(__builtin_amdgcn_readlane(int(key), j)) == key && j < lane;
+  }
+  return before;
+}
+
+// Called by all 64 lanes of one wavefront; sel[0 .. 64) and *count (LDS) receive the result (sel[i] = -1 from E on), then
+// publish() is called, then the global outputs are written if io.write.
 template <typename Publish>
 __device__ __forceinline__ void select_wave(const float* __restrict__ sc_mem, int s, int n, int nb_begin, int k_cap,
-                                            int entropy_topk, const SelectIo& io, int* sel, int* count,
+                                            int entropy_topk, const SelectIo& io, SelectWaveLds& lds, int* sel, int* count,
                                             Publish&& publish) {
   constexpr int kPer = kSelWavePerLane, kPart = 4;               // registers are walked a part at a time, as far as n goes
   const int lane = threadIdx.x & 63;
@@ -278,24 +304,28 @@ __device__ __forceinline__ void select_wave(const float* __restrict__ sc_mem, in
   const CutoffIn in(s, io);
   float theta = 0.f;
   if (!entropy_topk && n > 0) {
-    float mx = -INFINITY;
+    float mx = v[0];
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) mx = fmaxf(mx, v[i]);
+    for (int c = 0; c < kPer; c += kPart)
+      if (c < per) {
+#pragma unroll
+        for (int i = c; i < c + kPart; ++i) mx = fmaxf(mx, v[i]);
+      }
     mx = wave_max(mx);
     float z = 0.f, t = 0.f;
 #pragma unroll
     for (int c = 0; c < kPer; c += kPart)
       if (c < per) {
 #pragma unroll
-        for (int i = c; i < c + kPart; ++i)
-          if (lane + 64 * i < n) {
-            const float e = __expf(v[i] - mx);
-            z += e;
-            t += e * v[i];
-          }
+        for (int i = c; i < c + kPart; ++i) {
+          const bool in = lane + 64 * i < n;
+          const float e = in ? __expf(v[i] - mx) : 0.f;
+          z += e;
+          t += in ? e * v[i] : 0.f;
+        }
       }
-    z = wave_sum(z);
-    t = wave_sum(t);
+    z = wave_sum_scalar(z);
+    t = wave_sum_scalar(t);
     theta = fmaxf(logf(z) + mx - t / z, 0.f);
   }
   Cutoff cut(theta, n, k_cap, in, io);
@@ -303,56 +333,108 @@ __device__ __forceinline__ void select_wave(const float* __restrict__ sc_mem, in
   int mine = -1;                                                 // lane r: the r-th best block
   uint32_t mine_key = 0u;
   const int rounds = __builtin_amdgcn_readfirstlane(io.density_only && !entropy_topk ? 0 : entropy_topk ? min(k_cap, n) : cut.e);
+  sel[lane] = -1;
   if (rounds > 0) {
     uint32_t key[kPer];                                          // 0: no block
 #pragma unroll
-    for (int i = 0; i < kPer; ++i)
-      key[i] = lane + 64 * i < n ? max(uint32_t(select_key(v[i], 0) >> 32), 1u) : 0u;
-    // the lane's three best behind (than, at_than) in the order of descending keys and ascending registers, and the
-    // registers they are in
-    uint32_t best, next, third;
-    int at, at2, at3;
-    auto find_three = [&](uint32_t than, int at_than) {
-      best = next = third = 0u;
-      at = at2 = at3 = 0;
+    for (int i = 0; i < kPer; ++i) key[i] = 0u;
+#pragma unroll
+    for (int c = 0; c < kPer; c += kPart)
+      if (c < per) {
+#pragma unroll
+        for (int i = c; i < c + kPart; ++i)
+          key[i] = lane + 64 * i < n ? max(uint32_t(select_key(v[i], 0) >> 32), 1u) : 0u;
+      }
+    uint32_t cand = key[0];
+    int block = lane, n_cand = rounds > kSelFewRounds ? n : 65;
+    if (per > 1 && rounds > kSelFewRounds) {
+      uint32_t best = key[0];
+#pragma unroll
+      for (int c = 0; c < kPer; c += kPart)
+        if (c < per) {
+#pragma unroll
+          for (int i = c; i < c + kPart; ++i) best = max(best, key[i]);
+        }
+      int before = 0;
+#pragma unroll
+      for (int j = 0; j < 64; ++j) before += uint32_t(__builtin_amdgcn_readlane(int(best), j)) > best;
+      const uint32_t least = ~wave_max_u32(before < rounds ? ~best : 0u);   // (best > 0: every lane has a block)
+      n_cand = 0;
 #pragma unroll
       for (int c = 0; c < kPer; c += kPart)
         if (c < per) {
 #pragma unroll
           for (int i = c; i < c + kPart; ++i) {
-            const uint32_t k = key[i] < than || (key[i] == than && i > at_than) ? key[i] : 0u;
-            const bool c1 = k > best, c2 = k > next, c3 = k > third;
-            at3 = c2 ? at2 : c3 ? i : at3;
-            at2 = c1 ? at : c2 ? i : at2;
-            at = c1 ? i : at;
-            third = max(third, min(next, k));
-            next = max(next, min(best, k));
-            best = max(best, k);
+            const unsigned long long who = __ballot(key[i] >= least);
+            const int at = n_cand + int(__builtin_amdgcn_mbcnt_hi(uint32_t(who >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(who), 0u)));
+            if (key[i] >= least && at < 64) {
+              lds.key[at] = key[i];
+              lds.block[at] = lane + 64 * i;
+            }
+            n_cand += __builtin_popcountll(who);
           }
         }
-    };
-    find_three(0xffffffffu, -1);
-    int left = n > lane ? (n - lane + 63) >> 6 : 0;              // the lane's blocks that have not come out
-    for (int r = 0; r < rounds; ++r) {
-      const uint32_t top = wave_max_u32(best);
-      const unsigned long long who = __ballot(best == top);
-      int w = __builtin_ctzll(who);
-      if ((who & (who - 1ull)) != 0ull) {
-        const uint32_t low = wave_max_u32(best == top ? ~uint32_t(lane + 64 * at) : 0u);
-        w = int(~low) & 63;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      cand = lane < n_cand ? lds.key[lane] : 0u;
+      block = lds.block[lane];
+    }
+    if (n_cand <= 64) {
+      const int place = wave_place(cand, n_cand, lane);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (lane < n_cand && place < rounds) {
+        sel[place] = nb_begin + block;
+        lds.key[place] = cand;
       }
-      const int i_top = __builtin_amdgcn_readlane(at, w), b = w + 64 * i_top;
-      mine = lane == r ? nb_begin + b : mine;
-      mine_key = lane == r ? top : mine_key;
-      const bool won = lane == w;
-      best = won ? next : best;
-      at = won ? at2 : at;
-      next = won ? third : next;
-      at2 = won ? at3 : at2;
-      third = won ? 0u : third;
-      left -= won;
-      if (per > 3 && __ballot(won && best == 0u && left > 0) != 0ull) {
-        if (won) find_three(top, i_top);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      mine = sel[lane];
+      mine_key = lds.key[lane];
+    } else {
+      // the lane's three best behind (than, at_than) in the order of descending keys and ascending registers, and the
+      // registers they are in
+      uint32_t best, next, third;
+      int at, at2, at3;
+      auto find_three = [&](uint32_t than, int at_than) {
+        best = next = third = 0u;
+        at = at2 = at3 = 0;
+#pragma unroll
+        for (int c = 0; c < kPer; c += kPart)
+          if (c < per) {
+#pragma unroll
+            for (int i = c; i < c + kPart; ++i) {
+              const uint32_t k = key[i] < than || (key[i] == than && i > at_than) ? key[i] : 0u;
+              const bool c1 = k > best, c2 = k > next, c3 = k > third;
+              at3 = c2 ? at2 : c3 ? i : at3;
+              at2 = c1 ? at : c2 ? i : at2;
+              at = c1 ? i : at;
+              third = max(third, min(next, k));
+              next = max(next, min(best, k));
+              best = max(best, k);
+            }
+          }
+      };
+      find_three(0xffffffffu, -1);
+      int left = n > lane ? (n - lane + 63) >> 6 : 0;              // the lane's blocks that have not come out
+      for (int r = 0; r < rounds; ++r) {
+        const uint32_t top = wave_max_u32(best);
+        const unsigned long long who = __ballot(best == top);
+        int w = __builtin_ctzll(who);
+        if ((who & (who - 1ull)) != 0ull) {
+          const uint32_t low = wave_max_u32(best == top ? ~uint32_t(lane + 64 * at) : 0u);
+          w = int(~low) & 63;
+        }
+        const int i_top = __builtin_amdgcn_readlane(at, w), b = w + 64 * i_top;
+        mine = lane == r ? nb_begin + b : mine;
+        mine_key = lane == r ? top : mine_key;
+        const bool won = lane == w;
+        best = won ? next : best;
+        at = won ? at2 : at;
+        next = won ? third : next;
+        at2 = won ? at3 : at2;
+        third = won ? 0u : third;
+        left -= won;
+        if (per > 3 && __ballot(won && best == 0u && left > 0) != 0ull) {
+          if (won) find_three(top, i_top);
+        }
       }
     }
   }
@@ -365,7 +447,7 @@ __device__ __forceinline__ void select_wave(const float* __restrict__ sc_mem, in
     cut = Cutoff(fmaxf(logf(z) + mx - t / z, 0.f), n, k_cap, in, io);
   }
   if (lane >= cut.e) mine = -1;
-  if (lane < k_cap) sel[lane] = mine;
+  sel[lane] = mine;
   if (lane == 0) *count = cut.e;
   publish();
   if (io.write) {

@@ -1060,6 +1060,30 @@ def test_selection_by_one_wavefront_where_few_lanes_hold_the_best(n):
         assert idx[s].tolist() == want + [-1] * (k - e), f"row {s}"
 
 
+@pytest.mark.parametrize("n,k", [(64, 1), (65, 8), (128, 32), (500, 8), (1000, 1), (1024, 31)])
+def test_selection_by_one_wavefront_counts_its_candidates(n, k):
+    """The candidates are what is no smaller than the k-th largest of 64 lane maxima, up to 64 of them one to a lane: as many
+    as there are lanes and one more, ties across that least one, and as few as k."""
+    g = torch.Generator().manual_seed(n + k)
+    rows = torch.randn(5, 1024, generator=g)
+    rows[0] = torch.arange(1024.)                                # the maxima are the last 64 blocks: k candidates
+    rows[1] = 0.0
+    rows[1, :64] = torch.arange(64.) // 8                        # eight equal ones at every step
+    rows[2] = -1.0
+    rows[2, 7::64] = torch.arange(16.)                           # one lane holds 16 of the best, the other maxima are equal
+    rows[3] = 0.0
+    rows[3, torch.randperm(n, generator=g)[:64]] = 1.0           # 64 equal candidates
+    rows[4] = 0.0
+    rows[4, torch.randperm(n, generator=g)[:65]] = 1.0           # one too many
+    idx = torch.full((5, k), -2, dtype=torch.int32, device=DEV)
+    n_sel = torch.zeros(5, dtype=torch.int32, device=DEV)
+    B.select(5, rows.to(DEV), 1024, 1024, 0, torch.full((5,), n, dtype=torch.int32, device=DEV), k, None, None, idx, n_sel, None, None)
+    torch.cuda.synchronize()
+    assert n_sel.tolist() == [k] * 5
+    for s in range(5):
+        assert idx[s].tolist() == sorted(range(n), key=lambda b: (-float(rows[s, b]), b))[:k], f"row {s}"
+
+
 @pytest.mark.parametrize("n", [16, 32768 - 16, 32768, 32768 + 16, 8 * 32768 + 48, (1 << 20) + 16])
 def test_copy_into_host_memory(n):
     """The stores of a copy into pinned memory are bounded by the piece and by the copy's end."""
