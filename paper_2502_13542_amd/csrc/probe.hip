@@ -17,6 +17,7 @@
 // own (mean, M2) only, so everything else is done for all windows at once (kernels further
 // down).  Four launches for n windows instead of 3 n.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "launch.h"
@@ -25,12 +26,30 @@
 namespace actqkv {
 
 constexpr int kColLanes = 8;      // 16-byte column lanes of a slab
-constexpr int kRowsPerThread = 16;   // 16-byte loads a thread keeps in flight
+
+// Sums of values of eight row lanes: x[i] of the wavefront's lanes cl, cl + 8, ..., cl + 56 (column lane cl).  Halves of the
+// lanes take halves of the values (an exchange and an addition for two of them): lane bit 5 says which half of the 2 V values,
+// bit 4 which half of those; the V / 2 sums left are the same in both lanes of bit 3.
+template <int V>
+__device__ __forceinline__ void row_lane_sums(const float (&x)[2 * V], float (&out)[V / 2]) {
+  float y[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[V + i]), false, false);
+    y[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < V / 2; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(y[i]), __float_as_uint(y[V / 2 + i]), false, false);
+    const float t = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    out[i] = t + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(t), 0x128, 0xF, 0xF, true));   // row_ror:8
+  }
+}
 
 // apart[j] = sum over the slab's channels of (q_jc - mean_c)^2 / var_c for the rows of the
 // window (Eq. (7) summed over a slab); x holds pass 0 of the rows when there is one pass only.
-template <typename T, int RL, typename LoadPass>
-__device__ __forceinline__ void bias_partials(typename Vec<T>::raw (&x)[kRowsPerThread], LoadPass&& load_pass,
+template <typename T, int RL, int R, typename LoadPass>
+__device__ __forceinline__ void bias_partials(typename Vec<T>::raw (&x)[R], LoadPass&& load_pass,
                                               const float* mu_lds, const float* iv_lds,
                                               float* __restrict__ apart, int m, int m_pad, int n_pass,
                                               int cl, int rl) {
@@ -43,10 +62,10 @@ __device__ __forceinline__ void bias_partials(typename Vec<T>::raw (&x)[kRowsPer
   }
   for (int pass = 0; pass < n_pass; ++pass) {
     if (n_pass > 1) load_pass(pass);
-    const int r0 = (pass * RL + rl) * kRowsPerThread;
-    float a[kRowsPerThread];
+    const int r0 = (pass * RL + rl) * R;
+    float a[R];
 #pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i) {
+    for (int i = 0; i < R; ++i) {
       float f[V];
       Vec<T>::widen(x[i], f);
       float t = 0.f;
@@ -63,7 +82,7 @@ __device__ __forceinline__ void bias_partials(typename Vec<T>::raw (&x)[kRowsPer
     }
     if (cl == 0 && r0 < m_pad) {
 #pragma unroll
-      for (int i = 0; i < kRowsPerThread; i += 4) {
+      for (int i = 0; i < R; i += 4) {
         f32x4 o = {a[i], a[i + 1], a[i + 2], a[i + 3]};
         *reinterpret_cast<f32x4*>(apart + r0 + i) = o;
       }
@@ -72,18 +91,19 @@ __device__ __forceinline__ void bias_partials(typename Vec<T>::raw (&x)[kRowsPer
 }
 
 // grid (column slabs of 8*V channels, batch); 8 column lanes x RL row lanes; row lane rl takes rows
-// rl*16 .. rl*16+15 of every pass of 16 RL rows.
+// rl R .. rl R + R - 1 of every pass of R RL rows.
 // Pass 1 (update != 0): sums of (q - shift), shift = the old mean (or the window's first
 // query when there is no history), which keeps the squares free of cancellation; pairwise
 // merge into the running mean and M2.  The count n is published by the next kernel of the
 // chain (every workgroup here reads the old one).
 // Pass 2 (m > 1): apart[slab][j] = sum over the slab's channels of (q_jc - mean_c)^2 / var_c.
-// A window of at most 16 RL rows stays in registers between the passes.  RL follows the window's
-// length (launch_probe_t): there is one workgroup per slab however long the window is, and a pass
-// costs a memory round trip, so the more rows are requested at once the better.
-// Windows of 4096 and 2563 tokens, 8 heads of 128 channels (16 slabs): both windows' probe, score,
-// selection and attention 239 us with 32 row lanes here and 64 in weigh, 214 with 128 in both.
-template <typename T, int RL>
+// A window of at most R RL rows stays in registers between the passes.  RL and R follow the window's
+// length (launch_probe_t): there is one workgroup per slab however long the window is, a pass costs a memory round trip,
+// and what a thread does with its rows is instructions one after the other: as many row lanes as the window has use for,
+// the fewest rows each.  The probe's three launches with 32 or 64 row lanes of 16 rows each, and what is written below at weigh,
+// before / now: 256 tokens, 512 channels 11.9 / 10.1 us, 4096 channels 13.5 / 10.6; 600 tokens 13.9 / 12.6, 17.4 / 14.5; 2048 tokens
+// 20.4 / 18.3, 28.2 / 22.6.
+template <typename T, int RL, int R>
 __global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const T* __restrict__ q_win,
                                                                float* __restrict__ stats,
                                                                float* __restrict__ scratch, int update,
@@ -93,7 +113,7 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const 
   constexpr int V = Vec<T>::N;
   constexpr int SLAB = kColLanes * V;
   typedef typename Vec<T>::raw raw_t;
-  __shared__ float red[2][RL][SLAB];
+  __shared__ __attribute__((aligned(16))) float red[2][RL / 8][SLAB];
   __shared__ float mu_lds[SLAB], iv_lds[SLAB];
   const int s = blockIdx.y;
   const T* q = q_win + size_t(s) * m * d;
@@ -120,13 +140,13 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const 
     for (int v = 0; v < V; ++v) c[v] = st[4 + ch0 + v];
     Vec<T>::load(q + ch0, c_first);
   }
-  const int n_pass = (m + RL * kRowsPerThread - 1) / (RL * kRowsPerThread);
+  const int n_pass = (m + RL * R - 1) / (RL * R);
 
-  raw_t x[kRowsPerThread];
+  raw_t x[R];
   auto load_pass = [&](int pass) {
 #pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i) {   // all loads first: they overlap
-      const int r = (pass * RL + rl) * kRowsPerThread + i;
+    for (int i = 0; i < R; ++i) {   // all loads first: they overlap
+      const int r = (pass * RL + rl) * R + i;
       x[i] = Vec<T>::load_raw(q + size_t(r < m ? r : 0) * d + (col_ok ? ch0 : 0));
     }
   };
@@ -142,8 +162,8 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const 
     for (int pass = 0; pass < n_pass; ++pass) {
       if (pass > 0) load_pass(pass);
 #pragma unroll
-      for (int i = 0; i < kRowsPerThread; ++i) {
-        if ((pass * RL + rl) * kRowsPerThread + i < m) {
+      for (int i = 0; i < R; ++i) {
+        if ((pass * RL + rl) * R + i < m) {
           float f[V];
           Vec<T>::widen(x[i], f);
 #pragma unroll
@@ -155,10 +175,15 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const 
         }
       }
     }
+    float both[2 * V], sum[V / 2];
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      red[0][rl][cl * V + v] = s1[v];
-      red[1][rl][cl * V + v] = s2[v];
+    for (int v = 0; v < V; ++v) both[v] = s1[v], both[V + v] = s2[v];
+    row_lane_sums<V>(both, sum);
+    const int lane = threadIdx.x & 63;
+    if ((lane & 8) == 0) {
+      float* to = &red[lane >> 5][threadIdx.x >> 6][cl * V + ((lane >> 4) & 1) * (V / 2)];
+#pragma unroll
+      for (int i = 0; i < V / 2; ++i) to[i] = sum[i];
     }
     __syncthreads();
   }
@@ -168,8 +193,8 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const 
       float mean, m2, n_new;
       if (update) {
         float t1 = 0.f, t2 = 0.f;
-#pragma unroll 16
-        for (int k = 0; k < RL; ++k) {
+#pragma unroll
+        for (int k = 0; k < RL / 8; ++k) {
           t1 += red[0][k][col];
           t2 += red[1][k][col];
         }
@@ -196,7 +221,7 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_stats_bias_kernel(const 
   if (m == 1) return;   // a single token is its own probe: no weights needed
   __syncthreads();
 
-  bias_partials<T, RL>(x, load_pass, mu_lds, iv_lds, apart, m, m_pad, n_pass, cl, rl);
+  bias_partials<T, RL, R>(x, load_pass, mu_lds, iv_lds, apart, m, m_pad, n_pass, cl, rl);
 }
 
 // ---- consecutive windows of one sequence in one call
@@ -245,20 +270,26 @@ __global__ __launch_bounds__(kRmThreads) void probe_rows_moments_kernel(const T*
   const int rls = kRmThreads / cols, rl = int(threadIdx.x) / cols, col = int(threadIdx.x) - rl * cols;
   const int ch = (int(blockIdx.z) * cols + col) * V;
   const bool ok = ch < d && rl < rls;
-  float c[V], s1[V], s2[V];
+  float c[V], s1[V], s2[V], mean[V];
+  const bool single = gridDim.y == 1;
+  const float n_run = single ? stats[0] : 0.f;
   Vec<T>::load(q + (ok ? ch : 0), c);
-  if (gridDim.y == 1 && stats[0] > 0.f) {            // (n sums of squares about a point lose n * its distance^2)
-    const float* mean = stats + 4 + (ok ? ch : 0);
 #pragma unroll
-    for (int v = 0; v < V; ++v) c[v] = moments_about(c[v], 1.f, mean[v]);
-  }
+  for (int v = 0; v < V; ++v) mean[v] = single ? stats[4 + (ok ? ch : 0) + v] : 0.f;   // (asked for with the rest, used or not)
 #pragma unroll
   for (int v = 0; v < V; ++v) s1[v] = s2[v] = 0.f;
   const int r0 = rc * kRowChunk, r1 = min(r0 + kRowChunk, m);
-  for (int r = r0 + rl; r < r1; r += R * rls) {
-    raw_t x[R];
+  raw_t x[R];
+  auto load_rows = [&](int r) {
 #pragma unroll
     for (int i = 0; i < R; ++i) x[i] = Vec<T>::load_raw(q + size_t(min(r + i * rls, r1 - 1)) * d + (ok ? ch : 0));
+  };
+  load_rows(r0 + rl);
+  __builtin_amdgcn_sched_barrier(0);                 // (n sums of squares about a point lose n * its distance^2)
+#pragma unroll
+  for (int v = 0; v < V; ++v) c[v] = moments_about(c[v], n_run, mean[v]);
+  for (int r = r0 + rl; r < r1; r += R * rls) {
+    if (r != r0 + rl) load_rows(r);
 #pragma unroll
     for (int i = 0; i < R; ++i) {
       if (r + i * rls < r1) {
@@ -303,9 +334,11 @@ __global__ __launch_bounds__(kRmThreads) void probe_rows_moments_kernel(const T*
 // grid (d / 32), 1024 threads = 32 channels x 32 lanes.  The chunk sums of every window become the window's own
 // (mean, M2) in LDS: with fewer than 32 windows several lanes share one (32 / n, rounded down to a power of two), lane
 // u of them the chunks u, u + share, ..., whose sums are added in lane order.  Then lane 0 merges the windows into the
-// running statistics in window order (the merge of Eq. (8), as in probe_stats_bias_kernel).  The count is published by
+// running statistics in window order (the merge of Eq. (8), as in probe_stats_bias_kernel): one window after the other, so
+// its quotients of counts and the 1/var that follow from it are made by all lanes, before and after (with both in the
+// loop 11.6 us for 32 windows of 256 tokens with 512 channels in fp32, 5.8 so; 18.5 for 32 of 512 with 4096 beside the attention, 12.4 so).  The count is published by
 // the next kernel (every thread here reads the old one; `before` is what launches of this call have added to it).  At most
-// kChainTile windows a launch: 128 KB of LDS, and 8 KB for the lanes' sums.  (The tiles in one launch, as a loop: a window
+// kChainTile windows a launch: 132 KB of LDS, and 8 KB for the lanes' sums.  (The tiles in one launch, as a loop: a window
 // of 4096 tokens with 512 channels 24.3 us instead of 23.7.)
 constexpr int kChainTile = 512;
 template <typename T>
@@ -314,7 +347,7 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
                                                                  float* __restrict__ stats,
                                                                  float* __restrict__ stat_out, int n, int m,
                                                                  int d, int n_chunks, float eps, float before, int single) {
-  extern __shared__ float wm[];                      // [n][2][32]: the windows' own mean and M2
+  extern __shared__ float wm[];                      // [n][2][32]: the windows' own mean and M2, then the running ones | [n][2]
   __shared__ float lane_sum[2][32][32];
   constexpr int kBatch = 8;                          // chunks requested together
   const int cl = threadIdx.x & 31, wl = threadIdx.x >> 5;
@@ -323,8 +356,10 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
   int share = 1;
   while (share * 2 * n <= 32) share *= 2;
   const int u = wl % share;
-  float n_run = 0.f, mean = 0.f, m2 = 0.f;
-  if (wl == 0 && ch < d) n_run = stats[0] + before, mean = stats[4 + ch], m2 = stats[4 + d + ch];   // (in flight meanwhile)
+  float mean = 0.f, m2 = 0.f;
+  const float n_run = stats[0] + before;
+  if (wl == 0 && ch < d) mean = stats[4 + ch], m2 = stats[4 + d + ch];   // (in flight meanwhile)
+  float* count_of = wm + size_t(n) * 64;             // nb / n_new, n_old nb / n_new
   for (int w0 = 0; w0 < n; w0 += 32 / share) {
     const int w = w0 + wl / share;
     const bool live = w < n && ch < d;
@@ -358,32 +393,44 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
         }
     }
     if (live && u == 0) {
-      wm[(w * 2 + 0) * 32 + cl] = (single ? moments_about(first, n_run, mean) : first) + t1 / nb;   // (a single window: lane 0 alone comes here)
+      const float mean_b = (single ? moments_about(first, n_run, mean) : first) + t1 / nb;   // (a single window: lane 0 alone comes here)
+      wm[(w * 2 + 0) * 32 + cl] = mean_b;
       wm[(w * 2 + 1) * 32 + cl] = fmaxf(t2 - t1 * t1 / nb, 0.f);
+      stat_out[size_t(w) * 3 * d + 2 * d + ch] = mean_b;
     }
+  }
+  for (int w = threadIdx.x; w < n; w += 1024) {
+    const float n_old = n_run + float(w) * nb, n_new = n_old + nb;
+    count_of[2 * w] = nb / n_new;
+    count_of[2 * w + 1] = n_old * nb / n_new;
   }
   __syncthreads();
-  if (wl != 0 || ch >= d) return;
-  for (int w = 0; w < n; ++w) {
-    const float mean_b = wm[(w * 2 + 0) * 32 + cl], m2_b = wm[(w * 2 + 1) * 32 + cl];
-    const float n_new = n_run + nb;
-    if (n_run > 0.f) {
-      const float delta = mean_b - mean;
-      mean += delta * (nb / n_new);
-      m2 += m2_b + delta * delta * (n_run * nb / n_new);
-    } else {
-      mean = mean_b;
-      m2 = m2_b;
+  if (wl == 0 && ch < d) {
+    for (int w = 0; w < n; ++w) {
+      const float mean_b = wm[(w * 2 + 0) * 32 + cl], m2_b = wm[(w * 2 + 1) * 32 + cl];
+      if (w > 0 || n_run > 0.f) {
+        const float delta = mean_b - mean;
+        mean += delta * count_of[2 * w];
+        m2 += m2_b + delta * delta * count_of[2 * w + 1];
+      } else {
+        mean = mean_b;
+        m2 = m2_b;
+      }
+      wm[(w * 2 + 0) * 32 + cl] = mean;
+      wm[(w * 2 + 1) * 32 + cl] = m2;
     }
-    n_run = n_new;
-    const float var = n_run > 1.f ? m2 / (n_run - 1.f) : 0.f;
-    float* o = stat_out + size_t(w) * 3 * d + ch;
-    o[0] = mean;
-    o[d] = 1.f / fmaxf(var, eps);
-    o[2 * d] = mean_b;
+    stats[4 + ch] = mean;
+    stats[4 + d + ch] = m2;
   }
-  stats[4 + ch] = mean;
-  stats[4 + d + ch] = m2;
+  __syncthreads();
+  if (ch >= d) return;
+  for (int w = wl; w < n; w += 32) {
+    const float n_new = n_run + float(w) * nb + nb;
+    const float var = n_new > 1.f ? wm[(w * 2 + 1) * 32 + cl] / (n_new - 1.f) : 0.f;
+    float* o = stat_out + size_t(w) * 3 * d + ch;
+    o[0] = wm[(w * 2 + 0) * 32 + cl];
+    o[d] = 1.f / fmaxf(var, eps);
+  }
 }
 
 // grid (chunks, windows), NW wavefronts; wavefront v takes rows v, v + NW, ... of the chunk, a lane
@@ -532,75 +579,85 @@ __global__ __launch_bounds__(64 * NW) void probe_rows_bias_weigh_kernel(
   }
 }
 
-// One workgroup per window: the chunk sums in chunk order, Eq. (9)'s normalisation (uniform
-// weights, i.e. the window's mean, if every bias is zero), the weights, and what probe_finish
-// computes.
-__global__ __launch_bounds__(1024) void probe_chain_finish_kernel(
+// Per window: the sums over its chunks, Eq. (9)'s normalisation (uniform weights, i.e. the window's mean, if every bias
+// is zero) and the weights; with one workgroup per window also what probe_finish computes.  grid (windows, slabs): a
+// workgroup takes d / slabs channels, four to a thread and the chunks shared among 4096 / d threads (the one of u takes u,
+// u + share, ..., added in the order of u: whatever the slabs, the sums are the same).  All that bounds it is round trips: a thread
+// per channel and the chunks eight at a time, the sum of a_j one scalar load after the other, took 15.0 us for one
+// window of 4096 tokens with 1024 channels (64 chunks), now 4.8.
+constexpr int kCfThreads = 1024;
+__global__ __launch_bounds__(kCfThreads) void probe_chain_finish_kernel(
     const float* __restrict__ pprobe, const float* __restrict__ asum, const float* __restrict__ a_rows,
     const float* __restrict__ stat_in, float* __restrict__ probe_out, float* __restrict__ probe_kv_out,
     float* __restrict__ probe_norm_out, float* __restrict__ weights_out, int m, int m_pad, int d, int n_chunks,
     int asum_stride, int n_q_heads, int n_kv_heads, int head_dim) {
   __shared__ float red[32];
+  __shared__ f32x4 part[kCfThreads];
   extern __shared__ __attribute__((aligned(16))) float probe_lds[];   // [d]
-  const int w = blockIdx.x;
-  float total = 0.f;
-  for (int rc = 0; rc < n_chunks; ++rc) total += asum[size_t(w) * asum_stride + rc];
-  const bool uniform = !(total > 0.f);
-  const float inv = uniform ? 0.f : 1.f / total;
-  float* probe = probe_out + size_t(w) * d;
-  float ss = 0.f;
-  for (int ch = threadIdx.x; ch < d; ch += 1024) {
-    float t = 0.f;
-    constexpr int kBatch = 8;
-    for (int rc = 0; rc < n_chunks; rc += kBatch) {
-      float x[kBatch];
+  const int w = blockIdx.x, per = d / int(gridDim.y), groups = per / 4, share = 4 * kCfThreads / d;
+  const int u = int(threadIdx.x) / groups, ch = int(blockIdx.y) * per + (int(threadIdx.x) - u * groups) * 4;
+  const float* mine = pprobe + size_t(w) * n_chunks * d + ch;
+  f32x4 t = {0.f, 0.f, 0.f, 0.f};
+  auto add_chunks = [&](auto batch) {
+    constexpr int kBatch = decltype(batch)::value;
+    for (int rc = u; rc < n_chunks; rc += kBatch * share) {
+      f32x4 x[kBatch];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i)               // all loads first: they overlap
-        x[i] = pprobe[(size_t(w) * n_chunks + (rc + i < n_chunks ? rc + i : rc)) * d + ch];
+        x[i] = *reinterpret_cast<const f32x4*>(mine + size_t(rc + i * share < n_chunks ? rc + i * share : rc) * d);
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) t += rc + i < n_chunks ? x[i] : 0.f;
+      for (int i = 0; i < kBatch; ++i)
+        if (rc + i * share < n_chunks) t += x[i];
     }
-    t = uniform ? stat_in[size_t(w) * 3 * d + 2 * d + ch] : t * inv;
-    probe[ch] = t;
-    probe_lds[ch] = t;
-    ss += t * t;
+  };
+  if (u < share) {
+    if (n_chunks <= share) add_chunks(std::integral_constant<int, 1>{});
+    else if (n_chunks <= 8 * share) add_chunks(std::integral_constant<int, 8>{});
+    else add_chunks(std::integral_constant<int, 16>{});
   }
+  float total = 0.f;
+  for (int rc = threadIdx.x & 63; rc < n_chunks; rc += 64) total += asum[size_t(w) * asum_stride + rc];
+  total = wave_sum(total);
+  const bool uniform = !(total > 0.f);
+  const float inv = uniform ? 0.f : 1.f / total;
   if (weights_out != nullptr) {
-    for (int j = threadIdx.x; j < m; j += 1024)
+    for (int j = int(blockIdx.y * blockDim.x + threadIdx.x); j < m; j += int(gridDim.y * blockDim.x))
       weights_out[size_t(w) * m + j] = uniform ? 1.f / float(m) : a_rows[size_t(w) * m_pad + j] * inv;
   }
+  if (share > 1) {
+    part[threadIdx.x] = t;
+    __syncthreads();
+    if (u == 0)
+      for (int o = 1; o < min(share, n_chunks); ++o) t += part[o * groups + threadIdx.x];
+  }
+  float ss = 0.f;
+  if (u == 0) {
+    t = uniform ? *reinterpret_cast<const f32x4*>(stat_in + size_t(w) * 3 * d + 2 * d + ch) : t * inv;
+    *reinterpret_cast<f32x4*>(probe_out + size_t(w) * d + ch) = t;
+    *reinterpret_cast<f32x4*>(probe_lds + ch) = t;
+    ss = (t.x * t.x + t.y * t.y) + (t.z * t.z + t.w * t.w);
+  }
+  if (gridDim.y > 1) return;                         // (the scoring launch forms the norm and the per-KV-head sum)
   ss = block_sum(ss, red);                           // also orders the LDS writes before the reads below
   if (threadIdx.x == 0) probe_norm_out[w] = sqrtf(ss);
   const int g = n_q_heads / n_kv_heads;
   float* probe_kv = probe_kv_out + size_t(w) * n_kv_heads * head_dim;
-  for (int e = threadIdx.x; e < n_kv_heads * head_dim; e += 1024) {
+  for (int e = threadIdx.x; e < n_kv_heads * head_dim; e += kCfThreads) {
     const int hk = e / head_dim, dd = e - hk * head_dim;
-    float t = 0.f;
-    for (int i = 0; i < g; ++i) t += probe_lds[(hk * g + i) * head_dim + dd];
-    probe_kv[e] = t;
+    float kv = 0.f;
+    for (int i = 0; i < g; ++i) kv += probe_lds[(hk * g + i) * head_dim + dd];
+    probe_kv[e] = kv;
   }
 }
 
 constexpr int kWeighRows = 8;    // rows a thread takes per pass
-// The slabs' partials of one row, kBatch of them requested together: one round trip for 16 slabs, two for 64 (four as
-// 16 at a time: the probe of 256 tokens with 4096 channels 14.8 us, 13.5 so).
-template <int kBatch>
-__device__ __forceinline__ float slab_sum(const float* __restrict__ apart, int n_slabs, int m_pad) {
-  float t = 0.f;
-  for (int s0 = 0; s0 < n_slabs; s0 += kBatch) {
-    float p[kBatch];
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) p[i] = apart[size_t(s0 + i < n_slabs ? s0 + i : s0) * m_pad];
-#pragma unroll
-    for (int i = 0; i < kBatch; ++i) t += s0 + i < n_slabs ? p[i] : 0.f;
-  }
-  return t;
-}
 
 // grid (column slabs of 8*V channels, batch); 8 column lanes x RL row lanes.
 // Every workgroup adds the slabs' partials up to a_j (slab order), turns them into the
 // weights of Eq. (9) and sums w_j q_j over all rows for its channels.  The queries of the
-// first pass are requested before the partials, so both are in flight together.
+// first pass are requested before the partials, so both are in flight together.  The partials are read four rows to a
+// thread, at most 16 slabs to a thread while there are threads for the rest (instead of a row to a thread and all slabs one
+// after the other, four times as many loads; with one workgroup in four barriers more for 8 slabs: 0.6 us slower).
 template <typename T, int RL>
 __global__ __launch_bounds__(kColLanes * RL) void probe_weigh_kernel(const T* __restrict__ q_win,
                                                           const float* __restrict__ scratch,
@@ -615,7 +672,8 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_weigh_kernel(const T* __
   constexpr int kThreads = kColLanes * RL, kRows = RL * kWeighRows;      // threads, rows of a pass
   typedef typename Vec<T>::raw raw_t;
   __shared__ float red[32];
-  __shared__ float w_lds[kMaxWindow];
+  __shared__ __attribute__((aligned(16))) float w_lds[kMaxWindow];
+  __shared__ f32x4 part[kThreads];
   __shared__ float buf[kThreads / 64][SLAB];
   const int s = blockIdx.y;
   const T* q = q_win + size_t(s) * m * d;
@@ -635,12 +693,39 @@ __global__ __launch_bounds__(kColLanes * RL) void probe_weigh_kernel(const T* __
   };
   load_pass(0);
 
+  // thread (group of four rows, slab lane u): slabs u, u + share, ...  (m_pad is a multiple of 16; rows from m on hold 0)
   float tsum = 0.f;
-  for (int j = threadIdx.x; j < m && !mean_pooling; j += kThreads) {
-    const float t = n_slabs <= 8 ? slab_sum<8>(apart + j, n_slabs, m_pad) : n_slabs <= 16 ? slab_sum<16>(apart + j, n_slabs, m_pad)
-                                                                              : slab_sum<32>(apart + j, n_slabs, m_pad);
-    w_lds[j] = t;
-    tsum += t;
+  if (!mean_pooling) {
+    constexpr int kBatch = 16;
+    const int groups = m_pad / 4, u = int(threadIdx.x) / groups;
+    const int share = max(min(kThreads / groups, (n_slabs + kBatch - 1) / kBatch), 1);
+    for (int g = int(threadIdx.x) - u * groups; g < groups && u < share; g += kThreads) {
+      f32x4 t = {0.f, 0.f, 0.f, 0.f};
+      for (int s0 = u; s0 < n_slabs; s0 += kBatch * share) {
+        f32x4 p[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)             // all loads first: they overlap
+          p[i] = *reinterpret_cast<const f32x4*>(apart + size_t(s0 + i * share < n_slabs ? s0 + i * share : s0) * m_pad + 4 * g);
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+          if (s0 + i * share < n_slabs) t += p[i];
+      }
+      if (share == 1) {
+        *reinterpret_cast<f32x4*>(w_lds + 4 * g) = t;
+        tsum += (t.x + t.y) + (t.z + t.w);
+      } else {
+        part[threadIdx.x] = t;
+      }
+    }
+    if (share > 1) {
+      __syncthreads();
+      if (int(threadIdx.x) < groups) {
+        f32x4 t = part[threadIdx.x];
+        for (int o = 1; o < min(share, n_slabs); ++o) t += part[o * groups + threadIdx.x];
+        *reinterpret_cast<f32x4*>(w_lds + 4 * threadIdx.x) = t;
+        tsum = (t.x + t.y) + (t.z + t.w);
+      }
+    }
   }
   const float total = block_sum(tsum, red);          // |Phi|_1; orders the LDS writes as well
   const float inv_total = total > 0.f ? 1.f / total : 0.f;
@@ -734,11 +819,13 @@ __global__ __launch_bounds__(1024) void probe_identity_kernel(
                          probe_lds, red);
 }
 
-// A long window of few channels is a chain of one: a slab has one workgroup however long the window is (4096 tokens:
-// 512 channels 32.6 us in slabs, 22.6 row by row; 1024 channels 33.0, 28.9; but 2048 tokens of 1024 channels 20.8, 23.5,
-// and 4096 channels never).
+// A long window is a chain of one: a slab has one workgroup however long the window is, and holds 2048 rows in registers.
+// A window's step without its attention, in slabs / row by row: 2048 tokens 24.2 / 25.1 us (512 channels), 25.2 / 27.1 (1024),
+// 25.7 / 30.1 (2048); 2112 tokens 30.2 / 24.8, 31.8 / 26.8, 34.2 / 31.3; 4096 tokens 35.3 / 26.1, 37.3 / 28.3, 39.8 / 32.5.
+// With 4096 channels the slabs are many: 2112 tokens 38.0 / 44.2, 3584 tokens 45.5 / 47.5, 4096 tokens 48.7 / 47.6.
 static bool long_window(const actqkv_shape& sh, int batch, int m, int update_stats) {
-  return batch == 1 && (update_stats & ACTQKV_STATS_UPDATE) && m >= 2048 && m >= 4 * sh.n_q_heads * sh.head_dim;
+  const int d = sh.n_q_heads * sh.head_dim;
+  return batch == 1 && (update_stats & ACTQKV_STATS_UPDATE) && m > 2048 && (d <= 2048 || (d <= 64 * 64 && m >= 4096));
 }
 
 template <typename T>
@@ -757,7 +844,7 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
   const int mean_pooling = (update_stats & ACTQKV_PROBE_MEAN_POOLING) != 0;
   if ((update_stats & ACTQKV_PROBE_WINDOW_CHAIN) || long_window(sh, batch, m, update_stats)) {
     // the batch entries are consecutive windows of one sequence with one set of statistics
-    if (d > 64 * 64) {          // (not a long window: 4 d is more than the longest)
+    if (d > 64 * 64) {          // (not a long window)
       // rows wider than a wavefront of the row-major kernels holds: window after window
       const int dk = sh.n_kv_heads * sh.head_dim;
       for (int w = 0; w < batch; ++w) {
@@ -783,7 +870,7 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
                        stream, q_win, stats, part, m, d, n_chunks, cols);
     for (int w = 0; w < batch; w += kChainTile) {
       const int n = std::min(batch - w, kChainTile);
-      hipLaunchKernelGGL(probe_chain_stats_kernel<T>, dim3((d + 31) / 32), dim3(1024), size_t(n) * 64 * sizeof(float), stream,
+      hipLaunchKernelGGL(probe_chain_stats_kernel<T>, dim3((d + 31) / 32), dim3(1024), size_t(n) * 66 * sizeof(float), stream,
                          q_win + size_t(w) * m * d, part + size_t(w) * n_chunks * 2 * d, stats, stat + size_t(w) * 3 * d, n, m, d,
                          n_chunks, eps, float(w) * float(m), int(batch == 1));
     }
@@ -807,21 +894,29 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
     else if (groups <= 256) bias_weigh(probe_rows_bias_weigh_kernel<T, 4, 8, 2>, 4, 8);
     else if (groups <= 512) bias_weigh(probe_rows_bias_weigh_kernel<T, 8, 4, 1>, 8, 4);
     else if constexpr (V == 4) bias_weigh(probe_rows_bias_weigh_kernel<T, 16, 4, 1>, 16, 4);   // (4096 channels of 16 bits are 512)
-    hipLaunchKernelGGL(probe_chain_finish_kernel, dim3(batch), dim3(1024), size_t(d) * sizeof(float), stream, pprobe,
+    // One window, whose norm and per-KV-head sum the scoring launch forms, or, for wide rows, a launch of their own (4096
+    // tokens with 4096 channels: 40.9 us, one workgroup for all of it 46.2).
+    const bool spread = batch == 1 && d % 256 == 0 && (!finish || d > 2048);
+    const int slabs = spread ? d / 256 : 1;
+    hipLaunchKernelGGL(probe_chain_finish_kernel, dim3(batch, slabs), dim3(spread ? 64 * (4 * kCfThreads / d) : kCfThreads),
+                       size_t(d) * sizeof(float), stream, pprobe,
                        asum, a_rows, stat, probe, probe_kv, probe_norm, weights, m, m_pad, d, n_parts, asum_stride,
                        sh.n_q_heads, sh.n_kv_heads, sh.head_dim);
+    if (spread && finish)
+      hipLaunchKernelGGL(probe_finish_kernel, dim3(1), dim3(kFinishThreads), 0, stream, probe, probe_kv, probe_norm,
+                         sh.n_q_heads, sh.n_kv_heads, sh.head_dim);
     return hip_status("probe");
   }
   update_stats &= ACTQKV_STATS_UPDATE;
   if (update_stats || (m > 1 && !mean_pooling)) {
-    // the fewest row lanes that hold the window in registers, 128 at most (a workgroup has 1024 threads)
     auto launch = [&](auto kernel, int row_lanes) {
       hipLaunchKernelGGL(kernel, dim3(n_slabs, batch), dim3(kColLanes * row_lanes), 0, stream, q_win, stats, scratch,
                          update_stats, m, m_pad, d, eps, stats_stride, scratch_stride);
     };
-    if (m <= 32 * kRowsPerThread) launch(probe_stats_bias_kernel<T, 32>, 32);
-    else if (m <= 64 * kRowsPerThread) launch(probe_stats_bias_kernel<T, 64>, 64);
-    else launch(probe_stats_bias_kernel<T, 128>, 128);
+    if (m <= 64 * 4) launch(probe_stats_bias_kernel<T, 64, 4>, 64);
+    else if (m <= 64 * 8) launch(probe_stats_bias_kernel<T, 64, 8>, 64);
+    else if (m <= 128 * 8) launch(probe_stats_bias_kernel<T, 128, 8>, 128);
+    else launch(probe_stats_bias_kernel<T, 128, 16>, 128);
   }
   if (m == 1) {
     hipLaunchKernelGGL(probe_identity_kernel<T>, dim3(batch), dim3(1024), size_t(d) * sizeof(float),
@@ -843,7 +938,7 @@ static int launch_probe_t(const actqkv_shape& sh, int batch, int m, const T* q_w
 }
 
 bool probe_finish_apart(const actqkv_shape& sh, int batch, int m, int update_stats) {
-  return batch == 1 && m > 1 && !(update_stats & ACTQKV_PROBE_WINDOW_CHAIN) && !long_window(sh, batch, m, update_stats);
+  return batch == 1 && m > 1;
 }
 
 int launch_probe(const actqkv_shape& sh, int batch, int m, const void* q_win, float* stats,

@@ -2623,6 +2623,41 @@ def test_probe_of_consecutive_windows_in_one_call(dtype, hq, hkv, d, m, calls):
         B.build_probe(cs, 2, m, qd[:2], stats, B.PROBE_WINDOW_CHAIN, probe[:2], probe_kv[:2], norm[:2], None, ws)
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,d,m", [
+    ("bf16", 2, 2, 64, 256), ("bf16", 8, 2, 64, 257),            # 4 and 8 rows to a thread, 2 and 8 slabs
+    ("fp32", 6, 2, 64, 512), ("bf16", 18, 3, 64, 513),           # 12 slabs; 18: two threads share a group of four rows
+    ("bf16", 32, 8, 128, 1024), ("bf16", 32, 8, 128, 1025),      # 64 slabs; 8 and 16 rows to a thread
+    ("bf16", 18, 3, 64, 2048), ("bf16", 40, 8, 128, 2100),       # the largest window in registers; more, with rows too wide for the other way
+    ("fp32", 8, 2, 128, 2049), ("bf16", 28, 4, 128, 4096),       # long windows row by row: 1024 / 256 and 3584 / 256 workgroups at the end
+    ("bf16", 5, 1, 64, 2200),                                    # 320 channels: one workgroup, 12 threads to four channels
+])
+def test_probe_of_one_window_at_the_edges_of_its_kernels(dtype, hq, hkv, d, m):
+    """Two windows, the first without a history: statistics, probe, weights, norm and per-KV-head sum against the oracle."""
+    sh = LayerShape(hq, hkv, d, 128, 4, 128, 256, dtype)
+    cs, dd = B.c_shape(sh), hq * d
+    _say(f"[case] probe {dtype} H{hq}/Hk{hkv}/D{d} m={m}")
+    g = torch.Generator().manual_seed(m + dd)
+    q = torch.randn(2, m, hq, d, generator=g) * torch.tensor([1.0, 1.5]).view(2, 1, 1, 1) + torch.tensor([0.0, 0.3]).view(2, 1, 1, 1)
+    q = q.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    stats = torch.zeros(B.stats_floats(cs), device=DEV)
+    ws = torch.zeros(B.workspace_bytes(cs, 1, m, 8, 4), dtype=torch.uint8, device=DEV)
+    probe, kv, norm, w = (torch.zeros(x, device=DEV) for x in (dd, hkv * d, 1, m))
+    rs = orc.RunningStats(dd)
+    for t in range(2):
+        B.build_probe(cs, 1, m, q[t].to(DEV), stats, B.STATS_UPDATE, probe, kv, norm, w, ws)
+        torch.cuda.synchronize()
+        qw = f64(q[t]).reshape(m, dd)
+        want, w_want = orc.probe_query(qw, orc.activation_bias(qw, *rs.update(qw)))
+        assert rel_to_max(probe, want) < TOL_PROBE
+        assert rel_to_max(w, w_want) < TOL_WEIGHT
+        assert abs(float(norm) - np.linalg.norm(want)) < TOL_PROBE * np.linalg.norm(want)
+        assert rel_to_max(kv, want.reshape(hkv, hq // hkv, d).sum(axis=1).reshape(-1)) < TOL_PROBE
+    st = f64(stats)
+    assert st[0] == 2 * m
+    assert rel_to_max(st[4:4 + dd], rs.mean) < 1e-5
+    assert rel_to_max(st[4 + dd:4 + 2 * dd], rs.m2) < 1e-4
+
+
 @pytest.mark.parametrize("m", [4096, 2563, 512])
 def test_statistics_where_the_first_query_lies_far_from_the_others(m):
     """A window whose first query is K away from the old mean, which the sums of the window are about: M2 grows by K^2,
