@@ -8,6 +8,7 @@
 
 #include "common.h"
 #include "launch.h"
+#include "select_body.h"
 
 namespace actqkv {
 
@@ -106,7 +107,7 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
                                   const int32_t* n_sel, int k_cap, void* out, float* lse,
                                   const PfSplits& splits, float* scratch, unsigned int* counters,
                                   float scale, int sel_per_head, int first_cus, int late_cus,
-                                  hipStream_t stream, hipStream_t stream_late);
+                                  hipStream_t stream, hipStream_t stream_late, const SelectInside* inside);
 
 bool prefill_f32_supported(const actqkv_shape& sh, int m);
 size_t prefill_f32_scratch_bytes(const actqkv_shape& sh, int batch, int m);
@@ -115,7 +116,7 @@ int launch_attention_prefill_f32(const actqkv_shape& sh, int batch, int m, const
                                  const void* v_cache, int64_t seq_stride, int nb_capacity, const int32_t* n_ctx,
                                  const int32_t* idx, const int32_t* n_sel, int k_cap, void* out, float* lse,
                                  float* scratch, float scale, int sel_per_head,
-                                 hipStream_t stream);
+                                 hipStream_t stream, const SelectInside* inside);
 bool decode_fused_supported(const actqkv_shape& sh);
 size_t decode_mfma_scratch_floats(const actqkv_shape& sh, int batch, int k_cap);
 int launch_attention_decode_mfma(const actqkv_shape& sh, int batch, const void* q, const void* k_cache,
@@ -164,14 +165,14 @@ static size_t workspace_bytes_upto(const actqkv_shape& sh, int batch, int m, int
   if (prefill_mfma_supported(sh, m)) need = kCounterBytes + prefill_partials_most(sh, batch, m);
   for (int b = 1; b <= batch; ++b) need = std::max(need, workspace_bytes(sh, b, 1, nb_capacity, k_cap));
   need = std::max(need, kCounterBytes + align_up(probe_call_floats(sh, batch, m) * sizeof(float), 256));
-  return need;
+  return need + 256;   // Workspace::spare
 }
 
 int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, const void* k_cache,
                      const void* v_cache, int64_t seq_stride, int nb_capacity, const int32_t* n_ctx,
                      const int32_t* idx, const int32_t* n_sel, int k_cap, void* out, float* lse,
                      const Workspace& ws, int sel_per_head, hipStream_t stream, int first_cus, int late_cus,
-                     hipStream_t stream_late, bool pieces_of_one) {
+                     hipStream_t stream_late, bool pieces_of_one, const SelectInside* inside) {
   const float scale = sh.softmax_scale > 0.f ? sh.softmax_scale : 1.f / std::sqrt(float(sh.head_dim));
   if (m == 1)   // (no queue: one launch does all the work)
     return launch_attention_decode_mfma(sh, batch, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx,
@@ -183,9 +184,9 @@ int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, co
                                          pieces_of_one ? prefill_splits(sh, 1, m, k_cap, kChipCus)
                                                        : prefill_splits(sh, batch, m, k_cap, first_cus), ws.scratch_f32(),
                                          ws.counters(), scale, sel_per_head, first_cus, late_cus, stream,
-                                         stream_late);
+                                         stream_late, inside);
   return launch_attention_prefill_f32(sh, batch, m, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx, idx, n_sel,
-                                      k_cap, out, lse, ws.scratch_f32(), scale, sel_per_head, stream);
+                                      k_cap, out, lse, ws.scratch_f32(), scale, sel_per_head, stream, inside);
 }
 
 // Host-side checks of an attention call; `need` receives the scratch bytes the call uses.
@@ -446,7 +447,26 @@ int actqkv_window_step(const actqkv_shape* shape, int batch, int m, const void* 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const bool apart = nb_scored > nb_begin && probe_finish_apart(*shape, batch, m, update_stats);
   ACTQKV_TRY(launch_probe(*shape, batch, m, q_win, stats, update_stats, probe, probe_kv, probe_norm, weights, ws, st, !apart));
-  ACTQKV_TRY(apart ? launch_score_probe(*shape, probe, probe_kv, probe_norm, rep_keys, nb_scored, nb_begin, nb_end, scores, st)
+  // The selection inside the attention launch: the scoring launch keeps a copy of the budget for it behind what the call
+  // needs of the workspace (a workspace without those bytes: a launch of its own).  Four windows of 512 tokens at 64K with the
+  // selection as a launch of its own 244 us, inside 236; of 256 tokens with 64 channels 133, 128.
+  float* copy = ws.spare(need);
+  if (apart && copy != nullptr && select_inside_supported(nb_scored - nb_begin, k_cap, flags)) {
+    ACTQKV_TRY(launch_score_probe(*shape, probe, probe_kv, probe_norm, rep_keys, nb_scored, nb_begin, nb_end, scores,
+                                  budget_remaining, copy, st));
+    SelectInside inside;
+    inside.scores = scores;
+    inside.nb_begin = nb_begin;
+    inside.nb_capacity = nb_scored;
+    inside.nb_end = nb_end;
+    inside.entropy_topk = (flags & ACTQKV_SELECT_ENTROPY_TOPK) != 0;
+    inside.io = SelectIo{budget_remaining != nullptr ? copy : nullptr, theta_rest_sum, budget_remaining, idx, n_sel, theta, budget, false};
+    if (flags & ACTQKV_SELECT_GIVEN_COUNT) inside.io.count_in = n_sel;   // (clamped twice it is the same)
+    return launch_attention(*shape, batch, m, q_win, k_cache, v_cache, cache_seq_stride, nb_capacity, n_ctx, idx, n_sel, k_cap,
+                            out, lse, ws, 0, st, kChipCus, 0, nullptr, false, &inside);
+  }
+  ACTQKV_TRY(apart ? launch_score_probe(*shape, probe, probe_kv, probe_norm, rep_keys, nb_scored, nb_begin, nb_end, scores,
+                                        nullptr, nullptr, st)
                    : launch_score(*shape, batch, probe_kv, probe_norm, rep_keys, rep_seq_stride, nb_scored, nb_begin, nb_end,
                                   scores, score_stride, st));
   ACTQKV_TRY(launch_select(batch, scores, score_stride, nb_scored, nb_begin, nb_end, k_cap, flags, budget_remaining,

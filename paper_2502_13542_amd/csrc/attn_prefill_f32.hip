@@ -32,6 +32,7 @@
 
 #include "common.h"
 #include "launch.h"
+#include "select_body.h"
 
 namespace actqkv {
 
@@ -70,6 +71,7 @@ struct FfParams {
   int per_chip;            // query tiles whose workgroups make one for every compute unit
   int sel_per_head;
   float scale_log2e;
+  SelectInside sel;        // one sequence: its selection is made here
 };
 
 // Two fp32 values times a power of two -> the packed halves hi (rounded) and lo (what the rounding left, rounded).
@@ -126,6 +128,8 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
   extern __shared__ __attribute__((aligned(16))) char ff_lds[];   // [stage][K hi, K lo, V^T hi, V^T lo]
   __shared__ float factors[2][2][4];                // [stage][K: what scores are multiplied by, V: what values were][wavefront]
   __shared__ int32_t idx_lds[64];
+  __shared__ SelectWaveLds sel_lds;
+  __shared__ int sel_count;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, half = lane >> 5;
   const int group = p.n_q_heads / p.n_kv_heads;
@@ -143,20 +147,17 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
     if ((turn & 1) && (turn + 1) * p.per_chip <= p.n_qtiles) qtile = (2 * turn + 1) * p.per_chip - 1 - qtile;
   }
 
+  // (the last wavefront selects before it asks for anything else; the others have the first tile and their queries on the way)
+  const bool inside = p.sel.scores != nullptr;
   const size_t sel_row = p.sel_per_head ? size_t(s) * p.n_kv_heads + hk : size_t(s);
-  const int32_t my_idx = tid < p.k_cap ? p.idx[sel_row * p.k_cap + tid] : -1;
-  const int n_ctx_raw = p.n_ctx[s], n_sel_raw = p.n_sel[sel_row];
-  if (tid < 64) idx_lds[tid] = my_idx;
-  __syncthreads();
+  const int32_t my_idx = !inside && tid < p.k_cap ? p.idx[sel_row * p.k_cap + tid] : -1;
+  const int n_ctx_raw = p.n_ctx[s];
+  int n_sel_raw = inside ? 0 : p.n_sel[sel_row];
+  if (inside && wave == kFfWaves - 1) p.sel.run(p.k_cap, blockIdx.x == 0, sel_lds, idx_lds, &sel_count);
   const int n_ctx = min(max(n_ctx_raw, p.m), p.nb_capacity * kBlock);
   const WindowGeom g = window_geom(n_ctx, p.m, p.n_init, p.n_local);
   const int row_end = p.m * group;
   const int row_hi = (min((qtile + 1) * kFfRows, row_end) - 1) / group;
-  const TileList tl = make_tile_list(g, g.w0 + row_hi, idx_lds, n_sel_raw, p.k_cap, p.nb_capacity);
-  const int n_tiles = tl.count() * kPerBlock;
-  const int per = (n_tiles + p.splits - 1) / p.splits;
-  const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
-
   const int frow0 = qtile * kFfRows + wave * 32;             // first query row of this wavefront
   const bool wave_ok = frow0 < row_end;
   const int wpos_lo = g.w0 + min(frow0, row_end - 1) / group;
@@ -186,13 +187,6 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
   const char* vbase = reinterpret_cast<const char*>(p.v_cache + size_t(s) * p.seq_stride);
   constexpr uint32_t kBlockBytes = uint32_t(kBlock) * D * 4;
   struct Tile { int key0, lo, hi; };                         // first key, and the visible span within the tile
-  auto tile_at = [&](int t) {
-    int block, lo, hi;
-    tl.get(t / kPerBlock, block, lo, hi);
-    const int key0 = block * kBlock + (t % kPerBlock) * kKeys;
-    return Tile{__builtin_amdgcn_readfirstlane(key0), __builtin_amdgcn_readfirstlane(max(lo, key0)),
-                __builtin_amdgcn_readfirstlane(min(hi, key0 + kKeys))};
-  };
   auto block_offset = [&](int key0) { return (size_t(key0 / kBlock) * p.n_kv_heads + hk) * kBlockBytes; };
   f32x4 xk[4], xv[4];                                        // a tile on its way
   auto fetch_tile = [&](const Tile& t) {
@@ -268,11 +262,10 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
     }
   };
 
+  // the first piece begins with the initial tokens, whatever is selected
   Tile now{0, 0, 0}, next{0, 0, 0};
-  if (t_begin < t_end) {
-    now = tile_at(t_begin);
-    fetch_tile(now);
-  }
+  const bool early = split == 0 && g.i0 > 0;
+  if (early) fetch_tile(now);
   // ---- the queries: channels 16 j + 8 half .. + 7 of this lane's row, as halves of their multiples by 2^q_exp
   const float* qrow = p.q + ((size_t(s) * p.m + my_row) * p.n_q_heads + head) * D;
   u32x4 qh[kQ], ql[kQ];
@@ -304,6 +297,24 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
         qh[j][i] = h;
         ql[j][i] = l;
       }
+  }
+  if (!inside && tid < 64) idx_lds[tid] = my_idx;
+  __syncthreads();
+  if (inside) n_sel_raw = sel_count;
+  const TileList tl = make_tile_list(g, g.w0 + row_hi, idx_lds, n_sel_raw, p.k_cap, p.nb_capacity);
+  const int n_tiles = tl.count() * kPerBlock;
+  const int per = (n_tiles + p.splits - 1) / p.splits;
+  const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
+  auto tile_at = [&](int t) {
+    int block, lo, hi;
+    tl.get(t / kPerBlock, block, lo, hi);
+    const int key0 = block * kBlock + (t % kPerBlock) * kKeys;
+    return Tile{__builtin_amdgcn_readfirstlane(key0), __builtin_amdgcn_readfirstlane(max(lo, key0)),
+                __builtin_amdgcn_readfirstlane(min(hi, key0 + kKeys))};
+  };
+  if (t_begin < t_end) {
+    now = tile_at(t_begin);
+    if (!early) fetch_tile(now);
   }
   f32x16 acc_o[kDb];
 #pragma unroll
@@ -613,8 +624,9 @@ int launch_attention_prefill_f32(const actqkv_shape& sh, int batch, int m, const
                                  const void* v_cache, int64_t seq_stride, int nb_capacity, const int32_t* n_ctx,
                                  const int32_t* idx, const int32_t* n_sel, int k_cap, void* out, float* lse,
                                  float* scratch, float scale, int sel_per_head,
-                                 hipStream_t stream) {
+                                 hipStream_t stream, const SelectInside* inside) {
   FfParams p;
+  if (inside != nullptr) p.sel = *inside;
   p.q = static_cast<const float*>(q);
   p.k_cache = static_cast<const float*>(k_cache);
   p.v_cache = static_cast<const float*>(v_cache);

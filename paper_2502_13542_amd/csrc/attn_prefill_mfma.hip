@@ -34,6 +34,7 @@
 
 #include "common.h"
 #include "launch.h"
+#include "select_body.h"
 
 namespace actqkv {
 
@@ -111,6 +112,14 @@ struct PfParams {
   int sel_per_head;                 // 1: idx and n_sel have a row per (sequence, KV head), 0: per sequence
   unsigned int* queue;              // per KV head: items handed out beyond the first round; [kPfQueueDone]: workgroups that left
   float scale_log2e;
+  SelectInside sel;                 // one sequence: its selection is made here
+};
+
+// The selection of a work item in LDS.
+struct PfChosen {
+  int32_t idx[64];
+  int count;                        // (with PfParams::sel)
+  SelectWaveLds work;
 };
 
 // Final normalisation and store of one lane's share of a query row:
@@ -136,7 +145,7 @@ __device__ __forceinline__ void store_rows(const PfParams& p, const f32x16 (&acc
 
 // One work item: piece `slot` of the query tiles of (sequence s, KV head hk).  kTwoTermP: see prefill_two_terms.
 template <int D, int KS, bool kTwoTermP, bool kInLoop>
-__device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* lds, int hk, int slot, int s) {
+__device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* lds, PfChosen& chosen, int hk, int slot, int s) {
   constexpr int kDb = D / 32, kKs = D / 16;      // 32-channel groups of the output, 16-channel steps of a score
   constexpr int kRows = kPfRows<KS>, kRowGroups = kPfWaves / KS;   // query rows, groups of 32 of them
   constexpr int kNg = 4 / KS;                    // 32-key groups of a tile that are this wavefront's
@@ -165,24 +174,21 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
   }
 
   // the selected block indices are requested together with the two scalars they are used
-  // with, not after them (one memory round trip less before the first tile can be fetched)
-  __shared__ int32_t idx_lds[64];
+  // with, not after them (one memory round trip less before the first tile can be fetched); or the last wavefront
+  // selects, before it asks for anything else
+  const bool inside = p.sel.scores != nullptr;
   const size_t sel_row = p.sel_per_head ? size_t(s) * p.n_kv_heads + hk : size_t(s);
-  const int32_t my_idx = tid < p.k_cap ? p.idx[sel_row * p.k_cap + tid] : -1;
-  const int n_ctx_raw = p.n_ctx[s], n_sel_raw = p.n_sel[sel_row];
-  if (tid < 64) idx_lds[tid] = my_idx;
-  __syncthreads();
+  const int32_t my_idx = !inside && tid < p.k_cap ? p.idx[sel_row * p.k_cap + tid] : -1;
+  const int n_ctx_raw = p.n_ctx[s];
+  int n_sel_raw = inside ? 0 : p.n_sel[sel_row];
+  if (!kInLoop && inside && wave == kPfWaves - 1)
+    p.sel.run(p.k_cap, blockIdx.x == 0, chosen.work, chosen.idx, &chosen.count);
   const int n_ctx = min(max(n_ctx_raw, p.m), p.nb_capacity * kBlock);
   const WindowGeom g = window_geom(n_ctx, p.m, p.n_init, p.n_local);
   // The query rows of a (sequence, KV head) are numbered position by position, the G heads of a
   // position next to each other; a workgroup takes kRows consecutive ones, a wavefront 32.
   const int row_end = p.m * group;
   const int row_hi = (min((qtile + 1) * kRows, row_end) - 1) / group;
-  const TileList tl = make_tile_list(g, g.w0 + row_hi, idx_lds, n_sel_raw, p.k_cap, p.nb_capacity);
-  const int n_tiles = tl.count();
-  const int per = (n_tiles + splits - 1) / splits;
-  const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
-
   const int frow0 = qtile * kRows + rg * 32;                 // first query row of this wavefront
   const bool wave_ok = frow0 < row_end;
   const int wpos_lo = g.w0 + min(frow0, row_end - 1) / group;         // positions of its first and last row
@@ -242,13 +248,6 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     const int vr = (kLoads * wave + i) * 4 + (lane >> 4);
     gv[i] = uint32_t(vr) * 256 + (uint32_t((lane & 15) ^ (vr & 15)) << 4);
   }
-  // tile t of the list -> its block and visible span, in scalar registers
-  auto tile_at = [&](int t, int& block, int& lo, int& hi) {
-    tl.get(t, block, lo, hi);
-    block = __builtin_amdgcn_readfirstlane(block);
-    lo = __builtin_amdgcn_readfirstlane(lo);
-    hi = __builtin_amdgcn_readfirstlane(hi);
-  };
   auto fetch_tile = [&](int block, int stage) {
     const size_t off = (size_t(block) * p.n_kv_heads + hk) * kTileBytes;
     const char* kt = uniform_ptr(kc + off);
@@ -262,11 +261,29 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
       __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (__attribute__((address_space(3))) void*)(dst + kTileBytes + i * 1024), 16, gv[i], 0, 0, 0);
     }
   };
+  // the first piece begins with the initial tokens, whatever is selected
+  const bool early = split == 0 && g.i0 > 0;
+  if (early) fetch_tile(0, 0);
+  if (!inside && tid < 64) chosen.idx[tid] = my_idx;
+  __syncthreads();
+  if (inside) n_sel_raw = chosen.count;
+  const TileList tl = make_tile_list(g, g.w0 + row_hi, chosen.idx, n_sel_raw, p.k_cap, p.nb_capacity);
+  const int n_tiles = tl.count();
+  const int per = (n_tiles + splits - 1) / splits;
+  const int t_begin = split * per, t_end = min(n_tiles, t_begin + per);
+
+  // tile t of the list -> its block and visible span, in scalar registers
+  auto tile_at = [&](int t, int& block, int& lo, int& hi) {
+    tl.get(t, block, lo, hi);
+    block = __builtin_amdgcn_readfirstlane(block);
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    hi = __builtin_amdgcn_readfirstlane(hi);
+  };
 
   int block = 0, lo = 0, hi = 0;
   if (t_begin < t_end) {
     tile_at(t_begin, block, lo, hi);
-    fetch_tile(block, 0);
+    if (!early) fetch_tile(block, 0);
   }
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
@@ -607,15 +624,20 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
 template <int D, int KS, bool kTwoTermP>
 __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_kernel(PfParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  __shared__ PfChosen chosen;
   const int item = blockIdx.x / p.n_kv_heads, s = item / p.slots;
-  attn_prefill_item<D, KS, kTwoTermP, false>(p, lds, blockIdx.x % p.n_kv_heads, item - s * p.slots, s);
+  attn_prefill_item<D, KS, kTwoTermP, false>(p, lds, chosen, blockIdx.x % p.n_kv_heads, item - s * p.slots, s);
 }
 
 template <int D, int KS, bool kTwoTermP>
 __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_queued_kernel(PfParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   __shared__ int next_item;
+  __shared__ PfChosen chosen;
   const int hk = blockIdx.x % p.n_kv_heads;
+  // (one window: the same selection for all of its items; the barrier of the first item is behind it)
+  if (p.sel.scores != nullptr && threadIdx.x >= kPfThreads - 64)
+    p.sel.run(p.k_cap, blockIdx.x == 0, chosen.work, chosen.idx, &chosen.count);
   auto draw = [&]() {
     if (threadIdx.x == 0)
       next_item = p.wgs_per_head + int(__hip_atomic_fetch_add(p.queue + hk, 1u, __ATOMIC_RELAXED,
@@ -653,7 +675,7 @@ __global__ __launch_bounds__(kPfThreads) void attn_prefill_mfma_queued_kernel(Pf
       s = order[s];
       slot = p.slots - 1 - slot;
     }
-    attn_prefill_item<D, KS, kTwoTermP, true>(p, lds, hk, __builtin_amdgcn_readfirstlane(slot), __builtin_amdgcn_readfirstlane(s));
+    attn_prefill_item<D, KS, kTwoTermP, true>(p, lds, chosen, hk, __builtin_amdgcn_readfirstlane(slot), __builtin_amdgcn_readfirstlane(s));
     __syncthreads();                         // everybody is done with the LDS tiles of this item
     item = draw();
   }
@@ -793,8 +815,9 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
                                   const int32_t* n_sel, int k_cap, void* out, float* lse,
                                   const PfSplits& splits, float* scratch, unsigned int* counters,
                                   float scale, int sel_per_head, int first_cus, int late_cus,
-                                  hipStream_t stream, hipStream_t stream_late) {
+                                  hipStream_t stream, hipStream_t stream_late, const SelectInside* inside) {
   PfParams p;
+  if (inside != nullptr) p.sel = *inside;
   p.q = static_cast<const uint16_t*>(q);
   p.k_cache = static_cast<const uint16_t*>(k_cache);
   p.v_cache = static_cast<const uint16_t*>(v_cache);

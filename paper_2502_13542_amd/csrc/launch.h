@@ -103,6 +103,11 @@ struct Workspace {
   float* scratch_f32() const {
     return reinterpret_cast<float*>(static_cast<char*>(base) + kCounterBytes);
   }
+  // four bytes at its end that no launch of a call which needs `need` bytes uses, or NULL
+  float* spare(size_t need) const {
+    const size_t at = bytes / 16 * 16;
+    return at >= 16 && at - 16 >= need ? reinterpret_cast<float*>(static_cast<char*>(base) + at - 16) : nullptr;
+  }
 };
 
 // ---- launchers (one per entry point; arguments already validated) ----------
@@ -114,10 +119,13 @@ bool probe_finish_apart(const actqkv_shape& sh, int batch, int m, int update_sta
 int launch_score(const actqkv_shape& sh, int batch, const float* probe_kv, const float* probe_norm,
                  const void* rep_keys, int64_t seq_stride, int nb_capacity, int nb_begin,
                  const int32_t* nb_end, float* scores, int64_t score_stride, hipStream_t stream);
-// one sequence: norm and per-KV-head sum of the probe, and the scores, in one launch (at least one block)
+// one sequence: norm and per-KV-head sum of the probe, and the scores, in one launch (at least one block); budget, if not
+// NULL, is copied for a selection inside the attention launch
 int launch_score_probe(const actqkv_shape& sh, const float* probe, float* probe_kv, float* probe_norm,
                        const void* rep_keys, int nb_capacity, int nb_begin, const int32_t* nb_end, float* scores,
-                       hipStream_t stream);
+                       const float* budget, float* budget_copy, hipStream_t stream);
+struct SelectInside;
+bool select_inside_supported(int n_blocks, int k_cap, int flags);   // whether an attention launch can make this selection itself
 int launch_select(int batch, const float* scores, int64_t score_stride, int nb_capacity, int nb_begin,
                   const int32_t* nb_end, int k_cap, int flags, float* budget_remaining,
                   const float* theta_rest_sum, int32_t* idx, int32_t* n_sel, float* theta,
@@ -128,7 +136,8 @@ int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, co
                      const Workspace& ws, int sel_per_head, hipStream_t stream, int first_cus = kChipCus,
                      int late_cus = 0, hipStream_t stream_late = nullptr,   // late_cus > 0: a second team of
                                                        // workgroups for the queue, on stream_late
-                     bool pieces_of_one = false);      // cut the key tiles as in a call with one batch entry
+                     bool pieces_of_one = false,       // cut the key tiles as in a call with one batch entry
+                     const SelectInside* inside = nullptr);   // m > 1, one sequence: the selection is made in this launch
 int launch_score_per_head(const actqkv_shape& sh, int batch, const float* probe, const void* rep_keys,
                           int64_t seq_stride, int nb_capacity, int nb_begin, const int32_t* nb_end,
                           float* scores, int64_t score_stride, hipStream_t stream);

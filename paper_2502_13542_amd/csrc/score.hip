@@ -50,7 +50,8 @@ __global__ __launch_bounds__(1024) void score_probe_kernel(const float* __restri
                                                            float* __restrict__ probe_norm, const T* __restrict__ rep_keys,
                                                            int nb_capacity, int nb_begin, const int32_t* __restrict__ nb_end,
                                                            float* __restrict__ scores, int n_rep, int key_len, int group,
-                                                           int head_dim, float inv_sqrt_g) {
+                                                           int head_dim, float inv_sqrt_g, const float* __restrict__ budget,
+                                                           float* __restrict__ budget_copy) {
   extern __shared__ __attribute__((aligned(16))) float probe_lds[];  // [key_len]
   __shared__ float red[32];
   constexpr int kHeads = 8;                                          // the largest group
@@ -89,7 +90,10 @@ __global__ __launch_bounds__(1024) void score_probe_kernel(const float* __restri
   if (blockIdx.x == 0) {
     for (int e = e0; e < key_len; e += step)
       *reinterpret_cast<f32x4*>(probe_kv + e) = *reinterpret_cast<const f32x4*>(probe_lds + e);
-    if (threadIdx.x == 0) *probe_norm = pn;
+    if (threadIdx.x == 0) {
+      *probe_norm = pn;
+      if (budget != nullptr) *budget_copy = *budget;
+    }
   }
   if (b >= end) return;
   const float total = scorer.finish(probe_lds, pn, inv_sqrt_g);
@@ -345,13 +349,13 @@ static int score_waves(int batch, int n) {
 
 int launch_score_probe(const actqkv_shape& sh, const float* probe, float* probe_kv, float* probe_norm,
                        const void* rep_keys, int nb_capacity, int nb_begin, const int32_t* nb_end, float* scores,
-                       hipStream_t stream) {
+                       const float* budget, float* budget_copy, hipStream_t stream) {
   const int n = nb_capacity - nb_begin, key_len = sh.n_kv_heads * sh.head_dim, group = sh.n_q_heads / sh.n_kv_heads;
   const int waves = score_waves(1, n);
   auto launch = [&](auto kernel, auto* keys) {
     hipLaunchKernelGGL(kernel, dim3((n + waves - 1) / waves), dim3(64 * waves), size_t(key_len) * sizeof(float), stream, probe,
                        probe_kv, probe_norm, keys, nb_capacity, nb_begin, nb_end, scores, sh.n_rep, key_len, group, sh.head_dim,
-                       1.f / sqrtf(float(group)));
+                       1.f / sqrtf(float(group)), budget, budget_copy);
   };
   if (sh.dtype == ACTQKV_F32)
     launch(score_probe_kernel<float>, static_cast<const float*>(rep_keys));

@@ -49,6 +49,10 @@ __global__ __launch_bounds__(64) void select_wave_kernel(
               (flags & ACTQKV_SELECT_ENTROPY_TOPK) != 0, io, lds, sel, &count, [] {});
 }
 
+bool select_inside_supported(int n_blocks, int k_cap, int flags) {
+  return n_blocks <= 64 * kSelWavePerLane && k_cap <= kSelectWaveCap && !(flags & ACTQKV_SELECT_DENSITY_ONLY);
+}
+
 int launch_select(int batch, const float* scores, int64_t score_stride, int nb_capacity, int nb_begin,
                   const int32_t* nb_end, int k_cap, int flags, float* budget_remaining,
                   const float* theta_rest_sum, int32_t* idx, int32_t* n_sel, float* theta,

@@ -456,6 +456,24 @@ __device__ __forceinline__ void select_wave(const float* __restrict__ sc_mem, in
   }
 }
 
+// The selection of a window's one sequence inside its attention launch (scores NULL: idx and n_sel hold it already).  Every
+// workgroup repeats it, by one wavefront, while the others ask for their queries and the initial tokens; the first one writes it
+// out.  io.budget_in is a copy: budget_after is written while other workgroups still read.
+struct SelectInside {
+  const float* scores = nullptr;
+  int nb_begin = 0, nb_capacity = 0;
+  const int32_t* nb_end = nullptr;
+  int entropy_topk = 0;
+  SelectIo io = {};
+  // called by one wavefront
+  __device__ __forceinline__ void run(int k_cap, bool write, SelectWaveLds& lds, int* sel, int* count) const {
+    const int end = min(max(nb_end[0], nb_begin), nb_capacity);
+    SelectIo mine = io;
+    mine.write = write;
+    select_wave(scores + nb_begin, 0, max(end - nb_begin, 0), nb_begin, k_cap, entropy_topk, mine, lds, sel, count, [] {});
+  }
+};
+
 // The scores of one sequence as select_body reads them: the first kThreads stay in a register
 // per thread for all passes (their load does not wait for anything), the others come from memory.
 template <int kThreads>

@@ -1032,6 +1032,48 @@ def test_window_step_equals_the_four_calls(dtype, hq, hkv, d, m, batch, n_elig):
         assert (a[name] - b[name]).abs().max() <= bound * a[name].abs().max(), name
 
 
+@pytest.mark.parametrize("dtype,m,n_elig,k_cap,mode", [
+    ("bf16", 64, 70, 8, "cutoff"), ("bf16", 300, 5, 8, "plain"), ("fp32", 40, 200, 32, "cutoff"), ("fp32", 3000, 9, 4, "cutoff"),
+    ("bf16", 4100, 66, 6, "cutoff"), ("bf16", 64, 40, 16, "given"), ("fp32", 33, 40, 16, "topk"),
+    ("bf16", 64, 1024, 32, "cutoff"), ("bf16", 64, 1025, 8, "cutoff"), ("bf16", 64, 70, 33, "cutoff"),       # the last two: a launch of its own
+    ("bf16", 64, 70, 8, "density"), ("bf16", 64, 70, 8, "tight")])
+def test_window_step_that_selects_in_its_attention(dtype, m, n_elig, k_cap, mode):
+    """The same scores through actqkv_select and actqkv_retrieval_attention give the same selection, budget and output bit for
+    bit, call after call; a workspace without room for the copy of the budget ("tight") takes a launch of its own."""
+    sh = LayerShape(8, 2, 64, 128, 4, 128, 256, dtype)
+    cs = B.c_shape(sh)
+    n0 = 128 + 128 * n_elig + 256
+    nb = (n0 + m + 127) // 128
+    g = torch.Generator(device=DEV).manual_seed(m + n_elig)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rnd = lambda *x: torch.randn(*x, generator=g, device=DEV).to(td)  # noqa: E731
+    q, kc, vc, rep = rnd(m, 8, 64), rnd(nb, 2, 128, 64), rnd(nb, 2, 64, 128), rnd(nb, 4, 2, 64)
+    i32, f32 = dict(dtype=torch.int32, device=DEV), dict(dtype=torch.float32, device=DEV)
+    n_ctx, nb_end = torch.tensor([n0 + m], **i32), torch.tensor([1 + n_elig], **i32)
+    flags = {"given": B.SELECT_GIVEN_COUNT, "topk": B.SELECT_ENTROPY_TOPK, "density": B.SELECT_DENSITY_ONLY}.get(mode, 0)
+    cut = mode in ("cutoff", "topk", "tight")
+    ws = torch.zeros(B.workspace_bytes(cs, 1, m, nb, k_cap), dtype=torch.uint8, device=DEV)
+    if mode == "tight":
+        ws = ws[:-256]
+    first = torch.arange(1, k_cap + 1, **i32)[None] % (n_elig + 1)
+    new = lambda: dict(idx=first.clone(), n_sel=torch.tensor([3], **i32), theta=torch.zeros(1, **f32),  # noqa: E731
+                       bud=torch.zeros(1, **f32), left=torch.tensor([9.3], **f32), out=torch.zeros_like(q))
+    rest = torch.tensor([1.5], **f32)
+    st, scores = torch.zeros(1, B.stats_floats(cs), **f32), torch.zeros(1, nb, **f32)
+    probe, kv, norm, w = (torch.zeros(x, **f32) for x in (512, 128, 1, m))
+    for _ in range(3):
+        a, b = new(), new()
+        B.window_step(cs, 1, m, q, st, True, probe, kv, norm, w, rep, 0, 1 + n_elig, 1, nb_end, scores, nb, k_cap,
+                      a["left"] if cut else None, rest if cut else None, a["idx"], a["n_sel"], a["theta"], a["bud"], kc, vc, 0,
+                      nb, n_ctx, a["out"], None, ws, flags=flags)
+        B.select(1, scores, nb, 1 + n_elig, 1, nb_end, k_cap, b["left"] if cut else None, rest if cut else None, b["idx"], b["n_sel"],
+                 b["theta"], b["bud"], flags=flags)
+        B.retrieval_attention(cs, 1, m, q, kc, vc, 0, nb, n_ctx, b["idx"], b["n_sel"], k_cap, b["out"], None, ws)
+        torch.cuda.synchronize()
+        for name in a:
+            assert torch.equal(a[name], b[name]), name
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 129, 257, 1000, 1024])
 def test_selection_by_one_wavefront_where_few_lanes_hold_the_best(n):
     """The wavefront keeps three candidates per lane (block i is lane i % 64's): the best blocks all in one lane, in two,
