@@ -379,6 +379,21 @@ int actqkv_window_step(const actqkv_shape* shape, int batch, int m, const void* 
                        int64_t cache_seq_stride, int nb_capacity, const int32_t* n_ctx, void* out, float* lse,
                        void* workspace, size_t ws_bytes, void* stream);
 
+/* A decode step in ONE call of two launches: actqkv_decode_retrieve and actqkv_retrieval_attention with m = 1 and
+ * the arguments of the two, every storage type and head size, with their results (the selection runs inside the
+ * attention launch; budget_remaining is updated in place).
+ *   nb_scored    nb_capacity of actqkv_decode_retrieve (what scores, rep_keys and, with k_new, the caches are long);
+ *                nb_capacity is that of the attention.
+ *   flags        0 or ACTQKV_SELECT_ENTROPY_TOPK.
+ * Errors: as in the two calls; nothing is launched if one of them would be refused. */
+int actqkv_decode_step(const actqkv_shape* shape, int batch, const void* q_tok, const void* k_new, const void* v_new,
+                       const int32_t* pos0, void* k_cache, void* v_cache, int64_t cache_seq_stride, void* rep_keys,
+                       int64_t rep_seq_stride, int nb_scored, int nb_begin, const int32_t* nb_end, float* probe,
+                       float* probe_kv, float* probe_norm, float* scores, int64_t score_stride, int k_cap, int flags,
+                       float* budget_remaining, const float* theta_rest_sum, int32_t* idx, int32_t* n_sel, float* theta,
+                       float* budget, int nb_capacity, const int32_t* n_ctx, void* out, float* lse, void* workspace,
+                       size_t ws_bytes, void* stream);
+
 /* Everything of a decode step that comes before the attention, in ONE call of two launches
  * instead of four: the cache update (Sec. 3.1, Eq. (4); actqkv_append_kv with m = 1), the probe
  * of the one-token window (the query itself, Sec. 4.2; actqkv_build_probe with m = 1 and no

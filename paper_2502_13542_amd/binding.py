@@ -81,6 +81,8 @@ SIGNATURES = {
                                               _vp, _vp, _vp, _sz, _i, _i, _vp, _vp]),
     "actqkv_window_step": (_i, [_shp, _i, _i, _vp, _vp, _i, _vp, _vp, _vp, _vp, _vp, _i64, _i, _i, _vp, _vp, _i64, _i, _i, _vp,
                                 _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i64, _i, _vp, _vp, _vp, _vp, _sz, _vp]),
+    "actqkv_decode_step": (_i, [_shp, _i, _vp, _vp, _vp, _vp, _vp, _vp, _i64, _vp, _i64, _i, _i, _vp, _vp, _vp, _vp, _vp, _i64,
+                                _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _i, _vp, _vp, _vp, _vp, _sz, _vp]),
     "actqkv_copy_bytes": (_i, [_vp, _vp, _sz, _vp]),
     "actqkv_gather_blocks": (_i, [_shp, _i, _vp, _vp, _i64, _i, _vp, _vp, _i, _vp, _vp, _i64, _i, _i, _vp, _vp]),
     "actqkv_gather_blocks_cached": (_i, [_shp, _i, _vp, _vp, _i, _vp, _vp, _i, _vp, _vp, _i, _i, _i, _i, _i, _i, _i,
@@ -108,7 +110,7 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib = ctypes.CDLL(path)
     for name, (res, args) in SIGNATURES.items():
         if path != LIB_PATH and not hasattr(lib, name):
-            continue               # an older build: a call of what it lacks raises (LayerRunner.step needs actqkv_window_step)
+            continue               # an older build: a call of what it lacks raises (LayerRunner needs actqkv_window_step, actqkv_decode_step)
         fn = getattr(lib, name)
         fn.restype, fn.argtypes = res, args
     native = importlib.import_module("._native", __package__)
@@ -182,6 +184,17 @@ def window_step(shape: CShape, batch: int, m: int, q_win, stats, update_stats: i
                          rep_seq_stride, nb_scored, nb_begin, nb_end, scores, score_stride, k_cap, int(flags),
                          budget_remaining, theta_rest_sum, idx, n_sel, theta, budget, k_cache, v_cache, cache_seq_stride,
                          nb_capacity, n_ctx, out, lse, workspace, stream)
+
+
+def decode_step(shape: CShape, batch: int, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride: int, rep_keys,
+                rep_seq_stride: int, nb_scored: int, nb_begin: int, nb_end, probe, probe_kv, probe_norm, scores,
+                score_stride: int, k_cap: int, budget_remaining, theta_rest_sum, idx, n_sel, theta, budget, nb_capacity: int,
+                n_ctx, out, lse, workspace, stream=None, flags: int = 0) -> None:
+    """Cache update, probe, scores, selection and attention of a decode step in one call of two launches; see the header."""
+    _calls().decode_step(shape, batch, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride, rep_keys, rep_seq_stride,
+                         nb_scored, nb_begin, nb_end, probe, probe_kv, probe_norm, scores, score_stride, k_cap, int(flags),
+                         budget_remaining, theta_rest_sum, idx, n_sel, theta, budget, nb_capacity, n_ctx, out, lse, workspace,
+                         stream)
 
 
 def decode_retrieve(shape: CShape, batch: int, q_tok, k_new, v_new, pos0, k_cache, v_cache,

@@ -128,7 +128,7 @@ int launch_attention_decode_mfma(const actqkv_shape& sh, int batch, const void* 
 int launch_attention_decode_select(const actqkv_shape& sh, int batch, const void* q, const void* k_cache,
                                    const void* v_cache, int64_t seq_stride, int nb_capacity,
                                    const int32_t* n_ctx, const float* scores, int64_t score_stride, int nb_begin,
-                                   const int32_t* nb_end, int k_cap, int flags, const float* budget_in,
+                                   int nb_scored, const int32_t* nb_end, int k_cap, int flags, const float* budget_in,
                                    const float* theta_rest_sum, float* budget_after, int32_t* idx,
                                    int32_t* n_sel, float* theta, float* budget, void* out, float* lse,
                                    float* scratch, unsigned int* counters, float scale, hipStream_t stream);
@@ -165,7 +165,7 @@ static size_t workspace_bytes_upto(const actqkv_shape& sh, int batch, int m, int
   if (prefill_mfma_supported(sh, m)) need = kCounterBytes + prefill_partials_most(sh, batch, m);
   for (int b = 1; b <= batch; ++b) need = std::max(need, workspace_bytes(sh, b, 1, nb_capacity, k_cap));
   need = std::max(need, kCounterBytes + align_up(probe_call_floats(sh, batch, m) * sizeof(float), 256));
-  return need + 256;   // Workspace::spare
+  return need + Workspace::spare_bytes(batch);
 }
 
 int launch_attention(const actqkv_shape& sh, int batch, int m, const void* q, const void* k_cache,
@@ -295,6 +295,63 @@ size_t actqkv_workspace_bytes(const actqkv_shape* shape, int batch, int m, int n
     return 0;
   }
   return workspace_bytes_upto(*shape, batch, m, nb_capacity, k_cap);
+}
+
+static int decode_retrieve_check(const actqkv_shape* shape, int batch, const void* q_tok, const void* k_new,
+                                 const void* v_new, const int32_t* pos0, const void* k_cache, const void* v_cache,
+                                 int64_t cache_seq_stride, const void* rep_keys, int64_t rep_seq_stride,
+                                 int nb_capacity, int nb_begin, const int32_t* nb_end, const float* probe,
+                                 const float* probe_kv, const float* probe_norm, const float* scores, int64_t score_stride,
+                                 int k_cap, int flags, const float* budget_remaining, const float* theta_rest_sum,
+                                 const int32_t* idx, const int32_t* n_sel, const float* theta, const float* budget) {
+  ACTQKV_TRY(check_shape(shape));
+  ACTQKV_TRY(check_batch(batch));
+  if (flags & ~(ACTQKV_SELECT_ENTROPY_TOPK | ACTQKV_DECODE_SCORES_ONLY))
+    return set_error(ACTQKV_EINVAL, "decode_retrieve: unknown flag bits: %d", flags);
+  const bool select_too = !(flags & ACTQKV_DECODE_SCORES_ONLY);
+  if (nb_capacity < 1) return set_error(ACTQKV_EINVAL, "nb_capacity %d < 1", nb_capacity);
+  if (int64_t(nb_capacity) * shape->block_size > (int64_t(1) << 30))
+    return set_error(ACTQKV_ESHAPE, "cache of %d blocks exceeds 2^30 tokens", nb_capacity);
+  ACTQKV_TRY(check_blocks(nb_capacity, nb_begin, k_cap, true));
+  ACTQKV_REQUIRE_PTR(q_tok);
+  const bool update = k_new != nullptr || v_new != nullptr || pos0 != nullptr;
+  if (update) {
+    ACTQKV_REQUIRE_PTR(k_new);
+    ACTQKV_REQUIRE_PTR(v_new);
+    ACTQKV_REQUIRE_SMALL(pos0, 4);
+    ACTQKV_REQUIRE_PTR(k_cache);
+    ACTQKV_REQUIRE_PTR(v_cache);
+  }
+  ACTQKV_REQUIRE_PTR(rep_keys);
+  ACTQKV_REQUIRE_SMALL(nb_end, 4);
+  ACTQKV_OPTIONAL_PTR(probe);
+  ACTQKV_OPTIONAL_PTR(probe_kv);
+  ACTQKV_OPTIONAL_SMALL(probe_norm, 4);
+  ACTQKV_REQUIRE_SMALL(scores, 4);
+  if (select_too) {
+    ACTQKV_REQUIRE_SMALL(idx, 4);
+    ACTQKV_REQUIRE_SMALL(n_sel, 4);
+  }
+  if ((budget_remaining == nullptr) != (theta_rest_sum == nullptr))
+    return set_error(ACTQKV_EINVAL, "budget_remaining and theta_rest_sum must be given together");
+  ACTQKV_OPTIONAL_SMALL(budget_remaining, 4);
+  ACTQKV_OPTIONAL_SMALL(theta_rest_sum, 4);
+  ACTQKV_OPTIONAL_SMALL(theta, 4);
+  ACTQKV_OPTIONAL_SMALL(budget, 4);
+  if (score_stride < nb_capacity)
+    return set_error(ACTQKV_EINVAL, "score_stride %lld < nb_capacity %d", (long long)score_stride,
+                     nb_capacity);
+  const int64_t per_seq = int64_t(nb_capacity) * shape->n_kv_heads * shape->block_size * shape->head_dim;
+  const int64_t rep_per_seq = int64_t(nb_capacity) * shape->n_rep * shape->n_kv_heads * shape->head_dim;
+  if (batch > 1 && update && cache_seq_stride < per_seq)
+    return set_error(ACTQKV_EINVAL, "cache_seq_stride %lld < one sequence's cache %lld",
+                     (long long)cache_seq_stride, (long long)per_seq);
+  if (batch > 1 && rep_seq_stride < rep_per_seq)
+    return set_error(ACTQKV_EINVAL, "rep_seq_stride %lld < one sequence's representative keys %lld",
+                     (long long)rep_seq_stride, (long long)rep_per_seq);
+  if (cache_seq_stride % 8 != 0 || rep_seq_stride % 8 != 0)
+    return set_error(ACTQKV_EALIGN, "sequence strides must be multiples of 8 elements");
+  return ACTQKV_OK;
 }
 
 static int build_probe_check(const actqkv_shape* shape, int batch, int m, const void* q_win, const float* stats,
@@ -450,7 +507,7 @@ int actqkv_window_step(const actqkv_shape* shape, int batch, int m, const void* 
   // The selection inside the attention launch: the scoring launch keeps a copy of the budget for it behind what the call
   // needs of the workspace (a workspace without those bytes: a launch of its own).  Four windows of 512 tokens at 64K with the
   // selection as a launch of its own 244 us, inside 236; of 256 tokens with 64 channels 133, 128.
-  float* copy = ws.spare(need);
+  float* copy = ws.spare(need, batch);
   if (apart && copy != nullptr && select_inside_supported(nb_scored - nb_begin, k_cap, flags)) {
     ACTQKV_TRY(launch_score_probe(*shape, probe, probe_kv, probe_norm, rep_keys, nb_scored, nb_begin, nb_end, scores,
                                   budget_remaining, copy, st));
@@ -592,7 +649,7 @@ int actqkv_decode_select_attention(const actqkv_shape* shape, int batch, const v
   Workspace ws{workspace, ws_bytes};
   const float scale = shape->softmax_scale > 0.f ? shape->softmax_scale : 1.f / std::sqrt(float(shape->head_dim));
   return launch_attention_decode_select(*shape, batch, q, k_cache, v_cache, seq_stride, nb_capacity, n_ctx,
-                                        scores, score_stride, nb_begin, nb_end, k_cap, flags, budget_in,
+                                        scores, score_stride, nb_begin, nb_capacity, nb_end, k_cap, flags, budget_in,
                                         theta_rest_sum, budget_after, idx, n_sel, theta, budget, out, lse,
                                         ws.scratch_f32(), ws.counters(), scale,
                                         static_cast<hipStream_t>(stream));
@@ -837,57 +894,50 @@ int actqkv_decode_retrieve(const actqkv_shape* shape, int batch, const void* q_t
                            int k_cap, int flags, float* budget_remaining,
                            const float* theta_rest_sum, int32_t* idx, int32_t* n_sel, float* theta,
                            float* budget, void* stream) {
-  ACTQKV_TRY(check_shape(shape));
-  ACTQKV_TRY(check_batch(batch));
-  if (flags & ~(ACTQKV_SELECT_ENTROPY_TOPK | ACTQKV_DECODE_SCORES_ONLY))
-    return set_error(ACTQKV_EINVAL, "decode_retrieve: unknown flag bits: %d", flags);
-  const bool select_too = !(flags & ACTQKV_DECODE_SCORES_ONLY);
-  if (nb_capacity < 1) return set_error(ACTQKV_EINVAL, "nb_capacity %d < 1", nb_capacity);
-  if (int64_t(nb_capacity) * shape->block_size > (int64_t(1) << 30))
-    return set_error(ACTQKV_ESHAPE, "cache of %d blocks exceeds 2^30 tokens", nb_capacity);
-  ACTQKV_TRY(check_blocks(nb_capacity, nb_begin, k_cap, true));
-  ACTQKV_REQUIRE_PTR(q_tok);
-  const bool update = k_new != nullptr || v_new != nullptr || pos0 != nullptr;
-  if (update) {
-    ACTQKV_REQUIRE_PTR(k_new);
-    ACTQKV_REQUIRE_PTR(v_new);
-    ACTQKV_REQUIRE_SMALL(pos0, 4);
-    ACTQKV_REQUIRE_PTR(k_cache);
-    ACTQKV_REQUIRE_PTR(v_cache);
-  }
-  ACTQKV_REQUIRE_PTR(rep_keys);
-  ACTQKV_REQUIRE_SMALL(nb_end, 4);
-  ACTQKV_OPTIONAL_PTR(probe);
-  ACTQKV_OPTIONAL_PTR(probe_kv);
-  ACTQKV_OPTIONAL_SMALL(probe_norm, 4);
-  ACTQKV_REQUIRE_SMALL(scores, 4);
-  if (select_too) {
-    ACTQKV_REQUIRE_SMALL(idx, 4);
-    ACTQKV_REQUIRE_SMALL(n_sel, 4);
-  }
-  if ((budget_remaining == nullptr) != (theta_rest_sum == nullptr))
-    return set_error(ACTQKV_EINVAL, "budget_remaining and theta_rest_sum must be given together");
-  ACTQKV_OPTIONAL_SMALL(budget_remaining, 4);
-  ACTQKV_OPTIONAL_SMALL(theta_rest_sum, 4);
-  ACTQKV_OPTIONAL_SMALL(theta, 4);
-  ACTQKV_OPTIONAL_SMALL(budget, 4);
-  if (score_stride < nb_capacity)
-    return set_error(ACTQKV_EINVAL, "score_stride %lld < nb_capacity %d", (long long)score_stride,
-                     nb_capacity);
-  const int64_t per_seq = int64_t(nb_capacity) * shape->n_kv_heads * shape->block_size * shape->head_dim;
-  const int64_t rep_per_seq = int64_t(nb_capacity) * shape->n_rep * shape->n_kv_heads * shape->head_dim;
-  if (batch > 1 && update && cache_seq_stride < per_seq)
-    return set_error(ACTQKV_EINVAL, "cache_seq_stride %lld < one sequence's cache %lld",
-                     (long long)cache_seq_stride, (long long)per_seq);
-  if (batch > 1 && rep_seq_stride < rep_per_seq)
-    return set_error(ACTQKV_EINVAL, "rep_seq_stride %lld < one sequence's representative keys %lld",
-                     (long long)rep_seq_stride, (long long)rep_per_seq);
-  if (cache_seq_stride % 8 != 0 || rep_seq_stride % 8 != 0)
-    return set_error(ACTQKV_EALIGN, "sequence strides must be multiples of 8 elements");
+  ACTQKV_TRY(decode_retrieve_check(shape, batch, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride, rep_keys,
+                                   rep_seq_stride, nb_capacity, nb_begin, nb_end, probe, probe_kv, probe_norm, scores,
+                                   score_stride, k_cap, flags, budget_remaining, theta_rest_sum, idx, n_sel, theta, budget));
   return launch_decode_retrieve(*shape, batch, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride,
                                 rep_keys, rep_seq_stride, nb_capacity, nb_begin, nb_end, probe, probe_kv,
                                 probe_norm, scores, score_stride, k_cap, flags, budget_remaining,
                                 theta_rest_sum, idx, n_sel, theta, budget, static_cast<hipStream_t>(stream));
+}
+
+int actqkv_decode_step(const actqkv_shape* shape, int batch, const void* q_tok, const void* k_new, const void* v_new,
+                       const int32_t* pos0, void* k_cache, void* v_cache, int64_t cache_seq_stride, void* rep_keys,
+                       int64_t rep_seq_stride, int nb_scored, int nb_begin, const int32_t* nb_end, float* probe,
+                       float* probe_kv, float* probe_norm, float* scores, int64_t score_stride, int k_cap, int flags,
+                       float* budget_remaining, const float* theta_rest_sum, int32_t* idx, int32_t* n_sel, float* theta,
+                       float* budget, int nb_capacity, const int32_t* n_ctx, void* out, float* lse, void* workspace,
+                       size_t ws_bytes, void* stream) {
+  // everything is checked before anything is launched
+  if (flags & ACTQKV_DECODE_SCORES_ONLY) return set_error(ACTQKV_EINVAL, "decode_step: unknown flag bits: %d", flags);
+  ACTQKV_TRY(decode_retrieve_check(shape, batch, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride, rep_keys,
+                                   rep_seq_stride, nb_scored, nb_begin, nb_end, probe, probe_kv, probe_norm, scores,
+                                   score_stride, k_cap, flags, budget_remaining, theta_rest_sum, idx, n_sel, theta, budget));
+  size_t need = 0;
+  ACTQKV_TRY(attention_validate(shape, batch, 1, q_tok, k_cache, v_cache, cache_seq_stride, nb_capacity, n_ctx, idx, n_sel,
+                                k_cap, out, lse, kChipCus, &need));
+  if (workspace == nullptr || !aligned16(workspace))
+    return set_error(ACTQKV_EWORKSPACE, "workspace is NULL or not 16-byte aligned");
+  if (ws_bytes < need) return set_error(ACTQKV_EWORKSPACE, "workspace has %zu bytes, decode_step needs %zu", ws_bytes, need);
+  Workspace ws{workspace, ws_bytes};
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  // The selection inside the attention launch, on a copy of the budget that the scoring launch makes (a workspace without
+  // room for it: a launch of its own).
+  float* copy = ws.spare(need, batch);
+  ACTQKV_TRY(launch_decode_retrieve(*shape, batch, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride, rep_keys,
+                                    rep_seq_stride, nb_scored, nb_begin, nb_end, probe, probe_kv, probe_norm, scores,
+                                    score_stride, k_cap, copy != nullptr ? flags | ACTQKV_DECODE_SCORES_ONLY : flags,
+                                    budget_remaining, theta_rest_sum, idx, n_sel, theta, budget, st, copy));
+  if (copy == nullptr)
+    return launch_attention(*shape, batch, 1, q_tok, k_cache, v_cache, cache_seq_stride, nb_capacity, n_ctx, idx, n_sel, k_cap,
+                            out, lse, ws, 0, st);
+  const float scale = shape->softmax_scale > 0.f ? shape->softmax_scale : 1.f / std::sqrt(float(shape->head_dim));
+  return launch_attention_decode_select(*shape, batch, q_tok, k_cache, v_cache, cache_seq_stride, nb_capacity, n_ctx, scores,
+                                        score_stride, nb_begin, nb_scored, nb_end, k_cap, flags,
+                                        budget_remaining != nullptr ? copy : nullptr, theta_rest_sum, budget_remaining, idx,
+                                        n_sel, theta, budget, out, lse, ws.scratch_f32(), ws.counters(), scale, st);
 }
 
 int actqkv_cutoff_budgets(int batch, int n_layers, float k_mean, int k_cap, const float* theta, float* budget,

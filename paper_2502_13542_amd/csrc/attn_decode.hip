@@ -62,6 +62,7 @@ struct DcSelectParams {
   const int32_t* nb_end;
   int entropy_topk;
   SelectIo io;              // io.write is set per workgroup by the kernel
+  int nb_scored;            // blocks a row of scores holds
 };
 
 __device__ __forceinline__ bf16x8 dc_as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -393,18 +394,29 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_kernel(DcParams p) {
   dc_load_q<T, D>(p, s, hk, group, n, kq, qb);
   const int n_ctx = min(max(n_ctx_raw, 1), p.nb_capacity * kBlock);
   const WindowGeom g = window_geom(n_ctx, 1, p.n_init, p.n_local);
-  const TileList tl = make_tile_list(g, n_ctx - 1, p.idx + sel_row * p.k_cap, n_sel_raw, p.k_cap, p.nb_capacity);
-  const int n_items = tl.count() * (kBlock / DcShape<T, D>::kKeys);
+  // initial tokens and local span, which wait for the length alone, then the selected blocks: as in the kernel that selects
+  // for itself, so the two give the same bits
+  const TileList fixed = make_tile_list(g, n_ctx - 1, nullptr, 0, p.k_cap, p.nb_capacity);
+  TileList chosen = fixed;
+  chosen.n_init_tiles = 0;
+  chosen.n_tail_tiles = 0;
+  chosen.n_sel = min(max(n_sel_raw, 0), p.k_cap);
+  chosen.idx = p.idx + sel_row * p.k_cap;
+  constexpr int kPerTile = kBlock / DcShape<T, D>::kKeys;
+  const int n_fixed = fixed.count() * kPerTile, n_chosen = chosen.n_sel * kPerTile;
   DcAcc<D> a;
   a.clear();
   const T* kc = static_cast<const T*>(p.k_cache) + size_t(s) * p.seq_stride;
   const T* vc = static_cast<const T*>(p.v_cache) + size_t(s) * p.seq_stride;
 
-  dc_walk<T, D>(tl, wave * p.n_wg + wg, p.n_wg * n_waves, n_items, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
+  const int it0 = wave * p.n_wg + wg, stride = p.n_wg * n_waves;
+  dc_walk<T, D>(fixed, it0, stride, n_fixed, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
+  const int done = it0 < n_fixed ? (n_fixed - it0 + stride - 1) / stride : 0;      // of this wavefront's turns
+  dc_walk<T, D>(chosen, it0 + done * stride - n_fixed, stride, n_chosen, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
   dc_finish<T, D>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 }
 
-constexpr int kDcD = 128;        // the kernels below: bf16, 128 channels per head
+constexpr int kDcD = 128;        // decode_layer_kernel: bf16, 128 channels per head
 
 // The same attention with the selection step (Sec. 4.2, Eq. (11), Eq. (12); Alg. 1) inside it:
 // the step needs a launch of its own only because of its latency (two memory round trips and a
@@ -415,6 +427,7 @@ constexpr int kDcD = 128;        // the kernels below: bf16, 128 channels per he
 // the selection (initial tokens, local span) come first in the list, so a wavefront's first
 // loads go out before the selection starts.
 // blockDim = kDcThreads (the selection is written for that many threads).
+template <typename T, int D>
 __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams p, DcSelectParams sp) {
   extern __shared__ __attribute__((aligned(16))) float dc_lds[];
   __shared__ SelectLds<kDcThreads> sel_lds;
@@ -427,7 +440,7 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
   const int group = p.n_q_heads / p.n_kv_heads;
 
   const float* sc_mem = sp.scores + size_t(s) * sp.score_stride + sp.nb_begin;
-  const int end = min(max(sp.nb_end[s], sp.nb_begin), p.nb_capacity);   // (no wrap-around in the subtraction)
+  const int end = min(max(sp.nb_end[s], sp.nb_begin), sp.nb_scored);   // (no wrap-around in the subtraction)
   const int n_elig = max(end - sp.nb_begin, 0);
   // Rows that fit a wavefront's registers are selected by ONE wavefront, the last of the workgroup,
   // which does that before anything else; the others never meet a barrier on their way to their
@@ -450,33 +463,33 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
     __builtin_amdgcn_s_setprio(0);
   }
   // the scores of the sequence for the workgroup-wide selection: the load of the first 512 does not wait for anything
-  const ScoreRow<kDcThreads> sc{sc_mem, (!by_wave && int(threadIdx.x) < p.nb_capacity - sp.nb_begin) ? sc_mem[threadIdx.x] : 0.f};
+  const ScoreRow<kDcThreads> sc{sc_mem, (!by_wave && int(threadIdx.x) < sp.nb_scored - sp.nb_begin) ? sc_mem[threadIdx.x] : 0.f};
   const int n_ctx = min(max(p.n_ctx[s], 1), p.nb_capacity * kBlock);
   const WindowGeom g = window_geom(n_ctx, 1, p.n_init, p.n_local);
   // the list without the selection: initial tokens, then the local span
   const TileList fixed = make_tile_list(g, n_ctx - 1, nullptr, 0, p.k_cap, p.nb_capacity);
-  const int n_fixed = fixed.count() * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
-  u32x4 qb[DcShape<uint16_t, kDcD>::kQ];
-  dc_load_q<uint16_t, kDcD>(p, s, hk, group, n, kq, qb);
-  DcAcc<kDcD> a;
+  const int n_fixed = fixed.count() * (kBlock / DcShape<T, D>::kKeys);
+  u32x4 qb[DcShape<T, D>::kQ];
+  dc_load_q<T, D>(p, s, hk, group, n, kq, qb);
+  DcAcc<D> a;
   a.clear();
-  const uint16_t* kc = static_cast<const uint16_t*>(p.k_cache) + size_t(s) * p.seq_stride;
-  const uint16_t* vc = static_cast<const uint16_t*>(p.v_cache) + size_t(s) * p.seq_stride;
+  const T* kc = static_cast<const T*>(p.k_cache) + size_t(s) * p.seq_stride;
+  const T* vc = static_cast<const T*>(p.v_cache) + size_t(s) * p.seq_stride;
 
   // The items that do not depend on the selection come first in the list, and this wavefront's first one is
   // requested before the selection.  Neighbouring items go to different workgroups; the wavefronts that
   // select come last, short lists do not reach them.
   const int it0 = wave * p.n_wg + wg;
   const int stride = p.n_wg * n_waves;
-  DcItem<uint16_t, kDcD> r0;
+  DcItem<T, D> r0;
   int block0, part0;
-  const bool have0 = it0 < n_fixed && dc_item_span<uint16_t, kDcD>(fixed, it0, block0, part0, r0);
+  const bool have0 = it0 < n_fixed && dc_item_span<T, D>(fixed, it0, block0, part0, r0);
   if (have0) dc_issue(r0, kc, vc, block0, part0, hk, p.n_kv_heads, n, kq);
   __builtin_amdgcn_sched_barrier(0);
   if (!by_wave) select_body<kDcThreads>(sc, s, n_elig, sp.nb_begin, p.k_cap, sp.entropy_topk, io, sel_lds);
   __builtin_amdgcn_sched_barrier(0);
-  if (have0) dc_consume<uint16_t, kDcD>(r0, qb, a, p.scale_log2e, kq);
-  dc_walk<uint16_t, kDcD>(fixed, it0 + stride, stride, n_fixed, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
+  if (have0) dc_consume<T, D>(r0, qb, a, p.scale_log2e, kq);
+  dc_walk<T, D>(fixed, it0 + stride, stride, n_fixed, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
   if (by_wave) {
     // the selector has long finished as a rule; it always does, whatever the others do
     while (__hip_atomic_load(&sel_ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0) __builtin_amdgcn_s_sleep(1);
@@ -489,11 +502,11 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_select_kernel(DcParams
   chosen.n_tail_tiles = 0;
   chosen.n_sel = min(max(sel_lds.count, 0), p.k_cap);
   chosen.idx = sel_lds.sel;
-  const int n_chosen = chosen.n_sel * (kBlock / DcShape<uint16_t, kDcD>::kKeys);
+  const int n_chosen = chosen.n_sel * (kBlock / DcShape<T, D>::kKeys);
   const int done = it0 < n_fixed ? (n_fixed - it0 + stride - 1) / stride : 0;      // of this wavefront's turns
-  dc_walk<uint16_t, kDcD>(chosen, it0 + done * stride - n_fixed, stride, n_chosen, kc, vc, qb, a, p.scale_log2e, hk,
+  dc_walk<T, D>(chosen, it0 + done * stride - n_fixed, stride, n_chosen, kc, vc, qb, a, p.scale_log2e, hk,
                           p.n_kv_heads, n, kq);
-  dc_finish<uint16_t, kDcD>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
+  dc_finish<T, D>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 }
 
 // ---- a whole decode layer in ONE launch ---------------------------------------------------
@@ -828,7 +841,7 @@ int launch_attention_decode_mfma(const actqkv_shape& sh, int batch, const void* 
 int launch_attention_decode_select(const actqkv_shape& sh, int batch, const void* q, const void* k_cache,
                                    const void* v_cache, int64_t seq_stride, int nb_capacity,
                                    const int32_t* n_ctx, const float* scores, int64_t score_stride, int nb_begin,
-                                   const int32_t* nb_end, int k_cap, int flags, const float* budget_in,
+                                   int nb_scored, const int32_t* nb_end, int k_cap, int flags, const float* budget_in,
                                    const float* theta_rest_sum, float* budget_after, int32_t* idx,
                                    int32_t* n_sel, float* theta, float* budget, void* out, float* lse,
                                    float* scratch, unsigned int* counters, float scale, hipStream_t stream) {
@@ -838,15 +851,24 @@ int launch_attention_decode_select(const actqkv_shape& sh, int batch, const void
   sp.scores = scores;
   sp.score_stride = score_stride;
   sp.nb_begin = nb_begin;
+  sp.nb_scored = nb_scored;
   sp.nb_end = nb_end;
   sp.entropy_topk = (flags & ACTQKV_SELECT_ENTROPY_TOPK) != 0;
   sp.io = SelectIo{budget_in, theta_rest_sum, budget_after, idx, n_sel, theta, budget, false};
   const int group = sh.n_q_heads / sh.n_kv_heads;
-  const size_t lds = size_t(kDcMaxWaves) * group * (kDcD + 2) * sizeof(float);
+  const size_t lds = size_t(kDcMaxWaves) * group * (sh.head_dim + 2) * sizeof(float);
   if (p.n_wg > 1 && size_t(batch) * sh.n_kv_heads > kTicketCounters)
     return set_error(ACTQKV_EINVAL, "decode attention: more split (sequence, KV head) pairs than ticket counters");
-  hipLaunchKernelGGL(attn_decode_select_kernel, dim3(p.n_wg, sh.n_kv_heads, batch), dim3(kDcThreads), lds,
-                     stream, p, sp);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(p.n_wg, sh.n_kv_heads, batch), dim3(kDcThreads), lds, stream, p, sp);
+  };
+  if (sh.dtype == ACTQKV_F32) {
+    if (sh.head_dim == 64) launch(attn_decode_select_kernel<float, 64>);
+    else launch(attn_decode_select_kernel<float, 128>);
+  } else {
+    if (sh.head_dim == 64) launch(attn_decode_select_kernel<uint16_t, 64>);
+    else launch(attn_decode_select_kernel<uint16_t, 128>);
+  }
   return hip_status("attention with selection (decode)");
 }
 
@@ -863,6 +885,7 @@ int launch_decode_layer(const actqkv_shape& sh, int batch, const void* q, const 
   sp.scores = scores;
   sp.score_stride = score_stride;
   sp.nb_begin = nb_begin;
+  sp.nb_scored = nb_capacity;
   sp.nb_end = nb_end;
   sp.entropy_topk = (flags & ACTQKV_SELECT_ENTROPY_TOPK) != 0;
   sp.io = SelectIo{budget_in, theta_rest_sum, budget_after, idx, n_sel, theta, budget, false};

@@ -47,9 +47,12 @@ struct DrParams {
   int n_score_wg;
   int n_q_heads, n_kv_heads, head_dim, n_rep;
   float inv_sqrt_g;
+  const float* budget;      // kCopy: copied to budget_copy, for a selection inside the attention launch
+  float* budget_copy;
 };
 
-template <typename T>
+// (kCopy as an argument of the kernel cost the steps that have no use for it 0.3 us a launch)
+template <typename T, bool kCopy>
 __global__ __launch_bounds__(kDrThreads) void decode_score_kernel(DrParams<T> p) {
   constexpr int V = Vec<T>::N;
   extern __shared__ __attribute__((aligned(16))) unsigned char dr_lds[];
@@ -149,6 +152,8 @@ __global__ __launch_bounds__(kDrThreads) void decode_score_kernel(DrParams<T> p)
     if (p.probe_kv != nullptr)
       for (int e = threadIdx.x; e < key_len; e += kDrThreads) p.probe_kv[size_t(s) * key_len + e] = pkv_lds[e];
     if (p.probe_norm != nullptr && threadIdx.x == 0) p.probe_norm[s] = pn;
+    if constexpr (kCopy)
+      if (threadIdx.x == 0) p.budget_copy[s] = p.budget[s];
   }
   if (!live) return;
   const float total = scorer.finish(pkv_lds, pn, p.inv_sqrt_g);
@@ -166,8 +171,11 @@ static int launch_decode_score_t(const actqkv_shape& sh, int batch, DrParams<T> 
   p.inv_sqrt_g = 1.f / sqrtf(float(sh.n_q_heads / sh.n_kv_heads));
   const int roles = p.k_new != nullptr ? 2 : 0;
   const size_t lds = std::max(size_t(sh.n_kv_heads) * sh.head_dim * sizeof(float), size_t(2 * kBlock) * 4);
-  hipLaunchKernelGGL(decode_score_kernel<T>, dim3(p.n_score_wg + roles, batch), dim3(kDrThreads), lds, stream,
-                     p);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(p.n_score_wg + roles, batch), dim3(kDrThreads), lds, stream, p);
+  };
+  if (p.budget != nullptr) launch(decode_score_kernel<T, true>);
+  else launch(decode_score_kernel<T, false>);
   return hip_status("decode_retrieve (scores)");
 }
 
@@ -177,7 +185,7 @@ int launch_decode_retrieve(const actqkv_shape& sh, int batch, const void* q_tok,
                            int nb_begin, const int32_t* nb_end, float* probe, float* probe_kv,
                            float* probe_norm, float* scores, int64_t score_stride, int k_cap, int flags,
                            float* budget_remaining, const float* theta_rest_sum, int32_t* idx,
-                           int32_t* n_sel, float* theta, float* budget, hipStream_t stream) {
+                           int32_t* n_sel, float* theta, float* budget, hipStream_t stream, float* budget_copy) {
   auto fill = [&](auto& p) {
     p.pos0 = pos0;
     p.cache_stride = cache_stride;
@@ -190,6 +198,8 @@ int launch_decode_retrieve(const actqkv_shape& sh, int batch, const void* q_tok,
     p.probe_norm = probe_norm;
     p.scores = scores;
     p.score_stride = score_stride;
+    p.budget = budget_copy != nullptr ? budget_remaining : nullptr;
+    p.budget_copy = budget_copy;
   };
   int rc;
   if (sh.dtype == ACTQKV_F32) {

@@ -103,11 +103,12 @@ struct Workspace {
   float* scratch_f32() const {
     return reinterpret_cast<float*>(static_cast<char*>(base) + kCounterBytes);
   }
-  // four bytes at its end that no launch of a call which needs `need` bytes uses, or NULL
-  float* spare(size_t need) const {
-    const size_t at = bytes / 16 * 16;
-    return at >= 16 && at - 16 >= need ? reinterpret_cast<float*>(static_cast<char*>(base) + at - 16) : nullptr;
+  // a float per sequence at its end that no launch of a call which needs `need` bytes uses, or NULL
+  float* spare(size_t need, int batch) const {
+    const size_t mine = spare_bytes(batch), at = bytes / 16 * 16;
+    return at >= mine && at - mine >= need ? reinterpret_cast<float*>(static_cast<char*>(base) + at - mine) : nullptr;
   }
+  static size_t spare_bytes(int batch) { return align_up(size_t(batch) * sizeof(float), 256); }
 };
 
 // ---- launchers (one per entry point; arguments already validated) ----------
@@ -154,7 +155,8 @@ int launch_decode_retrieve(const actqkv_shape& sh, int batch, const void* q_tok,
                            float* probe_norm, float* scores, int64_t score_stride, int k_cap, int flags,
                            float* budget_remaining, const float* theta_rest_sum, int32_t* idx,
                            int32_t* n_sel, float* theta, float* budget,
-                           hipStream_t stream);   // k_new NULL: no cache update
+                           hipStream_t stream,    // k_new NULL: no cache update
+                           float* budget_copy = nullptr);   // [batch]: budget_remaining as it was
 
 // a whole decode layer in one launch (bf16, head_dim 128); k_new NULL: no cache update
 int launch_decode_layer(const actqkv_shape& sh, int batch, const void* q, const void* k_new, const void* v_new,

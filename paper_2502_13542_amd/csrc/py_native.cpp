@@ -228,7 +228,8 @@ template <typename... P> struct Entry<int(P...)> {
   X(score_blocks, "sq")                                          \
   X(score_blocks_per_head, "sq")                                 \
   X(select, "q")                                                 \
-  X(window_step, "ssssswq")
+  X(window_step, "ssssswq")                                      \
+  X(decode_step, "ssssssswq")
 
 #define ACTQKV_DEFINE(name, kinds)                                                          \
   Entry<decltype(actqkv_##name)> entry_##name;                                              \

@@ -114,6 +114,21 @@ def test_window_step_rejects(lib):
     assert call(wsb=100) == -4
 
 
+def test_decode_step_rejects(lib):
+    """What one of the two calls refuses, before anything is launched."""
+    cs = B.c_shape(LLAMA)
+    base = dict(shape=ctypes.byref(cs), batch=2, q=A16, kn=A16, vn=A16, pos=A16, kc=A16, vc=A16, cst=1 << 30, rep=A16, rs=1 << 24,
+                nbs=64, nbb=1, nbe=A16, probe=None, pkv=None, pn=None, sc=A16, ss=64, k=32, fl=0, bud=None, rest=None, idx=A16,
+                ns=A16, th=None, b=None, nb=64, n_ctx=A16, out=A16, lse=None, ws=A16, wsb=1 << 30, stream=None)
+    call = lambda **kw: lib.actqkv_decode_step(*{**base, **kw}.values())  # noqa: E731
+    assert call(shape=None) == -1 and call(q=None) == -1 and call(kn=None) == -1 and call(rep=A16 + 4) == -3
+    assert call(ss=10) == -1 and call(k=65) == -2 and call(idx=None) == -1 and call(bud=A16) == -1
+    assert call(fl=B.DECODE_SCORES_ONLY) == -1 and call(fl=B.SELECT_GIVEN_COUNT) == -1
+    assert call(out=None) == -1 and call(n_ctx=None) == -1 and call(kc=None) == -1
+    assert call(kn=None, vn=None, pos=None, kc=None) == -1 and b"k_cache" in lib.actqkv_last_error()
+    assert call(wsb=100) == -4 and call(ws=None) == -4
+
+
 @pytest.mark.parametrize("field,value,code", [("head_dim", 96, -2), ("n_kv_heads", 5, -2),
                                               ("block_size", 64, -2), ("n_rep", 17, -2),
                                               ("n_init", 100, -2), ("dtype", 7, -1),

@@ -1408,6 +1408,58 @@ def test_decode_full_size_layer_as_benchmarked():
         assert err < TOL_OUT["bf16"], f"decode output, sequence {s}"
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,d,bt,n_elig,k_cap,mode", [
+    ("fp32", 8, 2, 64, 4, [62, 5, 0, 40], 8, "cutoff"), ("fp32", 8, 8, 128, 1, [9], 4, "plain"), ("bf16", 8, 2, 64, 2, [300, 17], 32, "cutoff"),
+    ("bf16", 28, 4, 128, 3, [64, 65, 1], 40, "topk"), ("fp32", 8, 1, 64, 2, [1030, 1025], 8, "cutoff"), ("bf16", 8, 2, 64, 70, [6], 8, "cutoff"),
+    ("fp32", 8, 2, 64, 2, [20, 30], 8, "held"), ("bf16", 8, 2, 64, 2, [20, 30], 8, "tight")])
+def test_decode_step_equals_the_two_calls(dtype, hq, hkv, d, bt, n_elig, k_cap, mode):
+    """actqkv_decode_step against actqkv_decode_retrieve and actqkv_retrieval_attention: caches, scores, selection, budgets and
+    output bit for bit.  "held": the cache holds the token already; "tight": a workspace without room for the copy of the budgets."""
+    sh = LayerShape(hq, hkv, d, 128, 4, 128, 256, dtype)
+    cs = B.c_shape(sh)
+    n_elig = (n_elig * bt)[:bt]
+    _say(f"[case] decode step {dtype} H{hq}/Hk{hkv}/D{d} x {bt}, {n_elig[:3]} blocks, {mode}")
+    lens = [128 * (n + 4) + 7 * i + 1 for i, n in enumerate(n_elig)]
+    lens[0] = -(-lens[0] // 128) * 128                                   # its token completes a block
+    nb = (max(lens) + 127) // 128
+    g = torch.Generator(device=DEV).manual_seed(bt + d)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rnd = lambda *x: torch.randn(*x, generator=g, device=DEV).to(td)  # noqa: E731
+    q, kc0, vc0, rep0 = rnd(bt, 1, hq, d), rnd(bt, nb, hkv, 128, d), rnd(bt, nb, hkv, d, 128), rnd(bt, nb, 4, hkv, d)
+    kn, vn = (None, None) if mode == "held" else (rnd(bt, 1, hkv, d), rnd(bt, 1, hkv, d))
+    i32, f32 = dict(dtype=torch.int32, device=DEV), dict(dtype=torch.float32, device=DEV)
+    n_ctx, nb_end = torch.tensor(lens, **i32), torch.tensor([1 + n for n in n_elig], **i32)
+    pos0 = None if mode == "held" else n_ctx - 1
+    nbs = max(1 + max(n_elig), 1) if mode == "held" else nb
+    flags = B.SELECT_ENTROPY_TOPK if mode == "topk" else 0
+    rest = None if mode == "plain" else torch.linspace(0.5, 3.0, bt, **f32)
+    ws = torch.zeros(B.workspace_bytes(cs, bt, 1, nb, k_cap), dtype=torch.uint8, device=DEV)
+    if mode == "tight":
+        ws = ws[:-256]
+    res = []
+    for one in (False, True, True):
+        r = dict(kc=kc0.clone(), vc=vc0.clone(), rep=rep0.clone(), scores=torch.zeros(bt, nb, **f32), idx=torch.full((bt, k_cap), -2, **i32),
+                 n_sel=torch.zeros(bt, **i32), theta=torch.zeros(bt, **f32), bud=torch.zeros(bt, **f32),
+                 left=torch.linspace(6.0, 9.0, bt, **f32), out=torch.zeros_like(q))
+        left = None if rest is None else r["left"]
+        args = (cs, bt, q, kn, vn, pos0, r["kc"], r["vc"], kc0.stride(0), r["rep"], rep0.stride(0), nbs, 1, nb_end, None, None, None,
+                r["scores"], nb, k_cap, left, rest, r["idx"], r["n_sel"], r["theta"], r["bud"])
+        if one:
+            B.decode_step(*args, nb, n_ctx, r["out"], None, ws, flags=flags)
+        else:
+            B.decode_retrieve(*args, flags=flags)
+            B.retrieval_attention(cs, bt, 1, q, r["kc"], r["vc"], kc0.stride(0), nb, n_ctx, r["idx"], r["n_sel"], k_cap, r["out"], None, ws)
+        torch.cuda.synchronize()
+        res.append(r)
+    two, one, again = res
+    for name in two:
+        if name in ("theta", "bud", "left") and max(n_elig) > 1024:     # the workgroup's sums have another order with 512 threads
+            assert (two[name] - one[name]).abs().max() <= 1e-5 * two[name].abs().max(), name
+        else:
+            assert torch.equal(two[name], one[name]), name
+    assert torch.equal(one["out"], again["out"])
+
+
 @pytest.mark.parametrize("n,k_cap,mode", [(5, 8, "cutoff"), (511, 32, "cutoff"), (513, 32, "cutoff"), (1500, 64, "topk"),
                                           (4000, 16, "plain"), (0, 8, "cutoff")])
 def test_decode_attention_that_selects_for_itself(n, k_cap, mode):
