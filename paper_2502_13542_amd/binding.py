@@ -190,7 +190,7 @@ def decode_step(shape: CShape, batch: int, q_tok, k_new, v_new, pos0, k_cache, v
                 rep_seq_stride: int, nb_scored: int, nb_begin: int, nb_end, probe, probe_kv, probe_norm, scores,
                 score_stride: int, k_cap: int, budget_remaining, theta_rest_sum, idx, n_sel, theta, budget, nb_capacity: int,
                 n_ctx, out, lse, workspace, stream=None, flags: int = 0) -> None:
-    """Cache update, probe, scores, selection and attention of a decode step in one call of two launches; see the header."""
+    """Cache update, probe, scores, selection and attention of a decode step in one call; see the header."""
     _calls().decode_step(shape, batch, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride, rep_keys, rep_seq_stride,
                          nb_scored, nb_begin, nb_end, probe, probe_kv, probe_norm, scores, score_stride, k_cap, int(flags),
                          budget_remaining, theta_rest_sum, idx, n_sel, theta, budget, nb_capacity, n_ctx, out, lse, workspace,

@@ -924,8 +924,11 @@ int actqkv_decode_step(const actqkv_shape* shape, int batch, const void* q_tok, 
   Workspace ws{workspace, ws_bytes};
   hipStream_t st = static_cast<hipStream_t>(stream);
   // The selection inside the attention launch, on a copy of the budget that the scoring launch makes (a workspace without
-  // room for it: a launch of its own).
-  float* copy = ws.spare(need, batch);
+  // room for it: a launch of its own).  That launch walks the local span before the selected blocks, so its sums have another
+  // order; bf16 with 128 channels has actqkv_decode_select_attention for that, and keeps the bits of the two calls here.
+  // (The other attention in that order too: 8 sequences of 32K tokens, a selection per KV head, 29.2 -> 30.2 us, because full
+  // blocks and no longer a part of the last one are left for the last round.)
+  float* copy = decode_fused_supported(*shape) ? nullptr : ws.spare(need, batch);
   ACTQKV_TRY(launch_decode_retrieve(*shape, batch, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride, rep_keys,
                                     rep_seq_stride, nb_scored, nb_begin, nb_end, probe, probe_kv, probe_norm, scores,
                                     score_stride, k_cap, copy != nullptr ? flags | ACTQKV_DECODE_SCORES_ONLY : flags,

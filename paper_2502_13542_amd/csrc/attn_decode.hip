@@ -394,25 +394,14 @@ __global__ __launch_bounds__(kDcThreads) void attn_decode_kernel(DcParams p) {
   dc_load_q<T, D>(p, s, hk, group, n, kq, qb);
   const int n_ctx = min(max(n_ctx_raw, 1), p.nb_capacity * kBlock);
   const WindowGeom g = window_geom(n_ctx, 1, p.n_init, p.n_local);
-  // initial tokens and local span, which wait for the length alone, then the selected blocks: as in the kernel that selects
-  // for itself, so the two give the same bits
-  const TileList fixed = make_tile_list(g, n_ctx - 1, nullptr, 0, p.k_cap, p.nb_capacity);
-  TileList chosen = fixed;
-  chosen.n_init_tiles = 0;
-  chosen.n_tail_tiles = 0;
-  chosen.n_sel = min(max(n_sel_raw, 0), p.k_cap);
-  chosen.idx = p.idx + sel_row * p.k_cap;
-  constexpr int kPerTile = kBlock / DcShape<T, D>::kKeys;
-  const int n_fixed = fixed.count() * kPerTile, n_chosen = chosen.n_sel * kPerTile;
+  const TileList tl = make_tile_list(g, n_ctx - 1, p.idx + sel_row * p.k_cap, n_sel_raw, p.k_cap, p.nb_capacity);
+  const int n_items = tl.count() * (kBlock / DcShape<T, D>::kKeys);
   DcAcc<D> a;
   a.clear();
   const T* kc = static_cast<const T*>(p.k_cache) + size_t(s) * p.seq_stride;
   const T* vc = static_cast<const T*>(p.v_cache) + size_t(s) * p.seq_stride;
 
-  const int it0 = wave * p.n_wg + wg, stride = p.n_wg * n_waves;
-  dc_walk<T, D>(fixed, it0, stride, n_fixed, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
-  const int done = it0 < n_fixed ? (n_fixed - it0 + stride - 1) / stride : 0;      // of this wavefront's turns
-  dc_walk<T, D>(chosen, it0 + done * stride - n_fixed, stride, n_chosen, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
+  dc_walk<T, D>(tl, wave * p.n_wg + wg, p.n_wg * n_waves, n_items, kc, vc, qb, a, p.scale_log2e, hk, p.n_kv_heads, n, kq);
   dc_finish<T, D>(p, a, dc_lds, s, hk, wg, group, n, kq, wave, n_waves);
 }
 

@@ -1413,8 +1413,10 @@ def test_decode_full_size_layer_as_benchmarked():
     ("bf16", 28, 4, 128, 3, [64, 65, 1], 40, "topk"), ("fp32", 8, 1, 64, 2, [1030, 1025], 8, "cutoff"), ("bf16", 8, 2, 64, 70, [6], 8, "cutoff"),
     ("fp32", 8, 2, 64, 2, [20, 30], 8, "held"), ("bf16", 8, 2, 64, 2, [20, 30], 8, "tight")])
 def test_decode_step_equals_the_two_calls(dtype, hq, hkv, d, bt, n_elig, k_cap, mode):
-    """actqkv_decode_step against actqkv_decode_retrieve and actqkv_retrieval_attention: caches, scores, selection, budgets and
-    output bit for bit.  "held": the cache holds the token already; "tight": a workspace without room for the copy of the budgets."""
+    """actqkv_decode_step against actqkv_decode_retrieve and actqkv_retrieval_attention: caches, scores, selection and
+    budgets bit for bit; the output up to the order in which a row's keys are summed (at most 80 blocks of fp32 sums, 2^-24 of
+    their size each, and in bf16 one rounding that may fall the other way, 2^-8), and bit for bit with bf16 and 128 channels.  "held": the
+    cache holds the token already; "tight": a workspace without room for the copy of the budgets."""
     sh = LayerShape(hq, hkv, d, 128, 4, 128, 256, dtype)
     cs = B.c_shape(sh)
     n_elig = (n_elig * bt)[:bt]
@@ -1453,7 +1455,10 @@ def test_decode_step_equals_the_two_calls(dtype, hq, hkv, d, bt, n_elig, k_cap, 
         res.append(r)
     two, one, again = res
     for name in two:
-        if name in ("theta", "bud", "left") and max(n_elig) > 1024:     # the workgroup's sums have another order with 512 threads
+        if name == "out" and (dtype, d) != ("bf16", 128):
+            scale = (2. ** -8 if dtype == "bf16" else 0.) + 80 * 128 * 2. ** -24
+            assert (two["out"].float() - one["out"].float()).abs().max() <= scale * vc0.float().abs().max()
+        elif name in ("theta", "bud", "left") and max(n_elig) > 1024:     # the workgroup's sums have another order with 512 threads
             assert (two[name] - one[name]).abs().max() <= 1e-5 * two[name].abs().max(), name
         else:
             assert torch.equal(two[name], one[name]), name
