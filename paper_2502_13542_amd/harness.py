@@ -165,8 +165,8 @@ class LayerRunner:
                     budget_remaining: Optional[torch.Tensor] = None,
                     theta_rest_sum: Optional[torch.Tensor] = None, k_new=None, v_new=None, pos0=None,
                     lse=None, stream=None) -> None:
-        """A decode step in one call of two launches (actqkv_decode_step): (cache update,) probe and scores,
-        then selection and attention.  k_new, v_new, pos0: the new
+        """A decode step in one call (actqkv_decode_step), two launches but for bf16 with 128 channels, which
+        has decode_step_two_launches: (cache update,) probe and scores, then selection and attention.  k_new, v_new, pos0: the new
         token's key, value and position per sequence, or None if the cache already holds it."""
         sh, cs, bt = self.shape, self.cs, self.batch
         nb_begin = sh.n_init // sh.block_size
@@ -412,12 +412,20 @@ class PrefillPipeline:
         team of late_cus workgroups to the current stream, behind that preparation, where it
         takes its share of what is left in the chunk's queue.
         Chunks alternate between two workspaces, so a chunk's queue is never touched by the
-        next chunk's launches."""
+        next chunk's launches.
+
+        A pass of one chunk, and perhaps a ragged window, has little to put beside its attention: it stays on the
+        current stream, with all compute units, and single windows are one call each (both pairs of events of such
+        a window bracket its whole step).  Two waits between streams cost more: 32 windows of 256 tokens in fp32
+        155 us, 123 so."""
         r, plan = self.runner, self.plan
         sh, cs = r.shape, r.cs
         nb_begin = sh.n_init // sh.block_size
-        cur, last = torch.cuda.current_stream(), self.side
-        last.wait_stream(cur)
+        cur = torch.cuda.current_stream()
+        alone = plan.n_windows - (plan.rows[-1] != r.m) <= chunk
+        last = cur if alone else self.side
+        if not alone:
+            last.wait_stream(cur)
         self.chunk_starts = []
 
         def single(u):
@@ -432,11 +440,30 @@ class PrefillPipeline:
             B.select(1, r.scores, r.score_stride, nb_cap, nb_begin, plan.nb_end[u:u + 1], r.k_cap, bud,
                      rest, self.idx[u], self.n_sel[u:u + 1], None, None)
 
+        def step(u):
+            w0, rows = plan.w0[u], plan.rows[u]
+            bud = None if plan.budget is None else plan.budget[u:u + 1]
+            rest = None if plan.rest is None else plan.rest[u:u + 1]
+            held = rep_keys.numel() // (sh.n_rep * sh.n_kv_heads * sh.head_dim)
+            nb_cap = max(min(plan.nb_end_host[u], held, r.nb_capacity), nb_begin)
+            self.chunk_starts.append(u)
+            if events is not None:
+                events[u][0].record(cur)
+            B.window_step(cs, 1, rows, q[w0:w0 + rows], r.stats, True, r.probe, self.probe_kv[u], self.probe_norm[u:u + 1],
+                          None, rep_keys, 0, nb_cap, nb_begin, plan.nb_end[u:u + 1], r.scores, r.score_stride, r.k_cap, bud,
+                          rest, self.idx[u], self.n_sel[u:u + 1], None, None, k_cache, v_cache, 0, r.nb_capacity,
+                          plan.n_ctx[u:u + 1], out[w0:w0 + rows], None, r.workspace)
+            if events is not None:
+                events[u][1].record(cur)
+
         def attend(pending):
             t_first, call = pending
             if events is not None:
                 events[t_first][0].record(last)
-            self._attention(call, last, late_cus, cur)
+            if alone:
+                B.retrieval_attention(*call)
+            else:
+                self._attention(call, last, late_cus, cur)
             if events is not None:
                 events[t_first][1].record(last)
 
@@ -447,6 +474,12 @@ class PrefillPipeline:
                 n_p += 1
             if prelude_events is not None:
                 prelude_events[t0][0].record(cur)
+            if alone and n_p < 2:
+                step(t0)
+                if prelude_events is not None:
+                    prelude_events[t0][1].record(cur)
+                t0 += 1
+                continue
             if n_p >= 2:
                 w0, t1 = plan.w0[t0], t0 + n_p
                 B.build_probe(cs, n_p, r.m, q[w0:w0 + n_p * r.m], r.stats,
@@ -464,23 +497,28 @@ class PrefillPipeline:
                 single(t0)
             if prelude_events is not None:
                 prelude_events[t0][1].record(cur)
-            selected = torch.cuda.Event()
-            selected.record(cur)
-            if pending is not None:
-                attend(pending)          # the chunk before this one; its second team follows this preparation
-            last.wait_event(selected)
+            if not alone:
+                selected = torch.cuda.Event()
+                selected.record(cur)
+                if pending is not None:
+                    attend(pending)      # the chunk before this one; its second team follows this preparation
+                last.wait_event(selected)
             self.chunk_starts.append(t0)
             w0, rows = plan.w0[t0], plan.rows[t0]
             call = (cs, n_p, rows, q[w0:w0 + n_p * rows], k_cache, v_cache, 0, r.nb_capacity,
                     plan.n_ctx[t0:t0 + n_p], self.idx[t0:t0 + n_p], self.n_sel[t0:t0 + n_p],
                     r.k_cap, out[w0:w0 + n_p * rows], None)
             call += (self.ws_attn if n_chunks % 2 == 0 else self.ws_attn_b,)
-            pending = (t0, call)
+            if alone:
+                attend((t0, call))
+            else:
+                pending = (t0, call)
             n_chunks += 1
             t0 += n_p
         if pending is not None:
             attend(pending)
-        cur.wait_stream(last)
+        if not alone:
+            cur.wait_stream(last)
 
     def _run_three_streams(self, q, k_cache, v_cache, rep_keys, out, events, chunk, score_chunk) -> None:
         """The selection chain cut in two as well.  The probe of a window (statistics, bias,
