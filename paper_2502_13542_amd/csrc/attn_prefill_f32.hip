@@ -44,7 +44,6 @@ constexpr int kFfStageBytes = 4 * kFfHalf;
 constexpr int kFfLdsBytes = 2 * kFfStageBytes;
 constexpr int kFfLazy = 8;                        // see the running maximum
 constexpr int kFfTop = 14;                        // factors bring magnitudes up to [2^14, 2^15)
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 // Workgroups of a full launch: two per compute unit; with 128 channels a little less, so that their

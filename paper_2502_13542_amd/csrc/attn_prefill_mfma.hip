@@ -10,7 +10,7 @@
 // actqkv_select (read from device memory), the local span and the causal part of the window -
 // form one list of 128-key blocks; it is cut into `splits` contiguous pieces, one workgroup
 // each, so that a 512-token window still fills all 256 compute units; the workgroup that
-// finishes last among the pieces of a query tile merges them.  Workgroups of one
+// finishes last among the pieces of a query tile merges them, or, of many pieces, a second launch.  Workgroups of one
 // KV head sit on one XCD (blockIdx % Hk picks the head), so that head's gathered
 // tiles stay in that XCD's L2.
 //
@@ -47,6 +47,7 @@ template <int KS> constexpr int kPfRows = 32 * kPfWaves / KS;   // query rows of
 template <int D> constexpr int kPfTileBytes = kBlock * D * 2;           // one K or V^T tile of a (block, KV head)
 template <int D> constexpr int kPfLdsBytes = 2 * 2 * kPfTileBytes<D>;   // 2 stages x (K, V^T)
 constexpr int kMaxPfSplits = 8;
+constexpr int kMergeWaves = 2;                       // wavefronts of a workgroup of the merge launch
 constexpr float kLazyMaxLog2 = 8.f;                  // how far a tile's maximum may exceed the reference one
 constexpr int kPfOrderMax = 64;                      // batch entries the queue hands out longest first
 // Index of the "left" counter behind the per-head queue counters: 16384 channels in heads of 64 are 256 KV heads.
@@ -102,7 +103,8 @@ struct PfParams {
   int k_cap;
   uint16_t* out;
   float* lse;
-  uint64_t* part;          // [workgroup][split][wave][its 32-channel groups x 4 x 4 bf16 | (max, sum)][64 lanes]
+  uint64_t* part;          // [workgroup][split][wave][its 32-channel groups x 4 x 4 bf16 | (max, sum)][64 lanes]; or PfPiece
+  int merge_after;         // 1: a second launch merges the pieces, 0: the workgroup that finishes last (prefill_merge_after)
   unsigned int* counters;  // one ticket counter per (sequence, query tile, KV head), zero between launches
   int m, n_q_heads, n_kv_heads, n_init, n_local;
   int s_lo, rem, slots, n_qtiles;   // pieces per query tile (PfSplits)
@@ -120,6 +122,22 @@ struct PfChosen {
   int32_t idx[64];
   int count;                        // (with PfParams::sel)
   SelectWaveLds work;
+};
+
+// The partial result of one wavefront of a piece for the merge launch: kSlots times 16 bytes per lane, then (maximum, sum).
+template <int D, int KS, bool kTwoTermP>
+struct PfPiece {
+  static constexpr int kDb = D / 32;
+  static constexpr int kMine = kDb > KS ? kDb / KS : 1;      // 32-channel groups of a wavefront after its merge in LDS
+  static constexpr bool kHalf = KS == 1 && !kTwoTermP;       // normalised and bf16
+  static constexpr int kSlots = (kHalf ? 2 : 4) * kMine;
+  static constexpr int kWords = kSlots * 64 + 32;            // 16-byte words
+  static constexpr int kTake = 2;                            // slots of a wavefront of the merge
+  static constexpr int kUnits = kPfWaves / KS * (kDb < KS ? kDb : KS) * (kSlots / kTake);   // its wavefronts per query tile
+  static_assert(kPfPieces<D, KS, kTwoTermP> ? kPfWaves * kWords * 4 <= kPfPartialFloats && kUnits % kMergeWaves == 0 : true, "pieces");
+  static __device__ __forceinline__ u32x4* at(const PfParams& p, int s, int hk, int slot, int wave) {
+    return reinterpret_cast<u32x4*>(p.part) + (((size_t(s) * p.n_kv_heads + hk) * p.slots + slot) * kPfWaves + wave) * kWords;
+  }
 };
 
 // Final normalisation and store of one lane's share of a query row:
@@ -513,7 +531,30 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     if (row_ok && has_mine) store_rows<D, kMine>(p, acc_f, db0, m_run, l_tot, s, my_row, head, half);
     return;
   }
-  // The piece stores its output in the order the registers hold it (register-major, lane-minor: every
+  // A piece for the merge launch: in the order the registers hold it, 1 KB in a row per store instruction, normalised and as
+  // bf16 where PfPiece says so.
+  if (p.merge_after) {
+    using Piece = PfPiece<D, KS, kTwoTermP>;
+    if (!has_mine) return;
+    u32x4* mine = Piece::at(p, s, hk, slot, wave) + lane;
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+#pragma unroll
+    for (int k = 0; k < Piece::kSlots; ++k) {
+      u32x4 v;
+      if constexpr (Piece::kHalf) {
+        const f32x16& o = acc_f[k / 2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = pack_bf16x2(o[8 * (k % 2) + 2 * i] * inv, o[8 * (k % 2) + 2 * i + 1] * inv);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = __float_as_uint(acc_f[k / 4][4 * (k % 4) + i]);
+      }
+      mine[k * 64] = v;
+    }
+    reinterpret_cast<f32x2*>(mine - lane + Piece::kSlots * 64)[lane] = f32x2{m_run, l_tot};
+    return;
+  }
+  // Otherwise the piece stores its output in the order the registers hold it (register-major, lane-minor: every
   // store instruction writes one contiguous 512-byte row), plus its running max and sum: of a whole
   // query tile of one-term probabilities normalised and as bf16 (64 KB), otherwise as it is.
   constexpr bool kHalf = KS == 1 && !kTwoTermP;
@@ -572,7 +613,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     const uint64_t of = ml[s2 < kMaxPfSplits ? s2 : 0];
     const float v = s2 < splits ? __builtin_amdgcn_exp2f(__uint_as_float(uint32_t(of)) - m_safe) : 0.f;
     const float vl = s2 < splits ? v * __uint_as_float(uint32_t(of >> 32)) : 0.f;
-    l_all += vl;
+    if (s2 < splits) l_all = fmaf(v, __uint_as_float(uint32_t(of >> 32)), l_all);
     w_s[s2] = kHalf ? vl : v;
   }
 #pragma unroll
@@ -598,19 +639,102 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
           for (int i = 0; i < kPerGroup; ++i) {
             const uint32_t lo = uint32_t(raw[j][db * kPerGroup + i]), hi = uint32_t(raw[j][db * kPerGroup + i] >> 32);
             if constexpr (kHalf) {
-              acc_f[db][4 * i + 0] += w * bf16_lo(lo);
-              acc_f[db][4 * i + 1] += w * bf16_hi(lo);
-              acc_f[db][4 * i + 2] += w * bf16_lo(hi);
-              acc_f[db][4 * i + 3] += w * bf16_hi(hi);
+              acc_f[db][4 * i + 0] = fmaf(w, bf16_lo(lo), acc_f[db][4 * i + 0]);
+              acc_f[db][4 * i + 1] = fmaf(w, bf16_hi(lo), acc_f[db][4 * i + 1]);
+              acc_f[db][4 * i + 2] = fmaf(w, bf16_lo(hi), acc_f[db][4 * i + 2]);
+              acc_f[db][4 * i + 3] = fmaf(w, bf16_hi(hi), acc_f[db][4 * i + 3]);
             } else {
-              acc_f[db][2 * i] += w * __uint_as_float(lo);
-              acc_f[db][2 * i + 1] += w * __uint_as_float(hi);
+              acc_f[db][2 * i] = fmaf(w, __uint_as_float(lo), acc_f[db][2 * i]);
+              acc_f[db][2 * i + 1] = fmaf(w, __uint_as_float(hi), acc_f[db][2 * i + 1]);
             }
           }
       }
     }
   }
   if (row_ok) store_rows<D, kMine>(p, acc_f, db0, m_all, l_all, s, my_row, head, half);
+}
+
+// The pieces of a query tile, in their order:  out = sum_s w_s o_s / sum_s w_s with w_s = l_s 2^(m_s - M), M = max_s m_s,
+// o_s normalised (not normalised: sum_s v_s O_s / sum_s v_s l_s with v_s = 2^(m_s - M)).
+// A wavefront merges kTake 16-byte slots of the 32 rows of a wavefront of the attention, all its loads in flight at once; blocks
+// deal the KV heads like the attention's, so that a head's pieces are read on the XCD that wrote them.  Bound by its launch and one
+// round trip: 4 to 5 us for 256 pieces (prefill_merge_after has both sides).
+template <int D, int KS, bool kTwoTermP>
+__global__ __launch_bounds__(64 * kMergeWaves) void attn_prefill_merge_kernel(PfParams p) {
+  using Piece = PfPiece<D, KS, kTwoTermP>;
+  constexpr int kTake = Piece::kTake, kParts = Piece::kSlots / kTake;
+  constexpr int kRowGroups = kPfWaves / KS, kRows = kPfRows<KS>;
+  const int lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
+  const int hk = blockIdx.x % p.n_kv_heads;
+  const int unit = __builtin_amdgcn_readfirstlane((blockIdx.x / p.n_kv_heads) * kMergeWaves + (threadIdx.x >> 6));
+  const int item = unit / Piece::kUnits, wave = unit % Piece::kUnits / kParts, part = unit % kParts;
+  const int s = item / p.n_qtiles, qtile = item - s * p.n_qtiles;
+  const int n_lo = p.n_qtiles - p.rem;
+  const int splits = qtile < n_lo ? p.s_lo : p.s_lo + 1;
+  if (splits == 1) return;                                   // (the attention has stored its rows)
+  const int slot0 = qtile < n_lo ? qtile * p.s_lo : n_lo * p.s_lo + (qtile - n_lo) * splits;
+  const u32x4* piece = Piece::at(p, s, hk, slot0, wave);
+  f32x2 ml[kMaxPfSplits];
+  u32x4 raw[kMaxPfSplits][kTake];
+#pragma unroll
+  for (int i = 0; i < kMaxPfSplits; ++i) {
+    ml[i] = f32x2{-INFINITY, 0.f};
+#pragma unroll
+    for (int k = 0; k < kTake; ++k) raw[i][k] = u32x4{0, 0, 0, 0};
+    if (i < splits) {
+      const u32x4* from = piece + size_t(i) * (kPfWaves * Piece::kWords);
+      ml[i] = reinterpret_cast<const f32x2*>(from + Piece::kSlots * 64)[lane];
+#pragma unroll
+      for (int k = 0; k < kTake; ++k) raw[i][k] = from[(part * kTake + k) * 64 + lane];
+    }
+  }
+  float m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+  for (int i = 0; i < kMaxPfSplits; ++i)
+    if (i < splits) m_all = fmaxf(m_all, ml[i].x);
+  const float m_safe = m_all == -INFINITY ? 0.f : m_all;
+  float sum[kTake][Piece::kHalf ? 8 : 4];
+#pragma unroll
+  for (int k = 0; k < kTake; ++k)
+#pragma unroll
+    for (int j = 0; j < (Piece::kHalf ? 8 : 4); ++j) sum[k][j] = 0.f;
+#pragma unroll
+  for (int i = 0; i < kMaxPfSplits; ++i) {
+    if (i < splits) {
+      const float v = __builtin_amdgcn_exp2f(ml[i].x - m_safe), vl = v * ml[i].y;
+      l_all = fmaf(v, ml[i].y, l_all);
+#pragma unroll
+      for (int k = 0; k < kTake; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if constexpr (Piece::kHalf) {
+            sum[k][2 * j] = fmaf(vl, bf16_lo(raw[i][k][j]), sum[k][2 * j]);
+            sum[k][2 * j + 1] = fmaf(vl, bf16_hi(raw[i][k][j]), sum[k][2 * j + 1]);
+          } else {
+            sum[k][j] = fmaf(v, __uint_as_float(raw[i][k][j]), sum[k][j]);
+          }
+        }
+    }
+  }
+  const int group = p.n_q_heads / p.n_kv_heads;
+  const int frow = qtile * kRows + (wave % kRowGroups) * 32 + n;
+  if (frow >= p.m * group) return;
+  const int row = frow / group, head = hk * group + (frow - row * group);
+  const int db0 = (wave / kRowGroups) * Piece::kMine;
+  const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
+  uint16_t* op = p.out + ((size_t(s) * p.m + row) * p.n_q_heads + head) * D + db0 * 32 + 4 * half;
+#pragma unroll
+  for (int k = 0; k < kTake; ++k)
+#pragma unroll
+    for (int j = 0; j < (Piece::kHalf ? 2 : 1); ++j) {
+      const int at = (part * kTake + k) * (Piece::kHalf ? 2 : 1) + j;    // group of 8 channels
+      u32x2 v;
+      v.x = pack_bf16x2(sum[k][4 * j] * inv, sum[k][4 * j + 1] * inv);
+      v.y = pack_bf16x2(sum[k][4 * j + 2] * inv, sum[k][4 * j + 3] * inv);
+      *reinterpret_cast<u32x2*>(op + 8 * at) = v;
+    }
+  if (p.lse != nullptr && half == 0 && db0 == 0 && part == 0)
+    p.lse[(size_t(s) * p.n_q_heads + head) * p.m + row] = (m_all + log2f(l_all)) * 0.6931471805599453f;
 }
 
 // blockIdx.x = w * Hk + hk: consecutive ids differ in hk, and ids are dealt round-robin to the
@@ -711,47 +835,106 @@ static int prefill_mfma_qtiles(const actqkv_shape& sh, int m, int ks) {
   return (m * (sh.n_q_heads / sh.n_kv_heads) + rows - 1) / rows;
 }
 
+// Whether a second launch merges the pieces of a query tile; otherwise the workgroup that finishes last does.  That one
+// reads the others' results back at 8 bytes a lane past the L2s, 32 KB a piece (64 KB of 128 rows) and 8 KB per us, which nothing
+// overlaps in a single window; the launch costs 4 us whatever their number.  Single windows, last workgroup | launch:
+// 32 query and 8 KV heads of 128 channels, 384 tokens in 5 pieces of 256 rows 30.2 | 24.8 us, 1024 in 2 49.2 | 50.0; as 128 rows, 256 in 4
+// 23.2 | 21.3, 512 in 2 29.1 | 29.6; as 64 rows, 64 in 8 17.7 | 13.9, 128 in 4 17.4 | 16.0, 200 in 2 19.7 | 20.1; 28 and 4 heads, 768 in 3
+// pieces of 256 rows 36.9 | 37.1.  With fewer KV heads a query tile's pieces are on more XCDs, which the launch reads from more
+// slowly: 8 and 2 heads, 256 tokens as 64 rows in 8 19.4 | 16.0, 768 as 128 rows in 5 25.5 | 23.7, 1024 in 4 27.0 | 27.4; of 64 channels,
+// 256 in 8 13.9 | 12.3, 512 in 4 14.6 | 15.0, 1024 in 4 19.8 | 21.0.
+// Of several windows in a call the last workgroup merges, beside other items (a host-cache pass of 32K tokens in groups of four
+// windows of 512 took 3520 us so, 3696 with the launch); both do the same operations in the same order, written as fmaf, so windows in one call have the bits of single ones.
+static bool prefill_merge_after(const actqkv_shape& sh, int s_lo) {
+  return s_lo >= (sh.n_kv_heads >= 4 ? 4 : 5);
+}
+
 // How a call is cut up: the query rows of a workgroup (kPfRows of ks), the pieces of the key tiles.
 //
-// Whole query tiles of 256 rows use the matrix cores and the L2 best, but a single window has few
-// of them, and cutting its key tiles into pieces for other workgroups costs 10 to 15 us: partial
-// results out, a ticket, and one compute unit reading all of them back.  With fewer rows per
-// workgroup (its wavefronts share the keys of a tile and merge in LDS) there are fewer pieces and
-// less to merge, but a tile costs 16 % (2 sharing) or 69 % (4) more per row.  The choice is the least of
-// what the busiest compute unit needs by these measured figures, in us; windows of 512 tokens, 32
-// query and 8 KV heads of 128 channels, 10 blocks: 35.8 as 256 rows in 4 pieces, 32.3 as 128 rows in 2, 34.8 as 64 rows
-// in one; 128 tokens: 28.7, 20.4, 17.1; 32 windows of 512 in a call: 597, 692, 1009.
-// With 64 channels a tile is half the work and with two-term probabilities half as much again, in the same
-// proportions: over windows of 32 to 4096 tokens and groups of 1, 4 and 7 heads (3500 to 8192 tokens with 128 channels), alone and up
-// to 32 in a call, the choice took at most 8 % longer than the best of the three, as a rule 0 to 3 %.
-PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
-  PfSplits r{1, 0, 1, 1, 1};
-  if (!prefill_mfma_supported(sh, m)) return r;
+// Whole query tiles of 256 rows use the matrix cores and the L2 best, but a single window has few of them, and pieces of
+// their key tiles cost partial results, out and back.  With fewer rows per workgroup (its wavefronts share the keys of a tile and
+// merge in LDS) there are fewer pieces and less to merge, but a tile costs more per row.
+static PfSplits prefill_cut(const actqkv_shape& sh, int batch, int m, int cus, int ks, bool pieces) {
+  const int pairs = batch * sh.n_kv_heads;
+  PfSplits c;
+  c.ks = ks;
+  c.n_qtiles = prefill_mfma_qtiles(sh, m, ks);
+  // pieces where the query tiles leave compute units idle, never more than 8 per query tile; of whole
+  // query tiles, what does not divide evenly goes to the last ones of the window
+  const int per_pair = std::max(cus / pairs, c.n_qtiles);    // workgroups one pair may have
+  c.s_lo = pieces ? std::min(per_pair / c.n_qtiles, kMaxPfSplits) : 1;
+  c.rem = c.s_lo == kMaxPfSplits || ks > 1 || !pieces ? 0 : per_pair - c.s_lo * c.n_qtiles;
+  c.slots = c.s_lo * c.n_qtiles + c.rem;
+  return c;
+}
+
+// Several windows or sequences in a call, whose items differ in length with what each retrieves: the least of what the busiest
+// compute unit needs by these figures, in us, with half of k_cap retrieved; 32 windows of 512 tokens, 32 query and 8 KV heads of
+// 128 channels: 597 as 256 rows, 692 as 128, 1009 as 64.  With 64 channels a tile is half the work and with two-term probabilities half
+// as much again, in the same proportions: over windows of 32 to 4096 tokens and groups of 1, 4 and 7 heads, up to 32 in a call, the
+// choice took at most 8 % longer than the best of the three, as a rule 0 to 3 %.
+static PfSplits prefill_splits_many(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
   constexpr double kTileUs[] = {3.7, 2.1, 1.5}, kMergeUs[] = {6., 3.5, 2.}, kMergePieceUs[] = {1.1, 0.7, 0.5};
   constexpr double kItemUs = 8.;
-  const int pairs = batch * sh.n_kv_heads;
-  // key tiles of the last query tile and of an average one; half of k_cap retrieved
-  const double longest = (sh.n_init + sh.n_local + m) / double(kBlock) + k_cap / 2.0;
-  const double average = longest - m / double(2 * kBlock);
+  const bool two = prefill_two_terms(sh, m);
+  const double longest = (sh.n_init + sh.n_local + m) / double(kBlock) + k_cap / 2.0, average = longest - m / double(2 * kBlock);
+  PfSplits r{};
   double best = 0.;
   for (int i = 0; i < 3; ++i) {
-    PfSplits c;
-    c.ks = 1 << i;
-    c.n_qtiles = prefill_mfma_qtiles(sh, m, c.ks);
-    // pieces where the query tiles leave compute units idle, never more than 8 per query tile; of whole
-    // query tiles, what does not divide evenly goes to the last ones of the window
-    const int per_pair = std::max(cus / pairs, c.n_qtiles);    // workgroups one pair may have
-    const bool pieces = sh.head_dim == 64 || c.ks > 1 || !prefill_two_terms(sh, m);    // kPfPieces
-    c.s_lo = pieces ? std::min(per_pair / c.n_qtiles, kMaxPfSplits) : 1;
-    c.rem = c.s_lo == kMaxPfSplits || c.ks > 1 || !pieces ? 0 : per_pair - c.s_lo * c.n_qtiles;
-    c.slots = c.s_lo * c.n_qtiles + c.rem;
-    const double rounds = double(pairs) * c.slots / cus;
+    const PfSplits c = prefill_cut(sh, batch, m, cus, 1 << i, sh.head_dim == 64 || i > 0 || !two);    // kPfPieces
+    const double rounds = double(batch) * sh.n_kv_heads * c.slots / cus;
     double us = std::max(std::ceil(longest / c.s_lo), rounds * average / c.s_lo) * kTileUs[i] + kItemUs * std::max(rounds, 1.);
     if (c.slots > c.n_qtiles) us += kMergeUs[i] + kMergePieceUs[i] * c.s_lo;
     if (i == 0 || us < best) {
       best = us;
       r = c;
     }
+  }
+  return r;
+}
+
+// A single window: another cut than that where these figures, in us, make less of its launch: a tile (64 channels 0.75 of it,
+// two-term probabilities with 128 1.28 times), an item's start and end, and merging.  Against 490 launches measured - windows of 64 to
+// 4096 tokens, 8 blocks, 32, 28 and 8 query heads on 8, 4 and 2 KV heads, each cut in the three ways - they are 9 % off in the root
+// mean square.  The figures above took up to 36 % longer: 28 query and 4 KV heads, 640 tokens, as 70 items of 64 rows for each of the 4, a
+// few more than compute units, 37.8 us, as 35 of 128 rows 29.8.
+// For several windows in a call they are not taken: 26 of 256 tokens with up to 32 blocks as 256 rows 185 us a pass, as 128 170.
+PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
+  PfSplits r{1, 0, 1, 1, 1};
+  if (!prefill_mfma_supported(sh, m)) return r;
+  const PfSplits many = prefill_splits_many(sh, batch, m, k_cap, cus);
+  if (batch > 1) return many;
+  const bool two = prefill_two_terms(sh, m);
+  constexpr double kTileUs[] = {3.4, 2.23, 1.73};
+  constexpr double kItemUs = 2.2;
+  const double tile_scale = sh.head_dim == 64 ? 0.75 : two ? 1.28 : 1.;
+  // the window's own key tiles, which the first query tile does not see; those that 256 query rows span
+  const double own = m / double(kBlock), span = kPfRows<1> / double(sh.n_q_heads / sh.n_kv_heads) / kBlock;
+  auto needs = [&](const PfSplits& c, double retrieved) {
+    // key tiles of the last query tile and of an average one
+    const double longest = (sh.n_init + sh.n_local) / double(kBlock) + own + retrieved, average = longest - own / 2;
+    const double tile = kTileUs[c.ks >> 1] * tile_scale;
+    const double rounds = double(sh.n_kv_heads) * c.slots / cus, share = double(c.n_qtiles) / c.slots;
+    // the longest item (of the last query tile, or of the last one with a piece less), all of them over the compute units,
+    // and the two that share a compute unit where there are some more items than those
+    double most = std::ceil(longest / (c.s_lo + (c.rem > 0)));
+    if (c.rem > 0) most = std::max(most, std::ceil((longest - c.rem * span) / c.s_lo));
+    double us = std::max(most * tile + kItemUs, rounds * (average * share * tile + kItemUs));
+    if (rounds > 1.) us = std::max(us, 2 * ((longest - own / rounds) * share * tile + kItemUs));
+    if (c.slots > c.n_qtiles) {
+      const double kb = kPfRows<1> / c.ks * sh.head_dim * (c.ks == 1 && !two ? 2 : 4) / 1024.;    // of a piece
+      us += prefill_merge_after(sh, c.s_lo) ? 5.2 + 0.54 / 1024 * kb * sh.n_kv_heads * c.slots : 1.3 + 2.7 / 64 * kb * c.s_lo;
+    }
+    return us;
+  };
+  r = many;
+  // Only with fewer wavefronts to a row: windows in one call take the cut of a single one, and there a tile's cost per row counts.
+  for (int i = 0; 1 << i < many.ks; ++i) {
+    // Whole query tiles of one-term probabilities are not cut here: their partial results would be bf16, and no window with fp32
+    // ones, or with none, loses precision to a faster cut (8 and 2 heads, 3000 tokens 62.7 -> 52.3 us, not taken).
+    const PfSplits c = prefill_cut(sh, 1, m, cus, 1 << i, sh.head_dim == 64 || i > 0);
+    // a cut-off leaves a third of k_cap or less, without one there are as many: it has to be better for both
+    if (needs(c, 0.25 * k_cap) < needs(r, 0.25 * k_cap) && needs(c, k_cap) < needs(r, k_cap)) r = c;
   }
   return r;
 }
@@ -789,6 +972,12 @@ static int launch_pf(PfParams p, int late_per_head, hipStream_t stream, hipStrea
   else
     hipLaunchKernelGGL((attn_prefill_mfma_kernel<D, KS, kTwoTermP>), grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
   if (int rc = hip_status("attention (prefill, matrix cores)")) return rc;
+  if constexpr (kPfPieces<D, KS, kTwoTermP>) if (p.merge_after) {
+    const int units = p.items_per_head / p.slots * p.n_qtiles * PfPiece<D, KS, kTwoTermP>::kUnits;     // per KV head
+    hipLaunchKernelGGL((attn_prefill_merge_kernel<D, KS, kTwoTermP>), dim3(units / kMergeWaves * p.n_kv_heads),
+                       dim3(64 * kMergeWaves), 0, stream, p);
+    if (int rc = hip_status("attention (prefill, matrix cores, merge)")) return rc;
+  }
   if (late_per_head > 0) {
     p.late = 1;
     hipLaunchKernelGGL((attn_prefill_mfma_queued_kernel<D, KS, kTwoTermP>), dim3(late_per_head * p.n_kv_heads), dim3(kPfThreads),
@@ -851,6 +1040,7 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
   p.queue = counters + kTicketCounters;
   int late_per_head = late_cus / sh.n_kv_heads;
   if (p.items_per_head <= p.wgs_per_head) late_per_head = 0;   // a workgroup per item: no queue, no second team
+  p.merge_after = batch == 1 && prefill_merge_after(sh, splits.s_lo);
   p.team_total = (p.wgs_per_head + late_per_head) * sh.n_kv_heads;
   p.late = 0;
   if (sh.head_dim == 64) return launch_pf_ks<64, true>(splits.ks, p, late_per_head, stream, stream_late);

@@ -12,6 +12,7 @@ constexpr int kWave = 64;
 constexpr int kBlock = 128;  // tokens per KV block (the only supported block size)
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -25,7 +26,6 @@ __device__ __forceinline__ float bf16_hi(uint32_t packed) {
 // round-to-nearest-even; NaN stays NaN.  One instruction per pair (v_cvt_pk_bf16_f32); as integer arithmetic it was
 // eight for each value, 2 us of an item of the prefill attention: 32 windows of 512 tokens 583 us, 569 so.
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  typedef __attribute__((ext_vector_type(2))) float f32x2;
   typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }

@@ -686,6 +686,49 @@ def test_log_sum_exp_output(dtype, d, m, nw):
             assert np.abs(lse[i, :, r] - ref).max() < tol * max(1.0, np.abs(ref).max()), f"window {i} row {r}"
 
 
+@pytest.mark.parametrize("hq,hk,d,m,nw,n_sel", [
+    (8, 2, 128, 70, 1, 4),        # 64 query rows in 8 pieces, the last tile ragged
+    (28, 4, 128, 64, 1, 0),       # the same with 7 heads, fewer key tiles than pieces
+    (32, 8, 128, 33, 2, 3),       # two sequences, a query tile with two live rows
+    (28, 4, 128, 200, 1, 4),      # 128 rows in 5 pieces
+    (8, 2, 128, 1536, 1, 4),      # 256 rows in 5 and 6 pieces, partial results normalised in bf16
+    (8, 2, 64, 100, 1, 4),        # 64 channels: 64 rows in 8
+    (8, 2, 64, 768, 1, 2),        # 128 rows in 5
+    (8, 2, 64, 1536, 1, 4)])      # 256 rows in 5 and 6, fp32 partial results
+def test_pieces_merged_by_a_launch(hq, hk, d, m, nw, n_sel):
+    """Query tiles whose key tiles are cut into four pieces and more: output and lse of rows at the edges of query tiles against
+    the oracle, twice on one workspace with the same bits."""
+    sh = LayerShape(hq, hk, d, 128, 4, 128, 256, "bf16")
+    cs = B.c_shape(sh)
+    k_cap, base = 32, 9 * 128 + 40
+    nb = (base + m + 127) // 128
+    g = torch.Generator().manual_seed(m + d)
+    q = torch.randn(nw, m, hq, d, generator=g).to(torch.bfloat16)
+    k, v = (torch.randn(nb * 128, hk, d, generator=g).to(torch.bfloat16) for _ in range(2))
+    kc, vc = H.blocked_k(k.to(DEV), sh, nb), H.blocked_vt(v.to(DEV), sh, nb)
+    idx = torch.full((nw, k_cap), -1, dtype=torch.int32)
+    idx[:, :n_sel] = torch.tensor([5, 1, 3, 6], dtype=torch.int32)[:n_sel]
+    i32 = dict(dtype=torch.int32, device=DEV)
+    ws = torch.zeros(B.workspace_bytes(cs, nw, m, nb, k_cap), dtype=torch.uint8, device=DEV)
+    outs, lses = [], []
+    for _ in range(2):
+        outs.append(torch.full((nw, m, hq, d), float("nan"), dtype=torch.bfloat16, device=DEV))
+        lses.append(torch.full((nw, hq, m), float("nan"), device=DEV))
+        B.retrieval_attention(cs, nw, m, q.to(DEV), kc, vc, 0, nb, torch.full((nw,), base + m, **i32), idx.to(DEV),
+                              torch.full((nw,), n_sel, **i32), k_cap, outs[-1], lses[-1], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(lses[0], lses[1]) and torch.isfinite(outs[0]).all()
+    lse = lses[0].cpu().numpy()
+    group = hq // hk
+    for s in range(nw):
+        for r in sorted({0, 1, 64 // group, 256 // group - 1, m // 2, m - 2, m - 1} & set(range(m))):
+            pos = orc.key_positions(base, base + r, idx[s, :n_sel].tolist(), sh.n_init, sh.n_local, 128)
+            ref = orc.attention_rows(f64(q[s, r])[None], f64(k), f64(v), pos, sh.group)[0]
+            assert out_error(outs[0][s, r], ref) < TOL_OUT["bf16"], f"sequence {s} row {r}"
+            want = _lse_reference(q[s, r], k, pos, sh.group)
+            assert np.abs(lse[s, :, r] - want).max() < 2e-3 * max(1.0, np.abs(want).max()), f"sequence {s} row {r}"
+
+
 @pytest.mark.parametrize("dtype,d,m,nw", [("bf16", 128, 256, 1), ("bf16", 128, 256, 40), ("fp32", 64, 128, 2),
                                           ("bf16", 128, 1, 4), ("fp32", 64, 1, 2)])
 def test_softmax_scale_of_the_caller(dtype, d, m, nw):
