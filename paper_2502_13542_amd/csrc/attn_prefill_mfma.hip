@@ -613,7 +613,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
     const uint64_t of = ml[s2 < kMaxPfSplits ? s2 : 0];
     const float v = s2 < splits ? __builtin_amdgcn_exp2f(__uint_as_float(uint32_t(of)) - m_safe) : 0.f;
     const float vl = s2 < splits ? v * __uint_as_float(uint32_t(of >> 32)) : 0.f;
-    if (s2 < splits) l_all = fmaf(v, __uint_as_float(uint32_t(of >> 32)), l_all);
+    l_all = fmaf(v, s2 < splits ? __uint_as_float(uint32_t(of >> 32)) : 0.f, l_all);
     w_s[s2] = kHalf ? vl : v;
   }
 #pragma unroll
