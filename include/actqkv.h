@@ -535,6 +535,12 @@ int actqkv_gather_blocks_cached(const actqkv_shape* shape, int n_windows, const 
  * span from one working cache to the next and new blocks back to the host store. */
 int actqkv_copy_bytes(void* dst, const void* src, size_t bytes, void* stream);
 
+/* How an attention call of batch windows of m >= 2 tokens in bf16 is cut up (host only, nothing is launched): cut[0] query rows of
+ * a workgroup, cut[1] query tiles of a window and KV head, cut[2] pieces they are in altogether (equal: not cut; the tiles are
+ * cut into cut[2] / cut[1] pieces, rounded down, some into one more), cut[3] 1 if a second launch merges the pieces.
+ *   cus   compute units the call may fill (actqkv_retrieval_attention_teams: first_cus), 256 otherwise. */
+int actqkv_prefill_cut(const actqkv_shape* shape, int batch, int m, int k_cap, int cus, int32_t* cut);
+
 /* Message of the last error on this thread ("" if none). */
 const char* actqkv_last_error(void);
 

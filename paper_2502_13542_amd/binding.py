@@ -90,6 +90,7 @@ SIGNATURES = {
     "actqkv_retrieval_attention_windows": (_i, [_shp, _i, _i, _vp, _vp, _vp, _i, _vp, _vp, _vp, _i, _vp, _vp, _vp, _sz,
                                                 _i, _vp]),
     "actqkv_last_error": (ctypes.c_char_p, []),
+    "actqkv_prefill_cut": (_i, [_shp, _i, _i, _i, _i, _vp]),
     "actqkv_version": (_i, []),
 }
 
@@ -160,6 +161,14 @@ def workspace_bytes(shape: CShape, batch: int, m: int, nb_capacity: int, k_cap: 
     if n == 0:
         raise ActQKVError(-1, last_error())
     return n
+
+
+def prefill_cut(shape: CShape, batch: int, m: int, k_cap: int, cus: int = 256) -> tuple:
+    """(rows of a workgroup, query tiles, pieces altogether, merged by a launch) of an attention call; see the header."""
+    cut = (ctypes.c_int32 * 4)()
+    if load_library().actqkv_prefill_cut(ctypes.byref(shape), batch, m, k_cap, cus, cut) != 0:
+        raise ActQKVError(-1, last_error())
+    return tuple(cut)
 
 
 def append_kv(shape: CShape, batch: int, m: int, k_new, v_new, pos0, k_cache, v_cache,

@@ -101,6 +101,7 @@ static int check_blocks(int nb_capacity, int nb_begin, int k_cap, bool use_k) {
   } while (0)
 
 bool prefill_mfma_supported(const actqkv_shape& sh, int m);
+bool prefill_merge_after(const actqkv_shape& sh, int s_lo);
 int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, const void* q,
                                   const void* k_cache, const void* v_cache, int64_t seq_stride,
                                   int nb_capacity, const int32_t* n_ctx, const int32_t* idx,
@@ -976,6 +977,22 @@ int actqkv_cutoff_next_step(int batch, int n_layers, float k_mean, float theta_p
 }
 
 const char* actqkv_last_error(void) { return g_error; }
+
+int actqkv_prefill_cut(const actqkv_shape* shape, int batch, int m, int k_cap, int cus, int32_t* cut) {
+  ACTQKV_TRY(check_shape(shape));
+  ACTQKV_TRY(check_batch(batch));
+  if (m > kMaxWindow || !prefill_mfma_supported(*shape, m))
+    return set_error(ACTQKV_ESHAPE, "prefill_cut: bf16 and windows of 2 to %d tokens", kMaxWindow);
+  if (k_cap < 1 || k_cap > 64) return set_error(ACTQKV_ESHAPE, "k_cap %d not supported (1..64)", k_cap);
+  if (cus < 1 || cus > kChipCus) return set_error(ACTQKV_EINVAL, "cus %d outside 1..%d", cus, kChipCus);
+  if (cut == nullptr) return set_error(ACTQKV_EINVAL, "cut is NULL");
+  const PfSplits c = prefill_splits(*shape, batch, m, k_cap, cus);
+  cut[0] = 256 / c.ks;
+  cut[1] = c.n_qtiles;
+  cut[2] = c.slots;
+  cut[3] = batch == 1 && prefill_merge_after(*shape, c.s_lo);
+  return ACTQKV_OK;
+}
 
 int actqkv_version(void) { return ACTQKV_VERSION; }
 

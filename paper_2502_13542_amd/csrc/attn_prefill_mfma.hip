@@ -845,7 +845,7 @@ static int prefill_mfma_qtiles(const actqkv_shape& sh, int m, int ks) {
 // 256 in 8 13.9 | 12.3, 512 in 4 14.6 | 15.0, 1024 in 4 19.8 | 21.0.
 // Of several windows in a call the last workgroup merges, beside other items (a host-cache pass of 32K tokens in groups of four
 // windows of 512 took 3520 us so, 3696 with the launch); both do the same operations in the same order, written as fmaf, so windows in one call have the bits of single ones.
-static bool prefill_merge_after(const actqkv_shape& sh, int s_lo) {
+bool prefill_merge_after(const actqkv_shape& sh, int s_lo) {
   return s_lo >= (sh.n_kv_heads >= 4 ? 4 : 5);
 }
 
@@ -893,21 +893,20 @@ static PfSplits prefill_splits_many(const actqkv_shape& sh, int batch, int m, in
   return r;
 }
 
-// A single window: another cut than that where these figures, in us, make less of its launch: a tile (64 channels 0.75 of it,
-// two-term probabilities with 128 1.28 times), an item's start and end, and merging.  Against 490 launches measured - windows of 64 to
-// 4096 tokens, 8 blocks, 32, 28 and 8 query heads on 8, 4 and 2 KV heads, each cut in the three ways - they are 9 % off in the root
-// mean square.  The figures above took up to 36 % longer: 28 query and 4 KV heads, 640 tokens, as 70 items of 64 rows for each of the 4, a
-// few more than compute units, 37.8 us, as 35 of 128 rows 29.8.
-// For several windows in a call they are not taken: 26 of 256 tokens with up to 32 blocks as 256 rows 185 us a pass, as 128 170.
+// A single window with two-term probabilities: another cut than that where these figures, in us, make less of its launch: a
+// tile (64 channels 0.75 of it, 128 1.28 times), an item's start and end, and merging.  Against 490 launches measured they are
+// 9 % off in the root mean square.
+// One-term probabilities keep the cut above: they are rounded to bf16 against the running maximum of the wavefronts that share a
+// tile, so another cut rounds them elsewhere and gives outputs that differ by 1e-3 of themselves.  It costs time: 28 query
+// and 4 KV heads, 640 tokens, as 70 items of 64 rows for each of the 4, a few more than compute units, 37.8 us, as 35 of 128 rows 29.8.
 PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
   PfSplits r{1, 0, 1, 1, 1};
   if (!prefill_mfma_supported(sh, m)) return r;
   const PfSplits many = prefill_splits_many(sh, batch, m, k_cap, cus);
-  if (batch > 1) return many;
-  const bool two = prefill_two_terms(sh, m);
+  if (batch > 1 || !prefill_two_terms(sh, m)) return many;
   constexpr double kTileUs[] = {3.4, 2.23, 1.73};
   constexpr double kItemUs = 2.2;
-  const double tile_scale = sh.head_dim == 64 ? 0.75 : two ? 1.28 : 1.;
+  const double tile_scale = sh.head_dim == 64 ? 0.75 : 1.28;
   // the window's own key tiles, which the first query tile does not see; those that 256 query rows span
   const double own = m / double(kBlock), span = kPfRows<1> / double(sh.n_q_heads / sh.n_kv_heads) / kBlock;
   auto needs = [&](const PfSplits& c, double retrieved) {
@@ -922,7 +921,7 @@ PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int
     double us = std::max(most * tile + kItemUs, rounds * (average * share * tile + kItemUs));
     if (rounds > 1.) us = std::max(us, 2 * ((longest - own / rounds) * share * tile + kItemUs));
     if (c.slots > c.n_qtiles) {
-      const double kb = kPfRows<1> / c.ks * sh.head_dim * (c.ks == 1 && !two ? 2 : 4) / 1024.;    // of a piece
+      const double kb = kPfRows<1> / c.ks * sh.head_dim * 4 / 1024.;    // of a piece
       us += prefill_merge_after(sh, c.s_lo) ? 5.2 + 0.54 / 1024 * kb * sh.n_kv_heads * c.slots : 1.3 + 2.7 / 64 * kb * c.s_lo;
     }
     return us;
@@ -930,8 +929,6 @@ PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int
   r = many;
   // Only with fewer wavefronts to a row: windows in one call take the cut of a single one, and there a tile's cost per row counts.
   for (int i = 0; 1 << i < many.ks; ++i) {
-    // Whole query tiles of one-term probabilities are not cut here: their partial results would be bf16, and no window with fp32
-    // ones, or with none, loses precision to a faster cut (8 and 2 heads, 3000 tokens 62.7 -> 52.3 us, not taken).
     const PfSplits c = prefill_cut(sh, 1, m, cus, 1 << i, sh.head_dim == 64 || i > 0);
     // a cut-off leaves a third of k_cap or less, without one there are as many: it has to be better for both
     if (needs(c, 0.25 * k_cap) < needs(r, 0.25 * k_cap) && needs(c, k_cap) < needs(r, k_cap)) r = c;
