@@ -323,7 +323,8 @@ int actqkv_retrieval_attention_per_head(const actqkv_shape* shape, int batch, in
  *            work, so that the team starts once that work has drained and takes its share of
  *            whatever is left in the queue.  Nobody waits: if nothing is left, or the call has no
  *            queue (m = 1, fp32, a workgroup per item already), the second team leaves at once or
- *            is not launched at all.  The output does not depend on who runs which item.
+ *            is not launched at all.  The output does not depend on who runs which item.  With stream_late
+ *            the same as stream there is one launch of first_cus + late_cus (256 at most).
  *   stream, stream_late  both must be ordered behind the selection that wrote idx and n_sel.  The
  *            two launches share the workspace (the one case where work on two streams does); the
  *            next call on the same workspace must be ordered behind both streams.

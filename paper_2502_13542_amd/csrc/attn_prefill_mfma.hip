@@ -1033,7 +1033,14 @@ int launch_attention_prefill_mfma(const actqkv_shape& sh, int batch, int m, cons
   if (splits.slots > p.n_qtiles && size_t(batch) * p.n_qtiles * sh.n_kv_heads > kTicketCounters)
     return set_error(ACTQKV_EINVAL, "prefill attention: more split query tiles than ticket counters");
   p.items_per_head = splits.slots * batch;
-  p.wgs_per_head = std::min(p.items_per_head, std::max(1, first_cus / sh.n_kv_heads));
+  // On the first team's own stream a second team would come when all is done: its workgroups belong to the first one
+  // then (the cut stays that for first_cus).
+  int team_cus = first_cus;
+  if (late_cus > 0 && stream_late == stream) {
+    team_cus = std::min(first_cus + late_cus, kChipCus);
+    late_cus = 0;
+  }
+  p.wgs_per_head = std::min(p.items_per_head, std::max(1, team_cus / sh.n_kv_heads));
   p.queue = counters + kTicketCounters;
   int late_per_head = late_cus / sh.n_kv_heads;
   if (p.items_per_head <= p.wgs_per_head) late_per_head = 0;   // a workgroup per item: no queue, no second team

@@ -415,9 +415,9 @@ class PrefillPipeline:
         next chunk's launches.
 
         A pass of one chunk, and perhaps a ragged window, has little to put beside its attention: it stays on the
-        current stream, with all compute units, and single windows are one call each (both pairs of events of such
-        a window bracket its whole step).  Two waits between streams cost more: 32 windows of 256 tokens in fp32
-        155 us, 123 so."""
+        current stream, both teams as one, and a single window whose cut does not depend on attention_cus is one
+        call (both pairs of events of such a window bracket its whole step).  Two waits between streams cost more:
+        32 windows of 256 tokens in fp32 155 us, 123 so."""
         r, plan = self.runner, self.plan
         sh, cs = r.shape, r.cs
         nb_begin = sh.n_init // sh.block_size
@@ -440,6 +440,11 @@ class PrefillPipeline:
             B.select(1, r.scores, r.score_stride, nb_cap, nb_begin, plan.nb_end[u:u + 1], r.k_cap, bud,
                      rest, self.idx[u], self.n_sel[u:u + 1], None, None)
 
+        def one_call(rows):
+            # actqkv_window_step cuts the keys for 256 compute units; the bits of bf16 belong to the cut
+            return sh.dtype != "bf16" or rows == 1 or self.attention_cus >= 256 or (
+                B.prefill_cut(cs, 1, rows, r.k_cap, self.attention_cus) == B.prefill_cut(cs, 1, rows, r.k_cap))
+
         def step(u):
             w0, rows = plan.w0[u], plan.rows[u]
             bud = None if plan.budget is None else plan.budget[u:u + 1]
@@ -460,10 +465,7 @@ class PrefillPipeline:
             t_first, call = pending
             if events is not None:
                 events[t_first][0].record(last)
-            if alone:
-                B.retrieval_attention(*call)
-            else:
-                self._attention(call, last, late_cus, cur)
+            self._attention(call, last, late_cus, cur)
             if events is not None:
                 events[t_first][1].record(last)
 
@@ -474,7 +476,7 @@ class PrefillPipeline:
                 n_p += 1
             if prelude_events is not None:
                 prelude_events[t0][0].record(cur)
-            if alone and n_p < 2:
+            if alone and n_p < 2 and one_call(plan.rows[t0]):
                 step(t0)
                 if prelude_events is not None:
                     prelude_events[t0][1].record(cur)

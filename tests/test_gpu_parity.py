@@ -2675,6 +2675,42 @@ def test_pipeline_with_ragged_last_window_and_short_context():
         assert err < TOL_OUT["bf16"], f"last window of {n_ctx}: {err}"
 
 
+@pytest.mark.parametrize("hq,hk,d,dtype,m,n_ctx,cus", [
+    (8, 2, 128, "bf16", 512, 13 * 512 + 497, 224),     # other cuts for 224 compute units than for 256, chunk and last window
+    (28, 4, 128, "bf16", 256, 3 * 256 + 200, 128),
+    (32, 8, 128, "bf16", 512, 2 * 512 + 1, 128),       # a last window of one token
+    (8, 2, 64, "fp32", 256, 5 * 256 + 31, 224)])
+def test_pass_of_one_chunk_cuts_for_the_attentions_compute_units(hq, hk, d, dtype, m, n_ctx, cus):
+    """attention_cus says how a pass is cut up, and with it the bits of bf16 outputs: a pass that is one chunk gives those of
+    its attention calls made on that many compute units, with a second team on another stream or without."""
+    w = synth.scaled(synth.WORKLOADS["c3_128k"], shape=LayerShape(hq, hk, d, 128, 4, 128, 256, dtype), n_ctx=n_ctx, window=m,
+                     k_cap=8, name="one_chunk")
+    sh, cs = w.shape, B.c_shape(w.shape)
+    q, k, v = synth.gen_layer(w, "cpu", 0)
+    rep = synth.pick_rep_keys(k, 128, sh.n_rep)
+    qd, kc, vc = q.to(DEV), H.blocked_k(k.to(DEV), sh, w.n_blocks), H.blocked_vt(v.to(DEV), sh, w.n_blocks)
+    repd = torch.zeros(w.n_blocks, sh.n_rep, hk, d, dtype=rep.dtype, device=DEV)
+    repd[: rep.shape[0]] = rep.to(DEV)
+    runner = H.LayerRunner(sh, 1, m, w.n_blocks, w.k_cap, DEV)
+    plan = H.make_prefill_plan(sh, n_ctx, m, None, DEV)
+    pipe = H.PrefillPipeline(runner, plan)
+    n, last = n_ctx // m, n_ctx % m
+    if dtype == "bf16":
+        assert any(B.prefill_cut(cs, b, x, 8, cus) != B.prefill_cut(cs, b, x, 8) for b, x in ((n, m), (1, last)) if x > 1)
+    want = torch.zeros_like(qd)
+    for late in (0, 32):
+        out = torch.zeros_like(qd)
+        runner.reset()
+        pipe.run(qd, kc, vc, repd, out, True, chunk=32, batched=True, late_cus=late, attention_cus=cus)
+        for w0, b, rows in ((0, n, m), (n * m, 1, last)):
+            t = w0 // m
+            B.retrieval_attention_teams(cs, b, rows, qd[w0:w0 + b * rows], kc, vc, 0, w.n_blocks, plan.n_ctx[t:t + b],
+                                        pipe.idx[t:t + b], pipe.n_sel[t:t + b], 8, want[w0:w0 + b * rows], None, pipe.ws_attn,
+                                        cus, 0, None, None)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+
+
 def test_mean_pooling_probe_variant():
     """The ablation baseline: every token of the window weighs 1/m, the statistics are still kept."""
     sh = LayerShape(32, 8, 128, 128, 4, 128, 512, "bf16")
