@@ -422,7 +422,7 @@ class PrefillPipeline:
         sh, cs = r.shape, r.cs
         nb_begin = sh.n_init // sh.block_size
         cur = torch.cuda.current_stream()
-        alone = plan.n_windows - (plan.rows[-1] != r.m) <= chunk
+        alone = sum(rows == r.m for rows in plan.rows) <= chunk
         last = cur if alone else self.side
         if not alone:
             last.wait_stream(cur)

@@ -2711,6 +2711,21 @@ def test_pass_of_one_chunk_cuts_for_the_attentions_compute_units(hq, hk, d, dtyp
         assert torch.equal(out, want)
 
 
+def test_pass_over_no_windows():
+    """A context without tokens is a pass without launches, in every schedule."""
+    w = synth.scaled(synth.WORKLOADS["c2_32k"], n_ctx=512)
+    sh = w.shape
+    runner = H.LayerRunner(sh, 1, w.window, w.n_blocks, w.k_cap, DEV)
+    pipe = H.PrefillPipeline(runner, H.make_prefill_plan(sh, 0, w.window, None, DEV))
+    empty = lambda *s: torch.zeros(*s, dtype=torch.bfloat16, device=DEV)  # noqa: E731
+    nb, hk, d = w.n_blocks, sh.n_kv_heads, sh.head_dim
+    for kw in (dict(overlap=False), dict(score_chunk=4), dict(score_chunk=0), dict(batched=True, late_cus=32)):
+        out = empty(0, sh.n_q_heads, d)
+        pipe.run(empty(0, sh.n_q_heads, d), empty(nb, hk, 128, d), empty(nb, hk, d, 128), empty(nb, 4, hk, d), out, **kw)
+        torch.cuda.synchronize()
+        assert pipe.chunk_starts == []
+
+
 def test_mean_pooling_probe_variant():
     """The ablation baseline: every token of the window weighs 1/m, the statistics are still kept."""
     sh = LayerShape(32, 8, 128, 128, 4, 128, 512, "bf16")
