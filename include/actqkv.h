@@ -380,10 +380,10 @@ int actqkv_window_step(const actqkv_shape* shape, int batch, int m, const void* 
                        int64_t cache_seq_stride, int nb_capacity, const int32_t* n_ctx, void* out, float* lse,
                        void* workspace, size_t ws_bytes, void* stream);
 
-/* A decode step in ONE call: actqkv_decode_retrieve and actqkv_retrieval_attention with m = 1 and
- * the arguments of the two, every storage type and head size, with their results (the selection runs inside the
- * attention launch; the output up to the order in which a row's keys are summed; bf16 with head_dim 128: three launches and
- * bit for bit; budget_remaining is updated in place).
+/* A decode step in ONE call: actqkv_decode_retrieve and actqkv_retrieval_attention with m = 1 and the arguments of the two,
+ * every storage type and head size (budget_remaining is updated in place), with their results bit for bit.  One exception: where the
+ * selection runs inside the attention launch - fp32, or 64 channels per head, at most 1024 blocks in nb_begin .. nb_scored,
+ * k_cap at most 32 and a workspace of actqkv_workspace_bytes - the keys of a row are summed in another order.
  *   nb_scored    nb_capacity of actqkv_decode_retrieve (what scores, rep_keys and, with k_new, the caches are long);
  *                nb_capacity is that of the attention.
  *   flags        0 or ACTQKV_SELECT_ENTROPY_TOPK.

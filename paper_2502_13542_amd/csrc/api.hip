@@ -924,12 +924,14 @@ int actqkv_decode_step(const actqkv_shape* shape, int batch, const void* q_tok, 
   if (ws_bytes < need) return set_error(ACTQKV_EWORKSPACE, "workspace has %zu bytes, decode_step needs %zu", ws_bytes, need);
   Workspace ws{workspace, ws_bytes};
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // The selection inside the attention launch, on a copy of the budget that the scoring launch makes (a workspace without
-  // room for it: a launch of its own).  That launch walks the local span before the selected blocks, so its sums have another
-  // order; bf16 with 128 channels has actqkv_decode_select_attention for that, and keeps the bits of the two calls here.
+  // The selection inside the attention launch, on a copy of the budget that the scoring launch makes, where one wavefront
+  // selects (a workspace without room for the copy, and rows that a launch gives to 1024 threads: a launch of its own, in which a
+  // row is selected once and not by every workgroup).  The attention walks the local span before the selected blocks then, so its
+  // sums have another order; bf16 with 128 channels has actqkv_decode_select_attention for that, and keeps the bits of the two calls here.
   // (The other attention in that order too: 8 sequences of 32K tokens, a selection per KV head, 29.2 -> 30.2 us, because full
   // blocks and no longer a part of the last one are left for the last round.)
-  float* copy = decode_fused_supported(*shape) ? nullptr : ws.spare(need, batch);
+  const bool inside = !decode_fused_supported(*shape) && select_inside_supported(nb_scored - nb_begin, k_cap, flags);
+  float* copy = inside ? ws.spare(need, batch) : nullptr;
   ACTQKV_TRY(launch_decode_retrieve(*shape, batch, q_tok, k_new, v_new, pos0, k_cache, v_cache, cache_seq_stride, rep_keys,
                                     rep_seq_stride, nb_scored, nb_begin, nb_end, probe, probe_kv, probe_norm, scores,
                                     score_stride, k_cap, copy != nullptr ? flags | ACTQKV_DECODE_SCORES_ONLY : flags,
