@@ -505,26 +505,27 @@ int actqkv_window_step(const actqkv_shape* shape, int batch, int m, const void* 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const bool apart = nb_scored > nb_begin && probe_finish_apart(*shape, batch, m, update_stats);
   ACTQKV_TRY(launch_probe(*shape, batch, m, q_win, stats, update_stats, probe, probe_kv, probe_norm, weights, ws, st, !apart));
-  // The selection inside the attention launch: the scoring launch keeps a copy of the budget for it behind what the call
-  // needs of the workspace (a workspace without those bytes: a launch of its own).  Four windows of 512 tokens at 64K with the
+  // The selection inside the attention launch: the scoring launch keeps a copy of the cut-off state for it behind what the call
+  // needs of the workspace (a workspace without those bytes: a launch of its own), because a workgroup writes the results while
+  // others still read, and they may be written where the state was read (budget_remaining always is, theta may be theta_rest_sum).  Four windows of 512 tokens at 64K with the
   // selection as a launch of its own 244 us, inside 236; of 256 tokens with 64 channels 133, 128.
   float* copy = ws.spare(need, batch);
   if (apart && copy != nullptr && select_inside_supported(nb_scored - nb_begin, k_cap, flags)) {
     ACTQKV_TRY(launch_score_probe(*shape, probe, probe_kv, probe_norm, rep_keys, nb_scored, nb_begin, nb_end, scores,
-                                  budget_remaining, copy, st));
+                                  budget_remaining, theta_rest_sum, copy, st));
     SelectInside inside;
     inside.scores = scores;
     inside.nb_begin = nb_begin;
     inside.nb_capacity = nb_scored;
     inside.nb_end = nb_end;
     inside.entropy_topk = (flags & ACTQKV_SELECT_ENTROPY_TOPK) != 0;
-    inside.io = SelectIo{budget_remaining != nullptr ? copy : nullptr, theta_rest_sum, budget_remaining, idx, n_sel, theta, budget, false};
+    inside.io = SelectIo{budget_remaining != nullptr ? copy : nullptr, copy + 1, budget_remaining, idx, n_sel, theta, budget, false};
     if (flags & ACTQKV_SELECT_GIVEN_COUNT) inside.io.count_in = n_sel;   // (clamped twice it is the same)
     return launch_attention(*shape, batch, m, q_win, k_cache, v_cache, cache_seq_stride, nb_capacity, n_ctx, idx, n_sel, k_cap,
                             out, lse, ws, 0, st, kChipCus, 0, nullptr, false, &inside);
   }
   ACTQKV_TRY(apart ? launch_score_probe(*shape, probe, probe_kv, probe_norm, rep_keys, nb_scored, nb_begin, nb_end, scores,
-                                        nullptr, nullptr, st)
+                                        nullptr, nullptr, nullptr, st)
                    : launch_score(*shape, batch, probe_kv, probe_norm, rep_keys, rep_seq_stride, nb_scored, nb_begin, nb_end,
                                   scores, score_stride, st));
   ACTQKV_TRY(launch_select(batch, scores, score_stride, nb_scored, nb_begin, nb_end, k_cap, flags, budget_remaining,
@@ -924,7 +925,7 @@ int actqkv_decode_step(const actqkv_shape* shape, int batch, const void* q_tok, 
   if (ws_bytes < need) return set_error(ACTQKV_EWORKSPACE, "workspace has %zu bytes, decode_step needs %zu", ws_bytes, need);
   Workspace ws{workspace, ws_bytes};
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // The selection inside the attention launch, on a copy of the budget that the scoring launch makes, where one wavefront
+  // The selection inside the attention launch, on a copy of the cut-off state that the scoring launch makes, where one wavefront
   // selects (a workspace without room for the copy, and rows that a launch gives to 1024 threads: a launch of its own, in which a
   // row is selected once and not by every workgroup).  The attention walks the local span before the selected blocks then, so its
   // sums have another order; bf16 with 128 channels has actqkv_decode_select_attention for that, and keeps the bits of the two calls here.
@@ -942,7 +943,7 @@ int actqkv_decode_step(const actqkv_shape* shape, int batch, const void* q_tok, 
   const float scale = shape->softmax_scale > 0.f ? shape->softmax_scale : 1.f / std::sqrt(float(shape->head_dim));
   return launch_attention_decode_select(*shape, batch, q_tok, k_cache, v_cache, cache_seq_stride, nb_capacity, n_ctx, scores,
                                         score_stride, nb_begin, nb_scored, nb_end, k_cap, flags,
-                                        budget_remaining != nullptr ? copy : nullptr, theta_rest_sum, budget_remaining, idx,
+                                        budget_remaining != nullptr ? copy : nullptr, copy + batch, budget_remaining, idx,
                                         n_sel, theta, budget, out, lse, ws.scratch_f32(), ws.counters(), scale, st);
 }
 

@@ -47,8 +47,9 @@ struct DrParams {
   int n_score_wg;
   int n_q_heads, n_kv_heads, head_dim, n_rep;
   float inv_sqrt_g;
-  const float* budget;      // kCopy: copied to budget_copy, for a selection inside the attention launch
-  float* budget_copy;
+  const float* budget;      // kCopy: these are copied to cut_copy, one array after the other, for a selection inside the
+  const float* rest;        // attention launch
+  float* cut_copy;
 };
 
 // (kCopy as an argument of the kernel cost the steps that have no use for it 0.3 us a launch)
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(kDrThreads) void decode_score_kernel(DrParams<T> p)
       for (int e = threadIdx.x; e < key_len; e += kDrThreads) p.probe_kv[size_t(s) * key_len + e] = pkv_lds[e];
     if (p.probe_norm != nullptr && threadIdx.x == 0) p.probe_norm[s] = pn;
     if constexpr (kCopy)
-      if (threadIdx.x == 0) p.budget_copy[s] = p.budget[s];
+      if (threadIdx.x == 0) p.cut_copy[s] = p.budget[s], p.cut_copy[gridDim.y + s] = p.rest[s];
   }
   if (!live) return;
   const float total = scorer.finish(pkv_lds, pn, p.inv_sqrt_g);
@@ -185,7 +186,7 @@ int launch_decode_retrieve(const actqkv_shape& sh, int batch, const void* q_tok,
                            int nb_begin, const int32_t* nb_end, float* probe, float* probe_kv,
                            float* probe_norm, float* scores, int64_t score_stride, int k_cap, int flags,
                            float* budget_remaining, const float* theta_rest_sum, int32_t* idx,
-                           int32_t* n_sel, float* theta, float* budget, hipStream_t stream, float* budget_copy) {
+                           int32_t* n_sel, float* theta, float* budget, hipStream_t stream, float* cut_copy) {
   auto fill = [&](auto& p) {
     p.pos0 = pos0;
     p.cache_stride = cache_stride;
@@ -198,8 +199,9 @@ int launch_decode_retrieve(const actqkv_shape& sh, int batch, const void* q_tok,
     p.probe_norm = probe_norm;
     p.scores = scores;
     p.score_stride = score_stride;
-    p.budget = budget_copy != nullptr ? budget_remaining : nullptr;
-    p.budget_copy = budget_copy;
+    p.budget = cut_copy != nullptr ? budget_remaining : nullptr;
+    p.rest = theta_rest_sum;
+    p.cut_copy = cut_copy;
   };
   int rc;
   if (sh.dtype == ACTQKV_F32) {

@@ -103,12 +103,12 @@ struct Workspace {
   float* scratch_f32() const {
     return reinterpret_cast<float*>(static_cast<char*>(base) + kCounterBytes);
   }
-  // a float per sequence at its end that no launch of a call which needs `need` bytes uses, or NULL
+  // two floats per sequence at its end that no launch of a call which needs `need` bytes uses, or NULL
   float* spare(size_t need, int batch) const {
     const size_t mine = spare_bytes(batch), at = bytes / 16 * 16;
     return at >= mine && at - mine >= need ? reinterpret_cast<float*>(static_cast<char*>(base) + at - mine) : nullptr;
   }
-  static size_t spare_bytes(int batch) { return align_up(size_t(batch) * sizeof(float), 256); }
+  static size_t spare_bytes(int batch) { return align_up(size_t(batch) * 2 * sizeof(float), 256); }
 };
 
 // ---- launchers (one per entry point; arguments already validated) ----------
@@ -120,11 +120,11 @@ bool probe_finish_apart(const actqkv_shape& sh, int batch, int m, int update_sta
 int launch_score(const actqkv_shape& sh, int batch, const float* probe_kv, const float* probe_norm,
                  const void* rep_keys, int64_t seq_stride, int nb_capacity, int nb_begin,
                  const int32_t* nb_end, float* scores, int64_t score_stride, hipStream_t stream);
-// one sequence: norm and per-KV-head sum of the probe, and the scores, in one launch (at least one block); budget, if not
-// NULL, is copied for a selection inside the attention launch
+// one sequence: norm and per-KV-head sum of the probe, and the scores, in one launch (at least one block); budget and rest, if not
+// NULL, are copied to cut_copy for a selection inside the attention launch
 int launch_score_probe(const actqkv_shape& sh, const float* probe, float* probe_kv, float* probe_norm,
                        const void* rep_keys, int nb_capacity, int nb_begin, const int32_t* nb_end, float* scores,
-                       const float* budget, float* budget_copy, hipStream_t stream);
+                       const float* budget, const float* rest, float* cut_copy, hipStream_t stream);
 struct SelectInside;
 bool select_inside_supported(int n_blocks, int k_cap, int flags);   // whether an attention launch can make this selection itself
 int launch_select(int batch, const float* scores, int64_t score_stride, int nb_capacity, int nb_begin,
@@ -156,7 +156,7 @@ int launch_decode_retrieve(const actqkv_shape& sh, int batch, const void* q_tok,
                            float* budget_remaining, const float* theta_rest_sum, int32_t* idx,
                            int32_t* n_sel, float* theta, float* budget,
                            hipStream_t stream,    // k_new NULL: no cache update
-                           float* budget_copy = nullptr);   // [batch]: budget_remaining as it was
+                           float* cut_copy = nullptr);      // [2][batch]: budget_remaining and theta_rest_sum as they were
 
 // a whole decode layer in one launch (bf16, head_dim 128); k_new NULL: no cache update
 int launch_decode_layer(const actqkv_shape& sh, int batch, const void* q, const void* k_new, const void* v_new,

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(1024) void score_probe_kernel(const float* __restri
                                                            int nb_capacity, int nb_begin, const int32_t* __restrict__ nb_end,
                                                            float* __restrict__ scores, int n_rep, int key_len, int group,
                                                            int head_dim, float inv_sqrt_g, const float* __restrict__ budget,
-                                                           float* __restrict__ budget_copy) {
+                                                           const float* __restrict__ rest, float* __restrict__ cut_copy) {
   extern __shared__ __attribute__((aligned(16))) float probe_lds[];  // [key_len]
   __shared__ float red[32];
   constexpr int kHeads = 8;                                          // the largest group
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(1024) void score_probe_kernel(const float* __restri
       *reinterpret_cast<f32x4*>(probe_kv + e) = *reinterpret_cast<const f32x4*>(probe_lds + e);
     if (threadIdx.x == 0) {
       *probe_norm = pn;
-      if (budget != nullptr) *budget_copy = *budget;
+      if (budget != nullptr) cut_copy[0] = *budget, cut_copy[1] = *rest;
     }
   }
   if (b >= end) return;
@@ -349,13 +349,13 @@ static int score_waves(int batch, int n) {
 
 int launch_score_probe(const actqkv_shape& sh, const float* probe, float* probe_kv, float* probe_norm,
                        const void* rep_keys, int nb_capacity, int nb_begin, const int32_t* nb_end, float* scores,
-                       const float* budget, float* budget_copy, hipStream_t stream) {
+                       const float* budget, const float* rest, float* cut_copy, hipStream_t stream) {
   const int n = nb_capacity - nb_begin, key_len = sh.n_kv_heads * sh.head_dim, group = sh.n_q_heads / sh.n_kv_heads;
   const int waves = score_waves(1, n);
   auto launch = [&](auto kernel, auto* keys) {
     hipLaunchKernelGGL(kernel, dim3((n + waves - 1) / waves), dim3(64 * waves), size_t(key_len) * sizeof(float), stream, probe,
                        probe_kv, probe_norm, keys, nb_capacity, nb_begin, nb_end, scores, sh.n_rep, key_len, group, sh.head_dim,
-                       1.f / sqrtf(float(group)), budget, budget_copy);
+                       1.f / sqrtf(float(group)), budget, rest, cut_copy);
   };
   if (sh.dtype == ACTQKV_F32)
     launch(score_probe_kernel<float>, static_cast<const float*>(rep_keys));

@@ -458,7 +458,8 @@ __device__ __forceinline__ void select_wave(const float* __restrict__ sc_mem, in
 
 // The selection of a window's one sequence inside its attention launch (scores NULL: idx and n_sel hold it already).  Every
 // workgroup repeats it, by one wavefront, while the others ask for their queries and the initial tokens; the first one writes it
-// out.  io.budget_in is a copy: budget_after is written while other workgroups still read.
+// out.  io.budget_in and io.theta_rest_sum are copies: budget_after and theta, which may be the arrays these were, are written
+// while other workgroups still read.
 struct SelectInside {
   const float* scores = nullptr;
   int nb_begin = 0, nb_capacity = 0;

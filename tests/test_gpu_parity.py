@@ -1117,6 +1117,47 @@ def test_window_step_that_selects_in_its_attention(dtype, m, n_elig, k_cap, mode
             assert torch.equal(a[name], b[name]), name
 
 
+@pytest.mark.parametrize("dtype,m", [("fp32", 4096), ("bf16", 4096), ("fp32", 1), ("bf16", 1)])
+def test_theta_written_where_its_rest_was_read(dtype, m):
+    """theta and theta_rest_sum as one array: the results of actqkv_select, which reads before it writes, also where every
+    workgroup of an attention launch selects for itself (windows in more workgroups than the chip holds at once; decode steps of many
+    sequences), so that the last ones start when the first has written."""
+    bt, hq, hkv, n_elig, k_cap = (1 if m > 1 else 300), 32, 8, 50, 16
+    sh = LayerShape(hq, hkv, 64, 128, 4, 128, 256, dtype)
+    cs = B.c_shape(sh)
+    n0 = 128 + 128 * n_elig + 256
+    nb = (n0 + m + 127) // 128
+    g = torch.Generator(device=DEV).manual_seed(m)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rnd = lambda *x: torch.randn(*x, generator=g, device=DEV).to(td)  # noqa: E731
+    i32, f32 = dict(dtype=torch.int32, device=DEV), dict(dtype=torch.float32, device=DEV)
+    q, kc, vc, rep = rnd(bt, m, hq, 64), rnd(bt, nb, hkv, 128, 64), rnd(bt, nb, hkv, 64, 128), rnd(bt, nb, 4, hkv, 64)
+    n_ctx, nb_end = torch.full((bt,), n0 + m, **i32), torch.full((bt,), 1 + n_elig, **i32)
+    ws = torch.zeros(B.workspace_bytes(cs, bt, m, nb, k_cap), dtype=torch.uint8, device=DEV)
+    st, scores = torch.zeros(bt, B.stats_floats(cs), **f32), torch.zeros(bt, nb, **f32)
+    probe, kv, norm, w = (torch.zeros(bt, x, **f32) for x in (hq * 64, hkv * 64, 1, m))
+    new = lambda: dict(idx=torch.full((bt, k_cap), -1, **i32), n_sel=torch.zeros(bt, **i32), theta=torch.full((bt,), 0.7, **f32),  # noqa: E731
+                       bud=torch.zeros(bt, **f32), left=torch.full((bt,), 9.3, **f32), out=torch.zeros_like(q))
+    a, b = new(), new()
+    if m > 1:
+        B.window_step(cs, 1, m, q, st, True, probe, kv, norm, w, rep, 0, 1 + n_elig, 1, nb_end, scores, nb, k_cap, a["left"],
+                      a["theta"], a["idx"], a["n_sel"], a["theta"], a["bud"], kc, vc, 0, nb, n_ctx, a["out"], None, ws)
+    else:
+        B.decode_step(cs, bt, q, None, None, None, kc, vc, kc.stride(0), rep, rep.stride(0), 1 + n_elig, 1, nb_end, None, None, None,
+                      scores, nb, k_cap, a["left"], a["theta"], a["idx"], a["n_sel"], a["theta"], a["bud"], nb, n_ctx, a["out"],
+                      None, ws)
+    B.select(bt, scores, nb, 1 + n_elig, 1, nb_end, k_cap, b["left"], b["theta"], b["idx"], b["n_sel"], b["theta"], b["bud"])
+    B.retrieval_attention(cs, bt, m, q, kc, vc, 0 if m > 1 else kc.stride(0), nb, n_ctx, b["idx"], b["n_sel"], k_cap, b["out"], None, ws)
+    torch.cuda.synchronize()
+    assert (b["n_sel"] > 1).all() and (b["theta"] > 1.0).all()
+    for name in a:
+        if name == "out" and m == 1:                             # (the keys of a row in another order, as in the test of the step)
+            scale = (2. ** -8 if dtype == "bf16" else 0.) + 80 * 128 * 2. ** -24
+            assert (a["out"].float() - b["out"].float()).abs().max() <= scale * vc.float().abs().max()
+        else:
+            assert torch.equal(a[name], b[name]), name
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 129, 257, 1000, 1024])
 def test_selection_by_one_wavefront_where_few_lanes_hold_the_best(n):
     """The wavefront keeps three candidates per lane (block i is lane i % 64's): the best blocks all in one lane, in two,
