@@ -2,22 +2,22 @@
 // ones as fp32 products and sums give them, or closer.
 //
 // The fp32 matrix instruction does 256 operations per clock and compute unit, a sixteenth of the 16-bit one.  So a value
-// enters as two halves of 11 bits, hi = f16(x f) and lo = f16(x f - hi), f a power of two, and a product as three of the
-// four half products, lo hi + hi lo + hi hi, exact each, summed in fp32 (lo lo is below 2^-24 of the product).
-// f brings the largest magnitude to [2^14, 2^15): per 16 (64 channels) or 8 (128) keys, per query row, and per quarter of the
-// channels of V, so a value 2^15 times smaller than the largest beside it still has all of its 24 bits and a smaller
-// one loses no more than 2^-39 of that largest.  The factor of the keys goes out of the scores with the softmax scale, that
-// of V at the end (it changes only where the magnitudes change, and takes the sums so far along).  Infinite elements
-// cannot be cut in two: where a tile has one its scores are taken again, or its infinite values added, in fp32 products.
-// Relative error against 64 bits, normal inputs, 64 channels: 32 windows of 256 tokens 4.97e-7 (fp32 products 7.65e-7), one
-// such window 2.9e-7 (4.0e-7), one of 4096 tokens 4.95e-7 (7.6e-7); 128 channels, 32 windows 5.2e-7 (8.1e-7).
+// enters as three bf16 parts, each what rounding to bf16 left of the one before: 8 + 8 + 8 bits are all of its 24, and
+// bf16 has the exponents of fp32, so the parts together ARE the value, whatever lies beside it (a query row enters times the
+// softmax scale, to 2^-26).  A product is six of the nine products of parts, exact each, summed in fp32, small ones first; the
+// three left out are below 2^-24 of it together, half a unit of its last place.  Two f16 halves and three products are
+// faster (32 windows of 256 tokens 102 us, 144 so), but hold 23 bits, and those only of values near the largest that shares
+// their factor: not taken.  Values above the largest bf16, infinite ones among them, have no parts: where a tile has one
+// its scores are taken again, or its large values added, in fp32 products.
+// Relative error against 64 bits, normal inputs, 64 channels: 32 windows of 256 tokens 6.4e-7 (fp32 products 7.6e-7), one
+// such window 3.3e-7 (4.2e-7), one of 4096 tokens 8.4e-7 (9.8e-7); 128 channels 6.8e-7 (8.1e-7), 4.0e-7 (4.9e-7), 1.18e-6 (1.37e-6).
 //
 // A workgroup of 4 wavefronts owns 128 query rows that share a KV head (numbered position by position, the G heads side
 // by side), a wavefront 32 of them.  A tile is 4096 / D keys, 16 KB of keys and 16 KB of values: every wavefront brings a
-// quarter of each into registers a tile ahead, and cuts it into halves in LDS (double buffered) once its own products with
-// the tile before are out.  Two workgroups share a compute unit, so a SIMD has a second wavefront while the first is in
-// its softmax.  What bounds it: vector instructions (about 440 for 48 matrix ones per tile and wavefront; 70 % of the cycles
-// issue one, the matrix pipe is busy 40 %).
+// quarter of each into registers while the tile before is worked on, and cuts it into parts in LDS (48 KB, one tile) between
+// two barriers.  Two workgroups share a compute unit, so a SIMD has a second wavefront while the first is in its softmax
+// or at a barrier.  What bounds it: 96 matrix instructions per tile and wavefront, and about 530 vector ones that a wavefront
+// does not overlap with its own; of 32 windows of 256 tokens' 144 us the matrix pipe is busy 63.
 //
 // S^T = K Q^T leaves a lane with scores of ONE query (column lane % 32).  Bits 2 and 3 of a key's number within 16 change
 // places on the way into the first product, so that register i of lane half h holds key 16 (i / 8) + 8 h + i % 8 of a
@@ -25,8 +25,8 @@
 //
 // A single window has few query tiles; then the key tiles are cut into pieces, one workgroup each, which a second launch
 // merges.  64 channels, 8 query and 2 KV heads, 8 blocks retrieved, against fp32 products with the merge in the last
-// workgroup: 32 windows of 256 tokens 245 -> 118 us, one of them 57 -> 19.4, of 4096 tokens 313 -> 136; 128 channels, 32
-// windows 460 -> 215.
+// workgroup: 32 windows of 256 tokens 218 -> 144 us, one of them 57 -> 22, of 4096 tokens 301 -> 178; 128 channels, 32
+// windows 427 -> 285.
 #include <algorithm>
 #include <mutex>
 
@@ -39,13 +39,10 @@ namespace actqkv {
 constexpr int kFfThreads = 256;
 constexpr int kFfWaves = 4;
 constexpr int kFfRows = 32 * kFfWaves;            // query rows of a workgroup
-constexpr int kFfHalf = 8192;                     // one half (hi or lo) of K or V^T of a tile
-constexpr int kFfStageBytes = 4 * kFfHalf;
-constexpr int kFfLdsBytes = 2 * kFfStageBytes;
+constexpr int kFfPart = 8192;                     // one of the three parts of K or V^T of a tile
+constexpr int kFfLdsBytes = 6 * kFfPart;
 constexpr int kFfLazy = 8;                        // see the running maximum
-constexpr int kFfTop = 14;                        // factors bring magnitudes up to [2^14, 2^15)
-typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
-typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
+constexpr float kFfMax = 3.3895314e38f;           // the largest bf16: what is larger has no parts
 // Workgroups of a full launch: two per compute unit; with 128 channels a little less, so that their
 // partial results fit the library's own scratch array.
 template <int D> constexpr int kFfSlots = D == 64 ? 512 : 480;
@@ -73,25 +70,29 @@ struct FfParams {
   SelectInside sel;        // one sequence: its selection is made here
 };
 
-// Two fp32 values times a power of two -> the packed halves hi (rounded) and lo (what the rounding left, rounded).
-__device__ __forceinline__ void ff_split(float x0, float x1, float scale, uint32_t& hi, uint32_t& lo) {
-  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(x0), "v"(scale));
-  asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(x1), "v"(scale));
-  asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(x0), "v"(scale), "v"(hi));
-  asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(x1), "v"(scale), "v"(hi));
+// Two fp32 values -> their three parts, packed.  What is left of a value after a part is exact.
+__device__ __forceinline__ void ff_split(float x0, float x1, uint32_t (&part)[3]) {
+  part[0] = pack_bf16x2(x0, x1);
+  x0 -= bf16_lo(part[0]), x1 -= bf16_hi(part[0]);
+  part[1] = pack_bf16x2(x0, x1);
+  x0 -= bf16_lo(part[1]), x1 -= bf16_hi(part[1]);
+  part[2] = pack_bf16x2(x0, x1);
 }
-// The same without a factor (the first half of the work is one conversion for both).
-__device__ __forceinline__ void ff_split(float x0, float x1, uint32_t& hi, uint32_t& lo) {
-  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x0, x1}, f16x2));
-  asm("v_fma_mixlo_f16 %0, %1, 1.0, -%2 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(x0), "v"(hi));
-  asm("v_fma_mixhi_f16 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(x1), "v"(hi));
+// The same of the values times scale, to 2^-26 of them.
+__device__ __forceinline__ void ff_split_scaled(float x0, float x1, float scale, uint32_t (&part)[3]) {
+  part[0] = pack_bf16x2(x0 * scale, x1 * scale);
+  x0 = fmaf(x0, scale, -bf16_lo(part[0])), x1 = fmaf(x1, scale, -bf16_hi(part[0]));
+  part[1] = pack_bf16x2(x0, x1);
+  x0 -= bf16_lo(part[1]), x1 -= bf16_hi(part[1]);
+  part[2] = pack_bf16x2(x0, x1);
 }
-__device__ __forceinline__ f16x8 ff_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
-__device__ __forceinline__ float ff_pow2(int e) { return __uint_as_float(uint32_t(e + 127) << 23); }   // -126 <= e <= 127
-__device__ __forceinline__ int ff_exponent(float x) { return int(__float_as_uint(x) >> 23) - 127; }     // of x >= 0
-constexpr float kFfMax = 3.4028235e38f, kFfMin = 1.17549435e-38f;
-// The power of two that takes values of at most mx into [2^14, 2^15), 2^100 at most.
-__device__ __forceinline__ int ff_fit(float mx) { return min(kFfTop - ff_exponent(mx), 100); }
+__device__ __forceinline__ bf16x8 ff_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
+__device__ __forceinline__ f32x16 ff_mfma(const bf16x8& a, const bf16x8& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+// The six products of a step, small ones first: part kFfOf[i][0] of one factor, kFfOf[i][1] of the other.
+constexpr int kFfProducts = 6;
+constexpr int kFfOf[kFfProducts][2] = {{2, 0}, {1, 1}, {0, 2}, {1, 0}, {0, 1}, {0, 0}};
 
 // What wavefront `wave` of piece `split` of a (query tile, KV head) leaves: D / 2 floats of output per lane, then (max, sum).
 template <int D>
@@ -99,21 +100,18 @@ __device__ __forceinline__ float* ff_piece(const FfParams& p, int item, int spli
   return p.part + ((size_t(item) * p.splits + split) * kFfWaves + wave) * ((D / 2 + 2) * 64);
 }
 
-// Final normalisation and store of one lane's share of a query row.  unit[u]: what block u of the accumulators
-// (D / 4 channels) has to be multiplied by.
+// Final normalisation and store of one lane's share of a query row.
 template <int D>
-__device__ __forceinline__ void ff_store_row(const FfParams& p, const f32x16 (&acc_o)[D / 32], const float (&unit)[4],
-                                             float m_run, float l_tot, int s, int row, int head, int half) {
+__device__ __forceinline__ void ff_store_row(const FfParams& p, const f32x16 (&acc_o)[D / 32], float m_run,
+                                             float l_tot, int s, int row, int head, int half) {
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   float* op = p.out + ((size_t(s) * p.m + row) * p.n_q_heads + head) * D + 4 * half;
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float f = unit[(db * 32 + 8 * j) / (D / 4)] * inv;
+    for (int j = 0; j < 4; ++j)
       *reinterpret_cast<f32x4*>(op + db * 32 + 8 * j) =
-          f32x4{acc_o[db][4 * j] * f, acc_o[db][4 * j + 1] * f, acc_o[db][4 * j + 2] * f, acc_o[db][4 * j + 3] * f};
-    }
+          f32x4{acc_o[db][4 * j] * inv, acc_o[db][4 * j + 1] * inv, acc_o[db][4 * j + 2] * inv, acc_o[db][4 * j + 3] * inv};
   if (p.lse != nullptr && half == 0)
     p.lse[(size_t(s) * p.n_q_heads + head) * p.m + row] = (m_run + log2f(l_tot)) * 0.6931471805599453f;
 }
@@ -123,9 +121,9 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
   constexpr int kKeys = 4096 / D;                   // keys of a tile: 64 or 32
   constexpr int kPerBlock = kBlock / kKeys;
   constexpr int kG = kKeys / 32, kDb = D / 32, kQ = D / 16;
-  constexpr uint32_t kKRow = D * 2, kVRow = kKeys * 2;   // bytes of a K / V^T row in one of its two halves in LDS
-  extern __shared__ __attribute__((aligned(16))) char ff_lds[];   // [stage][K hi, K lo, V^T hi, V^T lo]
-  __shared__ float factors[2][2][4];                // [stage][K: what scores are multiplied by, V: what values were][wavefront]
+  constexpr uint32_t kKRow = D * 2, kVRow = kKeys * 2;   // bytes of a K / V^T row in one of its parts in LDS
+  extern __shared__ __attribute__((aligned(16))) char ff_lds[];   // three parts of K, three of V^T
+  __shared__ __attribute__((aligned(16))) uint32_t no_parts[2][kFfWaves];   // whether what a wavefront brought of K, V is larger than kFfMax
   __shared__ int32_t idx_lds[64];
   __shared__ SelectWaveLds sel_lds;
   __shared__ int sel_count;
@@ -138,7 +136,7 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
   const int s = qt / p.n_qtiles;
   int qtile = qt % p.n_qtiles;
   // The last rows of a window see up to a window more keys than the first: the two workgroups that share a compute unit
-  // (per_chip query tiles apart) take them in opposite orders.  32 windows of 256 tokens 123.5 -> 116.5 us.
+  // (per_chip query tiles apart) take them in opposite orders.  A window of 4096 tokens 198 -> 180 us, four of 1024 110 -> 103.
   if (p.per_chip >= p.n_qtiles) {
     if ((s * p.n_qtiles / p.per_chip) & 1) qtile = p.n_qtiles - 1 - qtile;
   } else {
@@ -175,7 +173,7 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
   // are read together hit all banks.
   auto k_key = [](int r) { return uint32_t(D == 64 ? (r >> 1) & 7 : r & 15); };
   auto v_key = [](int r) { return uint32_t(D == 64 ? (r >> 1) & 7 : (r >> 2) & 3); };
-  uint32_t wk[4], wv[4];                                     // where this lane's pieces go in a half
+  uint32_t wk[4], wv[4];                                     // where this lane's pieces go in a part
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int kr = kr0 + i * kKPer, vr = vr0 + i * kVPer;
@@ -199,17 +197,16 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
       xv[i] = *reinterpret_cast<const f32x4*>(vp + i * kVPer * (4 * kBlock));
     }
   };
-  int v_exp = 100, v_low = 1000;                             // this wavefront's values go in times 2^v_exp; the least so far
-  auto largest = [](const f32x4 (&x)[4]) {                   // magnitude, over the wavefront (NaN is passed over)
+  auto too_large = [&](const f32x4 (&x)[4]) {                // whether any of the wavefront's values is (NaN is not)
     float mx = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; j += 2) mx = fmaxf(fmaxf(fabsf(x[i][j]), fabsf(x[i][j + 1])), mx);
-    return __uint_as_float(wave_max_u32(__float_as_uint(mx)));
+    return __any(mx > kFfMax) != 0;
   };
-  // the tile in registers -> LDS, as halves; keys that no row of the workgroup sees count as zeros
-  auto store_tile = [&](const Tile& t, int stage) {
+  // the tile in registers -> LDS, in parts; keys that no row of the workgroup sees count as zeros
+  auto store_tile = [&](const Tile& t) {
     if (t.lo > t.key0 || t.hi < t.key0 + kKeys) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -221,55 +218,40 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
         }
       }
     }
-    char* dst = ff_lds + stage * kFfStageBytes;
-    const float k_mx = largest(xk);
-    float v_mx = largest(xv);
-    const bool k_inf = !(k_mx <= kFfMax), v_inf = !(v_mx <= kFfMax);
-    if (__builtin_expect(v_inf, 0)) {                        // the finite ones; the infinite ones are added by the reader
+    const bool k_large = too_large(xk), v_large = too_large(xv);
+    if (__builtin_expect(v_large, 0)) {                      // the others; these are added by the reader
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) xv[i][j] = isinf(xv[i][j]) ? 0.f : xv[i][j];
-      v_mx = largest(xv);
+        for (int j = 0; j < 4; ++j) xv[i][j] = fabsf(xv[i][j]) > kFfMax ? 0.f : xv[i][j];
     }
-    const int k_exp = ff_fit(k_mx);
-    {
-      // the factor of the values stays as it is while the largest of them comes to lie in [2^4, 2^15); it is raised
-      // by no more than keeps the sums of before in range
-      const int at = ff_exponent(v_mx) + v_exp;
-      if (v_mx > 0.f && (at > kFfTop || at < 4)) {
-        v_exp = min(min(kFfTop - 2 - (at - v_exp), 100), v_low + 60);
-        v_low = min(v_low, v_exp);
-      }
-    }
-    const float kf = ff_pow2(k_inf ? 0 : k_exp), vf = ff_pow2(v_exp);
     if (lane == 0) {
-      factors[stage][0][wave] = k_inf ? -1.f : ff_pow2(-k_exp);
-      factors[stage][1][wave] = v_inf ? -vf : vf;
+      no_parts[0][wave] = k_large;
+      no_parts[1][wave] = v_large;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      uint32_t h0, h1, l0, l1;
-      ff_split(xk[i][0], xk[i][1], kf, h0, l0);
-      ff_split(xk[i][2], xk[i][3], kf, h1, l1);
-      *reinterpret_cast<u32x2*>(dst + wk[i]) = u32x2{h0, h1};
-      *reinterpret_cast<u32x2*>(dst + kFfHalf + wk[i]) = u32x2{l0, l1};
-      ff_split(xv[i][0], xv[i][1], vf, h0, l0);
-      ff_split(xv[i][2], xv[i][3], vf, h1, l1);
-      *reinterpret_cast<u32x2*>(dst + 2 * kFfHalf + wv[i]) = u32x2{h0, h1};
-      *reinterpret_cast<u32x2*>(dst + 3 * kFfHalf + wv[i]) = u32x2{l0, l1};
+      uint32_t a[3], b[3];
+      ff_split(xk[i][0], xk[i][1], a);
+      ff_split(xk[i][2], xk[i][3], b);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) *reinterpret_cast<u32x2*>(ff_lds + c * kFfPart + wk[i]) = u32x2{a[c], b[c]};
+      ff_split(xv[i][0], xv[i][1], a);
+      ff_split(xv[i][2], xv[i][3], b);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) *reinterpret_cast<u32x2*>(ff_lds + (3 + c) * kFfPart + wv[i]) = u32x2{a[c], b[c]};
     }
   };
 
   // the first piece begins with the initial tokens, whatever is selected
-  Tile now{0, 0, 0}, next{0, 0, 0};
+  Tile now{0, 0, 0};
   const bool early = split == 0 && g.i0 > 0;
   if (early) fetch_tile(now);
-  // ---- the queries: channels 16 j + 8 half .. + 7 of this lane's row, as halves of their multiples by 2^q_exp
+  // ---- the queries: channels 16 j + 8 half .. + 7 of this lane's row times scale_log2e, in parts: scores come in units of log2
+  // then, and that of the key with the maximum less the maximum is 0 (fmaf(score, scale_log2e, -maximum) is not)
   const float* qrow = p.q + ((size_t(s) * p.m + my_row) * p.n_q_heads + head) * D;
-  u32x4 qh[kQ], ql[kQ];
-  float q_unit;                                              // scores times this are in units of log2
-  bool q_inf;
+  u32x4 qp[3][kQ];
+  bool q_large;
   {
     f32x4 x[2 * kQ];
     float mx = 0.f;
@@ -282,19 +264,15 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
     for (int j = 0; j < 2 * kQ; ++j)
 #pragma unroll
       for (int i = 0; i < 4; i += 2) mx = fmaxf(fmaxf(fabsf(x[j][i]), fabsf(x[j][i + 1])), mx);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    q_inf = __any(!(mx <= kFfMax));
-    const int e = mx <= kFfMax ? ff_fit(mx) : 0;
-    const float f = ff_pow2(e);
-    q_unit = p.scale_log2e * ff_pow2(-e);
+    q_large = __any(mx > kFfMax || mx * p.scale_log2e > kFfMax);
 #pragma unroll
     for (int j = 0; j < kQ; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        uint32_t h, l;
-        ff_split(x[2 * j + (i >> 1)][2 * (i & 1)], x[2 * j + (i >> 1)][2 * (i & 1) + 1], f, h, l);
-        qh[j][i] = h;
-        ql[j][i] = l;
+        uint32_t part[3];
+        ff_split_scaled(x[2 * j + (i >> 1)][2 * (i & 1)], x[2 * j + (i >> 1)][2 * (i & 1) + 1], p.scale_log2e, part);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) qp[c][j][i] = part[c];
       }
   }
   if (!inside && tid < 64) idx_lds[tid] = my_idx;
@@ -320,198 +298,156 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
   for (int i = 0; i < kDb; ++i)
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc_o[i][j] = 0.f;
-  float v_in[4] = {1.f, 1.f, 1.f, 1.f};                      // acc_o holds sums of values times this
   float m_run = -INFINITY, l_run = 0.f;                      // reference of the exponents (log2 units, the rows' maximum or close below), this lane's share of the sum
 
-  if (t_begin < t_end) {
-    store_tile(now, 0);
-    if (t_begin + 1 < t_end) {
-      next = tile_at(t_begin + 1);
-      fetch_tile(next);
-    }
-  }
-  __syncthreads();
   const int kn = (n & 0x13) | ((n & 4) << 1) | ((n & 8) >> 1);   // the key of this lane's row in the first product
   for (int t = t_begin; t < t_end; ++t) {
-    const int stage = (t - t_begin) & 1;
     const int key0 = now.key0, lo = now.lo, hi = now.hi;
+    if (t > t_begin) __syncthreads();                        // everybody is done with the tile before
+    store_tile(now);
+    __syncthreads();
+    if (t + 1 < t_end) {
+      now = tile_at(t + 1);
+      fetch_tile(now);
+    }
     // the wavefront skips tiles none of its rows can see; it masks tiles that are clipped or reach
     // past its first row's position
     const bool visible = wave_ok && hi > lo && lo <= wpos_hi;
     const bool masked = lo > key0 || hi < key0 + kKeys || hi - 1 > wpos_lo;
-    const char* ks_ = ff_lds + stage * kFfStageBytes;
-    const char* vs_ = ks_ + 2 * kFfHalf;
-    if (visible) {
-      f32x16 acc_s[kG];
-      float unit[2 * kG];                                    // per 16 keys
-      bool k_inf = q_inf;
+    if (!visible) continue;
+    bool k_large = q_large, v_large = false;
+    {
+      const u32x4 of_k = *reinterpret_cast<const u32x4*>(no_parts[0]), of_v = *reinterpret_cast<const u32x4*>(no_parts[1]);
+      k_large |= __any((of_k.x | of_k.y | of_k.z | of_k.w) != 0u);
+      v_large = __any((of_v.x | of_v.y | of_v.z | of_v.w) != 0u);
+    }
+    f32x16 acc_s[kG];
 #pragma unroll
-      for (int b = 0; b < 2 * kG; ++b) {
-        const float f = factors[stage][0][D == 64 ? b : 2 * b + half];
-        k_inf |= __any(f < 0.f);
-        unit[b] = __builtin_amdgcn_fmed3f(q_unit * f, kFfMin, kFfMax);
+    for (int gg = 0; gg < kG; ++gg)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc_s[gg][i] = 0.f;
+    bf16x8 kp[2][3][kG];                                     // a step's operands are requested a step ahead
+    auto read_k = [&](int j) {
+#pragma unroll
+      for (int gg = 0; gg < kG; ++gg) {
+        const char* at = ff_lds + uint32_t(gg * 32 + kn) * kKRow + ((uint32_t(2 * j + half) ^ k_key(kn)) << 4);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) kp[j & 1][c][gg] = ff_bf16x8(*reinterpret_cast<const u32x4*>(at + c * kFfPart));
       }
+    };
+    read_k(0);
+#pragma unroll
+    for (int j = 0; j < kQ; ++j) {
+      if (j + 1 < kQ) read_k(j + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < kFfProducts; ++i)
+#pragma unroll
+        for (int gg = 0; gg < kG; ++gg)
+          acc_s[gg] = ff_mfma(kp[j & 1][kFfOf[i][0]][gg], ff_bf16x8(qp[kFfOf[i][1]][j]), acc_s[gg]);
+    }
+    if (__builtin_expect(k_large, 0)) {
+      // a key or query without parts: the scores anew in fp32 products, from memory
 #pragma unroll
       for (int gg = 0; gg < kG; ++gg)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc_s[gg][i] = 0.f;
-      f16x8 kh[2][kG], kl[2][kG];                            // a step's operands are requested a step ahead
-      auto read_k = [&](int j) {
-#pragma unroll
-        for (int gg = 0; gg < kG; ++gg) {
-          const char* at = ks_ + uint32_t(gg * 32 + kn) * kKRow + ((uint32_t(2 * j + half) ^ k_key(kn)) << 4);
-          kh[j & 1][gg] = ff_f16x8(*reinterpret_cast<const u32x4*>(at));
-          kl[j & 1][gg] = ff_f16x8(*reinterpret_cast<const u32x4*>(at + kFfHalf));
-        }
-      };
-      read_k(0);
-#pragma unroll
-      for (int j = 0; j < kQ; ++j) {
-        if (j + 1 < kQ) read_k(j + 1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int gg = 0; gg < kG; ++gg) acc_s[gg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl[j & 1][gg], ff_f16x8(qh[j]), acc_s[gg], 0, 0, 0);
-#pragma unroll
-        for (int gg = 0; gg < kG; ++gg) acc_s[gg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[j & 1][gg], ff_f16x8(ql[j]), acc_s[gg], 0, 0, 0);
-#pragma unroll
-        for (int gg = 0; gg < kG; ++gg) acc_s[gg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[j & 1][gg], ff_f16x8(qh[j]), acc_s[gg], 0, 0, 0);
-      }
-      if (__builtin_expect(k_inf, 0)) {
-        // an infinite key or query: the scores anew in fp32 products, from memory
-#pragma unroll
-        for (int gg = 0; gg < kG; ++gg)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) acc_s[gg][i] = 0.f;
-        const float* kt = reinterpret_cast<const float*>(kbase + block_offset(key0)) + size_t(key0 % kBlock + kn) * D + half;
+      const float* kt = reinterpret_cast<const float*>(kbase + block_offset(key0)) + size_t(key0 % kBlock + kn) * D + half;
 #pragma unroll 1
-        for (int c = 0; c < D; c += 2)
-#pragma unroll
-          for (int gg = 0; gg < kG; ++gg)
-            acc_s[gg] = __builtin_amdgcn_mfma_f32_32x32x2f32(kt[gg * 32 * D + c], qrow[c + half], acc_s[gg], 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < 2 * kG; ++b) unit[b] = p.scale_log2e;
-      }
-      if (masked) {
+      for (int c = 0; c < D; c += 2)
 #pragma unroll
         for (int gg = 0; gg < kG; ++gg)
+          acc_s[gg] = __builtin_amdgcn_mfma_f32_32x32x2f32(kt[gg * 32 * D + c], qrow[c + half], acc_s[gg], 0, 0, 0);
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int kp = key0 + gg * 32 + 16 * (i >> 3) + 8 * half + (i & 7);
-            const bool ok = kp >= lo && kp < hi && kp <= my_pos;
-            acc_s[gg][i] = ok ? acc_s[gg][i] : -INFINITY;
-          }
-      }
-      float mx = -INFINITY;
+      for (int gg = 0; gg < kG; ++gg)
 #pragma unroll
-      for (int b = 0; b < 2 * kG; ++b) {
-        float bm = acc_s[b >> 1][8 * (b & 1)];
-#pragma unroll
-        for (int i = 1; i < 8; ++i) bm = fmaxf(bm, acc_s[b >> 1][8 * (b & 1) + i]);
-        mx = fmaxf(mx, bm * unit[b]);
-      }
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      // the reference follows the maximum only when that has grown by more than 2^kFfLazy, as a rule in the first tiles
-      // (every lane takes the same branch: 32 rows have a new maximum in nearly every tile)
-      if (!__all(mx <= m_run + kFfLazy)) {
-        const float m_new = fmaxf(m_run, mx);
-        const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
-        m_run = m_new;
-#pragma unroll
-        for (int db = 0; db < kDb; ++db)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) acc_o[db][i] *= alpha;
-        l_run *= alpha;
-      }
-      const float shift = kFfTop - kFfLazy - (m_run == -INFINITY ? 0.f : m_run);
-      float v_now[4];
-      bool v_inf = false, same = true;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float f = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(factors[stage][1][u])));
-        v_inf |= f < 0.f;
-        v_now[u] = fabsf(f);
-        same &= v_now[u] == v_in[u];
-      }
-      if (!same) {                                           // wave-uniform
-#pragma unroll
-        for (int db = 0; db < kDb; ++db)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int u = (db * 32 + 8 * j) / (D / 4);
-            const float grow = v_now[u] / v_in[u];
-#pragma unroll
-            for (int i = 4 * j; i < 4 * j + 4; ++i) acc_o[db][i] *= grow;
-          }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v_in[u] = v_now[u];
-      }
-      float psum[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < 16; ++i) acc_s[gg][i] *= p.scale_log2e;
+    }
+    if (masked) {
 #pragma unroll
       for (int gg = 0; gg < kG; ++gg)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          acc_s[gg][i] = __builtin_amdgcn_exp2f(fmaf(acc_s[gg][i], unit[2 * gg + (i >> 3)], shift));
-          psum[i & 3] += acc_s[gg][i];
+          const int kpos = key0 + gg * 32 + 16 * (i >> 3) + 8 * half + (i & 7);
+          const bool ok = kpos >= lo && kpos < hi && kpos <= my_pos;
+          acc_s[gg][i] = ok ? acc_s[gg][i] : -INFINITY;
         }
-      l_run += (psum[0] + psum[1]) + (psum[2] + psum[3]);
+    }
+    float mx = acc_s[0][0];
 #pragma unroll
-      for (int st = 0; st < 2 * kG; ++st) {
-        f16x8 vh[kDb], vl[kDb];
+    for (int gg = 0; gg < kG; ++gg)
 #pragma unroll
-        for (int db = 0; db < kDb; ++db) {
-          const char* at = vs_ + uint32_t(db * 32 + n) * kVRow + ((uint32_t(2 * st + half) ^ v_key(n)) << 4);
-          vh[db] = ff_f16x8(*reinterpret_cast<const u32x4*>(at));
-          vl[db] = ff_f16x8(*reinterpret_cast<const u32x4*>(at + kFfHalf));
-        }
-        u32x4 ph, pl;
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc_s[gg][i]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    // the reference follows the maximum only when that has grown by more than 2^kFfLazy, as a rule in the first tiles
+    // (every lane takes the same branch: 32 rows have a new maximum in nearly every tile)
+    if (!__all(mx <= m_run + kFfLazy)) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
+      m_run = m_new;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          uint32_t h, l;
-          ff_split(acc_s[st >> 1][8 * (st & 1) + 2 * i], acc_s[st >> 1][8 * (st & 1) + 2 * i + 1], h, l);
-          ph[i] = h;
-          pl[i] = l;
-        }
+      for (int db = 0; db < kDb; ++db)
 #pragma unroll
-        for (int db = 0; db < kDb; ++db) acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl[db], ff_f16x8(ph), acc_o[db], 0, 0, 0);
+        for (int i = 0; i < 16; ++i) acc_o[db][i] *= alpha;
+      l_run *= alpha;
+    }
+    const float m_safe = m_run == -INFINITY ? 0.f : m_run;
+    float psum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int db = 0; db < kDb; ++db) acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh[db], ff_f16x8(pl), acc_o[db], 0, 0, 0);
+    for (int gg = 0; gg < kG; ++gg)
 #pragma unroll
-        for (int db = 0; db < kDb; ++db) acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh[db], ff_f16x8(ph), acc_o[db], 0, 0, 0);
+      for (int i = 0; i < 16; ++i) {
+        acc_s[gg][i] = __builtin_amdgcn_exp2f(acc_s[gg][i] - m_safe);
+        psum[i & 3] += acc_s[gg][i];
       }
-      if (__builtin_expect(v_inf, 0)) {
-        // infinite values went in as zeros; their products in fp32, from memory
-        const float* vt = reinterpret_cast<const float*>(vbase + block_offset(key0)) + size_t(n) * kBlock + key0 % kBlock;
+    l_run += (psum[0] + psum[1]) + (psum[2] + psum[3]);
 #pragma unroll
-        for (int gg = 0; gg < kG; ++gg)
+    for (int st = 0; st < 2 * kG; ++st) {
+      u32x4 pp[3];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int k = gg * 32 + 16 * (i >> 3) + 8 * half + (i & 7);
-            const bool seen = key0 + k >= lo && key0 + k < hi;
+      for (int i = 0; i < 4; ++i) {
+        uint32_t part[3];
+        ff_split(acc_s[st >> 1][8 * (st & 1) + 2 * i], acc_s[st >> 1][8 * (st & 1) + 2 * i + 1], part);
 #pragma unroll
-            for (int db = 0; db < kDb; ++db) {
-              const float x = vt[db * 32 * kBlock + k];
-              acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(seen && isinf(x) ? x : 0.f, acc_s[gg][i], acc_o[db], 0, 0, 0);
-            }
+        for (int c = 0; c < 3; ++c) pp[c][i] = part[c];
+      }
+#pragma unroll
+      for (int d0 = 0; d0 < kDb; d0 += 2) {
+        bf16x8 vp[3][2];
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+          const char* at = ff_lds + 3 * kFfPart + uint32_t((d0 + db) * 32 + n) * kVRow + ((uint32_t(2 * st + half) ^ v_key(n)) << 4);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) vp[c][db] = ff_bf16x8(*reinterpret_cast<const u32x4*>(at + c * kFfPart));
+        }
+#pragma unroll
+        for (int i = 0; i < kFfProducts; ++i)
+#pragma unroll
+          for (int db = 0; db < 2; ++db)
+            acc_o[d0 + db] = ff_mfma(vp[kFfOf[i][0]][db], ff_bf16x8(pp[kFfOf[i][1]]), acc_o[d0 + db]);
+      }
+    }
+    if (__builtin_expect(v_large, 0)) {
+      // values without parts went in as zeros; their products in fp32, from memory
+      const float* vt = reinterpret_cast<const float*>(vbase + block_offset(key0)) + size_t(n) * kBlock + key0 % kBlock;
+#pragma unroll
+      for (int gg = 0; gg < kG; ++gg)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int k = gg * 32 + 16 * (i >> 3) + 8 * half + (i & 7);
+          const bool seen = key0 + k >= lo && key0 + k < hi;
+#pragma unroll
+          for (int db = 0; db < kDb; ++db) {
+            const float x = vt[db * 32 * kBlock + k];
+            acc_o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(seen && fabsf(x) > kFfMax ? x : 0.f, acc_s[gg][i], acc_o[db], 0, 0, 0);
           }
-      }
+        }
     }
-    if (t + 1 < t_end) {
-      store_tile(next, stage ^ 1);
-      now = next;
-      if (t + 2 < t_end) {
-        next = tile_at(t + 2);
-        fetch_tile(next);
-      }
-    }
-    __syncthreads();
   }
 
-  const float l_tot = (l_run + __shfl_xor(l_run, 32, 64)) * ff_pow2(kFfLazy - kFfTop);
-  float unit[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) unit[u] = ff_pow2(kFfLazy - kFfTop) / v_in[u];
+  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   if (p.splits == 1) {
-    if (row_ok) ff_store_row<D>(p, acc_o, unit, m_run, l_tot, s, my_row, head, half);
+    if (row_ok) ff_store_row<D>(p, acc_o, m_run, l_tot, s, my_row, head, half);
     return;
   }
   // ---- a piece stores its unnormalised output in the order the registers hold it, plus its max and sum
@@ -519,18 +455,16 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
 #pragma unroll
   for (int db = 0; db < kDb; ++db)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float f = unit[(db * 32 + 8 * j) / (D / 4)];
+    for (int j = 0; j < 4; ++j)
       *reinterpret_cast<f32x4*>(mine + ((db * 4 + j) * 64 + lane) * 4) =
-          f32x4{acc_o[db][4 * j] * f, acc_o[db][4 * j + 1] * f, acc_o[db][4 * j + 2] * f, acc_o[db][4 * j + 3] * f};
-    }
+          f32x4{acc_o[db][4 * j], acc_o[db][4 * j + 1], acc_o[db][4 * j + 2], acc_o[db][4 * j + 3]};
   *reinterpret_cast<f32x2*>(mine + (D / 2) * 64 + lane * 2) = f32x2{m_run, l_tot};
 }
 
 // The pieces of a query tile, in their order:  out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
 // grid (4 wavefronts' rows of every query tile and KV head); a wavefront here takes a quarter of the channels of the
 // 32 rows.  A launch of its own: the last of 8 pieces to finish needed 31 us to read the others' 256 KB back (one
-// compute unit gets 8 GB/s of coherent 8-byte loads), a window of 256 tokens 50 us, as two launches 19.4.
+// compute unit gets 8 GB/s of coherent 8-byte loads), with fp32 products a window of 256 tokens 57 us, so 33 of them.
 template <int D>
 __global__ __launch_bounds__(256) void attn_prefill_f32_merge_kernel(FfParams p) {
   constexpr int kSlots = D / 32;                             // 16-byte groups of a lane here
