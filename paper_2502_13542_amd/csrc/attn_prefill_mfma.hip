@@ -654,7 +654,7 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
   if (row_ok) store_rows<D, kMine>(p, acc_f, db0, m_all, l_all, s, my_row, head, half);
 }
 
-// The pieces of a query tile, in their order:  out = sum_s w_s o_s / sum_s w_s with w_s = l_s 2^(m_s - M), M = max_s m_s,
+// The pieces of a query tile of one window (prefill_merge_after), in their order:  out = sum_s w_s o_s / sum_s w_s with w_s = l_s 2^(m_s - M), M = max_s m_s,
 // o_s normalised (not normalised: sum_s v_s O_s / sum_s v_s l_s with v_s = 2^(m_s - M)).
 // A wavefront merges kTake 16-byte slots of the 32 rows of a wavefront of the attention, all its loads in flight at once; blocks
 // deal the KV heads like the attention's, so that a head's pieces are read on the XCD that wrote them.  Bound by its launch and one
@@ -667,13 +667,11 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_prefill_merge_kernel(Pf
   const int lane = threadIdx.x & 63, n = lane & 31, half = lane >> 5;
   const int hk = blockIdx.x % p.n_kv_heads;
   const int unit = __builtin_amdgcn_readfirstlane((blockIdx.x / p.n_kv_heads) * kMergeWaves + (threadIdx.x >> 6));
-  const int item = unit / Piece::kUnits, wave = unit % Piece::kUnits / kParts, part = unit % kParts;
-  const int s = item / p.n_qtiles, qtile = item - s * p.n_qtiles;
+  const int qtile = unit / Piece::kUnits, wave = unit % Piece::kUnits / kParts, part = unit % kParts;
   const int n_lo = p.n_qtiles - p.rem;
   const int splits = qtile < n_lo ? p.s_lo : p.s_lo + 1;
-  if (splits == 1) return;                                   // (the attention has stored its rows)
   const int slot0 = qtile < n_lo ? qtile * p.s_lo : n_lo * p.s_lo + (qtile - n_lo) * splits;
-  const u32x4* piece = Piece::at(p, s, hk, slot0, wave);
+  const u32x4* piece = Piece::at(p, 0, hk, slot0, wave);
   f32x2 ml[kMaxPfSplits];
   u32x4 raw[kMaxPfSplits][kTake];
 #pragma unroll
@@ -722,7 +720,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_prefill_merge_kernel(Pf
   const int row = frow / group, head = hk * group + (frow - row * group);
   const int db0 = (wave / kRowGroups) * Piece::kMine;
   const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
-  uint16_t* op = p.out + ((size_t(s) * p.m + row) * p.n_q_heads + head) * D + db0 * 32 + 4 * half;
+  uint16_t* op = p.out + (size_t(row) * p.n_q_heads + head) * D + db0 * 32 + 4 * half;
 #pragma unroll
   for (int k = 0; k < kTake; ++k)
 #pragma unroll
@@ -734,7 +732,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_prefill_merge_kernel(Pf
       *reinterpret_cast<u32x2*>(op + 8 * at) = v;
     }
   if (p.lse != nullptr && half == 0 && db0 == 0 && part == 0)
-    p.lse[(size_t(s) * p.n_q_heads + head) * p.m + row] = (m_all + log2f(l_all)) * 0.6931471805599453f;
+    p.lse[size_t(head) * p.m + row] = (m_all + log2f(l_all)) * 0.6931471805599453f;
 }
 
 // blockIdx.x = w * Hk + hk: consecutive ids differ in hk, and ids are dealt round-robin to the
@@ -970,7 +968,7 @@ static int launch_pf(PfParams p, int late_per_head, hipStream_t stream, hipStrea
     hipLaunchKernelGGL((attn_prefill_mfma_kernel<D, KS, kTwoTermP>), grid, dim3(kPfThreads), kPfLdsBytes<D>, stream, p);
   if (int rc = hip_status("attention (prefill, matrix cores)")) return rc;
   if constexpr (kPfPieces<D, KS, kTwoTermP>) if (p.merge_after) {
-    const int units = p.items_per_head / p.slots * p.n_qtiles * PfPiece<D, KS, kTwoTermP>::kUnits;     // per KV head
+    const int units = p.n_qtiles * PfPiece<D, KS, kTwoTermP>::kUnits;     // per KV head
     hipLaunchKernelGGL((attn_prefill_merge_kernel<D, KS, kTwoTermP>), dim3(units / kMergeWaves * p.n_kv_heads),
                        dim3(64 * kMergeWaves), 0, stream, p);
     if (int rc = hip_status("attention (prefill, matrix cores, merge)")) return rc;

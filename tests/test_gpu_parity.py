@@ -709,21 +709,25 @@ def test_log_sum_exp_output(dtype, d, m, nw):
             assert np.abs(lse[i, :, r] - ref).max() < tol * max(1.0, np.abs(ref).max()), f"window {i} row {r}"
 
 
-@pytest.mark.parametrize("hq,hk,d,m,nw,n_sel", [
-    (8, 2, 128, 70, 1, 4),        # 64 query rows in 8 pieces, the last tile ragged
-    (28, 4, 128, 64, 1, 0),       # the same with 7 heads, fewer key tiles than pieces
-    (32, 8, 128, 33, 2, 3),       # two sequences, a query tile with two live rows
-    (28, 4, 128, 200, 1, 4),      # 128 rows in 5 pieces
-    (8, 2, 128, 1536, 1, 4),      # 256 rows in 5 and 6 pieces, partial results normalised in bf16
-    (8, 2, 64, 100, 1, 4),        # 64 channels: 64 rows in 8
-    (8, 2, 64, 768, 1, 2),        # 128 rows in 5
-    (8, 2, 64, 1536, 1, 4)])      # 256 rows in 5 and 6, fp32 partial results
-def test_pieces_merged_by_a_launch(hq, hk, d, m, nw, n_sel):
-    """Query tiles whose key tiles are cut into four pieces and more: output and lse of rows at the edges of query tiles against
-    the oracle, twice on one workspace with the same bits."""
+@pytest.mark.parametrize("hq,hk,d,m,nw,n_sel,cut", [                       # cut: see actqkv_prefill_cut
+    (8, 2, 128, 70, 1, 4, (64, 5, 40, 1)),        # 64 query rows in 8 pieces, the last tile ragged
+    (28, 4, 128, 64, 1, 0, (64, 7, 56, 1)),       # the same with 7 heads, fewer key tiles than pieces
+    (32, 8, 128, 33, 1, 3, (64, 3, 24, 1)),       # a query tile with two live rows
+    (28, 4, 128, 200, 1, 4, (128, 11, 55, 1)),    # 128 rows in 5 pieces
+    (8, 2, 128, 1536, 1, 4, (256, 24, 128, 1)),   # 256 rows in 5 and 6 pieces, partial results normalised in bf16
+    (8, 2, 64, 100, 1, 4, (64, 7, 56, 1)),        # 64 channels: 64 rows in 8
+    (8, 2, 64, 768, 1, 2, (128, 24, 120, 1)),     # 128 rows in 5
+    (8, 2, 64, 1536, 1, 4, (256, 24, 128, 1)),    # 256 rows in 5 and 6, fp32 partial results
+    (32, 8, 128, 33, 2, 3, (64, 3, 15, 0)),       # the last workgroup merges: two sequences in 5 pieces
+    (28, 4, 128, 300, 1, 4, (128, 17, 51, 0)),    # 128 rows in 3
+    (8, 2, 64, 1700, 1, 4, (256, 27, 128, 0))])   # 256 rows in 4 and 5, fp32 partial results
+def test_pieces_merged(hq, hk, d, m, nw, n_sel, cut):
+    """Query tiles whose key tiles are cut into pieces, merged by a launch or by the last workgroup: output and lse of rows at
+    the edges of query tiles against the oracle, twice on one workspace with the same bits."""
     sh = LayerShape(hq, hk, d, 128, 4, 128, 256, "bf16")
     cs = B.c_shape(sh)
     k_cap, base = 32, 9 * 128 + 40
+    assert B.prefill_cut(cs, nw, m, k_cap) == cut
     nb = (base + m + 127) // 128
     g = torch.Generator().manual_seed(m + d)
     q = torch.randn(nw, m, hq, d, generator=g).to(torch.bfloat16)
