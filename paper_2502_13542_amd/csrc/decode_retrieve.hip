@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kDrThreads) void decode_score_kernel(DrParams<T> p)
       for (int e = threadIdx.x; e < key_len; e += kDrThreads) p.probe_kv[size_t(s) * key_len + e] = pkv_lds[e];
     if (p.probe_norm != nullptr && threadIdx.x == 0) p.probe_norm[s] = pn;
     if constexpr (kCopy)
-      if (threadIdx.x == 0) p.cut_copy[s] = p.budget[s], p.cut_copy[gridDim.y + s] = p.rest[s];
+      if (threadIdx.x < 2) p.cut_copy[threadIdx.x * gridDim.y + s] = (threadIdx.x == 0 ? p.budget : p.rest)[s];
   }
   if (!live) return;
   const float total = scorer.finish(pkv_lds, pn, p.inv_sqrt_g);
