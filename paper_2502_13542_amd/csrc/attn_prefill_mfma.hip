@@ -654,8 +654,9 @@ __device__ __forceinline__ void attn_prefill_item(const PfParams& p, uint16_t* l
   if (row_ok) store_rows<D, kMine>(p, acc_f, db0, m_all, l_all, s, my_row, head, half);
 }
 
-// The pieces of a query tile of one window (prefill_merge_after), in their order:  out = sum_s w_s o_s / sum_s w_s with w_s = l_s 2^(m_s - M), M = max_s m_s,
-// o_s normalised (not normalised: sum_s v_s O_s / sum_s v_s l_s with v_s = 2^(m_s - M)).
+// The pieces of a query tile of one window (prefill_merge_after), in their order:
+//   out = sum_s w_s o_s / sum_s w_s  with w_s = l_s 2^(m_s - M), M = max_s m_s, o_s normalised
+//   (not normalised: sum_s v_s O_s / sum_s v_s l_s  with v_s = 2^(m_s - M)).
 // A wavefront merges kTake 16-byte slots of the 32 rows of a wavefront of the attention, all its loads in flight at once; blocks
 // deal the KV heads like the attention's, so that a head's pieces are read on the XCD that wrote them.  Bound by its launch and one
 // round trip: 4 to 5 us for 256 pieces (prefill_merge_after has both sides).
@@ -833,16 +834,18 @@ static int prefill_mfma_qtiles(const actqkv_shape& sh, int m, int ks) {
   return (m * (sh.n_q_heads / sh.n_kv_heads) + rows - 1) / rows;
 }
 
-// Whether a second launch merges the pieces of a query tile; otherwise the workgroup that finishes last does.  That one
-// reads the others' results back at 8 bytes a lane past the L2s, 32 KB a piece (64 KB of 128 rows) and 8 KB per us, which nothing
-// overlaps in a single window; the launch costs 4 us whatever their number.  Single windows, last workgroup | launch:
-// 32 query and 8 KV heads of 128 channels, 384 tokens in 5 pieces of 256 rows 30.2 | 24.8 us, 1024 in 2 49.2 | 50.0; as 128 rows, 256 in 4
-// 23.2 | 21.3, 512 in 2 29.1 | 29.6; as 64 rows, 64 in 8 17.7 | 13.9, 128 in 4 17.4 | 16.0, 200 in 2 19.7 | 20.1; 28 and 4 heads, 768 in 3
-// pieces of 256 rows 36.9 | 37.1.  With fewer KV heads a query tile's pieces are on more XCDs, which the launch reads from more
-// slowly: 8 and 2 heads, 256 tokens as 64 rows in 8 19.4 | 16.0, 768 as 128 rows in 5 25.5 | 23.7, 1024 in 4 27.0 | 27.4; of 64 channels,
-// 256 in 8 13.9 | 12.3, 512 in 4 14.6 | 15.0, 1024 in 4 19.8 | 21.0.
-// Of several windows in a call the last workgroup merges, beside other items (a host-cache pass of 32K tokens in groups of four
-// windows of 512 took 3520 us so, 3696 with the launch); both do the same operations in the same order, written as fmaf, so windows in one call have the bits of single ones.
+// Whether a second launch merges the pieces of a query tile: in a single window, from four pieces on (five with fewer than four
+// KV heads); otherwise the workgroup that finishes last does.  That one reads the others' results back at 8 bytes a lane past
+// the L2s, 32 KB a piece (64 KB of 128 rows) and 8 KB per us, which nothing overlaps in a single window; the launch costs 4 us
+// whatever their number.  Of several windows in a call the last workgroup merges beside other items (a host-cache pass of 32K
+// tokens in groups of four windows of 512: 3520 us so, 3696 with the launch).  Both do the same operations in the same order,
+// written as fmaf, so windows in one call have the bits of single ones.
+// Single windows, last workgroup | launch, us:
+//   32 query and 8 KV heads of 128: 384 tokens, 5 pieces of 256 rows 30.2 | 24.8; 1024, 2 of 256 49.2 | 50.0; 256, 4 of 128 23.2 | 21.3;
+//   512, 2 of 128 29.1 | 29.6; 64, 8 of 64 17.7 | 13.9; 128, 4 of 64 17.4 | 16.0; 200, 2 of 64 19.7 | 20.1
+//   28 and 4 heads: 768 tokens, 3 pieces of 256 rows 36.9 | 37.1
+//   8 and 2 heads (a query tile's pieces are on more XCDs, which the launch reads from more slowly): 256 tokens, 8 pieces of 64
+//   rows 19.4 | 16.0; 768, 5 of 128 25.5 | 23.7; 1024, 4 of 128 27.0 | 27.4; of 64 channels 256, 8 13.9 | 12.3; 512, 4 14.6 | 15.0
 bool prefill_merge_after(const actqkv_shape& sh, int s_lo) {
   return s_lo >= (sh.n_kv_heads >= 4 ? 4 : 5);
 }
@@ -868,21 +871,26 @@ static PfSplits prefill_cut(const actqkv_shape& sh, int batch, int m, int cus, i
 
 // Several windows or sequences in a call, whose items differ in length with what each retrieves: the least of what the busiest
 // compute unit needs by these figures, in us, with half of k_cap retrieved; 32 windows of 512 tokens, 32 query and 8 KV heads of
-// 128 channels: 597 as 256 rows, 692 as 128, 1009 as 64.  With 64 channels a tile is half the work and with two-term probabilities half
-// as much again, in the same proportions: over windows of 32 to 4096 tokens and groups of 1, 4 and 7 heads, up to 32 in a call, the
-// choice took at most 8 % longer than the best of the three, as a rule 0 to 3 %.
-static PfSplits prefill_splits_many(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
+// 128 channels: 597 as 256 rows, 692 as 128, 1009 as 64.  With 64 channels a tile is half the work and with two-term
+// probabilities half as much again, in the same proportions: over windows of 32 to 4096 tokens and groups of 1, 4 and 7 heads, up
+// to 32 in a call, the choice took at most 8 % longer than the best of the three, as a rule 0 to 3 %.
+static double prefill_many_us(const actqkv_shape& sh, int batch, int m, int k_cap, int cus, const PfSplits& c) {
   constexpr double kTileUs[] = {3.7, 2.1, 1.5}, kMergeUs[] = {6., 3.5, 2.}, kMergePieceUs[] = {1.1, 0.7, 0.5};
   constexpr double kItemUs = 8.;
-  const bool two = prefill_two_terms(sh, m);
+  const int i = c.ks >> 1;
   const double longest = (sh.n_init + sh.n_local + m) / double(kBlock) + k_cap / 2.0, average = longest - m / double(2 * kBlock);
+  const double rounds = double(batch) * sh.n_kv_heads * c.slots / cus;
+  double us = std::max(std::ceil(longest / c.s_lo), rounds * average / c.s_lo) * kTileUs[i] + kItemUs * std::max(rounds, 1.);
+  if (c.slots > c.n_qtiles) us += kMergeUs[i] + kMergePieceUs[i] * c.s_lo;
+  return us;
+}
+static PfSplits prefill_splits_many(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
+  const bool two = prefill_two_terms(sh, m);
   PfSplits r{};
   double best = 0.;
   for (int i = 0; i < 3; ++i) {
     const PfSplits c = prefill_cut(sh, batch, m, cus, 1 << i, sh.head_dim == 64 || i > 0 || !two);    // kPfPieces
-    const double rounds = double(batch) * sh.n_kv_heads * c.slots / cus;
-    double us = std::max(std::ceil(longest / c.s_lo), rounds * average / c.s_lo) * kTileUs[i] + kItemUs * std::max(rounds, 1.);
-    if (c.slots > c.n_qtiles) us += kMergeUs[i] + kMergePieceUs[i] * c.s_lo;
+    const double us = prefill_many_us(sh, batch, m, k_cap, cus, c);
     if (i == 0 || us < best) {
       best = us;
       r = c;
@@ -897,6 +905,10 @@ static PfSplits prefill_splits_many(const actqkv_shape& sh, int batch, int m, in
 // One-term probabilities keep the cut above: they are rounded to bf16 against the running maximum of the wavefronts that share a
 // tile, so another cut rounds them elsewhere and gives outputs that differ by 1e-3 of themselves.  It costs time: 28 query
 // and 4 KV heads, 640 tokens, as 70 items of 64 rows for each of the 4, a few more than compute units, 37.8 us, as 35 of 128 rows 29.8.
+// Windows that come as groups in one call take the cut of a single one (actqkv_retrieval_attention_windows), so it must not
+// cost four of them time by the figures above.  64 channels, 32 query and 8 KV heads, 16 blocks, alone | four, the cut above
+// against the other one: 640 tokens 45.5 -> 29.8 | 122 -> 100 us (taken), 768 37.1 -> 34.2 | 106 -> 120 (not), 1200 63 -> 55 | 192 -> 204
+// (not); 8 query and 2 KV heads, 3000 tokens 55.6 -> 47.3 | 197 -> 145 (taken).
 PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int cus) {
   PfSplits r{1, 0, 1, 1, 1};
   if (!prefill_mfma_supported(sh, m)) return r;
@@ -925,11 +937,15 @@ PfSplits prefill_splits(const actqkv_shape& sh, int batch, int m, int k_cap, int
     return us;
   };
   r = many;
-  // Only with fewer wavefronts to a row: windows in one call take the cut of a single one, and there a tile's cost per row counts.
+  constexpr int kGroup = 4;
+  const double group_us = prefill_many_us(sh, kGroup, m, k_cap, cus, many);
+  // (only with fewer wavefronts to a row: in a group a tile's cost per row counts)
   for (int i = 0; 1 << i < many.ks; ++i) {
     const PfSplits c = prefill_cut(sh, 1, m, cus, 1 << i, sh.head_dim == 64 || i > 0);
     // a cut-off leaves a third of k_cap or less, without one there are as many: it has to be better for both
-    if (needs(c, 0.25 * k_cap) < needs(r, 0.25 * k_cap) && needs(c, k_cap) < needs(r, k_cap)) r = c;
+    if (prefill_many_us(sh, kGroup, m, k_cap, cus, c) <= group_us && needs(c, 0.25 * k_cap) < needs(r, 0.25 * k_cap) &&
+        needs(c, k_cap) < needs(r, k_cap))
+      r = c;
   }
   return r;
 }

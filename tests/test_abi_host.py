@@ -82,31 +82,50 @@ def test_workspace_serves_smaller_calls(lib):
                     assert B.workspace_bytes(cs, b2, m2, 1024, 32) <= big, (sh, batch, m, b2, m2)
 
 
+def _cut_us(cut, hk, batch, m, k_cap, cus):
+    """The figures by which the attention of several windows is cut up: microseconds of the busiest compute unit."""
+    rows, tiles, slots = cut[:3]
+    tile, merge, piece = {256: (3.7, 6.0, 1.1), 128: (2.1, 3.5, 0.7), 64: (1.5, 2.0, 0.5)}[rows]
+    longest, pieces, rounds = (128 + 512 + m) / 128 + k_cap / 2, slots // tiles, batch * hk * slots / cus
+    us = max(math.ceil(longest / pieces), rounds * (longest - m / 256) / pieces) * tile + 8 * max(rounds, 1.0)
+    return us + (merge + piece * pieces if slots > tiles else 0.0)
+
+
+def _best_cut(hq, hk, batch, m, k_cap, cus):
+    cuts = []
+    for ks in (1, 2, 4):
+        tiles = -(-m * (hq // hk) * ks // 256)
+        room = max(cus // (batch * hk), tiles)
+        pieces = min(room // tiles, 8)
+        cuts.append((256 // ks, tiles, pieces * tiles + (room - pieces * tiles if ks == 1 and pieces < 8 else 0)))
+    return min(cuts, key=lambda c: _cut_us(c, hk, batch, m, k_cap, cus))
+
+
 @pytest.mark.parametrize("hq,hk,cus", [(32, 8, 256), (28, 4, 256), (8, 2, 256), (32, 32, 256), (8, 8, 224), (28, 4, 224)])
 def test_cut_of_a_window_with_one_term_probabilities(lib, hq, hk, cus):
     """Windows of bf16 probabilities of one term: they are rounded against the maximum of the wavefronts that share a tile, so
-    the output's bits belong to the cut, and the cut is the least of the busiest compute unit's microseconds by one set of
-    figures, whether a window comes alone or not."""
+    the output's bits belong to the cut, and the cut is the least by one set of figures, whether a window comes alone or not."""
     cs = B.c_shape(LayerShape(hq, hk, 128, 128, 4, 128, 512, "bf16"))
     for batch in (1, 5):
         for k_cap in (6, 16, 32):
             for m in list(range(2, 1100, 37)) + [512, 513, 640, 678, 700, 1024, 2441, 2500]:
-                if 1 + 64 + 4 + (m + 127) // 128 + 2 > 96:
-                    continue                                  # two terms
-                longest = (128 + 512 + m) / 128 + k_cap / 2
-                options = []
-                for ks, tile, merge, piece in ((1, 3.7, 6.0, 1.1), (2, 2.1, 3.5, 0.7), (4, 1.5, 2.0, 0.5)):
-                    tiles = -(-m * (hq // hk) * ks // 256)
-                    room = max(cus // (batch * hk), tiles)
-                    pieces = min(room // tiles, 8)
-                    slots = pieces * tiles + (room - pieces * tiles if ks == 1 and pieces < 8 else 0)
-                    rounds = batch * hk * slots / cus
-                    us = max(math.ceil(longest / pieces), rounds * (longest - m / 256) / pieces) * tile + 8 * max(rounds, 1.0)
-                    options.append((us + (merge + piece * pieces if slots > tiles else 0.0), (256 // ks, tiles, slots)))
-                assert B.prefill_cut(cs, batch, m, k_cap, cus)[:3] == min(options)[1], (batch, k_cap, m)
+                assert B.prefill_cut(cs, batch, m, k_cap, cus)[:3] == _best_cut(hq, hk, batch, m, k_cap, cus), (batch, k_cap, m)
     for bad in (dict(batch=0), dict(m=1), dict(m=8193), dict(k_cap=65), dict(cus=257)):
         with pytest.raises(B.ActQKVError):
             B.prefill_cut(cs, **{**dict(batch=1, m=512, k_cap=8, cus=256), **bad})
+
+
+@pytest.mark.parametrize("hq,hk", [(32, 8), (8, 2), (32, 32)])
+def test_cut_of_a_window_with_64_channels(lib, hq, hk):
+    """Another cut for a single window is one by which four of them in a call, which take the same, are priced no higher."""
+    cs = B.c_shape(LayerShape(hq, hk, 64, 128, 4, 128, 512, "bf16"))
+    others = 0
+    for k_cap in (6, 16, 32):
+        for m in list(range(2, 4096, 61)) + [640, 768, 1200]:
+            cut, plain = B.prefill_cut(cs, 1, m, k_cap)[:3], _best_cut(hq, hk, 1, m, k_cap, 256)
+            others += cut != plain
+            assert cut == plain or _cut_us(cut, hk, 4, m, k_cap, 256) <= _cut_us(plain, hk, 4, m, k_cap, 256), (k_cap, m)
+    assert others > 0
 
 
 def test_build_probe_rejects(lib):
