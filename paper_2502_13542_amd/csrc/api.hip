@@ -505,10 +505,11 @@ int actqkv_window_step(const actqkv_shape* shape, int batch, int m, const void* 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const bool apart = nb_scored > nb_begin && probe_finish_apart(*shape, batch, m, update_stats);
   ACTQKV_TRY(launch_probe(*shape, batch, m, q_win, stats, update_stats, probe, probe_kv, probe_norm, weights, ws, st, !apart));
-  // The selection inside the attention launch: the scoring launch keeps a copy of the cut-off state for it behind what the call
-  // needs of the workspace (a workspace without those bytes: a launch of its own), because a workgroup writes the results while
-  // others still read, and they may be written where the state was read (budget_remaining always is, theta may be theta_rest_sum).  Four windows of 512 tokens at 64K with the
-  // selection as a launch of its own 244 us, inside 236; of 256 tokens with 64 channels 133, 128.
+  // The selection inside the attention launch (a workspace without room for the copy: a launch of its own).  A workgroup
+  // writes the results while others still read, and they may be written where the cut-off state was read (budget_remaining
+  // always is, theta may be theta_rest_sum): the scoring launch keeps a copy of it behind what the call needs of the workspace.
+  // Four windows of 512 tokens at 64K with the selection as a launch of its own 244 us, inside 236; of 256 tokens with 64
+  // channels 133, 128.
   float* copy = ws.spare(need, batch);
   if (apart && copy != nullptr && select_inside_supported(nb_scored - nb_begin, k_cap, flags)) {
     ACTQKV_TRY(launch_score_probe(*shape, probe, probe_kv, probe_norm, rep_keys, nb_scored, nb_begin, nb_end, scores,

@@ -298,7 +298,8 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
   for (int i = 0; i < kDb; ++i)
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc_o[i][j] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;                      // reference of the exponents (log2 units, the rows' maximum or close below), this lane's share of the sum
+  // reference of the exponents (log2 units, the row's maximum or close below), this lane's share of the sum
+  float m_run = -INFINITY, l_run = 0.f;
 
   const int kn = (n & 0x13) | ((n & 4) << 1) | ((n & 8) >> 1);   // the key of this lane's row in the first product
   for (int t = t_begin; t < t_end; ++t) {

@@ -335,11 +335,11 @@ __global__ __launch_bounds__(kRmThreads) void probe_rows_moments_kernel(const T*
 // (mean, M2) in LDS: with fewer than 32 windows several lanes share one (32 / n, rounded down to a power of two), lane
 // u of them the chunks u, u + share, ..., whose sums are added in lane order.  Then lane 0 merges the windows into the
 // running statistics in window order (the merge of Eq. (8), as in probe_stats_bias_kernel): one window after the other, so
-// its quotients of counts and the 1/var that follow from it are made by all lanes, before and after (with both in the
-// loop 11.6 us for 32 windows of 256 tokens with 512 channels in fp32, 5.8 so; 18.5 for 32 of 512 with 4096 beside the attention, 12.4 so).  The count is published by
-// the next kernel (every thread here reads the old one; `before` is what launches of this call have added to it).  At most
-// kChainTile windows a launch: 132 KB of LDS, and 8 KB for the lanes' sums.  (The tiles in one launch, as a loop: a window
-// of 4096 tokens with 512 channels 24.3 us instead of 23.7.)
+// its quotients of counts and the 1/var that follow from it are made by all lanes, before and after.  The count is published
+// by the next kernel (every thread here reads the old one; `before` is what launches of this call have added to it).  At most
+// kChainTile windows a launch: 132 KB of LDS, and 8 KB for the lanes' sums.
+// With both in the loop 11.6 us for 32 windows of 256 tokens with 512 channels in fp32, 5.8 so; 18.5 for 32 of 512 with 4096
+// beside the attention, 12.4 so.  The tiles in one launch, as a loop: a window of 4096 tokens with 512 channels 24.3 instead of 23.7.
 constexpr int kChainTile = 512;
 template <typename T>
 __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __restrict__ q_win,
@@ -437,9 +437,9 @@ __global__ __launch_bounds__(1024) void probe_chain_stats_kernel(const T* __rest
 // the 16-byte groups lane, lane + 64, ... of a row (NI of them: d <= 64 * NI * V channels), R rows at a time and the
 // next R in flight meanwhile (8 groups of each; with NI = 1 the chunk is R * NW rows and nothing follows).  For rows that are
 // not there the chunk's last one is requested once more (branches around the loads: 4 windows of 512 tokens with 4096 channels
-// 36.4 us instead of 35.3), and no weight is applied (0 times an infinite query is NaN).  NI is the least that holds a row: with room for 4096 channels whatever
-// the row (and half of the lanes of rows_moments idle, 8 rows at once), the four launches of 32 windows of 256 tokens with
-// 512 channels took 49 us, 26 so; of 4 windows of 512 tokens with 4096 channels 50, 36 (chunks of 32 rows).
+// 36.4 us instead of 35.3), and no weight is applied (0 times an infinite query is NaN).  NI is the least that holds a row:
+// with room for 4096 channels whatever the row (and half of the lanes of rows_moments idle, 8 rows at once), the four launches
+// of 32 windows of 256 tokens with 512 channels took 49 us, 26 so; of 4 windows of 512 tokens with 4096 channels 50, 36 (chunks of 32 rows).
 // LDS: mean and 1/var of the window (2 kRowLen floats), reused for the sum over the wavefronts.
 template <typename T, int NI, int NW, int R>
 __global__ __launch_bounds__(64 * NW) void probe_rows_bias_weigh_kernel(
