@@ -16,8 +16,8 @@
 // by side), a wavefront 32 of them.  A tile is 4096 / D keys, 16 KB of keys and 16 KB of values: every wavefront brings a
 // quarter of each into registers while the tile before is worked on, and cuts it into parts in LDS (48 KB, one tile) between
 // two barriers.  Two workgroups share a compute unit, so a SIMD has a second wavefront while the first is in its softmax
-// or at a barrier.  What bounds it: 96 matrix instructions per tile and wavefront, and about 530 vector ones that a wavefront
-// does not overlap with its own; of 32 windows of 256 tokens' 144 us the matrix pipe is busy 63.
+// or at a barrier.  What bounds it: 96 matrix instructions per tile and wavefront and six vector ones beside each, which a
+// wavefront hardly overlaps with its own matrix ones; the matrix pipe is busy in 64 % of the cycles (32 windows of 256 tokens).
 //
 // S^T = K Q^T leaves a lane with scores of ONE query (column lane % 32).  Bits 2 and 3 of a key's number within 16 change
 // places on the way into the first product, so that register i of lane half h holds key 16 (i / 8) + 8 h + i % 8 of a
