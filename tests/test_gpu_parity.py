@@ -720,7 +720,8 @@ def test_log_sum_exp_output(dtype, d, m, nw):
     (8, 2, 64, 1536, 1, 4, (256, 24, 128, 1)),    # 256 rows in 5 and 6, fp32 partial results
     (32, 8, 128, 33, 2, 3, (64, 3, 15, 0)),       # the last workgroup merges: two sequences in 5 pieces
     (28, 4, 128, 300, 1, 4, (128, 17, 51, 0)),    # 128 rows in 3
-    (8, 2, 64, 1700, 1, 4, (256, 27, 128, 0))])   # 256 rows in 4 and 5, fp32 partial results
+    (8, 2, 64, 1700, 1, 4, (128, 54, 108, 0)),    # 128 rows in 2
+    (8, 2, 64, 2200, 1, 4, (256, 35, 128, 0))])   # 256 rows in 3 and 4, fp32 partial results
 def test_pieces_merged(hq, hk, d, m, nw, n_sel, cut):
     """Query tiles whose key tiles are cut into pieces, merged by a launch or by the last workgroup: output and lse of rows at
     the edges of query tiles against the oracle, twice on one workspace with the same bits."""
