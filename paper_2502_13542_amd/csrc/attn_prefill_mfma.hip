@@ -903,8 +903,9 @@ static PfSplits prefill_splits_many(const actqkv_shape& sh, int batch, int m, in
 // tile (64 channels 0.75 of it, 128 1.28 times), an item's start and end, and merging.  Against 490 launches measured they are
 // 9 % off in the root mean square.
 // One-term probabilities keep the cut above: they are rounded to bf16 against the running maximum of the wavefronts that share a
-// tile, so another cut rounds them elsewhere and gives outputs that differ by 1e-3 of themselves.  It costs time: 28 query
-// and 4 KV heads, 640 tokens, as 70 items of 64 rows for each of the 4, a few more than compute units, 37.8 us, as 35 of 128 rows 29.8.
+// tile, so another cut rounds them elsewhere and gives outputs that differ by 1e-3 of themselves (two terms have 16 bits: 1e-4 of
+// the output at most, where a value lies close to the middle between two).  It costs time: 28 query and 4 KV heads, 640
+// tokens, as 70 items of 64 rows for each of the 4, a few more than compute units, 37.8 us, as 35 of 128 rows 29.8.
 // Windows that come as groups in one call take the cut of a single one (actqkv_retrieval_attention_windows), so it must not
 // cost four of them time by the figures above.  64 channels, 32 query and 8 KV heads, 16 blocks, alone | four, the cut above
 // against the other one: 640 tokens 45.5 -> 29.8 | 122 -> 100 us (taken), 768 37.1 -> 34.2 | 106 -> 120 (not), 1200 63 -> 55 | 192 -> 204
