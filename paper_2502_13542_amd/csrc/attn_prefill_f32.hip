@@ -3,12 +3,12 @@
 //
 // The fp32 matrix instruction does 256 operations per clock and compute unit, a sixteenth of the 16-bit one.  So a value
 // enters as three bf16 parts, each what rounding to bf16 left of the one before: 8 + 8 + 8 bits are all of its 24, and
-// bf16 has the exponents of fp32, so the parts together ARE the value, whatever lies beside it (a query row enters times the
-// softmax scale, to 2^-26).  A product is six of the nine products of parts, exact each, summed in fp32, small ones first; the
-// three left out are below 2^-24 of it together, half a unit of its last place.  Two f16 halves and three products are
-// faster (32 windows of 256 tokens 102 us, 144 so), but hold 23 bits, and those only of values near the largest that shares
-// their factor: not taken.  Values above the largest bf16, infinite ones among them, have no parts: where a tile has one
-// its scores are taken again, or its large values added, in fp32 products.
+// bf16 has the exponents of fp32, so the parts together ARE the value, whatever lies beside it (from 2^-109 on, smaller
+// ones to 2^-134; a query row enters times the softmax scale, to 2^-26).  A product is six of the nine products of parts,
+// exact each, summed in fp32, small ones first; the three left out are below 2^-24 of it together, half a unit of its last
+// place.  Two f16 halves and three products are faster (32 windows of 256 tokens 102 us, 146 so), but hold 23 bits, and
+// those only of values near the largest that shares their factor: not taken.  Values above the largest bf16, infinite ones
+// among them, have no parts: where a tile has one its scores are taken again, or its large values added, in fp32 products.
 // Relative error against 64 bits, normal inputs, 64 channels: 32 windows of 256 tokens 6.4e-7 (fp32 products 7.6e-7), one
 // such window 3.3e-7 (4.2e-7), one of 4096 tokens 8.4e-7 (9.8e-7); 128 channels 6.8e-7 (8.1e-7), 4.0e-7 (4.9e-7), 1.18e-6 (1.37e-6).
 //
@@ -25,8 +25,8 @@
 //
 // A single window has few query tiles; then the key tiles are cut into pieces, one workgroup each, which a second launch
 // merges.  64 channels, 8 query and 2 KV heads, 8 blocks retrieved, against fp32 products with the merge in the last
-// workgroup: 32 windows of 256 tokens 218 -> 144 us, one of them 57 -> 22, of 4096 tokens 301 -> 178; 128 channels, 32
-// windows 427 -> 285.
+// workgroup: 32 windows of 256 tokens 218 -> 146 us, one of them 57 -> 22, of 4096 tokens 301 -> 179; 128 channels, 32
+// windows 427 -> 296.
 #include <algorithm>
 #include <mutex>
 
@@ -41,7 +41,6 @@ constexpr int kFfWaves = 4;
 constexpr int kFfRows = 32 * kFfWaves;            // query rows of a workgroup
 constexpr int kFfPart = 8192;                     // one of the three parts of K or V^T of a tile
 constexpr int kFfLdsBytes = 6 * kFfPart;
-constexpr int kFfLazy = 8;                        // see the running maximum
 constexpr float kFfMax = 3.3895314e38f;           // the largest bf16: what is larger has no parts
 // Workgroups of a full launch: two per compute unit; with 128 channels a little less, so that their
 // partial results fit the library's own scratch array.
@@ -298,7 +297,7 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
   for (int i = 0; i < kDb; ++i)
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc_o[i][j] = 0.f;
-  // reference of the exponents (log2 units, the row's maximum or close below), this lane's share of the sum
+  // the row's maximum (log2 units), this lane's share of the sum
   float m_run = -INFINITY, l_run = 0.f;
 
   const int kn = (n & 0x13) | ((n & 4) << 1) | ((n & 8) >> 1);   // the key of this lane's row in the first product
@@ -380,9 +379,9 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
 #pragma unroll
       for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc_s[gg][i]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    // the reference follows the maximum only when that has grown by more than 2^kFfLazy, as a rule in the first tiles
-    // (every lane takes the same branch: 32 rows have a new maximum in nearly every tile)
-    if (!__all(mx <= m_run + kFfLazy)) {
+    // (every lane takes the same branch.  A reference that lags behind by up to 2^8 is 1 to 3 % faster, but probabilities
+    // above 1 overflow sums over values near the largest fp32)
+    if (!__all(mx <= m_run)) {
       const float m_new = fmaxf(m_run, mx);
       const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
       m_run = m_new;

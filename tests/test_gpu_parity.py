@@ -449,13 +449,14 @@ def test_probabilities_keep_more_than_bf16(d, group, m, nw):
 
 @pytest.mark.parametrize("d,group,m,nw", [(64, 4, 65, 1), (64, 4, 256, 40), (64, 2, 2100, 1), (128, 4, 33, 3), (128, 1, 300, 30)])
 @pytest.mark.parametrize("what", ["small and large", "tokens of all sizes", "infinite", "near the limits", "channels of all sizes",
-                                  "little weight on large values", "one key"])
+                                  "little weight on large values", "one key",
+                                  "the largest values"])
 def test_fp32_prefill_attention_over_the_range_of_floats(d, group, m, nw, what):
     """The parts that the products are taken in together are the fp32 values.  Queries of 1e-12 with keys of 1e12 and values of 1e-20;
     tokens whose keys and values differ by up to 2^20; infinite and NaN elements, where the result is what fp32 products give; values of
     2^-120 and a key above the largest bf16; channels of V that differ by up to 2^12 behind a tile whose values are 2^7 times larger and
     have little weight; keys of weight 2^-16 whose values are 2^16 times the heaviest key's; and all weight on one key, whose value is
-    the output bit for bit.  Memory behind the last token holds 1e30.
+    the output bit for bit; a value of 3e38 on the heaviest key, behind one whose score is 4 lower.  Memory behind the last token holds 1e30.
     Bound: a score's D products and sums in fp32, (D + 16) 2^-24 sum_c |q_c k_c|, twice (numerator and
     denominator) on every term of sum_j p_j |v_j|, and 2^-18 of that for exponentials, sums over the keys and the merge."""
     sh = LayerShape(2 * group, 2, d, 128, 4, 128, 256, "fp32")
@@ -479,11 +480,11 @@ def test_fp32_prefill_attention_over_the_range_of_floats(d, group, m, nw, what):
         k[int(idx[0, 0]) * 128 + 5, 0, 3] = 3.4e38                        # above the largest bf16, seen by all rows of a window
         q[:, :group, 3] = 0.
         q[0, 0, 3] = 2. ** -126
-    elif what in ("channels of all sizes", "little weight on large values", "one key"):
+    elif what in ("channels of all sizes", "little weight on large values", "one key", "the largest values"):
         heaviest = 127                                                    # an initial token; scores of one product each
         q, k = torch.zeros_like(q), torch.zeros_like(k)
         q[..., 0] = d ** 0.5
-        k[heaviest, :, 0] = {"channels of all sizes": 12., "little weight on large values": 11., "one key": 88.}[what]
+        k[heaviest, :, 0] = {"little weight on large values": 11., "one key": 88.}.get(what, 12.)
         if what == "channels of all sizes":
             k[:32, :, 0] = -6.
             v *= 2. ** torch.randint(-12, 1, (1, 2, d), generator=g)
@@ -491,6 +492,10 @@ def test_fp32_prefill_attention_over_the_range_of_floats(d, group, m, nw, what):
         elif what == "little weight on large values":
             v *= 2. ** 16
             v[heaviest] *= 2. ** -16
+        elif what == "the largest values":
+            k[5, :, 0] = 8.
+            v *= 1e36
+            v[heaviest] = 3e38 * torch.sign(v[heaviest])
     if what == "infinite":
         q[0, 0, 3], q[1, 1, 5] = np.inf, np.nan                          # two rows of the first window
         for i, key in ((0, 7), (nw // 2, 40), (nw - 1, 100)):             # in blocks that all rows of a window see
