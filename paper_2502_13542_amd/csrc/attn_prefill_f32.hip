@@ -17,7 +17,7 @@
 // quarter of each into registers while the tile before is worked on, and cuts it into parts in LDS (48 KB, one tile) between
 // two barriers.  Two workgroups share a compute unit, so a SIMD has a second wavefront while the first is in its softmax
 // or at a barrier.  What bounds it: 96 matrix instructions per tile and wavefront and six vector ones beside each, which a
-// wavefront hardly overlaps with its own matrix ones; the matrix pipe is busy in 64 % of the cycles (32 windows of 256 tokens).
+// wavefront hardly overlaps with its own matrix ones; the matrix pipe is busy in 63 % of the cycles (32 windows of 256 tokens).
 //
 // S^T = K Q^T leaves a lane with scores of ONE query (column lane % 32).  Bits 2 and 3 of a key's number within 16 change
 // places on the way into the first product, so that register i of lane half h holds key 16 (i / 8) + 8 h + i % 8 of a
@@ -122,7 +122,8 @@ __global__ __launch_bounds__(kFfThreads, 2) void attn_prefill_f32_kernel(FfParam
   constexpr int kG = kKeys / 32, kDb = D / 32, kQ = D / 16;
   constexpr uint32_t kKRow = D * 2, kVRow = kKeys * 2;   // bytes of a K / V^T row in one of its parts in LDS
   extern __shared__ __attribute__((aligned(16))) char ff_lds[];   // three parts of K, three of V^T
-  __shared__ __attribute__((aligned(16))) uint32_t no_parts[2][kFfWaves];   // whether what a wavefront brought of K, V is larger than kFfMax
+  // whether a wavefront brought values above kFfMax: [K, V^T][wavefront]
+  __shared__ __attribute__((aligned(16))) uint32_t no_parts[2][kFfWaves];
   __shared__ int32_t idx_lds[64];
   __shared__ SelectWaveLds sel_lds;
   __shared__ int sel_count;
